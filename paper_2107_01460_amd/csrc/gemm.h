@@ -1,19 +1,17 @@
-// LDS-tiled fp32 MFMA GEMM for gfx950 (v_mfma_f32_32x32x2_f32), shared by the rollout forward
+// LDS-tiled fp32 GEMM for gfx950 on split bf16 operands (split_bf16.h), shared by the rollout forward
 // pass and the PPO backward pass.  Three operand arrangements:
 //   NN  C[m][n] = sum_k A[m][k] * B[k][n]     activations x weights
 //   NT  C[m][n] = sum_k A[m][k] * B[n][k]     gradient x weights^T
 //   TN  C[m][n] = sum_k A[k][m] * B[k][n]     activations^T x gradient (split over k across workgroups)
 // "A" is always given by rows (optionally gathered through an index list), so a minibatch is read
-// in place from the trajectory.  Tiles are staged in LDS in their source orientation; the operand
-// fetch indexes them so that the 32 lanes of a half-wavefront hit 32 different banks.
+// in place from the trajectory.
 #pragma once
 #include <algorithm>
 
 #include "common.h"
+#include "split_bf16.h"
 
 namespace marl {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // Division of a sample index by a small run-time divisor (agents per row) without the 64-bit division sequence,
 // which is about 180 vector instructions and sat on the critical path of every row tile: for s < 2^31 and
@@ -74,7 +72,7 @@ inline bool small_div_ok(const SmallDiv& v, int64_t count) { return v.magic != 0
 enum GemmMode { GEMM_NN = 0, GEMM_NT = 1, GEMM_TN = 2 };
 enum GemmEpi {
   EPI_BIAS_TANH = 0,  // C = tanh(acc + aux_vec[n])
-  EPI_DTANH = 1,      // C = acc * (1 - aux_mat[m][n]^2);  column sums of C are added to colsum[n]
+  EPI_DTANH = 1,      // C = acc * (1 - aux_mat[m][n]^2)
   EPI_ATOMIC_ADD = 2, // C += acc (fp32 atomics; split-k partial results)
   EPI_STORE = 3       // C = acc + aux_vec[n] (aux_vec nullable)
 };
@@ -88,14 +86,14 @@ struct GemmArgs {
   const float* aux_vec;  // EPI_BIAS_TANH: bias [N]; EPI_STORE: nullable bias [N]
   const float* aux_mat;  // EPI_DTANH: previous activation [M][ldaux]
   int64_t ldaux;
-  float* colsum;         // TN: column sums of B are added here ([N], atomic), nullable; EPI_DTANH: column sums of C
+  float* colsum;         // TN: column sums of B are added here ([N], atomic), nullable
   int64_t M, N, K;
   int64_t k_per_split;   // TN: k range of one blockIdx.z
   int round_bf16;        // round stored results to bf16 precision (kept in fp32 storage)
   // TN with EPI_ATOMIC_ADD, nullable: k split z stores its products at split_out + z * split_count + m * ldc + n and its
   // column sums of B behind them (at + M * ldc + n) with plain stores instead of adding to C / colsum with atomics; the
   // caller then adds the splits in a fixed order (reduce_partials_kernel), which makes the result the same in every run.
-  // Only the large-tile kernel honours it: launch_gemm says whether it did.
+  // launch_gemm says whether the launch did.
   float* split_out;
   int64_t split_count;
 };
@@ -255,36 +253,145 @@ __device__ __forceinline__ void gemm_phase_w(const float* __restrict__ As, int k
   }
 }
 
-constexpr int kGemmBK = 16;
+constexpr int kGemmBK = 32;  // k per stage: two steps of the matrix instruction
 
-template <int MODE, int EPI, int BM, int BN, int WGM, int WGN>
-__global__ void __launch_bounds__(64 * WGM * WGN) gemm_f32_kernel(GemmArgs g) {
-  constexpr int NT = 64 * WGM * WGN;
+// BM x BN tile, four wavefronts (2 x 2 at BM = 128, side by side at BM = 32), k tiles of 32 in one LDS buffer of split
+// operands; the next k tile travels global -> registers while the current one is multiplied, and two workgroups per CU
+// cover each other's staging and barriers.  A tile is kept in LDS in its source orientation: k-contiguous tiles are read
+// with 16-byte reads (pitch 40 elements: an odd number of 16-byte units), the others with the transposing read (the
+// pitches put four consecutive rows on different quarters of the banks).
+// Bound: per k tile and wavefront 48 matrix instructions at BN = 128 (1536 cycles) against about 700 cycles of vector
+// instructions that split 32 staged values per thread, which the other workgroup's matrix instructions cover; at
+// contraction lengths of 128 .. 256 the activations' HBM traffic is the other bound.  Measured against the kernel on the
+// fp32 instruction that this one replaced: dW of 256 x 256 over 262 144 samples 295 -> 210 us; a training iteration whose
+// networks run layer by layer (147-256-6 and 147-192-1, 250 000 samples) 27.1 -> 19.9 ms.
+template <int MODE, int EPI, int BM, int BN, bool AVEC>
+__global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   constexpr int BK = kGemmBK;
-  constexpr int TM = BM / WGM / 32, TN = BN / WGN / 32;
-  static_assert(TM >= 1 && TN >= 1, "wave tile");
-  // LDS tiles in source orientation
-  constexpr bool A_ROWS_ARE_M = (MODE != GEMM_TN);  // A strip: [BM][BK] (rows m) or [BK][BM] (rows k)
-  constexpr bool B_ROWS_ARE_K = (MODE != GEMM_NT);  // B strip: [BK][BN] (rows k) or [BN][BK] (rows n)
-  constexpr int A_ROWS = A_ROWS_ARE_M ? BM : BK, A_COLS = A_ROWS_ARE_M ? BK : BM;
-  constexpr int B_ROWS = B_ROWS_ARE_K ? BK : BN, B_COLS = B_ROWS_ARE_K ? BN : BK;
-  constexpr int A_LD = A_ROWS_ARE_M ? BK + 1 : BM;
-  constexpr int B_LD = B_ROWS_ARE_K ? BN : BK + 1;
-  constexpr int A_PER = A_ROWS * A_COLS / NT, B_PER = B_ROWS * B_COLS / NT;
-  static_assert(A_ROWS * A_COLS % NT == 0 && B_ROWS * B_COLS % NT == 0, "strip size");
-  static_assert(NT % A_COLS == 0 || A_COLS % NT == 0, "A strip mapping");
-  __shared__ float As[A_ROWS * A_LD];
-  __shared__ float Bs[B_ROWS * B_LD];
+  constexpr int WM = BM == 128 ? 2 : 1, WN = 4 / WM, TM = BM / (32 * WM), TN = BN / (32 * WN);
+  static_assert(TM >= 1 && TN >= 1 && (BM == 128 || BM == 32), "wavefront tiles");
+  constexpr bool A_KCONT = (MODE != GEMM_TN);  // A tile stored [m][k] else [k][m]
+  constexpr bool B_KCONT = (MODE == GEMM_NT);  // B tile stored [n][k] else [k][n]
+  constexpr int PK = BK + 8;
+  constexpr int PMA = BM == 32 ? 32 : BM + 32, PNB = BN + 32;  // rows 16 or 48 banks apart
+  constexpr int A_PLANE = A_KCONT ? BM * PK : BK * PMA, B_PLANE = B_KCONT ? BN * PK : BK * PNB;
+  constexpr int A_VECS = BK * BM / 4 / 256, B_VECS = BK * BN / 4 / 256;  // 16-byte pieces a thread stages
+  static_assert(A_VECS >= 1 && B_VECS >= 1, "every thread stages");
+  __shared__ __attribute__((aligned(16))) bf16_t As[3 * A_PLANE];
+  __shared__ __attribute__((aligned(16))) bf16_t Bs[3 * B_PLANE];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
+  const int wm = wave / WN, wn = wave % WN;
   const int lo = lane & 31, hi = lane >> 5;
-  const int64_t m0 = (int64_t)blockIdx.x * BM, n0 = (int64_t)blockIdx.y * BN;
+  // Tiles that share an operand are neighbours on one XCD and meet in its L2: the column tiles of a row tile (NN, NT:
+  // the activations, read once per column tile otherwise), the output tiles of a k slab (TN: with the plain order 1074 MB
+  // came from HBM per launch at 256 x 256 outputs where 537 are algorithmic).
+  const unsigned lg = xcd_remap(blockIdx.x, gridDim.x);
+  const unsigned nbn = (unsigned)((g.N + BN - 1) / BN), nbm = (unsigned)((g.M + BM - 1) / BM);
+  const unsigned by = lg % nbn, bx = MODE == GEMM_TN ? (lg / nbn) % nbm : lg / nbn, bz = MODE == GEMM_TN ? lg / (nbn * nbm) : 0;
+  const int64_t m0 = (int64_t)bx * BM, n0 = (int64_t)by * BN;
   int64_t k_begin = 0, k_end = g.K;
   if (MODE == GEMM_TN) {
-    k_begin = (int64_t)blockIdx.z * g.k_per_split;
+    k_begin = (int64_t)bz * g.k_per_split;
     k_end = min(g.K, k_begin + g.k_per_split);
+    if (k_begin >= k_end) return;  // uniform
   }
+
+  // ---- global -> registers.  Indices past the end are clamped to the last element: rows and columns past the end feed
+  // outputs that are never stored, and of the k past the end one operand is set to zero.
+  float4 ra[A_VECS], rb[B_VECS];
+  const float* arow[A_VECS];           // A_KCONT: this thread's rows
+  int q[A_VECS], rem[A_VECS];          // TN: gather index and agent of this thread's next row of A, advanced by BK per stage
+  int32_t entry[A_VECS];               // ... and its gather entry, fetched one stage ahead
+  const int per = g.A.per, dq = BK / per, dr = BK - dq * per;
+  const int q_last = (int)((uint32_t)(k_end - 1) / (uint32_t)per), rem_last = (int)(k_end - 1) - q_last * per;
+  if (A_KCONT) {
+#pragma unroll
+    for (int p = 0; p < A_VECS; ++p) arow[p] = g.A.ptr(min(m0 + ((tid + 256 * p) >> 3), g.M - 1));
+  } else {
+#pragma unroll
+    for (int p = 0; p < A_VECS; ++p) {
+      const uint32_t k = (uint32_t)k_begin + (tid + 256 * p) / (BM / 4);
+      q[p] = (int)(k / (uint32_t)per);
+      rem[p] = (int)(k - q[p] * per);
+    }
+  }
+  auto fetch_entries = [&]() {  // TN with gathered rows: entries of the stage that (q, rem) stands at
+    if (MODE == GEMM_TN && g.A.gather != nullptr) {
+#pragma unroll
+      for (int p = 0; p < A_VECS; ++p) entry[p] = g.A.gather[min(q[p], q_last)];
+    }
+  };
+  auto fetch = [&](int64_t k0) {
+    if (A_KCONT) {
+      const int64_t k = k0 + 4 * (tid & 7);
+#pragma unroll
+      for (int p = 0; p < A_VECS; ++p) {
+        if (AVEC) {
+          const float4 v = *reinterpret_cast<const float4*>(arow[p] + min(k, k_end - 4));
+          ra[p] = k < k_end ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+        } else {
+          float e[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float v = arow[p][min(k + j, k_end - 1)];
+            e[j] = k + j < k_end ? v : 0.f;
+          }
+          ra[p] = make_float4(e[0], e[1], e[2], e[3]);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int p = 0; p < A_VECS; ++p) {
+        const int64_t m = m0 + 4 * ((tid + 256 * p) % (BM / 4));
+        const bool past = q[p] > q_last || (q[p] == q_last && rem[p] > rem_last);
+        const int qc = past ? q_last : q[p], rc = past ? rem_last : rem[p];
+        const int64_t row = (g.A.gather != nullptr ? (int64_t)entry[p] : (int64_t)qc) * per + rc;
+        const float* src = g.A.base + row * g.A.ld;
+        if (AVEC) {
+          ra[p] = *reinterpret_cast<const float4*>(src + min(m, g.M - 4));
+        } else {
+          ra[p] = make_float4(src[min(m, g.M - 1)], src[min(m + 1, g.M - 1)], src[min(m + 2, g.M - 1)], src[min(m + 3, g.M - 1)]);
+        }
+        q[p] += dq;
+        rem[p] += dr;
+        if (rem[p] >= per) {
+          rem[p] -= per;
+          ++q[p];
+        }
+      }
+      fetch_entries();
+    }
+#pragma unroll
+    for (int p = 0; p < B_VECS; ++p) {
+      const int f = tid + 256 * p;
+      if (B_KCONT) {  // k past the end meets a zero of A
+        const int64_t k = k0 + 4 * (f & 7), n = n0 + (f >> 3);
+        rb[p] = *reinterpret_cast<const float4*>(g.B + min(n, g.N - 1) * g.ldb + min(k, k_end - 4));
+      } else {
+        const int64_t k = k0 + f / (BN / 4), n = n0 + 4 * (f % (BN / 4));
+        float4 v = *reinterpret_cast<const float4*>(g.B + min(k, k_end - 1) * g.ldb + min(n, g.N - 4));
+        if (MODE == GEMM_TN && k >= k_end) v = make_float4(0.f, 0.f, 0.f, 0.f);
+        rb[p] = v;
+      }
+    }
+  };
+  auto stage = [&]() {
+#pragma unroll
+    for (int p = 0; p < A_VECS; ++p) {
+      const int f = tid + 256 * p;
+      store_split4(A_KCONT ? &As[(f >> 3) * PK + 4 * (f & 7)] : &As[(f / (BM / 4)) * PMA + 4 * (f % (BM / 4))], A_PLANE, ra[p]);
+    }
+#pragma unroll
+    for (int p = 0; p < B_VECS; ++p) {
+      const int f = tid + 256 * p;
+      store_split4(B_KCONT ? &Bs[(f >> 3) * PK + 4 * (f & 7)] : &Bs[(f / (BN / 4)) * PNB + 4 * (f % (BN / 4))], B_PLANE, rb[p]);
+    }
+  };
+
+  // TN: column sums of B (the bias gradient) ride along: each thread adds up the values it stages
+  float4 bsum = make_float4(0.f, 0.f, 0.f, 0.f);
+  const bool want_bsum = MODE == GEMM_TN && g.colsum != nullptr && bx == 0;
 
   floatx16 acc[TM][TN];
 #pragma unroll
@@ -294,421 +401,95 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_f32_kernel(GemmArgs g) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  float ra[A_PER], rb[B_PER];
-  // When A's strip rows are m, the row pointers do not change along k: look them up once.
-  const float* arow[A_PER];
-  if (A_ROWS_ARE_M) {
-#pragma unroll
-    for (int j = 0; j < A_PER; ++j) arow[j] = g.A.ptr(m0 + (tid + j * NT) / A_COLS);
-  }
+  const bf16_t* const a_frag = A_KCONT ? As + (wm * (BM / WM) + lo) * PK + 8 * hi : As + wm * (BM / WM) + frag_col_offset(lane, PMA);
+  const bf16_t* const b_frag = B_KCONT ? Bs + (wn * (BN / WN) + lo) * PK + 8 * hi : Bs + wn * (BN / WN) + frag_col_offset(lane, PNB);
 
-  auto fetch = [&](int64_t k0) {
-#pragma unroll
-    for (int j = 0; j < A_PER; ++j) {
-      const int e = tid + j * NT, r = e / A_COLS, c = e % A_COLS;
-      float v = 0.f;
-      if (A_ROWS_ARE_M) {
-        const int64_t k = k0 + c;
-        if (arow[j] != nullptr && k < k_end) v = arow[j][k];
-      } else {
-        const int64_t k = k0 + r, m = m0 + c;
-        if (k < k_end && m < g.M) {
-          const float* p = g.A.ptr(k);
-          v = p[m];
-        }
-      }
-      ra[j] = v;
-    }
-#pragma unroll
-    for (int j = 0; j < B_PER; ++j) {
-      const int e = tid + j * NT, r = e / B_COLS, c = e % B_COLS;
-      float v = 0.f;
-      if (B_ROWS_ARE_K) {
-        const int64_t k = k0 + r, n = n0 + c;
-        if (k < k_end && n < g.N) v = g.B[k * g.ldb + n];
-      } else {
-        const int64_t n = n0 + r, k = k0 + c;
-        if (k < k_end && n < g.N) v = g.B[n * g.ldb + k];
-      }
-      rb[j] = v;
-    }
-  };
-
-  // TN: column sums of B (the bias gradient).  B_COLS divides NT here, so a thread always stages the same column.
-  float bsum = 0.f;
-  const bool want_bsum = MODE == GEMM_TN && g.colsum != nullptr && blockIdx.x == 0;
-
-  if (k_begin < k_end) fetch(k_begin);
+  fetch_entries();
+  fetch(k_begin);
   for (int64_t k0 = k_begin; k0 < k_end; k0 += BK) {
+    stage();
+    if (MODE == GEMM_TN && want_bsum) {
 #pragma unroll
-    for (int j = 0; j < A_PER; ++j) {
-      const int e = tid + j * NT;
-      As[(e / A_COLS) * A_LD + (e % A_COLS)] = ra[j];
-    }
-#pragma unroll
-    for (int j = 0; j < B_PER; ++j) {
-      const int e = tid + j * NT;
-      Bs[(e / B_COLS) * B_LD + (e % B_COLS)] = rb[j];
-      if (MODE == GEMM_TN && want_bsum) bsum += rb[j];
+      for (int p = 0; p < B_VECS; ++p) {
+        bsum.x += rb[p].x; bsum.y += rb[p].y; bsum.z += rb[p].z; bsum.w += rb[p].w;
+      }
     }
     __syncthreads();
     if (k0 + BK < k_end) fetch(k0 + BK);
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      const int k = kk + hi;
-      float a[TM], b[TN];
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      Split8 a[TM], b[TN];
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int m = wm * (BM / WGM) + i * 32 + lo;
-        a[i] = A_ROWS_ARE_M ? As[m * A_LD + k] : As[k * A_LD + m];
-      }
+      for (int i = 0; i < TM; ++i)
+        a[i] = A_KCONT ? frag_row(a_frag + 32 * i * PK + 16 * ks, A_PLANE) : frag_col(a_frag + 32 * i + 16 * ks * PMA, PMA, A_PLANE);
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const int n = wn * (BN / WGN) + j * 32 + lo;
-        b[j] = B_ROWS_ARE_K ? Bs[k * B_LD + n] : Bs[n * B_LD + k];
-      }
+      for (int j = 0; j < TN; ++j)
+        b[j] = B_KCONT ? frag_row(b_frag + 32 * j * PK + 16 * ks, B_PLANE) : frag_col(b_frag + 32 * j + 16 * ks * PNB, PNB, B_PLANE);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_split(a[i], b[j], acc[i][j]);
     }
     __syncthreads();
   }
 
   if (MODE == GEMM_TN && want_bsum) {
-    static_assert(MODE != GEMM_TN || NT % B_COLS == 0, "a thread must stage one column");
-    const int64_t n = n0 + tid % B_COLS;
-    if (n < g.N) atomicAdd(&g.colsum[n], bsum);
+    // threads with equal tid % (BN/4) hold partial sums of the same four columns: combine them through LDS
+    float4* red = reinterpret_cast<float4*>(Bs);  // the tile is no longer needed (the loop ended with a barrier)
+    static_assert(B_PLANE * 3 * 2 >= 256 * 16, "room for the partial column sums");
+    red[tid] = bsum;
+    __syncthreads();
+    constexpr int GROUPS = 256 / (BN / 4);
+    if (tid < BN / 4 && n0 + 4 * tid < g.N) {
+      float4 t = red[tid];
+#pragma unroll
+      for (int u = 1; u < GROUPS; ++u) {
+        const float4 o = red[tid + u * (BN / 4)];
+        t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+      }
+      if (g.split_out != nullptr) {  // this k split's column sums, directly behind its copy of C
+        *reinterpret_cast<float4*>(g.split_out + (int64_t)bz * g.split_count + g.M * g.ldc + n0 + 4 * tid) = t;
+      } else {
+        float* dst = g.colsum + n0 + 4 * tid;
+        atomicAdd(dst + 0, t.x); atomicAdd(dst + 1, t.y); atomicAdd(dst + 2, t.z); atomicAdd(dst + 3, t.w);
+      }
+    }
   }
 
-  // Epilogue.  Accumulator register r of a lane holds C[8*(r/4) + 4*hi + r%4][lo] of its 32x32 tile.
+  // Epilogue (accumulator register r of a lane holds C[8*(r/4) + 4*hi + r%4][lo] of its 32x32 tile).
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int64_t n = n0 + wn * (BN / WGN) + j * 32 + lo;
-    const bool n_ok = n < g.N;
-    float csum = 0.f;
+  for (int jn = 0; jn < TN; ++jn) {
+    const int64_t n = n0 + wn * (BN / WN) + jn * 32 + lo;
+    if (n0 + wn * (BN / WN) + jn * 32 >= g.N) continue;  // uniform per wavefront: N is a multiple of 32
     float bias = 0.f;
-    if (EPI == EPI_BIAS_TANH && n_ok) bias = g.aux_vec[n];
-    if (EPI == EPI_STORE && n_ok && g.aux_vec != nullptr) bias = g.aux_vec[n];
+    if (EPI == EPI_BIAS_TANH) bias = g.aux_vec[n];
+    if (EPI == EPI_STORE && g.aux_vec != nullptr) bias = g.aux_vec[n];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
+      const int64_t mb = m0 + wm * (BM / WM) + i * 32 + 4 * hi;
+      float h[16];  // EPI_DTANH: all of the tile's operands requested before the first is used (C may alias them)
+      if (EPI == EPI_DTANH) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) h[r] = g.aux_mat[min(mb + 8 * (r / 4) + (r % 4), g.M - 1) * g.ldaux + n];
+      }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int64_t m = m0 + wm * (BM / WGM) + i * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        if (m < g.M && n_ok) {
-          float v = acc[i][j][r];
-          if (EPI == EPI_BIAS_TANH) {
-            v = tanh_f32(v + bias);
-            if (g.round_bf16) v = round_to_bf16(v);
-            g.C[m * g.ldc + n] = v;
-          } else if (EPI == EPI_DTANH) {
-            const float h = g.aux_mat[m * g.ldaux + n];
-            v = v * (1.0f - h * h);
-            if (g.round_bf16) v = round_to_bf16(v);
-            g.C[m * g.ldc + n] = v;
-            csum += v;
-          } else if (EPI == EPI_STORE) {
-            g.C[m * g.ldc + n] = v + bias;
-          } else {
-            atomicAdd(&g.C[m * g.ldc + n], v);
-          }
+        const int64_t m = mb + 8 * (r / 4) + (r % 4);
+        float v = acc[i][jn][r];
+        if (EPI == EPI_BIAS_TANH) {
+          v = tanh_f32(v + bias);
+          if (g.round_bf16) v = round_to_bf16(v);
+        } else if (EPI == EPI_DTANH) {
+          v = v * (1.0f - h[r] * h[r]);
+          if (g.round_bf16) v = round_to_bf16(v);
+        } else if (EPI == EPI_STORE) {
+          v += bias;
         }
-      }
-    }
-    if (EPI == EPI_DTANH && g.colsum != nullptr) {
-      csum += __shfl_xor(csum, 32);
-      if (hi == 0 && n_ok) atomicAdd(&g.colsum[n], csum);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
-// Second-generation kernel for the large shapes: 128 x BN tile (BN = 64 or 128), k-tile 32, four
-// wavefronts as 2 x 2, 16-byte global loads and LDS stores where the source rows are 16-byte
-// aligned (AVEC), operands fetched from LDS with one 16-byte read per four k-steps on k-contiguous
-// tiles.  Within a group of eight k values the lower half-wavefront supplies k = 0..3 and the
-// upper half k = 4..7 of both operands, so that each lane's four values are one aligned LDS read.
-// One LDS buffer; the next k-tile travels global -> registers while the current one is multiplied.
-// ---------------------------------------------------------------------------------------------
-constexpr int kG2BK = 32;
-constexpr int kG2PitchK = kG2BK + 4;  // k-contiguous tiles: pitch 36 floats keeps 16-byte alignment and spreads banks
-
-template <int MODE, int EPI, int BN, bool AVEC>
-__global__ void __launch_bounds__(256, 2) gemm2_f32_kernel(GemmArgs g) {
-  constexpr int BM = 128, BK = kG2BK, PK = kG2PitchK;
-  constexpr int TM = 2, TN = BN / 64;
-  constexpr bool A_KCONT = (MODE != GEMM_TN);  // A tile stored [m][k] (pitch PK) else [k][m] (pitch BM)
-  constexpr bool B_KCONT = (MODE == GEMM_NT);  // B tile stored [n][k] (pitch PK) else [k][n] (pitch BN)
-  constexpr int A_FLOATS = A_KCONT ? BM * PK : BK * BM;
-  constexpr int B_FLOATS = B_KCONT ? BN * PK : BK * BN;
-  __shared__ __attribute__((aligned(16))) float As[A_FLOATS];
-  __shared__ __attribute__((aligned(16))) float Bs[B_FLOATS];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int lo = lane & 31, hi = lane >> 5;
-  // TN: the tiles of one k slab are made neighbours on one XCD (workgroups are dealt round-robin to the eight XCDs in
-  // the order x, y, z), so that a slab of A / B is fetched from HBM once and found in that XCD's L2 by the other tiles
-  // that contract over it; with the plain (x, y, z) order every tile of a slab ran on another XCD and the operands
-  // were read twice (1074 MB per launch at 256 x 256 outputs where 537 are algorithmic).
-  unsigned bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
-  if (MODE == GEMM_TN) {
-    const unsigned lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    const unsigned lg = xcd_remap(lin, gridDim.x * gridDim.y * gridDim.z);
-    bx = lg % gridDim.x;
-    by = (lg / gridDim.x) % gridDim.y;
-    bz = lg / (gridDim.x * gridDim.y);
-  }
-  const int64_t n0 = (int64_t)by * BN;
-  // NN / NT: the workgroup is persistent over row tiles (tile, tile + gridDim.x, ...) and the first k-tile of
-  // the next row tile is already in flight while the current one finishes, so that neither the first load
-  // latency nor the epilogue of a row tile leaves the memory pipe idle.  TN: one output tile, k split over z.
-  const int64_t num_mt = (g.M + BM - 1) / BM;
-  int64_t k_begin = 0, k_end = g.K;
-  if (MODE == GEMM_TN) {
-    k_begin = (int64_t)bz * g.k_per_split;
-    k_end = min(g.K, k_begin + g.k_per_split);
-  }
-
-  floatx16 acc[TM][TN];
-
-  // ---- global -> register staging
-  // A, k-contiguous (NN/NT): vector: thread -> (row = tid/8 + 32p, 4 floats at k = 4*(tid%8)), p < 4
-  //                          scalar: thread -> (row = tid/32 + 8p, k = tid%32), p < 16
-  // A, m-contiguous (TN):    vector: thread -> (k = tid/32 + 8p, 4 floats at m = 4*(tid%32)), p < 4
-  //                          scalar: thread -> (k = tid/128 + 2p, m = tid%128), p < 16
-  constexpr int A_REGS = 16;
-  float ra[A_REGS];
-  const float* arow[AVEC ? 4 : 16];
-  int64_t m0_fetch = (int64_t)bx * BM;  // row tile the staging registers belong to
-  auto set_rows = [&](int64_t m0) {
-    m0_fetch = m0;
-    if (A_KCONT) {
-#pragma unroll
-      for (int p = 0; p < (AVEC ? 4 : 16); ++p) {
-        int64_t row = m0 + (AVEC ? (tid >> 3) + 32 * p : (tid >> 5) + 8 * p);
-        row = min(row, g.M - 1);  // rows past the end re-read the last row; their results are never stored
-        arow[p] = g.A.ptr(row);
-      }
-    }
-  };
-  // B, n-contiguous (NN/TN): thread -> (k = tid/(BN/4) + (1024/BN) p, 4 floats at n = 4*(tid % (BN/4)))
-  // B, k-contiguous (NT):    thread -> (n = tid/8 + 32p, 4 floats at k = 4*(tid%8)), p < BN/32
-  constexpr int B_VECS = BK * BN / 4 / 256;
-  float4 rb[B_VECS];
-
-  auto fetch = [&](int64_t k0) {
-    if (A_KCONT) {
-      if (AVEC) {
-        const int64_t k = k0 + 4 * (tid & 7);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (k < k_end) v = *reinterpret_cast<const float4*>(arow[p] + k);
-          ra[4 * p + 0] = v.x; ra[4 * p + 1] = v.y; ra[4 * p + 2] = v.z; ra[4 * p + 3] = v.w;
+        if (m < g.M) {
+          if (EPI != EPI_ATOMIC_ADD) g.C[m * g.ldc + n] = v;
+          else if (g.split_out != nullptr) g.split_out[(int64_t)bz * g.split_count + m * g.ldc + n] = v;
+          else atomicAdd(&g.C[m * g.ldc + n], v);
         }
-      } else {
-        const int64_t k = k0 + (tid & 31);
-#pragma unroll
-        for (int p = 0; p < 16; ++p) ra[p] = k < k_end ? arow[p][k] : 0.f;
-      }
-    } else {
-      if (AVEC) {
-        const int64_t m = m0_fetch + 4 * (tid & 31);
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          const int64_t k = k0 + (tid >> 5) + 8 * p;
-          float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (k < k_end && m < g.M) v = *reinterpret_cast<const float4*>(g.A.ptr(k) + m);
-          ra[4 * p + 0] = v.x; ra[4 * p + 1] = v.y; ra[4 * p + 2] = v.z; ra[4 * p + 3] = v.w;
-        }
-      } else {
-        const int64_t m = m0_fetch + (tid & 127);
-#pragma unroll
-        for (int p = 0; p < 16; ++p) {
-          const int64_t k = k0 + (tid >> 7) + 2 * p;
-          ra[p] = (k < k_end && m < g.M) ? g.A.ptr(k)[m] : 0.f;
-        }
-      }
-    }
-    if (B_KCONT) {
-      const int64_t k = k0 + 4 * (tid & 7);
-#pragma unroll
-      for (int p = 0; p < B_VECS; ++p) {
-        const int64_t n = n0 + (tid >> 3) + 32 * p;
-        rb[p] = k < k_end ? *reinterpret_cast<const float4*>(g.B + n * g.ldb + k) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    } else {
-      const int64_t n = n0 + 4 * (tid % (BN / 4));
-#pragma unroll
-      for (int p = 0; p < B_VECS; ++p) {
-        const int64_t k = k0 + tid / (BN / 4) + (1024 / BN) * p;
-        rb[p] = k < k_end ? *reinterpret_cast<const float4*>(g.B + k * g.ldb + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-    }
-  };
-
-  auto stage = [&]() {
-    if (A_KCONT) {
-      if (AVEC) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-          *reinterpret_cast<float4*>(&As[((tid >> 3) + 32 * p) * PK + 4 * (tid & 7)]) =
-              make_float4(ra[4 * p], ra[4 * p + 1], ra[4 * p + 2], ra[4 * p + 3]);
-      } else {
-#pragma unroll
-        for (int p = 0; p < 16; ++p) As[((tid >> 5) + 8 * p) * PK + (tid & 31)] = ra[p];
-      }
-    } else {
-      if (AVEC) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-          *reinterpret_cast<float4*>(&As[((tid >> 5) + 8 * p) * BM + 4 * (tid & 31)]) =
-              make_float4(ra[4 * p], ra[4 * p + 1], ra[4 * p + 2], ra[4 * p + 3]);
-      } else {
-#pragma unroll
-        for (int p = 0; p < 16; ++p) As[((tid >> 7) + 2 * p) * BM + (tid & 127)] = ra[p];
-      }
-    }
-    if (B_KCONT) {
-#pragma unroll
-      for (int p = 0; p < B_VECS; ++p) *reinterpret_cast<float4*>(&Bs[((tid >> 3) + 32 * p) * PK + 4 * (tid & 7)]) = rb[p];
-    } else {
-#pragma unroll
-      for (int p = 0; p < B_VECS; ++p)
-        *reinterpret_cast<float4*>(&Bs[(tid / (BN / 4) + (1024 / BN) * p) * BN + 4 * (tid % (BN / 4))]) = rb[p];
-    }
-  };
-
-  // TN: column sums of B (the bias gradient) ride along: each thread adds up the values it stages
-  float4 bsum = make_float4(0.f, 0.f, 0.f, 0.f);
-  const bool want_bsum = MODE == GEMM_TN && g.colsum != nullptr && bx == 0;
-
-  int64_t tile = bx;
-  if (tile < num_mt && k_begin < k_end) {
-    set_rows(tile * BM);
-    fetch(k_begin);
-  }
-  for (; tile < num_mt; tile += (MODE == GEMM_TN ? num_mt : (int64_t)gridDim.x)) {
-    const int64_t m0 = tile * BM;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    for (int64_t k0 = k_begin; k0 < k_end; k0 += BK) {
-      stage();
-      if (MODE == GEMM_TN && want_bsum) {
-#pragma unroll
-        for (int p = 0; p < B_VECS; ++p) {
-          bsum.x += rb[p].x; bsum.y += rb[p].y; bsum.z += rb[p].z; bsum.w += rb[p].w;
-        }
-      }
-      __syncthreads();
-      if (k0 + BK < k_end) {
-        fetch(k0 + BK);
-      } else if (MODE != GEMM_TN && tile + (int64_t)gridDim.x < num_mt) {
-        set_rows((tile + (int64_t)gridDim.x) * BM);
-        fetch(k_begin);
-      }
-#pragma unroll
-      for (int kb = 0; kb < BK; kb += 8) {
-        // lane (lo, hi) supplies k = kb + 4*hi + j in MFMA step j
-        float a[TM][4], b[TN][4];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int m = wm * 64 + i * 32 + lo;
-          if (A_KCONT) {
-            const float4 v = *reinterpret_cast<const float4*>(&As[m * PK + kb + 4 * hi]);
-            a[i][0] = v.x; a[i][1] = v.y; a[i][2] = v.z; a[i][3] = v.w;
-          } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) a[i][j] = As[(kb + 4 * hi + j) * BM + m];
-          }
-        }
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn) {
-          const int n = wn * (BN / 2) + jn * 32 + lo;
-          if (B_KCONT) {
-            const float4 v = *reinterpret_cast<const float4*>(&Bs[n * PK + kb + 4 * hi]);
-            b[jn][0] = v.x; b[jn][1] = v.y; b[jn][2] = v.z; b[jn][3] = v.w;
-          } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[jn][j] = Bs[(kb + 4 * hi + j) * BN + n];
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int jn = 0; jn < TN; ++jn)
-              acc[i][jn] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][j], b[jn][j], acc[i][jn], 0, 0, 0);
-      }
-      __syncthreads();
-    }
-
-    if (MODE == GEMM_TN && want_bsum) {
-      // threads with equal tid % (BN/4) hold partial sums of the same four columns: combine them through LDS
-      float4* red = reinterpret_cast<float4*>(Bs);  // the tile is no longer needed (the loop ended with a barrier)
-      red[tid] = bsum;
-      __syncthreads();
-      constexpr int GROUPS = 256 / (BN / 4);
-      if (tid < BN / 4) {
-        float4 t = red[tid];
-#pragma unroll
-        for (int q = 1; q < GROUPS; ++q) {
-          const float4 o = red[tid + q * (BN / 4)];
-          t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
-        }
-        if (g.split_out != nullptr) {  // this k split's column sums, directly behind its copy of C
-          *reinterpret_cast<float4*>(g.split_out + (int64_t)bz * g.split_count + g.M * g.ldc + n0 + 4 * tid) = t;
-        } else {
-          float* dst = g.colsum + n0 + 4 * tid;
-          atomicAdd(dst + 0, t.x); atomicAdd(dst + 1, t.y); atomicAdd(dst + 2, t.z); atomicAdd(dst + 3, t.w);
-        }
-      }
-    }
-
-    // Epilogue (accumulator register r of a lane holds C[8*(r/4) + 4*hi + r%4][lo] of its 32x32 tile).
-#pragma unroll
-    for (int jn = 0; jn < TN; ++jn) {
-      const int64_t n = n0 + wn * (BN / 2) + jn * 32 + lo;
-      float csum = 0.f, bias = 0.f;
-      if (EPI == EPI_BIAS_TANH) bias = g.aux_vec[n];
-      if (EPI == EPI_STORE && g.aux_vec != nullptr) bias = g.aux_vec[n];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t m = m0 + wm * 64 + i * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-          if (m < g.M) {
-            float v = acc[i][jn][r];
-            if (EPI == EPI_BIAS_TANH) {
-              v = tanh_f32(v + bias);
-              if (g.round_bf16) v = round_to_bf16(v);
-              g.C[m * g.ldc + n] = v;
-            } else if (EPI == EPI_DTANH) {
-              const float h = g.aux_mat[m * g.ldaux + n];
-              v = v * (1.0f - h * h);
-              if (g.round_bf16) v = round_to_bf16(v);
-              g.C[m * g.ldc + n] = v;
-              csum += v;
-            } else if (EPI == EPI_STORE) {
-              g.C[m * g.ldc + n] = v + bias;
-            } else if (g.split_out != nullptr) {
-              g.split_out[(int64_t)bz * g.split_count + m * g.ldc + n] = v;
-            } else {
-              atomicAdd(&g.C[m * g.ldc + n], v);
-            }
-          }
-        }
-      }
-      if (EPI == EPI_DTANH && g.colsum != nullptr) {
-        csum += __shfl_xor(csum, 32);
-        if (hi == 0) atomicAdd(&g.colsum[n], csum);
       }
     }
   }
@@ -716,48 +497,34 @@ __global__ void __launch_bounds__(256, 2) gemm2_f32_kernel(GemmArgs g) {
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Host-side dispatch over the tile shapes used by the library.
+// Host-side dispatch.  Every caller's N is a hidden width or three of them (a multiple of 32), its B 16-byte aligned with
+// a row pitch that keeps it so; A may start and step at any 4-byte boundary.
 // Returns true when the launch wrote its k splits to g.split_out (false: it added to C / colsum directly).
+template <int MODE, int EPI, int BM, int BN>
+inline void launch_gemm_inst(const GemmArgs& g, bool avec, hipStream_t s) {
+  unsigned blocks = (unsigned)(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN));
+  if (MODE == GEMM_TN) blocks *= (unsigned)((g.K + g.k_per_split - 1) / g.k_per_split);
+  if (avec) hipLaunchKernelGGL((gemm_split_kernel<MODE, EPI, BM, BN, true>), dim3(blocks), dim3(256), 0, s, g);
+  else hipLaunchKernelGGL((gemm_split_kernel<MODE, EPI, BM, BN, false>), dim3(blocks), dim3(256), 0, s, g);
+}
 template <int MODE, int EPI>
 inline bool launch_gemm(const GemmArgs& g_in, hipStream_t s) {
   GemmArgs g = g_in;
   const int64_t M = g.M, N = g.N;
   TimedLaunch timed(MODE == GEMM_NN ? KC_GEMM_NN : (MODE == GEMM_NT ? KC_GEMM_NT : KC_GEMM_TN),
                     2.0 * (double)g.M * (double)g.N * (double)g.K, s);
-  unsigned gz = 1;
-  if (MODE == GEMM_TN) gz = (unsigned)((g.K + g.k_per_split - 1) / g.k_per_split);
-  // Large shapes: N a multiple of 64, weights 16-byte aligned with a row pitch that keeps them so.
-  const bool b_ok = aligned16(g.B) && g.ldb % 4 == 0 && N % 64 == 0 && (MODE != GEMM_NT || g.K % 4 == 0);
-  if (b_ok && !(MODE == GEMM_TN && M <= 32)) {
-    const bool avec = aligned16(g.A.base) && g.A.ld % 4 == 0 && (MODE == GEMM_TN ? M % 4 == 0 : g.K % 4 == 0);
-    const int bn = N % 128 == 0 ? 128 : 64;
-    unsigned gx = (unsigned)((M + 127) / 128);
-    // (The kernel can also run persistently over row tiles with a smaller grid; measured slower here: stores
-    // share the load counter on this target, so the next tile's staged loads wait for the epilogue's stores.)
-    dim3 grid(gx, (unsigned)(N / bn), gz);
-    if (!(MODE == GEMM_TN && EPI == EPI_ATOMIC_ADD && g.ldc == N && N % 4 == 0)) g.split_out = nullptr;
-    if (bn == 128) {
-      if (avec) hipLaunchKernelGGL((gemm2_f32_kernel<MODE, EPI, 128, true>), grid, dim3(256), 0, s, g);
-      else hipLaunchKernelGGL((gemm2_f32_kernel<MODE, EPI, 128, false>), grid, dim3(256), 0, s, g);
-    } else {
-      if (avec) hipLaunchKernelGGL((gemm2_f32_kernel<MODE, EPI, 64, true>), grid, dim3(256), 0, s, g);
-      else hipLaunchKernelGGL((gemm2_f32_kernel<MODE, EPI, 64, false>), grid, dim3(256), 0, s, g);
+  const bool avec = aligned16(g.A.base) && g.A.ld % 4 == 0 && (MODE == GEMM_TN ? M % 4 == 0 : g.K % 4 == 0);
+  if (!(MODE == GEMM_TN && EPI == EPI_ATOMIC_ADD && g.ldc == N && N % 4 == 0)) g.split_out = nullptr;
+  if constexpr (MODE == GEMM_TN) {
+    if (M <= 32) {  // first-layer gradient of narrow observations: a 128-row tile would be three quarters padding
+      launch_gemm_inst<MODE, EPI, 32, 128>(g, avec, s);
+      return g.split_out != nullptr;
     }
-    return g.split_out != nullptr;
   }
-  g.split_out = nullptr;
-  if (MODE == GEMM_TN && M <= 32) {
-    // very thin output (first-layer gradient of the small networks)
-    dim3 grid(1, (unsigned)((N + 63) / 64), gz);
-    hipLaunchKernelGGL((gemm_f32_kernel<MODE, EPI, 32, 64, 1, 2>), grid, dim3(128), 0, s, g);
-  } else if (N % 128 == 0) {
-    dim3 grid((unsigned)((M + 127) / 128), (unsigned)(N / 128), gz);
-    hipLaunchKernelGGL((gemm_f32_kernel<MODE, EPI, 128, 128, 2, 2>), grid, dim3(256), 0, s, g);
-  } else {
-    dim3 grid((unsigned)((M + 127) / 128), (unsigned)((N + 63) / 64), gz);
-    hipLaunchKernelGGL((gemm_f32_kernel<MODE, EPI, 128, 64, 2, 2>), grid, dim3(256), 0, s, g);
-  }
-  return false;
+  // 64 columns where 128 would leave a half-empty last tile
+  if (N % 128 == 0) launch_gemm_inst<MODE, EPI, 128, 128>(g, avec, s);
+  else launch_gemm_inst<MODE, EPI, 128, 64>(g, avec, s);
+  return g.split_out != nullptr;
 }
 
 }  // namespace marl

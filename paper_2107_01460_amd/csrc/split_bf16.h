@@ -1,0 +1,93 @@
+// fp32 products on the bf16 matrix cores, at fp32 precision.
+//
+// An fp32 value is the exact sum of three bf16 values: h = bf16(x), m = bf16(x - h), l = x - h - m (round to nearest:
+// |m| <= 2^-9 |x|, |l| <= 2^-18 |x|, and the 24 significant bits of x are used up, so l is a bf16 value itself).  A product
+// of two such sums is nine bf16 products, each exact in fp32; the three smallest (m l, l m, l l) are together at most
+// 2^-26 of the product, a quarter of fp32's own rounding unit, and are left out.  The other six go to
+// v_mfma_f32_32x32x16_bf16, which accumulates in fp32.
+//
+// Rates measured on an MI355X: v_mfma_f32_32x32x2_f32 137 TFLOP/s, v_mfma_f32_32x32x16_bf16 2050 TFLOP/s, i.e. 342 TFLOP/s
+// of fp32 products.  Error against fp64 (tanh activations x normal weights, norm of the error over norm of the result,
+// 64 products of 32 x 32 outputs): contraction length 128: 1.63e-7 here, 2.02e-7 with the fp32 instruction; 304: 2.58e-7
+// and 3.12e-7; 1024: 4.86e-7 and 5.74e-7 -- the sixteen terms an instruction adds at once round less often.  With all nine
+// products the figures are the same in every digit shown.
+#pragma once
+#include "common.h"
+
+namespace marl {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef short shortx8 __attribute__((ext_vector_type(8)));
+
+// two values, each part packed as two bf16 (the first value in the low half)
+struct SplitPair {
+  uint32_t h, m, l;
+};
+__device__ __forceinline__ SplitPair split_pair(float x, float y) {
+  SplitPair s;
+  s.h = pack2_bf16(x, y);
+  x -= __uint_as_float(s.h << 16);
+  y -= __uint_as_float(s.h & 0xffff0000u);
+  s.m = pack2_bf16(x, y);
+  x -= __uint_as_float(s.m << 16);
+  y -= __uint_as_float(s.m & 0xffff0000u);
+  s.l = pack2_bf16(x, y);
+  return s;
+}
+
+// Eight values along the contraction of one row (A) or column (B): what a lane feeds to one matrix instruction -- of the
+// sixteen k of a step, lanes 0 .. 31 hold k = 0 .. 7, lanes 32 .. 63 hold k = 8 .. 15.
+struct Split8 {
+  bf16x8 h, m, l;
+};
+
+// acc += A B over sixteen k (the small products first)
+__device__ __forceinline__ floatx16 mfma_split(const Split8& a, const Split8& b, floatx16 acc) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc, 0, 0, 0);
+  return acc;
+}
+
+// ---- operands in LDS: three planes (h, m, l) of bf16, `plane` elements apart ------------------------------------------
+// Four consecutive values to the three planes with 8-byte stores.
+__device__ __forceinline__ void store_split4(bf16_t* dst, int plane, float4 v) {
+  const SplitPair a = split_pair(v.x, v.y), b = split_pair(v.z, v.w);
+  *reinterpret_cast<uint2*>(dst) = make_uint2(a.h, b.h);
+  *reinterpret_cast<uint2*>(dst + plane) = make_uint2(a.m, b.m);
+  *reinterpret_cast<uint2*>(dst + 2 * plane) = make_uint2(a.l, b.l);
+}
+// Fragment of a tile stored with the contraction contiguous: p points at this lane's row, k = 16 step + 8 (lane / 32).
+__device__ __forceinline__ Split8 frag_row(const bf16_t* p, int plane) {
+  Split8 f;
+  f.h = *reinterpret_cast<const bf16x8*>(p);
+  f.m = *reinterpret_cast<const bf16x8*>(p + plane);
+  f.l = *reinterpret_cast<const bf16x8*>(p + 2 * plane);
+  return f;
+}
+// Fragment of a tile stored with the contraction along the rows ([k][column]): the transposing LDS read gives each of the
+// sixteen lanes of a group one column of a 4 x 16 block whose rows the group's lanes address four elements at a time.
+// p points at frag_col_offset(lane, pitch) past the element (first k of the step, first of the 32 columns).
+__device__ __forceinline__ int frag_col_offset(int lane, int pitch) {
+  return (8 * (lane >> 5) + ((lane & 15) >> 2)) * pitch + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+}
+__device__ __forceinline__ bf16x8 read_col8(const bf16_t* p, int pitch) {
+  typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
+  const shortx4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)p);
+  const shortx4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4*)(p + 4 * pitch));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ Split8 frag_col(const bf16_t* p, int pitch, int plane) {
+  Split8 f;
+  f.h = read_col8(p, pitch);
+  f.m = read_col8(p + plane, pitch);
+  f.l = read_col8(p + 2 * plane, pitch);
+  return f;
+}
+
+}  // namespace marl
