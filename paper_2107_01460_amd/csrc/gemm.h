@@ -89,6 +89,7 @@ struct GemmArgs {
   float* colsum;         // TN: column sums of B are added here ([N], atomic), nullable
   int64_t M, N, K;
   int64_t k_per_split;   // TN: k range of one blockIdx.z
+  int c_rot;             // TN, multiple of 32 below N: column n of the product goes to column (n + c_rot) mod N of C and colsum
   int round_bf16;        // round stored results to bf16 precision (kept in fp32 storage)
   // TN with EPI_ATOMIC_ADD, nullable: k split z stores its products at split_out + z * split_count + m * ldc + n and its
   // column sums of B behind them (at + M * ldc + n) with plain stores instead of adding to C / colsum with atomics; the
@@ -441,6 +442,7 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
     __syncthreads();
     constexpr int GROUPS = 256 / (BN / 4);
     if (tid < BN / 4 && n0 + 4 * tid < g.N) {
+      const int64_t n = n0 + 4 * tid + g.c_rot, nd = n < g.N ? n : n - g.N;
       float4 t = red[tid];
 #pragma unroll
       for (int u = 1; u < GROUPS; ++u) {
@@ -448,9 +450,9 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
         t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
       }
       if (g.split_out != nullptr) {  // this k split's column sums, directly behind its copy of C
-        *reinterpret_cast<float4*>(g.split_out + (int64_t)bz * g.split_count + g.M * g.ldc + n0 + 4 * tid) = t;
+        *reinterpret_cast<float4*>(g.split_out + (int64_t)bz * g.split_count + g.M * g.ldc + nd) = t;
       } else {
-        float* dst = g.colsum + n0 + 4 * tid;
+        float* dst = g.colsum + nd;
         atomicAdd(dst + 0, t.x); atomicAdd(dst + 1, t.y); atomicAdd(dst + 2, t.z); atomicAdd(dst + 3, t.w);
       }
     }
@@ -461,6 +463,7 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   for (int jn = 0; jn < TN; ++jn) {
     const int64_t n = n0 + wn * (BN / WN) + jn * 32 + lo;
     if (n0 + wn * (BN / WN) + jn * 32 >= g.N) continue;  // uniform per wavefront: N is a multiple of 32
+    const int64_t nd = MODE == GEMM_TN && n + g.c_rot >= g.N ? n + g.c_rot - g.N : (MODE == GEMM_TN ? n + g.c_rot : n);
     float bias = 0.f;
     if (EPI == EPI_BIAS_TANH) bias = g.aux_vec[n];
     if (EPI == EPI_STORE && g.aux_vec != nullptr) bias = g.aux_vec[n];
@@ -487,8 +490,8 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
         }
         if (m < g.M) {
           if (EPI != EPI_ATOMIC_ADD) g.C[m * g.ldc + n] = v;
-          else if (g.split_out != nullptr) g.split_out[(int64_t)bz * g.split_count + m * g.ldc + n] = v;
-          else atomicAdd(&g.C[m * g.ldc + n], v);
+          else if (g.split_out != nullptr) g.split_out[(int64_t)bz * g.split_count + m * g.ldc + nd] = v;
+          else atomicAdd(&g.C[m * g.ldc + nd], v);
         }
       }
     }

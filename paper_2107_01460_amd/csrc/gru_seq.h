@@ -1,0 +1,379 @@
+// The GRU cell over a whole sequence in one launch each way: h' = (1 - z) n + z h for t = 0 .. T-1 and its gradient for
+// t = T-1 .. 0.  Sequences are independent of one another, so a workgroup keeps SM * 16 of them from the first step to the
+// last: the hidden state (forward) or its gradient (backward) never leaves the registers, the operand of the next
+// step's product is handed over through LDS, and nothing but the per-step records goes through memory.
+//
+// The product with the hidden-to-hidden weights runs transposed, weights x state, on v_mfma_f32_16x16x32_bf16 with split
+// operands (split_bf16.h): its result gives a lane four consecutive units of one sequence, so that every load and store of
+// a record is 16 bytes wide.  The weights come split and in the order a lane feeds them to the instruction
+// (gru_stage_weight below).
+//   H <= 128 (RES): H / 16 wavefronts of 16 units; all of the weights, 18 H^2 bytes, stay in the registers (144 of 256 per
+//     lane at H = 128).
+//   H <= 256: H / 32 wavefronts of 32 units; 18 H^2 bytes no longer fit a compute unit, so the weights are streamed from
+//     the L2 once per step, a contraction step or two ahead of their use.
+// Measured against one launch per step and direction on the fp32 instruction (128 steps of 768 sequences, 128 units):
+// forward 2.7 ms -> 0.25 ms, backward 3.6 ms -> 0.5 ms; a training iteration of 1024 environments 171 -> 51 ms.
+// Bound there: a step is a chain of 72 matrix instructions per wavefront, a barrier and the gate arithmetic, about 2 us.
+#pragma once
+#include "gemm.h"
+
+namespace marl {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+inline bool gru_seq_supported(int H) { return H % 32 == 0 && H <= 256; }
+inline int64_t gru_weight_floats(int H) { return (((int64_t)H * H * 9 / 2 + 63) / 64) * 64; }  // one staged copy
+
+// The element (k, c) of Wh [H][3H] in the two staged copies: three planes of bf16, in 512-element fragments of 16 units by
+// 32 along the contraction.
+__device__ __forceinline__ void gru_stage_weight(float v, int k, int c, int H, bf16_t* __restrict__ fwd, bf16_t* __restrict__ bwd) {
+  const SplitPair s = split_pair(v, 0.f);
+  const uint32_t part[3] = {s.h, s.m, s.l};
+  const int KS = H / 32, g = c / H, u = c - g * H;
+  const int64_t f = ((int64_t)((u / 16) * KS + k / 32) * 9 + g * 3) * 512 + ((u % 16) + 16 * ((k % 32) / 8)) * 8 + k % 8;
+  const int64_t b = ((int64_t)((k / 16) * 3 * KS + g * KS + u / 32) * 3) * 512 + ((k % 16) + 16 * ((u % 32) / 8)) * 8 + u % 8;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    fwd[f + 512 * p] = (bf16_t)part[p];
+    bwd[b + 512 * p] = (bf16_t)part[p];
+  }
+}
+
+__device__ __forceinline__ float sigmoid_f32(float x) { return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x)); }
+
+// The records of a step, [S1][4H]: forward (h Wh_n + bh_n, r, z, n); the backward pass replaces them by the gradients of
+// the pre-activations (of h Wh_n + bh_n, r, z, n), so that columns 0 .. 3H-1 are the gradient of the hidden products (new
+// gate first) and columns H .. 4H-1 that of the input products.
+struct GruFwdArgs {
+  const float* Gi;       // [T][S1][3H] input products, no bias
+  const bf16_t* W;       // staged weights
+  const float *bi, *bh;  // [3H]
+  const float* h_first;  // [S1][H] state before the first step; may be hs
+  float* hs;             // [T][S1][H] state after every step
+  float* rec;            // [T][S1][4H], nullable
+  const uint8_t* reset;  // nullable: reset[t * (S1 / per) + s / per] != 0: step t starts from a zero state;
+  int first_reset;       // entries of t = 0 are read only if this is set
+  int per;
+  int64_t S1;
+  int T;
+};
+
+// acc[i] += W[i] x B over 32 along the contraction, i-th of N independent tiles (small products first)
+__device__ __forceinline__ floatx4 mfma16(const bf16x8& a, const bf16x8& b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// Barrier for data exchanged through LDS only: global loads and stores stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+template <int KS, int SM, bool RES>
+__global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kernel(GruFwdArgs a) {
+  constexpr int H = 32 * KS, UB = RES ? 1 : 2, MT = 16 * SM, P = H + 8, PLANE = MT * P;
+  constexpr int THREADS = RES ? 128 * KS : 64 * KS;
+  __shared__ __attribute__((aligned(16))) bf16_t Hs[2][3 * PLANE];
+  __shared__ __attribute__((aligned(16))) float bias[4][H];  // r and z: both biases; n: input, hidden
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
+  const int64_t s0 = (int64_t)blockIdx.x * MT;
+  for (int j = tid; j < H; j += THREADS) {
+    bias[0][j] = a.bi[j] + a.bh[j];
+    bias[1][j] = a.bi[H + j] + a.bh[H + j];
+    bias[2][j] = a.bi[2 * H + j];
+    bias[3][j] = a.bh[2 * H + j];
+  }
+  int64_t srow[SM];  // clamped: rows past the end compute on the last one and store nothing
+  bool live[SM];
+  int64_t env[SM];
+#pragma unroll
+  for (int m = 0; m < SM; ++m) {
+    live[m] = s0 + 16 * m + lo < a.S1;
+    srow[m] = live[m] ? s0 + 16 * m + lo : a.S1 - 1;
+    env[m] = srow[m] / a.per;
+  }
+  const int64_t nenv = a.S1 / a.per;
+  int unit[UB];  // first of this lane's four units
+#pragma unroll
+  for (int b = 0; b < UB; ++b) unit[b] = 16 * (UB * wave + b) + 4 * q;
+
+  const WeightRsrc wsrc = weight_rsrc(reinterpret_cast<const float*>(a.W), H * H * 9 / 2);
+  int woff = UB * wave * KS * 9 * 1024 + lane * 16;  // this lane's bytes of its wavefront's fragments
+  auto load_w = [&](int i, bf16x8 (&w)[9]) {
+#pragma unroll
+    for (int f = 0; f < 9; ++f) w[f] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wsrc, woff, (i * 9 + f) * 1024, 0));
+  };
+  constexpr int NI = UB * KS;
+  bf16x8 w[RES ? NI : 2][9];
+#pragma unroll
+  for (int i = 0; i < (RES ? NI : 1); ++i) load_w(i, w[i]);
+
+  float4 h[UB][SM], gi[UB][SM][3];
+  auto load_gi = [&](int t, int b) {
+#pragma unroll
+    for (int m = 0; m < SM; ++m)
+#pragma unroll
+      for (int g = 0; g < 3; ++g) gi[b][m][g] = *reinterpret_cast<const float4*>(a.Gi + ((int64_t)t * a.S1 + srow[m]) * 3 * H + g * H + unit[b]);
+  };
+  auto hand_over = [&](int buf, int b, int m) { store_split4(&Hs[buf][(16 * m + lo) * P + unit[b]], PLANE, h[b][m]); };
+  int rs[SM];  // does the coming step start from a zero state
+  auto load_reset = [&](int t) {
+#pragma unroll
+    for (int m = 0; m < SM; ++m) rs[m] = a.reset != nullptr && (t > 0 || a.first_reset) ? a.reset[t * nenv + env[m]] : 0;
+  };
+  load_reset(0);
+#pragma unroll
+  for (int b = 0; b < UB; ++b) {
+    load_gi(0, b);
+#pragma unroll
+    for (int m = 0; m < SM; ++m) {
+      h[b][m] = *reinterpret_cast<const float4*>(a.h_first + srow[m] * H + unit[b]);
+      if (rs[m]) h[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
+      hand_over(0, b, m);
+    }
+  }
+  __syncthreads();
+
+#pragma unroll 1
+  for (int t = 0; t < a.T; ++t) {
+    if (!RES) asm volatile("" : "+v"(woff));  // the loads stay inside the loop: hoisted, they would be spilled
+    const bf16_t* const frag = &Hs[t & 1][lo * P + 8 * q];
+    if (t + 1 < a.T) load_reset(t + 1);
+#pragma unroll
+    for (int b = 0; b < UB; ++b) {
+      floatx4 acc[3][SM];
+#pragma unroll
+      for (int g = 0; g < 3; ++g)
+#pragma unroll
+        for (int m = 0; m < SM; ++m) acc[g][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const int i = b * KS + ks, slot = RES ? i : i & 1;
+        if (!RES) load_w((i + 1) % NI, w[(i + 1) & 1]);  // (NI is even: the ring goes on into the next step)
+        Split8 x[SM];
+#pragma unroll
+        for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * ks, PLANE);
+#define MARL_GRU_PRODUCT(WP, XP)            \
+  _Pragma("unroll") for (int g = 0; g < 3; ++g) \
+  _Pragma("unroll") for (int m = 0; m < SM; ++m) acc[g][m] = mfma16(w[slot][3 * g + WP], x[m].XP, acc[g][m]);
+        MARL_GRU_PRODUCT(2, h)
+        MARL_GRU_PRODUCT(0, l)
+        MARL_GRU_PRODUCT(1, m)
+        MARL_GRU_PRODUCT(1, h)
+        MARL_GRU_PRODUCT(0, m)
+        MARL_GRU_PRODUCT(0, h)
+#undef MARL_GRU_PRODUCT
+      }
+      float4 bs[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) bs[k] = *reinterpret_cast<const float4*>(&bias[k][unit[b]]);
+      float4 vr[SM], vz[SM], vn[SM], vh[SM], out[SM];
+#pragma unroll
+      for (int m = 0; m < SM; ++m) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          auto at = [e](const float4& v) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; };
+          auto put = [e](float4& v, float f) { (e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w) = f; };
+          const float r = sigmoid_f32(at(gi[b][m][0]) + (acc[0][m][e] + at(bs[0])));
+          const float z = sigmoid_f32(at(gi[b][m][1]) + (acc[1][m][e] + at(bs[1])));
+          const float hn = acc[2][m][e] + at(bs[3]);
+          const float n = tanh_f32((at(gi[b][m][2]) + at(bs[2])) + r * hn);
+          put(vr[m], r); put(vz[m], z); put(vh[m], hn); put(vn[m], n);
+          put(out[m], (1.0f - z) * n + z * at(h[b][m]));
+        }
+      }
+      if (t + 1 < a.T) load_gi(t + 1, b);  // ahead of this step's stores: the counter that loads wait on is in order
+#pragma unroll
+      for (int m = 0; m < SM; ++m) {
+        const int64_t row = (int64_t)t * a.S1 + srow[m];
+        if (live[m]) {
+          if (a.rec != nullptr) {
+            float* const d = a.rec + row * 4 * H + unit[b];
+            *reinterpret_cast<float4*>(d) = vh[m];
+            *reinterpret_cast<float4*>(d + H) = vr[m];
+            *reinterpret_cast<float4*>(d + 2 * H) = vz[m];
+            *reinterpret_cast<float4*>(d + 3 * H) = vn[m];
+          }
+          *reinterpret_cast<float4*>(a.hs + row * H + unit[b]) = out[m];
+        }
+        h[b][m] = rs[m] ? make_float4(0.f, 0.f, 0.f, 0.f) : out[m];
+        hand_over((t + 1) & 1, b, m);
+      }
+    }
+    lds_barrier();
+  }
+}
+
+struct GruBwdArgs {
+  const bf16_t* W;       // staged weights (backward copy)
+  const float* W3;       // [H][NOUT] output layer
+  const float* dl;       // [T][S1][NOUT] gradient of the outputs
+  float* rec;            // [T][S1][4H] records, replaced by gradients
+  const float* hs;       // [T][S1][H] state before every step (before a reset)
+  const uint8_t* reset;  // [T][S1 / per], as forward; entries of t = 0 are not read
+  int per;
+  int64_t S1;
+  int T;
+};
+
+template <int KS, int SM, bool RES, int NOUT>
+__global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kernel(GruBwdArgs a) {
+  constexpr int H = 32 * KS, UB = RES ? 1 : 2, MT = 16 * SM, P = 3 * H + 8, PLANE = MT * P;
+  constexpr int THREADS = RES ? 128 * KS : 64 * KS;
+  __shared__ __attribute__((aligned(16))) bf16_t Gs[3 * PLANE];
+  __shared__ __attribute__((aligned(16))) float W3s[H * NOUT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
+  const int64_t s0 = (int64_t)blockIdx.x * MT;
+  for (int j = tid; j < H * NOUT; j += THREADS) W3s[j] = a.W3[j];
+  int64_t srow[SM], env[SM];
+  bool live[SM];
+#pragma unroll
+  for (int m = 0; m < SM; ++m) {
+    live[m] = s0 + 16 * m + lo < a.S1;
+    srow[m] = live[m] ? s0 + 16 * m + lo : a.S1 - 1;
+    env[m] = srow[m] / a.per;
+  }
+  const int64_t nenv = a.S1 / a.per;
+  int unit[UB];
+#pragma unroll
+  for (int b = 0; b < UB; ++b) unit[b] = 16 * (UB * wave + b) + 4 * q;
+
+  constexpr int NI = 3 * KS, RING = RES ? NI : 3;  // NI is a multiple of 3
+  const WeightRsrc wsrc = weight_rsrc(reinterpret_cast<const float*>(a.W), H * H * 9 / 2);
+  int woff = UB * wave * NI * 3 * 1024 + lane * 16;
+  auto load_w = [&](int i, bf16x8 (&w)[UB][3]) {
+#pragma unroll
+    for (int b = 0; b < UB; ++b)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) w[b][p] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wsrc, woff, ((b * NI + i) * 3 + p) * 1024, 0));
+  };
+  bf16x8 w[RING][UB][3];
+#pragma unroll
+  for (int i = 0; i < (RES ? NI : 2); ++i) load_w(i, w[i]);
+
+  float4 rec[UB][SM][4], hp[UB][SM], carry[UB][SM];
+  float dl[SM][NOUT];
+  int rs[SM];
+  auto load_step = [&](int t, int b, int m) {
+    const int64_t row = (int64_t)t * a.S1 + srow[m];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rec[b][m][k] = *reinterpret_cast<const float4*>(a.rec + row * 4 * H + k * H + unit[b]);
+    hp[b][m] = *reinterpret_cast<const float4*>(a.hs + row * H + unit[b]);
+  };
+  auto load_row = [&](int t, int m) {
+    const int64_t row = (int64_t)t * a.S1 + srow[m];
+#pragma unroll
+    for (int k = 0; k < NOUT; ++k) dl[m][k] = a.dl[row * NOUT + k];
+    rs[m] = t > 0 ? a.reset[t * nenv + env[m]] : 0;
+  };
+#pragma unroll
+  for (int m = 0; m < SM; ++m) {
+    load_row(a.T - 1, m);
+#pragma unroll
+    for (int b = 0; b < UB; ++b) {
+      load_step(a.T - 1, b, m);
+      carry[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  __syncthreads();
+
+#pragma unroll 1
+  for (int t = a.T - 1; t >= 0; --t) {
+    if (!RES) asm volatile("" : "+v"(woff));
+    int was_reset[SM];
+#pragma unroll
+    for (int m = 0; m < SM; ++m) {
+      was_reset[m] = rs[m];
+#pragma unroll
+      for (int b = 0; b < UB; ++b) {
+        float4 gr, gz, gn, gh;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          auto at = [e](const float4& v) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; };
+          auto put = [e](float4& v, float f) { (e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w) = f; };
+          float dh = at(carry[b][m]);
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) dh = fmaf(dl[m][k], W3s[(unit[b] + e) * NOUT + k], dh);
+          const float hn = at(rec[b][m][0]), r = at(rec[b][m][1]), z = at(rec[b][m][2]), n = at(rec[b][m][3]);
+          const float hprev = rs[m] ? 0.f : at(hp[b][m]);
+          const float dpre_n = dh * (1.0f - z) * (1.0f - n * n);
+          put(gr, dpre_n * hn * r * (1.0f - r));
+          put(gz, dh * (hprev - n) * z * (1.0f - z));
+          put(gn, dpre_n);
+          put(gh, dpre_n * r);
+          put(carry[b][m], dh * z);
+        }
+        if (live[m]) {
+          float* const d = a.rec + ((int64_t)t * a.S1 + srow[m]) * 4 * H + unit[b];
+          *reinterpret_cast<float4*>(d) = gh;
+          *reinterpret_cast<float4*>(d + H) = gr;
+          *reinterpret_cast<float4*>(d + 2 * H) = gz;
+          *reinterpret_cast<float4*>(d + 3 * H) = gn;
+        }
+        bf16_t* const dst = &Gs[(16 * m + lo) * P + unit[b]];
+        store_split4(dst, PLANE, gr);
+        store_split4(dst + H, PLANE, gz);
+        store_split4(dst + 2 * H, PLANE, gh);
+        if (t > 0) load_step(t - 1, b, m);
+      }
+      if (t > 0) load_row(t - 1, m);
+    }
+    if (t == 0) break;  // uniform: nothing flows into the initial state
+    lds_barrier();
+    floatx4 acc[UB][SM];
+#pragma unroll
+    for (int b = 0; b < UB; ++b)
+#pragma unroll
+      for (int m = 0; m < SM; ++m) acc[b][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const bf16_t* const frag = Gs + lo * P + 8 * q;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int slot = i % RING;
+      if (!RES) load_w((i + 2) % NI, w[(i + 2) % RING]);
+      Split8 x[SM];
+#pragma unroll
+      for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * i, PLANE);
+#define MARL_GRU_PRODUCT(WP, XP)             \
+  _Pragma("unroll") for (int b = 0; b < UB; ++b) \
+  _Pragma("unroll") for (int m = 0; m < SM; ++m) acc[b][m] = mfma16(w[slot][b][WP], x[m].XP, acc[b][m]);
+      MARL_GRU_PRODUCT(2, h)
+      MARL_GRU_PRODUCT(0, l)
+      MARL_GRU_PRODUCT(1, m)
+      MARL_GRU_PRODUCT(1, h)
+      MARL_GRU_PRODUCT(0, m)
+      MARL_GRU_PRODUCT(0, h)
+#undef MARL_GRU_PRODUCT
+    }
+#pragma unroll
+    for (int b = 0; b < UB; ++b)
+#pragma unroll
+      for (int m = 0; m < SM; ++m) {
+        const float keep = was_reset[m] ? 0.f : 1.f;
+        carry[b][m].x = (acc[b][m][0] + carry[b][m].x) * keep;
+        carry[b][m].y = (acc[b][m][1] + carry[b][m].y) * keep;
+        carry[b][m].z = (acc[b][m][2] + carry[b][m].z) * keep;
+        carry[b][m].w = (acc[b][m][3] + carry[b][m].w) * keep;
+      }
+    lds_barrier();  // the tile has been read
+  }
+}
+
+// 16 sequences per workgroup while that leaves compute units idle, 32 (the same weights for twice the work) beyond.
+inline int gru_seq_tiles16(int64_t S1) { return S1 <= 256 * 16; }
+
+template <int KS>
+inline void launch_gru_fwd_ks(const GruFwdArgs& a, hipStream_t s) {
+  constexpr bool RES = KS <= 4;
+  const dim3 block(RES ? 128 * KS : 64 * KS);
+  if (gru_seq_tiles16(a.S1)) hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 1, RES>), dim3((unsigned)((a.S1 + 15) / 16)), block, 0, s, a);
+  else hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 2, RES>), dim3((unsigned)((a.S1 + 31) / 32)), block, 0, s, a);
+}
+template <int KS, int NOUT>
+inline void launch_gru_bwd_ks(const GruBwdArgs& a, hipStream_t s) {
+  constexpr bool RES = KS <= 4;
+  const dim3 block(RES ? 128 * KS : 64 * KS);
+  if (gru_seq_tiles16(a.S1)) hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, NOUT>), dim3((unsigned)((a.S1 + 15) / 16)), block, 0, s, a);
+  else hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 2, RES, NOUT>), dim3((unsigned)((a.S1 + 31) / 32)), block, 0, s, a);
+}
+
+}  // namespace marl

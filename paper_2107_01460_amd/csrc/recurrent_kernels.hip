@@ -5,12 +5,14 @@
 //
 // Every product with a weight matrix is an MFMA GEMM (gemm.h); the gate arithmetic is element-wise.  The products
 // that do not depend on the hidden state (the embedding e and its gate pre-activations e Wi) run once over all
-// T steps of a minibatch of sequences; only h Wh and the gates are stepped through time, forward for t = 0..T-1
-// and backward for t = T-1..0, where the weight gradients are again taken in one product over all steps.
+// T steps of a minibatch of sequences; h Wh and the gates are stepped through time by one kernel each way (gru_seq.h;
+// above 256 units by a product and an element-wise kernel per step), and the weight gradients are again taken in one
+// product over all steps.
 #include <algorithm>
 #include <cmath>
 
 #include "gemm.h"
+#include "gru_seq.h"
 #include "heads.h"
 #include "ppo_common.h"
 
@@ -42,9 +44,8 @@ RecOffsets rec_offsets(int64_t base, int Din, int H, int Dout) {
 // Working copy of the parameters with every block on a 64-float boundary (16-byte loads of weight rows).
 struct RecParamMap {
   int64_t src[17], dst[17];  // 16 blocks (actor 8, critic 8) + end
-  // per network, after the blocks: Wh and Wh transposed once more in the order a lane feeds them to the matrix cores
-  // straight from memory: element (k, n) of a [K][N] matrix at ((k / 4) * N + n) * 4 + k % 4
-  int64_t wh_op[2], wht_op[2];
+  // per network the sequence kernels cover, after the blocks: Wh split and in operand order, for each direction
+  int64_t wh_fwd[2], wh_bwd[2];
   int hidden[2];
   int64_t total;
 };
@@ -61,10 +62,10 @@ RecParamMap rec_param_map(const Dims& d) {
   m.hidden[0] = d.Ha;
   m.hidden[1] = d.Hc;
   for (int n = 0; n < 2; ++n) {
-    const int64_t sz = (((int64_t)m.hidden[n] * 3 * m.hidden[n] + 63) / 64) * 64;
-    m.wh_op[n] = off;
+    const int64_t sz = gru_seq_supported(m.hidden[n]) ? gru_weight_floats(m.hidden[n]) : 0;
+    m.wh_fwd[n] = off;
     off += sz;
-    m.wht_op[n] = off;
+    m.wh_bwd[n] = off;
     off += sz;
   }
   m.total = off;
@@ -84,11 +85,12 @@ __global__ void rec_stage_params_kernel(const float* __restrict__ src, float* __
   const float v = src[i];
   const int64_t e = i - pm.src[b];
   dst[pm.dst[b] + e] = v;
-  if (b == 4 || b == 12) {  // a Wh block [H][3H]: also its two operand-order copies
+  if (b == 4 || b == 12) {  // a Wh block [H][3H]
     const int net = b == 12, H = pm.hidden[net];
-    const int64_t k = e / (3 * H), c = e - k * (3 * H);
-    dst[pm.wh_op[net] + ((k / 4) * (3 * H) + c) * 4 + k % 4] = v;    // (k, c) of Wh
-    dst[pm.wht_op[net] + ((c / 4) * H + k) * 4 + c % 4] = v;          // (c, k) of Wh^T
+    if (H <= 256) {
+      const int k = (int)(e / (3 * H)), c = (int)(e - (int64_t)k * (3 * H));
+      gru_stage_weight(v, k, c, H, reinterpret_cast<bf16_t*>(dst + pm.wh_fwd[net]), reinterpret_cast<bf16_t*>(dst + pm.wh_bwd[net]));
+    }
   }
 }
 
@@ -97,23 +99,19 @@ __global__ void copy_f32_kernel(const float* __restrict__ src, float* __restrict
   if (i < n) dst[i] = src[i];
 }
 
-// h[s][j] = 0 where the previous step ended the episode of sample s's environment (per samples per environment).
-__global__ void mask_hidden_kernel(float* __restrict__ h, const uint8_t* __restrict__ done, int64_t n_elems, int H, int per) {
+// dst[s][j] = src[s][j], 0 where reset[s / per] (nullable) is set.  dst may be src.
+__global__ void mask_hidden_kernel(const float* src, float* dst, const uint8_t* __restrict__ reset, int64_t n_elems, int H, int per) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_elems) return;
-  const int64_t s = i / H;
-  if (done[s / per]) h[i] = 0.f;
+  dst[i] = reset != nullptr && reset[i / H / per] ? 0.f : src[i];
 }
 
-__device__ __forceinline__ float sigmoid_f32(float x) { return __builtin_amdgcn_rcpf(1.0f + fast_exp(-x)); }
-
-// Gate arithmetic of one step, one thread per (sample, hidden unit).  Gi / Gh are the products without their
-// biases.  hout may alias hprev.  hnext (nullable) gets hout * keep[s / per]: the input of the next step.
+// ---- one step at a time, for widths above 256: the arithmetic of gru_seq.h, one thread per (sample, hidden unit) -------
+// Gi / Gh are the products without their biases, hprev the state the step starts from.
 __global__ void __launch_bounds__(256) gru_forward_kernel(const float* __restrict__ Gi, const float* __restrict__ Gh,
                                                           const float* __restrict__ bi, const float* __restrict__ bh,
-                                                          const float* hprev, float* __restrict__ rzn,
-                                                          float* __restrict__ ghn, float* hout, float* __restrict__ hnext,
-                                                          const float* __restrict__ keep, int per, int64_t S, int H) {
+                                                          const float* __restrict__ hprev, float* __restrict__ rec,
+                                                          float* __restrict__ hout, int64_t S, int H) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= S * H) return;
   const int64_t s = i / H;
@@ -124,296 +122,68 @@ __global__ void __launch_bounds__(256) gru_forward_kernel(const float* __restric
   const float z = sigmoid_f32((gi[H + j] + bi[H + j]) + (gh[H + j] + bh[H + j]));
   const float hn = gh[2 * H + j] + bh[2 * H + j];
   const float n = tanh_f32((gi[2 * H + j] + bi[2 * H + j]) + r * hn);
-  const float h = (1.0f - z) * n + z * hprev[i];
-  if (rzn != nullptr) {
-    rzn[s * 3 * H + j] = r;
-    rzn[s * 3 * H + H + j] = z;
-    rzn[s * 3 * H + 2 * H + j] = n;
+  if (rec != nullptr) {
+    rec[s * 4 * H + j] = hn;
+    rec[s * 4 * H + H + j] = r;
+    rec[s * 4 * H + 2 * H + j] = z;
+    rec[s * 4 * H + 3 * H + j] = n;
   }
-  if (ghn != nullptr) ghn[i] = hn;
-  hout[i] = h;
-  if (hnext != nullptr) hnext[i] = h * keep[s / per];
+  hout[i] = (1.0f - z) * n + z * hprev[i];
 }
 
-// Backward of the gate arithmetic of one step.  dh = gradient from the next step (dh_next * keep_next, absent at the
-// last step) + the output layer's (dl W3^T).  Writes the gradients of the two gate products and dh * z, the direct
-// part of the gradient with respect to the incoming hidden state (the product dgh Wh^T is added by a GEMM).
+// dh = gradient from the next step (dh_next, absent at the last step; next_reset: that step started from zero) + the output
+// layer's (dl W3^T).  Replaces the step's records by the gradients and writes dh * z, the direct part of the gradient with
+// respect to the incoming state (the products with Wh^T are added by GEMMs).
 template <int NOUT>
-__global__ void __launch_bounds__(256) gru_backward_kernel(const float* __restrict__ dh_next, const float* __restrict__ keep_next,
+__global__ void __launch_bounds__(256) gru_backward_kernel(const float* __restrict__ dh_next, const uint8_t* __restrict__ next_reset,
                                                            const float* __restrict__ dl, const float* __restrict__ W3,
-                                                           const float* __restrict__ rzn, const float* __restrict__ ghn,
-                                                           const float* __restrict__ hprev, float* __restrict__ dgi,
-                                                           float* __restrict__ dgh, float* __restrict__ dhprev, int per,
+                                                           float* __restrict__ rec, const float* __restrict__ hs,
+                                                           const uint8_t* __restrict__ reset, float* __restrict__ dhprev, int per,
                                                            int64_t S, int H) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= S * H) return;
   const int64_t s = i / H;
   const int j = (int)(i - s * H);
-  float dh = dh_next != nullptr ? dh_next[i] * keep_next[s / per] : 0.f;
+  float dh = dh_next != nullptr && !next_reset[s / per] ? dh_next[i] : 0.f;
 #pragma unroll
   for (int k = 0; k < NOUT; ++k) dh = fmaf(dl[s * NOUT + k], W3[(int64_t)j * NOUT + k], dh);
-  const float r = rzn[s * 3 * H + j], z = rzn[s * 3 * H + H + j], n = rzn[s * 3 * H + 2 * H + j];
-  const float dn = dh * (1.0f - z);
-  const float dz = dh * (hprev[i] - n);
-  const float dpre_n = dn * (1.0f - n * n);
-  const float dr = dpre_n * ghn[i];
-  const float dpre_z = dz * z * (1.0f - z);
-  const float dpre_r = dr * r * (1.0f - r);
-  dgi[s * 3 * H + j] = dpre_r;
-  dgi[s * 3 * H + H + j] = dpre_z;
-  dgi[s * 3 * H + 2 * H + j] = dpre_n;
-  dgh[s * 3 * H + j] = dpre_r;
-  dgh[s * 3 * H + H + j] = dpre_z;
-  dgh[s * 3 * H + 2 * H + j] = dpre_n * r;
+  float* const q = rec + s * 4 * H + j;
+  const float hn = q[0], r = q[H], z = q[2 * H], n = q[3 * H];
+  const float hprev = reset != nullptr && reset[s / per] ? 0.f : hs[i];
+  const float dpre_n = dh * (1.0f - z) * (1.0f - n * n);
+  q[0] = dpre_n * r;
+  q[H] = dpre_n * hn * r * (1.0f - r);
+  q[2 * H] = dh * (hprev - n) * z * (1.0f - z);
+  q[3 * H] = dpre_n;
   dhprev[i] = dh * z;
 }
 
-// Index arrays of a minibatch of sequences: row r = t * J + j is trajectory row t * N + envs[j];
-// keep[r] = 0 where the step before t ended the episode of that environment (rows of t = 0 keep everything).
+// Index arrays of a minibatch of sequences: row r = t * J + j is trajectory row t * N + envs[j]; reset[r] = the step before t
+// ended the episode of that environment (never at t = 0); hrows[r] = the state row that step t starts from, r, or the row of
+// zeros behind the T + 1 slabs.
 __global__ void seq_index_kernel(const int32_t* __restrict__ envs, const uint8_t* __restrict__ done, int J, int N, int T,
-                                 int32_t* __restrict__ rows, float* __restrict__ keep) {
+                                 int32_t* __restrict__ rows, uint8_t* __restrict__ reset, int32_t* __restrict__ hrows) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= (int64_t)T * J) return;
   const int t = (int)(r / J), j = (int)(r - (int64_t)t * J);
   const int env = envs[j];
+  const bool z = t > 0 && done[(int64_t)(t - 1) * N + env];
   rows[r] = t * N + env;
-  keep[r] = (t > 0 && done[(int64_t)(t - 1) * N + env]) ? 0.f : 1.f;
+  reset[r] = z;
+  hrows[r] = z ? (T + 1) * J : (int32_t)r;
 }
 
-// dst[(j * per + a)][u] = h0[(envs[j] * per + a)][u]
+// dst[(j * per + a)][u] = h0[(envs[j] * per + a)][u]; zeros[0 .. per * H - 1] = 0
 __global__ void gather_hidden_kernel(const float* __restrict__ h0, const int32_t* __restrict__ envs, int J, int per, int H,
-                                     float* __restrict__ dst) {
+                                     float* __restrict__ dst, float* __restrict__ zeros) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (int64_t)J * per * H) return;
+  if (i < per * H) zeros[i] = 0.f;
   const int64_t q = i / H;
   const int u = (int)(i - q * H);
   const int j = (int)(q / per), a = (int)(q - (int64_t)j * per);
   dst[i] = h0[((int64_t)envs[j] * per + a) * H + u];
 }
-
-// ---- fused steps ---------------------------------------------------------------------------------------------
-// One time step of the cell in one kernel each way, for H <= 256: the product with the hidden-to-hidden weights runs
-// on the matrix cores with its A operand in LDS and the weights read in operand order straight from memory, and the
-// gate arithmetic is its epilogue (forward) or its prologue (backward).  A workgroup owns 32 samples and all H
-// units: H / 32 wavefronts, wavefront u the units 32 u .. 32 u + 31.
-
-constexpr int kStepRows = 32;
-inline bool fused_step_supported(int H) { return H % 32 == 0 && H <= 256; }
-inline size_t fused_fwd_lds(int H) { return sizeof(float) * kStepRows * (H + 4); }
-inline size_t fused_bwd_lds(int H) { return sizeof(float) * kStepRows * (3 * H + 4); }
-
-// Forward: gates of one step from Gi (input products, no bias) and hprev; see gru_forward_kernel for the outputs.
-__global__ void __launch_bounds__(512) gru_step_fwd_kernel(const float* __restrict__ Gi, const float* __restrict__ Wh_op,
-                                                           const float* __restrict__ bi, const float* __restrict__ bh,
-                                                           const float* hprev, float* __restrict__ rzn,
-                                                           float* __restrict__ ghn, float* hout, float* __restrict__ hnext,
-                                                           const float* __restrict__ keep, int per, int64_t S, int H) {
-  extern __shared__ __attribute__((aligned(16))) float lds[];
-  const int PH = H + 4;
-  float* Hs = lds;  // [32][PH]
-  // blockIdx.y: which share of the units this workgroup computes (blockDim.x / 64 wavefronts of 32 units each).  With
-  // few samples per step the units of a tile are split over several workgroups so that every CU has work; every one of
-  // them stages the whole h tile, so hout / hnext must then not alias hprev.
-  const int tid = threadIdx.x, lane = tid & 63, u = blockIdx.y * (blockDim.x >> 6) + (tid >> 6), lo = lane & 31, hi = lane >> 5;
-  const int nthreads = blockDim.x;
-  const int64_t s0 = (int64_t)blockIdx.x * kStepRows;
-  for (int f = tid; f < kStepRows * (H / 4); f += nthreads) {
-    const int r = f / (H / 4), c4 = f - r * (H / 4);
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (s0 + r < S) v = *reinterpret_cast<const float4*>(hprev + (s0 + r) * H + 4 * c4);
-    *reinterpret_cast<float4*>(&Hs[r * PH + 4 * c4]) = v;
-  }
-  const int n = u * 32 + lo;  // this lane's hidden unit
-  // the input products of this lane's 16 (sample, unit) elements, requested before the matrix loop
-  float gi[3][16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int64_t s = min(s0 + 8 * (r / 4) + 4 * hi + (r % 4), S - 1);
-#pragma unroll
-    for (int g = 0; g < 3; ++g) gi[g][r] = Gi[s * 3 * H + g * H + n];
-  }
-  __syncthreads();
-  floatx16 acc[3];
-#pragma unroll
-  for (int g = 0; g < 3; ++g)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[g][r] = 0.f;
-  const float* As = Hs + lo * PH + 4 * hi;
-  const float* Bg = Wh_op + ((int64_t)hi * 3 * H + n) * 4;  // quad `hi` of k group 0, column n of gate 0
-  const int ksteps = H / 8;  // a multiple of 4
-  // the weights of four k steps are in flight: a wavefront streams its own 3 x 32 columns of Wh from L2 and has
-  // nothing else to hide that latency behind
-  constexpr int kDepth = 4;
-  float4 bq[kDepth][3];
-  auto load_b = [&](int ks, float4 (&b3)[3]) {
-    const int kc = ks < ksteps ? ks : ksteps - 1;
-#pragma unroll
-    for (int g = 0; g < 3; ++g) b3[g] = *reinterpret_cast<const float4*>(Bg + ((int64_t)2 * kc * 3 * H + g * H) * 4);
-  };
-#pragma unroll
-  for (int d = 0; d < kDepth - 1; ++d) load_b(d, bq[d]);
-#pragma unroll 1
-  for (int k0 = 0; k0 < ksteps; k0 += kDepth) {
-#pragma unroll
-    for (int d = 0; d < kDepth; ++d) {
-      const int ks = k0 + d;
-      load_b(ks + kDepth - 1, bq[(d + kDepth - 1) % kDepth]);
-      const float4 av = *reinterpret_cast<const float4*>(As + 8 * ks);
-      const float af[4] = {av.x, av.y, av.z, av.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int g = 0; g < 3; ++g) {
-          const float4 b = bq[d][g];
-          acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], j == 0 ? b.x : j == 1 ? b.y : j == 2 ? b.z : b.w, acc[g], 0, 0, 0);
-        }
-    }
-  }
-  const float bir = bi[n], biz = bi[H + n], bin_ = bi[2 * H + n];
-  const float bhr = bh[n], bhz = bh[H + n], bhn = bh[2 * H + n];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int m = 8 * (r / 4) + 4 * hi + (r % 4);
-    const int64_t s = s0 + m;
-    if (s < S) {
-      const float rr = sigmoid_f32((gi[0][r] + bir) + (acc[0][r] + bhr));
-      const float zz = sigmoid_f32((gi[1][r] + biz) + (acc[1][r] + bhz));
-      const float hn = acc[2][r] + bhn;
-      const float nn = tanh_f32((gi[2][r] + bin_) + rr * hn);
-      const float h = (1.0f - zz) * nn + zz * Hs[m * PH + n];
-      if (rzn != nullptr) {
-        rzn[s * 3 * H + n] = rr;
-        rzn[s * 3 * H + H + n] = zz;
-        rzn[s * 3 * H + 2 * H + n] = nn;
-      }
-      if (ghn != nullptr) ghn[s * H + n] = hn;
-      hout[s * H + n] = h;
-      if (hnext != nullptr) hnext[s * H + n] = h * keep[s / per];
-    }
-  }
-}
-
-// Backward: the gate gradients of one step (see gru_backward_kernel) and, when want_dhprev, the whole gradient with
-// respect to the incoming hidden state: dh * z + dgh Wh^T.
-template <int NOUT>
-__global__ void __launch_bounds__(512) gru_step_bwd_kernel(const float* __restrict__ dh_next, const float* __restrict__ keep_next,
-                                                           const float* __restrict__ dl, const float* __restrict__ W3,
-                                                           const float* __restrict__ rzn, const float* __restrict__ ghn,
-                                                           const float* __restrict__ hprev, const float* __restrict__ WhT_op,
-                                                           float* __restrict__ dgi, float* __restrict__ dgh,
-                                                           float* dhprev, int want_dhprev, int per, int64_t S, int H) {
-  extern __shared__ __attribute__((aligned(16))) float lds[];
-  // The dgh tile, the A operand, is all that is kept in LDS ([32][PG]): the direct term dh * z travels through dhprev
-  // itself (written here by the thread that computes it, read back after the barrier by the thread that finishes that
-  // element), so that the 256-wide instantiation leaves room on a compute unit for a workgroup of the other network's
-  // kernel, which runs beside it on a second stream.
-  const int PG = 3 * H + 4;
-  float* Gs = lds;
-  const int tid = threadIdx.x, lane = tid & 63, u = tid >> 6, lo = lane & 31, hi = lane >> 5;
-  const int64_t s0 = (int64_t)blockIdx.x * kStepRows;
-  {  // gate arithmetic: thread -> unit j = tid % H, samples tid / H + 2 q
-    const int j = tid % H, mq = tid / H;
-    float w3[NOUT];
-#pragma unroll
-    for (int k = 0; k < NOUT; ++k) w3[k] = W3[(int64_t)j * NOUT + k];
-#pragma unroll 4
-    for (int q = 0; q < kStepRows / 2; ++q) {
-      const int m = mq + 2 * q;
-      const int64_t s = s0 + m;
-      float g_r = 0.f, g_z = 0.f, g_n = 0.f, g_hn = 0.f, dz_direct = 0.f;
-      if (s < S) {
-        const int64_t i = s * H + j;
-        float dh = dh_next != nullptr ? dh_next[i] * keep_next[s / per] : 0.f;
-#pragma unroll
-        for (int k = 0; k < NOUT; ++k) dh = fmaf(dl[s * NOUT + k], w3[k], dh);
-        const float r = rzn[s * 3 * H + j], z = rzn[s * 3 * H + H + j], n = rzn[s * 3 * H + 2 * H + j];
-        const float dn = dh * (1.0f - z);
-        const float dz = dh * (hprev[i] - n);
-        const float dpre_n = dn * (1.0f - n * n);
-        const float dr = dpre_n * ghn[i];
-        g_z = dz * z * (1.0f - z);
-        g_r = dr * r * (1.0f - r);
-        g_n = dpre_n;
-        g_hn = dpre_n * r;
-        dz_direct = dh * z;
-        dgi[s * 3 * H + j] = g_r;
-        dgi[s * 3 * H + H + j] = g_z;
-        dgi[s * 3 * H + 2 * H + j] = g_n;
-        dgh[s * 3 * H + j] = g_r;
-        dgh[s * 3 * H + H + j] = g_z;
-        dgh[s * 3 * H + 2 * H + j] = g_hn;
-        if (want_dhprev) dhprev[i] = dz_direct;
-      }
-      Gs[m * PG + j] = g_r;
-      Gs[m * PG + H + j] = g_z;
-      Gs[m * PG + 2 * H + j] = g_hn;
-    }
-  }
-  if (!want_dhprev) return;  // uniform
-  __syncthreads();  // orders the tile in LDS and this workgroup's stores to dhprev before the reads below
-  // dhprev tile = Ds + Gs WhT: wavefront u the 32 units 32 u .., contraction over the 3 H gate columns,
-  // two accumulators over alternate k steps so that consecutive MFMAs do not wait for each other
-  const int n = u * 32 + lo;
-  floatx16 acc[2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[a][r] = 0.f;
-  float direct[16];  // dh * z of this lane's output elements, requested before the product
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int64_t s = s0 + 8 * (r / 4) + 4 * hi + (r % 4);
-    direct[r] = s < S ? dhprev[s * H + n] : 0.f;
-  }
-  const float* As = Gs + lo * PG + 4 * hi;
-  const float* Bg = WhT_op + ((int64_t)hi * H + n) * 4;
-  const int ksteps = 3 * H / 8;  // a multiple of 12: H is a multiple of 32
-  constexpr int kDepth = 6;      // k steps in flight
-  float4 bq[kDepth];
-  auto load_b = [&](int ks, float4& b) {
-    const int kc = ks < ksteps ? ks : ksteps - 1;
-    b = *reinterpret_cast<const float4*>(Bg + (int64_t)2 * kc * H * 4);
-  };
-#pragma unroll
-  for (int d = 0; d < kDepth - 1; ++d) load_b(d, bq[d]);
-#pragma unroll 1
-  for (int k0 = 0; k0 < ksteps; k0 += kDepth) {
-#pragma unroll
-    for (int d = 0; d < kDepth; ++d) {
-      const int ks = k0 + d;
-      load_b(ks + kDepth - 1, bq[(d + kDepth - 1) % kDepth]);
-      const float4 av = *reinterpret_cast<const float4*>(As + 8 * ks);
-      const float4 b = bq[d];
-      acc[d & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, b.x, acc[d & 1], 0, 0, 0);
-      acc[d & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, b.y, acc[d & 1], 0, 0, 0);
-      acc[d & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, b.z, acc[d & 1], 0, 0, 0);
-      acc[d & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, b.w, acc[d & 1], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int m = 8 * (r / 4) + 4 * hi + (r % 4);
-    const int64_t s = s0 + m;
-    if (s < S) dhprev[s * H + n] = (acc[0][r] + acc[1][r]) + direct[r];
-  }
-}
-
-template <class K>
-int32_t allow_big_lds(K kern) {
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-    return MARL_E_LAUNCH;
-  return MARL_OK;
-}
-
-// One forward step: fused when the width allows it, else the GEMM + gate kernel pair.
-int32_t launch_step_forward(const float* Gi, const float* hprev, int64_t S, int H, const float* eff, const RecOffsets& o,
-                            const float* wh_op, float* GhT, float* rzn, float* ghn, float* hout, float* hnext,
-                            const float* keep, int per, hipStream_t s);
-template <int NOUT>
-int32_t launch_step_backward(const float* dh_next, const float* keep_next, const float* dl, const float* rzn,
-                             const float* ghn, const float* hprev, int64_t S, int H, const float* eff, const RecOffsets& o,
-                             const float* wht_op, float* dgi, float* dgh, float* dhprev, bool want_dhprev, int per,
-                             hipStream_t s);
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -449,59 +219,71 @@ void hidden_gates(const float* hprev, int64_t S, int H, const float* eff, const 
   launch_gemm<GEMM_NN, EPI_STORE>(g, s);
 }
 
-int32_t launch_step_forward(const float* Gi, const float* hprev, int64_t S, int H, const float* eff, const RecOffsets& o,
-                            const float* wh_op, float* GhT, float* rzn, float* ghn, float* hout, float* hnext,
-                            const float* keep, int per, hipStream_t s) {
-  if (fused_step_supported(H)) {
-    TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)S * H * 3.0 * H, s);
-    const int64_t tiles = (S + kStepRows - 1) / kStepRows;
-    int ysplit = 1;  // workgroups per tile: enough for one per CU where the state is not updated in place
-    if (hprev != hout && hprev != hnext)
-      while (tiles * ysplit < 256 && ysplit < H / 32) ysplit *= 2;
-    while ((H / 32) % ysplit != 0) ysplit /= 2;
-    hipLaunchKernelGGL(gru_step_fwd_kernel, dim3((unsigned)tiles, (unsigned)ysplit), dim3(2 * H / ysplit), fused_fwd_lds(H),
-                       s, Gi, wh_op, eff + o.bi, eff + o.bh, hprev, rzn, ghn, hout, hnext, keep, per, S, H);
-    return MARL_OK;
+// All steps of a, forward.  GhT [S1][3H] and hm [S1][H] are used above 256 units only.
+void gru_forward(const GruFwdArgs& a, int H, const float* eff, const RecOffsets& o, float* GhT, float* hm, hipStream_t s) {
+  if (gru_seq_supported(H)) {
+    TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)a.T * (double)a.S1 * H * 3.0 * H, s);
+    switch (H / 32) {
+      case 1: return launch_gru_fwd_ks<1>(a, s);
+      case 2: return launch_gru_fwd_ks<2>(a, s);
+      case 3: return launch_gru_fwd_ks<3>(a, s);
+      case 4: return launch_gru_fwd_ks<4>(a, s);
+      case 5: return launch_gru_fwd_ks<5>(a, s);
+      case 6: return launch_gru_fwd_ks<6>(a, s);
+      case 7: return launch_gru_fwd_ks<7>(a, s);
+      default: return launch_gru_fwd_ks<8>(a, s);
+    }
   }
-  hidden_gates(hprev, S, H, eff, o, GhT, s);
-  hipLaunchKernelGGL(gru_forward_kernel, dim3(blocks_for(S * H)), dim3(256), 0, s, Gi, GhT, eff + o.bi, eff + o.bh, hprev, rzn,
-                     ghn, hout, hnext, keep, per, S, H);
-  return MARL_OK;
+  for (int t = 0; t < a.T; ++t) {
+    const uint8_t* const reset = a.reset != nullptr && (t > 0 || a.first_reset) ? a.reset + (int64_t)t * (a.S1 / a.per) : nullptr;
+    hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(a.S1 * H)), dim3(256), 0, s, t > 0 ? a.hs + (int64_t)(t - 1) * a.S1 * H : a.h_first,
+                       hm, reset, a.S1 * H, H, a.per);
+    hidden_gates(hm, a.S1, H, eff, o, GhT, s);
+    hipLaunchKernelGGL(gru_forward_kernel, dim3(blocks_for(a.S1 * H)), dim3(256), 0, s, a.Gi + (int64_t)t * a.S1 * 3 * H, GhT, a.bi, a.bh, hm,
+                       a.rec != nullptr ? a.rec + (int64_t)t * a.S1 * 4 * H : (float*)nullptr, a.hs + (int64_t)t * a.S1 * H, a.S1, H);
+  }
 }
 
+// All steps of a, backward.  dhp [2][S1][H] is used above 256 units only.
 template <int NOUT>
-int32_t launch_step_backward(const float* dh_next, const float* keep_next, const float* dl, const float* rzn,
-                             const float* ghn, const float* hprev, int64_t S, int H, const float* eff, const RecOffsets& o,
-                             const float* wht_op, float* dgi, float* dgh, float* dhprev, bool want_dhprev, int per,
-                             hipStream_t s) {
-  if (fused_step_supported(H)) {
-    static bool configured = false;  // per NOUT
-    if (!configured) {
-      const int32_t rc = allow_big_lds(gru_step_bwd_kernel<NOUT>);
-      if (rc != MARL_OK) return rc;
-      configured = true;
+void gru_backward(const GruBwdArgs& a, int H, const float* eff, const RecOffsets& o, float* dhp, hipStream_t s) {
+  if (gru_seq_supported(H)) {
+    TimedLaunch timed(KC_GEMM_NT, 2.0 * (double)(a.T - 1) * (double)a.S1 * H * 3.0 * H, s);
+    switch (H / 32) {
+      case 1: return launch_gru_bwd_ks<1, NOUT>(a, s);
+      case 2: return launch_gru_bwd_ks<2, NOUT>(a, s);
+      case 3: return launch_gru_bwd_ks<3, NOUT>(a, s);
+      case 4: return launch_gru_bwd_ks<4, NOUT>(a, s);
+      case 5: return launch_gru_bwd_ks<5, NOUT>(a, s);
+      case 6: return launch_gru_bwd_ks<6, NOUT>(a, s);
+      case 7: return launch_gru_bwd_ks<7, NOUT>(a, s);
+      default: return launch_gru_bwd_ks<8, NOUT>(a, s);
     }
-    TimedLaunch timed(KC_GEMM_NT, want_dhprev ? 2.0 * (double)S * H * 3.0 * H : 0.0, s);
-    hipLaunchKernelGGL(gru_step_bwd_kernel<NOUT>, dim3((unsigned)((S + kStepRows - 1) / kStepRows)), dim3(2 * H),
-                       fused_bwd_lds(H), s, dh_next, keep_next, dl, eff + o.W3, rzn, ghn, hprev, wht_op, dgi, dgh, dhprev,
-                       (int)want_dhprev, per, S, H);
-    return MARL_OK;
   }
-  hipLaunchKernelGGL(gru_backward_kernel<NOUT>, dim3(blocks_for(S * H)), dim3(256), 0, s, dh_next, keep_next, dl, eff + o.W3,
-                     rzn, ghn, hprev, dgi, dgh, dhprev, per, S, H);
-  if (want_dhprev) {  // dL/dhprev += dgh Wh^T (what flows into the step before)
+  const int64_t J = a.S1 / a.per;
+  for (int t = a.T - 1; t >= 0; --t) {
+    float* const out = dhp + (int64_t)(t & 1) * a.S1 * H;
+    float* const rec = a.rec + (int64_t)t * a.S1 * 4 * H;
+    const bool last = t == a.T - 1;
+    hipLaunchKernelGGL(gru_backward_kernel<NOUT>, dim3(blocks_for(a.S1 * H)), dim3(256), 0, s,
+                       last ? (const float*)nullptr : dhp + (int64_t)((t + 1) & 1) * a.S1 * H, last ? (const uint8_t*)nullptr : a.reset + (t + 1) * J,
+                       a.dl + (int64_t)t * a.S1 * NOUT, a.W3, rec, a.hs + (int64_t)t * a.S1 * H, t > 0 ? a.reset + t * J : (const uint8_t*)nullptr,
+                       out, a.per, a.S1, H);
+    if (t == 0) break;
+    // dL/dhprev += dgh Wh^T: the columns of r and z, then the one of the new gate, which the records hold first
     GemmArgs g{};
-    g.A = RowSrc{dgh, 3 * H, nullptr, 1, S}; g.B = eff + o.Wh; g.ldb = 3 * H; g.C = dhprev; g.ldc = H;
-    g.M = S; g.N = H; g.K = 3 * H;
+    g.A = RowSrc{rec + H, 4 * H, nullptr, 1, a.S1}; g.B = eff + o.Wh; g.ldb = 3 * H; g.C = out; g.ldc = H;
+    g.M = a.S1; g.N = H; g.K = 2 * H;
+    launch_gemm<GEMM_NT, EPI_ATOMIC_ADD>(g, s);
+    g.A = RowSrc{rec, 4 * H, nullptr, 1, a.S1}; g.B = eff + o.Wh + 2 * H; g.K = H;
     launch_gemm<GEMM_NT, EPI_ATOMIC_ADD>(g, s);
   }
-  return MARL_OK;
 }
 
 // ---- rollout ---------------------------------------------------------------------------------------------
 
 struct RecRolloutWs {
-  float *eff, *ha, *hc, *hc_tmp, *E, *Gi, *Gh;
+  float *eff, *ha, *hc, *hc_tmp, *hm, *E, *Gi, *Gh;
 };
 RecRolloutWs carve_rec_rollout(const marl_config& c, void* ws, int64_t* total) {
   const Dims d = dims_of(c);
@@ -519,6 +301,7 @@ RecRolloutWs carve_rec_rollout(const marl_config& c, void* ws, int64_t* total) {
   w.ha = take(d.NA * d.Ha * 4);
   w.hc = take(Sc * d.Hc * 4);
   w.hc_tmp = take(Sc * d.Hc * 4);
+  w.hm = take(Sm * Hm * 4);
   w.E = take(Sm * Hm * 4);
   w.Gi = take(Sm * 3 * Hm * 4);
   w.Gh = take(Sm * 3 * Hm * 4);
@@ -526,11 +309,14 @@ RecRolloutWs carve_rec_rollout(const marl_config& c, void* ws, int64_t* total) {
   return w;
 }
 
-// One step of one recurrent network on S samples: hidden state h_in -> h_out (may alias).
-void rec_cell_step(const RowSrc& X, int64_t S, int Din, int H, const float* eff, const RecOffsets& o, const float* wh_op,
-                   const float* h_in, float* h_out, const RecRolloutWs& w, hipStream_t s) {
+// One step of one recurrent network on S samples: hidden state h_in -> h_out (may alias); reset (nullable) as in GruFwdArgs.
+void rec_cell_step(const RowSrc& X, int64_t S, int Din, int H, const float* eff, const RecOffsets& o, const float* wh_fwd,
+                   const float* h_in, float* h_out, const uint8_t* reset, int per, const RecRolloutWs& w, hipStream_t s) {
   embed_and_input_gates(X, S, Din, H, eff, o, w.E, w.Gi, s);
-  launch_step_forward(w.Gi, h_in, S, H, eff, o, wh_op, w.Gh, nullptr, nullptr, h_out, nullptr, nullptr, 1, s);
+  GruFwdArgs a{};
+  a.Gi = w.Gi; a.W = reinterpret_cast<const bf16_t*>(wh_fwd); a.bi = eff + o.bi; a.bh = eff + o.bh;
+  a.h_first = h_in; a.hs = h_out; a.reset = reset; a.first_reset = 1; a.per = per; a.S1 = S; a.T = 1;
+  gru_forward(a, H, eff, o, w.Gh, w.hm, s);
 }
 
 }  // namespace
@@ -556,13 +342,8 @@ int32_t launch_rollout_recurrent(const marl_config& c, marl_env_state st, const 
   hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(Sc * d.Hc)), dim3(256), 0, s, rec.hc0, w.hc, Sc * d.Hc);
   int32_t rc = launch_env_step(c, st, nullptr, tr.obs, nullptr, nullptr, /*do_step=*/false, s);
   if (rc != MARL_OK) return rc;
-  auto mask = [&](int t_done) {  // a new episode starts from the zero state
-    const uint8_t* dn = tr.done + (int64_t)t_done * d.N;
-    hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(NA * d.Ha)), dim3(256), 0, s, w.ha, dn, NA * d.Ha, d.Ha, d.A);
-    hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(Sc * d.Hc)), dim3(256), 0, s, w.hc, dn, Sc * d.Hc, d.Hc, per_c);
-  };
   for (int t = 0; t < d.T; ++t) {
-    if (t > 0) mask(t - 1);
+    const uint8_t* ended = t > 0 ? tr.done + (int64_t)(t - 1) * d.N : (const uint8_t*)nullptr;  // a new episode starts from the zero state
     const float* obs_t = tr.obs + (int64_t)t * slab;
     SampleArgs a{};
     a.uniforms = forced_uniforms ? forced_uniforms + (int64_t)t * NA * kActions : nullptr;
@@ -573,20 +354,20 @@ int32_t launch_rollout_recurrent(const marl_config& c, marl_env_state st, const 
     a.step = step_offset + (uint64_t)t;
     a.k0 = (uint32_t)(c.seed & 0xffffffffu);
     a.k1 = (uint32_t)(c.seed >> 32);
-    rec_cell_step(RowSrc{obs_t, d.D, nullptr, 1, NA}, NA, d.D, d.Ha, eff, oa, eff + pm.wh_op[0], w.ha, w.ha, w, s);
+    rec_cell_step(RowSrc{obs_t, d.D, nullptr, 1, NA}, NA, d.D, d.Ha, eff, oa, eff + pm.wh_fwd[0], w.ha, w.ha, ended, d.A, w, s);
     launch_actor_head_rollout(w.ha, NA, d.Ha, eff + oa.W3, eff + oa.b3,
                               tr.logits ? tr.logits + (int64_t)t * NA * kActions : (float*)nullptr, &a, s);
-    rec_cell_step(RowSrc{obs_t, d.Dc, nullptr, 1, Sc}, Sc, d.Dc, d.Hc, eff, oc, eff + pm.wh_op[1], w.hc, w.hc, w, s);
+    rec_cell_step(RowSrc{obs_t, d.Dc, nullptr, 1, Sc}, Sc, d.Dc, d.Hc, eff, oc, eff + pm.wh_fwd[1], w.hc, w.hc, ended, per_c, w, s);
     launch_critic_head_rollout(w.hc, Sc, d.Hc, eff + oc.W3, eff + oc.b3, tr.value + (int64_t)t * NA, d.central ? d.A : 1, s);
     rc = launch_env_step(c, st, a.action, tr.obs + (int64_t)(t + 1) * slab, tr.reward + (int64_t)t * NA,
                          tr.done + (int64_t)t * d.N, true, s);
     if (rc != MARL_OK) return rc;
   }
-  mask(d.T - 1);
-  hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(NA * d.Ha)), dim3(256), 0, s, w.ha, rec.ha1, NA * d.Ha);
-  hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(Sc * d.Hc)), dim3(256), 0, s, w.hc, rec.hc1, Sc * d.Hc);
+  const uint8_t* ended = tr.done + (int64_t)(d.T - 1) * d.N;
+  hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(NA * d.Ha)), dim3(256), 0, s, w.ha, rec.ha1, ended, NA * d.Ha, d.Ha, d.A);
+  hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(Sc * d.Hc)), dim3(256), 0, s, w.hc, rec.hc1, ended, Sc * d.Hc, d.Hc, per_c);
   // bootstrap value of the post-rollout observation; the hidden state of the next rollout stays as it is
-  rec_cell_step(RowSrc{tr.obs + (int64_t)d.T * slab, d.Dc, nullptr, 1, Sc}, Sc, d.Dc, d.Hc, eff, oc, eff + pm.wh_op[1], w.hc, w.hc_tmp, w, s);
+  rec_cell_step(RowSrc{tr.obs + (int64_t)d.T * slab, d.Dc, nullptr, 1, Sc}, Sc, d.Dc, d.Hc, eff, oc, eff + pm.wh_fwd[1], rec.hc1, w.hc_tmp, nullptr, per_c, w, s);
   launch_critic_head_rollout(w.hc_tmp, Sc, d.Hc, eff + oc.W3, eff + oc.b3, tr.last_value, d.central ? d.A : 1, s);
   return launch_status();
 }
@@ -597,13 +378,13 @@ namespace {
 
 // buffers of one network's forward and backward pass over a minibatch
 struct RecNetWs {
-  float *dl, *E, *G, *RZN, *GHN, *Hout, *Hprev, *GhT, *dGh, *dHp;
+  float *dl, *E, *G, *R, *Hs, *GhT, *hm, *dHp;  // R: records [S][4H]; Hs: states, T + 1 slabs and one row of zeros
 };
 struct RecUpdateWs {
   float *eff, *grad;
   Scalars* sc;
-  int32_t *ident, *rows;
-  float* keep;
+  int32_t *ident, *rows, *hrows;
+  uint8_t* reset;
   RecNetWs net[2];  // actor, critic: a set each, so that the two networks can run side by side
 };
 
@@ -625,20 +406,21 @@ RecUpdateWs carve_rec_update(const marl_config& c, void* ws, int64_t* total) {
   w.sc = (Scalars*)take(sizeof(Scalars));
   w.ident = (int32_t*)take((int64_t)d.N * 4);
   w.rows = (int32_t*)take(TJ * 4);
-  w.keep = (float*)take(TJ * 4);
+  w.hrows = (int32_t*)take(TJ * 4);
+  w.reset = (uint8_t*)take(TJ);
   for (int k = 0; k < 2; ++k) {
     const int64_t SH = k == 0 ? Sa * d.Ha : Sc * d.Hc, S1H = k == 0 ? S1a * d.Ha : S1c * d.Hc;
+    const int H = k == 0 ? d.Ha : d.Hc;
     RecNetWs& n = w.net[k];
     n.dl = (float*)take((k == 0 ? Sa * kActions : Sc) * 4);
     n.E = (float*)take(SH * 4);
     n.G = (float*)take(3 * SH * 4);
-    n.RZN = (float*)take(3 * SH * 4);
-    n.GHN = (float*)take(SH * 4);
-    n.Hout = (float*)take(SH * 4);
-    n.Hprev = (float*)take((SH + S1H) * 4);
-    n.GhT = (float*)take(3 * S1H * 4);
-    n.dGh = (float*)take(3 * SH * 4);
-    n.dHp = (float*)take(2 * S1H * 4);
+    n.R = (float*)take(4 * SH * 4);
+    n.Hs = (float*)take((SH + S1H + (int64_t)(k == 0 || !d.central ? d.A * H : H)) * 4);
+    const int64_t step = gru_seq_supported(H) ? 0 : S1H;  // one step's buffers
+    n.GhT = (float*)take(3 * step * 4);
+    n.hm = (float*)take(step * 4);
+    n.dHp = (float*)take(2 * step * 4);
   }
   if (total) *total = off;
   return w;
@@ -648,53 +430,43 @@ RecUpdateWs carve_rec_update(const marl_config& c, void* ws, int64_t* total) {
 // (`per` samples per environment row).  Samples are ordered [t][j][a].
 template <int NOUT, class LossFn>
 int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din, int H, const float* h0,
-                            const int32_t* envs, const float* eff, const RecOffsets& o, const float* wh_op,
-                            const float* wht_op, float* grad, const RecOffsets& go, const LossFn& fn, const RecNetWs& w,
-                            const float* keep, Scalars* sc, hipStream_t s) {
+                            const int32_t* envs, const float* eff, const RecOffsets& o, const float* wh_fwd,
+                            const float* wh_bwd, float* grad, const RecOffsets& go, const LossFn& fn, const RecNetWs& w,
+                            const uint8_t* reset, const int32_t* hrows, Scalars* sc, hipStream_t s) {
   const int64_t S1 = J * per, S = (int64_t)T * S1;
-  hipLaunchKernelGGL(gather_hidden_kernel, dim3(blocks_for(S1 * H)), dim3(256), 0, s, h0, envs, (int)J, per, H, w.Hprev);
+  hipLaunchKernelGGL(gather_hidden_kernel, dim3(blocks_for(S1 * H)), dim3(256), 0, s, h0, envs, (int)J, per, H, w.Hs, w.Hs + (S + S1) * H);
   embed_and_input_gates(X, S, Din, H, eff, o, w.E, w.G, s);
-  for (int t = 0; t < T; ++t) {
-    const float* hprev = w.Hprev + (int64_t)t * S1 * H;
-    const int32_t rc = launch_step_forward(w.G + (int64_t)t * S1 * 3 * H, hprev, S1, H, eff, o, wh_op, w.GhT,
-                                           w.RZN + (int64_t)t * S1 * 3 * H, w.GHN + (int64_t)t * S1 * H,
-                                           w.Hout + (int64_t)t * S1 * H,
-                                           t + 1 < T ? w.Hprev + (int64_t)(t + 1) * S1 * H : (float*)nullptr,
-                                           t + 1 < T ? keep + (int64_t)(t + 1) * J : (const float*)nullptr, per, s);
-    if (rc != MARL_OK) return rc;
-  }
+  GruFwdArgs f{};
+  f.Gi = w.G; f.W = reinterpret_cast<const bf16_t*>(wh_fwd); f.bi = eff + o.bi; f.bh = eff + o.bh;
+  f.h_first = w.Hs; f.hs = w.Hs + S1 * H; f.rec = w.R; f.reset = reset; f.first_reset = 0; f.per = per; f.S1 = S1; f.T = T;
+  gru_forward(f, H, eff, o, w.GhT, w.hm, s);
   {  // output layer, loss, dL/dout, W3 / b3 gradient over all steps
     const unsigned nb = (unsigned)std::min<int64_t>(2048, (S + kHeadTile - 1) / kHeadTile);
-    hipLaunchKernelGGL((loss_head_kernel<NOUT, LossFn, float>), dim3(nb), dim3(256), 0, s, w.Hout, S, H, eff + o.W3,
+    hipLaunchKernelGGL((loss_head_kernel<NOUT, LossFn, float>), dim3(nb), dim3(256), 0, s, w.Hs + S1 * H, S, H, eff + o.W3,
                        eff + o.b3, fn, w.dl, grad + go.W3, grad + go.b3, sc, 0.f);
   }
-  for (int t = T - 1; t >= 0; --t) {
-    float* dhp = w.dHp + (int64_t)(t & 1) * S1 * H;
-    const float* dh_next = t + 1 < T ? w.dHp + (int64_t)((t + 1) & 1) * S1 * H : (const float*)nullptr;
-    float* dgi = w.G + (int64_t)t * S1 * 3 * H;  // the input-gate products are no longer needed: their gradient takes their place
-    float* dgh = w.dGh + (int64_t)t * S1 * 3 * H;
-    const int32_t rc = launch_step_backward<NOUT>(dh_next, t + 1 < T ? keep + (int64_t)(t + 1) * J : (const float*)nullptr,
-                                                  w.dl + (int64_t)t * S1 * NOUT, w.RZN + (int64_t)t * S1 * 3 * H,
-                                                  w.GHN + (int64_t)t * S1 * H, w.Hprev + (int64_t)t * S1 * H, S1, H, eff, o,
-                                                  wht_op, dgi, dgh, dhp, t > 0, per, s);
-    if (rc != MARL_OK) return rc;
-  }
+  GruBwdArgs bw{};
+  bw.W = reinterpret_cast<const bf16_t*>(wh_bwd); bw.W3 = eff + o.W3; bw.dl = w.dl; bw.rec = w.R; bw.hs = w.Hs; bw.reset = reset;
+  bw.per = per; bw.S1 = S1; bw.T = T;
+  gru_backward<NOUT>(bw, H, eff, o, w.dHp, s);
   const int64_t tiles_h3 = ((H + 127) / 128) * ((3 * H + 127) / 128);
-  {  // gWh += Hprev^T dGh, gbh += column sums
+  const float* const dgh = w.R;      // [S][4H], columns n, r, z
+  const float* const dgi = w.R + H;  // [S][4H], columns r, z, n
+  {  // gWh += (states the steps start from)^T dGh, gbh += column sums; the new gate's columns go to the end
     GemmArgs g{};
-    g.A = RowSrc{w.Hprev, H, nullptr, 1, S}; g.B = w.dGh; g.ldb = 3 * H; g.C = grad + go.Wh; g.ldc = 3 * H;
+    g.A = RowSrc{w.Hs, H, hrows, per, S}; g.B = dgh; g.ldb = 4 * H; g.C = grad + go.Wh; g.ldc = 3 * H; g.c_rot = 2 * H;
     g.M = H; g.N = 3 * H; g.K = S; g.colsum = grad + go.bh; g.k_per_split = k_split(S, tiles_h3);
     launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s);
   }
   {  // gWi += E^T dGi, gbi += column sums
     GemmArgs g{};
-    g.A = RowSrc{w.E, H, nullptr, 1, S}; g.B = w.G; g.ldb = 3 * H; g.C = grad + go.Wi; g.ldc = 3 * H;
+    g.A = RowSrc{w.E, H, nullptr, 1, S}; g.B = dgi; g.ldb = 4 * H; g.C = grad + go.Wi; g.ldc = 3 * H;
     g.M = H; g.N = 3 * H; g.K = S; g.colsum = grad + go.bi; g.k_per_split = k_split(S, tiles_h3);
     launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s);
   }
   {  // dE = (dGi Wi^T) * (1 - e^2), in place over e
     GemmArgs g{};
-    g.A = RowSrc{w.G, 3 * H, nullptr, 1, S}; g.B = eff + o.Wi; g.ldb = 3 * H; g.C = w.E; g.ldc = H;
+    g.A = RowSrc{dgi, 4 * H, nullptr, 1, S}; g.B = eff + o.Wi; g.ldb = 3 * H; g.C = w.E; g.ldc = H;
     g.aux_mat = w.E; g.ldaux = H; g.M = S; g.N = H; g.K = 3 * H;
     launch_gemm<GEMM_NT, EPI_DTANH>(g, s);
   }
@@ -733,7 +505,7 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
       const int32_t* envs = (perm ? perm + (int64_t)e * d.N : w.ident) + (int64_t)mb * J;
       const float* eff = stage_params(d, params, w.eff, s);
       hipLaunchKernelGGL(zero_step_kernel, dim3(blocks_for(d.P)), dim3(256), 0, s, w.grad, d.P, w.sc, 1, (double*)nullptr, 0);
-      hipLaunchKernelGGL(seq_index_kernel, dim3(blocks_for(TJ)), dim3(256), 0, s, envs, tr.done, (int)J, d.N, d.T, w.rows, w.keep);
+      hipLaunchKernelGGL(seq_index_kernel, dim3(blocks_for(TJ)), dim3(256), 0, s, envs, tr.done, (int)J, d.N, d.T, w.rows, w.reset, w.hrows);
       LossCommon lc{};
       lc.rows = w.rows; lc.A = d.A; lc.ad = make_small_div(d.A); lc.rows_mb = TJ; lc.inv_B = (float)(1.0 / (double)(TJ * d.A));
       lc.sc = w.sc; lc.adv_stats = &w.sc->adv_sum; lc.normalize = c.normalize_adv; lc.clip_eps = c.clip_eps; lc.ent_coef = c.ent_coef;
@@ -752,14 +524,14 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
       {
         ActorLoss fn{lc, tr.action, tr.logp, tr.adv};
         rc_a = train_net_recurrent<kActions>(RowSrc{tr.obs, d.D, w.rows, d.A, TJ * d.A}, d.T, J, d.A, d.D, d.Ha, rec.ha0, envs,
-                                             eff, oa, eff + pm.wh_op[0], eff + pm.wht_op[0], w.grad, ga, fn, w.net[0], w.keep,
-                                             w.sc, s);
+                                             eff, oa, eff + pm.wh_fwd[0], eff + pm.wh_bwd[0], w.grad, ga, fn, w.net[0], w.reset,
+                                             w.hrows, w.sc, s);
       }
       {
         CriticLoss fn{lc, tr.ret, tr.value, d.central ? d.A : 1};
         const int per = d.central ? 1 : d.A;
         rc_c = train_net_recurrent<1>(RowSrc{tr.obs, d.Dc, w.rows, per, TJ * per}, d.T, J, per, d.Dc, d.Hc, rec.hc0, envs, eff,
-                                      oc, eff + pm.wh_op[1], eff + pm.wht_op[1], w.grad, gc, fn, w.net[1], w.keep, w.sc, s2);
+                                      oc, eff + pm.wh_fwd[1], eff + pm.wh_bwd[1], w.grad, gc, fn, w.net[1], w.reset, w.hrows, w.sc, s2);
       }
       if (s2 != s) {  // join also after an error, so that the caller's stream never runs ahead of work still queued beside it
         if (hipEventRecord(side->join, s2) != hipSuccess || hipStreamWaitEvent(s, side->join, 0) != hipSuccess) {

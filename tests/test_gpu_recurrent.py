@@ -260,3 +260,44 @@ def test_recurrent_full_size(M, orc):
         assert np.all(np.abs(st[:, i] - ostats[:, i]) < 20 * tol * np.maximum(np.abs(ostats[:, i]), 1e-2)), (i, st[:, i], ostats[:, i])
     assert np.all(st[:, 7] == 0)
     assert rel_err(gp.cpu().numpy() - p2, po - p2, floor=1.0) < 0.05
+
+
+# Widths on both sides of every change of kernel (weights in registers up to 128, streamed up to 256, one step at a time
+# above), with sample counts that leave ragged tiles, and both tile heights (32 sequences above 4096 per step).
+@pytest.mark.parametrize("ha,hc,n_envs,T", [(32, 160, 11, 7), (96, 192, 23, 5), (224, 128, 9, 6), (256, 288, 7, 5),
+                                            (320, 64, 10, 4), (64, 96, 1367, 3), (128, 32, 1371, 3), (32, 256, 1366, 3)])
+def test_recurrent_other_widths(M, orc, ha, hc, n_envs, T):
+    from gpu_util import load_traj
+    cfg = dict(W.CONFIGS[1], n_envs=n_envs, rollout_len=T, actor_hidden=ha, critic_hidden=hc, episode_cap=2, n_minibatches=1,
+               n_epochs=1, recurrent=1, max_grad_norm=0.0)
+    print("case", ha, hc, n_envs, T, flush=True)
+    params, _, otr, orec = oracle_rollout(orc, cfg)
+    sizes = M.query_sizes(cfg)
+    gs = M.EnvState(cfg)
+    M.env_reset(cfg, gs)
+    gtr = M.Traj(cfg, debug=True)
+    grec = load_rec(M, cfg, orec)
+    M.rollout_recurrent(cfg, gs, dev(params), gtr, grec, 300, M.alloc_workspace(sizes.rollout_workspace_bytes),
+                        forced_actions=dev(otr.action))
+    tol = REL_TOL[0]
+    assert otr.done[:-1].sum() > 0
+    for name in ("logits", "value", "last_value"):
+        assert err(getattr(gtr, name).cpu().numpy(), getattr(otr, name), cfg) < tol, name
+    assert err(grec.ha1.cpu().numpy(), orec.ha1, cfg) < tol and err(grec.hc1.cpu().numpy(), orec.hc1, cfg) < tol
+    perm = W.make_env_perm(cfg, seed=3)
+    po, mo, vo = params.copy(), np.zeros_like(params), np.zeros_like(params)
+    ostats, ograd = orc.rec_ppo_update(cfg, otr, orec, po, mo, vo, adam_step0=0, perm=perm)
+    gtr = load_traj(M, cfg, otr)
+    gp, gm, gv = dev(params), torch.zeros(params.size, device="cuda"), torch.zeros(params.size, device="cuda")
+    stats, gdump = torch.zeros((1, 8), device="cuda"), torch.zeros(params.size, device="cuda")
+    M.ppo_update_recurrent(cfg, gtr, grec, gp, gm, gv, 0, dev(perm), stats, gdump, M.alloc_workspace(sizes.update_workspace_bytes))
+    torch.cuda.synchronize()
+    g = gdump.cpu().numpy()
+    off = 0
+    for name, shape in W.param_layout(cfg):
+        n = int(np.prod(shape))
+        assert err(g[off:off + n], ograd[off:off + n], cfg) < tol, name
+        off += n
+    st = stats.cpu().numpy()[0]
+    for i in (0, 1, 2, 5, 6):
+        assert abs(st[i] - ostats[0, i]) < tol * max(abs(ostats[0, i]), 1e-2), (i, st[i], ostats[0, i])
