@@ -16,6 +16,7 @@
 // Bound there: a step is a chain of 72 matrix instructions per wavefront, a barrier and the gate arithmetic, about 2 us.
 #pragma once
 #include "gemm.h"
+#include "heads.h"
 
 namespace marl {
 
@@ -24,8 +25,9 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 inline bool gru_seq_supported(int H) { return H % 32 == 0 && H <= 256; }
 inline int64_t gru_weight_floats(int H) { return (((int64_t)H * H * 9 / 2 + 63) / 64) * 64; }  // one staged copy
 
-// The element (k, c) of Wh [H][3H] in the two staged copies: three planes of bf16, in 512-element fragments of 16 units by
+// The element (k, c) of gate weights [H][3H] in the two staged copies: three planes of bf16, in 512-element fragments of 16 units by
 // 32 along the contraction.
+template <bool FWD, bool BWD>
 __device__ __forceinline__ void gru_stage_weight(float v, int k, int c, int H, bf16_t* __restrict__ fwd, bf16_t* __restrict__ bwd) {
   const SplitPair s = split_pair(v, 0.f);
   const uint32_t part[3] = {s.h, s.m, s.l};
@@ -34,8 +36,8 @@ __device__ __forceinline__ void gru_stage_weight(float v, int k, int c, int H, b
   const int64_t b = ((int64_t)((k / 16) * 3 * KS + g * KS + u / 32) * 3) * 512 + ((k % 16) + 16 * ((u % 32) / 8)) * 8 + u % 8;
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
-    fwd[f + 512 * p] = (bf16_t)part[p];
-    bwd[b + 512 * p] = (bf16_t)part[p];
+    if (FWD) fwd[f + 512 * p] = (bf16_t)part[p];
+    if (BWD) bwd[b + 512 * p] = (bf16_t)part[p];
   }
 }
 
@@ -51,8 +53,8 @@ struct GruFwdArgs {
   const float* h_first;  // [S1][H] state before the first step; may be hs
   float* hs;             // [T][S1][H] state after every step
   float* rec;            // [T][S1][4H], nullable
-  const uint8_t* reset;  // nullable: reset[t * (S1 / per) + s / per] != 0: step t starts from a zero state;
-  int first_reset;       // entries of t = 0 are read only if this is set
+  // Step 0 starts from a zero state where reset0[s / per] is set, step t > 0 where reset[(t - 1) * (S1 / per) + s / per] is.
+  const uint8_t *reset0, *reset;  // reset0 nullable; reset is not read if T = 1
   int per;
   int64_t S1;
   int T;
@@ -119,7 +121,7 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
   int rs[SM];  // does the coming step start from a zero state
   auto load_reset = [&](int t) {
 #pragma unroll
-    for (int m = 0; m < SM; ++m) rs[m] = a.reset != nullptr && (t > 0 || a.first_reset) ? a.reset[t * nenv + env[m]] : 0;
+    for (int m = 0; m < SM; ++m) rs[m] = t > 0 ? a.reset[(t - 1) * nenv + env[m]] : (a.reset0 != nullptr ? a.reset0[env[m]] : 0);
   };
   load_reset(0);
 #pragma unroll
@@ -210,7 +212,7 @@ struct GruBwdArgs {
   const float* dl;       // [T][S1][NOUT] gradient of the outputs
   float* rec;            // [T][S1][4H] records, replaced by gradients
   const float* hs;       // [T][S1][H] state before every step (before a reset)
-  const uint8_t* reset;  // [T][S1 / per], as forward; entries of t = 0 are not read
+  const uint8_t* reset;  // [T - 1][S1 / per], as forward
   int per;
   int64_t S1;
   int T;
@@ -264,7 +266,7 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
     const int64_t row = (int64_t)t * a.S1 + srow[m];
 #pragma unroll
     for (int k = 0; k < NOUT; ++k) dl[m][k] = a.dl[row * NOUT + k];
-    rs[m] = t > 0 ? a.reset[t * nenv + env[m]] : 0;
+    rs[m] = t > 0 ? a.reset[(t - 1) * nenv + env[m]] : 0;
   };
 #pragma unroll
   for (int m = 0; m < SM; ++m) {
@@ -358,6 +360,242 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
   }
 }
 
+// ---- one rollout step of the actor: observation -> hidden state, logits, action ----------------------------------------
+// The whole cell of 16 * SM samples in one workgroup: embedding, both gate products, gates, output layer, sampling.  All
+// weights are streamed from the L2, split and in operand order, RING - 1 contraction steps ahead of their use; the hidden
+// product runs before the barrier that publishes the embedding.  Replaces an embedding product, an input-gate product, a
+// step of the cell and an output-layer kernel, whose intermediate results (5 H floats per sample) went through memory.
+// Bound: the weights' way from the L2 (664 KB per workgroup at 128 units and 75 inputs, 64 bytes per clock: 4.3 us) up to
+// one workgroup per compute unit, the matrix instructions beyond.  Measured: 3072 samples 12.6 us (four kernels: about 90),
+// 65 536 samples 127 us.
+struct GruActorArgs {
+  const float* obs;      // [S][D]
+  const bf16_t* We;      // staged embedding, K1 = D rounded up to 32 rows (gru_stage_embedding)
+  const bf16_t *Wi, *Wh; // staged gate weights
+  const float *be, *bi, *bh, *W3, *b3;
+  const float* h_in;     // [S][H]
+  float* h_out;          // [S][H], may be h_in
+  const uint8_t* reset;  // nullable [S / per]
+  int per;
+  int64_t S;
+  int D;
+  float* logits;         // nullable [S][6]
+  SampleArgs sample;
+};
+inline int64_t gru_embedding_floats(int D, int H) { return (int64_t)((D + 31) / 32 * 32) * H * 3 / 2; }
+
+// element (k, u) of the embedding [D][H], zeros for D <= k
+__device__ __forceinline__ void gru_stage_embedding(float v, int k, int u, int K1, bf16_t* __restrict__ dst) {
+  const SplitPair s = split_pair(v, 0.f);
+  const uint32_t part[3] = {s.h, s.m, s.l};
+  const int64_t f = ((int64_t)(u / 16) * (K1 / 32) + k / 32) * 3 * 512 + ((u % 16) + 16 * ((k % 32) / 8)) * 8 + k % 8;
+#pragma unroll
+  for (int p = 0; p < 3; ++p) dst[f + 512 * p] = (bf16_t)part[p];
+}
+
+template <int KS, int SM>
+__global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_step_kernel(GruActorArgs a) {
+  constexpr int H = 32 * KS, UB = KS <= 4 ? 1 : 2, MT = 16 * SM, P = H + 8, PLANE = MT * P, NOUT = kActions;
+  constexpr int THREADS = KS <= 4 ? 128 * KS : 64 * KS, WAVES = THREADS / 64;
+  constexpr int PX = 160 + 8, XPLANE = MT * PX;  // up to 147 inputs
+  static_assert(THREADS >= 2 * MT, "one thread per sample and Philox call");
+  __shared__ __attribute__((aligned(16))) bf16_t Hs[3 * PLANE];
+  __shared__ __attribute__((aligned(16))) bf16_t Xs[3 * XPLANE];  // inputs
+  __shared__ __attribute__((aligned(16))) bf16_t Es[3 * PLANE];   // embedding
+  __shared__ __attribute__((aligned(16))) float bias[5][H];  // embedding; r and z: both biases; n: input, hidden
+  __shared__ __attribute__((aligned(16))) float W3s[H * NOUT];
+  __shared__ float red[WAVES][MT][NOUT];
+  __shared__ float noise[MT][8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
+  const int64_t s0 = (int64_t)blockIdx.x * MT;
+  const int rows = (int)min((int64_t)MT, a.S - s0);
+  const int K1 = (a.D + 31) / 32 * 32, KS1 = K1 / 32;
+
+  constexpr int NI = UB * KS, RING = SM == 1 ? 4 : 2;
+  const WeightRsrc rs_e = weight_rsrc(reinterpret_cast<const float*>(a.We), K1 * H * 3 / 2);
+  const WeightRsrc rs_h = weight_rsrc(reinterpret_cast<const float*>(a.Wh), H * H * 9 / 2);
+  const WeightRsrc rs_i = weight_rsrc(reinterpret_cast<const float*>(a.Wi), H * H * 9 / 2);
+  const int woff = UB * wave * KS * 9 * 1024 + lane * 16;
+  bf16x8 w[RING][9];
+  auto load_w = [&](int i) {  // i < NI: hidden-to-hidden, then input-to-hidden
+#pragma unroll
+    for (int f = 0; f < 9; ++f)
+      w[i % RING][f] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(i < NI ? rs_h : rs_i, woff, ((i % NI) * 9 + f) * 1024, 0));
+  };
+
+  int64_t srow[SM];
+  bool live[SM];
+  int unit[UB];
+  float4 h[UB][SM];
+#pragma unroll
+  for (int b = 0; b < UB; ++b) unit[b] = 16 * (UB * wave + b) + 4 * q;
+#pragma unroll
+  for (int m = 0; m < SM; ++m) {
+    live[m] = s0 + 16 * m + lo < a.S;
+    srow[m] = live[m] ? s0 + 16 * m + lo : a.S - 1;
+    const bool zero = a.reset != nullptr && a.reset[srow[m] / a.per];
+#pragma unroll
+    for (int b = 0; b < UB; ++b) {
+      h[b][m] = *reinterpret_cast<const float4*>(a.h_in + srow[m] * H + unit[b]);
+      if (zero) h[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  for (int i = tid; i < MT * (K1 / 2); i += THREADS) {  // two columns of a row; zeros past the ends
+    const int r = i / (K1 / 2), c = 2 * (i - r * (K1 / 2));
+    const float* const src = a.obs + (s0 + r) * a.D + c;
+    const SplitPair v = split_pair(r < rows && c < a.D ? src[0] : 0.f, r < rows && c + 1 < a.D ? src[1] : 0.f);
+    bf16_t* const dst = Xs + r * PX + c;
+    *reinterpret_cast<uint32_t*>(dst) = v.h;
+    *reinterpret_cast<uint32_t*>(dst + XPLANE) = v.m;
+    *reinterpret_cast<uint32_t*>(dst + 2 * XPLANE) = v.l;
+  }
+  for (int j = tid; j < H; j += THREADS) {
+    bias[0][j] = a.be[j];
+    bias[1][j] = a.bi[j] + a.bh[j];
+    bias[2][j] = a.bi[H + j] + a.bh[H + j];
+    bias[3][j] = a.bi[2 * H + j];
+    bias[4][j] = a.bh[2 * H + j];
+  }
+  for (int j = tid; j < H * NOUT; j += THREADS) W3s[j] = a.W3[j];
+  const SampleArgs& sa = a.sample;
+  if (tid < 2 * MT && (tid >> 1) < rows) {  // log(-log u) of sample tid / 2, Philox call tid % 2 (see sample_uniforms)
+    const int64_t s = s0 + (tid >> 1);
+    const int call = tid & 1;
+    float u[4];
+    if (sa.uniforms) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u[k] = 4 * call + k < NOUT ? sa.uniforms[s * NOUT + 4 * call + k] : 0.5f;
+    } else {
+      const uint64_t step = sa.step + (sa.step_base != nullptr ? *sa.step_base : 0);
+      uint32_t o[4];
+      philox4x32_10((uint32_t)step, (uint32_t)(step >> 32), (uint32_t)s * 2u + (uint32_t)call, kStreamSample, sa.k0, sa.k1, o);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u[k] = rand_unit(o[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) noise[tid >> 1][4 * call + k] = logf(-logf(u[k]));
+  }
+#pragma unroll
+  for (int b = 0; b < UB; ++b)
+#pragma unroll
+    for (int m = 0; m < SM; ++m) store_split4(&Hs[(16 * m + lo) * P + unit[b]], PLANE, h[b][m]);
+#pragma unroll
+  for (int i = 0; i < RING - 1; ++i) load_w(i);
+  __syncthreads();
+
+  // ---- embedding
+#pragma unroll
+  for (int b = 0; b < UB; ++b) {
+    floatx4 acc[SM];
+#pragma unroll
+    for (int m = 0; m < SM; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int eoff = (UB * wave + b) * KS1 * 3 * 1024 + lane * 16;
+#pragma unroll 1
+    for (int ks = 0; ks < KS1; ++ks) {
+      bf16x8 e[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) e[p] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs_e, eoff, (ks * 3 + p) * 1024, 0));
+#pragma unroll
+      for (int m = 0; m < SM; ++m) {
+        const Split8 x = frag_row(Xs + (16 * m + lo) * PX + 32 * ks + 8 * q, XPLANE);
+        acc[m] = mfma16(e[2], x.h, acc[m]);
+        acc[m] = mfma16(e[0], x.l, acc[m]);
+        acc[m] = mfma16(e[1], x.m, acc[m]);
+        acc[m] = mfma16(e[1], x.h, acc[m]);
+        acc[m] = mfma16(e[0], x.m, acc[m]);
+        acc[m] = mfma16(e[0], x.h, acc[m]);
+      }
+    }
+    const float4 bs = *reinterpret_cast<const float4*>(&bias[0][unit[b]]);
+#pragma unroll
+    for (int m = 0; m < SM; ++m)
+      store_split4(&Es[(16 * m + lo) * P + unit[b]], PLANE,
+                   make_float4(tanh_f32(acc[m][0] + bs.x), tanh_f32(acc[m][1] + bs.y), tanh_f32(acc[m][2] + bs.z), tanh_f32(acc[m][3] + bs.w)));
+  }
+  // ---- gates: r and z of both products in one accumulator, n of the hidden and of the input product
+  floatx4 acc[UB][4][SM];
+#pragma unroll
+  for (int b = 0; b < UB; ++b)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int m = 0; m < SM; ++m) acc[b][g][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 2 * NI; ++i) {
+    const int b = (i % NI) / KS, ks = i % KS;
+    if (i + RING - 1 < 2 * NI) load_w(i + RING - 1);
+    if (i == NI) lds_barrier();  // the embedding is complete
+    Split8 x[SM];
+#pragma unroll
+    for (int m = 0; m < SM; ++m) x[m] = frag_row((i < NI ? Hs : Es) + (16 * m + lo) * P + 32 * ks + 8 * q, PLANE);
+#define MARL_GRU_PRODUCT(WP, XP)            \
+  _Pragma("unroll") for (int g = 0; g < 3; ++g) \
+  _Pragma("unroll") for (int m = 0; m < SM; ++m) acc[b][g == 2 && i >= NI ? 3 : g][m] = mfma16(w[i % RING][3 * g + WP], x[m].XP, acc[b][g == 2 && i >= NI ? 3 : g][m]);
+    MARL_GRU_PRODUCT(2, h)
+    MARL_GRU_PRODUCT(0, l)
+    MARL_GRU_PRODUCT(1, m)
+    MARL_GRU_PRODUCT(1, h)
+    MARL_GRU_PRODUCT(0, m)
+    MARL_GRU_PRODUCT(0, h)
+#undef MARL_GRU_PRODUCT
+  }
+  float part[SM][NOUT];
+#pragma unroll
+  for (int m = 0; m < SM; ++m)
+#pragma unroll
+    for (int k = 0; k < NOUT; ++k) part[m][k] = 0.f;
+#pragma unroll
+  for (int b = 0; b < UB; ++b) {
+#pragma unroll
+    for (int m = 0; m < SM; ++m) {
+      float out[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float hv = e == 0 ? h[b][m].x : e == 1 ? h[b][m].y : e == 2 ? h[b][m].z : h[b][m].w;
+        const float r = sigmoid_f32(acc[b][0][m][e] + bias[1][unit[b] + e]);
+        const float z = sigmoid_f32(acc[b][1][m][e] + bias[2][unit[b] + e]);
+        const float n = tanh_f32((acc[b][3][m][e] + bias[3][unit[b] + e]) + r * (acc[b][2][m][e] + bias[4][unit[b] + e]));
+        out[e] = (1.0f - z) * n + z * hv;
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) part[m][k] = fmaf(out[e], W3s[(unit[b] + e) * NOUT + k], part[m][k]);
+      }
+      if (live[m]) *reinterpret_cast<float4*>(a.h_out + srow[m] * H + unit[b]) = make_float4(out[0], out[1], out[2], out[3]);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < SM; ++m)
+#pragma unroll
+    for (int k = 0; k < NOUT; ++k) {  // the four lanes of a sample in this wavefront
+      float v = part[m][k];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (q == 0) red[wave][16 * m + lo][k] = v;
+    }
+  lds_barrier();
+  if (tid < rows) {
+    const int64_t s = s0 + tid;
+    float lg[NOUT], best = -INFINITY;
+    int act = 0;
+#pragma unroll
+    for (int k = 0; k < NOUT; ++k) {
+      float v = a.b3[k];
+#pragma unroll
+      for (int u = 0; u < WAVES; ++u) v += red[u][tid][k];
+      lg[k] = v;
+      if (a.logits != nullptr) a.logits[s * NOUT + k] = v;
+      const float z = v - noise[tid][k];  // Gumbel-max, lowest index on exact ties
+      if (z > best) {
+        best = z;
+        act = k;
+      }
+    }
+    if (sa.sampled) sa.sampled[s] = act;
+    if (sa.forced) act = sa.forced[s];
+    sa.action[s] = act;
+    sa.logp[s] = log_softmax_at(lg, act);
+  }
+}
+
 // 16 sequences per workgroup while that leaves compute units idle, 32 (the same weights for twice the work) beyond.
 inline int gru_seq_tiles16(int64_t S1) { return S1 <= 256 * 16; }
 
@@ -367,6 +605,12 @@ inline void launch_gru_fwd_ks(const GruFwdArgs& a, hipStream_t s) {
   const dim3 block(RES ? 128 * KS : 64 * KS);
   if (gru_seq_tiles16(a.S1)) hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 1, RES>), dim3((unsigned)((a.S1 + 15) / 16)), block, 0, s, a);
   else hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 2, RES>), dim3((unsigned)((a.S1 + 31) / 32)), block, 0, s, a);
+}
+template <int KS>
+inline void launch_gru_actor_ks(const GruActorArgs& a, hipStream_t s) {
+  const dim3 block(KS <= 4 ? 128 * KS : 64 * KS);
+  if (gru_seq_tiles16(a.S)) hipLaunchKernelGGL((gru_actor_step_kernel<KS, 1>), dim3((unsigned)((a.S + 15) / 16)), block, 0, s, a);
+  else hipLaunchKernelGGL((gru_actor_step_kernel<KS, 2>), dim3((unsigned)((a.S + 31) / 32)), block, 0, s, a);
 }
 template <int KS, int NOUT>
 inline void launch_gru_bwd_ks(const GruBwdArgs& a, hipStream_t s) {

@@ -89,14 +89,9 @@ __global__ void rec_stage_params_kernel(const float* __restrict__ src, float* __
     const int net = b == 12, H = pm.hidden[net];
     if (H <= 256) {
       const int k = (int)(e / (3 * H)), c = (int)(e - (int64_t)k * (3 * H));
-      gru_stage_weight(v, k, c, H, reinterpret_cast<bf16_t*>(dst + pm.wh_fwd[net]), reinterpret_cast<bf16_t*>(dst + pm.wh_bwd[net]));
+      gru_stage_weight<true, true>(v, k, c, H, reinterpret_cast<bf16_t*>(dst + pm.wh_fwd[net]), reinterpret_cast<bf16_t*>(dst + pm.wh_bwd[net]));
     }
   }
-}
-
-__global__ void copy_f32_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = src[i];
 }
 
 // dst[s][j] = src[s][j], 0 where reset[s / per] (nullable) is set.  dst may be src.
@@ -235,7 +230,7 @@ void gru_forward(const GruFwdArgs& a, int H, const float* eff, const RecOffsets&
     }
   }
   for (int t = 0; t < a.T; ++t) {
-    const uint8_t* const reset = a.reset != nullptr && (t > 0 || a.first_reset) ? a.reset + (int64_t)t * (a.S1 / a.per) : nullptr;
+    const uint8_t* const reset = t > 0 ? a.reset + (int64_t)(t - 1) * (a.S1 / a.per) : a.reset0;
     hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(a.S1 * H)), dim3(256), 0, s, t > 0 ? a.hs + (int64_t)(t - 1) * a.S1 * H : a.h_first,
                        hm, reset, a.S1 * H, H, a.per);
     hidden_gates(hm, a.S1, H, eff, o, GhT, s);
@@ -266,8 +261,8 @@ void gru_backward(const GruBwdArgs& a, int H, const float* eff, const RecOffsets
     float* const rec = a.rec + (int64_t)t * a.S1 * 4 * H;
     const bool last = t == a.T - 1;
     hipLaunchKernelGGL(gru_backward_kernel<NOUT>, dim3(blocks_for(a.S1 * H)), dim3(256), 0, s,
-                       last ? (const float*)nullptr : dhp + (int64_t)((t + 1) & 1) * a.S1 * H, last ? (const uint8_t*)nullptr : a.reset + (t + 1) * J,
-                       a.dl + (int64_t)t * a.S1 * NOUT, a.W3, rec, a.hs + (int64_t)t * a.S1 * H, t > 0 ? a.reset + t * J : (const uint8_t*)nullptr,
+                       last ? (const float*)nullptr : dhp + (int64_t)((t + 1) & 1) * a.S1 * H, last ? (const uint8_t*)nullptr : a.reset + t * J,
+                       a.dl + (int64_t)t * a.S1 * NOUT, a.W3, rec, a.hs + (int64_t)t * a.S1 * H, t > 0 ? a.reset + (t - 1) * J : (const uint8_t*)nullptr,
                        out, a.per, a.S1, H);
     if (t == 0) break;
     // dL/dhprev += dgh Wh^T: the columns of r and z, then the one of the new gate, which the records hold first
@@ -282,13 +277,21 @@ void gru_backward(const GruBwdArgs& a, int H, const float* eff, const RecOffsets
 
 // ---- rollout ---------------------------------------------------------------------------------------------
 
+// The critic's values do not steer the rollout: it runs over the stored observations afterwards, this many steps at a time
+// (as many as keep a chunk's intermediate results at 131 072 samples).
+int64_t rec_critic_steps(const Dims& d) {
+  const int64_t Sc = d.central ? d.N : d.NA;
+  return std::max<int64_t>(1, std::min<int64_t>(d.T + 1, 131072 / Sc));
+}
+
 struct RecRolloutWs {
-  float *eff, *ha, *hc, *hc_tmp, *hm, *E, *Gi, *Gh;
+  float *eff, *we, *wi, *ha, *hm, *E, *Gi, *Gh, *Hs;
 };
 RecRolloutWs carve_rec_rollout(const marl_config& c, void* ws, int64_t* total) {
   const Dims d = dims_of(c);
-  const int64_t Sc = d.central ? d.N : d.NA;
-  const int64_t Hm = std::max(d.Ha, d.Hc), Sm = d.NA;
+  const int64_t Sc = d.central ? d.N : d.NA, chunk = rec_critic_steps(d) * Sc;
+  const bool fused_actor = gru_seq_supported(d.Ha), stepped_critic = !gru_seq_supported(d.Hc);
+  const int64_t one_a = fused_actor ? 0 : d.NA * d.Ha, one_c = stepped_critic ? Sc * d.Hc : 0;  // one step's buffers
   char* p = static_cast<char*>(ws);
   int64_t off = 0;
   auto take = [&](int64_t bytes) {
@@ -298,25 +301,43 @@ RecRolloutWs carve_rec_rollout(const marl_config& c, void* ws, int64_t* total) {
   };
   RecRolloutWs w;
   w.eff = take(rec_param_map(d).total * 4);
+  w.we = take(fused_actor ? gru_embedding_floats(d.D, d.Ha) * 4 : 0);
+  w.wi = take(fused_actor ? gru_weight_floats(d.Ha) * 4 : 0);
   w.ha = take(d.NA * d.Ha * 4);
-  w.hc = take(Sc * d.Hc * 4);
-  w.hc_tmp = take(Sc * d.Hc * 4);
-  w.hm = take(Sm * Hm * 4);
-  w.E = take(Sm * Hm * 4);
-  w.Gi = take(Sm * 3 * Hm * 4);
-  w.Gh = take(Sm * 3 * Hm * 4);
+  w.hm = take(std::max(one_a, one_c) * 4);
+  w.Gh = take(3 * std::max(one_a, one_c) * 4);
+  w.E = take(std::max(one_a, chunk * d.Hc) * 4);
+  w.Gi = take(3 * std::max(one_a, chunk * d.Hc) * 4);
+  w.Hs = take(chunk * d.Hc * 4);
   if (total) *total = off;
   return w;
 }
 
-// One step of one recurrent network on S samples: hidden state h_in -> h_out (may alias); reset (nullable) as in GruFwdArgs.
-void rec_cell_step(const RowSrc& X, int64_t S, int Din, int H, const float* eff, const RecOffsets& o, const float* wh_fwd,
-                   const float* h_in, float* h_out, const uint8_t* reset, int per, const RecRolloutWs& w, hipStream_t s) {
-  embed_and_input_gates(X, S, Din, H, eff, o, w.E, w.Gi, s);
-  GruFwdArgs a{};
-  a.Gi = w.Gi; a.W = reinterpret_cast<const bf16_t*>(wh_fwd); a.bi = eff + o.bi; a.bh = eff + o.bh;
-  a.h_first = h_in; a.hs = h_out; a.reset = reset; a.first_reset = 1; a.per = per; a.S1 = S; a.T = 1;
-  gru_forward(a, H, eff, o, w.Gh, w.hm, s);
+// The actor's embedding [D][H] and input-gate weights [H][3H] for gru_actor_step_kernel.
+__global__ void rec_stage_actor_kernel(const float* __restrict__ We, const float* __restrict__ Wi, int D, int K1, int H,
+                                       bf16_t* __restrict__ we, bf16_t* __restrict__ wi) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < K1 * H) {
+    const int k = i / H, u = i - k * H;
+    gru_stage_embedding(k < D ? We[k * H + u] : 0.f, k, u, K1, we);
+  } else if (i < K1 * H + 3 * H * H) {
+    const int e = i - K1 * H, k = e / (3 * H);
+    gru_stage_weight<true, false>(Wi[e], k, e - k * 3 * H, H, wi, nullptr);
+  }
+}
+
+void launch_actor_step(const GruActorArgs& a, int H, hipStream_t s) {
+  TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)a.S * H * ((double)a.D + 6.0 * H), s);
+  switch (H / 32) {
+    case 1: return launch_gru_actor_ks<1>(a, s);
+    case 2: return launch_gru_actor_ks<2>(a, s);
+    case 3: return launch_gru_actor_ks<3>(a, s);
+    case 4: return launch_gru_actor_ks<4>(a, s);
+    case 5: return launch_gru_actor_ks<5>(a, s);
+    case 6: return launch_gru_actor_ks<6>(a, s);
+    case 7: return launch_gru_actor_ks<7>(a, s);
+    default: return launch_gru_actor_ks<8>(a, s);
+  }
 }
 
 }  // namespace
@@ -338,13 +359,19 @@ int32_t launch_rollout_recurrent(const marl_config& c, marl_env_state st, const 
   const int64_t NA = d.NA, slab = NA * d.D;
   const int64_t Sc = d.central ? d.N : NA;
   const int per_c = d.central ? 1 : d.A;
-  hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(NA * d.Ha)), dim3(256), 0, s, rec.ha0, w.ha, NA * d.Ha);
-  hipLaunchKernelGGL(copy_f32_kernel, dim3(blocks_for(Sc * d.Hc)), dim3(256), 0, s, rec.hc0, w.hc, Sc * d.Hc);
+  const bool fused_actor = gru_seq_supported(d.Ha);
+  if (fused_actor) {
+    const int K1 = (d.D + 31) / 32 * 32;
+    hipLaunchKernelGGL(rec_stage_actor_kernel, dim3(blocks_for((int64_t)K1 * d.Ha + 3 * (int64_t)d.Ha * d.Ha)), dim3(256), 0, s, eff + oa.We,
+                       eff + oa.Wi, d.D, K1, d.Ha, reinterpret_cast<bf16_t*>(w.we), reinterpret_cast<bf16_t*>(w.wi));
+  }
   int32_t rc = launch_env_step(c, st, nullptr, tr.obs, nullptr, nullptr, /*do_step=*/false, s);
   if (rc != MARL_OK) return rc;
   for (int t = 0; t < d.T; ++t) {
     const uint8_t* ended = t > 0 ? tr.done + (int64_t)(t - 1) * d.N : (const uint8_t*)nullptr;  // a new episode starts from the zero state
     const float* obs_t = tr.obs + (int64_t)t * slab;
+    const float* h_in = t > 0 ? w.ha : rec.ha0;
+    float* const logits = tr.logits ? tr.logits + (int64_t)t * NA * kActions : (float*)nullptr;
     SampleArgs a{};
     a.uniforms = forced_uniforms ? forced_uniforms + (int64_t)t * NA * kActions : nullptr;
     a.forced = forced_actions ? forced_actions + (int64_t)t * NA : nullptr;
@@ -354,21 +381,47 @@ int32_t launch_rollout_recurrent(const marl_config& c, marl_env_state st, const 
     a.step = step_offset + (uint64_t)t;
     a.k0 = (uint32_t)(c.seed & 0xffffffffu);
     a.k1 = (uint32_t)(c.seed >> 32);
-    rec_cell_step(RowSrc{obs_t, d.D, nullptr, 1, NA}, NA, d.D, d.Ha, eff, oa, eff + pm.wh_fwd[0], w.ha, w.ha, ended, d.A, w, s);
-    launch_actor_head_rollout(w.ha, NA, d.Ha, eff + oa.W3, eff + oa.b3,
-                              tr.logits ? tr.logits + (int64_t)t * NA * kActions : (float*)nullptr, &a, s);
-    rec_cell_step(RowSrc{obs_t, d.Dc, nullptr, 1, Sc}, Sc, d.Dc, d.Hc, eff, oc, eff + pm.wh_fwd[1], w.hc, w.hc, ended, per_c, w, s);
-    launch_critic_head_rollout(w.hc, Sc, d.Hc, eff + oc.W3, eff + oc.b3, tr.value + (int64_t)t * NA, d.central ? d.A : 1, s);
+    if (fused_actor) {
+      GruActorArgs g{};
+      g.obs = obs_t; g.We = reinterpret_cast<const bf16_t*>(w.we); g.Wi = reinterpret_cast<const bf16_t*>(w.wi);
+      g.Wh = reinterpret_cast<const bf16_t*>(eff + pm.wh_fwd[0]); g.be = eff + oa.be; g.bi = eff + oa.bi; g.bh = eff + oa.bh;
+      g.W3 = eff + oa.W3; g.b3 = eff + oa.b3; g.h_in = h_in; g.h_out = w.ha; g.reset = ended; g.per = d.A; g.S = NA; g.D = d.D;
+      g.logits = logits; g.sample = a;
+      launch_actor_step(g, d.Ha, s);
+    } else {
+      embed_and_input_gates(RowSrc{obs_t, d.D, nullptr, 1, NA}, NA, d.D, d.Ha, eff, oa, w.E, w.Gi, s);
+      GruFwdArgs g{};
+      g.Gi = w.Gi; g.bi = eff + oa.bi; g.bh = eff + oa.bh; g.h_first = h_in; g.hs = w.ha; g.reset0 = ended; g.per = d.A; g.S1 = NA; g.T = 1;
+      gru_forward(g, d.Ha, eff, oa, w.Gh, w.hm, s);
+      launch_actor_head_rollout(w.ha, NA, d.Ha, eff + oa.W3, eff + oa.b3, logits, &a, s);
+    }
     rc = launch_env_step(c, st, a.action, tr.obs + (int64_t)(t + 1) * slab, tr.reward + (int64_t)t * NA,
                          tr.done + (int64_t)t * d.N, true, s);
     if (rc != MARL_OK) return rc;
   }
   const uint8_t* ended = tr.done + (int64_t)(d.T - 1) * d.N;
   hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(NA * d.Ha)), dim3(256), 0, s, w.ha, rec.ha1, ended, NA * d.Ha, d.Ha, d.A);
-  hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(Sc * d.Hc)), dim3(256), 0, s, w.hc, rec.hc1, ended, Sc * d.Hc, d.Hc, per_c);
-  // bootstrap value of the post-rollout observation; the hidden state of the next rollout stays as it is
-  rec_cell_step(RowSrc{tr.obs + (int64_t)d.T * slab, d.Dc, nullptr, 1, Sc}, Sc, d.Dc, d.Hc, eff, oc, eff + pm.wh_fwd[1], rec.hc1, w.hc_tmp, nullptr, per_c, w, s);
-  launch_critic_head_rollout(w.hc_tmp, Sc, d.Hc, eff + oc.W3, eff + oc.b3, tr.last_value, d.central ? d.A : 1, s);
+  // the critic over the observations of steps 0 .. T; the last is the bootstrap value, and the hidden state of the next
+  // rollout is the one before it
+  const int64_t steps = rec_critic_steps(d);
+  int64_t n_prev = 0;
+  for (int64_t t0 = 0; t0 <= d.T; t0 += steps) {
+    const int64_t n = std::min<int64_t>(steps, d.T + 1 - t0);
+    embed_and_input_gates(RowSrc{tr.obs + t0 * slab, d.Dc, nullptr, 1, n * Sc}, n * Sc, d.Dc, d.Hc, eff, oc, w.E, w.Gi, s);
+    GruFwdArgs g{};
+    g.Gi = w.Gi; g.W = reinterpret_cast<const bf16_t*>(eff + pm.wh_fwd[1]); g.bi = eff + oc.bi; g.bh = eff + oc.bh;
+    g.h_first = t0 > 0 ? w.Hs + (n_prev - 1) * Sc * d.Hc : rec.hc0; g.hs = w.Hs;
+    g.reset0 = t0 > 0 ? tr.done + (t0 - 1) * d.N : (const uint8_t*)nullptr; g.reset = tr.done + t0 * d.N;
+    g.per = per_c; g.S1 = Sc; g.T = (int)n;
+    gru_forward(g, d.Hc, eff, oc, w.Gh, w.hm, s);
+    const int64_t nv = std::min<int64_t>(n, d.T - t0);  // steps with a value of their own
+    if (nv > 0) launch_critic_head_rollout(w.Hs, nv * Sc, d.Hc, eff + oc.W3, eff + oc.b3, tr.value + t0 * NA, d.central ? d.A : 1, s);
+    if (nv < n) launch_critic_head_rollout(w.Hs + nv * Sc * d.Hc, Sc, d.Hc, eff + oc.W3, eff + oc.b3, tr.last_value, d.central ? d.A : 1, s);
+    if (t0 <= d.T - 1 && d.T - 1 < t0 + n)
+      hipLaunchKernelGGL(mask_hidden_kernel, dim3(blocks_for(Sc * d.Hc)), dim3(256), 0, s, w.Hs + (d.T - 1 - t0) * Sc * d.Hc, rec.hc1, ended,
+                         Sc * d.Hc, d.Hc, per_c);
+    n_prev = n;
+  }
   return launch_status();
 }
 
@@ -438,7 +491,7 @@ int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din,
   embed_and_input_gates(X, S, Din, H, eff, o, w.E, w.G, s);
   GruFwdArgs f{};
   f.Gi = w.G; f.W = reinterpret_cast<const bf16_t*>(wh_fwd); f.bi = eff + o.bi; f.bh = eff + o.bh;
-  f.h_first = w.Hs; f.hs = w.Hs + S1 * H; f.rec = w.R; f.reset = reset; f.first_reset = 0; f.per = per; f.S1 = S1; f.T = T;
+  f.h_first = w.Hs; f.hs = w.Hs + S1 * H; f.rec = w.R; f.reset = reset + J; f.per = per; f.S1 = S1; f.T = T;
   gru_forward(f, H, eff, o, w.GhT, w.hm, s);
   {  // output layer, loss, dL/dout, W3 / b3 gradient over all steps
     const unsigned nb = (unsigned)std::min<int64_t>(2048, (S + kHeadTile - 1) / kHeadTile);
@@ -446,7 +499,7 @@ int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din,
                        eff + o.b3, fn, w.dl, grad + go.W3, grad + go.b3, sc, 0.f);
   }
   GruBwdArgs bw{};
-  bw.W = reinterpret_cast<const bf16_t*>(wh_bwd); bw.W3 = eff + o.W3; bw.dl = w.dl; bw.rec = w.R; bw.hs = w.Hs; bw.reset = reset;
+  bw.W = reinterpret_cast<const bf16_t*>(wh_bwd); bw.W3 = eff + o.W3; bw.dl = w.dl; bw.rec = w.R; bw.hs = w.Hs; bw.reset = reset + J;
   bw.per = per; bw.S1 = S1; bw.T = T;
   gru_backward<NOUT>(bw, H, eff, o, w.dHp, s);
   const int64_t tiles_h3 = ((H + 127) / 128) * ((3 * H + 127) / 128);
