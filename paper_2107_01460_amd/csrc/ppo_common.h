@@ -249,101 +249,167 @@ struct CriticLoss {
   }
 };
 
-// Output layer + loss + gradient of the output layer.  Persistent over tiles of 64 samples so that the
-// W3 / b3 gradient and the loss statistics leave each workgroup once.
-template <int NOUT, class LossFn, typename HT>
-__global__ void __launch_bounds__(256) loss_head_kernel(const HT* __restrict__ H2, int64_t S, int H,
-                                                        const float* __restrict__ W3, const float* __restrict__ b3,
-                                                        LossFn fn, float* __restrict__ dl_out,
-                                                        float* __restrict__ gW3, float* __restrict__ gb3,
-                                                        Scalars* sc, float b3_bias_unused) {
-  __shared__ HeadLds L;
-  __shared__ float dls[kHeadTile * NOUT];
-  const int tid = threadIdx.x;
-  const int nchunks = (H + kHeadChunk - 1) / kHeadChunk;  // <= 4
-  float gw[4][NOUT];
-#pragma unroll
-  for (int c = 0; c < 4; ++c)
-#pragma unroll
-    for (int k = 0; k < NOUT; ++k) gw[c][k] = 0.f;
-  float gb[NOUT];
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) gb[k] = 0.f;
-  float st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-  float bias[NOUT];
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) bias[k] = b3[k];
+// Output layer + loss + gradient of the output layer, up to 512 hidden units (a multiple of 32).  Persistent over tiles of
+// 32 samples whose activations sit in LDS at their whole width; a workgroup's share of the W3 / b3 gradient leaves it once,
+// with plain stores, and is added in a fixed order by the launcher.  (With atomics the 2048 workgroups queued up on the same
+// few cache lines: 460 us of the 480 us a launch on 98 304 samples took; 131 us for 1 048 576 now, 537 MB of activations.)
+// Bound: memory and, per tile, a chain of three barriers, which the other workgroup of the compute unit and the next
+// tile's loads, already in flight, cover.
+constexpr int kLossHeadGrid = 512;
+constexpr int kLossTile = 32;
+inline int64_t loss_head_partial_floats(int H, int nout) { return (int64_t)kLossHeadGrid * (H * nout + nout); }
+inline size_t loss_head_lds(int H, int nout) { return sizeof(float) * (kLossTile * (H + 4) + H * nout + 8 * nout * kLossTile + kLossTile * 8); }
 
-  const int64_t ntiles = (S + kHeadTile - 1) / kHeadTile;
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t s0 = tile * kHeadTile;
-    float out[NOUT];
-    head_tile<NOUT>(H2, s0, S, H, W3, L, out);
-    if (tid < kHeadTile) {
-      float dl[NOUT];
+// NQ: 16-byte pieces of a row per staging thread, at least H / 32 (the last piece again beyond that)
+template <int NOUT, int NQ, class LossFn>
+__global__ void __launch_bounds__(256, 2) loss_head_kernel(const float* __restrict__ H2, int64_t S, int H,
+                                                           const float* __restrict__ W3, const float* __restrict__ b3,
+                                                           LossFn fn, float* __restrict__ dl_out, float* __restrict__ partial,
+                                                           Scalars* sc) {
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  const int P = H + 4;
+  float* const tile = lds;                              // [32][P]
+  float* const w3 = tile + kLossTile * P;               // [H][NOUT]
+  float* const red = w3 + H * NOUT;                     // [8][NOUT][32]
+  float* const dls = red + 8 * NOUT * kLossTile;        // [32][8]
+  const int tid = threadIdx.x;
+  const int row = tid >> 3, c0 = 4 * (tid & 7), nq = H / 32;  // staging: row, every eighth 16-byte piece of it
+  const int smp = tid & 31, grp = tid >> 5;                   // output layer: sample, share of the units
+  const int units = H <= 128 ? 128 : 256, parts = 256 / units, part = tid / units;  // W3 gradient: unit tid % units (+ units), share of the samples
+  float gw[2][NOUT], gb[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, bias[NOUT];
 #pragma unroll
-      for (int k = 0; k < NOUT; ++k) dl[k] = 0.f;
-      const int64_t s = s0 + tid;
-      if (s < S) {
+  for (int k = 0; k < NOUT; ++k) {
+    gw[0][k] = gw[1][k] = gb[k] = 0.f;
+    bias[k] = b3[k];
+  }
+  const LossPrep prep = fn.prepare();
+  for (int i = tid; i < H * NOUT; i += 256) w3[i] = W3[i];
+  const int64_t ntiles = (S + kLossTile - 1) / kLossTile;
+  float4 v[NQ];
+  typename LossFn::In in;
+  auto fetch = [&](int64_t t) {
+    const float* const src = H2 + min(t * kLossTile + row, S - 1) * H + c0;  // rows past the end: the last row, with a zero gradient
 #pragma unroll
-        for (int k = 0; k < NOUT; ++k) out[k] += bias[k];
-        fn(s, out, dl, st);
+    for (int q = 0; q < NQ; ++q) v[q] = *reinterpret_cast<const float4*>(src + 32 * min(q, nq - 1));
+    if (tid < kLossTile) in = fn.load(min(t * kLossTile + tid, S - 1));
+  };
+  if (blockIdx.x < ntiles) fetch(blockIdx.x);
+  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const int64_t s0 = t * kLossTile;
 #pragma unroll
-        for (int k = 0; k < NOUT; ++k) {
-          dl_out[s * NOUT + k] = dl[k];
-          gb[k] += dl[k];
+    for (int q = 0; q < NQ; ++q) *reinterpret_cast<float4*>(&tile[row * P + c0 + 32 * min(q, nq - 1)]) = v[q];
+    const typename LossFn::In cur = in;
+    __syncthreads();
+    if (t + gridDim.x < ntiles) fetch(t + gridDim.x);
+    {
+      float acc[NOUT];
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) acc[k] = 0.f;
+      const int per = H / 8;  // a multiple of 4
+#pragma unroll 2
+      for (int i = grp * per; i < (grp + 1) * per; i += 4) {
+        const float4 hv = *reinterpret_cast<const float4*>(&tile[smp * P + i]);
+        const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
+        float wv[4 * NOUT];
+#pragma unroll
+        for (int q = 0; q < NOUT; ++q) {
+          const float4 w = *reinterpret_cast<const float4*>(&w3[i * NOUT + 4 * q]);
+          wv[4 * q] = w.x; wv[4 * q + 1] = w.y; wv[4 * q + 2] = w.z; wv[4 * q + 3] = w.w;
         }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) acc[k] = fmaf(hh[j], wv[j * NOUT + k], acc[k]);
       }
 #pragma unroll
-      for (int k = 0; k < NOUT; ++k) dls[tid * NOUT + k] = dl[k];
+      for (int k = 0; k < NOUT; ++k) red[(grp * NOUT + k) * kLossTile + smp] = acc[k];
     }
     __syncthreads();
-    // gW3[i][k] += sum_s H2[s][i] * dl[s][k]; thread -> hidden unit i = tid % 128 of each chunk, half of the samples
-    const int i = tid & (kHeadChunk - 1), half = tid >> 7;
+    if (tid < kLossTile) {
+      float out[NOUT], dl[NOUT];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (c < nchunks) {
-        const int h0 = c * kHeadChunk, hc = min(kHeadChunk, H - h0);
-        if (nchunks > 1) {  // the tile in LDS holds the last chunk only: stage chunk c again
-          __syncthreads();
-          for (int r = tid >> 6; r < kHeadTile; r += 4) {
-            const int64_t s = s0 + r;
-            for (int cc = tid & 63; cc < hc; cc += 64) L.tile[r * (kHeadChunk + 1) + cc] = s < S ? load_act(H2, s * H + h0 + cc) : 0.f;
-          }
-          __syncthreads();
-        }
-        if (i < hc) {
-          for (int s = half * 32; s < half * 32 + 32; ++s) {
-            const float h = L.tile[s * (kHeadChunk + 1) + i];
+      for (int k = 0; k < NOUT; ++k) {
+        out[k] = bias[k];
+        dl[k] = 0.f;
 #pragma unroll
-            for (int k = 0; k < NOUT; ++k) gw[c][k] = fmaf(h, dls[s * NOUT + k], gw[c][k]);
-          }
+        for (int g = 0; g < 8; ++g) out[k] += red[(g * NOUT + k) * kLossTile + tid];
+      }
+      if (s0 + tid < S) {
+        fn.compute(cur, prep, out, dl, st);
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) dl_out[(s0 + tid) * NOUT + k] = dl[k];
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) dls[tid * 8 + k] = k < NOUT ? dl[k < NOUT ? k : 0] : 0.f;
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) gb[k] += dl[k];
+    }
+    __syncthreads();
+    // gW3[i][k] += sum_s H2[s][i] * dl[s][k]
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int i = tid % units + c * units;
+      if (i < H) {
+        const int n = kLossTile / parts;
+#pragma unroll 4
+        for (int s = part * n; s < (part + 1) * n; ++s) {
+          const float h = tile[s * P + i];
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) gw[c][k] = fmaf(h, dls[s * 8 + k], gw[c][k]);
         }
       }
     }
+    __syncthreads();  // the tile has been read
   }
-  // flush
-  const int i = tid & (kHeadChunk - 1);
+  float* const own = partial + (int64_t)blockIdx.x * (H * NOUT + NOUT);
+  if (parts == 2) {  // H <= 128: the two halves of the samples
+    if (part == 1) {
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
-    if (c < nchunks && c * kHeadChunk + i < H) {
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) atomicAdd(&gW3[(int64_t)(c * kHeadChunk + i) * NOUT + k], gw[c][k]);
+      for (int k = 0; k < NOUT; ++k) tile[(tid - units) * NOUT + k] = gw[0][k];
     }
-  if (tid < kHeadTile) {  // one wavefront: reduce across its lanes, lane 0 adds
+    __syncthreads();
+    if (part == 0) {
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) gw[0][k] += tile[tid * NOUT + k];
+    }
+  }
+  if (part == 0) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      if (tid + c * units < H) {
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) own[(tid + c * units) * NOUT + k] = gw[c][k];
+      }
+  }
+  if (tid < 64) {  // one wavefront: reduce across its lanes (32 of them hold zeros)
 #pragma unroll
     for (int k = 0; k < NOUT; ++k) {
-      float v = gb[k];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if (tid == 0) atomicAdd(&gb3[k], v);
+      float g = gb[k];
+      for (int o = 32; o > 0; o >>= 1) g += __shfl_xor(g, o);
+      if (tid == 0) own[H * NOUT + k] = g;
     }
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      float v = st[k];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if (tid == 0 && v != 0.f) atomicAdd(&sc->acc[k], v);
+      float g = st[k];
+      for (int o = 32; o > 0; o >>= 1) g += __shfl_xor(g, o);
+      if (tid == 0 && g != 0.f) atomicAdd(&sc->acc[k], g);
     }
   }
+}
+
+// gW3: [H][NOUT], the gradient of b3 directly behind it; partial: loss_head_partial_floats
+template <int NOUT, class LossFn>
+inline int32_t launch_loss_head(const float* H2, int64_t S, int H, const float* W3, const float* b3, const LossFn& fn, float* dl,
+                                float* gW3, float* partial, Scalars* sc, hipStream_t s) {
+  auto kern = H <= 128 ? loss_head_kernel<NOUT, 4, LossFn> : H <= 256 ? loss_head_kernel<NOUT, 8, LossFn> : loss_head_kernel<NOUT, 16, LossFn>;
+  const size_t bytes = loss_head_lds(H, NOUT);
+  if (bytes > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+    return MARL_E_LAUNCH;
+  const unsigned nb = (unsigned)std::min<int64_t>(kLossHeadGrid, (S + kLossTile - 1) / kLossTile);
+  hipLaunchKernelGGL(kern, dim3(nb), dim3(256), bytes, s, H2, S, H, W3, b3, fn, dl, partial, sc);
+  launch_reduce_partials(partial, (int)nb, (int64_t)H * NOUT + NOUT, gW3, s);
+  return MARL_OK;
 }
 
 // Squared gradient norm in two fixed-order stages (no atomics, so the clipping factor is the same bits in every run):

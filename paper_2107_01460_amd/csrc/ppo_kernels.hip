@@ -307,7 +307,7 @@ struct UpdateWsView {
   float *h1c, *h2c, *dz1c, *dlc;
   float* partial;  // per-workgroup copies of one network's gradient (two-stage reduction of the fused training kernel)
   float* partial_w1;
-  float* partial_head;  // per-workgroup W3 / b3 gradients of the output-layer kernels (bf16 configuration; register-resident fp32 critic)
+  float* partial_head;  // per-workgroup W3 / b3 gradients of the output-layer kernels 
   float* split_ws;      // fp32 layer-by-layer networks: the k splits of a weight-gradient product, added in a fixed order
   int64_t split_floats;
   // bf16 configuration: one set of activation buffers, used by the actor and then by the critic
@@ -362,7 +362,9 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
     if (!fused_train_supported(d.Ha, d.D)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Ha, d.D));
     if (!fused_train_supported(d.Hc, d.Dc)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Hc, d.Dc));
     v.split_ws = v.split_floats > 0 ? (float*)take(v.split_floats * 4) : nullptr;
-    v.partial_head = (d.Hc == kWregN || d.Ha == kWregN) ? (float*)take((int64_t)kFusedFwdTrainGrid * (kWregN * kActions + kActions) * 4) : nullptr;
+    int64_t head = std::max(loss_head_partial_floats(d.Ha, kActions), loss_head_partial_floats(d.Hc, 1));
+    if (d.Hc == kWregN || d.Ha == kWregN) head = std::max(head, (int64_t)kFusedFwdTrainGrid * (kWregN * kActions + kActions));
+    v.partial_head = (float*)take(head * 4);
   } else {
     const int64_t Sp = round_up64(std::max(Sa, Sc));
     const int64_t Dp = round_up64(std::max(d.D, d.Dc)), H = std::max(d.Ha, d.Hc);
@@ -636,9 +638,9 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
             if (rc != MARL_OK) return rc;
           } else {
             mlp_hidden_forward(Xa, Sa, d.D, d.Ha, eff + oa.W1, eff + oa.b1, eff + oa.W2, eff + oa.b2, w.h1a, w.h2a, d.bf16, s);
-            const unsigned nb = (unsigned)std::min<int64_t>(2048, (Sa + kHeadTile - 1) / kHeadTile);
-            hipLaunchKernelGGL((loss_head_kernel<kActions, ActorLoss, float>), dim3(nb), dim3(256), 0, s, w.h2a, Sa, d.Ha,
-                               eff + oa.W3, eff + oa.b3, fn, w.dla, w.grad + ga.W3, w.grad + ga.b3, sck, 0.f);
+            const int32_t rc = launch_loss_head<kActions>(w.h2a, Sa, d.Ha, eff + oa.W3, eff + oa.b3, fn, w.dla, w.grad + ga.W3,
+                                                          w.partial_head, sck, s);
+            if (rc != MARL_OK) return rc;
           }
           mlp_backward<kActions>(Xa, Sa, d.D, d.Ha, eff + oa.W2, eff + oa.W3, w.h1a, w.h2a, w.dz1a, w.dla, w.grad + ga.W1,
                                  w.grad + ga.b1, w.grad + ga.W2, w.grad + ga.b2, d.bf16, fused_a, nullptr, w.split_ws, w.split_floats, s);
@@ -680,9 +682,9 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
             if (rc != MARL_OK) return rc;
           } else {
             mlp_hidden_forward(Xc, Sc, d.Dc, d.Hc, eff + oc.W1, eff + oc.b1, eff + oc.W2, eff + oc.b2, w.h1c, w.h2c, d.bf16, s);
-            const unsigned nb = (unsigned)std::min<int64_t>(2048, (Sc + kHeadTile - 1) / kHeadTile);
-            hipLaunchKernelGGL((loss_head_kernel<1, CriticLoss, float>), dim3(nb), dim3(256), 0, s, w.h2c, Sc, d.Hc, eff + oc.W3,
-                               eff + oc.b3, fn, w.dlc, w.grad + gc.W3, w.grad + gc.b3, sck, 0.f);
+            const int32_t rc = launch_loss_head<1>(w.h2c, Sc, d.Hc, eff + oc.W3, eff + oc.b3, fn, w.dlc, w.grad + gc.W3,
+                                                   w.partial_head, sck, s);
+            if (rc != MARL_OK) return rc;
           }
           mlp_backward<1>(Xc, Sc, d.Dc, d.Hc, eff + oc.W2, eff + oc.W3, w.h1c, w.h2c, w.dz1c, w.dlc, w.grad + gc.W1,
                           w.grad + gc.b1, w.grad + gc.W2, w.grad + gc.b2, d.bf16, fused_c, w.partial_w1, w.split_ws, w.split_floats, s);

@@ -183,10 +183,22 @@ __global__ void gather_hidden_kernel(const float* __restrict__ h0, const int32_t
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-int64_t k_split(int64_t K, int64_t tiles_mn) {  // about four workgroups per CU, k ranges in multiples of the k tile
-  const int64_t want = std::max<int64_t>(1, 1024 / std::max<int64_t>(1, tiles_mn));
-  const int64_t per = (K + want - 1) / want;
-  return std::max<int64_t>(256, ((per + kGemmBK - 1) / kGemmBK) * kGemmBK);
+// Splits of a weight gradient's sum over the samples: two workgroups per CU, k ranges in multiples of the k tile.  Every
+// split stores its own copy and the copies are added in a fixed order; at 98 304 samples, 128 x 384 outputs: 341 splits
+// adding with atomics 186 us, 170 copies 70 us.
+int64_t split_want(int M, int N) { return std::max<int64_t>(1, 512 / (((M + 127) / 128) * ((N + 127) / 128))); }
+int64_t split_floats(int M, int N) { return split_want(M, N) * ((int64_t)M * N + N); }
+
+// gW [M][N] += A^T B over K samples, the column sums of B (the bias gradient) directly behind it
+void weight_gradient(const RowSrc& A, const float* B, int64_t ldb, int M, int N, int64_t K, int c_rot, float* gW, float* split, hipStream_t s) {
+  GemmArgs g{};
+  g.A = A; g.B = B; g.ldb = ldb; g.C = gW; g.ldc = N; g.c_rot = c_rot;
+  g.M = M; g.N = N; g.K = K; g.colsum = gW + (int64_t)M * N;
+  const int64_t want = split_want(M, N), per = (K + want - 1) / want;
+  g.k_per_split = std::max<int64_t>(256, ((per + kGemmBK - 1) / kGemmBK) * kGemmBK);
+  g.split_out = split; g.split_count = (int64_t)M * N + N;
+  if (launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s))
+    launch_reduce_partials(split, (int)((K + g.k_per_split - 1) / g.k_per_split), g.split_count, gW, s);
 }
 
 const float* stage_params(const Dims& d, const float* params, float* scratch, hipStream_t s) {
@@ -431,7 +443,7 @@ namespace {
 
 // buffers of one network's forward and backward pass over a minibatch
 struct RecNetWs {
-  float *dl, *E, *G, *R, *Hs, *GhT, *hm, *dHp;  // R: records [S][4H]; Hs: states, T + 1 slabs and one row of zeros
+  float *dl, *E, *G, *R, *Hs, *GhT, *hm, *dHp, *partial, *split;  // R: records [S][4H]; Hs: states, T + 1 slabs and one row of zeros
 };
 struct RecUpdateWs {
   float *eff, *grad;
@@ -474,6 +486,8 @@ RecUpdateWs carve_rec_update(const marl_config& c, void* ws, int64_t* total) {
     n.GhT = (float*)take(3 * step * 4);
     n.hm = (float*)take(step * 4);
     n.dHp = (float*)take(2 * step * 4);
+    n.partial = (float*)take(loss_head_partial_floats(H, k == 0 ? kActions : 1) * 4);
+    n.split = (float*)take(std::max(split_floats(H, 3 * H), split_floats(k == 0 ? d.D : d.Dc, H)) * 4);
   }
   if (total) *total = off;
   return w;
@@ -493,43 +507,25 @@ int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din,
   f.Gi = w.G; f.W = reinterpret_cast<const bf16_t*>(wh_fwd); f.bi = eff + o.bi; f.bh = eff + o.bh;
   f.h_first = w.Hs; f.hs = w.Hs + S1 * H; f.rec = w.R; f.reset = reset + J; f.per = per; f.S1 = S1; f.T = T;
   gru_forward(f, H, eff, o, w.GhT, w.hm, s);
-  {  // output layer, loss, dL/dout, W3 / b3 gradient over all steps
-    const unsigned nb = (unsigned)std::min<int64_t>(2048, (S + kHeadTile - 1) / kHeadTile);
-    hipLaunchKernelGGL((loss_head_kernel<NOUT, LossFn, float>), dim3(nb), dim3(256), 0, s, w.Hs + S1 * H, S, H, eff + o.W3,
-                       eff + o.b3, fn, w.dl, grad + go.W3, grad + go.b3, sc, 0.f);
-  }
+  // output layer, loss, dL/dout, W3 / b3 gradient over all steps
+  const int32_t rc = launch_loss_head<NOUT>(w.Hs + S1 * H, S, H, eff + o.W3, eff + o.b3, fn, w.dl, grad + go.W3, w.partial, sc, s);
+  if (rc != MARL_OK) return rc;
   GruBwdArgs bw{};
   bw.W = reinterpret_cast<const bf16_t*>(wh_bwd); bw.W3 = eff + o.W3; bw.dl = w.dl; bw.rec = w.R; bw.hs = w.Hs; bw.reset = reset + J;
   bw.per = per; bw.S1 = S1; bw.T = T;
   gru_backward<NOUT>(bw, H, eff, o, w.dHp, s);
-  const int64_t tiles_h3 = ((H + 127) / 128) * ((3 * H + 127) / 128);
   const float* const dgh = w.R;      // [S][4H], columns n, r, z
   const float* const dgi = w.R + H;  // [S][4H], columns r, z, n
-  {  // gWh += (states the steps start from)^T dGh, gbh += column sums; the new gate's columns go to the end
-    GemmArgs g{};
-    g.A = RowSrc{w.Hs, H, hrows, per, S}; g.B = dgh; g.ldb = 4 * H; g.C = grad + go.Wh; g.ldc = 3 * H; g.c_rot = 2 * H;
-    g.M = H; g.N = 3 * H; g.K = S; g.colsum = grad + go.bh; g.k_per_split = k_split(S, tiles_h3);
-    launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s);
-  }
-  {  // gWi += E^T dGi, gbi += column sums
-    GemmArgs g{};
-    g.A = RowSrc{w.E, H, nullptr, 1, S}; g.B = dgi; g.ldb = 4 * H; g.C = grad + go.Wi; g.ldc = 3 * H;
-    g.M = H; g.N = 3 * H; g.K = S; g.colsum = grad + go.bi; g.k_per_split = k_split(S, tiles_h3);
-    launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s);
-  }
+  // gWh += (states the steps start from)^T dGh, the new gate's columns last; gWi += E^T dGi
+  weight_gradient(RowSrc{w.Hs, H, hrows, per, S}, dgh, 4 * H, H, 3 * H, S, 2 * H, grad + go.Wh, w.split, s);
+  weight_gradient(RowSrc{w.E, H, nullptr, 1, S}, dgi, 4 * H, H, 3 * H, S, 0, grad + go.Wi, w.split, s);
   {  // dE = (dGi Wi^T) * (1 - e^2), in place over e
     GemmArgs g{};
     g.A = RowSrc{dgi, 4 * H, nullptr, 1, S}; g.B = eff + o.Wi; g.ldb = 3 * H; g.C = w.E; g.ldc = H;
     g.aux_mat = w.E; g.ldaux = H; g.M = S; g.N = H; g.K = 3 * H;
     launch_gemm<GEMM_NT, EPI_DTANH>(g, s);
   }
-  {  // gWe += X^T dE, gbe += column sums
-    GemmArgs g{};
-    g.A = X; g.B = w.E; g.ldb = H; g.C = grad + go.We; g.ldc = H;
-    g.M = Din; g.N = H; g.K = S; g.colsum = grad + go.be;
-    g.k_per_split = k_split(S, ((Din + 127) / 128) * ((H + 127) / 128));
-    launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s);
-  }
+  weight_gradient(X, w.E, H, Din, H, S, 0, grad + go.We, w.split, s);
   return MARL_OK;
 }
 
