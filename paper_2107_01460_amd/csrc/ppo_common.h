@@ -285,19 +285,20 @@ __global__ void __launch_bounds__(256, 2) loss_head_kernel(const float* __restri
   const LossPrep prep = fn.prepare();
   for (int i = tid; i < H * NOUT; i += 256) w3[i] = W3[i];
   const int64_t ntiles = (S + kLossTile - 1) / kLossTile;
-  float4 v[NQ];
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  f4 v[NQ];
   typename LossFn::In in;
   auto fetch = [&](int64_t t) {
     const float* const src = H2 + min(t * kLossTile + row, S - 1) * H + c0;  // rows past the end: the last row, with a zero gradient
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) v[q] = *reinterpret_cast<const float4*>(src + 32 * min(q, nq - 1));
+    for (int q = 0; q < NQ; ++q) v[q] = *reinterpret_cast<const f4*>(src + 32 * min(q, nq - 1));
     if (tid < kLossTile) in = fn.load(min(t * kLossTile + tid, S - 1));
   };
   if (blockIdx.x < ntiles) fetch(blockIdx.x);
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const int64_t s0 = t * kLossTile;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) *reinterpret_cast<float4*>(&tile[row * P + c0 + 32 * min(q, nq - 1)]) = v[q];
+    for (int q = 0; q < NQ; ++q) *reinterpret_cast<f4*>(&tile[row * P + c0 + 32 * min(q, nq - 1)]) = v[q];
     const typename LossFn::In cur = in;
     __syncthreads();
     if (t + gridDim.x < ntiles) fetch(t + gridDim.x);
