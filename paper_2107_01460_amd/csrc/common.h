@@ -59,15 +59,21 @@ inline NetOffsets net_offsets(int64_t base, int Din, int H, int Dout) {
 // starts on a 64-float boundary, so that 16-byte loads of weight rows are always aligned.
 struct ParamMap {
   int64_t src[13], dst[13];  // 12 blocks (actor 6, critic 6) + end
-  // After the 12 blocks, per network: W1, W2 and W2 transposed once more in the order the matrix-core kernels
-  // read their B operand straight from memory: element (k, n) of a [K][H] matrix at ((k / 4) * H + n) * 4 + k % 4,
-  // so that the four k values a lane feeds to consecutive MFMAs are one 16-byte load, contiguous across lanes.
-  // W1 is zero-padded to kpad1 rows (a multiple of 16).
+  // After the 12 blocks, per network: W1, W2 and W2 transposed once more for the fused kernels (widths 64, 128, 256), split
+  // into three bf16 parts and in the order the matrix-core kernels read their B operand straight from memory: part p of
+  // element (k, n) of a [K][H] matrix at split_weight_index(k, n, H) + p * split_weight_plane(H), in bf16 elements, so that
+  // the eight k values of a lane are one 16-byte load, contiguous across lanes.  W1 is zero-padded to kpad1 rows (a
+  // multiple of 16).
   int64_t sw_w1[2], sw_w2[2], sw_w2t[2];
+  bool split[2];  // whether the copies are filled (fp32 networks of those widths)
   int din[2], kpad1[2];
   int hidden[2];
   int64_t total;             // floats of the whole working copy
+  int64_t split_extra;       // ... of which the third parts of the split copies (more than fp32 copies would take)
 };
+inline bool split_weights_width(int H) { return H == 64 || H == 128 || H == 256; }
+__host__ __device__ inline int64_t split_weight_index(int64_t k, int64_t n, int64_t H) { return ((k / 16 * 6 + k % 16 / 8) * H + n) * 8 + k % 8; }
+__host__ __device__ inline int64_t split_weight_plane(int64_t H) { return 16 * H; }
 inline ParamMap param_map(const Dims& d) {
   ParamMap m;
   const NetOffsets a = net_offsets(0, d.D, d.Ha, kActions), c = net_offsets(d.Pa, d.Dc, d.Hc, 1);
@@ -82,15 +88,20 @@ inline ParamMap param_map(const Dims& d) {
   m.hidden[1] = d.Hc;
   m.din[0] = d.D;
   m.din[1] = d.Dc;
+  m.split_extra = 0;
   for (int n = 0; n < 2; ++n) {
     const int64_t H = m.hidden[n];
     m.kpad1[n] = (m.din[n] + 15) / 16 * 16;
-    m.sw_w1[n] = off;
-    off += ((m.kpad1[n] * H + 63) / 64) * 64;
-    m.sw_w2[n] = off;
-    off += ((H * H + 63) / 64) * 64;
-    m.sw_w2t[n] = off;
-    off += ((H * H + 63) / 64) * 64;
+    m.split[n] = split_weights_width((int)H) && !d.bf16;
+    auto copy = [&](int64_t floats) {
+      const int64_t at = off, extra = split_weights_width((int)H) ? floats / 2 : 0;
+      off += (floats + extra + 63) / 64 * 64;
+      m.split_extra += extra;
+      return at;
+    };
+    m.sw_w1[n] = copy(m.kpad1[n] * H);
+    m.sw_w2[n] = copy(H * H);
+    m.sw_w2t[n] = copy(H * H);
   }
   m.total = off;
   return m;

@@ -7,7 +7,7 @@
 // Workgroup = 4 wavefronts on a tile of BM samples x H hidden units: (BM/32) x (H/32) MFMA tiles of
 // 32x32, one or two per wavefront; several small workgroups per CU overlap each other's phases.  The row tile of
 // the input sits in LDS at its whole width; the weights go straight from the operand-order copies in global memory
-// (L2-resident) into registers with 16-byte loads (gemm_phase_regs), so a layer has no staging buffer and no barrier
+// (L2-resident) into registers with 16-byte loads (gemm_phase_w_any), so a layer has no staging buffer and no barrier
 // of its own.
 #pragma once
 #include "gemm.h"
@@ -22,7 +22,7 @@ struct FusedFwdArgs {
   int xvec;   // 1: rows are 16-byte aligned and Din % 4 == 0: 16-byte loads of X.  2: rows start at any 4-byte boundary of a
               // buffer whose two ends are 16-byte aligned: a row is fetched as the aligned 16-byte chunks that cover it
   const float *W1, *b1, *W2, *b2, *W3, *b3;  // aligned working copy, W[in][H]
-  const float *W1s, *W2s;  // operand-order copies: (k, n) at ((k / 4) * H + n) * 4 + k % 4; W1s zero-padded to kpad1 rows
+  const float *W1s, *W2s;  // split operand-order copies (ParamMap); W1s zero-padded to kpad1 rows
   int kpad1;               // Din rounded up to a multiple of 16
   int px;                  // pitch of the X tile in LDS: a multiple of 4 with px / 4 odd, >= kpad1
   float* h1_out;   // training: [S][H]
@@ -43,8 +43,10 @@ inline int fused_forward_px(int Din) {
   return px;
 }
 
-template <int H, int BM, int NOUT, bool TRAIN, class Finish>
-__global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, Finish fin) {
+// The kernel's body: workgroup `bid` of `nblk` that share the tiles.  DIRECT: weights from W1 / W2 (unstaged parameters) on
+// the fp32 instruction instead of the split copies.
+template <int H, int BM, int NOUT, bool TRAIN, bool DIRECT, class Finish>
+__device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const Finish& fin, const unsigned bid, const unsigned nblk) {
   constexpr int PH = H + 4, GROUPS = 256 / BM;
   constexpr int NTN = H / 32, MT = BM / 32, TILES = MT * NTN, TPW = TILES / 4;
   static_assert(TILES % 4 == 0 && (TPW == 1 || TPW == 2), "4 wavefronts share the tile evenly");
@@ -66,6 +68,9 @@ __global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, F
   const int lo = lane & 31, hi = lane >> 5;
   const int mt = (wave * TPW) / NTN, nt0 = (wave * TPW) % NTN;  // this wavefront's tiles: (mt, nt0 .. nt0+TPW-1)
 
+  const WeightRsrc rsW1 = split_weight_rsrc(a.W1s, a.kpad1, H), rsW2 = split_weight_rsrc(a.W2s, H, H);
+  const int wlane = (hi * H + nt0 * 32 + lo) * 4;  // this lane's 16 bytes of a group's half `hi` in a split weight copy
+
   // output-layer gradient, persistent over the tiles of this workgroup: thread -> hidden unit tid % H
   constexpr int HPARTS = (256 / H) > 0 ? (256 / H) : 1;  // threads per hidden unit
   constexpr int SPP = BM / HPARTS;        // samples each of them sums per tile
@@ -77,7 +82,7 @@ __global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, F
   for (int i = tid; i < BM * px; i += NTH) L.Xs[i] = 0.f;        // the padding columns stay zero for good
   __syncthreads();
   const int64_t ntiles = (a.S + BM - 1) / BM;
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  for (int64_t tile = bid; tile < ntiles; tile += nblk) {
     const int64_t s0 = tile * BM;
     const int rows_left = (int)min((int64_t)BM, a.S - s0);
     float* const h1_tile = TRAIN ? a.h1_out + s0 * H : nullptr;    // uniform bases: lanes add 32-bit offsets
@@ -143,9 +148,13 @@ __global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, F
     };
     // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS (and HBM when training)
     zero_acc();
+    if (DIRECT) {
 #pragma unroll
-    for (int q = 0; q < TPW; ++q)
-      gemm_phase_regs<H>(L.Xs + (mt * 32 + lo) * px + 4 * hi, a.W1s + (hi * H + (nt0 + q) * 32 + lo) * 4, a.kpad1 / 16, acc[q]);
+      for (int q = 0; q < TPW; ++q)
+        gemm_phase_direct<H>(L.Xs + (mt * 32 + lo) * px + 4 * hi, a.W1 + (nt0 + q) * 32 + lo, a.Din, hi, a.kpad1 / 16, acc[q]);
+    } else {
+      gemm_phase_w_any<H, TPW>(L.Xs + (mt * 32 + lo) * px + 8 * hi, rsW1, wlane, a.kpad1 / 16, acc);
+    }
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
       const int n = (nt0 + q) * 32 + lo;
@@ -162,9 +171,13 @@ __global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, F
     __syncthreads();  // the h1 tile is complete
     // ---- layer 2: h2 = tanh(h1 W2 + b2), kept in registers
     zero_acc();
+    if (DIRECT) {
 #pragma unroll
-    for (int q = 0; q < TPW; ++q)
-      gemm_phase_regs<H>(L.Hs + (mt * 32 + lo) * PH + 4 * hi, a.W2s + (hi * H + (nt0 + q) * 32 + lo) * 4, H / 16, acc[q]);
+      for (int q = 0; q < TPW; ++q)
+        gemm_phase_direct<H>(L.Hs + (mt * 32 + lo) * PH + 4 * hi, a.W2 + (nt0 + q) * 32 + lo, H, hi, H / 16, acc[q]);
+    } else {
+      gemm_phase_w_any<H, TPW>(L.Hs + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, H / 16, acc);
+    }
     __syncthreads();  // every wavefront is past its last read of h1
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
@@ -267,7 +280,7 @@ __global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, F
   }
   if (TRAIN) {
     const int i = tid % H;
-    float* const own = (H == 256 && a.partial3 != nullptr) ? a.partial3 + (int64_t)blockIdx.x * (H * NOUT + NOUT) : nullptr;
+    float* const own = (H == 256 && a.partial3 != nullptr) ? a.partial3 + (int64_t)bid * (H * NOUT + NOUT) : nullptr;
 #pragma unroll
     for (int k = 0; k < NOUT; ++k) {
       if (own != nullptr) own[i * NOUT + k] = gw[k];
@@ -291,6 +304,18 @@ __global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, F
       }
     }
   }
+}
+
+template <int H, int BM, int NOUT, bool TRAIN, class Finish>
+__global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, Finish fin) {
+  fused_forward_body<H, BM, NOUT, TRAIN, false, Finish>(a, fin, blockIdx.x, gridDim.x);
+}
+
+// Both networks of a small call in one launch, with unstaged weights: workgroups 0 .. grid_a - 1 the first.
+template <int HA, int HB, int NOUT_A, int NOUT_B, class FinishA, class FinishB>
+__global__ void __launch_bounds__(256, 2) fused_forward_small_kernel(FusedFwdArgs a, FinishA fa, FusedFwdArgs b, FinishB fb, unsigned grid_a) {
+  if (blockIdx.x < grid_a) fused_forward_body<HA, HA == 64 ? 64 : 32, NOUT_A, false, true, FinishA>(a, fa, blockIdx.x, grid_a);
+  else fused_forward_body<HB, HB == 64 ? 64 : 32, NOUT_B, false, true, FinishB>(b, fb, blockIdx.x - grid_a, gridDim.x - grid_a);
 }
 
 // Which (H, BM) pairs exist: H = 64 -> BM 64; H = 128 or 256 -> BM 32.
@@ -320,6 +345,41 @@ inline int32_t launch_fused_forward_inst(const FusedFwdArgs& a, const Finish& fi
   if (TRAIN && H == 256 && a.partial3 != nullptr && rc == MARL_OK)
     launch_reduce_partials(a.partial3, (int)grid, (int64_t)H * NOUT + NOUT, a.gW3, s);
   return rc;
+}
+
+// Few enough rows that a call is a chain of latencies: one launch on the unstaged parameters (a tile's wavefronts read
+// them once, 4 bytes at a time) against a staging kernel and a launch per network.  One row of 3 agents, 128/128 units:
+// forward and sampling 25 -> 19 us, the same bits.
+constexpr int64_t kForwardSmall = 2048;
+
+template <int HA, int HB, int NOUT_A, int NOUT_B, class FinishA, class FinishB>
+inline int32_t launch_fused_forward_small_inst(const FusedFwdArgs& a, const FinishA& fa, const FusedFwdArgs& b, const FinishB& fb, hipStream_t s) {
+  auto kern = fused_forward_small_kernel<HA, HB, NOUT_A, NOUT_B, FinishA, FinishB>;
+  const size_t bytes = std::max(fused_forward_lds_bytes(HA, a.Din, NOUT_A), fused_forward_lds_bytes(HB, b.Din, NOUT_B));
+  if (bytes > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+    return MARL_E_LAUNCH;
+  const unsigned grid_a = (unsigned)((a.S + (HA == 64 ? 64 : 32) - 1) / (HA == 64 ? 64 : 32));
+  const unsigned grid_b = (unsigned)((b.S + (HB == 64 ? 64 : 32) - 1) / (HB == 64 ? 64 : 32));
+  if (grid_a + grid_b == 0) return MARL_OK;
+  hipLaunchKernelGGL(kern, dim3(grid_a + grid_b), dim3(256), bytes, s, a, fa, b, fb, grid_a);
+  return launch_status();
+}
+// a network with S = 0 is left out
+template <int NOUT_A, int NOUT_B, class FinishA, class FinishB>
+inline int32_t launch_fused_forward_small(int HA, const FusedFwdArgs& a, const FinishA& fa, int HB, const FusedFwdArgs& b, const FinishB& fb, hipStream_t s) {
+  TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)a.S * ((double)a.Din * HA + (double)HA * HA) + 2.0 * (double)b.S * ((double)b.Din * HB + (double)HB * HB), s);
+  switch (HA / 64 * 10 + HB / 64) {
+    case 11: return launch_fused_forward_small_inst<64, 64, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 12: return launch_fused_forward_small_inst<64, 128, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 14: return launch_fused_forward_small_inst<64, 256, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 21: return launch_fused_forward_small_inst<128, 64, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 22: return launch_fused_forward_small_inst<128, 128, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 24: return launch_fused_forward_small_inst<128, 256, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 41: return launch_fused_forward_small_inst<256, 64, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 42: return launch_fused_forward_small_inst<256, 128, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    default: return launch_fused_forward_small_inst<256, 256, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+  }
 }
 
 template <int NOUT, bool TRAIN, class Finish>

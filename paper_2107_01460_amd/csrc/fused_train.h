@@ -6,8 +6,8 @@
 //
 // Workgroup = 8 wavefronts, persistent, one per CU.  Row tile = BM samples (64 at H = 128, 128 at H = 64), so
 // that a layer output is 8 MFMA tiles of 32x32, one per wavefront.  The three products against weights (layer 1,
-// layer 2, dz1) take their A operand from the tile in LDS and their B operand from registers: the weights of a whole
-// product are requested one phase ahead (buffer loads from the operand-order copies, L2-resident; see PhaseW in
+// layer 2, dz1) take their A operand from the tile in LDS and their B operand from registers: the first weights of a
+// product are requested one phase ahead (buffer loads from the split operand-order copies, L2-resident; see PhaseW in
 // gemm.h), so there is no weight staging buffer, no barrier inside a layer and no wait for the L2 inside a product.
 // Per tile:
 //   layer 1 -> h1 (LDS) | layer 2 -> h2 (registers + LDS) |
@@ -19,6 +19,10 @@
 // chunks that cover each row) after layer 2 -- no load is waited for where it is issued, and none sits in front of a
 // load that is.  At the end a workgroup stores its partial gradient into a copy of its own, every sum in a fixed
 // order; reduce_partials_kernel adds the copies.
+// Every product runs on the bf16 instruction with operands split into three parts (split_bf16.h): the weights are staged
+// split, the activations are split in registers on the way from LDS.  Against the fp32 instruction, 1 048 576 samples of
+// 75 inputs, 128 units, 6 outputs: 1522 -> 1104 us; 27 inputs, 64 units: 862 -> 761 us.  Bound: the vector instructions
+// that split (a row tile is split once per column tile) and the chain of phases of one workgroup per CU.
 #pragma once
 #include "gemm.h"
 
@@ -44,7 +48,7 @@ struct FusedTrainArgs {
   int Din;
   int px;  // pitch of the X tile in LDS: multiple of 4, px/4 odd, >= 32*ceil(Din/32)
   const float *W1, *b1, *W2, *b2, *W3, *b3;  // aligned working copy, W[in][H]
-  const float *W1s, *W2s, *W2Ts;             // operand-order copies: (k, n) at ((k / 4) * H + n) * 4 + k % 4; W1s zero-padded to 16-row groups
+  const float *W1s, *W2s, *W2Ts;             // split operand-order copies (ParamMap); W1s zero-padded to 16-row groups
   float *gW1, *gb1, *gW2, *gb2, *gW3, *gb3;  // gradient blocks, accumulated with atomics
   float* stats;                              // 5 floats, atomics
   // Two-stage reduction of the gradient (nullable): the six blocks above are one contiguous range of `gcount` floats
@@ -62,70 +66,34 @@ constexpr size_t fused_train_lds_floats(int H, int BM, int NOUT, int NW, int px,
          (size_t)(BM < 64 ? 64 : BM) * (NOUT + 5);
 }
 
-// acc[q] += A^T B_q over the samples kb0 .. kb0 + klen of a row tile held in LDS: A column block at Ap (pitch pa),
-// B column blocks at Bp + 32 q (pitch pb).  The operands of the next k step are read before the MFMAs of the
-// current one are issued, so the LDS latency hides behind the matrix pipe even with one wavefront per SIMD.
-template <int NB>
+// acc[q] += A_q^T B over the samples kb0 .. kb0 + klen (a multiple of 16) of a row tile held in LDS: the NA column blocks
+// A_q at Ap + 32 q (pitch pa) and the NB column blocks B_q at Bp + 32 q (pitch pb), one of NA, NB being 1.  The values of
+// the next 16 samples are read before the matrix instructions of the current ones are issued.
+template <int NA, int NB>
 __device__ __forceinline__ void outer_product_accumulate(const float* __restrict__ Ap, int pa, const float* __restrict__ Bp,
                                                          int pb, int kb0, int klen, int hi, floatx16* acc) {
-  float af[4], bf[NB][4];
-  auto read = [&](int kb, float (&x)[4], float (&y)[NB][4]) {
+  static_assert(NA == 1 || NB == 1, "one block shared by the others");
+  float af[NA][8], bf[NB][8];
+  auto read = [&](int kb) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      x[j] = Ap[(kb + 4 * hi + j) * pa];
+    for (int j = 0; j < 8; ++j) {
 #pragma unroll
-      for (int q = 0; q < NB; ++q) y[q][j] = Bp[(kb + 4 * hi + j) * pb + 32 * q];
+      for (int q = 0; q < NA; ++q) af[q][j] = Ap[(kb + 8 * hi + j) * pa + 32 * q];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) bf[q][j] = Bp[(kb + 8 * hi + j) * pb + 32 * q];
     }
   };
-  read(kb0, af, bf);
-#pragma unroll 2
-  for (int kb = kb0; kb < kb0 + klen; kb += 8) {
-    float an[4], bn[NB][4];
-    const int kn = kb + 8 < kb0 + klen ? kb + 8 : kb;  // the last step re-reads its own operands
-    read(kn, an, bn);
+  read(kb0);
+#pragma unroll 1
+  for (int kb = kb0; kb < kb0 + klen; kb += 16) {
+    Split8 a[NA], b[NB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int q = 0; q < NA; ++q) a[q] = split8(af[q]);
 #pragma unroll
-      for (int q = 0; q < NB; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], bf[q][j], acc[q], 0, 0, 0);
+    for (int q = 0; q < NB; ++q) b[q] = split8(bf[q]);
+    read(kb + 16 < kb0 + klen ? kb + 16 : kb);  // the last step re-reads its own operands
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      af[j] = an[j];
-#pragma unroll
-      for (int q = 0; q < NB; ++q) bf[q][j] = bn[q][j];
-    }
-  }
-}
-
-// acc[q] += A_q^T B over the samples kb0 .. kb0 + klen: the NA row blocks A_q at Ap + 32 q (pitch pa) share the
-// column block B at Bp (pitch pb).  NA independent accumulation chains keep the matrix pipe fed from one wavefront.
-template <int NA>
-__device__ __forceinline__ void outer_product_accumulate_rows(const float* __restrict__ Ap, int pa, const float* __restrict__ Bp,
-                                                              int pb, int kb0, int klen, int hi, floatx16* acc) {
-  float af[NA][4], bf[4];
-  auto read = [&](int kb, float (&x)[NA][4], float (&y)[4]) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      y[j] = Bp[(kb + 4 * hi + j) * pb];
-#pragma unroll
-      for (int q = 0; q < NA; ++q) x[q][j] = Ap[(kb + 4 * hi + j) * pa + 32 * q];
-    }
-  };
-  read(kb0, af, bf);
-#pragma unroll 2
-  for (int kb = kb0; kb < kb0 + klen; kb += 8) {
-    float an[NA][4], bn[4];
-    const int kn = kb + 8 < kb0 + klen ? kb + 8 : kb;  // the last step re-reads its own operands
-    read(kn, an, bn);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int q = 0; q < NA; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[q][j], bf[j], acc[q], 0, 0, 0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      bf[j] = bn[j];
-#pragma unroll
-      for (int q = 0; q < NA; ++q) af[q][j] = an[q][j];
-    }
+    for (int q = 0; q < NA * NB; ++q) acc[q] = mfma_split(a[NA == 1 ? 0 : q], b[NB == 1 ? 0 : q], acc[q]);
   }
 }
 
@@ -144,7 +112,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   // dW1: wavefront -> (column tile wave % NTN of the gradient, share wave / NTN of the tile's samples); it holds all
   // Q1 row tiles of that column (they share the dz1 operand), Q1 independent accumulation chains
   constexpr int Q1 = DMAX / 32, KS1 = NW / NTN, KLEN1 = BM / KS1;
-  static_assert(NW % NTN == 0 && BM % KS1 == 0 && KLEN1 % 8 == 0, "dW1 sample shares");
+  static_assert(NW % NTN == 0 && BM % KS1 == 0 && KLEN1 % 16 == 0, "dW1 sample shares");
   constexpr int HPARTS = NT / H, SPP = BM / HPARTS;
   constexpr int KG1 = DMAX / 16, KG2 = H / 16;  // k groups of layer 1 (at most) and of the H-deep products
 
@@ -202,7 +170,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   const float bias1 = a.b1[nt * 32 + lo], bias2 = a.b2[nt * 32 + lo];
   const int kpad1 = 16 * ((a.Din + 15) / 16);  // layer 1 contracts over the input width rounded up to a k group (W1 is zero-padded to it)
   const int wlane = (hi * H + nt * 32 + lo) * 4;  // this lane's 16 bytes of k quad `hi` in an operand-order weight copy
-  const WeightRsrc rsW1 = weight_rsrc(a.W1s, kpad1 * H), rsW2 = weight_rsrc(a.W2s, H * H), rsW2T = weight_rsrc(a.W2Ts, H * H);
+  const WeightRsrc rsW1 = split_weight_rsrc(a.W1s, kpad1, H), rsW2 = split_weight_rsrc(a.W2s, H, H), rsW2T = split_weight_rsrc(a.W2Ts, H, H);
 
   // ---- staging helpers.  The inputs of the next tile come in two steps: the gather entries at the top of a
   // tile, the rows themselves half a tile later, so that neither dependent load is ever waited for.
@@ -266,8 +234,8 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     store_tile_inputs(Xs0);
     __syncthreads();
   }
-  PhaseW<KG1> pw1;  // layer 1's weights: the first half requested before dW1 of the tile before (here for the first tile)
-  phase_w_request<H, KG1, 0, KG1 / 2>(pw1, rsW1, wlane, kpad1 / 16);
+  PhaseW<KG1> pw1;  // layer 1's weights: the first of them requested before dW1 of the tile before (here for the first tile)
+  phase_w_request<H, KG1>(pw1, rsW1, wlane, kpad1 / 16);
   for (int it = 0; tile < ntiles; tile += nblk, ++it) {
     const int64_t s0 = tile * BM;
     const bool have_next = tile + nblk < ntiles;
@@ -282,8 +250,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     // ---- layer 1
-    phase_w_request<H, KG1, KG1 / 2, KG1>(pw1, rsW1, wlane, kpad1 / 16);
-    gemm_phase_w<KG1>(Xs + (mt * 32 + lo) * px + 4 * hi, kpad1 / 16, acc, pw1);
+    gemm_phase_w<H, KG1>(Xs + (mt * 32 + lo) * px + 8 * hi, rsW1, wlane, kpad1 / 16, &acc, pw1);
     PhaseW<KG2> pw2;  // layer 2's weights arrive during the tanh epilogue of layer 1
     phase_w_request<H, KG2>(pw2, rsW2, wlane, KG2);
     PHASE_MARK(1);
@@ -302,7 +269,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     PHASE_MARK(2);
     // ---- layer 2
     __syncthreads();  // the h1 tile is complete
-    gemm_phase_w<KG2>(H1 + (mt * 32 + lo) * PH + 4 * hi, KG2, acc, pw2);
+    gemm_phase_w<H, KG2>(H1 + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, KG2, &acc, pw2);
     PHASE_MARK(3);
     fetch_tile_inputs((tile + nblk) * BM);  // lands during the ALU phases and dW2
     floatx16 h2r;  // h2 of this wavefront's tile
@@ -428,13 +395,13 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       const int it = t0 / NTN, jt = t0 % NTN;
       const int ks = (wave * DW2_TPW) / (NTN * NTN);
       constexpr int KLEN = BM / DW2_KS;
-      outer_product_accumulate<DW2_TPW>(H1 + it * 32 + lo, PH, H2 + jt * 32 + lo, PH, ks * KLEN, KLEN, hi, acc2);
+      outer_product_accumulate<1, DW2_TPW>(H1 + it * 32 + lo, PH, H2 + jt * 32 + lo, PH, ks * KLEN, KLEN, hi, acc2);
     }
     PHASE_MARK(9);
     // ---- dz1 = (dz2 W2^T) * (1 - h1^2), in place over h1
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    gemm_phase_w<KG2>(H2 + (mt * 32 + lo) * PH + 4 * hi, KG2, acc, pwz);
+    gemm_phase_w<H, KG2>(H2 + (mt * 32 + lo) * PH + 8 * hi, rsW2T, wlane, KG2, &acc, pwz);
     __syncthreads();  // every wavefront is done reading h1 (dW2) before its tiles are overwritten
     PHASE_MARK(10);
     {
@@ -455,8 +422,8 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     __syncthreads();
     PHASE_MARK(11);
     // ---- dW1 += X^T dz1   (the next tile's layer-1 weights arrive meanwhile)
-    phase_w_request<H, KG1, 0, KG1 / 2>(pw1, rsW1, wlane, kpad1 / 16);
-    outer_product_accumulate_rows<Q1>(Xs + lo, px, H1 + (wave % NTN) * 32 + lo, PH, (wave / NTN) * KLEN1, KLEN1, hi, acc1);
+    phase_w_request<H, KG1>(pw1, rsW1, wlane, kpad1 / 16);
+    outer_product_accumulate<Q1, 1>(Xs + lo, px, H1 + (wave % NTN) * 32 + lo, PH, (wave / NTN) * KLEN1, KLEN1, hi, acc1);
     PHASE_MARK(12);
     __syncthreads();  // the tile buffers are reused by the next row tile
     PHASE_MARK(13);

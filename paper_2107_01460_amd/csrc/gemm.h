@@ -143,112 +143,118 @@ __device__ __forceinline__ float tanh_f32(float x) {
   return 1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f);
 }
 
-// acc += A B for this wavefront's 32x32 tile: A rows in LDS (As points at this lane's row, + 4 * hi), B in global
-// memory in operand order (element (k, n) of the [K][LDB] matrix at ((k / 4) * LDB + n) * 4 + k % 4; Bg points at
-// this lane's 16 bytes of k quad `hi`), `kgroups` groups of 16 along k.  B goes straight from the cache hierarchy
-// into registers with 16-byte loads that are contiguous across the wavefront, one group ahead of its use, so a
-// layer needs no staging buffer and no barrier of its own.  Both operands must be readable (zero-padded) up to
-// 16 * kgroups along k.
-// B of the first two groups may come in already loaded (b00 b01: group 0, b10 b11: group 1; see gemm_phase_prefetch):
-// a phase that follows a barrier or an element-wise epilogue then starts on operands requested before it, instead of
-// waiting an L2 round trip for them.
-struct PhaseB {
-  float4 b00, b01, b10, b11;
-};
-template <int LDB>
-__device__ __forceinline__ PhaseB gemm_phase_prefetch(const float* __restrict__ Bg, int kgroups) {
-  const int g1 = kgroups > 1 ? 1 : 0;
-  PhaseB p;
-  p.b00 = *reinterpret_cast<const float4*>(Bg);
-  p.b01 = *reinterpret_cast<const float4*>(Bg + (int64_t)8 * LDB);
-  p.b10 = *reinterpret_cast<const float4*>(Bg + ((int64_t)16 * g1) * LDB);
-  p.b11 = *reinterpret_cast<const float4*>(Bg + ((int64_t)16 * g1 + 8) * LDB);
-  return p;
-}
-
-template <int LDB, bool PRE = false>
-__device__ __forceinline__ void gemm_phase_regs(const float* __restrict__ As, const float* __restrict__ Bg, int kgroups,
-                                                floatx16& acc, PhaseB pre = PhaseB()) {
-  constexpr int kDepth = 3;  // groups in flight: the one in use and two on their way
-  float4 av[kDepth][2], bv[kDepth][2];
-  auto load = [&](int g, float4 (&a2)[2], float4 (&b2)[2]) {
-    const int gc = g < kgroups ? g : kgroups - 1;  // past the end: re-read the last group
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      a2[u] = *reinterpret_cast<const float4*>(As + 16 * gc + 8 * u);
-      b2[u] = *reinterpret_cast<const float4*>(Bg + ((int64_t)16 * gc + 8 * u) * LDB);
-    }
-  };
-#pragma unroll
-  for (int d = 0; d < kDepth - 1; ++d) load(d, av[d], bv[d]);
-  if (PRE) {
-    bv[0][0] = pre.b00; bv[0][1] = pre.b01; bv[1][0] = pre.b10; bv[1][1] = pre.b11;
-  }
-#pragma unroll 1
-  for (int g0 = 0; g0 < kgroups; g0 += kDepth) {
-#pragma unroll
-    for (int d = 0; d < kDepth; ++d) {
-      const int g = g0 + d;
-      if (g < kgroups) {  // uniform
-        load(g + kDepth - 1, av[(d + kDepth - 1) % kDepth], bv[(d + kDepth - 1) % kDepth]);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const float af[4] = {av[d][u].x, av[d][u].y, av[d][u].z, av[d][u].w};
-          const float bf[4] = {bv[d][u].x, bv[d][u].y, bv[d][u].z, bv[d][u].w};
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], bf[j], acc, 0, 0, 0);
-        }
-      }
-    }
-  }
-}
-
-// All B fragments of one product against weights, for this lane: KG groups of 16 along k, two 16-byte loads each
-// (operand-order copy: element (k, n) at ((k / 4) * LDB + n) * 4 + k % 4; lane_off is this lane's offset
-// (hi * LDB + n) * 4 in floats).  The loads are buffer loads -- a resource descriptor in scalar registers, ONE vector
-// register with the lane's byte offset for all of them, the group's offset as a scalar: as global loads each of them
-// got a 64-bit address register pair of its own, computed outside the tile loop and kept (or spilled) across it.  The whole set is requested one phase AHEAD of the product that uses it -- during the element-wise epilogue
-// or the LDS-only product in front of it -- so that the product never waits for the L2: with two or three groups in
-// flight (gemm_phase_regs) every workgroup of the chip asks the same few cache lines at the same moment and the
-// answers take longer than the 16 matrix instructions that were meant to cover them.
-template <int KG>
+// Products of a row tile against weights: A, the activations, in LDS as fp32 (split into bf16 parts on the way to the
+// instruction), B from a split operand-order copy of the weights (ParamMap) straight from the cache hierarchy into
+// registers, so that a layer needs no staging buffer and no barrier of its own.  The first kPhaseRing groups of 16 along k
+// are requested one phase AHEAD of the product -- during the element-wise epilogue or the LDS-only product in front of it
+// -- and the others as their slots become free, so that the product does not wait for the L2.  The loads are buffer
+// loads: a resource descriptor in scalar registers, ONE vector register with the lane's byte offset for all of them, the
+// group's offset as a scalar (as global loads each of them got a 64-bit address register pair of its own).
+// NT column tiles of 32 side by side share their rows of A.
+constexpr int kPhaseRing = 4;
+template <int KG, int NT = 1>
 struct PhaseW {
-  float4 w[KG][2];
+  static constexpr int RING = KG < kPhaseRing ? KG : kPhaseRing;
+  bf16x8 w[RING][NT][3];
 };
 typedef __amdgpu_buffer_rsrc_t WeightRsrc;
 // descriptor of `floats` floats at p (raw buffer, no swizzle; reads past the end return zero)
 __device__ __forceinline__ WeightRsrc weight_rsrc(const float* p, int floats) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, floats * 4, 0x00020000);
 }
-template <int LDB, int KG, int G0 = 0, int G1 = KG>  // groups G0 .. G1 - 1
-__device__ __forceinline__ void phase_w_request(PhaseW<KG>& pw, WeightRsrc B, int lane_off, int kgroups) {
+// descriptor of a split [K][H] copy
+__device__ __forceinline__ WeightRsrc split_weight_rsrc(const float* p, int K, int H) { return weight_rsrc(p, K * H * 3 / 2); }
+// lane_off: (hi * H + n) * 4 for this lane's column n
+template <int H, int KG, int NT>
+__device__ __forceinline__ void phase_w_load_at(PhaseW<KG, NT>& pw, int slot, WeightRsrc B, int lane_off, int g) {
 #pragma unroll
-  for (int g = G0; g < G1; ++g) {
-    const int gc = g < kgroups ? g : kgroups - 1;  // past the end: the last group again (never used)
+  for (int q = 0; q < NT; ++q)
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      pw.w[g][u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(B, lane_off * 4, (16 * gc + 8 * u) * LDB * 4, 0));
-  }
+    for (int p = 0; p < 3; ++p)
+      pw.w[slot][q][p] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(B, lane_off * 4 + 512 * q, (g * 3 + p) * 32 * H, 0));
 }
-// acc += A B for this wavefront's 32x32 tile: A rows in LDS (As points at this lane's row, + 4 * hi; the fragments of
-// the next group are read before the matrix instructions of the current one), B from pw.
-template <int KG>
-__device__ __forceinline__ void gemm_phase_w(const float* __restrict__ As, int kgroups, floatx16& acc, const PhaseW<KG>& pw) {
-  float4 av[2][2];
-  av[0][0] = *reinterpret_cast<const float4*>(As);
-  av[0][1] = *reinterpret_cast<const float4*>(As + 8);
+template <int H, int KG, int NT>
+__device__ __forceinline__ void phase_w_load(PhaseW<KG, NT>& pw, WeightRsrc B, int lane_off, int g, int kgroups) {
+  phase_w_load_at<H>(pw, g % PhaseW<KG, NT>::RING, B, lane_off, g < kgroups ? g : kgroups - 1);  // past the end: the last group again (never used)
+}
+template <int H, int KG, int NT = 1>
+__device__ __forceinline__ void phase_w_request(PhaseW<KG, NT>& pw, WeightRsrc B, int lane_off, int kgroups) {
+#pragma unroll
+  for (int g = 0; g < PhaseW<KG, NT>::RING; ++g) phase_w_load<H>(pw, B, lane_off, g, kgroups);
+}
+// acc[q] += A B_q for this wavefront's 32x32 tiles: A rows in LDS (As points at this lane's row, + 8 * hi; the values of
+// the next group are read before the matrix instructions of the current one).  Both operands are readable (zero-padded) up
+// to 16 * kgroups along k.
+template <int H, int KG, int NT = 1>
+__device__ __forceinline__ void gemm_phase_w(const float* __restrict__ As, WeightRsrc B, int lane_off, int kgroups, floatx16* acc, PhaseW<KG, NT>& pw) {
+  constexpr int RING = PhaseW<KG, NT>::RING;
+  float4 a0 = *reinterpret_cast<const float4*>(As), a1 = *reinterpret_cast<const float4*>(As + 4);
 #pragma unroll
   for (int g = 0; g < KG; ++g) {
     if (g < kgroups) {  // uniform
+      const Split8 a = split8(a0, a1);
       const int gn = g + 1 < kgroups ? g + 1 : g;
-      av[(g + 1) & 1][0] = *reinterpret_cast<const float4*>(As + 16 * gn);
-      av[(g + 1) & 1][1] = *reinterpret_cast<const float4*>(As + 16 * gn + 8);
+      a0 = *reinterpret_cast<const float4*>(As + 16 * gn);
+      a1 = *reinterpret_cast<const float4*>(As + 16 * gn + 4);
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const float af[4] = {av[g & 1][u].x, av[g & 1][u].y, av[g & 1][u].z, av[g & 1][u].w};
-        const float bf[4] = {pw.w[g][u].x, pw.w[g][u].y, pw.w[g][u].z, pw.w[g][u].w};
+      for (int q = 0; q < NT; ++q) acc[q] = mfma_split(a, Split8{pw.w[g % RING][q][0], pw.w[g % RING][q][1], pw.w[g % RING][q][2]}, acc[q]);
+      if (g + RING < KG) phase_w_load<H>(pw, B, lane_off, g + RING, kgroups);
+    }
+  }
+}
+// The same with a run-time number of groups, no request ahead: the groups in flight are the one in use and two on their way.
+template <int H, int NT>
+__device__ __forceinline__ void gemm_phase_w_any(const float* __restrict__ As, WeightRsrc B, int lane_off, int kgroups, floatx16* acc) {
+  PhaseW<3, NT> pw;
+  phase_w_load<H>(pw, B, lane_off, 0, kgroups);
+  phase_w_load<H>(pw, B, lane_off, 1, kgroups);
+#pragma unroll 1
+  for (int g0 = 0; g0 < kgroups; g0 += 3) {
+    const int rest = kgroups - g0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], bf[j], acc, 0, 0, 0);
+    for (int d = 0; d < 3; ++d) {
+      if (d < rest) {  // uniform
+        phase_w_load_at<H>(pw, (d + 2) % 3, B, lane_off, min(g0 + d + 2, kgroups - 1));
+        const float* const p = As + 16 * (g0 + d);
+        const Split8 a = split8(*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4));
+#pragma unroll
+        for (int q = 0; q < NT; ++q) acc[q] = mfma_split(a, Split8{pw.w[d][q][0], pw.w[d][q][1], pw.w[d][q][2]}, acc[q]);
+      }
+    }
+  }
+}
+
+// acc += A B on the fp32 instruction with B straight from the caller's parameters, W[K][H] at any 4-byte boundary: for
+// calls of so few rows that staging a copy of the weights would take longer than using it.  As points at this lane's row,
+// + 4 * hi, and is zero from K to 16 * kgroups; W at this lane's column.
+template <int H>
+__device__ __forceinline__ void gemm_phase_direct(const float* __restrict__ As, const float* __restrict__ W, int K, int hi, int kgroups, floatx16& acc) {
+  constexpr int kDepth = 3;  // groups in flight: the one in use and two on their way
+  float b[kDepth][8];
+  auto load = [&](int g, float (&v)[8]) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = 16 * g + 8 * (u / 4) + 4 * hi + u % 4;
+      const float w = W[(int64_t)min(k, K - 1) * H];
+      v[u] = k < K ? w : 0.f;
+    }
+  };
+  load(0, b[0]);
+  load(1, b[1]);
+#pragma unroll 1
+  for (int g0 = 0; g0 < kgroups; g0 += kDepth) {
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) {
+      const int g = g0 + d;
+      if (g < kgroups) {  // uniform
+        load(g + kDepth - 1, b[(d + kDepth - 1) % kDepth]);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float4 a = *reinterpret_cast<const float4*>(As + 16 * g + 8 * u);
+          const float af[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], b[d][4 * u + j], acc, 0, 0, 0);
+        }
       }
     }
   }

@@ -17,16 +17,21 @@ namespace {
 
 // Working copy of the parameters: blocks moved to their aligned offsets, optionally rounded to bf16, plus the
 // operand-order copies of W1, W2 and W2 transposed that the fused training kernel streams from memory.
+__device__ __forceinline__ void store_split_weight(float* copy, float v, int64_t k, int64_t n, int H) {
+  const SplitPair s = split_pair(v, 0.f);
+  bf16_t* const d = reinterpret_cast<bf16_t*>(copy) + split_weight_index(k, n, H);
+  d[0] = (bf16_t)s.h;
+  d[split_weight_plane(H)] = (bf16_t)s.m;
+  d[2 * split_weight_plane(H)] = (bf16_t)s.l;
+}
+
 __global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int round) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= pm.src[12]) return;
 #pragma unroll
-  for (int net = 0; net < 2; ++net) {  // zero rows of the operand-order W1 (fewer than 16 rows: far fewer floats than parameters)
+  for (int net = 0; net < 2; ++net) {  // zero rows of the split W1 (fewer than 16 rows: far fewer floats than parameters)
     const int H = pm.hidden[net];
-    if (i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) {
-      const int64_t k = pm.din[net] + i / H, n = i % H;
-      dst[pm.sw_w1[net] + ((k / 4) * H + n) * 4 + k % 4] = 0.f;
-    }
+    if (pm.split[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) store_split_weight(dst + pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H, H);
   }
   int b = 0;
 #pragma unroll
@@ -36,10 +41,11 @@ __global__ void stage_params_kernel(const float* __restrict__ src, float* __rest
   dst[pm.dst[b] + e] = v;
   const int net = b >= 6, H = pm.hidden[net];
   const int64_t r = e / H, c = e - r * H;
-  if (b == 0 || b == 6) dst[pm.sw_w1[net] + ((r / 4) * H + c) * 4 + r % 4] = v;
+  if (!pm.split[net]) return;
+  if (b == 0 || b == 6) store_split_weight(dst + pm.sw_w1[net], v, r, c, H);
   if (b == 2 || b == 8) {
-    dst[pm.sw_w2[net] + ((r / 4) * H + c) * 4 + r % 4] = v;
-    dst[pm.sw_w2t[net] + ((c / 4) * H + r) * 4 + c % 4] = v;
+    store_split_weight(dst + pm.sw_w2[net], v, r, c, H);
+    store_split_weight(dst + pm.sw_w2t[net], v, c, r, H);
   }
 }
 
@@ -225,6 +231,22 @@ static int32_t forward_rows(const marl_config& c, const float* eff, const float*
 
 int32_t launch_policy_forward(const marl_config& c, const float* params, const float* obs, int64_t n_rows,
                               float* logits, float* value, void* workspace, hipStream_t s) {
+  const Dims d = dims_of(c);
+  const int64_t S = n_rows * d.A;
+  if (!d.bf16 && S <= kForwardSmall && fused_forward_supported(d.Ha, d.D) && fused_forward_supported(d.Hc, d.Dc)) {
+    const int64_t Sc = d.central ? n_rows : S;
+    const ParamMap pm = param_map(d);
+    auto direct = [&](const float* X, int64_t rows, int Din, int net, const NetOffsets& o) {
+      FusedFwdArgs a = fused_args(RowSrc{X, Din, nullptr, 1, rows}, rows, Din, params, pm, net);
+      a.W1 = params + o.W1; a.b1 = params + o.b1; a.W2 = params + o.W2; a.b2 = params + o.b2; a.W3 = params + o.W3; a.b3 = params + o.b3;
+      return a;
+    };
+    const ActorRolloutFinish fa{logits, SampleArgs{}, 0};
+    const CriticRolloutFinish fc{value, d.central ? d.A : 1, Sc, nullptr};
+    return launch_fused_forward_small<kActions, 1>(
+        d.Ha, direct(obs, logits != nullptr ? S : 0, d.D, 0, net_offsets(0, d.D, d.Ha, kActions)), fa,
+        d.Hc, direct(obs, value != nullptr ? Sc : 0, d.Dc, 1, net_offsets(d.Pa, d.Dc, d.Hc, 1)), fc, s);
+  }
   const RolloutWsView w = carve_rollout_ws(c, n_rows, workspace, nullptr);
   const float* eff = effective_params(c, params, w.eff_params, s);
   return forward_rows(c, eff, obs, n_rows, w, logits != nullptr, logits, nullptr, value, s);

@@ -9,6 +9,9 @@
 // trajectory (observations, actions, log-probabilities, rewards, dones) is streamed out.  The critic's values do not
 // steer the rollout and are computed in one pass over the stored observations afterwards.
 //
+// Both layers run on split bf16 operands (gemm.h, PhaseW); a step of 32 samples at 128 units is a chain of about 7.5 us
+// (7.7 with the fp32 instruction), 65 536 samples per step 38 us (43).
+//
 // The same kernel with EVAL = true is the greedy evaluation block: argmax actions, no trajectory, and the
 // per-environment return / length / episode counts accumulated in registers.
 #pragma once
@@ -20,7 +23,7 @@ namespace marl {
 struct RolloutFusedArgs {
   EnvParams p;
   marl_env_state st;
-  const float *W1s, *W2s, *b1, *b2, *W3, *b3;  // actor: operand-order W1 / W2, aligned biases and output layer
+  const float *W1s, *W2s, *b1, *b2, *W3, *b3;  // actor: split operand-order W1 / W2, aligned biases and output layer
   int kpad1, px;
   int T;  // steps to take
   // training rollout
@@ -152,10 +155,10 @@ __global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <=
     }
   };
 
-  // the weights of a whole layer are requested a phase ahead (buffer loads: one descriptor, one lane offset)
+  // the first weights of a layer are requested a phase ahead (buffer loads: one descriptor, one lane offset)
   constexpr int KG1 = (D + 15) / 16, KG2 = H / 16;
   const int wlane = (hi * H + nt * 32 + lo) * 4;
-  const WeightRsrc rsW1 = weight_rsrc(a.W1s, a.kpad1 * H), rsW2 = weight_rsrc(a.W2s, H * H);
+  const WeightRsrc rsW1 = split_weight_rsrc(a.W1s, a.kpad1, H), rsW2 = split_weight_rsrc(a.W2s, H, H);
   PhaseW<KG1> pw1;
   phase_w_request<H, KG1>(pw1, rsW1, wlane, a.kpad1 / 16);
   for (int t = 0;; ++t) {
@@ -169,7 +172,7 @@ __global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <=
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    gemm_phase_w<KG1>(Xs + (mt * 32 + lo) * px + 4 * hi, a.kpad1 / 16, acc, pw1);
+    gemm_phase_w<H, KG1>(Xs + (mt * 32 + lo) * px + 8 * hi, rsW1, wlane, a.kpad1 / 16, &acc, pw1);
     PhaseW<KG2> pw2;  // layer 2's weights arrive during the tanh of layer 1
     phase_w_request<H, KG2>(pw2, rsW2, wlane, KG2);
     {
@@ -184,7 +187,7 @@ __global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <=
     // ---- layer 2: h2 = tanh(h1 W2 + b2)
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    gemm_phase_w<KG2>(Hs + (mt * 32 + lo) * PH + 4 * hi, KG2, acc, pw2);
+    gemm_phase_w<H, KG2>(Hs + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, KG2, &acc, pw2);
     phase_w_request<H, KG1>(pw1, rsW1, wlane, a.kpad1 / 16);  // layer 1 of the next step
     __syncthreads();  // every wavefront is past its last read of h1
     {
