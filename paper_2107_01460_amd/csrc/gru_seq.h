@@ -71,6 +71,12 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Where a wavefront starts its walk along the contraction when it streams weights: the wavefronts' fragments are a multiple
+// of 4 KB apart, so that in step they would all ask the same memory channels of the L2 at the same time.
+__device__ __forceinline__ int gru_rotation(int first, int steps) {
+  return __builtin_amdgcn_readfirstlane((int)((first + blockIdx.x / 8) % steps));
+}
+
 template <int KS, int SM, bool RES>
 __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kernel(GruFwdArgs a) {
   constexpr int H = 32 * KS, UB = RES ? 1 : 2, MT = 16 * SM, P = H + 8, PLANE = MT * P;
@@ -101,14 +107,20 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
 
   const WeightRsrc wsrc = weight_rsrc(reinterpret_cast<const float*>(a.W), H * H * 9 / 2);
   int woff = UB * wave * KS * 9 * 1024 + lane * 16;  // this lane's bytes of its wavefront's fragments
+  constexpr bool ROT = !RES && SM == 1;
+  const int rot = ROT ? gru_rotation(wave, KS) : 0;
+  auto step_of = [&](int ks) { return !ROT ? ks : ks + rot < KS ? ks + rot : ks + rot - KS; };
   auto load_w = [&](int i, bf16x8 (&w)[9]) {
 #pragma unroll
-    for (int f = 0; f < 9; ++f) w[f] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wsrc, woff, (i * 9 + f) * 1024, 0));
+    for (int f = 0; f < 9; ++f)
+      w[f] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(wsrc, woff, ((i / KS * KS + step_of(i % KS)) * 9 + f) * 1024, 0));
   };
-  constexpr int NI = UB * KS;
-  bf16x8 w[RES ? NI : 2][9];
+  // streamed: contraction steps in flight, a divisor of NI (the ring goes on into the next step)
+  constexpr int NI = UB * KS, RING = RES ? NI : SM == 1 && NI % 4 == 0 ? 4 : 2;
+  static_assert(NI % RING == 0, "ring");
+  bf16x8 w[RING][9];
 #pragma unroll
-  for (int i = 0; i < (RES ? NI : 1); ++i) load_w(i, w[i]);
+  for (int i = 0; i < (RES ? NI : RING - 1); ++i) load_w(i, w[i]);
 
   float4 h[UB][SM], gi[UB][SM][3];
   auto load_gi = [&](int t, int b) {
@@ -150,11 +162,11 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
         for (int m = 0; m < SM; ++m) acc[g][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        const int i = b * KS + ks, slot = RES ? i : i & 1;
-        if (!RES) load_w((i + 1) % NI, w[(i + 1) & 1]);  // (NI is even: the ring goes on into the next step)
+        const int i = b * KS + ks, slot = i % RING;
+        if (!RES) load_w((i + RING - 1) % NI, w[(i + RING - 1) % RING]);
         Split8 x[SM];
 #pragma unroll
-        for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * ks, PLANE);
+        for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * step_of(ks), PLANE);
 #define MARL_GRU_PRODUCT(WP, XP)            \
   _Pragma("unroll") for (int g = 0; g < 3; ++g) \
   _Pragma("unroll") for (int m = 0; m < SM; ++m) acc[g][m] = mfma16(w[slot][3 * g + WP], x[m].XP, acc[g][m]);
@@ -251,7 +263,7 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
   };
   bf16x8 w[RING][UB][3];
 #pragma unroll
-  for (int i = 0; i < (RES ? NI : 2); ++i) load_w(i, w[i]);
+  for (int i = 0; i < (RES ? NI : RING - 1); ++i) load_w(i, w[i]);
 
   float4 rec[UB][SM][4], hp[UB][SM], carry[UB][SM];
   float dl[SM][NOUT];
@@ -331,7 +343,7 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int slot = i % RING;
-      if (!RES) load_w((i + 2) % NI, w[(i + 2) % RING]);
+      if (!RES) load_w((i + RING - 1) % NI, w[(i + RING - 1) % RING]);
       Split8 x[SM];
 #pragma unroll
       for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * i, PLANE);
@@ -596,8 +608,10 @@ __global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_ste
   }
 }
 
-// 16 sequences per workgroup while that leaves compute units idle, 32 (the same weights for twice the work) beyond.
-inline int gru_seq_tiles16(int64_t S1) { return S1 <= 256 * 16; }
+// Sequences per workgroup: 16 while that leaves compute units idle, 32 (the same weights for twice the work) beyond.  The
+// line is the same where the weights are streamed and the workgroups share the L2: 128 steps of 2100 sequences, 256 units,
+// backward: 2.4 ms in 132 workgroups of 16, 3.2 ms in 66 of 32.
+inline bool gru_seq_tiles16(int64_t S1) { return S1 <= 256 * 16; }
 
 template <int KS>
 inline void launch_gru_fwd_ks(const GruFwdArgs& a, hipStream_t s) {
