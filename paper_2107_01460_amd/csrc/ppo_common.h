@@ -253,6 +253,8 @@ struct CriticLoss {
 // 32 samples whose activations sit in LDS at their whole width; a workgroup's share of the W3 / b3 gradient leaves it once,
 // with plain stores, and is added in a fixed order by the launcher.  (With atomics the 2048 workgroups queued up on the same
 // few cache lines: 460 us of the 480 us a launch on 98 304 samples took; 131 us for 1 048 576 now, 537 MB of activations.)
+// DZ2: H2 is replaced by dz2 = (dL/dout W3^T)(1 - h2^2), the gradient of its pre-activations, which the tile in LDS gives
+// without another pass over the activations (a kernel of its own took 76 us for 50 000 samples of 192 units).
 // Bound: memory and, per tile, a chain of three barriers, which the other workgroup of the compute unit and the next
 // tile's loads, already in flight, cover.
 constexpr int kLossHeadGrid = 512;
@@ -261,8 +263,8 @@ inline int64_t loss_head_partial_floats(int H, int nout) { return (int64_t)kLoss
 inline size_t loss_head_lds(int H, int nout) { return sizeof(float) * (kLossTile * (H + 4) + H * nout + 8 * nout * kLossTile + kLossTile * 8); }
 
 // NQ: 16-byte pieces of a row per staging thread, at least H / 32 (the last piece again beyond that)
-template <int NOUT, int NQ, class LossFn>
-__global__ void __launch_bounds__(256, 2) loss_head_kernel(const float* __restrict__ H2, int64_t S, int H,
+template <int NOUT, int NQ, bool DZ2, class LossFn>
+__global__ void __launch_bounds__(256, 2) loss_head_kernel(float* H2, int64_t S, int H,
                                                            const float* __restrict__ W3, const float* __restrict__ b3,
                                                            LossFn fn, float* __restrict__ dl_out, float* __restrict__ partial,
                                                            Scalars* sc) {
@@ -284,6 +286,13 @@ __global__ void __launch_bounds__(256, 2) loss_head_kernel(const float* __restri
   }
   const LossPrep prep = fn.prepare();
   for (int i = tid; i < H * NOUT; i += 256) w3[i] = W3[i];
+  float wu[2][NOUT];  // DZ2: the output weights of this thread's units
+  if (DZ2) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) wu[c][k] = W3[min(tid % units + c * units, H - 1) * NOUT + k];
+  }
   const int64_t ntiles = (S + kLossTile - 1) / kLossTile;
   typedef float f4 __attribute__((ext_vector_type(4)));
   f4 v[NQ];
@@ -351,12 +360,19 @@ __global__ void __launch_bounds__(256, 2) loss_head_kernel(const float* __restri
     for (int c = 0; c < 2; ++c) {
       const int i = tid % units + c * units;
       if (i < H) {
-        const int n = kLossTile / parts;
+        const int n = kLossTile / parts, live = (int)min((int64_t)kLossTile, S - s0);
+        float* const dst = H2 + s0 * H + i;
 #pragma unroll 4
         for (int s = part * n; s < (part + 1) * n; ++s) {
           const float h = tile[s * P + i];
+          float d = 0.f;
 #pragma unroll
-          for (int k = 0; k < NOUT; ++k) gw[c][k] = fmaf(h, dls[s * 8 + k], gw[c][k]);
+          for (int k = 0; k < NOUT; ++k) {
+            const float dl = dls[s * 8 + k];
+            gw[c][k] = fmaf(h, dl, gw[c][k]);
+            if (DZ2) d = fmaf(dl, wu[c][k], d);
+          }
+          if (DZ2 && s < live) dst[s * H] = d * (1.0f - h * h);
         }
       }
     }
@@ -399,10 +415,10 @@ __global__ void __launch_bounds__(256, 2) loss_head_kernel(const float* __restri
 }
 
 // gW3: [H][NOUT], the gradient of b3 directly behind it; partial: loss_head_partial_floats
-template <int NOUT, class LossFn>
-inline int32_t launch_loss_head(const float* H2, int64_t S, int H, const float* W3, const float* b3, const LossFn& fn, float* dl,
+template <int NOUT, bool DZ2, class LossFn>
+inline int32_t launch_loss_head(float* H2, int64_t S, int H, const float* W3, const float* b3, const LossFn& fn, float* dl,
                                 float* gW3, float* partial, Scalars* sc, hipStream_t s) {
-  auto kern = H <= 128 ? loss_head_kernel<NOUT, 4, LossFn> : H <= 256 ? loss_head_kernel<NOUT, 8, LossFn> : loss_head_kernel<NOUT, 16, LossFn>;
+  auto kern = H <= 128 ? loss_head_kernel<NOUT, 4, DZ2, LossFn> : H <= 256 ? loss_head_kernel<NOUT, 8, DZ2, LossFn> : loss_head_kernel<NOUT, 16, DZ2, LossFn>;
   const size_t bytes = loss_head_lds(H, NOUT);
   if (bytes > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)

@@ -260,44 +260,6 @@ __global__ void __launch_bounds__(NT) loss_head_bf16_kernel(bf16_t* __restrict__
   }
 }
 
-// In place: H2[s][j] <- (sum_k dl[s][k] W3[j][k]) * (1 - H2[s][j]^2); column sums -> gb2.
-template <int NOUT>
-__global__ void __launch_bounds__(256) dz2_kernel(float* __restrict__ H2, const float* __restrict__ dl,
-                                                  const float* __restrict__ W3, float* __restrict__ gb2, int64_t S,
-                                                  int H, int cb, int rows_per_block, int round_bf16) {
-  __shared__ float red[256];
-  const int tid = threadIdx.x;
-  const int rg_count = 256 / cb;
-  const int rg = tid / cb, jl = tid - rg * cb;
-  const int j = blockIdx.y * cb + jl;
-  const bool on = rg < rg_count && j < H;
-  float w[NOUT];
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) w[k] = on ? W3[(int64_t)j * NOUT + k] : 0.f;
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-  const int64_t r1 = min(S, r0 + rows_per_block);
-  float csum = 0.f;
-  if (on) {
-    for (int64_t r = r0 + rg; r < r1; r += rg_count) {
-      float g = 0.f;
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) g = fmaf(dl[r * NOUT + k], w[k], g);
-      const float h = H2[r * H + j];
-      float v = g * (1.0f - h * h);
-      if (round_bf16) v = round_to_bf16(v);
-      H2[r * H + j] = v;
-      csum += v;
-    }
-  }
-  red[tid] = on ? csum : 0.f;
-  __syncthreads();
-  if (gb2 != nullptr && tid < cb && j < H) {
-    float t = 0.f;
-    for (int g2 = 0; g2 < rg_count; ++g2) t += red[g2 * cb + tid];
-    atomicAdd(&gb2[j], t);
-  }
-}
-
 struct UpdateWsView {
   float *eff_params, *grad;
   Scalars* sc;        // two sets: optimiser step k accumulates into set k % 2 while its Adam kernel zeroes the other
@@ -316,7 +278,7 @@ struct UpdateWsView {
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
-int64_t split_want(int64_t tiles_mn) { return std::max<int64_t>(1, 1024 / std::max<int64_t>(1, tiles_mn)); }
+int64_t split_want(int64_t tiles_mn) { return std::max<int64_t>(1, 512 / std::max<int64_t>(1, tiles_mn)); }
 // floats of workspace for the k splits of dW2 (H x H + H) and dW1 (Din x H + H) of one layer-by-layer network
 int64_t split_ws_floats(int H, int Din) {
   const int64_t t2 = ((H + 127) / 128) * ((H + 127) / 128), t1 = ((Din + 127) / 128) * ((H + 127) / 128);
@@ -384,7 +346,7 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
 }
 
 int64_t pick_k_split(int64_t K, int64_t tiles_mn) {
-  // enough workgroups for ~4 per CU, each with a k range that is a multiple of the k tile
+  // enough workgroups for two per CU, each with a k range that is a multiple of the k tile
   int64_t want = split_want(tiles_mn);
   int64_t per = (K + want - 1) / want;
   per = std::max<int64_t>(256, ((per + kGemmBK - 1) / kGemmBK) * kGemmBK);
@@ -429,11 +391,9 @@ int32_t train_forward_wreg(const RowSrc& X, int64_t S, int Din, const float* W1,
   return rc;
 }
 
-// Backward through one network given dL/d(output layer) in dl; h2 is overwritten by dz2.
-template <int NOUT>
-void mlp_backward(const RowSrc& X, int64_t S, int Din, int H, const float* W2, const float* W3, float* h1, float* h2,
-                  float* dz1, const float* dl, float* gW1, float* gb1, float* gW2, float* gb2, bool bf16,
-                  bool dz2_ready, float* wacc_partial, float* split_ws, int64_t split_floats, hipStream_t s) {
+// Backward through one network given dz2, the gradient of the second hidden layer's pre-activations.
+void mlp_backward(const RowSrc& X, int64_t S, int Din, int H, const float* W2, const float* h1, const float* dz2,
+                  float* dz1, float* gW1, float* gb1, float* gW2, float* gb2, bool bf16, float* wacc_partial, float* split_ws, int64_t split_floats, hipStream_t s) {
   // a weight-gradient product writes its k splits to split_ws and has them added in a fixed order, where the workspace
   // has room and the bias gradient directly follows the weight gradient (its column sums ride along)
   auto split_launch = [&](GemmArgs& g, float* gW, float* gb, int64_t rows) {
@@ -444,19 +404,14 @@ void mlp_backward(const RowSrc& X, int64_t S, int Din, int H, const float* W2, c
     }
     if (launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s)) launch_reduce_partials(split_ws, (int)nz, count, gW, s);
   };
-  if (!dz2_ready) {
-    const int cb = std::min(H, 256), rpb = 256;
-    dim3 grid((unsigned)((S + rpb - 1) / rpb), (unsigned)((H + cb - 1) / cb));
-    hipLaunchKernelGGL(dz2_kernel<NOUT>, grid, dim3(256), 0, s, h2, dl, W3, (float*)nullptr, S, H, cb, rpb, (int)bf16);
-  }
   {  // gW2 += h1^T dz2, gb2 += column sums
     GemmArgs g{};
-    g.A = RowSrc{h1, H, nullptr, 1, S}; g.B = h2; g.ldb = H; g.C = gW2; g.ldc = H;
+    g.A = RowSrc{h1, H, nullptr, 1, S}; g.B = dz2; g.ldb = H; g.C = gW2; g.ldc = H;
     g.M = H; g.N = H; g.K = S; g.colsum = gb2;
     g.k_per_split = pick_k_split(S, ((H + 127) / 128) * ((H + 127) / 128));
     split_launch(g, gW2, gb2, H);
   }
-  const RowSrc dz2_rows{h2, H, nullptr, 1, S};
+  const RowSrc dz2_rows{dz2, H, nullptr, 1, S};
   if (!bf16 && wreg_worthwhile(S) && wreg_gemm_supported<WREG_DTANH>(dz2_rows, H, H)) {
     // dz1 = (dz2 W2^T) * (1 - h1^2) with W2 resident in registers
     WregArgs g{};
@@ -465,7 +420,7 @@ void mlp_backward(const RowSrc& X, int64_t S, int Din, int H, const float* W2, c
     launch_wreg_gemm<WREG_DTANH>(g, s);
   } else {  // dz1 = (dz2 W2^T) * (1 - h1^2), gb1 += column sums
     GemmArgs g{};
-    g.A = RowSrc{h2, H, nullptr, 1, S}; g.B = W2; g.ldb = H; g.C = dz1; g.ldc = H;
+    g.A = RowSrc{dz2, H, nullptr, 1, S}; g.B = W2; g.ldb = H; g.C = dz1; g.ldc = H;
     g.aux_mat = h1; g.ldaux = H; g.colsum = nullptr;
     g.M = S; g.N = H; g.K = H; g.round_bf16 = bf16;
     launch_gemm<GEMM_NT, EPI_DTANH>(g, s);
@@ -638,12 +593,12 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
             if (rc != MARL_OK) return rc;
           } else {
             mlp_hidden_forward(Xa, Sa, d.D, d.Ha, eff + oa.W1, eff + oa.b1, eff + oa.W2, eff + oa.b2, w.h1a, w.h2a, d.bf16, s);
-            const int32_t rc = launch_loss_head<kActions>(w.h2a, Sa, d.Ha, eff + oa.W3, eff + oa.b3, fn, w.dla, w.grad + ga.W3,
+            const int32_t rc = launch_loss_head<kActions, true>(w.h2a, Sa, d.Ha, eff + oa.W3, eff + oa.b3, fn, w.dla, w.grad + ga.W3,
                                                           w.partial_head, sck, s);
             if (rc != MARL_OK) return rc;
           }
-          mlp_backward<kActions>(Xa, Sa, d.D, d.Ha, eff + oa.W2, eff + oa.W3, w.h1a, w.h2a, w.dz1a, w.dla, w.grad + ga.W1,
-                                 w.grad + ga.b1, w.grad + ga.W2, w.grad + ga.b2, d.bf16, fused_a, nullptr, w.split_ws, w.split_floats, s);
+          mlp_backward(Xa, Sa, d.D, d.Ha, eff + oa.W2, w.h1a, w.h2a, w.dz1a, w.grad + ga.W1, w.grad + ga.b1, w.grad + ga.W2,
+                       w.grad + ga.b2, d.bf16, nullptr, w.split_ws, w.split_floats, s);
         }
       }
       // ---- critic
@@ -682,12 +637,12 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
             if (rc != MARL_OK) return rc;
           } else {
             mlp_hidden_forward(Xc, Sc, d.Dc, d.Hc, eff + oc.W1, eff + oc.b1, eff + oc.W2, eff + oc.b2, w.h1c, w.h2c, d.bf16, s);
-            const int32_t rc = launch_loss_head<1>(w.h2c, Sc, d.Hc, eff + oc.W3, eff + oc.b3, fn, w.dlc, w.grad + gc.W3,
+            const int32_t rc = launch_loss_head<1, true>(w.h2c, Sc, d.Hc, eff + oc.W3, eff + oc.b3, fn, w.dlc, w.grad + gc.W3,
                                                    w.partial_head, sck, s);
             if (rc != MARL_OK) return rc;
           }
-          mlp_backward<1>(Xc, Sc, d.Dc, d.Hc, eff + oc.W2, eff + oc.W3, w.h1c, w.h2c, w.dz1c, w.dlc, w.grad + gc.W1,
-                          w.grad + gc.b1, w.grad + gc.W2, w.grad + gc.b2, d.bf16, fused_c, w.partial_w1, w.split_ws, w.split_floats, s);
+          mlp_backward(Xc, Sc, d.Dc, d.Hc, eff + oc.W2, w.h1c, w.h2c, w.dz1c, w.grad + gc.W1, w.grad + gc.b1, w.grad + gc.W2,
+                       w.grad + gc.b2, d.bf16, w.partial_w1, w.split_ws, w.split_floats, s);
         }
       }
       // ---- clip + Adam

@@ -508,7 +508,7 @@ int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din,
   f.h_first = w.Hs; f.hs = w.Hs + S1 * H; f.rec = w.R; f.reset = reset + J; f.per = per; f.S1 = S1; f.T = T;
   gru_forward(f, H, eff, o, w.GhT, w.hm, s);
   // output layer, loss, dL/dout, W3 / b3 gradient over all steps
-  const int32_t rc = launch_loss_head<NOUT>(w.Hs + S1 * H, S, H, eff + o.W3, eff + o.b3, fn, w.dl, grad + go.W3, w.partial, sc, s);
+  const int32_t rc = launch_loss_head<NOUT, false>(w.Hs + S1 * H, S, H, eff + o.W3, eff + o.b3, fn, w.dl, grad + go.W3, w.partial, sc, s);
   if (rc != MARL_OK) return rc;
   GruBwdArgs bw{};
   bw.W = reinterpret_cast<const bf16_t*>(wh_bwd); bw.W3 = eff + o.W3; bw.dl = w.dl; bw.rec = w.R; bw.hs = w.Hs; bw.reset = reset + J;
