@@ -270,9 +270,14 @@ __device__ __forceinline__ void forage_transition(uint32_t (&ag)[CA], uint32_t (
   dn_out = dn;
 }
 
+// One channel of one cell of an observation window, as fp32 or as bf16.  Every value a window can hold -- a level of eight
+// bits, 0.5, 1, 2 -- is exact in bf16: its lower 16 bits are zero.
+__device__ __forceinline__ void paint_cell(float& o, float v) { o = v; }
+__device__ __forceinline__ void paint_cell(bf16_t& o, float v) { o = (bf16_t)(__float_as_uint(v) >> 16); }
+
 // The lane's V x V x 3 window into w[0 .. 3 V V): walls and zeros first, then the entities that fall inside it.
-template <int V, int CA, int CF>
-__device__ __forceinline__ void forage_paint(float* w, const uint32_t (&ag)[CA], const uint32_t (&fd)[CF], int a,
+template <int V, int CA, int CF, typename T>
+__device__ __forceinline__ void forage_paint(T* w, const uint32_t (&ag)[CA], const uint32_t (&fd)[CF], int a,
                                              const EnvParams& p) {
   constexpr int h = (V - 1) / 2;
   uint32_t me = 0;
@@ -285,21 +290,21 @@ __device__ __forceinline__ void forage_paint(float* w, const uint32_t (&ag)[CA],
     for (int dx = -h; dx <= h; ++dx) {
       const int rr = r0 + dy, cc = c0 + dx;
       const bool wall = rr < 0 || rr >= p.G || cc < 0 || cc >= p.G;
-      float* o = w + ((dy + h) * V + (dx + h)) * 3;
-      o[0] = 0.f;
-      o[1] = 0.f;
-      o[2] = wall ? 1.f : 0.f;
+      T* o = w + ((dy + h) * V + (dx + h)) * 3;
+      paint_cell(o[0], 0.f);
+      paint_cell(o[1], 0.f);
+      paint_cell(o[2], wall ? 1.f : 0.f);
     }
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
     const int dy = e_row(ag[b]) - r0, dx = e_col(ag[b]) - c0;
-    if (b < p.A && dy >= -h && dy <= h && dx >= -h && dx <= h) w[((dy + h) * V + (dx + h)) * 3 + 0] = (float)e_lvl(ag[b]);
+    if (b < p.A && dy >= -h && dy <= h && dx >= -h && dx <= h) paint_cell(w[((dy + h) * V + (dx + h)) * 3 + 0], (float)e_lvl(ag[b]));
   }
 #pragma unroll
   for (int f = 0; f < CF; ++f) {
     const int dy = e_row(fd[f]) - r0, dx = e_col(fd[f]) - c0;
     if (f < p.F && e_lvl(fd[f]) != 0 && dy >= -h && dy <= h && dx >= -h && dx <= h)
-      w[((dy + h) * V + (dx + h)) * 3 + 1] = (float)e_lvl(fd[f]);
+      paint_cell(w[((dy + h) * V + (dx + h)) * 3 + 1], (float)e_lvl(fd[f]));
   }
 }
 
@@ -476,8 +481,8 @@ __device__ __forceinline__ void wh_transition(uint32_t (&ag)[CA], uint32_t (&fd)
   dn_out = dn;
 }
 
-template <int V, int CA, int CF>
-__device__ __forceinline__ void wh_paint(float* w, const uint32_t (&ag)[CA], const uint32_t (&fd)[CF], int a,
+template <int V, int CA, int CF, typename T>
+__device__ __forceinline__ void wh_paint(T* w, const uint32_t (&ag)[CA], const uint32_t (&fd)[CF], int a,
                                          const EnvParams& p) {
   constexpr int h = (V - 1) / 2;
   uint32_t me = 0;
@@ -490,23 +495,23 @@ __device__ __forceinline__ void wh_paint(float* w, const uint32_t (&ag)[CA], con
     for (int dx = -h; dx <= h; ++dx) {
       const int rr = r0 + dy, cc = c0 + dx;
       const bool wall = rr < 0 || rr >= p.G || cc < 0 || cc >= p.G;
-      float* o = w + ((dy + h) * V + (dx + h)) * 3;
-      o[0] = 0.f;
-      o[1] = 0.f;
-      o[2] = wall ? 1.f : (wh_goal(p.G, rr, cc) ? 0.5f : 0.f);
+      T* o = w + ((dy + h) * V + (dx + h)) * 3;
+      paint_cell(o[0], 0.f);
+      paint_cell(o[1], 0.f);
+      paint_cell(o[2], wall ? 1.f : (wh_goal(p.G, rr, cc) ? 0.5f : 0.f));
     }
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
     const int dy = e_row(ag[b]) - r0, dx = e_col(ag[b]) - c0;
     if (b < p.A && dy >= -h && dy <= h && dx >= -h && dx <= h)
-      w[((dy + h) * V + (dx + h)) * 3 + 0] = e_lvl(ag[b]) != 0 ? 2.f : 1.f;
+      paint_cell(w[((dy + h) * V + (dx + h)) * 3 + 0], e_lvl(ag[b]) != 0 ? 2.f : 1.f);
   }
 #pragma unroll
   for (int f = 0; f < CF; ++f) {
     const int dy = e_row(fd[f]) - r0, dx = e_col(fd[f]) - c0;
     if (f < p.F && dy >= -h && dy <= h && dx >= -h && dx <= h) {
-      float* o = &w[((dy + h) * V + (dx + h)) * 3 + 1];
-      *o = fmaxf(*o, (float)e_lvl(fd[f]));
+      T* o = &w[((dy + h) * V + (dx + h)) * 3 + 1];
+      paint_cell(*o, fmaxf(load_act(o, 0), (float)e_lvl(fd[f])));
     }
   }
 }

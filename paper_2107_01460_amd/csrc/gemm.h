@@ -202,7 +202,30 @@ __device__ __forceinline__ void gemm_phase_w(const float* __restrict__ As, Weigh
     }
   }
 }
-// The same with a run-time number of groups, no request ahead: the groups in flight are the one in use and two on their way.
+// The transposed product, weights x samples: acc += B^T A^T for this wavefront's 32 units x 32 samples, so that a lane holds
+// four times four consecutive units of one sample.  A by rows of split planes in LDS (xs points at this lane's row, + 8 * hi;
+// planes `plane` elements apart).  EXACT: one plane, the values are exact in bf16 and the lower parts' products are zero.
+template <int H, int KG, bool EXACT>
+__device__ __forceinline__ void gemm_phase_t(const bf16_t* xs, int plane, WeightRsrc B, int lane_off, int kgroups, floatx16& acc, PhaseW<KG>& pw) {
+  constexpr int RING = PhaseW<KG>::RING;
+#pragma unroll
+  for (int g = 0; g < KG; ++g) {
+    if (g < kgroups) {  // uniform
+      const Split8 w{pw.w[g % RING][0][0], pw.w[g % RING][0][1], pw.w[g % RING][0][2]};
+      if (EXACT) {
+        const bf16x8 x = *reinterpret_cast<const bf16x8*>(xs + 16 * g);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w.l, x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w.m, x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w.h, x, acc, 0, 0, 0);
+      } else {
+        acc = mfma_split(w, frag_row(xs + 16 * g, plane), acc);
+      }
+      if (g + RING < KG) phase_w_load<H>(pw, B, lane_off, g + RING, kgroups);
+    }
+  }
+}
+
+// gemm_phase_w with a run-time number of groups, no request ahead: the groups in flight are the one in use and two on their way.
 template <int H, int NT>
 __device__ __forceinline__ void gemm_phase_w_any(const float* __restrict__ As, WeightRsrc B, int lane_off, int kgroups, floatx16* acc) {
   PhaseW<3, NT> pw;

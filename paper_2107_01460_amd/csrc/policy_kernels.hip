@@ -279,8 +279,6 @@ static RolloutFusedArgs rollout_fused_args(const marl_config& c, marl_env_state 
   a.p = env_params(c);
   a.st = st;
   a.W1s = eff + pm.sw_w1[0]; a.W2s = eff + pm.sw_w2[0]; a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
-  a.kpad1 = pm.kpad1[0];
-  a.px = fused_forward_px(d.D);
   return a;
 }
 

@@ -9,8 +9,10 @@
 // trajectory (observations, actions, log-probabilities, rewards, dones) is streamed out.  The critic's values do not
 // steer the rollout and are computed in one pass over the stored observations afterwards.
 //
-// Both layers run on split bf16 operands (gemm.h, PhaseW); a step of 32 samples at 128 units is a chain of about 7.5 us
-// (7.7 with the fp32 instruction), 65 536 samples per step 38 us (43).
+// Both layers run on split bf16 operands, transposed (gemm_phase_t): the windows hold small integers and halves, exact in
+// bf16, so layer 1 takes half the products, h1 is split once, and the output layer starts from the registers that layer 2
+// ends in.  A step is a chain of latencies: 128 steps of 3072 samples at 128 units 0.84 ms (with fp32 tiles, split by every
+// wavefront that reads them, 1.0 ms), of 65 536 samples 4.7 ms (4.8).
 //
 // The same kernel with EVAL = true is the greedy evaluation block: argmax actions, no trajectory, and the
 // per-environment return / length / episode counts accumulated in registers.
@@ -24,7 +26,6 @@ struct RolloutFusedArgs {
   EnvParams p;
   marl_env_state st;
   const float *W1s, *W2s, *b1, *b2, *W3, *b3;  // actor: split operand-order W1 / W2, aligned biases and output layer
-  int kpad1, px;
   int T;  // steps to take
   // training rollout
   float* obs;  // [T+1][N][A][D]
@@ -58,25 +59,31 @@ __device__ __forceinline__ float log_softmax_fast(const float lg[kActions], int 
   return la - m - __builtin_amdgcn_logf(se) * 0.6931471805599453f;
 }
 
-template <int H, int BM, int V, int CA, int KIND, bool EVAL>
-__global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <= 5)) ? 3 : 1) rollout_fused_kernel(RolloutFusedArgs a) {
-  constexpr int D = 3 * V * V, PH = H + 4, GROUPS = 256 / BM, NOUT = kActions;
+// pitch of a window in LDS, in elements: the width rounded up to a k group, and an odd number of 16-byte units
+constexpr int rollout_fused_px(int D) { return (D + 15) / 16 * 16 + 8; }
+
+// OCC: workgroups per CU the registers are capped for
+template <int H, int BM, int V, int CA, int KIND, bool EVAL, int OCC>
+__global__ void __launch_bounds__(256, OCC) rollout_fused_kernel(RolloutFusedArgs a) {
+  constexpr int D = 3 * V * V, PX = rollout_fused_px(D), PH = H + 8, HPLANE = BM * PH, NOUT = kActions;
   constexpr int NTN = H / 32, MT = BM / 32, TILES = MT * NTN;
   static_assert(TILES == 4, "one 32x32 MFMA tile per wavefront");
   static_assert(BM <= 64, "the env lanes are lanes of one wavefront");
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  const int px = a.px;
-  float* const Xs2 = lds;                      // [2][BM][px]  observation windows of two consecutive steps, k-contiguous;
-                                               //              columns D .. px stay zero
-  float* const Hs = Xs2 + 2 * BM * px;         // [BM][PH]  h1, then h2
-  float* const red = Hs + BM * PH;             // [GROUPS][BM][NOUT]
-  float* const W3s = red + GROUPS * BM * NOUT; // [H][NOUT]
-  float* const noise = W3s + H * NOUT;         // [2][BM][8] log(-log u) of the step's uniforms, two steps alternating
+  bf16_t* const Xs2 = reinterpret_cast<bf16_t*>(lds);  // [2][BM][PX]  observation windows of two consecutive steps (exact in bf16),
+                                                       //              k-contiguous; columns D .. PX stay zero
+  bf16_t* const Hs = Xs2 + 2 * BM * PX;                // [3][BM][PH]  h1, split
+  float* const red = reinterpret_cast<float*>(Hs + 3 * HPLANE);  // [NTN][NOUT][BM] shares of the output layer
+  float* const W3s = red + NTN * NOUT * BM;            // [H][NOUT]
+  float* const noise = W3s + H * NOUT;                 // [2][BM][8] log(-log u) of the step's uniforms, two steps alternating
+  float* const b1s = noise + 2 * BM * 8;               // [H]
+  float* const b2s = b1s + H;                          // [H]
 
   const EnvParams& p = a.p;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo = lane & 31, hi = lane >> 5;
   const int mt = wave / NTN, nt = wave % NTN;
+  const int srow = mt * 32 + lo, u0 = nt * 32 + 4 * hi;  // this lane's sample of the tile; its units are u0 + 8 j .. + 3
   const int A = p.A, N = p.N;
   const int epw = BM / A;  // envs of this workgroup
   const int64_t env0 = (int64_t)blockIdx.x * epw;
@@ -126,7 +133,11 @@ __global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <=
   };
 
   for (int i = tid; i < H * NOUT; i += 256) W3s[i] = a.W3[i];
-  for (int i = tid; i < 2 * BM * px; i += 256) Xs2[i] = 0.f;  // padding columns and unused rows stay zero for good
+  for (int i = tid; i < H; i += 256) {
+    b1s[i] = a.b1[i];
+    b2s[i] = a.b2[i];
+  }
+  for (int i = tid; i < BM * PX; i += 256) reinterpret_cast<uint32_t*>(Xs2)[i] = 0u;  // padding columns and unused rows stay zero for good
   if (is_env_wave) {
     load_env_state<CA, CA, KIND>(ag, fd, a.st, p, nn, active);
     t_ep = a.st.t_in_ep[nn];
@@ -134,96 +145,85 @@ __global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <=
   }
   __syncthreads();
   if (active) {
-    if (KIND == 0) forage_paint<V, CA, CA>(Xs2 + lane * px, ag, fd, ai, p);
-    else wh_paint<V, CA, CA>(Xs2 + lane * px, ag, fd, ai, p);
+    if (KIND == 0) forage_paint<V, CA, CA>(Xs2 + lane * PX, ag, fd, ai, p);
+    else wh_paint<V, CA, CA>(Xs2 + lane * PX, ag, fd, ai, p);
   }
   if (a.T > 0) draw_noise(0);
-  // the biases of this lane's column and of the output layer stay in registers for all T steps
-  const float bias1 = a.b1[nt * 32 + lo], bias2 = a.b2[nt * 32 + lo];
+  // the output layer's bias stays in registers for all T steps
   float b3r[NOUT];
 #pragma unroll
   for (int k = 0; k < NOUT; ++k) b3r[k] = a.b3[k];
   // The windows of step t sit in tile t & 1: while the env lanes paint the windows of step t + 1 into the other tile, the
   // wavefronts that are idle then copy tile t & 1 out as slab t of the trajectory.  Thread j of them (0 .. 191).
   auto store_slab = [&](int t, int j, int nthreads) {
-    const float* const Xt = Xs2 + (t & 1) * BM * px;
+    const bf16_t* const Xt = Xs2 + (t & 1) * BM * PX;
     float* const out = a.obs + ((int64_t)t * N + env0) * A * D;
     const int count = samples_here * D;
     for (int i = j; i < count; i += nthreads) {
       const int r = i / D, c = i - r * D;
-      out[i] = Xt[r * px + c];
+      out[i] = from_bf16(Xt[r * PX + c]);
     }
   };
 
   // the first weights of a layer are requested a phase ahead (buffer loads: one descriptor, one lane offset)
   constexpr int KG1 = (D + 15) / 16, KG2 = H / 16;
   const int wlane = (hi * H + nt * 32 + lo) * 4;
-  const WeightRsrc rsW1 = split_weight_rsrc(a.W1s, a.kpad1, H), rsW2 = split_weight_rsrc(a.W2s, H, H);
+  const WeightRsrc rsW1 = split_weight_rsrc(a.W1s, 16 * KG1, H), rsW2 = split_weight_rsrc(a.W2s, H, H);
   PhaseW<KG1> pw1;
-  phase_w_request<H, KG1>(pw1, rsW1, wlane, a.kpad1 / 16);
+  phase_w_request<H, KG1>(pw1, rsW1, wlane, KG1);
   for (int t = 0;; ++t) {
     __syncthreads();  // the windows (and the noise) of step t are complete
     if (t == a.T) {
       if (!EVAL) store_slab(t, tid, 256);  // the post-rollout observation
       break;
     }
-    const float* const Xs = Xs2 + (t & 1) * BM * px;
-    // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS
+    const bf16_t* const Xs = Xs2 + (t & 1) * BM * PX;
+    int uw = u0;  // the weights and biases in LDS are read in every step: kept across steps, they would take 96 registers
+    asm volatile("" : "+v"(uw));
+    // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS.  Both layers are computed transposed (gemm_phase_t).
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    gemm_phase_w<H, KG1>(Xs + (mt * 32 + lo) * px + 8 * hi, rsW1, wlane, a.kpad1 / 16, &acc, pw1);
+    gemm_phase_t<H, KG1, true>(Xs + srow * PX + 8 * hi, 0, rsW1, wlane, KG1, acc, pw1);
     PhaseW<KG2> pw2;  // layer 2's weights arrive during the tanh of layer 1
     phase_w_request<H, KG2>(pw2, rsW2, wlane, KG2);
-    {
-      const int col = nt * 32 + lo;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        Hs[m * PH + col] = tanh_f32(acc[r] + bias1);
-      }
+    for (int j = 0; j < 4; ++j) {
+      const float4 bs = *reinterpret_cast<const float4*>(&b1s[uw + 8 * j]);
+      store_split4(&Hs[srow * PH + u0 + 8 * j], HPLANE,
+                   make_float4(tanh_f32(acc[4 * j] + bs.x), tanh_f32(acc[4 * j + 1] + bs.y), tanh_f32(acc[4 * j + 2] + bs.z), tanh_f32(acc[4 * j + 3] + bs.w)));
     }
     __syncthreads();  // h1 complete; every wavefront is past its reads of the windows
-    // ---- layer 2: h2 = tanh(h1 W2 + b2)
+    // ---- layer 2: h2 = tanh(h1 W2 + b2), and this wavefront's units' share of the output layer
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    gemm_phase_w<H, KG2>(Hs + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, KG2, &acc, pw2);
-    phase_w_request<H, KG1>(pw1, rsW1, wlane, a.kpad1 / 16);  // layer 1 of the next step
-    __syncthreads();  // every wavefront is past its last read of h1
+    gemm_phase_t<H, KG2, false>(Hs + srow * PH + 8 * hi, HPLANE, rsW2, wlane, KG2, acc, pw2);
+    phase_w_request<H, KG1>(pw1, rsW1, wlane, KG1);  // layer 1 of the next step
     {
-      const int col = nt * 32 + lo;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        Hs[m * PH + col] = tanh_f32(acc[r] + bias2);
-      }
-    }
-    __syncthreads();
-    // ---- output layer on the ALUs: thread -> (sample tid % BM, slice tid / BM of the hidden units)
-    {
-      const int s = tid % BM, grp = tid / BM;
-      constexpr int PER = H / GROUPS;
-      static_assert(PER % 4 == 0, "hidden units are read four at a time");
       float part[NOUT];
 #pragma unroll
       for (int k = 0; k < NOUT; ++k) part[k] = 0.f;
-#pragma unroll 2
-      for (int i = grp * PER; i < (grp + 1) * PER; i += 4) {
-        const float4 hv = *reinterpret_cast<const float4*>(&Hs[s * PH + i]);
-        const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float4 bs = *reinterpret_cast<const float4*>(&b2s[uw + 8 * j]);
+        const float h[4] = {tanh_f32(acc[4 * j] + bs.x), tanh_f32(acc[4 * j + 1] + bs.y), tanh_f32(acc[4 * j + 2] + bs.z), tanh_f32(acc[4 * j + 3] + bs.w)};
         float wv[4 * NOUT];
 #pragma unroll
         for (int q = 0; q < NOUT; ++q) {
-          const float4 w4 = *reinterpret_cast<const float4*>(&W3s[i * NOUT + 4 * q]);
+          const float4 w4 = *reinterpret_cast<const float4*>(&W3s[(uw + 8 * j) * NOUT + 4 * q]);
           wv[4 * q] = w4.x; wv[4 * q + 1] = w4.y; wv[4 * q + 2] = w4.z; wv[4 * q + 3] = w4.w;
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int k = 0; k < NOUT; ++k) part[k] = fmaf(hh[j], wv[j * NOUT + k], part[k]);
+          for (int k = 0; k < NOUT; ++k) part[k] = fmaf(h[e], wv[e * NOUT + k], part[k]);
+        __builtin_amdgcn_sched_barrier(0);  // one quarter's weights in registers at a time
       }
 #pragma unroll
-      for (int k = 0; k < NOUT; ++k) red[(grp * BM + s) * NOUT + k] = part[k];
+      for (int k = 0; k < NOUT; ++k) {
+        const float v = part[k] + __shfl_xor(part[k], 32);
+        if (hi == 0) red[(nt * NOUT + k) * BM + srow] = v;
+      }
     }
     __syncthreads();
     if (!is_env_wave) {
@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <=
       for (int k = 0; k < NOUT; ++k) {
         float v = b3r[k];
 #pragma unroll
-        for (int gq = 0; gq < GROUPS; ++gq) v += red[(gq * BM + row) * NOUT + k];
+        for (int q = 0; q < NTN; ++q) v += red[(q * NOUT + k) * BM + row];
         lg[k] = v;
       }
       int my_act = 0;
@@ -305,9 +305,9 @@ __global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <=
         if (ai == 0) a.done[(int64_t)t * N + n] = dn ? 1 : 0;
       }
       if (active) {  // the windows of step t + 1 into the other tile
-        float* const Xn = Xs2 + ((t + 1) & 1) * BM * px;
-        if (KIND == 0) forage_paint<V, CA, CA>(Xn + lane * px, ag, fd, ai, p);
-        else wh_paint<V, CA, CA>(Xn + lane * px, ag, fd, ai, p);
+        bf16_t* const Xn = Xs2 + ((t + 1) & 1) * BM * PX;
+        if (KIND == 0) forage_paint<V, CA, CA>(Xn + lane * PX, ag, fd, ai, p);
+        else wh_paint<V, CA, CA>(Xn + lane * PX, ag, fd, ai, p);
       }
     }
   }
@@ -325,10 +325,10 @@ __global__ void __launch_bounds__(256, ((H == 64 && CA <= 2) || (CA <= 4 && V <=
 inline bool rollout_fused_supported(int H, int A) { return (H == 64 || H == 128) && A <= 8; }
 inline int rollout_fused_bm(int H) { return H == 64 ? 64 : 32; }
 
-template <int H, int BM, int V, int CA, int KIND, bool EVAL>
+template <int H, int BM, int V, int CA, int KIND, bool EVAL, int OCC = (CA <= 4 && V <= 5) ? 2 : 1>
 inline int32_t launch_rollout_fused_inst(const RolloutFusedArgs& a, hipStream_t s) {
-  auto kern = rollout_fused_kernel<H, BM, V, CA, KIND, EVAL>;
-  const size_t bytes = (2 * (size_t)BM * a.px + (size_t)BM * (H + 4) + 256 * (size_t)kActions + (size_t)H * kActions + 2 * BM * 8) * sizeof(float);
+  auto kern = rollout_fused_kernel<H, BM, V, CA, KIND, EVAL, OCC>;
+  const size_t bytes = 2 * (size_t)BM * (2 * rollout_fused_px(3 * V * V) + 3 * (H + 8)) + sizeof(float) * ((H / 32) * kActions * BM + H * kActions + 2 * BM * 8 + 2 * H);
   static bool configured = false;  // per instantiation
   if (!configured) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
@@ -345,7 +345,12 @@ template <int V, int KIND, bool EVAL>
 inline int32_t launch_rollout_fused_view(int H, const RolloutFusedArgs& a, hipStream_t s) {
   const int cap = a.p.A > a.p.F ? a.p.A : a.p.F;  // every loop over entities is unrolled to the capacity
   if constexpr (V == 3 && KIND == 0) {  // the small foraging shape (two agents, one food): half the unrolled entity loops
-    if (cap <= 2 && H == 64) return launch_rollout_fused_inst<64, 64, V, 2, KIND, EVAL>(a, s);
+    if (cap <= 2 && H == 64) {
+      // three workgroups per CU cost spilled registers and pay where the chip is full: 4096 workgroups 2.25 against
+      // 2.66 ms, two workgroups 74 against 68 us
+      if (!EVAL && a.p.N > 512 * (64 / a.p.A)) return launch_rollout_fused_inst<64, 64, V, 2, KIND, EVAL, 3>(a, s);
+      return launch_rollout_fused_inst<64, 64, V, 2, KIND, EVAL>(a, s);
+    }
   }
   if (H == 64) {
     if (cap <= 4) return launch_rollout_fused_inst<64, 64, V, 4, KIND, EVAL>(a, s);
