@@ -65,6 +65,9 @@ struct ParamMap {
   // the eight k values of a lane are one 16-byte load, contiguous across lanes.  W1 is zero-padded to kpad1 rows (a
   // multiple of 16).
   int64_t sw_w1[2], sw_w2[2], sw_w2t[2];
+  // The actor's W1 and W2 as fp32 in the order of rollout_fp32_kernel: element (k, n) at ((k / 4) * H + n) * 4 + k % 4 (zero-padded
+  // like the split copy).  Filled for a rollout only; -1 where no such kernel exists (its widths are 64 and 128).
+  int64_t op_w1, op_w2;
   bool split[2];  // whether the copies are filled (fp32 networks of those widths)
   int din[2], kpad1[2];
   int hidden[2];
@@ -102,6 +105,14 @@ inline ParamMap param_map(const Dims& d) {
     m.sw_w1[n] = copy(m.kpad1[n] * H);
     m.sw_w2[n] = copy(H * H);
     m.sw_w2t[n] = copy(H * H);
+  }
+  m.op_w1 = m.op_w2 = -1;
+  if (!d.bf16 && (d.Ha == 64 || d.Ha == 128)) {
+    m.op_w1 = off;
+    off += (int64_t)m.kpad1[0] * d.Ha;
+    m.op_w2 = off;
+    off += (int64_t)d.Ha * d.Ha;
+    m.split_extra += off - m.op_w1;
   }
   m.total = off;
   return m;

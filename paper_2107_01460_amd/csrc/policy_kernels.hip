@@ -25,7 +25,7 @@ __device__ __forceinline__ void store_split_weight(float* copy, float v, int64_t
   d[2 * split_weight_plane(H)] = (bf16_t)s.l;
 }
 
-__global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int round) {
+__global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int round, int for_rollout) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= pm.src[12]) return;
 #pragma unroll
@@ -41,6 +41,14 @@ __global__ void stage_params_kernel(const float* __restrict__ src, float* __rest
   dst[pm.dst[b] + e] = v;
   const int net = b >= 6, H = pm.hidden[net];
   const int64_t r = e / H, c = e - r * H;
+  if (for_rollout && pm.op_w1 >= 0) {
+    if (i < (int64_t)(pm.kpad1[0] - pm.din[0]) * pm.hidden[0]) {
+      const int64_t k = pm.din[0] + i / pm.hidden[0], n = i % pm.hidden[0];
+      dst[pm.op_w1 + ((k / 4) * pm.hidden[0] + n) * 4 + k % 4] = 0.f;
+    }
+    if (b == 0) dst[pm.op_w1 + ((r / 4) * H + c) * 4 + r % 4] = v;
+    if (b == 2) dst[pm.op_w2 + ((r / 4) * H + c) * 4 + r % 4] = v;
+  }
   if (!pm.split[net]) return;
   if (b == 0 || b == 6) store_split_weight(dst + pm.sw_w1[net], v, r, c, H);
   if (b == 2 || b == 8) {
@@ -156,10 +164,10 @@ Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, in
   return bf16_net_weights(base + ((bf16_net_weight_elems(d.D, d.Ha) + 63) / 64) * 64, d.Dc, d.Hc);
 }
 
-const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s) {
+const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, bool for_rollout) {
   const Dims d = dims_of(c);
   hipLaunchKernelGGL(stage_params_kernel, dim3((unsigned)((d.P + 255) / 256)), dim3(256), 0, s, params, scratch,
-                     param_map(d), (int)d.bf16);
+                     param_map(d), (int)d.bf16, (int)for_rollout);
   if (d.bf16) {
     const NetOffsets oa = net_offsets(0, d.D, d.Ha, kActions), oc = net_offsets(d.Pa, d.Dc, d.Hc, 1);
     stage_weights_bf16(params + oa.W1, params + oa.W2, d.D, d.Ha, effective_bf16_weights(c, scratch, 0), s);
@@ -248,7 +256,7 @@ int32_t launch_policy_forward(const marl_config& c, const float* params, const f
         d.Hc, direct(obs, value != nullptr ? Sc : 0, d.Dc, 1, net_offsets(d.Pa, d.Dc, d.Hc, 1)), fc, s);
   }
   const RolloutWsView w = carve_rollout_ws(c, n_rows, workspace, nullptr);
-  const float* eff = effective_params(c, params, w.eff_params, s);
+  const float* eff = effective_params(c, params, w.eff_params, s, false);
   return forward_rows(c, eff, obs, n_rows, w, logits != nullptr, logits, nullptr, value, s);
 }
 
@@ -279,6 +287,12 @@ static RolloutFusedArgs rollout_fused_args(const marl_config& c, marl_env_state 
   a.p = env_params(c);
   a.st = st;
   a.W1s = eff + pm.sw_w1[0]; a.W2s = eff + pm.sw_w2[0]; a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
+  if (pm.op_w1 >= 0) {
+    a.W1o = eff + pm.op_w1;
+    a.W2o = eff + pm.op_w2;
+  }
+  a.kpad1 = pm.kpad1[0];
+  a.px = fused_forward_px(d.D);
   return a;
 }
 
@@ -292,7 +306,7 @@ int32_t launch_rollout(const marl_config& c, marl_env_state st, const float* par
                        void* workspace, hipStream_t s, const uint64_t* step_base) {
   const Dims d = dims_of(c);
   const RolloutWsView w = carve_rollout_ws(c, d.N, workspace, nullptr);
-  const float* eff = effective_params(c, params, w.eff_params, s);
+  const float* eff = effective_params(c, params, w.eff_params, s, /*for_rollout=*/true);
   const int64_t NA = d.NA, slab = NA * d.D;
   int32_t rc;
   // The values do not steer the rollout (the parameters are constant during it): where the critic's forward pass
@@ -432,7 +446,7 @@ int32_t launch_evaluate(const marl_config& c, marl_env_state st, const float* pa
   const Dims d = dims_of(c);
   const EvalWsView e = carve_eval_ws(c, workspace, nullptr);
   const RolloutWsView w = carve_rollout_ws(c, d.N, e.rollout_ws, nullptr);
-  const float* eff = effective_params(c, params, w.eff_params, s);
+  const float* eff = effective_params(c, params, w.eff_params, s, false);
   const int64_t steps = (int64_t)n_episodes * c.episode_cap;
   if (use_fused_rollout(c)) {  // the whole block in one launch, statistics in registers
     RolloutFusedArgs a = rollout_fused_args(c, st, eff);

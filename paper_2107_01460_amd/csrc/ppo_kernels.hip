@@ -17,7 +17,7 @@ namespace marl {
 // implemented in policy_kernels.hip
 void mlp_hidden_forward(const RowSrc& X, int64_t S, int Din, int H, const float* W1, const float* b1, const float* W2,
                         const float* b2, float* h1, float* h2, bool bf16, hipStream_t s);
-const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s);
+const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, bool for_rollout);
 int64_t effective_param_floats(const marl_config& c);
 Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, int net);
 
@@ -536,7 +536,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
       UpdateWsView wk = w;  // the view the helpers get: this step's scalars
       wk.sc = sck;
       const int32_t* rows = (perm ? perm + (int64_t)e * R : w.ident) + (int64_t)mb * rows_mb;
-      const float* eff = effective_params(c, params, w.eff_params, s);
+      const float* eff = effective_params(c, params, w.eff_params, s, false);
       LossCommon lc{};
       lc.rows = rows; lc.A = d.A; lc.ad = make_small_div(d.A); lc.rows_mb = rows_mb; lc.inv_B = (float)(1.0 / (double)(rows_mb * d.A));
       lc.sc = sck; lc.adv_stats = w.adv_stats + 2 * step; lc.normalize = c.normalize_adv; lc.clip_eps = c.clip_eps;

@@ -11,8 +11,7 @@
 //
 // Both layers run on split bf16 operands, transposed (gemm_phase_t): the windows hold small integers and halves, exact in
 // bf16, so layer 1 takes half the products, h1 is split once, and the output layer starts from the registers that layer 2
-// ends in.  A step is a chain of latencies: 128 steps of 3072 samples at 128 units 0.84 ms (with fp32 tiles, split by every
-// wavefront that reads them, 1.0 ms), of 65 536 samples 4.7 ms (4.8).
+// ends in.  A step is a chain of latencies: 128 steps of 3072 samples at 128 units 0.84 ms, with fp32 tiles 1.0 ms.
 //
 // The same kernel with EVAL = true is the greedy evaluation block: argmax actions, no trajectory, and the
 // per-environment return / length / episode counts accumulated in registers.
@@ -26,6 +25,8 @@ struct RolloutFusedArgs {
   EnvParams p;
   marl_env_state st;
   const float *W1s, *W2s, *b1, *b2, *W3, *b3;  // actor: split operand-order W1 / W2, aligned biases and output layer
+  const float *W1o, *W2o;  // fp32 operand-order W1 / W2 (training rollouts; ParamMap)
+  int kpad1, px;           // ... rows of W1o, pitch of an fp32 window
   int T;  // steps to take
   // training rollout
   float* obs;  // [T+1][N][A][D]
@@ -58,6 +59,10 @@ __device__ __forceinline__ float log_softmax_fast(const float lg[kActions], int 
   }
   return la - m - __builtin_amdgcn_logf(se) * 0.6931471805599453f;
 }
+
+}  // namespace marl
+#include "rollout_fp32.h"
+namespace marl {
 
 // pitch of a window in LDS, in elements: the width rounded up to a k group, and an odd number of 16-byte units
 constexpr int rollout_fused_px(int D) { return (D + 15) / 16 * 16 + 8; }
@@ -323,10 +328,25 @@ __global__ void __launch_bounds__(256, OCC) rollout_fused_kernel(RolloutFusedArg
 
 // Networks and views the kernel is instantiated for: hidden width 64 (64-sample tiles) or 128 (32-sample tiles).
 inline bool rollout_fused_supported(int H, int A) { return (H == 64 || H == 128) && A <= 8; }
+// Workgroups up to which a training rollout is a chain of latencies (two per CU); beyond, rollout_fp32_kernel.
+constexpr unsigned kRolloutSplitGrid = 512;
 inline int rollout_fused_bm(int H) { return H == 64 ? 64 : 32; }
 
 template <int H, int BM, int V, int CA, int KIND, bool EVAL, int OCC = (CA <= 4 && V <= 5) ? 2 : 1>
 inline int32_t launch_rollout_fused_inst(const RolloutFusedArgs& a, hipStream_t s) {
+  const int epw = BM / a.p.A;
+  const unsigned grid = (unsigned)((a.p.N + epw - 1) / epw);
+  if constexpr (!EVAL) {
+    if (grid > kRolloutSplitGrid) {
+      auto kern32 = rollout_fp32_kernel<H, BM, V, CA, KIND, ((H == 64 && CA <= 2) || (CA <= 4 && V <= 5)) ? 3 : 1>;
+      const size_t bytes32 = (2 * (size_t)BM * a.px + (size_t)BM * (H + 4) + 256 * (size_t)kActions + (size_t)H * kActions + 2 * BM * 8) * sizeof(float);
+      if (bytes32 > 64 * 1024 &&
+          hipFuncSetAttribute(reinterpret_cast<const void*>(kern32), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+        return MARL_E_LAUNCH;
+      hipLaunchKernelGGL(kern32, dim3(grid), dim3(256), bytes32, s, a);
+      return launch_status();
+    }
+  }
   auto kern = rollout_fused_kernel<H, BM, V, CA, KIND, EVAL, OCC>;
   const size_t bytes = 2 * (size_t)BM * (2 * rollout_fused_px(3 * V * V) + 3 * (H + 8)) + sizeof(float) * ((H / 32) * kActions * BM + H * kActions + 2 * BM * 8 + 2 * H);
   static bool configured = false;  // per instantiation
@@ -335,8 +355,6 @@ inline int32_t launch_rollout_fused_inst(const RolloutFusedArgs& a, hipStream_t 
       return MARL_E_LAUNCH;
     configured = true;
   }
-  const int epw = BM / a.p.A;
-  const unsigned grid = (unsigned)((a.p.N + epw - 1) / epw);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(256), bytes, s, a);
   return launch_status();
 }
@@ -345,12 +363,7 @@ template <int V, int KIND, bool EVAL>
 inline int32_t launch_rollout_fused_view(int H, const RolloutFusedArgs& a, hipStream_t s) {
   const int cap = a.p.A > a.p.F ? a.p.A : a.p.F;  // every loop over entities is unrolled to the capacity
   if constexpr (V == 3 && KIND == 0) {  // the small foraging shape (two agents, one food): half the unrolled entity loops
-    if (cap <= 2 && H == 64) {
-      // three workgroups per CU cost spilled registers and pay where the chip is full: 4096 workgroups 2.25 against
-      // 2.66 ms, two workgroups 74 against 68 us
-      if (!EVAL && a.p.N > 512 * (64 / a.p.A)) return launch_rollout_fused_inst<64, 64, V, 2, KIND, EVAL, 3>(a, s);
-      return launch_rollout_fused_inst<64, 64, V, 2, KIND, EVAL>(a, s);
-    }
+    if (cap <= 2 && H == 64) return launch_rollout_fused_inst<64, 64, V, 2, KIND, EVAL>(a, s);
   }
   if (H == 64) {
     if (cap <= 4) return launch_rollout_fused_inst<64, 64, V, 4, KIND, EVAL>(a, s);
