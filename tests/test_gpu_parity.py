@@ -417,3 +417,27 @@ def test_greedy_evaluation_block(M, orc, k):
     host = gs.to_host()
     for f in M.EnvState.FIELDS:
         assert np.array_equal(host[f][..., clear], getattr(os_, f)[..., clear]), f
+
+
+# policy_forward changes kernels at 2048 samples (both networks in one launch on the unstaged parameters up to there): a call
+# on either side of the line against the same rows in small calls.  Two fp32 evaluations of sums of up to 300 terms through
+# two layers differ by a few units of 2^-24 of the output's scale: 5e-6 of it is 80 of them.
+@pytest.mark.parametrize("ha,hc,central,n_rows", [(128, 128, 0, 682), (128, 128, 0, 683), (64, 256, 1, 700), (256, 64, 1, 1031)])
+def test_forward_around_the_small_call_limit(M, ha, hc, central, n_rows):
+    cfg = dict(W.CONFIGS[1], n_envs=n_rows, rollout_len=1, n_minibatches=1, actor_hidden=ha, critic_hidden=hc, central_critic=central)
+    A, D = cfg["n_agents"], 3 * cfg["view"] ** 2
+    params = dev(W.init_params(cfg, bias_scale=0.1))
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    obs = torch.randint(0, 4, (n_rows, A, D), device="cuda", generator=gen).float()
+    ws = M.alloc_workspace(M.query_sizes(cfg).rollout_workspace_bytes)
+
+    def forward(x):
+        n = x.shape[0]
+        lg, v = torch.empty((n, A, 6), device="cuda"), torch.empty((n, A), device="cuda")
+        M.policy_forward(cfg, params, x, n, lg, v, ws)
+        return lg, v
+
+    lg, v = forward(obs)
+    parts = [forward(obs[i:i + 211].clone()) for i in range(0, n_rows, 211)]
+    for got, ref in ((lg, torch.cat([p[0] for p in parts])), (v, torch.cat([p[1] for p in parts]))):
+        assert torch.isfinite(got).all() and float((got - ref).abs().max()) < 5e-6 * float(ref.abs().max())
