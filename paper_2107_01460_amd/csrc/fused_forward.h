@@ -153,7 +153,15 @@ __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const 
       for (int q = 0; q < TPW; ++q)
         gemm_phase_direct<H>(L.Xs + (mt * 32 + lo) * px + 4 * hi, a.W1 + (nt0 + q) * 32 + lo, a.Din, hi, a.kpad1 / 16, acc[q]);
     } else {
-      gemm_phase_w_any<H, TPW>(L.Xs + (mt * 32 + lo) * px + 8 * hi, rsW1, wlane, a.kpad1 / 16, acc);
+      const float* const xa = L.Xs + (mt * 32 + lo) * px + 8 * hi;
+      gemm_phase_w_any<H, false, TPW>(xa, rsW1, wlane, a.kpad1 / 16, acc);
+      float all = 0.f;
+#pragma unroll
+      for (int q = 0; q < TPW; ++q) all = sum_of(all, acc[q]);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(all != all) != 0, 0)) {  // an input out of split_pair's range?
+        zero_acc();
+        gemm_phase_w_any<H, true, TPW>(xa, rsW1, wlane, a.kpad1 / 16, acc);
+      }
     }
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
@@ -176,7 +184,7 @@ __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const 
       for (int q = 0; q < TPW; ++q)
         gemm_phase_direct<H>(L.Hs + (mt * 32 + lo) * PH + 4 * hi, a.W2 + (nt0 + q) * 32 + lo, H, hi, H / 16, acc[q]);
     } else {
-      gemm_phase_w_any<H, TPW>(L.Hs + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, H / 16, acc);
+      gemm_phase_w_any<H, false, TPW>(L.Hs + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, H / 16, acc);
     }
     __syncthreads();  // every wavefront is past its last read of h1
 #pragma unroll

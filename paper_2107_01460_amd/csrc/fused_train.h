@@ -69,7 +69,7 @@ constexpr size_t fused_train_lds_floats(int H, int BM, int NOUT, int NW, int px,
 // acc[q] += A_q^T B over the samples kb0 .. kb0 + klen (a multiple of 16) of a row tile held in LDS: the NA column blocks
 // A_q at Ap + 32 q (pitch pa) and the NB column blocks B_q at Bp + 32 q (pitch pb), one of NA, NB being 1.  The values of
 // the next 16 samples are read before the matrix instructions of the current ones are issued.
-template <int NA, int NB>
+template <bool A_ANY, bool B_ANY, int NA, int NB>
 __device__ __forceinline__ void outer_product_accumulate(const float* __restrict__ Ap, int pa, const float* __restrict__ Bp,
                                                          int pb, int kb0, int klen, int hi, floatx16* acc) {
   static_assert(NA == 1 || NB == 1, "one block shared by the others");
@@ -88,9 +88,9 @@ __device__ __forceinline__ void outer_product_accumulate(const float* __restrict
   for (int kb = kb0; kb < kb0 + klen; kb += 16) {
     Split8 a[NA], b[NB];
 #pragma unroll
-    for (int q = 0; q < NA; ++q) a[q] = split8(af[q]);
+    for (int q = 0; q < NA; ++q) a[q] = split8<A_ANY>(af[q]);
 #pragma unroll
-    for (int q = 0; q < NB; ++q) b[q] = split8(bf[q]);
+    for (int q = 0; q < NB; ++q) b[q] = split8<B_ANY>(bf[q]);
     read(kb + 16 < kb0 + klen ? kb + 16 : kb);  // the last step re-reads its own operands
 #pragma unroll
     for (int q = 0; q < NA * NB; ++q) acc[q] = mfma_split(a[NA == 1 ? 0 : q], b[NB == 1 ? 0 : q], acc[q]);
@@ -127,15 +127,13 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   float* dls = red + NT * NOUT;           // [BM][8]
   float* W3s = dls + BM * 8;               // [H][NOUT]
   float* const xdump = W3s + H * NOUT;     // one float: where the staged values that are not part of a row go
+  int* const nan_note = reinterpret_cast<int*>(xdump + 1);
   float* const b3s = xdump + 4;            // [8] the output layer's bias
   // per-sample-slot sums that only the first BM threads touch, once per tile (b3 gradient, loss statistics): in LDS
   // rather than in 11 registers of every thread, which this kernel does not have to spare
   constexpr int AS = NOUT + 5;
   float* const accS = b3s + 8;             // [max(BM, 64)][AS]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lo = lane & 31, hi = lane >> 5;
-  const int mt = wave / NTN, nt = wave % NTN;  // forward / dz tile of this wavefront
   // where this workgroup's gradient goes: the gradient itself, or its own copy of the range
   float* const gout = a.partial != nullptr ? a.partial + (int64_t)bid * (a.pstride != 0 ? a.pstride : a.gcount) : a.gW1;
   // (a copy needs no zeroing: the flush at the end writes every one of its elements exactly once)
@@ -146,289 +144,315 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   float* const gW3 = gout + (a.gW3 - a.gW1);
   float* const gb3 = gout + (a.gb3 - a.gW1);
   const int px = a.px;
-  for (int i = tid; i < (XDB ? 2 : 1) * BM * px; i += NT) Xs0[i] = 0.f;  // the padding columns stay zero for good
-  for (int i = tid; i < H * NOUT; i += NT) W3s[i] = a.W3[i];
-  if (tid < NOUT) b3s[tid] = a.b3[tid];
-  __syncthreads();
-
   floatx16 acc1[Q1], acc2[DW2_TPW];  // dW1 / dW2 tiles of this wavefront, persistent
-#pragma unroll
-  for (int q = 0; q < Q1; ++q)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc1[q][r] = 0.f;
-#pragma unroll
-  for (int q = 0; q < DW2_TPW; ++q)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc2[q][r] = 0.f;
   float gw[NOUT];
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) gw[k] = 0.f;
-  for (int i = tid; i < (BM < 64 ? 64 : BM) * AS; i += NT) accS[i] = 0.f;  // ordered before its first use by the barriers below
-  float gb1r = 0.f, gb2r = 0.f;  // bias gradients of column nt*32+lo (lanes hi == 0)
-  // the biases of this lane's column, once: a load inside the tile loop would be waited for on the spot, and with it
-  // (loads return in order) the next tile's rows requested just before
-  const float bias1 = a.b1[nt * 32 + lo], bias2 = a.b2[nt * 32 + lo];
-  const int kpad1 = 16 * ((a.Din + 15) / 16);  // layer 1 contracts over the input width rounded up to a k group (W1 is zero-padded to it)
-  const int wlane = (hi * H + nt * 32 + lo) * 4;  // this lane's 16 bytes of k quad `hi` in an operand-order weight copy
-  const WeightRsrc rsW1 = split_weight_rsrc(a.W1s, kpad1, H), rsW2 = split_weight_rsrc(a.W2s, H, H), rsW2T = split_weight_rsrc(a.W2Ts, H, H);
+  float gb1r, gb2r;  // bias gradients of column nt*32+lo (lanes hi == 0)
+  // All of the workgroup's tiles.
+  auto train_tiles = [&](auto any) {
+    constexpr bool ANY = decltype(any)::value;
+    int tid = threadIdx.x;
+    if (ANY) asm volatile("" : "+v"(tid));  // no address is kept in registers from one form to the other
+    const int lane = tid & 63, wave = tid >> 6;
+    const int lo = lane & 31, hi = lane >> 5;
+    const int mt = wave / NTN, nt = wave % NTN;  // forward / dz tile of this wavefront
+    for (int i = tid; i < (XDB ? 2 : 1) * BM * px; i += NT) Xs0[i] = 0.f;  // the padding columns stay zero for good
+    for (int i = tid; i < H * NOUT; i += NT) W3s[i] = a.W3[i];
+    if (tid < NOUT) b3s[tid] = a.b3[tid];
+    if (!ANY && tid == 0) *nan_note = 0;
+    __syncthreads();
 
-  // ---- staging helpers.  The inputs of the next tile come in two steps: the gather entries at the top of a
-  // tile, the rows themselves half a tile later, so that neither dependent load is ever waited for.
-  // A row of X starts at any 4-byte boundary (its width need not be a multiple of four), so it is fetched as the
-  // aligned 16-byte chunks that cover it -- a few wide loads per thread instead of one 4-byte load per element,
-  // which the address path serves no faster -- and sorted out on the way into LDS: element j of chunk q is column
-  // 4 q + j - xoff of the row, xoff being where the row starts inside its first chunk.  (The base of X is 16-byte
-  // aligned and rows before / after a row exist, so the chunks never leave the buffer.)
-  float4 xr[XV];
-  int xoff = 0;
-  typename LossFn::In lin_next{};
-  int32_t xentry = 0, lentry = 0;
-  const int xrow_l = tid / TPR, xcol0 = tid % TPR;
-  const auto prep = fn.prepare();
-  // These requests are issued for every tile slot, also past a workgroup's last tile (row indices are clamped to the
-  // last sample and the values never used): with the same loads in every iteration the compiler can count the loads
-  // in flight and wait for exactly the ones it needs, where a conditional request makes every wait a wait for all.
-  auto fetch_tile_entries = [&](int64_t s0) {
-    xentry = a.X.template gather_entry<true>(min(s0 + xrow_l, a.S - 1));
-    if (tid < BM) lentry = fn.template row_entry<true>(min(s0 + tid, a.S - 1));
-  };
-  auto fetch_tile_inputs = [&](int64_t s0) {
-    const float* const row = a.X.template ptr_with<true>(min(s0 + xrow_l, a.S - 1), xentry);
-    xoff = (int)((reinterpret_cast<uintptr_t>(row) >> 2) & 3);
-    // (pointer arithmetic, not an integer round trip: the loads stay global loads -- a flat load also counts as an
-    // LDS operation, and every barrier would wait for these rows)
-    const float4* const chunk = reinterpret_cast<const float4*>(row - xoff);
-    const int last = ((xoff + a.Din + 3) >> 2) - 1;  // chunks past the row: the last one again (none of its elements is stored)
 #pragma unroll
-    for (int p = 0; p < XV; ++p) xr[p] = chunk[min(xcol0 + TPR * p, last)];
-  };
-  // (the loss inputs of the next tile are requested right after the loss of the current one, into the same registers)
-  auto fetch_tile_loss_inputs = [&](int64_t s0) {
-    if (tid < BM) lin_next = fn.template load_with<true>(min(s0 + tid, a.S - 1), lentry);
-  };
-  auto store_tile_inputs = [&](float* Xdst) {
-    float* const xdst = Xdst + xrow_l * px - xoff;
+    for (int q = 0; q < Q1; ++q)
 #pragma unroll
-    for (int p = 0; p < XV; ++p) {
-      const float v[4] = {xr[p].x, xr[p].y, xr[p].z, xr[p].w};
+      for (int r = 0; r < 16; ++r) acc1[q][r] = 0.f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = 4 * (xcol0 + TPR * p) + j - xoff;
-        float* const dst = (c >= 0 && c < a.Din) ? xdst + 4 * (xcol0 + TPR * p) + j : xdump;
-        *dst = v[j];
+    for (int q = 0; q < DW2_TPW; ++q)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc2[q][r] = 0.f;
+#pragma unroll
+    for (int k = 0; k < NOUT; ++k) gw[k] = 0.f;
+    for (int i = tid; i < (BM < 64 ? 64 : BM) * AS; i += NT) accS[i] = 0.f;  // ordered before its first use by the barriers below
+    gb1r = gb2r = 0.f;
+    // the biases of this lane's column, once: a load inside the tile loop would be waited for on the spot, and with it
+    // (loads return in order) the next tile's rows requested just before
+    const float bias1 = a.b1[nt * 32 + lo], bias2 = a.b2[nt * 32 + lo];
+    const int kpad1 = 16 * ((a.Din + 15) / 16);  // layer 1 contracts over the input width rounded up to a k group (W1 is zero-padded to it)
+    const int wlane = (hi * H + nt * 32 + lo) * 4;  // this lane's 16 bytes of k quad `hi` in an operand-order weight copy
+    const WeightRsrc rsW1 = split_weight_rsrc(a.W1s, kpad1, H), rsW2 = split_weight_rsrc(a.W2s, H, H), rsW2T = split_weight_rsrc(a.W2Ts, H, H);
+
+    // ---- staging helpers.  The inputs of the next tile come in two steps: the gather entries at the top of a
+    // tile, the rows themselves half a tile later, so that neither dependent load is ever waited for.
+    // A row of X starts at any 4-byte boundary (its width need not be a multiple of four), so it is fetched as the
+    // aligned 16-byte chunks that cover it -- a few wide loads per thread instead of one 4-byte load per element,
+    // which the address path serves no faster -- and sorted out on the way into LDS: element j of chunk q is column
+    // 4 q + j - xoff of the row, xoff being where the row starts inside its first chunk.  (The base of X is 16-byte
+    // aligned and rows before / after a row exist, so the chunks never leave the buffer.)
+    float4 xr[XV];
+    int xoff = 0;
+    typename LossFn::In lin_next{};
+    int32_t xentry = 0, lentry = 0;
+    const int xrow_l = tid / TPR, xcol0 = tid % TPR;
+    const auto prep = fn.prepare();
+    // These requests are issued for every tile slot, also past a workgroup's last tile (row indices are clamped to the
+    // last sample and the values never used): with the same loads in every iteration the compiler can count the loads
+    // in flight and wait for exactly the ones it needs, where a conditional request makes every wait a wait for all.
+    auto fetch_tile_entries = [&](int64_t s0) {
+      xentry = a.X.template gather_entry<true>(min(s0 + xrow_l, a.S - 1));
+      if (tid < BM) lentry = fn.template row_entry<true>(min(s0 + tid, a.S - 1));
+    };
+    auto fetch_tile_inputs = [&](int64_t s0) {
+      const float* const row = a.X.template ptr_with<true>(min(s0 + xrow_l, a.S - 1), xentry);
+      xoff = (int)((reinterpret_cast<uintptr_t>(row) >> 2) & 3);
+      // (pointer arithmetic, not an integer round trip: the loads stay global loads -- a flat load also counts as an
+      // LDS operation, and every barrier would wait for these rows)
+      const float4* const chunk = reinterpret_cast<const float4*>(row - xoff);
+      const int last = ((xoff + a.Din + 3) >> 2) - 1;  // chunks past the row: the last one again (none of its elements is stored)
+#pragma unroll
+      for (int p = 0; p < XV; ++p) xr[p] = chunk[min(xcol0 + TPR * p, last)];
+    };
+    // (the loss inputs of the next tile are requested right after the loss of the current one, into the same registers)
+    auto fetch_tile_loss_inputs = [&](int64_t s0) {
+      if (tid < BM) lin_next = fn.template load_with<true>(min(s0 + tid, a.S - 1), lentry);
+    };
+    auto store_tile_inputs = [&](float* Xdst) {
+      float* const xdst = Xdst + xrow_l * px - xoff;
+#pragma unroll
+      for (int p = 0; p < XV; ++p) {
+        const float v[4] = {xr[p].x, xr[p].y, xr[p].z, xr[p].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int c = 4 * (xcol0 + TPR * p) + j - xoff;
+          float* const dst = (c >= 0 && c < a.Din) ? xdst + 4 * (xcol0 + TPR * p) + j : xdump;
+          *dst = v[j];
+        }
       }
+    };
+    const int64_t ntiles = (a.S + BM - 1) / BM;
+    int64_t tile = bid;
+    if (tile < ntiles) {
+      fetch_tile_entries(tile * BM);
+      fetch_tile_inputs(tile * BM);
+      fetch_tile_loss_inputs(tile * BM);
+      fetch_tile_entries((tile + nblk) * BM);
     }
-  };
-  const int64_t ntiles = (a.S + BM - 1) / BM;
-  int64_t tile = bid;
-  if (tile < ntiles) {
-    fetch_tile_entries(tile * BM);
-    fetch_tile_inputs(tile * BM);
-    fetch_tile_loss_inputs(tile * BM);
-    fetch_tile_entries((tile + nblk) * BM);
-  }
 #ifdef MARL_PHASE_TIMERS
-  long long phase_t0_ = (long long)__builtin_amdgcn_s_memtime();
+    long long phase_t0_ = (long long)__builtin_amdgcn_s_memtime();
 #endif
-  if (XDB && tile < ntiles) {
-    store_tile_inputs(Xs0);
-    __syncthreads();
-  }
-  PhaseW<KG1> pw1;  // layer 1's weights: the first of them requested before dW1 of the tile before (here for the first tile)
-  phase_w_request<H, KG1>(pw1, rsW1, wlane, kpad1 / 16);
-  for (int it = 0; tile < ntiles; tile += nblk, ++it) {
-    const int64_t s0 = tile * BM;
-    const bool have_next = tile + nblk < ntiles;
-    float* const Xs = XDB ? Xs0 + (it & 1) * BM * px : Xs0;
-    if (!XDB) {  // ---- this tile's observations to LDS
-      store_tile_inputs(Xs);
+    if (XDB && tile < ntiles) {
+      store_tile_inputs(Xs0);
+      __syncthreads();
     }
-    if (!XDB) __syncthreads();
+    PhaseW<KG1> pw1;  // layer 1's weights: the first of them requested before dW1 of the tile before (here for the first tile)
+    phase_w_request<H, KG1>(pw1, rsW1, wlane, kpad1 / 16);
+    for (int it = 0; tile < ntiles; tile += nblk, ++it) {
+      const int64_t s0 = tile * BM;
+      const bool have_next = tile + nblk < ntiles;
+      float* const Xs = XDB ? Xs0 + (it & 1) * BM * px : Xs0;
+      if (!XDB) {  // ---- this tile's observations to LDS
+        store_tile_inputs(Xs);
+      }
+      if (!XDB) __syncthreads();
 
-    PHASE_MARK(0);
-    floatx16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    // ---- layer 1
-    gemm_phase_w<H, KG1>(Xs + (mt * 32 + lo) * px + 8 * hi, rsW1, wlane, kpad1 / 16, &acc, pw1);
-    PhaseW<KG2> pw2;  // layer 2's weights arrive during the tanh epilogue of layer 1
-    phase_w_request<H, KG2>(pw2, rsW2, wlane, KG2);
-    PHASE_MARK(1);
-    {
-      const int n = nt * 32 + lo;
-      const float bias = bias1;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        float v = tanh_f32(acc[r] + bias);
-        H1[m * PH + n] = v;
-        acc[r] = 0.f;
-        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    PHASE_MARK(2);
-    // ---- layer 2
-    __syncthreads();  // the h1 tile is complete
-    gemm_phase_w<H, KG2>(H1 + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, KG2, &acc, pw2);
-    PHASE_MARK(3);
-    fetch_tile_inputs((tile + nblk) * BM);  // lands during the ALU phases and dW2
-    floatx16 h2r;  // h2 of this wavefront's tile
-    {
-      const int n = nt * 32 + lo;
-      const float bias = bias2;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        float v = tanh_f32(acc[r] + bias);
-        h2r[r] = v;
-        H2[m * PH + n] = v;
-        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    __syncthreads();
-    PHASE_MARK(4);
-    // ---- output layer on the ALUs: thread -> (sample tid % BM, slice tid / BM of the hidden units); 16-byte LDS reads
-    {
-      const int s = tid % BM, grp = tid / BM;
-      constexpr int PER = H / GROUPS;
-      static_assert(PER % 4 == 0, "hidden units are read four at a time");
-      float part[NOUT];
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) part[k] = 0.f;
-#pragma unroll 2
-      for (int i = grp * PER; i < (grp + 1) * PER; i += 4) {
-        const float4 hv = *reinterpret_cast<const float4*>(&H2[s * PH + i]);
-        const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
-        float wv[4 * NOUT];  // W3 rows i..i+3: 4 * NOUT consecutive floats, the same for every lane of the wavefront
-#pragma unroll
-        for (int q = 0; q < NOUT; ++q) {
-          const float4 t = *reinterpret_cast<const float4*>(&W3s[i * NOUT + 4 * q]);
-          wv[4 * q] = t.x; wv[4 * q + 1] = t.y; wv[4 * q + 2] = t.z; wv[4 * q + 3] = t.w;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int k = 0; k < NOUT; ++k) part[k] = fmaf(hh[j], wv[j * NOUT + k], part[k]);
-      }
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) red[(grp * NOUT + k) * BM + s] = part[k];
-    }
-    __syncthreads();
-    PHASE_MARK(5);
-    if (tid < BM) {
-      float out[NOUT], dl[NOUT];
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) {
-        float v = b3s[k];
-#pragma unroll
-        for (int gq = 0; gq < GROUPS; ++gq) v += red[(gq * NOUT + k) * BM + tid];
-        out[k] = v;
-        dl[k] = 0.f;
-      }
-      float st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-      if (s0 + tid < a.S) fn.compute(lin_next, prep, out, dl, st);
-      float d8[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) d8[k] = k < NOUT ? dl[k < NOUT ? k : 0] : 0.f;
-      *reinterpret_cast<float4*>(&dls[tid * 8]) = make_float4(d8[0], d8[1], d8[2], d8[3]);
-      *reinterpret_cast<float4*>(&dls[tid * 8 + 4]) = make_float4(d8[4], d8[5], d8[6], d8[7]);
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) accS[tid * AS + k] += dl[k];
-#pragma unroll
-      for (int k = 0; k < 5; ++k) accS[tid * AS + NOUT + k] += st[k];
-    }
-    fetch_tile_loss_inputs((tile + nblk) * BM);
-    // the gather entries of the tile after the next: requested here, where the next wait on a global load (the weights
-    // of the dz1 product) is a whole dW2 phase away, and not in front of layer 1, whose first in-loop weight group
-    // would wait for them (loads return in order)
-    fetch_tile_entries((tile + 2 * (int64_t)nblk) * BM);
-    __syncthreads();
-    PHASE_MARK(6);
-    // ---- W3 gradient: gW3[i][k] += sum_s h2[s][i] dl[s][k]   (thread -> hidden unit tid % H, a share of the samples)
-    {
-      const int i = tid % H, part = tid / H;
-#pragma unroll 4
-      for (int s = part * SPP; s < (part + 1) * SPP; ++s) {
-        const float h = H2[s * PH + i];
-        const float4 d0 = *reinterpret_cast<const float4*>(&dls[s * 8]);
-        float dv[8] = {d0.x, d0.y, d0.z, d0.w, 0.f, 0.f, 0.f, 0.f};
-        if (NOUT > 4) {
-          const float4 d1 = *reinterpret_cast<const float4*>(&dls[s * 8 + 4]);
-          dv[4] = d1.x; dv[5] = d1.y; dv[6] = d1.z; dv[7] = d1.w;
-        }
-#pragma unroll
-        for (int k = 0; k < NOUT; ++k) gw[k] = fmaf(h, dv[k], gw[k]);
-      }
-    }
-    __syncthreads();
-    PHASE_MARK(7);
-    // ---- dz2 = (dl W3^T) * (1 - h2^2) -> LDS over h2; the rank-NOUT product runs on the matrix cores (k padded to 8)
-    {
-      const int n = nt * 32 + lo;
-      const float4 av = *reinterpret_cast<const float4*>(&dls[(mt * 32 + lo) * 8 + 4 * hi]);
-      const float af[4] = {av.x, av.y, av.z, av.w};
-      float bf[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bf[j] = (4 * hi + j < NOUT) ? W3s[n * NOUT + (4 * hi + j < NOUT ? 4 * hi + j : 0)] : 0.f;
+      PHASE_MARK(0);
+      floatx16 acc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+      // ---- layer 1
+      gemm_phase_w<H, ANY, KG1>(Xs + (mt * 32 + lo) * px + 8 * hi, rsW1, wlane, kpad1 / 16, &acc, pw1);
+      PhaseW<KG2> pw2;  // layer 2's weights arrive during the tanh epilogue of layer 1
+      phase_w_request<H, KG2>(pw2, rsW2, wlane, KG2);
+      PHASE_MARK(1);
+      {
+        const int n = nt * 32 + lo;
+        const float bias = bias1;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], bf[j], acc, 0, 0, 0);
-      float csum = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        float v = acc[r] * (1.0f - h2r[r] * h2r[r]);
-        H2[m * PH + n] = v;
-        csum += v;
+        for (int r = 0; r < 16; ++r) {
+          const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
+          float v = tanh_f32(acc[r] + bias);
+          H1[m * PH + n] = v;
+          acc[r] = 0.f;
+          if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
       }
-      csum += __shfl_xor(csum, 32);
-      gb2r += csum;
-    }
-    __syncthreads();
-    PHASE_MARK(8);
-    PhaseW<KG2> pwz;  // the weights of the dz1 product arrive during dW2, whose operands are all in LDS
-    phase_w_request<H, KG2>(pwz, rsW2T, wlane, KG2);
-    // ---- dW2 += h1^T dz2   (k runs over the samples of the tile)
-    {
-      const int t0 = (wave * DW2_TPW) % (NTN * NTN);
-      const int it = t0 / NTN, jt = t0 % NTN;
-      const int ks = (wave * DW2_TPW) / (NTN * NTN);
-      constexpr int KLEN = BM / DW2_KS;
-      outer_product_accumulate<1, DW2_TPW>(H1 + it * 32 + lo, PH, H2 + jt * 32 + lo, PH, ks * KLEN, KLEN, hi, acc2);
-    }
-    PHASE_MARK(9);
-    // ---- dz1 = (dz2 W2^T) * (1 - h1^2), in place over h1
+      PHASE_MARK(2);
+      // ---- layer 2
+      __syncthreads();  // the h1 tile is complete
+      gemm_phase_w<H, false, KG2>(H1 + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, KG2, &acc, pw2);
+      PHASE_MARK(3);
+      fetch_tile_inputs((tile + nblk) * BM);  // lands during the ALU phases and dW2
+      floatx16 h2r;  // h2 of this wavefront's tile
+      {
+        const int n = nt * 32 + lo;
+        const float bias = bias2;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    gemm_phase_w<H, KG2>(H2 + (mt * 32 + lo) * PH + 8 * hi, rsW2T, wlane, KG2, &acc, pwz);
-    __syncthreads();  // every wavefront is done reading h1 (dW2) before its tiles are overwritten
-    PHASE_MARK(10);
-    {
-      const int n = nt * 32 + lo;
-      float csum = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        const float h = H1[m * PH + n];
-        float v = acc[r] * (1.0f - h * h);
-        H1[m * PH + n] = v;  // only this wavefront touches its tile of h1 from here on until the barrier
-        csum += v;
+        for (int r = 0; r < 16; ++r) {
+          const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
+          float v = tanh_f32(acc[r] + bias);
+          h2r[r] = v;
+          H2[m * PH + n] = v;
+          if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
       }
-      csum += __shfl_xor(csum, 32);
-      gb1r += csum;
+      __syncthreads();
+      PHASE_MARK(4);
+      // ---- output layer on the ALUs: thread -> (sample tid % BM, slice tid / BM of the hidden units); 16-byte LDS reads
+      {
+        const int s = tid % BM, grp = tid / BM;
+        constexpr int PER = H / GROUPS;
+        static_assert(PER % 4 == 0, "hidden units are read four at a time");
+        float part[NOUT];
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) part[k] = 0.f;
+#pragma unroll 2
+        for (int i = grp * PER; i < (grp + 1) * PER; i += 4) {
+          const float4 hv = *reinterpret_cast<const float4*>(&H2[s * PH + i]);
+          const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
+          float wv[4 * NOUT];  // W3 rows i..i+3: 4 * NOUT consecutive floats, the same for every lane of the wavefront
+#pragma unroll
+          for (int q = 0; q < NOUT; ++q) {
+            const float4 t = *reinterpret_cast<const float4*>(&W3s[i * NOUT + 4 * q]);
+            wv[4 * q] = t.x; wv[4 * q + 1] = t.y; wv[4 * q + 2] = t.z; wv[4 * q + 3] = t.w;
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int k = 0; k < NOUT; ++k) part[k] = fmaf(hh[j], wv[j * NOUT + k], part[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) red[(grp * NOUT + k) * BM + s] = part[k];
+      }
+      __syncthreads();
+      PHASE_MARK(5);
+      if (tid < BM) {
+        float out[NOUT], dl[NOUT];
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) {
+          float v = b3s[k];
+#pragma unroll
+          for (int gq = 0; gq < GROUPS; ++gq) v += red[(gq * NOUT + k) * BM + tid];
+          out[k] = v;
+          dl[k] = 0.f;
+        }
+        float st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+        if (s0 + tid < a.S) fn.compute(lin_next, prep, out, dl, st);
+        float d8[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) d8[k] = k < NOUT ? dl[k < NOUT ? k : 0] : 0.f;
+        *reinterpret_cast<float4*>(&dls[tid * 8]) = make_float4(d8[0], d8[1], d8[2], d8[3]);
+        *reinterpret_cast<float4*>(&dls[tid * 8 + 4]) = make_float4(d8[4], d8[5], d8[6], d8[7]);
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) accS[tid * AS + k] += dl[k];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) accS[tid * AS + NOUT + k] += st[k];
+      }
+      fetch_tile_loss_inputs((tile + nblk) * BM);
+      // the gather entries of the tile after the next: requested here, where the next wait on a global load (the weights
+      // of the dz1 product) is a whole dW2 phase away, and not in front of layer 1, whose first in-loop weight group
+      // would wait for them (loads return in order)
+      fetch_tile_entries((tile + 2 * (int64_t)nblk) * BM);
+      __syncthreads();
+      PHASE_MARK(6);
+      // ---- W3 gradient: gW3[i][k] += sum_s h2[s][i] dl[s][k]   (thread -> hidden unit tid % H, a share of the samples)
+      {
+        const int i = tid % H, part = tid / H;
+#pragma unroll 4
+        for (int s = part * SPP; s < (part + 1) * SPP; ++s) {
+          const float h = H2[s * PH + i];
+          const float4 d0 = *reinterpret_cast<const float4*>(&dls[s * 8]);
+          float dv[8] = {d0.x, d0.y, d0.z, d0.w, 0.f, 0.f, 0.f, 0.f};
+          if (NOUT > 4) {
+            const float4 d1 = *reinterpret_cast<const float4*>(&dls[s * 8 + 4]);
+            dv[4] = d1.x; dv[5] = d1.y; dv[6] = d1.z; dv[7] = d1.w;
+          }
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) gw[k] = fmaf(h, dv[k], gw[k]);
+        }
+      }
+      __syncthreads();
+      PHASE_MARK(7);
+      // ---- dz2 = (dl W3^T) * (1 - h2^2) -> LDS over h2; the rank-NOUT product runs on the matrix cores (k padded to 8)
+      {
+        const int n = nt * 32 + lo;
+        const float4 av = *reinterpret_cast<const float4*>(&dls[(mt * 32 + lo) * 8 + 4 * hi]);
+        const float af[4] = {av.x, av.y, av.z, av.w};
+        float bf[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bf[j] = (4 * hi + j < NOUT) ? W3s[n * NOUT + (4 * hi + j < NOUT ? 4 * hi + j : 0)] : 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], bf[j], acc, 0, 0, 0);
+        float csum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
+          float v = acc[r] * (1.0f - h2r[r] * h2r[r]);
+          H2[m * PH + n] = v;
+          csum += v;
+        }
+        csum += __shfl_xor(csum, 32);
+        gb2r += csum;
+      }
+      __syncthreads();
+      PHASE_MARK(8);
+      PhaseW<KG2> pwz;  // the weights of the dz1 product arrive during dW2, whose operands are all in LDS
+      phase_w_request<H, KG2>(pwz, rsW2T, wlane, KG2);
+      // ---- dW2 += h1^T dz2   (k runs over the samples of the tile)
+      {
+        const int t0 = (wave * DW2_TPW) % (NTN * NTN);
+        const int it = t0 / NTN, jt = t0 % NTN;
+        const int ks = (wave * DW2_TPW) / (NTN * NTN);
+        constexpr int KLEN = BM / DW2_KS;
+        outer_product_accumulate<false, ANY, 1, DW2_TPW>(H1 + it * 32 + lo, PH, H2 + jt * 32 + lo, PH, ks * KLEN, KLEN, hi, acc2);
+      }
+      PHASE_MARK(9);
+      // ---- dz1 = (dz2 W2^T) * (1 - h1^2), in place over h1
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+      gemm_phase_w<H, ANY, KG2>(H2 + (mt * 32 + lo) * PH + 8 * hi, rsW2T, wlane, KG2, &acc, pwz);
+      __syncthreads();  // every wavefront is done reading h1 (dW2) before its tiles are overwritten
+      PHASE_MARK(10);
+      {
+        const int n = nt * 32 + lo;
+        float csum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
+          const float h = H1[m * PH + n];
+          float v = acc[r] * (1.0f - h * h);
+          H1[m * PH + n] = v;  // only this wavefront touches its tile of h1 from here on until the barrier
+          csum += v;
+        }
+        csum += __shfl_xor(csum, 32);
+        gb1r += csum;
+      }
+      if (XDB && have_next) store_tile_inputs(Xs0 + ((it & 1) ^ 1) * BM * px);  // the next tile's observations
+      __syncthreads();
+      PHASE_MARK(11);
+      // ---- dW1 += X^T dz1   (the next tile's layer-1 weights arrive meanwhile)
+      phase_w_request<H, KG1>(pw1, rsW1, wlane, kpad1 / 16);
+      outer_product_accumulate<ANY, ANY, Q1, 1>(Xs + lo, px, H1 + (wave % NTN) * 32 + lo, PH, (wave / NTN) * KLEN1, KLEN1, hi, acc1);
+      PHASE_MARK(12);
+      __syncthreads();  // the tile buffers are reused by the next row tile
+      PHASE_MARK(13);
     }
-    if (XDB && have_next) store_tile_inputs(Xs0 + ((it & 1) ^ 1) * BM * px);  // the next tile's observations
+
+  };
+  train_tiles(std::false_type{});
+  {
+    float all = 0.f;
+#pragma unroll
+    for (int q = 0; q < Q1; ++q) all = sum_of(all, acc1[q]);
+#pragma unroll
+    for (int q = 0; q < DW2_TPW; ++q) all = sum_of(all, acc2[q]);
+    if (__builtin_amdgcn_ballot_w64(all != all) != 0) *nan_note = 1;
     __syncthreads();
-    PHASE_MARK(11);
-    // ---- dW1 += X^T dz1   (the next tile's layer-1 weights arrive meanwhile)
-    phase_w_request<H, KG1>(pw1, rsW1, wlane, kpad1 / 16);
-    outer_product_accumulate<Q1, 1>(Xs + lo, px, H1 + (wave % NTN) * 32 + lo, PH, (wave / NTN) * KLEN1, KLEN1, hi, acc1);
-    PHASE_MARK(12);
-    __syncthreads();  // the tile buffers are reused by the next row tile
-    PHASE_MARK(13);
+    if (__builtin_expect(__builtin_amdgcn_readfirstlane(*nan_note) != 0, 0)) train_tiles(std::true_type{});
   }
 
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lo = lane & 31, hi = lane >> 5;
+  const int mt = wave / NTN, nt = wave % NTN;
   // ---- flush the register-resident gradients.  Into the workgroup's own copy (a.partial): where several wavefronts
   // (or threads) hold parts of one sum, the parts of all but the first contributor go through LDS (the tile buffers
   // are free now) and the first contributor adds them in a FIXED order before one plain store, so that the copy --
@@ -558,7 +582,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
 
 template <int H, int BM, int NOUT, int DMAX, int NW, class LossFn>
 __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) fused_train_kernel(FusedTrainArgs a, LossFn fn) {
-  fused_train_body<H, BM, NOUT, DMAX, NW, LossFn>(a, fn, blockIdx.x, gridDim.x);
+  fused_train_body<H, BM, NOUT, DMAX, NW>(a, fn, blockIdx.x, gridDim.x);
 }
 
 // Two networks of the same shape on the same number of samples in ONE launch: workgroups 0 .. grid_a - 1 train the
@@ -567,8 +591,8 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) fused_train_kernel(F
 template <int H, int BM, int NOUT_A, int NOUT_B, int DMAX, int NW, class LossA, class LossB>
 __global__ void __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) fused_train_pair_kernel(FusedTrainArgs a, LossA fa, FusedTrainArgs b,
                                                                                    LossB fb, unsigned grid_a) {
-  if (blockIdx.x < grid_a) fused_train_body<H, BM, NOUT_A, DMAX, NW, LossA>(a, fa, blockIdx.x, grid_a);
-  else fused_train_body<H, BM, NOUT_B, DMAX, NW, LossB>(b, fb, blockIdx.x - grid_a, gridDim.x - grid_a);
+  if (blockIdx.x < grid_a) fused_train_body<H, BM, NOUT_A, DMAX, NW>(a, fa, blockIdx.x, grid_a);
+  else fused_train_body<H, BM, NOUT_B, DMAX, NW>(b, fb, blockIdx.x - grid_a, gridDim.x - grid_a);
 }
 
 // (an input row is staged as the aligned 16-byte chunks that cover it: up to three values more than its width)

@@ -7,6 +7,7 @@
 // in place from the trajectory.
 #pragma once
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "split_bf16.h"
@@ -184,15 +185,15 @@ __device__ __forceinline__ void phase_w_request(PhaseW<KG, NT>& pw, WeightRsrc B
 }
 // acc[q] += A B_q for this wavefront's 32x32 tiles: A rows in LDS (As points at this lane's row, + 8 * hi; the values of
 // the next group are read before the matrix instructions of the current one).  Both operands are readable (zero-padded) up
-// to 16 * kgroups along k.
-template <int H, int KG, int NT = 1>
+// to 16 * kgroups along k.  ANY: A may hold values out of split_pair's range.
+template <int H, bool ANY, int KG, int NT = 1>
 __device__ __forceinline__ void gemm_phase_w(const float* __restrict__ As, WeightRsrc B, int lane_off, int kgroups, floatx16* acc, PhaseW<KG, NT>& pw) {
   constexpr int RING = PhaseW<KG, NT>::RING;
   float4 a0 = *reinterpret_cast<const float4*>(As), a1 = *reinterpret_cast<const float4*>(As + 4);
 #pragma unroll
   for (int g = 0; g < KG; ++g) {
     if (g < kgroups) {  // uniform
-      const Split8 a = split8(a0, a1);
+      const Split8 a = split8<ANY>(a0, a1);
       const int gn = g + 1 < kgroups ? g + 1 : g;
       a0 = *reinterpret_cast<const float4*>(As + 16 * gn);
       a1 = *reinterpret_cast<const float4*>(As + 16 * gn + 4);
@@ -226,7 +227,7 @@ __device__ __forceinline__ void gemm_phase_t(const bf16_t* xs, int plane, Weight
 }
 
 // gemm_phase_w with a run-time number of groups, no request ahead: the groups in flight are the one in use and two on their way.
-template <int H, int NT>
+template <int H, bool ANY, int NT>
 __device__ __forceinline__ void gemm_phase_w_any(const float* __restrict__ As, WeightRsrc B, int lane_off, int kgroups, floatx16* acc) {
   PhaseW<3, NT> pw;
   phase_w_load<H>(pw, B, lane_off, 0, kgroups);
@@ -239,7 +240,7 @@ __device__ __forceinline__ void gemm_phase_w_any(const float* __restrict__ As, W
       if (d < rest) {  // uniform
         phase_w_load_at<H>(pw, (d + 2) % 3, B, lane_off, min(g0 + d + 2, kgroups - 1));
         const float* const p = As + 16 * (g0 + d);
-        const Split8 a = split8(*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4));
+        const Split8 a = split8<ANY>(*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4));
 #pragma unroll
         for (int q = 0; q < NT; ++q) acc[q] = mfma_split(a, Split8{pw.w[d][q][0], pw.w[d][q][1], pw.w[d][q][2]}, acc[q]);
       }
@@ -328,7 +329,8 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   }
 
   // ---- global -> registers.  Indices past the end are clamped to the last element: rows and columns past the end feed
-  // outputs that are never stored, and of the k past the end one operand is set to zero.
+  // outputs that are never stored; of the k past the end both operands are set to zero (zero times the infinity that the
+  // last element may be would be a NaN).
   float4 ra[A_VECS], rb[B_VECS];
   const float* arow[A_VECS];           // A_KCONT: this thread's rows
   int q[A_VECS], rem[A_VECS];          // TN: gather index and agent of this thread's next row of A, advanced by BK per stage
@@ -338,13 +340,6 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   if (A_KCONT) {
 #pragma unroll
     for (int p = 0; p < A_VECS; ++p) arow[p] = g.A.ptr(min(m0 + ((tid + 256 * p) >> 3), g.M - 1));
-  } else {
-#pragma unroll
-    for (int p = 0; p < A_VECS; ++p) {
-      const uint32_t k = (uint32_t)k_begin + (tid + 256 * p) / (BM / 4);
-      q[p] = (int)(k / (uint32_t)per);
-      rem[p] = (int)(k - q[p] * per);
-    }
   }
   auto fetch_entries = [&]() {  // TN with gathered rows: entries of the stage that (q, rem) stands at
     if (MODE == GEMM_TN && g.A.gather != nullptr) {
@@ -383,6 +378,7 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
         } else {
           ra[p] = make_float4(src[min(m, g.M - 1)], src[min(m + 1, g.M - 1)], src[min(m + 2, g.M - 1)], src[min(m + 3, g.M - 1)]);
         }
+        if (past) ra[p] = make_float4(0.f, 0.f, 0.f, 0.f);
         q[p] += dq;
         rem[p] += dr;
         if (rem[p] >= per) {
@@ -395,73 +391,92 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
 #pragma unroll
     for (int p = 0; p < B_VECS; ++p) {
       const int f = tid + 256 * p;
-      if (B_KCONT) {  // k past the end meets a zero of A
+      if (B_KCONT) {  // (K is a multiple of the k tile: a hidden width, or two or three of them)
         const int64_t k = k0 + 4 * (f & 7), n = n0 + (f >> 3);
         rb[p] = *reinterpret_cast<const float4*>(g.B + min(n, g.N - 1) * g.ldb + min(k, k_end - 4));
       } else {
         const int64_t k = k0 + f / (BN / 4), n = n0 + 4 * (f % (BN / 4));
-        float4 v = *reinterpret_cast<const float4*>(g.B + min(k, k_end - 1) * g.ldb + min(n, g.N - 4));
-        if (MODE == GEMM_TN && k >= k_end) v = make_float4(0.f, 0.f, 0.f, 0.f);
-        rb[p] = v;
+        const float4 v = *reinterpret_cast<const float4*>(g.B + min(k, k_end - 1) * g.ldb + min(n, g.N - 4));
+        rb[p] = k < k_end ? v : make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
   };
-  auto stage = [&]() {
+  auto stage = [&](auto any) {
+    constexpr bool ANY = decltype(any)::value;
 #pragma unroll
     for (int p = 0; p < A_VECS; ++p) {
       const int f = tid + 256 * p;
-      store_split4(A_KCONT ? &As[(f >> 3) * PK + 4 * (f & 7)] : &As[(f / (BM / 4)) * PMA + 4 * (f % (BM / 4))], A_PLANE, ra[p]);
+      store_split4<ANY>(A_KCONT ? &As[(f >> 3) * PK + 4 * (f & 7)] : &As[(f / (BM / 4)) * PMA + 4 * (f % (BM / 4))], A_PLANE, ra[p]);
     }
 #pragma unroll
     for (int p = 0; p < B_VECS; ++p) {
       const int f = tid + 256 * p;
-      store_split4(B_KCONT ? &Bs[(f >> 3) * PK + 4 * (f & 7)] : &Bs[(f / (BN / 4)) * PNB + 4 * (f % (BN / 4))], B_PLANE, rb[p]);
+      store_split4<ANY>(B_KCONT ? &Bs[(f >> 3) * PK + 4 * (f & 7)] : &Bs[(f / (BN / 4)) * PNB + 4 * (f % (BN / 4))], B_PLANE, rb[p]);
     }
   };
 
   // TN: column sums of B (the bias gradient) ride along: each thread adds up the values it stages
-  float4 bsum = make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 bsum;
   const bool want_bsum = MODE == GEMM_TN && g.colsum != nullptr && bx == 0;
 
   floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
   const bf16_t* const a_frag = A_KCONT ? As + (wm * (BM / WM) + lo) * PK + 8 * hi : As + wm * (BM / WM) + frag_col_offset(lane, PMA);
   const bf16_t* const b_frag = B_KCONT ? Bs + (wn * (BN / WN) + lo) * PK + 8 * hi : Bs + wn * (BN / WN) + frag_col_offset(lane, PNB);
 
-  fetch_entries();
-  fetch(k_begin);
-  for (int64_t k0 = k_begin; k0 < k_end; k0 += BK) {
-    stage();
-    if (MODE == GEMM_TN && want_bsum) {
+  auto multiply = [&](auto any) {  // the whole k range; any: the operands may hold values out of split_pair's range
+    int64_t kb = k_begin;
+    if (decltype(any)::value) kb += opaque_zero();  // no address is kept in registers from one form to the other
+    if (!A_KCONT) {
 #pragma unroll
-      for (int p = 0; p < B_VECS; ++p) {
-        bsum.x += rb[p].x; bsum.y += rb[p].y; bsum.z += rb[p].z; bsum.w += rb[p].w;
+      for (int p = 0; p < A_VECS; ++p) {
+        const uint32_t k = (uint32_t)kb + (tid + 256 * p) / (BM / 4);
+        q[p] = (int)(k / (uint32_t)per);
+        rem[p] = (int)(k - q[p] * per);
       }
     }
-    __syncthreads();
-    if (k0 + BK < k_end) fetch(k0 + BK);
 #pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      Split8 a[TM], b[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        a[i] = A_KCONT ? frag_row(a_frag + 32 * i * PK + 16 * ks, A_PLANE) : frag_col(a_frag + 32 * i + 16 * ks * PMA, PMA, A_PLANE);
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        b[j] = B_KCONT ? frag_row(b_frag + 32 * j * PK + 16 * ks, B_PLANE) : frag_col(b_frag + 32 * j + 16 * ks * PNB, PNB, B_PLANE);
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    bsum = make_float4(0.f, 0.f, 0.f, 0.f);
+    fetch_entries();
+    fetch(kb);
+    for (int64_t k0 = kb; k0 < k_end; k0 += BK) {
+      stage(any);
+      if (MODE == GEMM_TN && want_bsum) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_split(a[i], b[j], acc[i][j]);
+        for (int p = 0; p < B_VECS; ++p) {
+          bsum.x += rb[p].x; bsum.y += rb[p].y; bsum.z += rb[p].z; bsum.w += rb[p].w;
+        }
+      }
+      __syncthreads();
+      if (k0 + BK < k_end) fetch(k0 + BK);
+#pragma unroll
+      for (int ks = 0; ks < BK / 16; ++ks) {
+        Split8 a[TM], b[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          a[i] = A_KCONT ? frag_row(a_frag + 32 * i * PK + 16 * ks, A_PLANE) : frag_col(a_frag + 32 * i + 16 * ks * PMA, PMA, A_PLANE);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          b[j] = B_KCONT ? frag_row(b_frag + 32 * j * PK + 16 * ks, B_PLANE) : frag_col(b_frag + 32 * j + 16 * ks * PNB, PNB, B_PLANE);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = mfma_split(a[i], b[j], acc[i][j]);
+      }
+      __syncthreads();
     }
-    __syncthreads();
-  }
+  };
+  multiply(std::false_type{});
+  float all = 0.f;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) all = sum_of(all, acc[i][j]);
+  if (__builtin_expect(any_in_workgroup(all != all), 0)) multiply(std::true_type{});
 
   if (MODE == GEMM_TN && want_bsum) {
     // threads with equal tid % (BN/4) hold partial sums of the same four columns: combine them through LDS

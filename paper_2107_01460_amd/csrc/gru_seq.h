@@ -29,7 +29,7 @@ inline int64_t gru_weight_floats(int H) { return (((int64_t)H * H * 9 / 2 + 63) 
 // 32 along the contraction.
 template <bool FWD, bool BWD>
 __device__ __forceinline__ void gru_stage_weight(float v, int k, int c, int H, bf16_t* __restrict__ fwd, bf16_t* __restrict__ bwd) {
-  const SplitPair s = split_pair(v, 0.f);
+  const SplitPair s = split_pair_any(v, 0.f);
   const uint32_t part[3] = {s.h, s.m, s.l};
   const int KS = H / 32, g = c / H, u = c - g * H;
   const int64_t f = ((int64_t)((u / 16) * KS + k / 32) * 9 + g * 3) * 512 + ((u % 16) + 16 * ((k % 32) / 8)) * 8 + k % 8;
@@ -129,13 +129,19 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
 #pragma unroll
       for (int g = 0; g < 3; ++g) gi[b][m][g] = *reinterpret_cast<const float4*>(a.Gi + ((int64_t)t * a.S1 + srow[m]) * 3 * H + g * H + unit[b]);
   };
-  auto hand_over = [&](int buf, int b, int m) { store_split4(&Hs[buf][(16 * m + lo) * P + unit[b]], PLANE, h[b][m]); };
+  bool wild = false;  // was a state out of split_pair's range to begin with?  (One step's state is at most the last one's or 1.)
+  auto hand_over = [&](int buf, int b, int m) {
+    bf16_t* const dst = &Hs[buf][(16 * m + lo) * P + unit[b]];
+    if (wild) store_split4<true>(dst, PLANE, h[b][m]);
+    else store_split4<false>(dst, PLANE, h[b][m]);
+  };
   int rs[SM];  // does the coming step start from a zero state
   auto load_reset = [&](int t) {
 #pragma unroll
     for (int m = 0; m < SM; ++m) rs[m] = t > 0 ? a.reset[(t - 1) * nenv + env[m]] : (a.reset0 != nullptr ? a.reset0[env[m]] : 0);
   };
   load_reset(0);
+  float top = 0.f;
 #pragma unroll
   for (int b = 0; b < UB; ++b) {
     load_gi(0, b);
@@ -143,9 +149,14 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
     for (int m = 0; m < SM; ++m) {
       h[b][m] = *reinterpret_cast<const float4*>(a.h_first + srow[m] * H + unit[b]);
       if (rs[m]) h[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
-      hand_over(0, b, m);
+      top = max_abs(top, h[b][m]);
     }
   }
+  wild = split_out_of_range(top * 0x1p10f);  // room for a million steps' rounding
+#pragma unroll
+  for (int b = 0; b < UB; ++b)
+#pragma unroll
+    for (int m = 0; m < SM; ++m) hand_over(0, b, m);
   __syncthreads();
 
 #pragma unroll 1
@@ -325,9 +336,15 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
           *reinterpret_cast<float4*>(d + 3 * H) = gn;
         }
         bf16_t* const dst = &Gs[(16 * m + lo) * P + unit[b]];
-        store_split4(dst, PLANE, gr);
-        store_split4(dst + H, PLANE, gz);
-        store_split4(dst + 2 * H, PLANE, gh);
+        if (split_out_of_range(max_abs(max_abs(max_abs(0.f, gr), gz), gh))) {
+          store_split4<true>(dst, PLANE, gr);
+          store_split4<true>(dst + H, PLANE, gz);
+          store_split4<true>(dst + 2 * H, PLANE, gh);
+        } else {
+          store_split4<false>(dst, PLANE, gr);
+          store_split4<false>(dst + H, PLANE, gz);
+          store_split4<false>(dst + 2 * H, PLANE, gh);
+        }
         if (t > 0) load_step(t - 1, b, m);
       }
       if (t > 0) load_row(t - 1, m);
@@ -398,7 +415,7 @@ inline int64_t gru_embedding_floats(int D, int H) { return (int64_t)((D + 31) / 
 
 // element (k, u) of the embedding [D][H], zeros for D <= k
 __device__ __forceinline__ void gru_stage_embedding(float v, int k, int u, int K1, bf16_t* __restrict__ dst) {
-  const SplitPair s = split_pair(v, 0.f);
+  const SplitPair s = split_pair_any(v, 0.f);
   const uint32_t part[3] = {s.h, s.m, s.l};
   const int64_t f = ((int64_t)(u / 16) * (K1 / 32) + k / 32) * 3 * 512 + ((u % 16) + 16 * ((k % 32) / 8)) * 8 + k % 8;
 #pragma unroll
@@ -455,7 +472,7 @@ __global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_ste
   for (int i = tid; i < MT * (K1 / 2); i += THREADS) {  // two columns of a row; zeros past the ends
     const int r = i / (K1 / 2), c = 2 * (i - r * (K1 / 2));
     const float* const src = a.obs + (s0 + r) * a.D + c;
-    const SplitPair v = split_pair(r < rows && c < a.D ? src[0] : 0.f, r < rows && c + 1 < a.D ? src[1] : 0.f);
+    const SplitPair v = split_pair_any(r < rows && c < a.D ? src[0] : 0.f, r < rows && c + 1 < a.D ? src[1] : 0.f);
     bf16_t* const dst = Xs + r * PX + c;
     *reinterpret_cast<uint32_t*>(dst) = v.h;
     *reinterpret_cast<uint32_t*>(dst + XPLANE) = v.m;
@@ -490,7 +507,7 @@ __global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_ste
 #pragma unroll
   for (int b = 0; b < UB; ++b)
 #pragma unroll
-    for (int m = 0; m < SM; ++m) store_split4(&Hs[(16 * m + lo) * P + unit[b]], PLANE, h[b][m]);
+    for (int m = 0; m < SM; ++m) store_split4<true>(&Hs[(16 * m + lo) * P + unit[b]], PLANE, h[b][m]);
 #pragma unroll
   for (int i = 0; i < RING - 1; ++i) load_w(i);
   __syncthreads();
@@ -521,8 +538,8 @@ __global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_ste
     const float4 bs = *reinterpret_cast<const float4*>(&bias[0][unit[b]]);
 #pragma unroll
     for (int m = 0; m < SM; ++m)
-      store_split4(&Es[(16 * m + lo) * P + unit[b]], PLANE,
-                   make_float4(tanh_f32(acc[m][0] + bs.x), tanh_f32(acc[m][1] + bs.y), tanh_f32(acc[m][2] + bs.z), tanh_f32(acc[m][3] + bs.w)));
+      store_split4<false>(&Es[(16 * m + lo) * P + unit[b]], PLANE,
+                          make_float4(tanh_f32(acc[m][0] + bs.x), tanh_f32(acc[m][1] + bs.y), tanh_f32(acc[m][2] + bs.z), tanh_f32(acc[m][3] + bs.w)));
   }
   // ---- gates: r and z of both products in one accumulator, n of the hidden and of the input product
   floatx4 acc[UB][4][SM];

@@ -18,7 +18,7 @@ namespace {
 // Working copy of the parameters: blocks moved to their aligned offsets, optionally rounded to bf16, plus the
 // operand-order copies of W1, W2 and W2 transposed that the fused training kernel streams from memory.
 __device__ __forceinline__ void store_split_weight(float* copy, float v, int64_t k, int64_t n, int H) {
-  const SplitPair s = split_pair(v, 0.f);
+  const SplitPair s = split_pair_any(v, 0.f);
   bf16_t* const d = reinterpret_cast<bf16_t*>(copy) + split_weight_index(k, n, H);
   d[0] = (bf16_t)s.h;
   d[split_weight_plane(H)] = (bf16_t)s.m;

@@ -195,8 +195,8 @@ __global__ void __launch_bounds__(256, OCC) rollout_fused_kernel(RolloutFusedArg
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float4 bs = *reinterpret_cast<const float4*>(&b1s[uw + 8 * j]);
-      store_split4(&Hs[srow * PH + u0 + 8 * j], HPLANE,
-                   make_float4(tanh_f32(acc[4 * j] + bs.x), tanh_f32(acc[4 * j + 1] + bs.y), tanh_f32(acc[4 * j + 2] + bs.z), tanh_f32(acc[4 * j + 3] + bs.w)));
+      store_split4<false>(&Hs[srow * PH + u0 + 8 * j], HPLANE,
+                          make_float4(tanh_f32(acc[4 * j] + bs.x), tanh_f32(acc[4 * j + 1] + bs.y), tanh_f32(acc[4 * j + 2] + bs.z), tanh_f32(acc[4 * j + 3] + bs.w)));
     }
     __syncthreads();  // h1 complete; every wavefront is past its reads of the windows
     // ---- layer 2: h2 = tanh(h1 W2 + b2), and this wavefront's units' share of the output layer

@@ -25,6 +25,9 @@ typedef short shortx8 __attribute__((ext_vector_type(8)));
 struct SplitPair {
   uint32_t h, m, l;
 };
+// Magnitudes from here on round to infinity in bf16: the only values that split_pair does not represent (a NaN gives NaNs).
+constexpr float kSplitLimit = 0x1.ffp127f;
+// For values below the limit, such as results of tanh.  split_pair_any takes every value.
 __device__ __forceinline__ SplitPair split_pair(float x, float y) {
   SplitPair s;
   s.h = pack2_bf16(x, y);
@@ -36,6 +39,42 @@ __device__ __forceinline__ SplitPair split_pair(float x, float y) {
   s.l = pack2_bf16(x, y);
   return s;
 }
+// A finite value at the limit or above takes the largest bf16 as its first part.  An infinity is (+-1, 0, +-inf): of the six
+// products that mfma_split adds, the one of the last part with the other factor's first is then the infinity (a NaN where
+// that factor is zero), those of the first part are finite or, from a second infinity, the same infinity, and the middle
+// part's are zero -- with the infinity as the first part, infinity times a zero lower part would make every sum a NaN.
+// (What is left: a finite product of 2^136 or more, far past the largest fp32 value, may be a NaN instead of an infinity.)
+__device__ __forceinline__ SplitPair split_pair_any(float x, float y) {
+  auto first = [](float v, uint32_t h) -> uint32_t {
+    const uint32_t sign = (__float_as_uint(v) >> 16) & 0x8000u;
+    return __builtin_isinf(v) ? 0x3f80u | sign : fabsf(v) >= kSplitLimit ? 0x7f7fu | sign : h & 0xffffu;
+  };
+  SplitPair s;
+  s.h = pack2_bf16(x, y);
+  s.h = first(x, s.h) | first(y, s.h >> 16) << 16;
+  const float rx = x - __uint_as_float(s.h << 16), ry = y - __uint_as_float(s.h & 0xffff0000u);  // +-inf for an infinity
+  s.m = pack2_bf16(__builtin_isinf(x) ? 0.f : rx, __builtin_isinf(y) ? 0.f : ry);
+  s.l = pack2_bf16(rx - __uint_as_float(s.m << 16), ry - __uint_as_float(s.m & 0xffff0000u));
+  return s;
+}
+// A value that split_pair does not represent has a NaN among its parts and makes every sum it enters a NaN.  So the kernels
+// split with split_pair, look for a NaN in the sums, and where there is one do the work again with split_pair_any.  (Looking
+// at the operands took a comparison per value and, in the inner loops, registers: 5 % of a training iteration, this 1 %.)
+__device__ __forceinline__ float sum_of(float s, const floatx16& v) {  // (a NaN also where infinities meet: done again for nothing)
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s += v[r];
+  return s;
+}
+__device__ __forceinline__ bool any_in_workgroup(bool b) { return __builtin_amdgcn_readfirstlane(__syncthreads_or(b)) != 0; }
+// A zero that the compiler does not know
+__device__ __forceinline__ int opaque_zero() {
+  int z = 0;
+  asm volatile("" : "+v"(z));
+  return __builtin_amdgcn_readfirstlane(z);
+}
+// Does any lane hold one (m: a magnitude; fmaxf passes over NaNs)?
+__device__ __forceinline__ bool split_out_of_range(float m) { return __builtin_expect(__builtin_amdgcn_ballot_w64(m >= kSplitLimit) != 0, 0); }
+__device__ __forceinline__ float max_abs(float m, float4 v) { return fmaxf(fmaxf(m, fmaxf(fabsf(v.x), fabsf(v.y))), fmaxf(fabsf(v.z), fabsf(v.w))); }
 
 // Eight values along the contraction of one row (A) or column (B): what a lane feeds to one matrix instruction -- of the
 // sixteen k of a step, lanes 0 .. 31 hold k = 0 .. 7, lanes 32 .. 63 hold k = 8 .. 15.
@@ -43,8 +82,11 @@ struct Split8 {
   bf16x8 h, m, l;
 };
 
+template <bool ANY>
+__device__ __forceinline__ SplitPair split_two(float x, float y) { return ANY ? split_pair_any(x, y) : split_pair(x, y); }
+template <bool ANY>
 __device__ __forceinline__ Split8 split8(const float (&v)[8]) {
-  const SplitPair a = split_pair(v[0], v[1]), b = split_pair(v[2], v[3]), c = split_pair(v[4], v[5]), d = split_pair(v[6], v[7]);
+  const SplitPair a = split_two<ANY>(v[0], v[1]), b = split_two<ANY>(v[2], v[3]), c = split_two<ANY>(v[4], v[5]), d = split_two<ANY>(v[6], v[7]);
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   Split8 s;
   s.h = __builtin_bit_cast(bf16x8, u32x4{a.h, b.h, c.h, d.h});
@@ -52,9 +94,10 @@ __device__ __forceinline__ Split8 split8(const float (&v)[8]) {
   s.l = __builtin_bit_cast(bf16x8, u32x4{a.l, b.l, c.l, d.l});
   return s;
 }
+template <bool ANY>
 __device__ __forceinline__ Split8 split8(float4 x, float4 y) {
   const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-  return split8(v);
+  return split8<ANY>(v);
 }
 
 // acc += A B over sixteen k (the small products first)
@@ -70,8 +113,9 @@ __device__ __forceinline__ floatx16 mfma_split(const Split8& a, const Split8& b,
 
 // ---- operands in LDS: three planes (h, m, l) of bf16, `plane` elements apart ------------------------------------------
 // Four consecutive values to the three planes with 8-byte stores.
+template <bool ANY>
 __device__ __forceinline__ void store_split4(bf16_t* dst, int plane, float4 v) {
-  const SplitPair a = split_pair(v.x, v.y), b = split_pair(v.z, v.w);
+  const SplitPair a = split_two<ANY>(v.x, v.y), b = split_two<ANY>(v.z, v.w);
   *reinterpret_cast<uint2*>(dst) = make_uint2(a.h, b.h);
   *reinterpret_cast<uint2*>(dst + plane) = make_uint2(a.m, b.m);
   *reinterpret_cast<uint2*>(dst + 2 * plane) = make_uint2(a.l, b.l);
