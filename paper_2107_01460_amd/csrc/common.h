@@ -65,7 +65,7 @@ struct ParamMap {
   // the eight k values of a lane are one 16-byte load, contiguous across lanes.  W1 is zero-padded to kpad1 rows (a
   // multiple of 16).
   int64_t sw_w1[2], sw_w2[2], sw_w2t[2];
-  // The actor's W1 and W2 as fp32 in the order of rollout_fp32_kernel: element (k, n) at ((k / 4) * H + n) * 4 + k % 4 (zero-padded
+  // The actor's W1 and W2 as fp32 in the order of rollout_train_kernel: element (k, n) at ((k / 4) * H + n) * 4 + k % 4 (zero-padded
   // like the split copy).  Filled for a rollout only; -1 where no such kernel exists (its widths are 64 and 128).
   int64_t op_w1, op_w2;
   bool split[2];  // whether the copies are filled (fp32 networks of those widths)

@@ -269,7 +269,7 @@ int32_t launch_sample(const marl_config& c, const float* logits, const float* un
   return launch_status();
 }
 
-static int32_t launch_rollout_fused(const marl_config& c, bool eval, const RolloutFusedArgs& a, hipStream_t s) {
+static int32_t launch_rollout_fused(const marl_config& c, bool eval, const RolloutArgs& a, hipStream_t s) {
   switch (c.view) {
     case 3: return launch_rollout_fused_v3(c.actor_hidden, eval, a, s);
     case 5: return launch_rollout_fused_v5(c.actor_hidden, eval, a, s);
@@ -278,21 +278,16 @@ static int32_t launch_rollout_fused(const marl_config& c, bool eval, const Rollo
   }
 }
 
-// The actor's part of the arguments of the fused rollout kernel.
-static RolloutFusedArgs rollout_fused_args(const marl_config& c, marl_env_state st, const float* eff) {
+// The actor's part of the arguments of the fused rollout and evaluation kernels.
+static RolloutArgs rollout_fused_args(const marl_config& c, marl_env_state st, const float* eff, bool eval) {
   const Dims d = dims_of(c);
   const ParamMap pm = param_map(d);
   const NetOffsets o = padded_offsets(pm, 0);
-  RolloutFusedArgs a{};
+  RolloutArgs a{};
   a.p = env_params(c);
   a.st = st;
-  a.W1s = eff + pm.sw_w1[0]; a.W2s = eff + pm.sw_w2[0]; a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
-  if (pm.op_w1 >= 0) {
-    a.W1o = eff + pm.op_w1;
-    a.W2o = eff + pm.op_w2;
-  }
-  a.kpad1 = pm.kpad1[0];
-  a.px = fused_forward_px(d.D);
+  a.W1 = eff + (eval ? pm.sw_w1[0] : pm.op_w1); a.W2 = eff + (eval ? pm.sw_w2[0] : pm.op_w2);
+  a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
   return a;
 }
 
@@ -315,7 +310,7 @@ int32_t launch_rollout(const marl_config& c, marl_env_state st, const float* par
   const bool batch_values = !d.bf16 && fused_forward_supported(d.Hc, d.Dc);
   if (use_fused_rollout(c)) {
     // all T steps in one launch: a workgroup keeps its environments on chip and streams the trajectory out
-    RolloutFusedArgs a = rollout_fused_args(c, st, eff);
+    RolloutArgs a = rollout_fused_args(c, st, eff, false);
     a.T = d.T;
     a.obs = tr.obs; a.action = tr.action; a.logp = tr.logp; a.reward = tr.reward; a.done = tr.done;
     a.logits = tr.logits; a.sampled = tr.sampled; a.uniforms = forced_uniforms; a.forced = forced_actions;
@@ -449,7 +444,7 @@ int32_t launch_evaluate(const marl_config& c, marl_env_state st, const float* pa
   const float* eff = effective_params(c, params, w.eff_params, s, false);
   const int64_t steps = (int64_t)n_episodes * c.episode_cap;
   if (use_fused_rollout(c)) {  // the whole block in one launch, statistics in registers
-    RolloutFusedArgs a = rollout_fused_args(c, st, eff);
+    RolloutArgs a = rollout_fused_args(c, st, eff, true);
     a.T = (int)steps;
     a.ev = out;
     a.n_episodes = n_episodes;

@@ -1,0 +1,157 @@
+// The greedy evaluation block as ONE kernel, as rollout_train.h: argmax actions, no trajectory, and the per-environment
+// return / length / episode counts accumulated in registers.
+//
+// Both layers run on split bf16 operands, transposed (gemm_phase_t): the windows hold small integers and halves, exact in
+// bf16, so layer 1 takes half the products, h1 is split once, and the output layer starts from the registers that layer 2
+// ends in.  A step is a chain of latencies: 200 steps of 384 samples at 128 units 1.23 ms, with fp32 tiles 1.48 ms.
+#pragma once
+#include "rollout_common.h"
+
+namespace marl {
+
+// pitch of a window in LDS, in elements: the width rounded up to a k group, and an odd number of 16-byte units
+constexpr int rollout_eval_px(int D) { return (D + 15) / 16 * 16 + 8; }
+
+// OCC: workgroups per CU the registers are capped for
+template <int H, int BM, int V, int CA, int KIND, int OCC>
+__global__ void __launch_bounds__(256, OCC) rollout_eval_kernel(RolloutArgs a) {
+  constexpr int D = 3 * V * V, PX = rollout_eval_px(D), PH = H + 8, HPLANE = BM * PH, NOUT = kActions;
+  constexpr int NTN = H / 32, MT = BM / 32, TILES = MT * NTN;
+  static_assert(TILES == 4, "one 32x32 MFMA tile per wavefront");
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  bf16_t* const Xs2 = reinterpret_cast<bf16_t*>(lds);  // [2][BM][PX]  observation windows of two consecutive steps (exact in bf16),
+                                                       //              k-contiguous; columns D .. PX stay zero
+  bf16_t* const Hs = Xs2 + 2 * BM * PX;                // [3][BM][PH]  h1, split
+  float* const red = reinterpret_cast<float*>(Hs + 3 * HPLANE);  // [NTN][NOUT][BM] shares of the output layer
+  float* const W3s = red + NTN * NOUT * BM;            // [H][NOUT]
+  float* const b1s = W3s + H * NOUT;                   // [H]
+  float* const b2s = b1s + H;                          // [H]
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lo = lane & 31, hi = lane >> 5;
+  const int mt = wave / NTN, nt = wave % NTN;
+  const int srow = mt * 32 + lo, u0 = nt * 32 + 4 * hi;  // this lane's sample of the tile; its units are u0 + 8 j .. + 3
+  RolloutEnvs<BM, V, CA, KIND> env(a, wave, lane);
+  float ret_sum = 0.f;
+  int len_sum = 0, episodes = 0;
+
+  for (int i = tid; i < H * NOUT; i += 256) W3s[i] = a.W3[i];
+  for (int i = tid; i < H; i += 256) {
+    b1s[i] = a.b1[i];
+    b2s[i] = a.b2[i];
+  }
+  for (int i = tid; i < BM * PX; i += 256) reinterpret_cast<uint32_t*>(Xs2)[i] = 0u;  // padding columns and unused rows stay zero for good
+  if (env.is_env_wave) env.load();
+  __syncthreads();
+  if (env.active) env.paint(Xs2 + lane * PX);
+  // the output layer's bias stays in registers for all T steps
+  float b3r[NOUT];
+#pragma unroll
+  for (int k = 0; k < NOUT; ++k) b3r[k] = a.b3[k];
+  // the first weights of a layer are requested a phase ahead (buffer loads: one descriptor, one lane offset)
+  constexpr int KG1 = (D + 15) / 16, KG2 = H / 16;
+  const int wlane = (hi * H + nt * 32 + lo) * 4;
+  const WeightRsrc rsW1 = split_weight_rsrc(a.W1, 16 * KG1, H), rsW2 = split_weight_rsrc(a.W2, H, H);
+  PhaseW<KG1> pw1;
+  phase_w_request<H, KG1>(pw1, rsW1, wlane, KG1);
+  for (int t = 0; t < a.T; ++t) {
+    __syncthreads();  // the windows of step t are complete
+    const bf16_t* const Xs = Xs2 + (t & 1) * BM * PX;
+    int uw = u0;  // the weights and biases in LDS are read in every step: kept across steps, they would take 96 registers
+    asm volatile("" : "+v"(uw));
+    // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS.  Both layers are computed transposed (gemm_phase_t).
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    gemm_phase_t<H, KG1, true>(Xs + srow * PX + 8 * hi, 0, rsW1, wlane, KG1, acc, pw1);
+    PhaseW<KG2> pw2;  // layer 2's weights arrive during the tanh of layer 1
+    phase_w_request<H, KG2>(pw2, rsW2, wlane, KG2);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float4 bs = *reinterpret_cast<const float4*>(&b1s[uw + 8 * j]);
+      store_split4<false>(&Hs[srow * PH + u0 + 8 * j], HPLANE,
+                          make_float4(tanh_f32(acc[4 * j] + bs.x), tanh_f32(acc[4 * j + 1] + bs.y), tanh_f32(acc[4 * j + 2] + bs.z), tanh_f32(acc[4 * j + 3] + bs.w)));
+    }
+    __syncthreads();  // h1 complete; every wavefront is past its reads of the windows
+    // ---- layer 2: h2 = tanh(h1 W2 + b2), and this wavefront's units' share of the output layer
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    gemm_phase_t<H, KG2, false>(Hs + srow * PH + 8 * hi, HPLANE, rsW2, wlane, KG2, acc, pw2);
+    phase_w_request<H, KG1>(pw1, rsW1, wlane, KG1);  // layer 1 of the next step
+    {
+      float part[NOUT];
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) part[k] = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float4 bs = *reinterpret_cast<const float4*>(&b2s[uw + 8 * j]);
+        const float h[4] = {tanh_f32(acc[4 * j] + bs.x), tanh_f32(acc[4 * j + 1] + bs.y), tanh_f32(acc[4 * j + 2] + bs.z), tanh_f32(acc[4 * j + 3] + bs.w)};
+        float wv[4 * NOUT];
+#pragma unroll
+        for (int q = 0; q < NOUT; ++q) {
+          const float4 w4 = *reinterpret_cast<const float4*>(&W3s[(uw + 8 * j) * NOUT + 4 * q]);
+          wv[4 * q] = w4.x; wv[4 * q + 1] = w4.y; wv[4 * q + 2] = w4.z; wv[4 * q + 3] = w4.w;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) part[k] = fmaf(h[e], wv[e * NOUT + k], part[k]);
+        __builtin_amdgcn_sched_barrier(0);  // one quarter's weights in registers at a time
+      }
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) {
+        const float v = part[k] + __shfl_xor(part[k], 32);
+        if (hi == 0) red[(nt * NOUT + k) * BM + srow] = v;
+      }
+    }
+    __syncthreads();
+    if (env.is_env_wave) {
+      // ---- the env lanes: logits -> action -> transition -> next window
+      const int row = lane < BM ? lane : 0;
+      float lg[NOUT];
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) {
+        float v = b3r[k];
+#pragma unroll
+        for (int q = 0; q < NTN; ++q) v += red[(q * NOUT + k) * BM + row];
+        lg[k] = v;
+      }
+      int my_act = 0;
+      float top = lg[0];  // largest logit, lowest index on exact ties
+#pragma unroll
+      for (int k = 1; k < NOUT; ++k)
+        if (lg[k] > top) {
+          top = lg[k];
+          my_act = k;
+        }
+      float rew;
+      bool dn;
+      env.step(my_act, rew, dn);
+      // team reward = the agents' rewards added in ascending agent index, then added to the running sum (fp32)
+      float team = 0.f;
+#pragma unroll
+      for (int b = 0; b < CA; ++b) {
+        const float rb = __shfl(rew, min(env.le * env.A + b, 63));
+        if (b < env.A) team += rb;
+      }
+      if (env.active) {
+        if (episodes < a.n_episodes) {
+          ret_sum += team;
+          len_sum += 1;
+          if (dn) episodes += 1;
+        }
+        env.paint(Xs2 + ((t + 1) & 1) * BM * PX + lane * PX);  // the windows of step t + 1 into the other tile
+      }
+    }
+  }
+  if (env.active) {
+    env.store();
+    if (env.ai == 0) {
+      a.ev.ret_sum[env.n] = ret_sum;
+      a.ev.len_sum[env.n] = len_sum;
+      a.ev.episodes[env.n] = episodes;
+    }
+  }
+}
+
+}  // namespace marl

@@ -1,0 +1,267 @@
+// The whole training rollout as ONE kernel: a workgroup owns a block of environments for all T time steps.
+//
+// Environments never interact and the parameters are constant during a rollout, so nothing has to be exchanged between
+// workgroups: each keeps the state of its BM / A environments in the registers of one lane per env-agent, paints the
+// agents' observation windows straight into the LDS tile that is the A operand of the actor's first layer, runs both
+// hidden layers on the matrix cores (weights in operand order from the L2), the output layer and the Gumbel-max sampling on
+// the ALUs, hands the actions to the env lanes through cross-lane reads, resolves the transition in registers, and paints
+// the next observation -- only the trajectory (observations, actions, log-probabilities, rewards, dones) is streamed out.
+// The critic's values do not steer the rollout and are computed in one pass over the stored observations afterwards.
+//
+// The products run on the fp32 instruction for every number of environments.  Short rollouts of few environments, chains of
+// latencies, are a fifth faster on split bf16 operands as in rollout_eval.h (128 steps of 3072 samples at 128 units 0.84
+// against 1.0 ms), but a sampled action is a discrete choice: with one arithmetic below some number of environments and
+// another one above, an environment's run depends on how many others share the launch.
+#pragma once
+#include "rollout_common.h"
+
+namespace marl {
+
+// log-softmax(lg)[a] with the hardware exp2 / log2 units (a value, not a decision: the relative error of about
+// 1e-6 is far inside the tolerance of a log-probability)
+__device__ __forceinline__ float log_softmax_fast(const float lg[kActions], int a) {
+  float m = lg[0];
+#pragma unroll
+  for (int k = 1; k < kActions; ++k) m = fmaxf(m, lg[k]);
+  float se = 0.f, la = 0.f;
+#pragma unroll
+  for (int k = 0; k < kActions; ++k) {
+    se += __builtin_amdgcn_exp2f((lg[k] - m) * 1.4426950408889634f);
+    la = (k == a) ? lg[k] : la;
+  }
+  return la - m - __builtin_amdgcn_logf(se) * 0.6931471805599453f;
+}
+
+// All B fragments of one product against weights, for this lane: KG groups of 16 along k, two 16-byte buffer loads each
+// (ParamMap; lane_off is this lane's offset (hi * LDB + n) * 4 in floats).  The whole set is requested one phase ahead of the
+// product that uses it.
+template <int KG>
+struct PhaseW32 {
+  float4 w[KG][2];
+};
+template <int LDB, int KG>
+__device__ __forceinline__ void phase_w32_request(PhaseW32<KG>& pw, WeightRsrc B, int lane_off) {
+#pragma unroll
+  for (int g = 0; g < KG; ++g)
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      pw.w[g][u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(B, lane_off * 4, (16 * g + 8 * u) * LDB * 4, 0));
+}
+// acc += A B for this wavefront's 32x32 tile: A rows in LDS (As points at this lane's row, + 4 * hi; the fragments of
+// the next group are read before the matrix instructions of the current one), B from pw.
+template <int KG>
+__device__ __forceinline__ void gemm_phase_w32(const float* __restrict__ As, floatx16& acc, const PhaseW32<KG>& pw) {
+  float4 av[2][2];
+  av[0][0] = *reinterpret_cast<const float4*>(As);
+  av[0][1] = *reinterpret_cast<const float4*>(As + 8);
+#pragma unroll
+  for (int g = 0; g < KG; ++g) {
+    const int gn = g + 1 < KG ? g + 1 : g;
+    av[(g + 1) & 1][0] = *reinterpret_cast<const float4*>(As + 16 * gn);
+    av[(g + 1) & 1][1] = *reinterpret_cast<const float4*>(As + 16 * gn + 8);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const float af[4] = {av[g & 1][u].x, av[g & 1][u].y, av[g & 1][u].z, av[g & 1][u].w};
+      const float bf[4] = {pw.w[g][u].x, pw.w[g][u].y, pw.w[g][u].z, pw.w[g][u].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], bf[j], acc, 0, 0, 0);
+    }
+  }
+}
+
+// pitch of a window in LDS, in floats: a multiple of four, with an odd number of 16-byte units
+constexpr int rollout_train_px(int D) { return (D + 15) / 16 * 16 + 4; }
+
+// OCC: workgroups per CU the registers are capped for
+template <int H, int BM, int V, int CA, int KIND, int OCC>
+__global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) {
+  constexpr int D = 3 * V * V, PX = rollout_train_px(D), KPAD = (D + 15) / 16 * 16, PH = H + 4, GROUPS = 256 / BM, NOUT = kActions;
+  constexpr int NTN = H / 32, MT = BM / 32, TILES = MT * NTN;
+  static_assert(TILES == 4, "one 32x32 MFMA tile per wavefront");
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  float* const Xs2 = lds;                      // [2][BM][PX]  observation windows of two consecutive steps, k-contiguous;
+                                               //              columns D .. PX stay zero
+  float* const Hs = Xs2 + 2 * BM * PX;         // [BM][PH]  h1, then h2
+  float* const red = Hs + BM * PH;             // [GROUPS][BM][NOUT]
+  float* const W3s = red + GROUPS * BM * NOUT; // [H][NOUT]
+  float* const noise = W3s + H * NOUT;         // [2][BM][8] log(-log u) of the step's uniforms, two steps alternating
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lo = lane & 31, hi = lane >> 5;
+  const int mt = wave / NTN, nt = wave % NTN;
+  RolloutEnvs<BM, V, CA, KIND> env(a, wave, lane);
+  const int64_t NA = (int64_t)a.p.N * a.p.A;
+  // ---- the other three wavefronts draw the sampling noise of the NEXT step while the env lanes work: it depends on
+  // (step, sample) only.  Thread j of them: sample slot j % BM, Philox call j / BM (call 0: actions 0..3, call 1: 4, 5).
+  const int nz_s = env.other % BM, nz_call = env.other / BM;
+  const bool nz_on = !env.is_env_wave && nz_call < 2 && nz_s < env.samples_here;
+  const uint64_t step_base = (a.step_base != nullptr) ? *a.step_base : 0;
+
+  auto draw_noise = [&](int t) {  // noise of step t into buffer t & 1
+    if (!nz_on) return;
+    float* const dst = noise + ((t & 1) * BM + nz_s) * 8 + 4 * nz_call;
+    const int64_t s = env.env0 * env.A + nz_s;
+    float u[4];
+    if (a.uniforms) {
+      const float* src = a.uniforms + ((int64_t)t * NA + s) * NOUT + 4 * nz_call;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u[k] = (4 * nz_call + k < NOUT) ? src[k] : 0.5f;
+    } else {
+      const uint64_t step = a.step0 + step_base + (uint64_t)t;
+      uint32_t o[4];
+      philox4x32_10((uint32_t)step, (uint32_t)(step >> 32), (uint32_t)s * 2u + (uint32_t)nz_call, kStreamSample, a.p.k0, a.p.k1, o);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) u[k] = rand_unit(o[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dst[k] = logf(-logf(u[k]));  // the same fp32 operations as the per-step sampler
+  };
+
+  for (int i = tid; i < H * NOUT; i += 256) W3s[i] = a.W3[i];
+  for (int i = tid; i < 2 * BM * PX; i += 256) Xs2[i] = 0.f;  // padding columns and unused rows stay zero for good
+  if (env.is_env_wave) env.load();
+  __syncthreads();
+  if (env.active) env.paint(Xs2 + lane * PX);
+  if (a.T > 0) draw_noise(0);
+  // the biases of this lane's column and of the output layer stay in registers for all T steps
+  const float bias1 = a.b1[nt * 32 + lo], bias2 = a.b2[nt * 32 + lo];
+  float b3r[NOUT];
+#pragma unroll
+  for (int k = 0; k < NOUT; ++k) b3r[k] = a.b3[k];
+  // The windows of step t sit in tile t & 1: while the env lanes paint the windows of step t + 1 into the other tile, the
+  // wavefronts that are idle then copy tile t & 1 out as slab t of the trajectory.  Thread j of them (0 .. 191).
+  auto store_slab = [&](int t, int j, int nthreads) {
+    const float* const Xt = Xs2 + (t & 1) * BM * PX;
+    float* const out = a.obs + ((int64_t)t * a.p.N + env.env0) * env.A * D;
+    const int count = env.samples_here * D;
+    for (int i = j; i < count; i += nthreads) {
+      const int r = i / D, c = i - r * D;
+      out[i] = Xt[r * PX + c];
+    }
+  };
+
+  // the weights of a whole layer are requested a phase ahead (buffer loads: one descriptor, one lane offset)
+  constexpr int KG1 = KPAD / 16, KG2 = H / 16;
+  const int wlane = (hi * H + nt * 32 + lo) * 4;
+  const WeightRsrc rsW1 = weight_rsrc(a.W1, KPAD * H), rsW2 = weight_rsrc(a.W2, H * H);
+  PhaseW32<KG1> pw1;
+  phase_w32_request<H, KG1>(pw1, rsW1, wlane);
+  for (int t = 0;; ++t) {
+    __syncthreads();  // the windows (and the noise) of step t are complete
+    if (t == a.T) {
+      store_slab(t, tid, 256);  // the post-rollout observation
+      break;
+    }
+    const float* const Xs = Xs2 + (t & 1) * BM * PX;
+    // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    gemm_phase_w32<KG1>(Xs + (mt * 32 + lo) * PX + 4 * hi, acc, pw1);
+    PhaseW32<KG2> pw2;  // layer 2's weights arrive during the tanh of layer 1
+    phase_w32_request<H, KG2>(pw2, rsW2, wlane);
+    {
+      const int col = nt * 32 + lo;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
+        Hs[m * PH + col] = tanh_f32(acc[r] + bias1);
+      }
+    }
+    __syncthreads();  // h1 complete; every wavefront is past its reads of the windows
+    // ---- layer 2: h2 = tanh(h1 W2 + b2)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    gemm_phase_w32<KG2>(Hs + (mt * 32 + lo) * PH + 4 * hi, acc, pw2);
+    phase_w32_request<H, KG1>(pw1, rsW1, wlane);  // layer 1 of the next step
+    __syncthreads();  // every wavefront is past its last read of h1
+    {
+      const int col = nt * 32 + lo;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
+        Hs[m * PH + col] = tanh_f32(acc[r] + bias2);
+      }
+    }
+    __syncthreads();
+    // ---- output layer on the ALUs: thread -> (sample tid % BM, slice tid / BM of the hidden units)
+    {
+      const int s = tid % BM, grp = tid / BM;
+      constexpr int PER = H / GROUPS;
+      static_assert(PER % 4 == 0, "hidden units are read four at a time");
+      float part[NOUT];
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) part[k] = 0.f;
+#pragma unroll 2
+      for (int i = grp * PER; i < (grp + 1) * PER; i += 4) {
+        const float4 hv = *reinterpret_cast<const float4*>(&Hs[s * PH + i]);
+        const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
+        float wv[4 * NOUT];
+#pragma unroll
+        for (int q = 0; q < NOUT; ++q) {
+          const float4 w4 = *reinterpret_cast<const float4*>(&W3s[i * NOUT + 4 * q]);
+          wv[4 * q] = w4.x; wv[4 * q + 1] = w4.y; wv[4 * q + 2] = w4.z; wv[4 * q + 3] = w4.w;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) part[k] = fmaf(hh[j], wv[j * NOUT + k], part[k]);
+      }
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) red[(grp * BM + s) * NOUT + k] = part[k];
+    }
+    __syncthreads();
+    if (!env.is_env_wave) {
+      if (t + 1 < a.T) draw_noise(t + 1);
+      store_slab(t, env.other, 192);
+    } else {
+      // ---- the env lanes: logits -> action -> transition -> next window
+      const int row = lane < BM ? lane : 0;
+      float lg[NOUT];
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) {
+        float v = b3r[k];
+#pragma unroll
+        for (int gq = 0; gq < GROUPS; ++gq) v += red[(gq * BM + row) * NOUT + k];
+        lg[k] = v;
+      }
+      int my_act = 0;
+      if (env.active) {
+        const int64_t o = (int64_t)t * NA + env.s_glob;
+        if (a.logits) {
+#pragma unroll
+          for (int k = 0; k < NOUT; ++k) a.logits[o * NOUT + k] = lg[k];
+        }
+        // Gumbel-max: argmax_k lg[k] - log(-log u[k]), lowest k on exact ties
+        const float* const g = noise + ((t & 1) * BM + lane) * 8;
+        const float4 g0 = *reinterpret_cast<const float4*>(g);
+        const float2 g1 = *reinterpret_cast<const float2*>(g + 4);
+        const float gk[NOUT] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y};
+        float best = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) {
+          const float z = lg[k] - gk[k];
+          if (z > best) {
+            best = z;
+            my_act = k;
+          }
+        }
+        if (a.sampled) a.sampled[o] = my_act;
+        if (a.forced) my_act = a.forced[o];
+        a.action[o] = my_act;
+        a.logp[o] = log_softmax_fast(lg, my_act);
+      }
+      float rew;
+      bool dn;
+      env.step(my_act, rew, dn);
+      if (env.active) {
+        a.reward[(int64_t)t * NA + env.s_glob] = rew;
+        if (env.ai == 0) a.done[(int64_t)t * a.p.N + env.n] = dn ? 1 : 0;
+        env.paint(Xs2 + ((t + 1) & 1) * BM * PX + lane * PX);  // the windows of step t + 1 into the other tile
+      }
+    }
+  }
+  if (env.active) env.store();
+}
+
+}  // namespace marl

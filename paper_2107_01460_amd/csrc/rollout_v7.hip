@@ -3,7 +3,7 @@
 
 namespace marl {
 
-int32_t launch_rollout_fused_v7(int H, bool eval, const RolloutFusedArgs& a, hipStream_t s) {
+int32_t launch_rollout_fused_v7(int H, bool eval, const RolloutArgs& a, hipStream_t s) {
   return launch_rollout_fused_tu<7>(H, eval, a, s);
 }
 

@@ -1,0 +1,47 @@
+"""An environment's run does not depend on how many others share the launch: its random streams are keyed by its own index,
+and every size of call computes with the same arithmetic, so the same environments come out bit for bit.  (A sampled
+action is a discrete choice: logits that differ in the last bit are, somewhere among millions of them, another run.)
+"""
+import pytest
+import torch
+
+import workloads as W
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import paper_2107_01460_amd as m
+    return m
+
+
+def run(M, cfg, params):
+    st, tr = M.EnvState(cfg), M.Traj(cfg, debug=True)
+    M.env_reset(cfg, st)
+    ws = M.alloc_workspace(M.query_sizes(cfg).rollout_workspace_bytes)
+    M.rollout(cfg, st, params, tr, 7, ws)
+    return tr
+
+
+# environments per launch around 512 workgroups of the rollout kernels (32 environments each at 64 units and two agents, 10 at
+# 128 units and three), and a handful; the layer-by-layer networks
+@pytest.mark.parametrize("k,sizes,kw", [
+    (5, (37, 512 * 32, 512 * 32 + 1), {}),
+    (2, (37, 512 * 10, 512 * 10 + 1), {}),
+    (2, (37, 600), dict(actor_hidden=192, critic_hidden=256)),
+])
+def test_rollout_does_not_depend_on_the_batch(M, k, sizes, kw):
+    base = W.scaled(W.CONFIGS[k - 1], rollout_len=4, n_minibatches=1, n_epochs=1, episode_cap=3, **kw)
+    params = dev(W.init_params(base, bias_scale=0.1))
+    ref = None
+    for n in sorted(sizes, reverse=True):
+        print("case", k, kw, n, flush=True)
+        tr = run(M, W.scaled(base, n_envs=n), params)
+        if ref is None:
+            ref = tr
+            continue
+        for f in ("obs", "action", "sampled", "logits", "logp", "reward", "done", "value"):
+            assert torch.equal(getattr(tr, f), getattr(ref, f)[:, :n]), (n, f)
+        assert torch.equal(tr.last_value, ref.last_value[:n]), n
