@@ -21,16 +21,23 @@ def run(M, cfg, params):
     st, tr = M.EnvState(cfg), M.Traj(cfg, debug=True)
     M.env_reset(cfg, st)
     ws = M.alloc_workspace(M.query_sizes(cfg).rollout_workspace_bytes)
-    M.rollout(cfg, st, params, tr, 7, ws)
-    return tr
+    if not cfg["recurrent"]:
+        M.rollout(cfg, st, params, tr, 7, ws)
+        return tr, ()
+    rec = M.RecState(cfg)
+    M.rollout_recurrent(cfg, st, params, tr, rec, 7, ws)
+    return tr, (rec.ha1, rec.hc1)
 
 
 # environments per launch around 512 workgroups of the rollout kernels (32 environments each at 64 units and two agents, 10 at
-# 128 units and three), and a handful; the layer-by-layer networks
+# 128 units and three), and a handful; the layer-by-layer networks; the recurrent ones around 4096 samples per step, where
+# the cell's kernels change their tile, with weights in registers and streamed
 @pytest.mark.parametrize("k,sizes,kw", [
     (5, (37, 512 * 32, 512 * 32 + 1), {}),
     (2, (37, 512 * 10, 512 * 10 + 1), {}),
     (2, (37, 600), dict(actor_hidden=192, critic_hidden=256)),
+    (2, (37, 1365, 1366), dict(recurrent=1, actor_hidden=128, critic_hidden=192)),
+    (2, (37, 1365, 1366), dict(recurrent=1, actor_hidden=256, critic_hidden=64)),
 ])
 def test_rollout_does_not_depend_on_the_batch(M, k, sizes, kw):
     base = W.scaled(W.CONFIGS[k - 1], rollout_len=4, n_minibatches=1, n_epochs=1, episode_cap=3, **kw)
@@ -38,10 +45,12 @@ def test_rollout_does_not_depend_on_the_batch(M, k, sizes, kw):
     ref = None
     for n in sorted(sizes, reverse=True):
         print("case", k, kw, n, flush=True)
-        tr = run(M, W.scaled(base, n_envs=n), params)
+        tr, state = run(M, W.scaled(base, n_envs=n), params)
         if ref is None:
-            ref = tr
+            ref, ref_state = tr, state
             continue
         for f in ("obs", "action", "sampled", "logits", "logp", "reward", "done", "value"):
             assert torch.equal(getattr(tr, f), getattr(ref, f)[:, :n]), (n, f)
         assert torch.equal(tr.last_value, ref.last_value[:n]), n
+        for a, b in zip(state, ref_state):
+            assert torch.equal(a, b[:n]), n
