@@ -1,0 +1,44 @@
+"""Greedy evaluation blocks of shapes that none of the workloads has, against the oracle: both worlds, every view, both widths of
+the one-launch kernel, entity counts on both sides of its unrolled capacities, ragged last workgroups."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import paper_2107_01460_amd as m
+    return m
+
+
+@pytest.mark.parametrize("kind,grid,agents,food,level,view,hidden,n_envs", [
+    (0, 9, 6, 3, 2, 7, 128, 23), (0, 8, 3, 4, 2, 3, 64, 70), (0, 10, 5, 5, 3, 5, 64, 61), (0, 8, 2, 2, 2, 7, 64, 67),
+    (1, 8, 3, 5, 2, 3, 64, 45), (1, 10, 4, 4, 2, 7, 128, 33), (2, 9, 5, 6, 2, 5, 128, 41), (2, 8, 2, 8, 3, 7, 64, 97)])
+def test_evaluation_block(M, orc, kind, grid, agents, food, level, view, hidden, n_envs):
+    cfg = W.scaled(W.CONFIGS[0], env_kind=kind, grid=grid, n_agents=agents, n_food=food, max_level=level, view=view, n_envs=n_envs,
+                   actor_hidden=hidden, critic_hidden=hidden, episode_cap=9, n_minibatches=1, rollout_len=1)
+    E = 3
+    print("case", kind, grid, agents, food, view, hidden, n_envs, flush=True)
+    params = W.init_params(cfg, bias_scale=0.3)
+    os_ = orc.EnvState(cfg)
+    orc.env_reset(cfg, os_)
+    oret, olen, oeps, gap = orc.evaluate(cfg, os_, params, E)
+    gs, out = M.EnvState(cfg), M.EvalStats(cfg)
+    M.env_reset(cfg, gs)
+    M.evaluate(cfg, gs, dev(params), E, out, M.alloc_workspace(M.query_sizes(cfg).eval_workspace_bytes))
+    torch.cuda.synchronize()
+    # the environments whose two largest logits were never closer than an fp32 evaluation can tell apart: with logits spread
+    # over about 1, one decision in a thousand is that close, and a run of six agents makes 27 x 6 = 162 of them
+    clear = gap > 8e-4 * max(1.0, float(np.abs(params).max()))
+    assert clear.mean() > 0.6, clear.mean()
+    assert np.all(out.episodes.cpu().numpy() == E) and np.all(oeps == E)
+    assert np.array_equal(out.ret_sum.cpu().numpy()[clear].view(np.uint32), oret[clear].view(np.uint32))
+    assert np.array_equal(out.len_sum.cpu().numpy()[clear], olen[clear])
+    host = gs.to_host()
+    for f in M.EnvState.FIELDS:
+        assert np.array_equal(host[f][..., clear], getattr(os_, f)[..., clear]), f
