@@ -194,7 +194,7 @@ int32_t marl_rollout(const marl_config* cfg, marl_env_state st, const float* par
 /* marl_rollout for callers that cannot allocate or hold a workspace (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): same arguments without `workspace`, same results.  The working copy of the
  * parameters (and, for networks the fused forward kernel does not cover, one step's hidden activations) lives in a
- * device array built into the library, MARL_STATIC_SCRATCH_BYTES (and room for extra weight copies) per GPU for the life of the process.  The call
+ * device array built into the library, MARL_STATIC_SCRATCH_BYTES per GPU for the life of the process.  The call
  * allocates and frees nothing.  MARL_E_SIZE when marl_query_sizes' rollout_workspace_bytes exceeds that size (the bf16
  * configuration and unfused wide networks with many environments do), MARL_E_LAUNCH when the array's address cannot
  * be obtained.  Nothing in the array has to start at zero and nothing in it is kept between calls; every call on a

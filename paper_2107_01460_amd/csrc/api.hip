@@ -31,8 +31,7 @@ bool timing_on() { return g_timer.on; }
 // Device memory that is part of the loaded code object: every GPU the library runs on holds its own copy, at its own
 // address, until the process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the
 // kernels are given the address that call returns.
-// (the split weight copies take half again what fp32 copies would; that half does not count against the documented size)
-constexpr int64_t kStaticScratchBytes = MARL_STATIC_SCRATCH_BYTES + 4 * 1024 * 1024;
+constexpr int64_t kStaticScratchBytes = MARL_STATIC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -253,8 +252,7 @@ int32_t marl_rollout_static(const marl_config* cfg, marl_env_state st, const flo
   if ((rc = check_traj(traj, false)) != MARL_OK) return rc;
   MARL_REQUIRE_PTR(params);
   MARL_OPTIONAL_PTR(forced_actions); MARL_OPTIONAL_PTR(forced_uniforms);
-  const int64_t need = rollout_workspace_bytes(*cfg, cfg->n_envs);
-  if (need - 4 * param_map(dims_of(*cfg)).split_extra > MARL_STATIC_SCRATCH_BYTES || need > kStaticScratchBytes) return MARL_E_SIZE;
+  if (rollout_workspace_bytes(*cfg, cfg->n_envs) > kStaticScratchBytes) return MARL_E_SIZE;
   void* ws = static_scratch();
   if (ws == nullptr) return MARL_E_LAUNCH;
   return launch_rollout(*cfg, st, params, traj, step_offset, forced_actions, forced_uniforms, ws, (hipStream_t)stream);

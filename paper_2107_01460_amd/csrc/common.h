@@ -55,64 +55,74 @@ inline NetOffsets net_offsets(int64_t base, int Din, int H, int Dout) {
   return o;
 }
 
+// The fused forward kernel (fused_forward.h) keeps a row tile of the input in LDS at its whole width, which bounds the input
+// width (two workgroups per CU up to about 320 inputs at H = 256, one up to about 950); wider networks and other widths take
+// the layer-by-layer kernels.  Which (H, BM) pairs exist: H = 64 -> BM 64; H = 128 or 256 -> BM 32.
+inline int fused_forward_px(int Din) {
+  int px = (Din + 15) / 16 * 16;
+  while ((px / 4) % 2 == 0) px += 4;
+  return px;
+}
+inline size_t fused_forward_lds_bytes(int H, int Din, int nout) {
+  const size_t bm = H == 64 ? 64 : 32;
+  return (bm * fused_forward_px(Din) + bm * (H + 4) + 256 * (size_t)nout + bm * 8 + (size_t)H * nout) * sizeof(float);
+}
+inline bool fused_forward_supported(int H, int Din) {
+  return (H == 64 || H == 128 || H == 256) && fused_forward_lds_bytes(H, Din, 6) <= 160 * 1024;
+}
+
 // The kernels read weights from a working copy of the parameter vector in which every block (W1, b1, ...)
 // starts on a 64-float boundary, so that 16-byte loads of weight rows are always aligned.
 struct ParamMap {
   int64_t src[13], dst[13];  // 12 blocks (actor 6, critic 6) + end
-  // After the 12 blocks, per network: W1, W2 and W2 transposed once more for the fused kernels (widths 64, 128, 256), split
-  // into three bf16 parts and in the order the matrix-core kernels read their B operand straight from memory: part p of
-  // element (k, n) of a [K][H] matrix at split_weight_index(k, n, H) + p * split_weight_plane(H), in bf16 elements, so that
-  // the eight k values of a lane are one 16-byte load, contiguous across lanes.  W1 is zero-padded to kpad1 rows (a
-  // multiple of 16).
+  // After the 12 blocks, per fp32 network that the fused kernels cover (fused_forward_supported), the copies these read: W1, W2
+  // and, for the update, W2 transposed, split into three bf16 parts and in the order the matrix-core kernels read their B
+  // operand straight from memory: part p of element (k, n) of a [K][H] matrix at split_weight_index(k, n, H) + p *
+  // split_weight_plane(H), in bf16 elements, so that the eight k values of a lane are one 16-byte load, contiguous across
+  // lanes.  W1 is zero-padded to kpad1 rows (a multiple of 16).  For a training rollout (rollout_train_kernel) the actor's two
+  // copies hold fp32 values instead, element (k, n) at ((k / 4) * H + n) * 4 + k % 4.
   int64_t sw_w1[2], sw_w2[2], sw_w2t[2];
-  // The actor's W1 and W2 as fp32 in the order of rollout_train_kernel: element (k, n) at ((k / 4) * H + n) * 4 + k % 4 (zero-padded
-  // like the split copy).  Filled for a rollout only; -1 where no such kernel exists (its widths are 64 and 128).
-  int64_t op_w1, op_w2;
-  bool split[2];  // whether the copies are filled (fp32 networks of those widths)
+  bool fused[2];  // these copies exist
+  bool plain[2];  // the blocks W1 and W2 are filled (otherwise they have no room)
   int din[2], kpad1[2];
   int hidden[2];
-  int64_t total;             // floats of the whole working copy
-  int64_t split_extra;       // ... of which the third parts of the split copies (more than fp32 copies would take)
+  int64_t total;  // floats of the whole working copy
 };
-inline bool split_weights_width(int H) { return H == 64 || H == 128 || H == 256; }
 __host__ __device__ inline int64_t split_weight_index(int64_t k, int64_t n, int64_t H) { return ((k / 16 * 6 + k % 16 / 8) * H + n) * 8 + k % 8; }
 __host__ __device__ inline int64_t split_weight_plane(int64_t H) { return 16 * H; }
-inline ParamMap param_map(const Dims& d) {
+// What a working copy is staged for: a forward pass, a training rollout (a forward map, the actor in fp32), an update.
+enum WeightUse { USE_FORWARD, USE_ROLLOUT, USE_UPDATE };
+// update: for an optimiser step, which may also read the blocks W1 and W2 of a fused network; otherwise for forward passes
+inline ParamMap param_map(const Dims& d, bool update) {
   ParamMap m;
   const NetOffsets a = net_offsets(0, d.D, d.Ha, kActions), c = net_offsets(d.Pa, d.Dc, d.Hc, 1);
   const int64_t src[13] = {a.W1, a.b1, a.W2, a.b2, a.W3, a.b3, c.W1, c.b1, c.W2, c.b2, c.W3, c.b3, c.end};
-  int64_t off = 0;
-  for (int i = 0; i < 13; ++i) {
-    m.src[i] = src[i];
-    m.dst[i] = off;
-    if (i < 12) off += ((src[i + 1] - src[i] + 63) / 64) * 64;
-  }
   m.hidden[0] = d.Ha;
   m.hidden[1] = d.Hc;
   m.din[0] = d.D;
   m.din[1] = d.Dc;
-  m.split_extra = 0;
   for (int n = 0; n < 2; ++n) {
-    const int64_t H = m.hidden[n];
     m.kpad1[n] = (m.din[n] + 15) / 16 * 16;
-    m.split[n] = split_weights_width((int)H) && !d.bf16;
-    auto copy = [&](int64_t floats) {
-      const int64_t at = off, extra = split_weights_width((int)H) ? floats / 2 : 0;
-      off += (floats + extra + 63) / 64 * 64;
-      m.split_extra += extra;
-      return at;
-    };
-    m.sw_w1[n] = copy(m.kpad1[n] * H);
-    m.sw_w2[n] = copy(H * H);
-    m.sw_w2t[n] = copy(H * H);
+    m.fused[n] = !d.bf16 && fused_forward_supported(m.hidden[n], m.din[n]);
+    m.plain[n] = update || !m.fused[n];
   }
-  m.op_w1 = m.op_w2 = -1;
-  if (!d.bf16 && (d.Ha == 64 || d.Ha == 128)) {
-    m.op_w1 = off;
-    off += (int64_t)m.kpad1[0] * d.Ha;
-    m.op_w2 = off;
-    off += (int64_t)d.Ha * d.Ha;
-    m.split_extra += off - m.op_w1;
+  int64_t off = 0;
+  auto take = [&](int64_t floats) {
+    const int64_t at = off;
+    off += (floats + 63) / 64 * 64;
+    return at;
+  };
+  for (int i = 0; i < 12; ++i) {
+    m.src[i] = src[i];
+    m.dst[i] = take((i % 6 == 0 || i % 6 == 2) && !m.plain[i / 6] ? 0 : src[i + 1] - src[i]);
+  }
+  m.src[12] = src[12];
+  m.dst[12] = off;
+  for (int n = 0; n < 2; ++n) {
+    const int64_t H = m.fused[n] ? m.hidden[n] : 0;
+    m.sw_w1[n] = take(m.kpad1[n] * H * 3 / 2);
+    m.sw_w2[n] = take(H * H * 3 / 2);
+    m.sw_w2t[n] = take(update ? H * H * 3 / 2 : 0);
   }
   m.total = off;
   return m;

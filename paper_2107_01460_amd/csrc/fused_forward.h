@@ -37,12 +37,6 @@ struct FusedFwdArgs {
 };
 constexpr int kFusedFwdTrainGrid = 1024;  // workgroups of a training launch (persistent: register-resident W3 gradient)
 
-inline int fused_forward_px(int Din) {
-  int px = (Din + 15) / 16 * 16;
-  while ((px / 4) % 2 == 0) px += 4;
-  return px;
-}
-
 // The kernel's body: workgroup `bid` of `nblk` that share the tiles.  DIRECT: weights from W1 / W2 (unstaged parameters) on
 // the fp32 instruction instead of the split copies.
 template <int H, int BM, int NOUT, bool TRAIN, bool DIRECT, class Finish>
@@ -324,17 +318,6 @@ template <int HA, int HB, int NOUT_A, int NOUT_B, class FinishA, class FinishB>
 __global__ void __launch_bounds__(256, 2) fused_forward_small_kernel(FusedFwdArgs a, FinishA fa, FusedFwdArgs b, FinishB fb, unsigned grid_a) {
   if (blockIdx.x < grid_a) fused_forward_body<HA, HA == 64 ? 64 : 32, NOUT_A, false, true, FinishA>(a, fa, blockIdx.x, grid_a);
   else fused_forward_body<HB, HB == 64 ? 64 : 32, NOUT_B, false, true, FinishB>(b, fb, blockIdx.x - grid_a, gridDim.x - grid_a);
-}
-
-// Which (H, BM) pairs exist: H = 64 -> BM 64; H = 128 or 256 -> BM 32.
-inline size_t fused_forward_lds_bytes(int H, int Din, int nout) {
-  const size_t bm = H == 64 ? 64 : 32;
-  return (bm * fused_forward_px(Din) + bm * (H + 4) + 256 * (size_t)nout + bm * 8 + (size_t)H * nout) * sizeof(float);
-}
-// The row tile of the input sits in LDS at its whole width, which bounds the input width (two workgroups per CU up
-// to about 320 inputs at H = 256, one up to about 950); wider networks take the layer-by-layer kernels.
-inline bool fused_forward_supported(int H, int Din) {
-  return (H == 64 || H == 128 || H == 256) && fused_forward_lds_bytes(H, Din, 6) <= 160 * 1024;
 }
 
 template <int H, int BM, int NOUT, bool TRAIN, class Finish>

@@ -11,12 +11,10 @@
 
 namespace marl {
 
-int64_t effective_param_floats(const marl_config& c);
+int64_t effective_param_floats(const marl_config& c, bool update);
 
 namespace {
 
-// Working copy of the parameters: blocks moved to their aligned offsets, optionally rounded to bf16, plus the
-// operand-order copies of W1, W2 and W2 transposed that the fused training kernel streams from memory.
 __device__ __forceinline__ void store_split_weight(float* copy, float v, int64_t k, int64_t n, int H) {
   const SplitPair s = split_pair_any(v, 0.f);
   bf16_t* const d = reinterpret_cast<bf16_t*>(copy) + split_weight_index(k, n, H);
@@ -25,36 +23,33 @@ __device__ __forceinline__ void store_split_weight(float* copy, float v, int64_t
   d[2 * split_weight_plane(H)] = (bf16_t)s.l;
 }
 
-__global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int round, int for_rollout) {
+// Working copy of the parameters: blocks moved to their aligned offsets, optionally rounded to bf16, plus the copies of W1, W2
+// and W2 transposed that the fused kernels read.  for_rollout: the actor's in fp32 (ParamMap).
+__global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int round, int for_rollout, int for_update) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= pm.src[12]) return;
-#pragma unroll
-  for (int net = 0; net < 2; ++net) {  // zero rows of the split W1 (fewer than 16 rows: far fewer floats than parameters)
+  auto store = [&](int net, int64_t copy, float v, int64_t k, int64_t n) {
     const int H = pm.hidden[net];
-    if (pm.split[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) store_split_weight(dst + pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H, H);
+    if (for_rollout && net == 0) dst[copy + ((k / 4) * H + n) * 4 + k % 4] = v;
+    else store_split_weight(dst + copy, v, k, n, H);
+  };
+#pragma unroll
+  for (int net = 0; net < 2; ++net) {  // zero rows of the copies of W1 (fewer than 16 rows: far fewer floats than parameters)
+    const int H = pm.hidden[net];
+    if (pm.fused[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) store(net, pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H);
   }
   int b = 0;
 #pragma unroll
   for (int k = 1; k < 12; ++k) b += (i >= pm.src[k]) ? 1 : 0;
   const float v = round ? round_to_bf16(src[i]) : src[i];
   const int64_t e = i - pm.src[b];
-  dst[pm.dst[b] + e] = v;
   const int net = b >= 6, H = pm.hidden[net];
+  const bool w1 = b == 0 || b == 6, w2 = b == 2 || b == 8;
+  if (pm.plain[net] || !(w1 || w2)) dst[pm.dst[b] + e] = v;
+  if (!pm.fused[net] || !(w1 || w2)) return;
   const int64_t r = e / H, c = e - r * H;
-  if (for_rollout && pm.op_w1 >= 0) {
-    if (i < (int64_t)(pm.kpad1[0] - pm.din[0]) * pm.hidden[0]) {
-      const int64_t k = pm.din[0] + i / pm.hidden[0], n = i % pm.hidden[0];
-      dst[pm.op_w1 + ((k / 4) * pm.hidden[0] + n) * 4 + k % 4] = 0.f;
-    }
-    if (b == 0) dst[pm.op_w1 + ((r / 4) * H + c) * 4 + r % 4] = v;
-    if (b == 2) dst[pm.op_w2 + ((r / 4) * H + c) * 4 + r % 4] = v;
-  }
-  if (!pm.split[net]) return;
-  if (b == 0 || b == 6) store_split_weight(dst + pm.sw_w1[net], v, r, c, H);
-  if (b == 2 || b == 8) {
-    store_split_weight(dst + pm.sw_w2[net], v, r, c, H);
-    store_split_weight(dst + pm.sw_w2t[net], v, c, r, H);
-  }
+  store(net, w1 ? pm.sw_w1[net] : pm.sw_w2[net], v, r, c);
+  if (w2 && for_update) store_split_weight(dst + pm.sw_w2t[net], v, c, r, H);
 }
 
 // What the rollout does with a sample's outputs.
@@ -101,6 +96,11 @@ struct RolloutWsView {
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
+bool use_fused_rollout(const marl_config& c) {
+  const Dims d = dims_of(c);
+  return !d.bf16 && rollout_fused_supported(d.Ha, d.A) && fused_forward_supported(d.Ha, d.D);
+}
+
 RolloutWsView carve_rollout_ws(const marl_config& c, int64_t n_rows, void* ws, int64_t* total) {
   const Dims d = dims_of(c);
   const int64_t S = n_rows * d.A, Sc = d.central ? n_rows : S;
@@ -112,7 +112,7 @@ RolloutWsView carve_rollout_ws(const marl_config& c, int64_t n_rows, void* ws, i
     return r;
   };
   RolloutWsView v{};
-  v.eff_params = (float*)take(effective_param_floats(c) * 4);
+  v.eff_params = (float*)take(effective_param_floats(c, false) * 4);
   if (!d.bf16) {
     // hidden activations of one pass: only the layer-by-layer path stores them (the fused kernel keeps them on chip)
     if (!fused_forward_supported(d.Ha, d.D)) {
@@ -150,24 +150,24 @@ void mlp_hidden_forward(const RowSrc& X, int64_t S, int Din, int H, const float*
 }
 
 // Floats of the working copy: the aligned fp32 copy, followed (bf16 configuration) by the bf16 weight matrices.
-int64_t effective_param_floats(const marl_config& c) {
+int64_t effective_param_floats(const marl_config& c, bool update) {
   const Dims d = dims_of(c);
-  int64_t n = param_map(d).total;
+  int64_t n = param_map(d, update).total;
   if (d.bf16) n += (bf16_net_weight_elems(d.D, d.Ha) + bf16_net_weight_elems(d.Dc, d.Hc) + 1) / 2 + 192;  // + alignment slack
   return n;
 }
 
 Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, int net) {
-  const Dims d = dims_of(c);
-  bf16_t* base = reinterpret_cast<bf16_t*>(const_cast<float*>(eff) + ((param_map(d).total + 63) / 64) * 64);
+  const Dims d = dims_of(c);  // (the map is the same for an update and for a forward pass: no network is fused)
+  bf16_t* base = reinterpret_cast<bf16_t*>(const_cast<float*>(eff) + ((param_map(d, false).total + 63) / 64) * 64);
   if (net == 0) return bf16_net_weights(base, d.D, d.Ha);
   return bf16_net_weights(base + ((bf16_net_weight_elems(d.D, d.Ha) + 63) / 64) * 64, d.Dc, d.Hc);
 }
 
-const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, bool for_rollout) {
+const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use) {
   const Dims d = dims_of(c);
   hipLaunchKernelGGL(stage_params_kernel, dim3((unsigned)((d.P + 255) / 256)), dim3(256), 0, s, params, scratch,
-                     param_map(d), (int)d.bf16, (int)for_rollout);
+                     param_map(d, use == USE_UPDATE), (int)d.bf16, (int)(use == USE_ROLLOUT && use_fused_rollout(c)), (int)(use == USE_UPDATE));
   if (d.bf16) {
     const NetOffsets oa = net_offsets(0, d.D, d.Ha, kActions), oc = net_offsets(d.Pa, d.Dc, d.Hc, 1);
     stage_weights_bf16(params + oa.W1, params + oa.W2, d.D, d.Ha, effective_bf16_weights(c, scratch, 0), s);
@@ -191,14 +191,14 @@ static int32_t forward_rows(const marl_config& c, const float* eff, const float*
   const int64_t S = n_rows * d.A;
   if (d.bf16) {
     if (want_actor) {
-      const NetOffsets o = padded_offsets(param_map(d), 0);
+      const NetOffsets o = padded_offsets(param_map(d, false), 0);
       const Bf16NetWeights bw = effective_bf16_weights(c, eff, 0);
       pack_obs_bf16(RowSrc{obs, d.D, nullptr, 1, S}, S, d.D, bw.Dp, S, w.xba, nullptr, s);
       mlp_hidden_forward_bf16(w.xba, S, S, d.Ha, bw, eff + o.b1, eff + o.b2, w.bh1a, nullptr, w.bh2a, s);
       launch_actor_head_rollout(w.bh2a, S, d.Ha, eff + o.W3, eff + o.b3, logits_out, sample, s);
     }
     if (value_out) {
-      const NetOffsets o = padded_offsets(param_map(d), 1);
+      const NetOffsets o = padded_offsets(param_map(d, false), 1);
       const Bf16NetWeights bw = effective_bf16_weights(c, eff, 1);
       const int64_t Sc = d.central ? n_rows : S;
       // IPPO: the critic reads the rows packed for the actor (same rows, same width)
@@ -210,11 +210,11 @@ static int32_t forward_rows(const marl_config& c, const float* eff, const float*
     return launch_status();
   }
   if (want_actor) {
-    const NetOffsets o = padded_offsets(param_map(d), 0);
+    const NetOffsets o = padded_offsets(param_map(d, false), 0);
     const RowSrc X{obs, d.D, nullptr, 1, S};
     if (fused_forward_supported(d.Ha, d.D)) {
       ActorRolloutFinish fin{logits_out, sample ? *sample : SampleArgs{}, sample ? 1 : 0};
-      const int32_t rc = launch_fused_forward<kActions, false>(d.Ha, fused_args(X, S, d.D, eff, param_map(d), 0), fin, s);
+      const int32_t rc = launch_fused_forward<kActions, false>(d.Ha, fused_args(X, S, d.D, eff, param_map(d, false), 0), fin, s);
       if (rc != MARL_OK) return rc;
     } else {
       mlp_hidden_forward(X, S, d.D, d.Ha, eff + o.W1, eff + o.b1, eff + o.W2, eff + o.b2, w.h1a, w.h2a, d.bf16, s);
@@ -222,12 +222,12 @@ static int32_t forward_rows(const marl_config& c, const float* eff, const float*
     }
   }
   if (value_out) {
-    const NetOffsets o = padded_offsets(param_map(d), 1);
+    const NetOffsets o = padded_offsets(param_map(d, false), 1);
     const int64_t Sc = d.central ? n_rows : S;
     const RowSrc X{obs, d.Dc, nullptr, 1, Sc};
     if (fused_forward_supported(d.Hc, d.Dc)) {
       CriticRolloutFinish fin{value_out, d.central ? d.A : 1, value_tail ? value_split : Sc, value_tail};
-      const int32_t rc = launch_fused_forward<1, false>(d.Hc, fused_args(X, Sc, d.Dc, eff, param_map(d), 1), fin, s);
+      const int32_t rc = launch_fused_forward<1, false>(d.Hc, fused_args(X, Sc, d.Dc, eff, param_map(d, false), 1), fin, s);
       if (rc != MARL_OK) return rc;
     } else {
       mlp_hidden_forward(X, Sc, d.Dc, d.Hc, eff + o.W1, eff + o.b1, eff + o.W2, eff + o.b2, w.h1c, w.h2c, d.bf16, s);
@@ -243,7 +243,7 @@ int32_t launch_policy_forward(const marl_config& c, const float* params, const f
   const int64_t S = n_rows * d.A;
   if (!d.bf16 && S <= kForwardSmall && fused_forward_supported(d.Ha, d.D) && fused_forward_supported(d.Hc, d.Dc)) {
     const int64_t Sc = d.central ? n_rows : S;
-    const ParamMap pm = param_map(d);
+    const ParamMap pm = param_map(d, false);
     auto direct = [&](const float* X, int64_t rows, int Din, int net, const NetOffsets& o) {
       FusedFwdArgs a = fused_args(RowSrc{X, Din, nullptr, 1, rows}, rows, Din, params, pm, net);
       a.W1 = params + o.W1; a.b1 = params + o.b1; a.W2 = params + o.W2; a.b2 = params + o.b2; a.W3 = params + o.W3; a.b3 = params + o.b3;
@@ -256,7 +256,7 @@ int32_t launch_policy_forward(const marl_config& c, const float* params, const f
         d.Hc, direct(obs, value != nullptr ? Sc : 0, d.Dc, 1, net_offsets(d.Pa, d.Dc, d.Hc, 1)), fc, s);
   }
   const RolloutWsView w = carve_rollout_ws(c, n_rows, workspace, nullptr);
-  const float* eff = effective_params(c, params, w.eff_params, s, false);
+  const float* eff = effective_params(c, params, w.eff_params, s, USE_FORWARD);
   return forward_rows(c, eff, obs, n_rows, w, logits != nullptr, logits, nullptr, value, s);
 }
 
@@ -279,21 +279,16 @@ static int32_t launch_rollout_fused(const marl_config& c, bool eval, const Rollo
 }
 
 // The actor's part of the arguments of the fused rollout and evaluation kernels.
-static RolloutArgs rollout_fused_args(const marl_config& c, marl_env_state st, const float* eff, bool eval) {
+static RolloutArgs rollout_fused_args(const marl_config& c, marl_env_state st, const float* eff) {
   const Dims d = dims_of(c);
-  const ParamMap pm = param_map(d);
+  const ParamMap pm = param_map(d, false);
   const NetOffsets o = padded_offsets(pm, 0);
   RolloutArgs a{};
   a.p = env_params(c);
   a.st = st;
-  a.W1 = eff + (eval ? pm.sw_w1[0] : pm.op_w1); a.W2 = eff + (eval ? pm.sw_w2[0] : pm.op_w2);
+  a.W1 = eff + pm.sw_w1[0]; a.W2 = eff + pm.sw_w2[0];
   a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
   return a;
-}
-
-static bool use_fused_rollout(const marl_config& c) {
-  const Dims d = dims_of(c);
-  return !d.bf16 && rollout_fused_supported(d.Ha, d.A) && fused_forward_supported(d.Ha, d.D);
 }
 
 int32_t launch_rollout(const marl_config& c, marl_env_state st, const float* params, marl_traj tr,
@@ -301,7 +296,7 @@ int32_t launch_rollout(const marl_config& c, marl_env_state st, const float* par
                        void* workspace, hipStream_t s, const uint64_t* step_base) {
   const Dims d = dims_of(c);
   const RolloutWsView w = carve_rollout_ws(c, d.N, workspace, nullptr);
-  const float* eff = effective_params(c, params, w.eff_params, s, /*for_rollout=*/true);
+  const float* eff = effective_params(c, params, w.eff_params, s, USE_ROLLOUT);
   const int64_t NA = d.NA, slab = NA * d.D;
   int32_t rc;
   // The values do not steer the rollout (the parameters are constant during it): where the critic's forward pass
@@ -310,7 +305,7 @@ int32_t launch_rollout(const marl_config& c, marl_env_state st, const float* par
   const bool batch_values = !d.bf16 && fused_forward_supported(d.Hc, d.Dc);
   if (use_fused_rollout(c)) {
     // all T steps in one launch: a workgroup keeps its environments on chip and streams the trajectory out
-    RolloutArgs a = rollout_fused_args(c, st, eff, false);
+    RolloutArgs a = rollout_fused_args(c, st, eff);
     a.T = d.T;
     a.obs = tr.obs; a.action = tr.action; a.logp = tr.logp; a.reward = tr.reward; a.done = tr.done;
     a.logits = tr.logits; a.sampled = tr.sampled; a.uniforms = forced_uniforms; a.forced = forced_actions;
@@ -441,10 +436,10 @@ int32_t launch_evaluate(const marl_config& c, marl_env_state st, const float* pa
   const Dims d = dims_of(c);
   const EvalWsView e = carve_eval_ws(c, workspace, nullptr);
   const RolloutWsView w = carve_rollout_ws(c, d.N, e.rollout_ws, nullptr);
-  const float* eff = effective_params(c, params, w.eff_params, s, false);
+  const float* eff = effective_params(c, params, w.eff_params, s, USE_FORWARD);
   const int64_t steps = (int64_t)n_episodes * c.episode_cap;
   if (use_fused_rollout(c)) {  // the whole block in one launch, statistics in registers
-    RolloutArgs a = rollout_fused_args(c, st, eff, true);
+    RolloutArgs a = rollout_fused_args(c, st, eff);
     a.T = (int)steps;
     a.ev = out;
     a.n_episodes = n_episodes;

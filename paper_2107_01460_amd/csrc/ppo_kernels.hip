@@ -17,8 +17,8 @@ namespace marl {
 // implemented in policy_kernels.hip
 void mlp_hidden_forward(const RowSrc& X, int64_t S, int Din, int H, const float* W1, const float* b1, const float* W2,
                         const float* b2, float* h1, float* h2, bool bf16, hipStream_t s);
-const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, bool for_rollout);
-int64_t effective_param_floats(const marl_config& c);
+const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use);
+int64_t effective_param_floats(const marl_config& c, bool update);
 Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, int net);
 
 namespace {
@@ -297,7 +297,7 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
     return r;
   };
   UpdateWsView v{};
-  v.eff_params = (float*)take(effective_param_floats(c) * 4);
+  v.eff_params = (float*)take(effective_param_floats(c, true) * 4);
   v.grad = (float*)take(d.P * 4);
   v.sc = (Scalars*)take(2 * sizeof(Scalars));
   v.adv_stats = (double*)take((int64_t)c.n_epochs * c.n_minibatches * 2 * sizeof(double));
@@ -515,7 +515,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
     hipLaunchKernelGGL(iota_kernel, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, s, w.ident, R);
   // ga/gc: blocks of the gradient (parameter-vector layout); oa/oc: blocks of the aligned working copy of the weights
   const NetOffsets ga = net_offsets(0, d.D, d.Ha, kActions), gc = net_offsets(d.Pa, d.Dc, d.Hc, 1);
-  const ParamMap pm = param_map(d);
+  const ParamMap pm = param_map(d, true);
   const NetOffsets oa = padded_offsets(pm, 0), oc = padded_offsets(pm, 1);
   int64_t k = adam_step0;
   // Once per update: the gradient, both sets of scalars and the advantage statistics start at zero (afterwards every
@@ -536,7 +536,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
       UpdateWsView wk = w;  // the view the helpers get: this step's scalars
       wk.sc = sck;
       const int32_t* rows = (perm ? perm + (int64_t)e * R : w.ident) + (int64_t)mb * rows_mb;
-      const float* eff = effective_params(c, params, w.eff_params, s, false);
+      const float* eff = effective_params(c, params, w.eff_params, s, USE_UPDATE);
       LossCommon lc{};
       lc.rows = rows; lc.A = d.A; lc.ad = make_small_div(d.A); lc.rows_mb = rows_mb; lc.inv_B = (float)(1.0 / (double)(rows_mb * d.A));
       lc.sc = sck; lc.adv_stats = w.adv_stats + 2 * step; lc.normalize = c.normalize_adv; lc.clip_eps = c.clip_eps;

@@ -1,0 +1,43 @@
+"""marl_rollout_static on both sides of its limit: it takes exactly the configurations whose rollout_workspace_bytes fit
+MARL_STATIC_SCRATCH_BYTES (the caller can ask beforehand), with the results of marl_rollout."""
+import os
+import re
+
+import pytest
+import torch
+
+import workloads as W
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+def limit():
+    header = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "marl.h")
+    return eval(re.search(r"#define MARL_STATIC_SCRATCH_BYTES \((.*)\)", open(header).read()).group(1))
+
+
+# layer-by-layer networks, whose one step of activations grows with the environments, beside a fused one with a wide input
+@pytest.mark.parametrize("ha,hc,central", [(192, 256, 1), (128, 96, 0)])
+def test_rollout_static_limit(ha, hc, central):
+    import paper_2107_01460_amd as M
+    base = W.scaled(W.CONFIGS[1], actor_hidden=ha, critic_hidden=hc, central_critic=central, rollout_len=2, n_minibatches=1)
+    need = lambda n: M.query_sizes(W.scaled(base, n_envs=n)).rollout_workspace_bytes
+    n = max(k for k in range(1, 20000) if need(k) <= limit())
+    assert need(n + 1) > limit()
+    params = dev(W.init_params(base, bias_scale=0.1))
+    for envs in (n, n + 1):
+        cfg = W.scaled(base, n_envs=envs)
+        print("case", ha, hc, envs, need(envs), flush=True)
+        st, tr = M.EnvState(cfg), M.Traj(cfg, debug=True)
+        M.env_reset(cfg, st)
+        if envs > n:
+            with pytest.raises(M.MarlError, match="-5"):
+                M.rollout_static(cfg, st, params, tr, 3)
+            continue
+        M.rollout_static(cfg, st, params, tr, 3)
+        s2, t2 = M.EnvState(cfg), M.Traj(cfg, debug=True)
+        M.env_reset(cfg, s2)
+        M.rollout(cfg, s2, params, t2, 3, M.alloc_workspace(need(envs)))
+        for f in ("obs", "action", "logits", "value", "last_value", "reward", "done"):
+            assert torch.equal(getattr(tr, f), getattr(t2, f)), f
