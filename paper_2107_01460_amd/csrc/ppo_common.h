@@ -254,7 +254,8 @@ struct CriticLoss {
 // with plain stores, and is added in a fixed order by the launcher.  (With atomics the 2048 workgroups queued up on the same
 // few cache lines: 460 us of the 480 us a launch on 98 304 samples took; 131 us for 1 048 576 now, 537 MB of activations.)
 // DZ2: H2 is replaced by dz2 = (dL/dout W3^T)(1 - h2^2), the gradient of its pre-activations, which the tile in LDS gives
-// without another pass over the activations (a kernel of its own took 76 us for 50 000 samples of 192 units).
+// without another pass over the activations (a kernel of its own took 76 us for 50 000 samples of 192 units).  Otherwise dL/dout
+// goes to dl_out [S][NOUT] and H2 stays.
 // Bound: memory and, per tile, a chain of three barriers, which the other workgroup of the compute unit and the next
 // tile's loads, already in flight, cover.
 constexpr int kLossHeadGrid = 512;
@@ -346,8 +347,10 @@ __global__ void __launch_bounds__(256, 2) loss_head_kernel(float* H2, int64_t S,
       }
       if (s0 + tid < S) {
         fn.compute(cur, prep, out, dl, st);
+        if (!DZ2) {
 #pragma unroll
-        for (int k = 0; k < NOUT; ++k) dl_out[(s0 + tid) * NOUT + k] = dl[k];
+          for (int k = 0; k < NOUT; ++k) dl_out[(s0 + tid) * NOUT + k] = dl[k];
+        }
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) dls[tid * 8 + k] = k < NOUT ? dl[k < NOUT ? k : 0] : 0.f;

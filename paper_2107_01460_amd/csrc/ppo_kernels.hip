@@ -265,11 +265,11 @@ struct UpdateWsView {
   Scalars* sc;        // two sets: optimiser step k accumulates into set k % 2 while its Adam kernel zeroes the other
   double* adv_stats;  // [n_epochs * n_minibatches][2]: sum and sum of squares of every minibatch's advantages
   int32_t* ident;
-  float *h1a, *h2a, *dz1a, *dla;
-  float *h1c, *h2c, *dz1c, *dlc;
+  float *h1a, *h2a, *dz1a;
+  float *h1c, *h2c, *dz1c;
   float* partial;  // per-workgroup copies of one network's gradient (two-stage reduction of the fused training kernel)
   float* partial_w1;
-  float* partial_head;  // per-workgroup W3 / b3 gradients of the output-layer kernels 
+  float* partial_head;  // per-workgroup W3 / b3 gradients of the output-layer kernels
   float* split_ws;      // fp32 layer-by-layer networks: the k splits of a weight-gradient product, added in a fixed order
   int64_t split_floats;
   // bf16 configuration: one set of activation buffers, used by the actor and then by the critic
@@ -308,11 +308,9 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
     v.h1a = (float*)take(Sap * d.Ha * 4);
     v.h2a = (float*)take(Sap * d.Ha * 4);
     v.dz1a = (float*)take(Sap * d.Ha * 4);
-    v.dla = (float*)take(Sa * kActions * 4);
     v.h1c = (float*)take(Scp * d.Hc * 4);
     v.h2c = (float*)take(Scp * d.Hc * 4);
     v.dz1c = (float*)take(Scp * d.Hc * 4);
-    v.dlc = (float*)take(Sc * 4);
     int64_t pmax = 0;
     if (fused_train_supported(d.Ha, d.D)) pmax = std::max<int64_t>(pmax, d.Pa);
     if (fused_train_supported(d.Hc, d.Dc)) pmax = std::max<int64_t>(pmax, d.P - d.Pa);
@@ -330,8 +328,6 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
   } else {
     const int64_t Sp = round_up64(std::max(Sa, Sc));
     const int64_t Dp = round_up64(std::max(d.D, d.Dc)), H = std::max(d.Ha, d.Hc);
-    v.dla = (float*)take(Sa * kActions * 4);
-    v.dlc = (float*)take(Sc * 4);
     v.xb = (bf16_t*)take(Sp * Dp * 2);
     v.xbT = (bf16_t*)take(Sp * Dp * 2);
     v.bh1 = (bf16_t*)take(Sp * H * 2);
@@ -444,8 +440,7 @@ void mlp_backward(const RowSrc& X, int64_t S, int Din, int H, const float* W2, c
 // cores; the output layer, the loss and dz2 stay on the ALUs in fp32.
 template <int NOUT, class LossFn>
 void train_net_bf16(const RowSrc& X, int64_t S, int Din, int H, const Bf16NetWeights& bw, const float* eff,
-                    const NetOffsets& o, float* grad, const NetOffsets& go, const LossFn& fn, float* dl,
-                    const UpdateWsView& w, bool packed, hipStream_t s) {
+                    const NetOffsets& o, float* grad, const NetOffsets& go, const LossFn& fn, const UpdateWsView& w, bool packed, hipStream_t s) {
   const int64_t Sp = round_up64(S);
   if (!packed) pack_obs_bf16(X, S, Din, bw.Dp, Sp, w.xb, w.xbT, s);  // packed: the previous network left these very rows there
   mlp_hidden_forward_bf16(w.xb, S, Sp, H, bw, eff + o.b1, eff + o.b2, w.bh1, w.bh1T, w.bh2, s);
@@ -569,7 +564,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
       if (!pair) {
         ActorLoss fn{lc, tr.action, tr.logp, tr.adv};
         if (d.bf16) {
-          train_net_bf16<kActions>(Xa, Sa, d.D, d.Ha, effective_bf16_weights(c, eff, 0), eff, oa, w.grad, ga, fn, w.dla, wk, false, s);
+          train_net_bf16<kActions>(Xa, Sa, d.D, d.Ha, effective_bf16_weights(c, eff, 0), eff, oa, w.grad, ga, fn, wk, false, s);
         } else if (fused_train_supported(d.Ha, d.D) && Sa < ((int64_t)1 << 31)) {
           FusedTrainArgs ta{};
           ta.X = Xa; ta.S = Sa; ta.Din = d.D; ta.px = fused_train_px(d.D);
@@ -593,7 +588,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
             if (rc != MARL_OK) return rc;
           } else {
             mlp_hidden_forward(Xa, Sa, d.D, d.Ha, eff + oa.W1, eff + oa.b1, eff + oa.W2, eff + oa.b2, w.h1a, w.h2a, d.bf16, s);
-            const int32_t rc = launch_loss_head<kActions, true>(w.h2a, Sa, d.Ha, eff + oa.W3, eff + oa.b3, fn, w.dla, w.grad + ga.W3,
+            const int32_t rc = launch_loss_head<kActions, true>(w.h2a, Sa, d.Ha, eff + oa.W3, eff + oa.b3, fn, nullptr, w.grad + ga.W3,
                                                           w.partial_head, sck, s);
             if (rc != MARL_OK) return rc;
           }
@@ -607,7 +602,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
         CriticLoss fn{lc, tr.ret, tr.value, d.central ? d.A : 1};
         if (d.bf16) {
           // IPPO: the critic reads the rows the actor has just packed (same rows, same width)
-          train_net_bf16<1>(Xc, Sc, d.Dc, d.Hc, effective_bf16_weights(c, eff, 1), eff, oc, w.grad, gc, fn, w.dlc, wk, !d.central, s);
+          train_net_bf16<1>(Xc, Sc, d.Dc, d.Hc, effective_bf16_weights(c, eff, 1), eff, oc, w.grad, gc, fn, wk, !d.central, s);
         } else if (fused_train_supported(d.Hc, d.Dc) && Sc < ((int64_t)1 << 31)) {
           FusedTrainArgs ta{};
           ta.X = Xc; ta.S = Sc; ta.Din = d.Dc; ta.px = fused_train_px(d.Dc);
@@ -637,7 +632,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
             if (rc != MARL_OK) return rc;
           } else {
             mlp_hidden_forward(Xc, Sc, d.Dc, d.Hc, eff + oc.W1, eff + oc.b1, eff + oc.W2, eff + oc.b2, w.h1c, w.h2c, d.bf16, s);
-            const int32_t rc = launch_loss_head<1, true>(w.h2c, Sc, d.Hc, eff + oc.W3, eff + oc.b3, fn, w.dlc, w.grad + gc.W3,
+            const int32_t rc = launch_loss_head<1, true>(w.h2c, Sc, d.Hc, eff + oc.W3, eff + oc.b3, fn, nullptr, w.grad + gc.W3,
                                                    w.partial_head, sck, s);
             if (rc != MARL_OK) return rc;
           }
