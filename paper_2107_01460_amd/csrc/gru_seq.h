@@ -104,8 +104,9 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
   // Streamed: a wavefront starts its walk along the contraction at a step of its own, since the wavefronts' fragments are a
   // multiple of 4 KB apart and in step would all ask the same memory channels of the L2 at the same time (128 steps of 2048
   // sequences, 256 units: 3.45 -> 3.0 ms).  It depends on the wavefront, that is on the units, and on nothing else: a sequence's
-  // sums are the same wherever in a batch of whatever size it is.
-  const int rot = RES ? 0 : __builtin_amdgcn_readfirstlane(wave);
+  // sums are the same wherever in a batch of whatever size it is.  (The remainder tells the compiler the range, and with it that
+  // the steps' offsets need no comparison each: an iteration of 16 384 environments 446 -> 432 ms.)
+  const int rot = RES ? 0 : __builtin_amdgcn_readfirstlane(wave % KS);
   auto step_of = [&](int ks) { return RES ? ks : ks + rot < KS ? ks + rot : ks + rot - KS; };
   auto load_w = [&](int i, bf16x8 (&w)[9]) {
 #pragma unroll
