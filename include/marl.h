@@ -244,7 +244,9 @@ int32_t marl_train_step(const marl_config* cfg, marl_env_state st, float* params
 
 /* Recurrent IPPO / MAPPO (Section 2 and Section 4 list them beside the feed-forward systems).  As marl_rollout, with
  * the hidden states carried from rec.h*0 through the T steps and left in rec.h*1.  workspace: rollout_workspace_bytes
- * of the recurrent configuration.  MARL_E_CONFIG unless cfg->recurrent = 1. */
+ * of the recurrent configuration; beside the weights and one step's states it holds 20 * critic_hidden bytes for each of
+ * up to 32768 critic samples (or one step's, if those are more): the critic runs over the stored observations in chunks.
+ * MARL_E_CONFIG unless cfg->recurrent = 1. */
 int32_t marl_rollout_recurrent(const marl_config* cfg, marl_env_state st, const float* params, marl_traj traj,
                                marl_rec_state rec, uint64_t step_offset, const int32_t* forced_actions,
                                const float* forced_uniforms, void* workspace, void* stream);
