@@ -20,6 +20,12 @@
  *     which keeps host state, is not thread-safe and waits for events; a product caller never needs it.
  *   - Return value: MARL_OK (0) or a negative marl_status.  Validation happens on the host
  *     before anything is launched; a call that returns an error has launched nothing.
+ *   - Arithmetic (precision 0): every product of the networks has fp32 accuracy (fp32 operands, fp32 sums); infinities
+ *     and NaNs propagate as in fp32.  Sums are added in an order that depends on the sizes, so outputs of different calls
+ *     agree to fp32 rounding, not bit for bit: in particular marl_policy_forward takes another kernel, and an observation's
+ *     logits and value have other last bits, from 2049 samples (n_rows * n_agents) on.  Where a last bit decides an action
+ *     there is one order for every size: the trajectory of environment n in marl_rollout, marl_rollout_recurrent and
+ *     marl_evaluate depends on the seed, n and the parameters, bit for bit, and not on n_envs.
  *   - Index conventions: N envs, A agents, F food items, D = 3*view*view observation floats,
  *     T rollout length.  Trajectory arrays are time-major and densely packed; a "row" is one
  *     (t, n) pair, row index t*N + n, and carries its A agent samples.

@@ -339,8 +339,13 @@ inline int32_t launch_fused_forward_inst(const FusedFwdArgs& a, const Finish& fi
 }
 
 // Few enough rows that a call is a chain of latencies: one launch on the unstaged parameters (a tile's wavefronts read
-// them once, 4 bytes at a time) against a staging kernel and a launch per network.  One row of 3 agents, 128/128 units:
-// forward and sampling 25 -> 19 us, the same bits.
+// them once, 4 bytes at a time) against a staging kernel and a launch per network on split operands.  Measured, us, one
+// launch / staged:
+//   75 inputs, 128 / 128 units:   3 000 samples 12 / 24   12 288 samples 23 / 27   49 152 samples 80 / 53
+//   147 inputs, 256 / 256 units:  3 000 samples 39 / 44    5 000 samples 50 / 46   20 480 samples 147 / 83
+//   147 and 882 inputs, 256 / 128 units:  3 600 samples 41 / 65   24 576 samples 159 / 90
+// The line lies below the smallest size at which any of them crosses (about 4 000).  The one launch runs on the fp32
+// instruction, so that an output's last bits differ on the two sides.
 constexpr int64_t kForwardSmall = 2048;
 
 template <int HA, int HB, int NOUT_A, int NOUT_B, class FinishA, class FinishB>

@@ -54,3 +54,22 @@ def test_rollout_does_not_depend_on_the_batch(M, k, sizes, kw):
         assert torch.equal(tr.last_value, ref.last_value[:n]), n
         for a, b in zip(state, ref_state):
             assert torch.equal(a, b[:n]), n
+
+
+@pytest.mark.parametrize("hidden", [64, 128, 192, 256])
+def test_evaluation_does_not_depend_on_the_batch(M, hidden):
+    base = W.scaled(W.CONFIGS[1], rollout_len=1, n_minibatches=1, episode_cap=6, actor_hidden=hidden)
+    params = dev(W.init_params(base, bias_scale=0.1))
+    ref = None
+    for n in (1100, 37):
+        cfg = W.scaled(base, n_envs=n)
+        print("case", hidden, n, flush=True)
+        st, out = M.EnvState(cfg), M.EvalStats(cfg)
+        M.env_reset(cfg, st)
+        M.evaluate(cfg, st, params, 2, out, M.alloc_workspace(M.query_sizes(cfg).eval_workspace_bytes))
+        got = [out.ret_sum, out.len_sum] + [getattr(st, f) for f in M.EnvState.FIELDS]
+        if ref is None:
+            ref = got
+            continue
+        for a, b in zip(got, ref):
+            assert torch.equal(a, b[..., :n])
