@@ -21,7 +21,7 @@
 // order; reduce_partials_kernel adds the copies.
 // Every product runs on the bf16 instruction with operands split into three parts (split_bf16.h): the weights are staged
 // split, the activations are split in registers on the way from LDS.  Against the fp32 instruction, 1 048 576 samples of
-// 75 inputs, 128 units, 6 outputs: 1522 -> 1104 us; 27 inputs, 64 units: 862 -> 761 us.  Bound: the vector instructions
+// 75 inputs, 128 units, 6 outputs: 1522 -> 1122 us; 2 097 152 of 27 inputs, 64 units: 862 -> 731 us.  Bound: the vector instructions
 // that split (a row tile is split once per column tile) and the chain of phases of one workgroup per CU.
 #pragma once
 #include "gemm.h"

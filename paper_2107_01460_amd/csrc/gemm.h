@@ -294,8 +294,9 @@ constexpr int kGemmBK = 32;  // k per stage: two steps of the matrix instruction
 // Bound: per k tile and wavefront 48 matrix instructions at BN = 128 (1536 cycles) against about 700 cycles of vector
 // instructions that split 32 staged values per thread, which the other workgroup's matrix instructions cover; at
 // contraction lengths of 128 .. 256 the activations' HBM traffic is the other bound.  Measured against the kernel on the
-// fp32 instruction that this one replaced: dW of 256 x 256 over 262 144 samples 295 -> 210 us; a training iteration whose
-// networks run layer by layer (147-256-6 and 147-192-1, 250 000 samples) 27.1 -> 19.9 ms.
+// fp32 instruction that this one replaced: dW of 256 x 256 over 262 144 samples 295 -> 196 us; a training iteration whose
+// networks run layer by layer (147-256-6 and 147-192-1, 250 000 samples) 27.1 -> 19.9 ms.  The check for NaNs at the end of a
+// tile (values out of split_pair's range) costs 1 %.
 template <int MODE, int EPI, int BM, int BN, bool AVEC>
 __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   constexpr int BK = kGemmBK;

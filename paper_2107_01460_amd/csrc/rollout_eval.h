@@ -3,7 +3,7 @@
 //
 // Both layers run on split bf16 operands, transposed (gemm_phase_t): the windows hold small integers and halves, exact in
 // bf16, so layer 1 takes half the products, h1 is split once, and the output layer starts from the registers that layer 2
-// ends in.  A step is a chain of latencies: 200 steps of 384 samples at 128 units 1.23 ms, with fp32 tiles 1.48 ms.
+// ends in.  A step is a chain of latencies: 200 steps of 384 samples at 128 units 1.2 ms, with fp32 tiles 1.48 ms.
 #pragma once
 #include "rollout_common.h"
 

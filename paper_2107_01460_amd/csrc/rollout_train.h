@@ -9,8 +9,8 @@
 // The critic's values do not steer the rollout and are computed in one pass over the stored observations afterwards.
 //
 // The products run on the fp32 instruction for every number of environments.  Short rollouts of few environments, chains of
-// latencies, are a fifth faster on split bf16 operands as in rollout_eval.h (128 steps of 3072 samples at 128 units 0.84
-// against 1.0 ms), but a sampled action is a discrete choice: with one arithmetic below some number of environments and
+// latencies, are a fifth faster on split bf16 operands as in rollout_eval.h (128 steps of 3072 samples at 128 units 0.83
+// against 1.02 ms), but a sampled action is a discrete choice: with one arithmetic below some number of environments and
 // another one above, an environment's run depends on how many others share the launch.
 #pragma once
 #include "rollout_common.h"
