@@ -106,11 +106,11 @@ struct GemmArgs {
 // does the same with one slab per k split when the caller passes split_out; without it, it adds with atomics.
 
 // out[i] += sum_b partial[b * count + i], the copies added in a fixed order, so that the result does not depend on the
-// run.  A workgroup takes 32 consecutive elements; its 8 thread groups sum the copies b = g, g + 8, g + 16, ... of an
+// run; elements from `head` on go to tail[i - head] instead.  A workgroup takes 32 consecutive elements; its 8 thread groups sum the copies b = g, g + 8, g + 16, ... of an
 // element (four interleaved running sums each, so that four loads are in flight), and one thread per element adds the
 // eight group sums through LDS, again in a fixed order.
 static __global__ void __launch_bounds__(256) reduce_partials_kernel(const float* __restrict__ partial, int nblocks, int64_t count,
-                                                                     float* __restrict__ out) {
+                                                                     float* __restrict__ out, int64_t head, float* __restrict__ tail) {
   __shared__ float part[8][32];
   const int e = threadIdx.x & 31, g = threadIdx.x >> 5;
   const int64_t i = (int64_t)blockIdx.x * 32 + e;
@@ -129,11 +129,13 @@ static __global__ void __launch_bounds__(256) reduce_partials_kernel(const float
     float v = part[0][e];
 #pragma unroll
     for (int q = 1; q < 8; ++q) v += part[q][e];
-    out[i] += v;
+    float* const dst = i < head ? out + i : tail + (i - head);
+    *dst += v;
   }
 }
-inline void launch_reduce_partials(const float* partial, int nblocks, int64_t count, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((count + 31) / 32)), dim3(256), 0, s, partial, nblocks, count, out);
+inline void launch_reduce_partials(const float* partial, int nblocks, int64_t count, float* out, hipStream_t s, int64_t head = INT64_MAX,
+                                   float* tail = nullptr) {
+  hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((count + 31) / 32)), dim3(256), 0, s, partial, nblocks, count, out, head, tail);
 }
 
 // tanh(x) = 1 - 2 / (e^{2x} + 1) with the hardware exp2 and reciprocal: absolute error ~1e-7 (the values feed

@@ -3,11 +3,13 @@
 // The two hidden layers of each network are MFMA GEMMs (gemm.h); the narrow output layer
 // (6 logits or 1 value) runs on the vector ALUs of the "head" kernel, which also draws the
 // action by Gumbel-max from Philox uniforms and evaluates its log-probability.
-#include "bf16_path.h"
+#include "bf16_net.h"
 #include "fused_forward.h"
 #include "gemm.h"
 #include "heads.h"
 #include "rollout_fused.h"
+
+#include <tuple>
 
 namespace marl {
 
@@ -90,8 +92,7 @@ FusedFwdArgs fused_args(const RowSrc& X, int64_t S, int Din, const float* eff, c
 }
 
 struct RolloutWsView {
-  float *eff_params, *h1a, *h2a, *h1c, *h2c;   // fp32 path
-  bf16_t *xba, *bh1a, *bh2a, *xbc, *bh1c, *bh2c;  // bf16 configuration
+  float *eff_params, *h1a, *h2a, *h1c, *h2c;  // activations: layer-by-layer fp32 networks
 };
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
@@ -124,12 +125,13 @@ RolloutWsView carve_rollout_ws(const marl_config& c, int64_t n_rows, void* ws, i
       v.h2c = (float*)take(Sc * d.Hc * 4);
     }
   } else {
-    v.xba = (bf16_t*)take(S * round_up64(d.D) * 2);
-    v.bh1a = (bf16_t*)take(S * d.Ha * 2);
-    v.bh2a = (bf16_t*)take(S * d.Ha * 2);
-    v.xbc = (bf16_t*)take(Sc * round_up64(d.Dc) * 2);
-    v.bh1c = (bf16_t*)take(Sc * d.Hc * 2);
-    v.bh2c = (bf16_t*)take(Sc * d.Hc * 2);
+    // The bf16 networks keep their activations on chip.  The size stays what a call that stored them needed (packed input, both
+    // hidden layers), since marl_rollout_static decides by it what it takes.
+    for (const auto& [rows, din, H] : {std::tuple<int64_t, int, int>{S, d.D, d.Ha}, std::tuple<int64_t, int, int>{Sc, d.Dc, d.Hc}}) {
+      take(rows * round_up64(din) * 2);
+      take(rows * H * 2);
+      take(rows * H * 2);
+    }
   }
   if (total) *total = off;
   return v;
@@ -160,8 +162,8 @@ int64_t effective_param_floats(const marl_config& c, bool update) {
 Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, int net) {
   const Dims d = dims_of(c);  // (the map is the same for an update and for a forward pass: no network is fused)
   bf16_t* base = reinterpret_cast<bf16_t*>(const_cast<float*>(eff) + ((param_map(d, false).total + 63) / 64) * 64);
-  if (net == 0) return bf16_net_weights(base, d.D, d.Ha);
-  return bf16_net_weights(base + ((bf16_net_weight_elems(d.D, d.Ha) + 63) / 64) * 64, d.Dc, d.Hc);
+  if (net == 0) return Bf16NetWeights{base, (int)round_up64(d.D)};
+  return Bf16NetWeights{base + ((bf16_net_weight_elems(d.D, d.Ha) + 63) / 64) * 64, (int)round_up64(d.Dc)};
 }
 
 const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use) {
@@ -170,8 +172,9 @@ const float* effective_params(const marl_config& c, const float* params, float* 
                      param_map(d, use == USE_UPDATE), (int)d.bf16, (int)(use == USE_ROLLOUT && use_fused_rollout(c)), (int)(use == USE_UPDATE));
   if (d.bf16) {
     const NetOffsets oa = net_offsets(0, d.D, d.Ha, kActions), oc = net_offsets(d.Pa, d.Dc, d.Hc, 1);
-    stage_weights_bf16(params + oa.W1, params + oa.W2, d.D, d.Ha, effective_bf16_weights(c, scratch, 0), s);
-    stage_weights_bf16(params + oc.W1, params + oc.W2, d.Dc, d.Hc, effective_bf16_weights(c, scratch, 1), s);
+    const Bf16NetWeights wa = effective_bf16_weights(c, scratch, 0), wc = effective_bf16_weights(c, scratch, 1);
+    launch_bf16_stage(Bf16StageNet{params + oa.W1, params + oa.W2, wa.w, d.D, wa.Kp, d.Ha},
+                      Bf16StageNet{params + oc.W1, params + oc.W2, wc.w, d.Dc, wc.Kp, d.Hc}, s);
   }
   return scratch;
 }
@@ -183,29 +186,30 @@ int64_t rollout_workspace_bytes(const marl_config& c, int64_t n_rows) {
 }
 
 // One forward pass over n_rows observation rows.  Any of logits / value / sampling outputs may be absent.
-// value_tail (nullable): the values of rows value_split .. n_rows go there instead (fused critic kernel only).
+// value_tail (nullable): the values of rows value_split .. n_rows go there instead (kernels that keep a row's activations on chip only).
 static int32_t forward_rows(const marl_config& c, const float* eff, const float* obs, int64_t n_rows,
                             const RolloutWsView& w, bool want_actor, float* logits_out, const SampleArgs* sample,
                             float* value_out, hipStream_t s, int64_t value_split = -1, float* value_tail = nullptr) {
   const Dims d = dims_of(c);
   const int64_t S = n_rows * d.A;
   if (d.bf16) {
+    auto args = [&](int net, int64_t rows, int Din) {
+      const NetOffsets o = padded_offsets(param_map(d, false), net);
+      Bf16NetArgs a{};
+      a.X = RowSrc{obs, Din, nullptr, 1, rows}; a.S = rows; a.Din = Din; a.w = effective_bf16_weights(c, eff, net);
+      a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
+      return a;
+    };
     if (want_actor) {
-      const NetOffsets o = padded_offsets(param_map(d, false), 0);
-      const Bf16NetWeights bw = effective_bf16_weights(c, eff, 0);
-      pack_obs_bf16(RowSrc{obs, d.D, nullptr, 1, S}, S, d.D, bw.Dp, S, w.xba, nullptr, s);
-      mlp_hidden_forward_bf16(w.xba, S, S, d.Ha, bw, eff + o.b1, eff + o.b2, w.bh1a, nullptr, w.bh2a, s);
-      launch_actor_head_rollout(w.bh2a, S, d.Ha, eff + o.W3, eff + o.b3, logits_out, sample, s);
+      ActorRolloutFinish fin{logits_out, sample ? *sample : SampleArgs{}, sample ? 1 : 0};
+      const int32_t rc = launch_bf16_forward<kActions>(d.Ha, args(0, S, d.D), fin, s);
+      if (rc != MARL_OK) return rc;
     }
     if (value_out) {
-      const NetOffsets o = padded_offsets(param_map(d, false), 1);
-      const Bf16NetWeights bw = effective_bf16_weights(c, eff, 1);
       const int64_t Sc = d.central ? n_rows : S;
-      // IPPO: the critic reads the rows packed for the actor (same rows, same width)
-      const bool shared = want_actor && !d.central;
-      if (!shared) pack_obs_bf16(RowSrc{obs, d.Dc, nullptr, 1, Sc}, Sc, d.Dc, bw.Dp, Sc, w.xbc, nullptr, s);
-      mlp_hidden_forward_bf16(shared ? w.xba : w.xbc, Sc, Sc, d.Hc, bw, eff + o.b1, eff + o.b2, w.bh1c, nullptr, w.bh2c, s);
-      launch_critic_head_rollout(w.bh2c, Sc, d.Hc, eff + o.W3, eff + o.b3, value_out, d.central ? d.A : 1, s);
+      CriticRolloutFinish fin{value_out, d.central ? d.A : 1, value_tail ? value_split : Sc, value_tail};
+      const int32_t rc = launch_bf16_forward<1>(d.Hc, args(1, Sc, d.Dc), fin, s);
+      if (rc != MARL_OK) return rc;
     }
     return launch_status();
   }
@@ -300,9 +304,9 @@ int32_t launch_rollout(const marl_config& c, marl_env_state st, const float* par
   const int64_t NA = d.NA, slab = NA * d.D;
   int32_t rc;
   // The values do not steer the rollout (the parameters are constant during it): where the critic's forward pass
-  // needs no per-row workspace (the fused fp32 kernel), the values of all T steps and of the post-rollout observation
+  // needs no per-row workspace (the fused fp32 kernel, the bf16 networks), the values of all T steps and of the post-rollout observation
   // are computed in one pass over the stored observations afterwards instead of one small launch per step.
-  const bool batch_values = !d.bf16 && fused_forward_supported(d.Hc, d.Dc);
+  const bool batch_values = d.bf16 || fused_forward_supported(d.Hc, d.Dc);
   if (use_fused_rollout(c)) {
     // all T steps in one launch: a workgroup keeps its environments on chip and streams the trajectory out
     RolloutArgs a = rollout_fused_args(c, st, eff);

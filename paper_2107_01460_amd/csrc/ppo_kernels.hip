@@ -4,7 +4,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "bf16_path.h"
+#include "bf16_net.h"
 #include "fused_forward.h"
 #include "fused_train.h"
 #include "gemm.h"
@@ -23,243 +23,6 @@ Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, in
 
 namespace {
 
-// Output layer + loss + W3 / b3 gradient + dz2 for bf16 activations of up to HMAX hidden units.  The whole 64-sample
-// tile of h2 sits in LDS as bf16 (one pass over HBM, 16-byte loads) and serves the output layer, the W3 gradient
-// and dz2 = (dL/dout W3^T) * (1 - h2^2), which overwrites h2 in place (row-major, the A operand of dz1) and goes to
-// the sample-blocked transposed copy dz2T (zeros for the samples S .. 64 * tiles; the B operand of the W2 gradient).
-// Persistent over tiles so that the gradients and statistics leave a workgroup once.
-template <int NOUT, class LossFn, int HMAX, int NT>
-__global__ void __launch_bounds__(NT) loss_head_bf16_kernel(bf16_t* __restrict__ H2, int64_t S, int H,
-                                                             const float* __restrict__ W3, const float* __restrict__ b3,
-                                                             LossFn fn, bf16_t* __restrict__ dz2T, float* __restrict__ gW3,
-                                                             float* __restrict__ gb3, Scalars* sc, float* __restrict__ partial) {
-  // partial (nullable): this workgroup's W3 / b3 gradient goes to partial + blockIdx.x * (H * NOUT + NOUT) with plain
-  // stores and is added to gW3 (with gb3 directly behind it) by the reduction kernel afterwards
-  constexpr int PITCH = HMAX + 8;  // elements; an odd number of 16-byte units, so row-per-lane 16-byte reads spread over the banks
-  __shared__ __attribute__((aligned(16))) bf16_t T[kHeadTile * PITCH];
-  __shared__ __attribute__((aligned(16))) float W3s[HMAX * NOUT];
-  constexpr int NG = NT / 64;  // wavefronts: eight (two per SIMD cover each other's LDS latencies) where there is enough work per tile, else four
-  __shared__ float red[NG * NOUT * kHeadTile];
-  __shared__ __attribute__((aligned(16))) float dls[kHeadTile * 8];
-  const int tid = threadIdx.x, lane = tid & 63, grp = tid >> 6;
-  for (int e = tid; e < H * NOUT; e += NT) W3s[e] = W3[e];
-  const auto prep = fn.prepare();
-  // dz2: thread -> the eight hidden units 8 (tid % CPR) .. + 7 of the rows tid / CPR + (NT / CPR) q; their W3 rows
-  float w8[8][NOUT];
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-#pragma unroll
-    for (int k = 0; k < NOUT; ++k) {
-      const int i = 8 * (tid % (HMAX / 8)) + e;
-      w8[e][k] = i < H ? W3[(int64_t)i * NOUT + k] : 0.f;
-    }
-  constexpr int UMAX = 2;  // W3 gradient: thread -> the pair of hidden units 2 (tid % 256), + 1 and one share of the tile's samples
-  constexpr int SHARES = NT / 256;
-  static_assert(HMAX == 512 && (NT == 256 || NT == 512), "256 pairs of hidden units x 1 or 2 shares of the samples");
-  float gw[UMAX][NOUT], gb[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) {
-    gb[k] = 0.f;
-#pragma unroll
-    for (int u = 0; u < UMAX; ++u) gw[u][k] = 0.f;
-  }
-  const int vec_per_row = H / 8, per_grp = H / NG;
-  const int64_t ntiles = (S + kHeadTile - 1) / kHeadTile;
-  // A tile travels global -> registers -> LDS: all of a thread's 16-byte pieces are requested at once, and the next
-  // tile's are requested before this tile's arithmetic, so that no load is waited for on its own.
-  constexpr int NV = kHeadTile * (HMAX / 8) / NT;  // pieces per thread at the full width
-  constexpr int CPR = HMAX / 8;                     // 16-byte pieces of a row at the full width
-  static_assert(NT % CPR == 0 && NV * (NT / CPR) == kHeadTile, "a thread's pieces are one column of the tile");
-  uint4 tv[NV];
-  auto fetch_tile = [&](int64_t tile) {
-    const int64_t s0 = tile * kHeadTile;
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {  // thread -> rows tid / CPR + (NT / CPR) q, 16-byte piece tid % CPR of the row
-      const int r = tid / CPR + (NT / CPR) * q, c8 = tid % CPR;
-      tv[q] = make_uint4(0u, 0u, 0u, 0u);
-      if (c8 < vec_per_row && s0 + r < S) tv[q] = *reinterpret_cast<const uint4*>(&H2[(s0 + r) * H + 8 * c8]);
-    }
-  };
-  // The loss inputs of a sample sit behind a dependent pair of loads (row order entry, then the row): the first
-  // wavefront requests the entries of the next tile at the top of a tile and the rows after the output layer, so
-  // that neither is waited for in front of the loss.
-  typename LossFn::In lin_next{};
-  int32_t lentry = 0;
-  if ((int64_t)blockIdx.x < ntiles) {
-    fetch_tile(blockIdx.x);
-    const int64_t s = (int64_t)blockIdx.x * kHeadTile + tid;
-    if (tid < kHeadTile && s < S) lin_next = fn.load(s);
-  }
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t s0 = tile * kHeadTile;
-    const int64_t s_next = (tile + gridDim.x) * kHeadTile + tid;  // this thread's sample of the next tile
-    const bool next_live = tid < kHeadTile && tile + gridDim.x < ntiles && s_next < S;
-    const typename LossFn::In lin = lin_next;
-    if (next_live) lentry = fn.row_entry(s_next);
-    __syncthreads();  // the previous tile has been consumed (and W3s is in place)
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      const int r = tid / CPR + (NT / CPR) * q, c8 = tid % CPR;
-      if (c8 < vec_per_row) *reinterpret_cast<uint4*>(&T[r * PITCH + 8 * c8]) = tv[q];
-    }
-    __syncthreads();
-    if (tile + gridDim.x < ntiles) fetch_tile(tile + gridDim.x);
-    {  // output layer: thread -> sample `lane`, share `grp` (one of NG) of the hidden units
-      float part[NOUT];
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) part[k] = 0.f;
-#pragma unroll 4
-      for (int i = grp * per_grp; i < (grp + 1) * per_grp; i += 8) {
-        const uint4 hv = *reinterpret_cast<const uint4*>(&T[lane * PITCH + i]);
-        const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
-        float hh[8];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          hh[2 * q] = __uint_as_float(hw[q] << 16);
-          hh[2 * q + 1] = __uint_as_float(hw[q] & 0xffff0000u);
-        }
-        float wv[8 * NOUT];
-#pragma unroll
-        for (int q = 0; q < 2 * NOUT; ++q) {
-          const float4 t = *reinterpret_cast<const float4*>(&W3s[i * NOUT + 4 * q]);
-          wv[4 * q] = t.x; wv[4 * q + 1] = t.y; wv[4 * q + 2] = t.z; wv[4 * q + 3] = t.w;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-#pragma unroll
-          for (int k = 0; k < NOUT; ++k) part[k] = fmaf(hh[j], wv[j * NOUT + k], part[k]);
-      }
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) red[(grp * NOUT + k) * kHeadTile + lane] = part[k];
-    }
-    if (next_live) lin_next = fn.load_with(s_next, lentry);
-    __syncthreads();
-    if (tid < kHeadTile) {
-      float out[NOUT], dl[NOUT];
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) {
-        float v = 0.f;
-#pragma unroll
-        for (int gq = 0; gq < NG; ++gq) v += red[(gq * NOUT + k) * kHeadTile + tid];
-        out[k] = b3[k] + v;
-        dl[k] = 0.f;
-      }
-      const int64_t s = s0 + tid;
-      if (s < S) {
-        fn.compute(lin, prep, out, dl, st);
-#pragma unroll
-        for (int k = 0; k < NOUT; ++k) gb[k] += dl[k];
-      }
-#pragma unroll
-      for (int k = 0; k < 8; ++k) dls[tid * 8 + k] = k < NOUT ? dl[k < NOUT ? k : 0] : 0.f;
-    }
-    __syncthreads();
-    // gW3[i][k] += sum_s h2[s][i] dl[s][k]: thread -> hidden units 2 (tid % 256), + 1 (one 4-byte LDS read per sample),
-    // samples (64 / SHARES) (tid / 256) .. 
-    const int pr = tid & 255, s_lo = (tid >> 8) * (kHeadTile / SHARES);
-#pragma unroll 8
-    for (int s = s_lo; s < s_lo + kHeadTile / SHARES; ++s) {
-      const float4 d0 = *reinterpret_cast<const float4*>(&dls[s * 8]);
-      float dv[8] = {d0.x, d0.y, d0.z, d0.w, 0.f, 0.f, 0.f, 0.f};
-      if (NOUT > 4) {
-        const float4 d1 = *reinterpret_cast<const float4*>(&dls[s * 8 + 4]);
-        dv[4] = d1.x; dv[5] = d1.y; dv[6] = d1.z; dv[7] = d1.w;
-      }
-      const uint32_t hw = 2 * pr < H ? *reinterpret_cast<const uint32_t*>(&T[s * PITCH + 2 * pr]) : 0u;
-      const float hp[2] = {__uint_as_float(hw << 16), __uint_as_float(hw & 0xffff0000u)};
-#pragma unroll
-      for (int u = 0; u < UMAX; ++u)
-#pragma unroll
-        for (int k = 0; k < NOUT; ++k) gw[u][k] = fmaf(hp[u], dv[k], gw[u][k]);
-    }
-    __syncthreads();  // every thread has read the h2 it needs; the tile is overwritten with dz2
-#pragma unroll 4
-    for (int q = 0; q < NV; ++q) {
-      const int r = tid / CPR + (NT / CPR) * q, c8 = tid % CPR;
-      if (c8 < vec_per_row) {
-        const uint4 hv = *reinterpret_cast<const uint4*>(&T[r * PITCH + 8 * c8]);
-        const float4 d0 = *reinterpret_cast<const float4*>(&dls[r * 8]);
-        float dv[8] = {d0.x, d0.y, d0.z, d0.w, 0.f, 0.f, 0.f, 0.f};
-        if (NOUT > 4) {
-          const float4 d1 = *reinterpret_cast<const float4*>(&dls[r * 8 + 4]);
-          dv[4] = d1.x; dv[5] = d1.y; dv[6] = d1.z; dv[7] = d1.w;
-        }
-        const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
-        uint32_t ow[4];
-#pragma unroll
-        for (int p2 = 0; p2 < 4; ++p2) {
-          float o2[2];
-#pragma unroll
-          for (int z = 0; z < 2; ++z) {
-            const float h = __uint_as_float(z == 0 ? hw[p2] << 16 : hw[p2] & 0xffff0000u);
-            float g = 0.f;
-#pragma unroll
-            for (int k = 0; k < NOUT; ++k) g = fmaf(dv[k], w8[2 * p2 + z][k], g);
-            o2[z] = g * (1.0f - h * h);  // rows past the end carry dl = 0
-          }
-          ow[p2] = pack2_bf16(o2[0], o2[1]);
-        }
-        const uint4 ov = make_uint4(ow[0], ow[1], ow[2], ow[3]);
-        if (s0 + r < S) *reinterpret_cast<uint4*>(&H2[(s0 + r) * H + 8 * c8]) = ov;
-        *reinterpret_cast<uint4*>(&T[r * PITCH + 8 * c8]) = ov;
-      }
-    }
-    __syncthreads();
-    // transposed copy: thread -> hidden unit tid / 8 + (NT / 8) q, samples 8 (tid % 8) .. + 7 (a wavefront writes 1 KB in one piece)
-    for (int q = 0; (NT / 8) * q < H; ++q) {
-      const int dd = (tid >> 3) + (NT / 8) * q, ss = 8 * (tid & 7);
-      uint32_t ow[4];
-#pragma unroll
-      for (int p2 = 0; p2 < 4; ++p2)
-        ow[p2] = (uint32_t)T[(ss + 2 * p2) * PITCH + dd] | ((uint32_t)T[(ss + 2 * p2 + 1) * PITCH + dd] << 16);
-      *reinterpret_cast<uint4*>(&dz2T[((s0 >> 6) * H + dd) * 64 + ss]) = make_uint4(ow[0], ow[1], ow[2], ow[3]);
-    }
-  }
-  // two shares of the samples meet in LDS (the tile buffer is free after the last barrier of the loop)
-  float* const comb = reinterpret_cast<float*>(T);
-  if (SHARES == 2) {
-    __syncthreads();
-    if (tid >= 256) {
-#pragma unroll
-      for (int u = 0; u < UMAX; ++u)
-#pragma unroll
-        for (int k = 0; k < NOUT; ++k) comb[(u * NOUT + k) * 256 + (tid & 255)] = gw[u][k];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < UMAX; ++u) {
-    const int i = 2 * tid + u;
-    if (tid < 256 && i < H) {
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k)
-        if (SHARES == 2) gw[u][k] += comb[(u * NOUT + k) * 256 + tid];
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) {
-        if (partial != nullptr) partial[(int64_t)blockIdx.x * (H * NOUT + NOUT) + (int64_t)i * NOUT + k] = gw[u][k];
-        else atomicAdd(&gW3[(int64_t)i * NOUT + k], gw[u][k]);
-      }
-    }
-  }
-  if (tid < kHeadTile) {  // one wavefront
-#pragma unroll
-    for (int k = 0; k < NOUT; ++k) {
-      float v = gb[k];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if (tid == 0) {
-        if (partial != nullptr) partial[(int64_t)blockIdx.x * (H * NOUT + NOUT) + (int64_t)H * NOUT + k] = v;
-        else atomicAdd(&gb3[k], v);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      float v = st[k];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if (tid == 0 && v != 0.f) atomicAdd(&sc->acc[k], v);
-    }
-  }
-}
-
 struct UpdateWsView {
   float *eff_params, *grad;
   Scalars* sc;        // two sets: optimiser step k accumulates into set k % 2 while its Adam kernel zeroes the other
@@ -272,8 +35,8 @@ struct UpdateWsView {
   float* partial_head;  // per-workgroup W3 / b3 gradients of the output-layer kernels
   float* split_ws;      // fp32 layer-by-layer networks: the k splits of a weight-gradient product, added in a fixed order
   int64_t split_floats;
-  // bf16 configuration: one set of activation buffers, used by the actor and then by the critic
-  bf16_t *xb, *xbT, *bh1, *bh1T, *bh2, *dz2T, *dz1T;
+  // bf16 configuration: one set of buffers, used by the actor and then by the critic
+  bf16_t *bh1, *bdz2, *bdz1;
 };
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
@@ -326,16 +89,13 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
     if (d.Hc == kWregN || d.Ha == kWregN) head = std::max(head, (int64_t)kFusedFwdTrainGrid * (kWregN * kActions + kActions));
     v.partial_head = (float*)take(head * 4);
   } else {
-    const int64_t Sp = round_up64(std::max(Sa, Sc));
-    const int64_t Dp = round_up64(std::max(d.D, d.Dc)), H = std::max(d.Ha, d.Hc);
-    v.xb = (bf16_t*)take(Sp * Dp * 2);
-    v.xbT = (bf16_t*)take(Sp * Dp * 2);
-    v.bh1 = (bf16_t*)take(Sp * H * 2);
-    v.bh1T = (bf16_t*)take(Sp * H * 2);
-    v.bh2 = (bf16_t*)take(Sp * H * 2);
-    v.dz2T = (bf16_t*)take(Sp * H * 2);
-    v.dz1T = (bf16_t*)take(Sp * H * 2);
-    v.partial_head = (float*)take((int64_t)512 * (H * kActions + kActions) * 4);
+    const int64_t SH = std::max(Sa * d.Ha, Sc * d.Hc);
+    v.bh1 = (bf16_t*)take(SH * 2);
+    v.bdz2 = (bf16_t*)take(SH * 2);
+    v.bdz1 = (bf16_t*)take(SH * 2);
+    v.partial_head = (float*)take(std::max(bf16_net_grid(d.Ha) * bf16_net_partial_floats(d.Ha, kActions), bf16_net_grid(d.Hc) * bf16_net_partial_floats(d.Hc, 1)) * 4);
+    v.split_ws = (float*)take(std::max(std::max(bf16_wgrad_floats(false, d.Ha, d.Ha, Sa), bf16_wgrad_floats(true, d.D, d.Ha, Sa)),
+                                       std::max(bf16_wgrad_floats(false, d.Hc, d.Hc, Sc), bf16_wgrad_floats(true, d.Dc, d.Hc, Sc))) * 4);
   }
   if (total) *total = off;
   return v;
@@ -436,45 +196,26 @@ void mlp_backward(const RowSrc& X, int64_t S, int Din, int H, const float* W2, c
   }
 }
 
-// Forward, loss and backward of one network in the bf16 configuration: every product runs on the bf16 matrix
-// cores; the output layer, the loss and dz2 stay on the ALUs in fp32.
+// Forward, loss and backward of one network in the bf16 configuration.
 template <int NOUT, class LossFn>
-void train_net_bf16(const RowSrc& X, int64_t S, int Din, int H, const Bf16NetWeights& bw, const float* eff,
-                    const NetOffsets& o, float* grad, const NetOffsets& go, const LossFn& fn, const UpdateWsView& w, bool packed, hipStream_t s) {
-  const int64_t Sp = round_up64(S);
-  if (!packed) pack_obs_bf16(X, S, Din, bw.Dp, Sp, w.xb, w.xbT, s);  // packed: the previous network left these very rows there
-  mlp_hidden_forward_bf16(w.xb, S, Sp, H, bw, eff + o.b1, eff + o.b2, w.bh1, w.bh1T, w.bh2, s);
-  const unsigned nb = (unsigned)std::min<int64_t>(512, (S + kHeadTile - 1) / kHeadTile);
-  float* const hp = (go.b3 == go.W3 + (int64_t)H * NOUT) ? w.partial_head : nullptr;  // b3's gradient directly follows W3's
-  // output layer, loss and dz2 in one pass over h2 (the tiles cover the samples up to Sp: dz2T is zero-padded)
-  constexpr int HEAD_NT = NOUT > 1 ? 512 : 256;  // the one-output head has too little work per tile for eight wavefronts
-  hipLaunchKernelGGL((loss_head_bf16_kernel<NOUT, LossFn, 512, HEAD_NT>), dim3(nb), dim3(HEAD_NT), 0, s, w.bh2, S, H, eff + o.W3,
-                     eff + o.b3, fn, w.dz2T, grad + go.W3, grad + go.b3, w.sc, hp);
-  if (hp != nullptr) launch_reduce_partials(hp, (int)nb, (int64_t)H * NOUT + NOUT, grad + go.W3, s);
-  auto k_split = [&](int64_t tiles_mn) {  // ~4 workgroups per CU, k ranges in multiples of the k tile
-    const int64_t want = std::max<int64_t>(1, 1024 / std::max<int64_t>(1, tiles_mn));
-    return std::max<int64_t>(512, round_up64((Sp + want - 1) / want));
-  };
-  {  // gW2 += h1^T dz2, gb2 += column sums of dz2
-    GemmBf16Args g{};
-    g.A = w.bh1T; g.a_rows = H; g.B = w.dz2T; g.b_rows = H;
-    g.M = H; g.N = H; g.K = Sp; g.Cf = grad + go.W2; g.ldcf = H; g.rowsum_b = grad + go.b2;
-    g.k_per_split = k_split(((H + 127) / 128) * ((H + 127) / 128));
-    launch_gemm_bf16<BEPI_ATOMIC>(g, s);
+int32_t train_net_bf16(const RowSrc& X, int64_t S, int Din, int H, const Bf16NetWeights& bw, const float* eff,
+                       const NetOffsets& o, float* grad, const NetOffsets& go, const LossFn& fn, const UpdateWsView& w, hipStream_t s) {
+  Bf16NetArgs a{};
+  a.X = X; a.S = S; a.Din = Din; a.w = bw; a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
+  a.h1 = w.bh1; a.dz2 = w.bdz2; a.dz1 = w.bdz1; a.partial = w.partial_head;
+  unsigned grid = 0;
+  int32_t rc;
+  {
+    TimedLaunch timed(KC_FUSED_TRAIN, 2.0 * (double)S * ((double)Din * H + 2.0 * (double)H * H), s);
+    rc = launch_bf16_net_rows<64, NOUT, true>(H, a, fn, &grid, s);
   }
-  {  // dz1 = (dz2 W2^T) * (1 - h1^2), transposed copy only
-    GemmBf16Args g{};
-    g.A = w.bh2; g.lda = H; g.a_rows = S; g.B = bw.W2; g.ldb = H; g.b_rows = H;
-    g.M = S; g.N = H; g.K = H; g.CT = w.dz1T; g.ct_cols = Sp; g.aux = w.bh1; g.ldaux = H;
-    launch_gemm_bf16<BEPI_DTANH_T>(g, s);
-  }
-  {  // gW1 += X^T dz1, gb1 += column sums of dz1
-    GemmBf16Args g{};
-    g.A = w.xbT; g.a_rows = bw.Dp; g.B = w.dz1T; g.b_rows = H;
-    g.M = Din; g.N = H; g.K = Sp; g.Cf = grad + go.W1; g.ldcf = H; g.rowsum_b = grad + go.b1;
-    g.k_per_split = k_split(((Din + 127) / 128) * ((H + 127) / 128));
-    launch_gemm_bf16<BEPI_ATOMIC>(g, s);
-  }
+  if (rc != MARL_OK) return rc;
+  launch_reduce_partials(w.partial_head, (int)grid, bf16_net_partial_floats(H, NOUT), grad + go.W3, s, (int64_t)H * NOUT + NOUT, w.sc->acc);
+  Bf16WgradArgs g{};
+  g.A = w.bh1; g.lda = H; g.B = w.bdz2; g.S = S; g.M = H; g.N = H; g.out = w.split_ws;
+  if ((rc = launch_bf16_wgrad(false, g, grad + go.W2, s)) != MARL_OK) return rc;
+  g.X = X; g.B = w.bdz1; g.M = Din;
+  return launch_bf16_wgrad(true, g, grad + go.W1, s);
 }
 
 }  // namespace
@@ -564,7 +305,8 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
       if (!pair) {
         ActorLoss fn{lc, tr.action, tr.logp, tr.adv};
         if (d.bf16) {
-          train_net_bf16<kActions>(Xa, Sa, d.D, d.Ha, effective_bf16_weights(c, eff, 0), eff, oa, w.grad, ga, fn, wk, false, s);
+          const int32_t rc = train_net_bf16<kActions>(Xa, Sa, d.D, d.Ha, effective_bf16_weights(c, eff, 0), eff, oa, w.grad, ga, fn, wk, s);
+          if (rc != MARL_OK) return rc;
         } else if (fused_train_supported(d.Ha, d.D) && Sa < ((int64_t)1 << 31)) {
           FusedTrainArgs ta{};
           ta.X = Xa; ta.S = Sa; ta.Din = d.D; ta.px = fused_train_px(d.D);
@@ -601,8 +343,8 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
       if (!pair) {
         CriticLoss fn{lc, tr.ret, tr.value, d.central ? d.A : 1};
         if (d.bf16) {
-          // IPPO: the critic reads the rows the actor has just packed (same rows, same width)
-          train_net_bf16<1>(Xc, Sc, d.Dc, d.Hc, effective_bf16_weights(c, eff, 1), eff, oc, w.grad, gc, fn, wk, !d.central, s);
+          const int32_t rc = train_net_bf16<1>(Xc, Sc, d.Dc, d.Hc, effective_bf16_weights(c, eff, 1), eff, oc, w.grad, gc, fn, wk, s);
+          if (rc != MARL_OK) return rc;
         } else if (fused_train_supported(d.Hc, d.Dc) && Sc < ((int64_t)1 << 31)) {
           FusedTrainArgs ta{};
           ta.X = Xc; ta.S = Sc; ta.Din = d.Dc; ta.px = fused_train_px(d.Dc);

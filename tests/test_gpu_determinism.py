@@ -5,8 +5,8 @@ gradient of the networks that take the whole-network training kernel is reduced 
 workgroup added in turn through LDS, the per-workgroup copies added in a fixed grouping, the gradient norm as per-block
 shares added by a fixed tree),
 so their parameters must be equal bit for bit as well, and so are the layer-by-layer kernels of the 256-wide fp32
-critic (k splits and per-workgroup copies added in a fixed order); the bf16 configuration still meets in fp32 atomics and
-is held to 0.1 of the parameter change in its norm.  The reported loss statistics are summed with atomics in every configuration."""
+critic (k splits and per-workgroup copies added in a fixed order) and the bf16 networks; the bf16 configuration is held to
+0.1 of the parameter change in its norm.  The reported loss statistics are summed with atomics in every configuration."""
 import numpy as np
 import pytest
 import torch

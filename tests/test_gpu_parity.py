@@ -256,10 +256,8 @@ def test_ppo_single_minibatch_gradient(M, orc, k, clipv, norm):
 
 @pytest.mark.parametrize("ha,hc,view", [(128, 64, 7), (256, 256, 5), (512, 256, 5), (256, 512, 7)])
 def test_bf16_other_widths(M, orc, ha, hc, view):
-    """bf16 networks of other widths than config 4's 147-512-512.  Which GEMM kernel a product takes depends on
-    them: output widths that are no multiple of 256 take the 128 x 128 tile kernel, the others the kernel with
-    the weights resident in registers, in a different instantiation for every contraction length (padded input
-    width 128 or 192, hidden width 256 or 512); dz1 at width 256 takes the tile kernel again."""
+    """bf16 networks of other widths than config 4's 147-512-512: every width is an instantiation of its own, with its own
+    arrangement of wavefronts, and the weight gradients take the smaller output tile up to 128 units."""
     kw = dict(actor_hidden=ha, critic_hidden=hc, view=view)
     check_policy_forward(M, orc, small(4, **kw), 40 + view)
     check_single_minibatch_gradient(M, orc, small(4, n_epochs=1, n_minibatches=1, max_grad_norm=0.0, **kw), 4)
@@ -275,8 +273,8 @@ def test_fp32_other_widths(M, orc, ha, hc):
 
 
 def test_bf16_odd_chunk_count(M, orc):
-    """816 samples (17 environments): the weight-gradient kernel's k ranges hold 8 and 5 chunks of 64 samples, so
-    the chunk-pair loop ends on a single chunk, and the last 64-row tile of the other kernels is ragged."""
+    """816 samples (17 environments): the weight-gradient kernel's last k range holds a single chunk of 48 samples, so the
+    chunk-pair loop ends on half a pair, and the last 64-row tile of the other kernels is ragged."""
     check_single_minibatch_gradient(M, orc, small(4, n_envs=17, n_epochs=1, n_minibatches=1, max_grad_norm=0.0), 4)
 
 
