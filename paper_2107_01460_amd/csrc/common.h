@@ -55,9 +55,9 @@ inline NetOffsets net_offsets(int64_t base, int Din, int H, int Dout) {
   return o;
 }
 
-// The fused forward kernel (fused_forward.h) keeps a row tile of the input in LDS at its whole width, which bounds the input
-// width (two workgroups per CU up to about 320 inputs at H = 256, one up to about 950); wider networks and other widths take
-// the layer-by-layer kernels.  Which (H, BM) pairs exist: H = 64 -> BM 64; H = 128 or 256 -> BM 32.
+// The forward kernel of small calls (fused_forward.h) keeps a row tile of the input in LDS at its whole width, which bounds the
+// input width (two workgroups per CU up to about 320 inputs at H = 256, one up to about 950); wider networks and other widths take
+// the larger calls' kernels.  Which (H, BM) pairs exist: H = 64 -> BM 64; H = 128 or 256 -> BM 32.
 inline int fused_forward_px(int Din) {
   int px = (Din + 15) / 16 * 16;
   while ((px / 4) % 2 == 0) px += 4;
@@ -71,15 +71,20 @@ inline bool fused_forward_supported(int H, int Din) {
   return (H == 64 || H == 128 || H == 256) && fused_forward_lds_bytes(H, Din, 6) <= 160 * 1024;
 }
 
+// split_net.h takes a row tile of a network of up to this many hidden units (any multiple of 32) through the whole network: three
+// bf16 planes of 64 rows have to fit a compute unit's LDS.
+constexpr int kSplitNetMaxH = 320;
+inline bool split_net_supported(int H) { return H <= kSplitNetMaxH; }
+
 // The kernels read weights from a working copy of the parameter vector in which every block (W1, b1, ...)
 // starts on a 64-float boundary, so that 16-byte loads of weight rows are always aligned.
 struct ParamMap {
   int64_t src[13], dst[13];  // 12 blocks (actor 6, critic 6) + end
-  // After the 12 blocks, per fp32 network that the fused kernels cover (fused_forward_supported), the copies these read: W1, W2
-  // and, for the update, W2 transposed, split into three bf16 parts and in the order the matrix-core kernels read their B
+  // After the 12 blocks, per fp32 network that the fused kernels cover (split_net_supported), the copies these read, one directly
+  // behind the other: W1, W2 and, for the update, W2 transposed, split into three bf16 parts and in the order the matrix-core kernels read their B
   // operand straight from memory: part p of element (k, n) of a [K][H] matrix at split_weight_index(k, n, H) + p *
   // split_weight_plane(H), in bf16 elements, so that the eight k values of a lane are one 16-byte load, contiguous across
-  // lanes.  W1 is zero-padded to kpad1 rows (a multiple of 16).  For a training rollout (rollout_train_kernel) the actor's two
+  // lanes.  W1 is zero-padded to kpad1 rows (a multiple of 32).  For a training rollout (rollout_train_kernel) the actor's two
   // copies hold fp32 values instead, element (k, n) at ((k / 4) * H + n) * 4 + k % 4.
   int64_t sw_w1[2], sw_w2[2], sw_w2t[2];
   bool fused[2];  // these copies exist
@@ -102,8 +107,8 @@ inline ParamMap param_map(const Dims& d, bool update) {
   m.din[0] = d.D;
   m.din[1] = d.Dc;
   for (int n = 0; n < 2; ++n) {
-    m.kpad1[n] = (m.din[n] + 15) / 16 * 16;
-    m.fused[n] = !d.bf16 && fused_forward_supported(m.hidden[n], m.din[n]);
+    m.kpad1[n] = (m.din[n] + 31) / 32 * 32;
+    m.fused[n] = !d.bf16 && split_net_supported(m.hidden[n]);
     m.plain[n] = update || !m.fused[n];
   }
   int64_t off = 0;

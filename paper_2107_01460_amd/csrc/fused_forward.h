@@ -1,14 +1,8 @@
-// Fused network forward pass: both hidden layers, the output layer and whatever consumes the outputs
-// (sampling during the rollout, the PPO loss during the update) in one kernel, with the first hidden
-// activation kept in LDS between the two MFMA GEMMs.  In training mode the kernel also produces what the
-// backward pass needs: h1 and dz2 = dL/d(pre-activation of layer 2) go to HBM once, h2 never does, and the
-// output-layer gradient (W3, b3) is accumulated in registers across the row tiles a workgroup owns.
+// Forward pass of small calls: both hidden layers, the output layer and whatever consumes the outputs of both networks in one
+// launch, on the caller's unstaged parameters and the fp32 instruction, with the first hidden activation kept in LDS.
 //
-// Workgroup = 4 wavefronts on a tile of BM samples x H hidden units: (BM/32) x (H/32) MFMA tiles of
-// 32x32, one or two per wavefront; several small workgroups per CU overlap each other's phases.  The row tile of
-// the input sits in LDS at its whole width; the weights go straight from the operand-order copies in global memory
-// (L2-resident) into registers with 16-byte loads (gemm_phase_w_any), so a layer has no staging buffer and no barrier
-// of its own.
+// Workgroup = 4 wavefronts on a tile of BM samples x H hidden units: (BM/32) x (H/32) MFMA tiles of 32x32, one or two per
+// wavefront.  The row tile of the input sits in LDS at its whole width; a tile's wavefronts read the weights once.
 #pragma once
 #include "gemm.h"
 #include "heads.h"
@@ -21,25 +15,13 @@ struct FusedFwdArgs {
   int Din;
   int xvec;   // 1: rows are 16-byte aligned and Din % 4 == 0: 16-byte loads of X.  2: rows start at any 4-byte boundary of a
               // buffer whose two ends are 16-byte aligned: a row is fetched as the aligned 16-byte chunks that cover it
-  const float *W1, *b1, *W2, *b2, *W3, *b3;  // aligned working copy, W[in][H]
-  const float *W1s, *W2s;  // split operand-order copies (ParamMap); W1s zero-padded to kpad1 rows
+  const float *W1, *b1, *W2, *b2, *W3, *b3;  // W[in][H], at any 4-byte boundary
   int kpad1;               // Din rounded up to a multiple of 16
   int px;                  // pitch of the X tile in LDS: a multiple of 4 with px / 4 odd, >= kpad1
-  float* h1_out;   // training: [S][H]
-  float* dz2_out;  // training: [S][H]
-  float* gW3;      // training: [H][NOUT] accumulated with atomics
-  float* gb3;      // training: [NOUT]
-  float* stats;    // training: 5 floats accumulated with atomics (policy loss, value loss, entropy, KL, clip fraction)
-  // training, H = 256 (one thread per hidden unit), nullable: workgroup b stores its share of the W3 gradient and, behind
-  // it, of the b3 gradient at partial3 + b * (H * NOUT + NOUT) with plain stores; the launcher then adds the copies to
-  // gW3 (which gb3 must directly follow) in a fixed order.  Room for kFusedFwdTrainGrid copies.
-  float* partial3;
 };
-constexpr int kFusedFwdTrainGrid = 1024;  // workgroups of a training launch (persistent: register-resident W3 gradient)
 
-// The kernel's body: workgroup `bid` of `nblk` that share the tiles.  DIRECT: weights from W1 / W2 (unstaged parameters) on
-// the fp32 instruction instead of the split copies.
-template <int H, int BM, int NOUT, bool TRAIN, bool DIRECT, class Finish>
+// The kernel's body: workgroup `bid` of `nblk` that share the tiles.
+template <int H, int BM, int NOUT, class Finish>
 __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const Finish& fin, const unsigned bid, const unsigned nblk) {
   constexpr int PH = H + 4, GROUPS = 256 / BM;
   constexpr int NTN = H / 32, MT = BM / 32, TILES = MT * NTN, TPW = TILES / 4;
@@ -49,28 +31,17 @@ __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const 
   constexpr int TPR = NTH / BM;  // threads staging one row of X
   extern __shared__ __attribute__((aligned(16))) float lds[];
   struct {
-    float *Xs, *Hs, *red, *dls, *W3s;
+    float *Xs, *Hs, *red, *W3s;
   } L;
   const int px = a.px;
   L.Xs = lds;                          // [BM][px]   input rows, k-contiguous; columns Din .. px stay zero
   L.Hs = L.Xs + BM * px;               // [BM][PH]   h1, then h2
   L.red = L.Hs + BM * PH;              // [GROUPS][BM][NOUT]
-  L.dls = L.red + GROUPS * BM * NOUT;  // [BM][8]    dL/d(outputs), rows padded to 8 with zeros (MFMA operand)
-  L.W3s = L.dls + BM * 8;              // [H][NOUT]
+  L.W3s = L.red + GROUPS * BM * NOUT;  // [H][NOUT]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo = lane & 31, hi = lane >> 5;
   const int mt = (wave * TPW) / NTN, nt0 = (wave * TPW) % NTN;  // this wavefront's tiles: (mt, nt0 .. nt0+TPW-1)
-
-  const WeightRsrc rsW1 = split_weight_rsrc(a.W1s, a.kpad1, H), rsW2 = split_weight_rsrc(a.W2s, H, H);
-  const int wlane = (hi * H + nt0 * 32 + lo) * 4;  // this lane's 16 bytes of a group's half `hi` in a split weight copy
-
-  // output-layer gradient, persistent over the tiles of this workgroup: thread -> hidden unit tid % H
-  constexpr int HPARTS = (256 / H) > 0 ? (256 / H) : 1;  // threads per hidden unit
-  constexpr int SPP = BM / HPARTS;        // samples each of them sums per tile
-  float gw[NOUT], gb[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) gw[k] = gb[k] = 0.f;
 
   for (int i = tid; i < H * NOUT; i += NTH) L.W3s[i] = a.W3[i];  // ordered before its first use by the barriers of layer 1
   for (int i = tid; i < BM * px; i += NTH) L.Xs[i] = 0.f;        // the padding columns stay zero for good
@@ -78,9 +49,6 @@ __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const 
   const int64_t ntiles = (a.S + BM - 1) / BM;
   for (int64_t tile = bid; tile < ntiles; tile += nblk) {
     const int64_t s0 = tile * BM;
-    const int rows_left = (int)min((int64_t)BM, a.S - s0);
-    float* const h1_tile = TRAIN ? a.h1_out + s0 * H : nullptr;    // uniform bases: lanes add 32-bit offsets
-    float* const dz2_tile = TRAIN ? a.dz2_out + s0 * H : nullptr;
     // ---- this tile's rows to LDS: thread -> row tid / TPR, every TPR-th 16-byte (or 4-byte) piece of it, four
     // (twelve) loads in flight at a time.  Rows past the end re-read the last row (their results are never stored).
     {
@@ -140,23 +108,11 @@ __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
     };
-    // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS (and HBM when training)
+    // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS
     zero_acc();
-    if (DIRECT) {
 #pragma unroll
-      for (int q = 0; q < TPW; ++q)
-        gemm_phase_direct<H>(L.Xs + (mt * 32 + lo) * px + 4 * hi, a.W1 + (nt0 + q) * 32 + lo, a.Din, hi, a.kpad1 / 16, acc[q]);
-    } else {
-      const float* const xa = L.Xs + (mt * 32 + lo) * px + 8 * hi;
-      gemm_phase_w_any<H, false, TPW>(xa, rsW1, wlane, a.kpad1 / 16, acc);
-      float all = 0.f;
-#pragma unroll
-      for (int q = 0; q < TPW; ++q) all = sum_of(all, acc[q]);
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(all != all) != 0, 0)) {  // an input out of split_pair's range?
-        zero_acc();
-        gemm_phase_w_any<H, true, TPW>(xa, rsW1, wlane, a.kpad1 / 16, acc);
-      }
-    }
+    for (int q = 0; q < TPW; ++q)
+      gemm_phase_direct<H>(L.Xs + (mt * 32 + lo) * px + 4 * hi, a.W1 + (nt0 + q) * 32 + lo, a.Din, hi, a.kpad1 / 16, acc[q]);
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
       const int n = (nt0 + q) * 32 + lo;
@@ -166,20 +122,15 @@ __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const 
         const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
         float v = tanh_f32(acc[q][r] + bias);
         L.Hs[m * PH + n] = v;
-        if (TRAIN && m < rows_left) h1_tile[m * H + n] = v;
         if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four elements in flight at a time keeps registers bounded
       }
     }
     __syncthreads();  // the h1 tile is complete
     // ---- layer 2: h2 = tanh(h1 W2 + b2), kept in registers
     zero_acc();
-    if (DIRECT) {
 #pragma unroll
-      for (int q = 0; q < TPW; ++q)
-        gemm_phase_direct<H>(L.Hs + (mt * 32 + lo) * PH + 4 * hi, a.W2 + (nt0 + q) * 32 + lo, H, hi, H / 16, acc[q]);
-    } else {
-      gemm_phase_w_any<H, false, TPW>(L.Hs + (mt * 32 + lo) * PH + 8 * hi, rsW2, wlane, H / 16, acc);
-    }
+    for (int q = 0; q < TPW; ++q)
+      gemm_phase_direct<H>(L.Hs + (mt * 32 + lo) * PH + 4 * hi, a.W2 + (nt0 + q) * 32 + lo, H, hi, H / 16, acc[q]);
     __syncthreads();  // every wavefront is past its last read of h1
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
@@ -189,12 +140,10 @@ __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const 
       for (int r = 0; r < 16; ++r) {
         const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
         float v = tanh_f32(acc[q][r] + bias);
-        acc[q][r] = v;
         L.Hs[m * PH + n] = v;
         if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // W3 rows of this thread's columns, for the head (ALU) and for dz2
     __syncthreads();
     // ---- output layer on the ALUs: thread -> (sample tid % BM, slice tid / BM of the hidden units)
     {
@@ -224,118 +173,25 @@ __device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const 
     }
     __syncthreads();
     if (tid < BM) {
-      float out[NOUT], dl[NOUT];
+      float out[NOUT];
 #pragma unroll
       for (int k = 0; k < NOUT; ++k) {
         float v = a.b3[k];
 #pragma unroll
         for (int gq = 0; gq < GROUPS; ++gq) v += L.red[(gq * BM + tid) * NOUT + k];
         out[k] = v;
-        dl[k] = 0.f;
       }
-      if (s0 + tid < a.S) fin(s0 + tid, out, dl, st);
-      if (TRAIN) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) L.dls[tid * 8 + k] = k < NOUT ? dl[k < NOUT ? k : 0] : 0.f;
-#pragma unroll
-        for (int k = 0; k < NOUT; ++k) gb[k] += dl[k];
-      }
-    }
-    if (TRAIN) {
-      __syncthreads();
-      // ---- dz2 = (dl W3^T) * (1 - h2^2): the rank-NOUT product runs on the matrix cores (k padded to 8) and
-      // lands in the same lane layout as the register-resident h2
-      const float4 av = *reinterpret_cast<const float4*>(&L.dls[(mt * 32 + lo) * 8 + 4 * hi]);
-      const float af[4] = {av.x, av.y, av.z, av.w};
-#pragma unroll
-      for (int q = 0; q < TPW; ++q) {
-        const int n = (nt0 + q) * 32 + lo;
-        float bf[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bf[j] = (4 * hi + j < NOUT) ? L.W3s[n * NOUT + (4 * hi + j < NOUT ? 4 * hi + j : 0)] : 0.f;
-        floatx16 gacc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) gacc[r] = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) gacc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], bf[j], gacc, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-          const float h = acc[q][r];
-          float v = gacc[r] * (1.0f - h * h);
-          if (m < rows_left) dz2_tile[m * H + n] = v;
-          if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      // ---- gW3[i][k] += sum_s h2[s][i] dl[s][k]
-      {
-        const int i = tid % H, part = tid / H;
-#pragma unroll 4
-        for (int s = part * SPP; s < (part + 1) * SPP; ++s) {
-          const float h = L.Hs[s * PH + i];
-#pragma unroll
-          for (int k = 0; k < NOUT; ++k) gw[k] = fmaf(h, L.dls[s * 8 + k], gw[k]);
-        }
-      }
+      if (s0 + tid < a.S) fin(s0 + tid, out, nullptr, nullptr);
     }
     __syncthreads();  // the tile buffers are reused by the next row tile
   }
-  if (TRAIN) {
-    const int i = tid % H;
-    float* const own = (H == 256 && a.partial3 != nullptr) ? a.partial3 + (int64_t)bid * (H * NOUT + NOUT) : nullptr;
-#pragma unroll
-    for (int k = 0; k < NOUT; ++k) {
-      if (own != nullptr) own[i * NOUT + k] = gw[k];
-      else atomicAdd(&a.gW3[i * NOUT + k], gw[k]);
-    }
-    if (wave == 0) {  // samples live in threads tid < BM <= 64
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) {
-        float v = gb[k];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0) {
-          if (own != nullptr) own[H * NOUT + k] = v;
-          else atomicAdd(&a.gb3[k], v);
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < 5; ++k) {
-        float v = st[k];
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if (lane == 0 && v != 0.f) atomicAdd(&a.stats[k], v);
-      }
-    }
-  }
-}
-
-template <int H, int BM, int NOUT, bool TRAIN, class Finish>
-__global__ void __launch_bounds__(256, 2) fused_forward_kernel(FusedFwdArgs a, Finish fin) {
-  fused_forward_body<H, BM, NOUT, TRAIN, false, Finish>(a, fin, blockIdx.x, gridDim.x);
 }
 
 // Both networks of a small call in one launch, with unstaged weights: workgroups 0 .. grid_a - 1 the first.
 template <int HA, int HB, int NOUT_A, int NOUT_B, class FinishA, class FinishB>
 __global__ void __launch_bounds__(256, 2) fused_forward_small_kernel(FusedFwdArgs a, FinishA fa, FusedFwdArgs b, FinishB fb, unsigned grid_a) {
-  if (blockIdx.x < grid_a) fused_forward_body<HA, HA == 64 ? 64 : 32, NOUT_A, false, true, FinishA>(a, fa, blockIdx.x, grid_a);
-  else fused_forward_body<HB, HB == 64 ? 64 : 32, NOUT_B, false, true, FinishB>(b, fb, blockIdx.x - grid_a, gridDim.x - grid_a);
-}
-
-template <int H, int BM, int NOUT, bool TRAIN, class Finish>
-inline int32_t launch_fused_forward_inst(const FusedFwdArgs& a, const Finish& fin, hipStream_t s) {
-  auto kern = fused_forward_kernel<H, BM, NOUT, TRAIN, Finish>;
-  const size_t bytes = fused_forward_lds_bytes(H, a.Din, NOUT);
-  static bool configured = false;  // per instantiation
-  if (!configured) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return MARL_E_LAUNCH;
-    configured = true;
-  }
-  const int64_t tiles = (a.S + BM - 1) / BM;
-  const unsigned grid = (unsigned)std::min<int64_t>(tiles, TRAIN ? kFusedFwdTrainGrid : 2048);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(256), bytes, s, a, fin);
-  const int32_t rc = launch_status();
-  if (TRAIN && H == 256 && a.partial3 != nullptr && rc == MARL_OK)
-    launch_reduce_partials(a.partial3, (int)grid, (int64_t)H * NOUT + NOUT, a.gW3, s);
-  return rc;
+  if (blockIdx.x < grid_a) fused_forward_body<HA, HA == 64 ? 64 : 32, NOUT_A, FinishA>(a, fa, blockIdx.x, grid_a);
+  else fused_forward_body<HB, HB == 64 ? 64 : 32, NOUT_B, FinishB>(b, fb, blockIdx.x - grid_a, gridDim.x - grid_a);
 }
 
 // Few enough rows that a call is a chain of latencies: one launch on the unstaged parameters (a tile's wavefronts read
@@ -376,15 +232,6 @@ inline int32_t launch_fused_forward_small(int HA, const FusedFwdArgs& a, const F
     case 42: return launch_fused_forward_small_inst<256, 128, NOUT_A, NOUT_B>(a, fa, b, fb, s);
     default: return launch_fused_forward_small_inst<256, 256, NOUT_A, NOUT_B>(a, fa, b, fb, s);
   }
-}
-
-template <int NOUT, bool TRAIN, class Finish>
-inline int32_t launch_fused_forward(int H, const FusedFwdArgs& a, const Finish& fin, hipStream_t s) {
-  // algorithmic flops of the two hidden layers
-  TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)a.S * ((double)a.Din * H + (double)H * H), s);
-  if (H == 64) return launch_fused_forward_inst<64, 64, NOUT, TRAIN, Finish>(a, fin, s);
-  if (H == 128) return launch_fused_forward_inst<128, 32, NOUT, TRAIN, Finish>(a, fin, s);
-  return launch_fused_forward_inst<256, 32, NOUT, TRAIN, Finish>(a, fin, s);
 }
 
 }  // namespace marl

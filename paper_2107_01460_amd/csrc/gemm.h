@@ -91,7 +91,6 @@ struct GemmArgs {
   int64_t M, N, K;
   int64_t k_per_split;   // TN: k range of one blockIdx.z
   int c_rot;             // TN, multiple of 32 below N: column n of the product goes to column (n + c_rot) mod N of C and colsum
-  int round_bf16;        // round stored results to bf16 precision (kept in fp32 storage)
   // TN with EPI_ATOMIC_ADD, nullable: k split z stores its products at split_out + z * split_count + m * ldc + n and its
   // column sums of B behind them (at + M * ldc + n) with plain stores instead of adding to C / colsum with atomics; the
   // caller then adds the splits in a fixed order (reduce_partials_kernel), which makes the result the same in every run.
@@ -224,28 +223,6 @@ __device__ __forceinline__ void gemm_phase_t(const bf16_t* xs, int plane, Weight
         acc = mfma_split(w, frag_row(xs + 16 * g, plane), acc);
       }
       if (g + RING < KG) phase_w_load<H>(pw, B, lane_off, g + RING, kgroups);
-    }
-  }
-}
-
-// gemm_phase_w with a run-time number of groups, no request ahead: the groups in flight are the one in use and two on their way.
-template <int H, bool ANY, int NT>
-__device__ __forceinline__ void gemm_phase_w_any(const float* __restrict__ As, WeightRsrc B, int lane_off, int kgroups, floatx16* acc) {
-  PhaseW<3, NT> pw;
-  phase_w_load<H>(pw, B, lane_off, 0, kgroups);
-  phase_w_load<H>(pw, B, lane_off, 1, kgroups);
-#pragma unroll 1
-  for (int g0 = 0; g0 < kgroups; g0 += 3) {
-    const int rest = kgroups - g0;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      if (d < rest) {  // uniform
-        phase_w_load_at<H>(pw, (d + 2) % 3, B, lane_off, min(g0 + d + 2, kgroups - 1));
-        const float* const p = As + 16 * (g0 + d);
-        const Split8 a = split8<ANY>(*reinterpret_cast<const float4*>(p), *reinterpret_cast<const float4*>(p + 4));
-#pragma unroll
-        for (int q = 0; q < NT; ++q) acc[q] = mfma_split(a, Split8{pw.w[d][q][0], pw.w[d][q][1], pw.w[d][q][2]}, acc[q]);
-      }
     }
   }
 }
@@ -528,10 +505,8 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
         float v = acc[i][jn][r];
         if (EPI == EPI_BIAS_TANH) {
           v = tanh_f32(v + bias);
-          if (g.round_bf16) v = round_to_bf16(v);
         } else if (EPI == EPI_DTANH) {
           v = v * (1.0f - h[r] * h[r]);
-          if (g.round_bf16) v = round_to_bf16(v);
         } else if (EPI == EPI_STORE) {
           v += bias;
         }

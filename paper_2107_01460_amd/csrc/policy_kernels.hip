@@ -8,8 +8,7 @@
 #include "gemm.h"
 #include "heads.h"
 #include "rollout_fused.h"
-
-#include <tuple>
+#include "split_net.h"
 
 namespace marl {
 
@@ -36,7 +35,7 @@ __global__ void stage_params_kernel(const float* __restrict__ src, float* __rest
     else store_split_weight(dst + copy, v, k, n, H);
   };
 #pragma unroll
-  for (int net = 0; net < 2; ++net) {  // zero rows of the copies of W1 (fewer than 16 rows: far fewer floats than parameters)
+  for (int net = 0; net < 2; ++net) {  // zero rows of the copies of W1 (fewer than 32 rows: far fewer floats than parameters)
     const int H = pm.hidden[net];
     if (pm.fused[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) store(net, pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H);
   }
@@ -80,14 +79,21 @@ struct CriticRolloutFinish {
   }
 };
 
-FusedFwdArgs fused_args(const RowSrc& X, int64_t S, int Din, const float* eff, const ParamMap& pm, int net) {
-  const NetOffsets o = padded_offsets(pm, net);
+FusedFwdArgs direct_args(const RowSrc& X, int64_t S, int Din, const float* params, const NetOffsets& o) {
   FusedFwdArgs a{};
   a.X = X; a.S = S; a.Din = Din;
   a.xvec = aligned16(X.base) && X.ld % 4 == 0 && Din % 4 == 0;
   if (!a.xvec && X.gather == nullptr && aligned16(X.base) && (X.nrows * X.ld) % 4 == 0) a.xvec = 2;
-  a.W1 = eff + o.W1; a.b1 = eff + o.b1; a.W2 = eff + o.W2; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
-  a.W1s = eff + pm.sw_w1[net]; a.W2s = eff + pm.sw_w2[net]; a.kpad1 = pm.kpad1[net]; a.px = fused_forward_px(Din);
+  a.W1 = params + o.W1; a.b1 = params + o.b1; a.W2 = params + o.W2; a.b2 = params + o.b2; a.W3 = params + o.W3; a.b3 = params + o.b3;
+  a.kpad1 = (Din + 15) / 16 * 16; a.px = fused_forward_px(Din);
+  return a;
+}
+
+SplitNetArgs split_net_args(const RowSrc& X, int64_t S, int Din, const float* eff, const ParamMap& pm, int net) {
+  const NetOffsets o = padded_offsets(pm, net);
+  SplitNetArgs a{};
+  a.X = X; a.S = S; a.Din = Din; a.Kp = pm.kpad1[net]; a.W = eff + pm.sw_w1[net];
+  a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
   return a;
 }
 
@@ -102,6 +108,23 @@ bool use_fused_rollout(const marl_config& c) {
   return !d.bf16 && rollout_fused_supported(d.Ha, d.A) && fused_forward_supported(d.Ha, d.D);
 }
 
+// floats of a working copy for a forward pass that goes layer by layer (64, 128 and 256 units: on split copies)
+int64_t layerwise_param_floats(const marl_config& c) {
+  const Dims d = dims_of(c);
+  int64_t n = 0;
+  auto add = [&](int64_t floats) { n += (floats + 63) / 64 * 64; };
+  for (int k = 0; k < 2; ++k) {
+    const int64_t H = k ? d.Hc : d.Ha, din = k ? d.Dc : d.D, out = k ? 1 : kActions;
+    const bool copies = !d.bf16 && fused_forward_supported((int)H, (int)din);
+    add(copies ? (din + 15) / 16 * 16 * H * 3 / 2 : din * H);
+    add(H);
+    add(copies ? H * H * 3 / 2 : H * H);
+    add(H); add(H * out); add(out);
+  }
+  if (d.bf16) n += (bf16_net_weight_elems(d.D, d.Ha) + bf16_net_weight_elems(d.Dc, d.Hc) + 1) / 2 + 192;
+  return n;
+}
+
 RolloutWsView carve_rollout_ws(const marl_config& c, int64_t n_rows, void* ws, int64_t* total) {
   const Dims d = dims_of(c);
   const int64_t S = n_rows * d.A, Sc = d.central ? n_rows : S;
@@ -114,25 +137,22 @@ RolloutWsView carve_rollout_ws(const marl_config& c, int64_t n_rows, void* ws, i
   };
   RolloutWsView v{};
   v.eff_params = (float*)take(effective_param_floats(c, false) * 4);
-  if (!d.bf16) {
-    // hidden activations of one pass: only the layer-by-layer path stores them (the fused kernel keeps them on chip)
-    if (!fused_forward_supported(d.Ha, d.D)) {
-      v.h1a = (float*)take(S * d.Ha * 4);
-      v.h2a = (float*)take(S * d.Ha * 4);
-    }
-    if (!fused_forward_supported(d.Hc, d.Dc)) {
-      v.h1c = (float*)take(Sc * d.Hc * 4);
-      v.h2c = (float*)take(Sc * d.Hc * 4);
-    }
-  } else {
-    // The bf16 networks keep their activations on chip.  The size stays what a call that stored them needed (packed input, both
-    // hidden layers), since marl_rollout_static decides by it what it takes.
-    for (const auto& [rows, din, H] : {std::tuple<int64_t, int, int>{S, d.D, d.Ha}, std::tuple<int64_t, int, int>{Sc, d.Dc, d.Hc}}) {
-      take(rows * round_up64(din) * 2);
-      take(rows * H * 2);
-      take(rows * H * 2);
-    }
+  const int H[2] = {d.Ha, d.Hc}, din[2] = {d.D, d.Dc};
+  const int64_t rows[2] = {S, Sc};
+  if (!d.bf16) {  // hidden activations of one pass: only the layer-by-layer path stores them
+    float** const h[2][2] = {{&v.h1a, &v.h2a}, {&v.h1c, &v.h2c}};
+    for (int n = 0; n < 2; ++n)
+      if (!split_net_supported(H[n]))
+        for (float** p2 : h[n]) *p2 = (float*)take(rows[n] * H[n] * 4);
   }
+  // marl_rollout_static decides by this size what it takes, so it stays at least what a call needs that goes layer by layer: the
+  // parameters and both hidden layers of a pass, packed inputs in bf16 (fp32 of 64, 128 and 256 units: no activations).
+  int64_t by_layer = align256(layerwise_param_floats(c) * 4);
+  for (int n = 0; n < 2; ++n) {
+    if (d.bf16) by_layer += align256(rows[n] * round_up64(din[n]) * 2) + 2 * align256(rows[n] * H[n] * 2);
+    else if (!fused_forward_supported(H[n], din[n])) by_layer += 2 * align256(rows[n] * H[n] * 4);
+  }
+  off = std::max(off, by_layer);
   if (total) *total = off;
   return v;
 }
@@ -140,14 +160,14 @@ RolloutWsView carve_rollout_ws(const marl_config& c, int64_t n_rows, void* ws, i
 }  // namespace
 
 void mlp_hidden_forward(const RowSrc& X, int64_t S, int Din, int H, const float* W1, const float* b1, const float* W2,
-                        const float* b2, float* h1, float* h2, bool bf16, hipStream_t s) {
+                        const float* b2, float* h1, float* h2, hipStream_t s) {
   GemmArgs g{};
   g.A = X; g.B = W1; g.ldb = H; g.C = h1; g.ldc = H; g.aux_vec = b1;
-  g.M = S; g.N = H; g.K = Din; g.round_bf16 = bf16;
+  g.M = S; g.N = H; g.K = Din;
   launch_gemm<GEMM_NN, EPI_BIAS_TANH>(g, s);
   GemmArgs g2{};
   g2.A = RowSrc{h1, H, nullptr, 1, S}; g2.B = W2; g2.ldb = H; g2.C = h2; g2.ldc = H; g2.aux_vec = b2;
-  g2.M = S; g2.N = H; g2.K = H; g2.round_bf16 = bf16;
+  g2.M = S; g2.N = H; g2.K = H;
   launch_gemm<GEMM_NN, EPI_BIAS_TANH>(g2, s);
 }
 
@@ -216,12 +236,12 @@ static int32_t forward_rows(const marl_config& c, const float* eff, const float*
   if (want_actor) {
     const NetOffsets o = padded_offsets(param_map(d, false), 0);
     const RowSrc X{obs, d.D, nullptr, 1, S};
-    if (fused_forward_supported(d.Ha, d.D)) {
+    if (split_net_supported(d.Ha)) {
       ActorRolloutFinish fin{logits_out, sample ? *sample : SampleArgs{}, sample ? 1 : 0};
-      const int32_t rc = launch_fused_forward<kActions, false>(d.Ha, fused_args(X, S, d.D, eff, param_map(d, false), 0), fin, s);
+      const int32_t rc = launch_split_forward<kActions>(d.Ha, split_net_args(X, S, d.D, eff, param_map(d, false), 0), fin, s);
       if (rc != MARL_OK) return rc;
     } else {
-      mlp_hidden_forward(X, S, d.D, d.Ha, eff + o.W1, eff + o.b1, eff + o.W2, eff + o.b2, w.h1a, w.h2a, d.bf16, s);
+      mlp_hidden_forward(X, S, d.D, d.Ha, eff + o.W1, eff + o.b1, eff + o.W2, eff + o.b2, w.h1a, w.h2a, s);
       launch_actor_head_rollout(w.h2a, S, d.Ha, eff + o.W3, eff + o.b3, logits_out, sample, s);
     }
   }
@@ -229,12 +249,12 @@ static int32_t forward_rows(const marl_config& c, const float* eff, const float*
     const NetOffsets o = padded_offsets(param_map(d, false), 1);
     const int64_t Sc = d.central ? n_rows : S;
     const RowSrc X{obs, d.Dc, nullptr, 1, Sc};
-    if (fused_forward_supported(d.Hc, d.Dc)) {
+    if (split_net_supported(d.Hc)) {
       CriticRolloutFinish fin{value_out, d.central ? d.A : 1, value_tail ? value_split : Sc, value_tail};
-      const int32_t rc = launch_fused_forward<1, false>(d.Hc, fused_args(X, Sc, d.Dc, eff, param_map(d, false), 1), fin, s);
+      const int32_t rc = launch_split_forward<1>(d.Hc, split_net_args(X, Sc, d.Dc, eff, param_map(d, false), 1), fin, s);
       if (rc != MARL_OK) return rc;
     } else {
-      mlp_hidden_forward(X, Sc, d.Dc, d.Hc, eff + o.W1, eff + o.b1, eff + o.W2, eff + o.b2, w.h1c, w.h2c, d.bf16, s);
+      mlp_hidden_forward(X, Sc, d.Dc, d.Hc, eff + o.W1, eff + o.b1, eff + o.W2, eff + o.b2, w.h1c, w.h2c, s);
       launch_critic_head_rollout(w.h2c, Sc, d.Hc, eff + o.W3, eff + o.b3, value_out, d.central ? d.A : 1, s);
     }
   }
@@ -247,17 +267,12 @@ int32_t launch_policy_forward(const marl_config& c, const float* params, const f
   const int64_t S = n_rows * d.A;
   if (!d.bf16 && S <= kForwardSmall && fused_forward_supported(d.Ha, d.D) && fused_forward_supported(d.Hc, d.Dc)) {
     const int64_t Sc = d.central ? n_rows : S;
-    const ParamMap pm = param_map(d, false);
-    auto direct = [&](const float* X, int64_t rows, int Din, int net, const NetOffsets& o) {
-      FusedFwdArgs a = fused_args(RowSrc{X, Din, nullptr, 1, rows}, rows, Din, params, pm, net);
-      a.W1 = params + o.W1; a.b1 = params + o.b1; a.W2 = params + o.W2; a.b2 = params + o.b2; a.W3 = params + o.W3; a.b3 = params + o.b3;
-      return a;
-    };
+    auto direct = [&](int64_t rows, int Din, const NetOffsets& o) { return direct_args(RowSrc{obs, Din, nullptr, 1, rows}, rows, Din, params, o); };
     const ActorRolloutFinish fa{logits, SampleArgs{}, 0};
     const CriticRolloutFinish fc{value, d.central ? d.A : 1, Sc, nullptr};
     return launch_fused_forward_small<kActions, 1>(
-        d.Ha, direct(obs, logits != nullptr ? S : 0, d.D, 0, net_offsets(0, d.D, d.Ha, kActions)), fa,
-        d.Hc, direct(obs, value != nullptr ? Sc : 0, d.Dc, 1, net_offsets(d.Pa, d.Dc, d.Hc, 1)), fc, s);
+        d.Ha, direct(logits != nullptr ? S : 0, d.D, net_offsets(0, d.D, d.Ha, kActions)), fa,
+        d.Hc, direct(value != nullptr ? Sc : 0, d.Dc, net_offsets(d.Pa, d.Dc, d.Hc, 1)), fc, s);
   }
   const RolloutWsView w = carve_rollout_ws(c, n_rows, workspace, nullptr);
   const float* eff = effective_params(c, params, w.eff_params, s, USE_FORWARD);
@@ -304,9 +319,9 @@ int32_t launch_rollout(const marl_config& c, marl_env_state st, const float* par
   const int64_t NA = d.NA, slab = NA * d.D;
   int32_t rc;
   // The values do not steer the rollout (the parameters are constant during it): where the critic's forward pass
-  // needs no per-row workspace (the fused fp32 kernel, the bf16 networks), the values of all T steps and of the post-rollout observation
+  // needs no per-row workspace (whole networks in one kernel), the values of all T steps and of the post-rollout observation
   // are computed in one pass over the stored observations afterwards instead of one small launch per step.
-  const bool batch_values = d.bf16 || fused_forward_supported(d.Hc, d.Dc);
+  const bool batch_values = d.bf16 || split_net_supported(d.Hc);
   if (use_fused_rollout(c)) {
     // all T steps in one launch: a workgroup keeps its environments on chip and streams the trajectory out
     RolloutArgs a = rollout_fused_args(c, st, eff);

@@ -5,18 +5,17 @@
 #include <cmath>
 
 #include "bf16_net.h"
-#include "fused_forward.h"
 #include "fused_train.h"
 #include "gemm.h"
-#include "wreg_gemm.h"
 #include "heads.h"
 #include "ppo_common.h"
+#include "split_net.h"
 
 namespace marl {
 
 // implemented in policy_kernels.hip
 void mlp_hidden_forward(const RowSrc& X, int64_t S, int Din, int H, const float* W1, const float* b1, const float* W2,
-                        const float* b2, float* h1, float* h2, bool bf16, hipStream_t s);
+                        const float* b2, float* h1, float* h2, hipStream_t s);
 const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use);
 int64_t effective_param_floats(const marl_config& c, bool update);
 Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, int net);
@@ -31,7 +30,6 @@ struct UpdateWsView {
   float *h1a, *h2a, *dz1a;
   float *h1c, *h2c, *dz1c;
   float* partial;  // per-workgroup copies of one network's gradient (two-stage reduction of the fused training kernel)
-  float* partial_w1;
   float* partial_head;  // per-workgroup W3 / b3 gradients of the output-layer kernels
   float* split_ws;      // fp32 layer-by-layer networks: the k splits of a weight-gradient product, added in a fixed order
   int64_t split_floats;
@@ -66,27 +64,24 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
   v.adv_stats = (double*)take((int64_t)c.n_epochs * c.n_minibatches * 2 * sizeof(double));
   v.ident = (int32_t*)take(R * 4);
   if (!d.bf16) {
-    // activations: rows rounded up to the 64-row tiles of the register-resident kernels, which store whole tiles
-    const int64_t Sap = round_up64(Sa), Scp = round_up64(Sc);
-    v.h1a = (float*)take(Sap * d.Ha * 4);
-    v.h2a = (float*)take(Sap * d.Ha * 4);
-    v.dz1a = (float*)take(Sap * d.Ha * 4);
-    v.h1c = (float*)take(Scp * d.Hc * 4);
-    v.h2c = (float*)take(Scp * d.Hc * 4);
-    v.dz1c = (float*)take(Scp * d.Hc * 4);
+    v.h1a = (float*)take(Sa * d.Ha * 4);
+    v.h2a = (float*)take(Sa * d.Ha * 4);
+    v.dz1a = (float*)take(Sa * d.Ha * 4);
+    v.h1c = (float*)take(Sc * d.Hc * 4);
+    v.h2c = (float*)take(Sc * d.Hc * 4);
+    v.dz1c = (float*)take(Sc * d.Hc * 4);
     int64_t pmax = 0;
     if (fused_train_supported(d.Ha, d.D)) pmax = std::max<int64_t>(pmax, d.Pa);
     if (fused_train_supported(d.Hc, d.Dc)) pmax = std::max<int64_t>(pmax, d.P - d.Pa);
     v.partial = pmax > 0 ? (float*)take((int64_t)kFusedTrainMaxGrid * pmax * 4) : nullptr;
-    // ... and of the first-layer gradient of the 256-wide critic (accumulator-resident transposed product)
-    v.partial_w1 = (d.Hc == kWregN && d.Dc == 300) ? (float*)take((int64_t)kWaccMaxGrid * (300 + 1) * kWregN * 4) : nullptr;
     // the k splits of the layer-by-layer weight gradients (at most `want` splits of pick_k_split per product)
     v.split_floats = 0;
     if (!fused_train_supported(d.Ha, d.D)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Ha, d.D));
     if (!fused_train_supported(d.Hc, d.Dc)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Hc, d.Dc));
     v.split_ws = v.split_floats > 0 ? (float*)take(v.split_floats * 4) : nullptr;
     int64_t head = std::max(loss_head_partial_floats(d.Ha, kActions), loss_head_partial_floats(d.Hc, 1));
-    if (d.Hc == kWregN || d.Ha == kWregN) head = std::max(head, (int64_t)kFusedFwdTrainGrid * (kWregN * kActions + kActions));
+    if (split_net_supported(d.Ha)) head = std::max(head, split_net_partial_floats(d.Ha, kActions));
+    if (split_net_supported(d.Hc)) head = std::max(head, split_net_partial_floats(d.Hc, 1));
     v.partial_head = (float*)take(head * 4);
   } else {
     const int64_t SH = std::max(Sa * d.Ha, Sc * d.Hc);
@@ -109,91 +104,52 @@ int64_t pick_k_split(int64_t K, int64_t tiles_mn) {
   return per;
 }
 
-// Forward and loss of one 256-wide fp32 network with each layer's weights resident in registers: h1 goes to HBM,
-// the second hidden activation never does, `dz2` gets dL/d(pre-activation of layer 2), the output layer's gradient
-// and the loss statistics are accumulated.
-// The register-resident kernels pay for loading a whole weight matrix per workgroup (and for one round of atomics per
-// workgroup in the transposed product): they win from about four 64-row tiles per workgroup on, i.e. 65 536 rows on
-// 256 compute units (measured at the shape of workload 3: 16 384 rows 28.1 against 24.7 ms per step with the LDS-tiled
-// kernels, 65 536 rows equal, 262 144 rows 134 against 152 ms).
-inline bool wreg_worthwhile(int64_t S) { return S >= 256 * kWregBM * 4; }
-inline bool wreg_forward_supported(const RowSrc& X, int64_t S, int Din, int H) {
-  return H == kWregN && wreg_worthwhile(S) && wreg_gemm_supported<WREG_BIAS_TANH>(X, Din, H);
-}
-template <int NOUT, class LossFn>
-int32_t train_forward_wreg(const RowSrc& X, int64_t S, int Din, const float* W1, const float* b1, const float* W2,
-                           const float* b2, const float* W3, const float* b3, float* h1, float* dz2, float* gW3,
-                           float* gb3, float* stats, const LossFn& fn, float* partial3, hipStream_t s) {
-  {
-    WregArgs g{};
-    g.A = X; g.S = S; g.Kin = Din; g.B = W1; g.ldb = kWregN; g.b_kcont = 0; g.C = h1; g.bias = b1;
-    TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)S * Din * kWregN, s);
-    const int32_t rc = launch_wreg_gemm<WREG_BIAS_TANH>(g, s);
-    if (rc != MARL_OK) return rc;
+// gW [rows][H] += A^T B, gb += column sums of B.  The k splits go to split_ws and are added in a fixed order, where the workspace
+// has room and the bias gradient directly follows the weight gradient (its column sums ride along).
+void weight_gradient(const RowSrc& A, const float* B, int64_t S, int rows, int H, float* gW, float* gb, float* split_ws, int64_t split_floats, hipStream_t s) {
+  GemmArgs g{};
+  g.A = A; g.B = B; g.ldb = H; g.C = gW; g.ldc = H;
+  g.M = rows; g.N = H; g.K = S; g.colsum = gb;
+  g.k_per_split = pick_k_split(S, ((rows + 127) / 128) * ((H + 127) / 128));
+  const int64_t count = (int64_t)rows * H + H, nz = (g.K + g.k_per_split - 1) / g.k_per_split;
+  if (split_ws != nullptr && gb == gW + (int64_t)rows * H && nz * count <= split_floats) {
+    g.split_out = split_ws;
+    g.split_count = count;
   }
-  WregArgs g{};
-  g.A = RowSrc{h1, kWregN, nullptr, 1, S}; g.S = S; g.Kin = kWregN; g.B = W2; g.ldb = kWregN; g.b_kcont = 0; g.C = dz2;
-  g.bias = b2; g.W3 = W3; g.b3 = b3; g.gW3 = gW3; g.gb3 = gb3; g.stats = stats;
-  g.partial3 = partial3;  // (nullable) per-workgroup copies of the W3 / b3 gradient, added in a fixed order below
-  int32_t rc;
-  {
-    TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)S * kWregN * kWregN, s);
-    rc = launch_wreg_loss<NOUT>(g, fn, s);
-  }
-  if (rc == MARL_OK && partial3 != nullptr) {
-    const int64_t tiles = (S + kWregBM - 1) / kWregBM;
-    launch_reduce_partials(partial3, (int)std::min<int64_t>(tiles, 256), (int64_t)kWregN * NOUT + NOUT, gW3, s);
-  }
-  return rc;
+  if (launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s)) launch_reduce_partials(split_ws, (int)nz, count, gW, s);
 }
 
 // Backward through one network given dz2, the gradient of the second hidden layer's pre-activations.
-void mlp_backward(const RowSrc& X, int64_t S, int Din, int H, const float* W2, const float* h1, const float* dz2,
-                  float* dz1, float* gW1, float* gb1, float* gW2, float* gb2, bool bf16, float* wacc_partial, float* split_ws, int64_t split_floats, hipStream_t s) {
-  // a weight-gradient product writes its k splits to split_ws and has them added in a fixed order, where the workspace
-  // has room and the bias gradient directly follows the weight gradient (its column sums ride along)
-  auto split_launch = [&](GemmArgs& g, float* gW, float* gb, int64_t rows) {
-    const int64_t count = rows * H + H, nz = (g.K + g.k_per_split - 1) / g.k_per_split;
-    if (split_ws != nullptr && gb == gW + rows * H && nz * count <= split_floats) {
-      g.split_out = split_ws;
-      g.split_count = count;
-    }
-    if (launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s)) launch_reduce_partials(split_ws, (int)nz, count, gW, s);
-  };
-  {  // gW2 += h1^T dz2, gb2 += column sums
-    GemmArgs g{};
-    g.A = RowSrc{h1, H, nullptr, 1, S}; g.B = dz2; g.ldb = H; g.C = gW2; g.ldc = H;
-    g.M = H; g.N = H; g.K = S; g.colsum = gb2;
-    g.k_per_split = pick_k_split(S, ((H + 127) / 128) * ((H + 127) / 128));
-    split_launch(g, gW2, gb2, H);
+void mlp_backward(const RowSrc& X, int64_t S, int Din, int H, const float* W2, const float* h1, const float* dz2, float* dz1, float* grad,
+                  const NetOffsets& go, const UpdateWsView& w, hipStream_t s) {
+  weight_gradient(RowSrc{h1, H, nullptr, 1, S}, dz2, S, H, H, grad + go.W2, grad + go.b2, w.split_ws, w.split_floats, s);
+  GemmArgs g{};  // dz1 = (dz2 W2^T) * (1 - h1^2)
+  g.A = RowSrc{dz2, H, nullptr, 1, S}; g.B = W2; g.ldb = H; g.C = dz1; g.ldc = H;
+  g.aux_mat = h1; g.ldaux = H;
+  g.M = S; g.N = H; g.K = H;
+  launch_gemm<GEMM_NT, EPI_DTANH>(g, s);
+  weight_gradient(X, dz1, S, Din, H, grad + go.W1, grad + go.b1, w.split_ws, w.split_floats, s);
+}
+
+// Forward, loss and backward of one fp32 network whose row tiles go through it in one kernel.
+template <int NOUT, class LossFn>
+int32_t train_net_split(const RowSrc& X, int64_t S, int Din, int H, const float* eff, const ParamMap& pm, int net, float* grad, const NetOffsets& go,
+                        const LossFn& fn, const UpdateWsView& w, float* h1, float* dz2, float* dz1, hipStream_t s) {
+  const NetOffsets o = padded_offsets(pm, net);
+  SplitNetArgs a{};
+  a.X = X; a.S = S; a.Din = Din; a.Kp = pm.kpad1[net]; a.W = eff + pm.sw_w1[net];
+  a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
+  a.h1 = h1; a.dz2 = dz2; a.dz1 = dz1; a.partial = w.partial_head;
+  unsigned grid = 0;
+  {
+    TimedLaunch timed(KC_FUSED_TRAIN, 2.0 * (double)S * ((double)Din * H + 2.0 * (double)H * H), s);
+    const int32_t rc = launch_split_net_rows<kSplitTrainRows, NOUT, true>(H, a, fn, &grid, s);
+    if (rc != MARL_OK) return rc;
   }
-  const RowSrc dz2_rows{dz2, H, nullptr, 1, S};
-  if (!bf16 && wreg_worthwhile(S) && wreg_gemm_supported<WREG_DTANH>(dz2_rows, H, H)) {
-    // dz1 = (dz2 W2^T) * (1 - h1^2) with W2 resident in registers
-    WregArgs g{};
-    g.A = dz2_rows; g.S = S; g.Kin = H; g.B = W2; g.ldb = H; g.b_kcont = 1; g.C = dz1; g.aux = h1;
-    TimedLaunch timed(KC_GEMM_NT, 2.0 * (double)S * H * H, s);
-    launch_wreg_gemm<WREG_DTANH>(g, s);
-  } else {  // dz1 = (dz2 W2^T) * (1 - h1^2), gb1 += column sums
-    GemmArgs g{};
-    g.A = RowSrc{dz2, H, nullptr, 1, S}; g.B = W2; g.ldb = H; g.C = dz1; g.ldc = H;
-    g.aux_mat = h1; g.ldaux = H; g.colsum = nullptr;
-    g.M = S; g.N = H; g.K = H; g.round_bf16 = bf16;
-    launch_gemm<GEMM_NT, EPI_DTANH>(g, s);
-  }
-  if (!bf16 && wreg_worthwhile(S) && wacc_gemm_supported(X, Din, H)) {  // gW1 += X^T dz1, gb1 += column sums, the gradient resident in registers
-    WaccArgs g{};
-    g.A = X; g.S = S; g.B = dz1; g.C = gW1; g.colsum = gb1;
-    g.partial = (gb1 == gW1 + (int64_t)Din * H) ? wacc_partial : nullptr;  // the bias gradient directly follows the weight gradient
-    TimedLaunch timed(KC_GEMM_TN, 2.0 * (double)S * Din * H, s);
-    launch_wacc_gemm(g, Din, s);
-  } else {  // gW1 += X^T dz1
-    GemmArgs g{};
-    g.A = X; g.B = dz1; g.ldb = H; g.C = gW1; g.ldc = H;
-    g.M = Din; g.N = H; g.K = S; g.colsum = gb1;
-    g.k_per_split = pick_k_split(S, ((Din + 127) / 128) * ((H + 127) / 128));
-    split_launch(g, gW1, gb1, Din);
-  }
+  launch_reduce_partials(w.partial_head, (int)grid, (int64_t)H * NOUT + NOUT + 5, grad + go.W3, s, (int64_t)H * NOUT + NOUT, w.sc->acc);
+  weight_gradient(RowSrc{h1, H, nullptr, 1, S}, dz2, S, H, H, grad + go.W2, grad + go.b2, w.split_ws, w.split_floats, s);
+  weight_gradient(X, dz1, S, Din, H, grad + go.W1, grad + go.b1, w.split_ws, w.split_floats, s);
+  return launch_status();
 }
 
 // Forward, loss and backward of one network in the bf16 configuration.
@@ -301,7 +257,6 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
         if (rc != MARL_OK) return rc;
       }
       // ---- actor
-      const bool fused_a = fused_forward_supported(d.Ha, d.D);
       if (!pair) {
         ActorLoss fn{lc, tr.action, tr.logp, tr.adv};
         if (d.bf16) {
@@ -317,29 +272,18 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
           ta.partial = w.partial; ta.gcount = d.Pa;
           const int32_t rc = launch_fused_train<kActions>(d.Ha, ta, fn, s);
           if (rc != MARL_OK) return rc;
+        } else if (split_net_supported(d.Ha)) {
+          const int32_t rc = train_net_split<kActions>(Xa, Sa, d.D, d.Ha, eff, pm, 0, w.grad, ga, fn, wk, w.h1a, w.h2a, w.dz1a, s);
+          if (rc != MARL_OK) return rc;
         } else {
-          if (fused_a) {
-            FusedFwdArgs fa{};
-            fa.X = Xa; fa.S = Sa; fa.Din = d.D; fa.xvec = aligned16(Xa.base) && Xa.ld % 4 == 0 && d.D % 4 == 0;
-            fa.W1 = eff + oa.W1; fa.b1 = eff + oa.b1; fa.W2 = eff + oa.W2; fa.b2 = eff + oa.b2; fa.W3 = eff + oa.W3;
-            fa.b3 = eff + oa.b3; fa.h1_out = w.h1a; fa.dz2_out = w.h2a; fa.gW3 = w.grad + ga.W3; fa.gb3 = w.grad + ga.b3;
-            fa.stats = sck->acc;
-            fa.partial3 = ga.b3 == ga.W3 + (int64_t)d.Ha * kActions ? w.partial_head : nullptr;
-            fa.W1s = eff + pm.sw_w1[0]; fa.W2s = eff + pm.sw_w2[0]; fa.kpad1 = pm.kpad1[0]; fa.px = fused_forward_px(d.D);
-            const int32_t rc = launch_fused_forward<kActions, true>(d.Ha, fa, fn, s);
-            if (rc != MARL_OK) return rc;
-          } else {
-            mlp_hidden_forward(Xa, Sa, d.D, d.Ha, eff + oa.W1, eff + oa.b1, eff + oa.W2, eff + oa.b2, w.h1a, w.h2a, d.bf16, s);
-            const int32_t rc = launch_loss_head<kActions, true>(w.h2a, Sa, d.Ha, eff + oa.W3, eff + oa.b3, fn, nullptr, w.grad + ga.W3,
-                                                          w.partial_head, sck, s);
-            if (rc != MARL_OK) return rc;
-          }
-          mlp_backward(Xa, Sa, d.D, d.Ha, eff + oa.W2, w.h1a, w.h2a, w.dz1a, w.grad + ga.W1, w.grad + ga.b1, w.grad + ga.W2,
-                       w.grad + ga.b2, d.bf16, nullptr, w.split_ws, w.split_floats, s);
+          mlp_hidden_forward(Xa, Sa, d.D, d.Ha, eff + oa.W1, eff + oa.b1, eff + oa.W2, eff + oa.b2, w.h1a, w.h2a, s);
+          const int32_t rc = launch_loss_head<kActions, true>(w.h2a, Sa, d.Ha, eff + oa.W3, eff + oa.b3, fn, nullptr, w.grad + ga.W3,
+                                                              w.partial_head, sck, s);
+          if (rc != MARL_OK) return rc;
+          mlp_backward(Xa, Sa, d.D, d.Ha, eff + oa.W2, w.h1a, w.h2a, w.dz1a, w.grad, ga, wk, s);
         }
       }
       // ---- critic
-      const bool fused_c = fused_forward_supported(d.Hc, d.Dc);
       if (!pair) {
         CriticLoss fn{lc, tr.ret, tr.value, d.central ? d.A : 1};
         if (d.bf16) {
@@ -355,31 +299,15 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
           ta.partial = w.partial; ta.gcount = d.P - d.Pa;
           const int32_t rc = launch_fused_train<1>(d.Hc, ta, fn, s);
           if (rc != MARL_OK) return rc;
+        } else if (split_net_supported(d.Hc)) {
+          const int32_t rc = train_net_split<1>(Xc, Sc, d.Dc, d.Hc, eff, pm, 1, w.grad, gc, fn, wk, w.h1c, w.h2c, w.dz1c, s);
+          if (rc != MARL_OK) return rc;
         } else {
-          if (wreg_forward_supported(Xc, Sc, d.Dc, d.Hc)) {
-            const int32_t rc = train_forward_wreg<1>(Xc, Sc, d.Dc, eff + oc.W1, eff + oc.b1, eff + oc.W2, eff + oc.b2,
-                                                     eff + oc.W3, eff + oc.b3, w.h1c, w.h2c, w.grad + gc.W3,
-                                                     w.grad + gc.b3, sck->acc, fn,
-                                                     gc.b3 == gc.W3 + (int64_t)kWregN ? w.partial_head : nullptr, s);
-            if (rc != MARL_OK) return rc;
-          } else if (fused_c) {
-            FusedFwdArgs fa{};
-            fa.X = Xc; fa.S = Sc; fa.Din = d.Dc; fa.xvec = aligned16(Xc.base) && Xc.ld % 4 == 0 && d.Dc % 4 == 0;
-            fa.W1 = eff + oc.W1; fa.b1 = eff + oc.b1; fa.W2 = eff + oc.W2; fa.b2 = eff + oc.b2; fa.W3 = eff + oc.W3;
-            fa.b3 = eff + oc.b3; fa.h1_out = w.h1c; fa.dz2_out = w.h2c; fa.gW3 = w.grad + gc.W3; fa.gb3 = w.grad + gc.b3;
-            fa.stats = sck->acc;
-            fa.partial3 = gc.b3 == gc.W3 + (int64_t)d.Hc ? w.partial_head : nullptr;
-            fa.W1s = eff + pm.sw_w1[1]; fa.W2s = eff + pm.sw_w2[1]; fa.kpad1 = pm.kpad1[1]; fa.px = fused_forward_px(d.Dc);
-            const int32_t rc = launch_fused_forward<1, true>(d.Hc, fa, fn, s);
-            if (rc != MARL_OK) return rc;
-          } else {
-            mlp_hidden_forward(Xc, Sc, d.Dc, d.Hc, eff + oc.W1, eff + oc.b1, eff + oc.W2, eff + oc.b2, w.h1c, w.h2c, d.bf16, s);
-            const int32_t rc = launch_loss_head<1, true>(w.h2c, Sc, d.Hc, eff + oc.W3, eff + oc.b3, fn, nullptr, w.grad + gc.W3,
-                                                   w.partial_head, sck, s);
-            if (rc != MARL_OK) return rc;
-          }
-          mlp_backward(Xc, Sc, d.Dc, d.Hc, eff + oc.W2, w.h1c, w.h2c, w.dz1c, w.grad + gc.W1, w.grad + gc.b1, w.grad + gc.W2,
-                       w.grad + gc.b2, d.bf16, w.partial_w1, w.split_ws, w.split_floats, s);
+          mlp_hidden_forward(Xc, Sc, d.Dc, d.Hc, eff + oc.W1, eff + oc.b1, eff + oc.W2, eff + oc.b2, w.h1c, w.h2c, s);
+          const int32_t rc = launch_loss_head<1, true>(w.h2c, Sc, d.Hc, eff + oc.W3, eff + oc.b3, fn, nullptr, w.grad + gc.W3,
+                                                       w.partial_head, sck, s);
+          if (rc != MARL_OK) return rc;
+          mlp_backward(Xc, Sc, d.Dc, d.Hc, eff + oc.W2, w.h1c, w.h2c, w.dz1c, w.grad, gc, wk, s);
         }
       }
       // ---- clip + Adam
