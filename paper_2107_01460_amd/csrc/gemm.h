@@ -280,11 +280,11 @@ template <int MODE, int EPI, int BM, int BN, bool AVEC>
 __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   constexpr int BK = kGemmBK;
   constexpr int WM = BM == 128 ? 2 : 1, WN = 4 / WM, TM = BM / (32 * WM), TN = BN / (32 * WN);
-  static_assert(TM >= 1 && TN >= 1 && (BM == 128 || BM == 32), "wavefront tiles");
+  static_assert(TM >= 1 && TN >= 1 && (BM == 128 || MODE == GEMM_TN), "wavefront tiles");
   constexpr bool A_KCONT = (MODE != GEMM_TN);  // A tile stored [m][k] else [k][m]
   constexpr bool B_KCONT = (MODE == GEMM_NT);  // B tile stored [n][k] else [k][n]
   constexpr int PK = BK + 8;
-  constexpr int PMA = BM == 32 ? 32 : BM + 32, PNB = BN + 32;  // rows 16 or 48 banks apart
+  constexpr int PMA = BM % 64 == 32 ? BM : BM + 32, PNB = BN + 32;  // rows 16 or 48 banks apart
   constexpr int A_PLANE = A_KCONT ? BM * PK : BK * PMA, B_PLANE = B_KCONT ? BN * PK : BK * PNB;
   constexpr int A_VECS = BK * BM / 4 / 256, B_VECS = BK * BN / 4 / 256;  // 16-byte pieces a thread stages
   static_assert(A_VECS >= 1 && B_VECS >= 1, "every thread stages");
@@ -522,6 +522,28 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Rows of an output tile of a TN product of M x N: the tile that leaves the least padding (rows of a first-layer gradient are an
+// input width: 75 take 96 instead of 128, 147 160 instead of 256, 27 32; all but 128 rows go with 128 columns).  50 000 samples, 256
+// outputs: 147 rows 53 -> 43 us; 98 304 samples, 128 outputs, 75 rows 60 -> 50 us; 262 144 samples, 256 outputs, 300 rows 335 us (its
+// gradient resident in the accumulators, fp32 instruction) -> 250 us.  (Requesting a k tile two tiles ahead instead of one changed
+// nothing at 128 columns and cost 40 % at 64: the loads are not what a k tile waits for.)
+inline int gemm_tn_rows(int64_t M, int64_t N) {
+  auto padded = [](int64_t n, int64_t tile) { return (n + tile - 1) / tile * tile; };
+  int best = 128;
+  int64_t least = padded(M, 128) * padded(N, N % 128 == 0 ? 128 : 64);
+  for (int bm : {160, 96, 32})
+    if (padded(M, bm) * padded(N, 128) < least) {
+      best = bm;
+      least = padded(M, bm) * padded(N, 128);
+    }
+  return best;
+}
+// Output tiles of it
+inline int64_t gemm_tn_tiles(int64_t M, int64_t N) {
+  const int bm = gemm_tn_rows(M, N);
+  return ((M + bm - 1) / bm) * ((N + 127) / 128);
+}
+
 // Host-side dispatch.  Every caller's N is a hidden width or three of them (a multiple of 32), its B 16-byte aligned with
 // a row pitch that keeps it so; A may start and step at any 4-byte boundary.
 // Returns true when the launch wrote its k splits to g.split_out (false: it added to C / colsum directly).
@@ -541,8 +563,11 @@ inline bool launch_gemm(const GemmArgs& g_in, hipStream_t s) {
   const bool avec = aligned16(g.A.base) && g.A.ld % 4 == 0 && (MODE == GEMM_TN ? M % 4 == 0 : g.K % 4 == 0);
   if (!(MODE == GEMM_TN && EPI == EPI_ATOMIC_ADD && g.ldc == N && N % 4 == 0)) g.split_out = nullptr;
   if constexpr (MODE == GEMM_TN) {
-    if (M <= 32) {  // first-layer gradient of narrow observations: a 128-row tile would be three quarters padding
-      launch_gemm_inst<MODE, EPI, 32, 128>(g, avec, s);
+    const int bm = gemm_tn_rows(M, N);
+    if (bm != 128) {
+      if (bm == 32) launch_gemm_inst<MODE, EPI, 32, 128>(g, avec, s);
+      else if (bm == 96) launch_gemm_inst<MODE, EPI, 96, 128>(g, avec, s);
+      else launch_gemm_inst<MODE, EPI, 160, 128>(g, avec, s);
       return g.split_out != nullptr;
     }
   }

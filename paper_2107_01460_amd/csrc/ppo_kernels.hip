@@ -42,7 +42,7 @@ int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 int64_t split_want(int64_t tiles_mn) { return std::max<int64_t>(1, 512 / std::max<int64_t>(1, tiles_mn)); }
 // floats of workspace for the k splits of dW2 (H x H + H) and dW1 (Din x H + H) of one layer-by-layer network
 int64_t split_ws_floats(int H, int Din) {
-  const int64_t t2 = ((H + 127) / 128) * ((H + 127) / 128), t1 = ((Din + 127) / 128) * ((H + 127) / 128);
+  const int64_t t2 = gemm_tn_tiles(H, H), t1 = gemm_tn_tiles(Din, H);
   return std::max(split_want(t2) * ((int64_t)H * H + H), split_want(t1) * ((int64_t)Din * H + H));
 }
 
@@ -110,7 +110,7 @@ void weight_gradient(const RowSrc& A, const float* B, int64_t S, int rows, int H
   GemmArgs g{};
   g.A = A; g.B = B; g.ldb = H; g.C = gW; g.ldc = H;
   g.M = rows; g.N = H; g.K = S; g.colsum = gb;
-  g.k_per_split = pick_k_split(S, ((rows + 127) / 128) * ((H + 127) / 128));
+  g.k_per_split = pick_k_split(S, gemm_tn_tiles(rows, H));
   const int64_t count = (int64_t)rows * H + H, nz = (g.K + g.k_per_split - 1) / g.k_per_split;
   if (split_ws != nullptr && gb == gW + (int64_t)rows * H && nz * count <= split_floats) {
     g.split_out = split_ws;

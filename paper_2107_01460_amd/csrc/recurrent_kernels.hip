@@ -186,7 +186,7 @@ unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 // Splits of a weight gradient's sum over the samples: two workgroups per CU, k ranges in multiples of the k tile.  Every
 // split stores its own copy and the copies are added in a fixed order; at 98 304 samples, 128 x 384 outputs: 341 splits
 // adding with atomics 186 us, 170 copies 70 us.
-int64_t split_want(int M, int N) { return std::max<int64_t>(1, 512 / (((M + 127) / 128) * ((N + 127) / 128))); }
+int64_t split_want(int M, int N) { return std::max<int64_t>(1, 512 / gemm_tn_tiles(M, N)); }
 int64_t split_floats(int M, int N) { return split_want(M, N) * ((int64_t)M * N + N); }
 
 // gW [M][N] += A^T B over K samples, the column sums of B (the bias gradient) directly behind it

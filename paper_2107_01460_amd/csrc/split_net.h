@@ -3,6 +3,16 @@
 // epilogue that produces them); the split weights stream from the L2 in one sequence of k steps that runs on from layer to layer
 // and from tile to tile.  In training the kernel also takes the loss, the output layer's gradient and the gradients of both
 // hidden layers' pre-activations; h1 and h2 stay in registers for them, h1, dz2 and dz1 go to memory for the weight gradients.
+//
+// Measured on an MI355X.  Minibatch of 262 144 samples, 300 inputs, 256 units, one output, everything but the weight gradients:
+// 347 + 331 + 297 us as three kernels with the weights resident in registers, on the fp32 instruction -> 707 us here; 50 000 samples,
+// 147 inputs: 256 units, six outputs 143 + 64 (32-row tiles, then dz1 as a product of its own) -> 143 us, 192 units, one output 42 + 38
+// + 30 + 38 (layer by layer) -> 109 us.  Training iterations: 1000 environments, 256 / 192 units 15.8 -> 12.4 ms; 16 384 environments,
+// central critic of 256 units 96.7 -> 92.2 ms.
+// Bound: the weights' way from the L2 -- 1.28 MB per tile of 32 rows and 256 units, read at about 15 TB/s by the whole chip, which
+// two workgroups per CU keep going through each other's phases.  64-row tiles halve the bytes, but only one workgroup fits a CU and
+// its phases without products (tanh, loss, gradients: 37 of 81 thousand cycles) leave the L2 idle: 718 us at the first of these sizes,
+// 160 and 126 us at the others.  Forward passes of many samples hold less and take the 64-row tiles.
 #pragma once
 #include <type_traits>
 
@@ -51,9 +61,11 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
   constexpr int XR = (BM / 2 + NW - 1) / NW;               // pairs of input rows a wavefront stages
   constexpr int GPW = (BM / 16 + NW - 1) / NW;             // groups of 16 samples whose outputs a wavefront takes
   constexpr int W3P = NOUT > 1 ? 8 : 1;
-  // forward passes: the next tile's first piece of input waits in registers, and exact inputs take half of layer 1's products (in
-  // training the CU's other workgroup covers the input's latency, and the registers are wanted for two workgroups)
-  constexpr bool AHEAD = !TRAIN && H > 128 && NW <= 8, EXACT_X = !TRAIN;
+  // Forward passes above 128 units: the next tile's first piece of input waits in registers, and exact inputs take half of layer 1's
+  // products (2.1 million samples, 300 inputs, 256 units: 3.61 -> 2.99 ms).  In training and in narrow networks other workgroups of the
+  // CU cover the input's latency, and the registers are wanted for them (16.9 million samples, 27 inputs, 64 units: 2.23 ms with the
+  // second form of layer 1, 2.06 without).
+  constexpr bool AHEAD = !TRAIN && H > 128 && NW <= 8, EXACT_X = !TRAIN && H > 128;
   extern __shared__ __attribute__((aligned(16))) bf16_t split_net_lds[];
   bf16_t* const tile = split_net_lds;                            // [3][BM][P] X, h1, h2, dz2
   bf16_t* const w3t = tile + 3 * PLANE;                          // [3][8][P]  W3 transposed, split, rows past NOUT zero
@@ -480,6 +492,7 @@ inline int32_t launch_split_net_rows(int H, const SplitNetArgs& a, const Fin& fi
 }
 
 // forward pass; what becomes of the outputs is fin's business
+// Tiles of 32 rows below one 64-row tile per CU; the same bits in both.
 constexpr int64_t kSplitSmallRows = 16384;
 template <int NOUT, class Fin>
 inline int32_t launch_split_forward(int H, const SplitNetArgs& a, const Fin& fin, hipStream_t s) {
