@@ -24,16 +24,15 @@ import numpy as np  # noqa: E402
 ORACLE_SAMPLE_ENVS = {1: 64, 2: 64, 3: 48, 4: 2, 5: 2048}
 ORACLE_MAX_PROCS = 16          # the CPU share of a one-GPU machine, whatever the affinity mask shows
 # TFLOP/s, TFLOP/s, TFLOP/s, GB/s.  mfma_f32_split: fp32 products as six bf16 products (csrc/split_bf16.h), which is how the
-# training and GEMM kernels of the fp32 workloads run; the rollout kernel and the register-resident critic kernels of
-# workload 3 (part of the gemm classes there) run on the fp32 instruction.
+# training and GEMM kernels of the fp32 workloads run; the rollout kernel runs on the fp32 instruction.
 PEAK = {"mfma_f32": 157.3, "mfma_f32_split": 2500.0 / 6, "mfma_bf16": 2500.0, "hbm": 8000.0}
 # (timed steps, warm-up steps) of the short runs of the other workloads in the default invocation
 SIDE_RUNS = {1: (300, 30), 2: (30, 4), 3: (8, 2), 4: (4, 1), 5: (20, 3)}
 # rocprofv3 PMC summaries (FETCH_SIZE / WRITE_SIZE per launch, scaled by a plain copy of known size) by workload, and
-# the kernel-name prefix of each timed kernel class in them
+# a pattern of the kernel names of each timed kernel class in them
 PMC_PROFILE = {"c3_15x15_4ag_mappo": "profiles/bench_c3_pmc_hbm_traffic.txt",
                "c5_8x8_2ag_ippo_wide": "profiles/bench_c5_pmc_hbm_traffic.txt"}
-CLASS_KERNEL = {"fused_train": "fused_train_kernel<", "env_step": "env_step_kernel<", "gae": "gae_kernel",
+CLASS_KERNEL = {"fused_train": r"fused_train_kernel<|split_net_kernel<\d+, \d+, \d+, true", "env_step": "env_step_kernel<", "gae": "gae_kernel",
                 "rollout": "rollout_train_kernel<"}
 
 
@@ -57,26 +56,27 @@ def gemm_flops_per_step(cfg, W):
 
 
 def pmc_traffic(cfg_name, kernel_class):
-    """HBM bytes per launch (read + write) of a kernel class from the committed rocprofv3 PMC summary of the workload.
+    """HBM bytes per launch (read + write; the average of its kernels' launches) of a kernel class from the committed rocprofv3 PMC
+    summary of the workload.
     None when the workload or the class has no summary; an error when the summary exists but does not list the kernel
     (the profile no longer describes the build)."""
-    path, prefix = PMC_PROFILE.get(cfg_name), CLASS_KERNEL.get(kernel_class)
-    if path is None or prefix is None:
+    path, pattern = PMC_PROFILE.get(cfg_name), CLASS_KERNEL.get(kernel_class)
+    if path is None or pattern is None:
         return None, None
     full = os.path.join(ROOT, path)
     if not os.path.exists(full):
         raise RuntimeError(f"{path} is missing: bench.py quotes its HBM traffic figures")
-    best = None
+    launches, total = 0, 0.0
     for ln in open(full):
-        if ln.startswith(prefix):
+        if re.match(pattern, ln):
             mb = re.findall(r"->\s+([0-9.]+) MB", ln)
             n = re.search(r"\bn=\s*(\d+)", ln)
             if len(mb) == 2 and n:
-                cand = (int(n.group(1)), (float(mb[0]) + float(mb[1])) * 1e6)
-                best = cand if best is None or cand[0] > best[0] else best   # the instantiation launched most often
-    if best is None:
-        raise RuntimeError(f"{path} lists no kernel named {prefix}...: refresh the profile for this build")
-    return best[1], path
+                launches += int(n.group(1))
+                total += int(n.group(1)) * (float(mb[0]) + float(mb[1])) * 1e6
+    if launches == 0:
+        raise RuntimeError(f"{path} lists no kernel named {pattern}...: refresh the profile for this build")
+    return total / launches, path
 
 
 # ---- CPU oracle beside it ---------------------------------------------------------------------------------------------

@@ -42,7 +42,7 @@ def one_run(M, cfg, params0, perm):
     return snaps, p.cpu().numpy(), m.cpu().numpy(), v.cpu().numpy(), stats.cpu().numpy()
 
 
-# (3, 8192): 65 536 critic rows per minibatch, the size from which the 256-wide critic takes its register-resident kernels
+# (3, 8192): 65 536 critic rows per minibatch, more tiles than the critic's training kernel has workgroups
 @pytest.mark.parametrize("k,exact,n_envs", [(2, True, 1024), (3, True, 512), (3, True, 8192), (4, False, 96), (1, True, 700),
                                             (5, True, 3000)])
 def test_two_runs_agree(k, exact, n_envs):

@@ -151,8 +151,8 @@ def tiled_perm(cfg_full, cfg_small, perm_small, seed):
     return out
 
 
-# The last case is workload 3 at 4097 = 17 x 241 environments: minibatches of 65 552 rows, the smallest size at which
-# the update takes the register-resident critic kernels, with a ragged last tile (65 552 = 1024 x 64 + 16).
+# The last case is workload 3 at 4097 = 17 x 241 environments: critic minibatches of 65 552 rows, a ragged last tile
+# (65 552 = 2048 x 32 + 16).
 @pytest.mark.parametrize("k,n_envs,tile", [(1, None, None), (2, None, None), (3, None, None), (4, None, None),
                                            (5, None, None), (3, 4097, 17)])
 def test_full_size_ppo_update_tiled(M, orc, k, n_envs, tile):
