@@ -482,15 +482,24 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
     }
   }
 
-  // Epilogue (accumulator register r of a lane holds C[8*(r/4) + 4*hi + r%4][lo] of its 32x32 tile).
+  // Epilogue (accumulator register r of a lane holds C[8*(r/4) + 4*hi + r%4][lo] of its 32x32 tile).  The biases arrive before the first
+  // store: a load that is waited for between the stores waits for all stores before it, and the compiler moves the loads and the
+  // arithmetic to where a row is stored (98 304 samples, 128 x 384 with a bias: 98 -> 76 us; 75 x 128 with tanh: 53 -> 38 us).
+  float bias[TN];
+#pragma unroll
+  for (int jn = 0; jn < TN; ++jn) {
+    bias[jn] = 0.f;
+    if (EPI == EPI_BIAS_TANH || (EPI == EPI_STORE && g.aux_vec != nullptr)) bias[jn] = g.aux_vec[min(n0 + wn * (BN / WN) + jn * 32 + lo, g.N - 1)];
+  }
+  if (EPI == EPI_BIAS_TANH || EPI == EPI_STORE) {
+#pragma unroll
+    for (int jn = 0; jn < TN; ++jn) asm volatile("" : "+v"(bias[jn]));
+  }
 #pragma unroll
   for (int jn = 0; jn < TN; ++jn) {
     const int64_t n = n0 + wn * (BN / WN) + jn * 32 + lo;
     if (n0 + wn * (BN / WN) + jn * 32 >= g.N) continue;  // uniform per wavefront: N is a multiple of 32
     const int64_t nd = MODE == GEMM_TN && n + g.c_rot >= g.N ? n + g.c_rot - g.N : (MODE == GEMM_TN ? n + g.c_rot : n);
-    float bias = 0.f;
-    if (EPI == EPI_BIAS_TANH) bias = g.aux_vec[n];
-    if (EPI == EPI_STORE && g.aux_vec != nullptr) bias = g.aux_vec[n];
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int64_t mb = m0 + wm * (BM / WM) + i * 32 + 4 * hi;
@@ -504,11 +513,11 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
         const int64_t m = mb + 8 * (r / 4) + (r % 4);
         float v = acc[i][jn][r];
         if (EPI == EPI_BIAS_TANH) {
-          v = tanh_f32(v + bias);
+          v = tanh_f32(v + bias[jn]);
         } else if (EPI == EPI_DTANH) {
           v = v * (1.0f - h[r] * h[r]);
         } else if (EPI == EPI_STORE) {
-          v += bias;
+          v += bias[jn];
         }
         if (m < g.M) {
           if (EPI != EPI_ATOMIC_ADD) g.C[m * g.ldc + n] = v;
