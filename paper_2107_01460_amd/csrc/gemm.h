@@ -11,6 +11,7 @@
 
 #include "common.h"
 #include "split_bf16.h"
+#include "tn_plan.h"
 
 namespace marl {
 
@@ -89,7 +90,7 @@ struct GemmArgs {
   int64_t ldaux;
   float* colsum;         // TN: column sums of B are added here ([N], atomic), nullable
   int64_t M, N, K;
-  int64_t k_per_split;   // TN: k range of one blockIdx.z
+  int64_t k_per_split;   // TN: samples of a k range (launch_gemm fills it in, from tn_plan)
   int c_rot;             // TN, multiple of 32 below N: column n of the product goes to column (n + c_rot) mod N of C and colsum
   // TN with EPI_ATOMIC_ADD, nullable: k split z stores its products at split_out + z * split_count + m * ldc + n and its
   // column sums of B behind them (at + M * ldc + n) with plain stores instead of adding to C / colsum with atomics; the
@@ -263,7 +264,6 @@ __device__ __forceinline__ void gemm_phase_direct(const float* __restrict__ As, 
   }
 }
 
-constexpr int kGemmBK = 32;  // k per stage: two steps of the matrix instruction
 
 // BM x BN tile, four wavefronts (2 x 2 at BM = 128, side by side at BM = 32), k tiles of 32 in one LDS buffer of split
 // operands; the next k tile travels global -> registers while the current one is multiplied, and two workgroups per CU
@@ -531,28 +531,6 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Rows of an output tile of a TN product of M x N: the tile that leaves the least padding (rows of a first-layer gradient are an
-// input width: 75 take 96 instead of 128, 147 160 instead of 256, 27 32; all but 128 rows go with 128 columns).  50 000 samples, 256
-// outputs: 147 rows 53 -> 43 us; 98 304 samples, 128 outputs, 75 rows 60 -> 50 us; 262 144 samples, 256 outputs, 300 rows 335 us (its
-// gradient resident in the accumulators, fp32 instruction) -> 250 us.  (Requesting a k tile two tiles ahead instead of one changed
-// nothing at 128 columns and cost 40 % at 64: the loads are not what a k tile waits for.)
-inline int gemm_tn_rows(int64_t M, int64_t N) {
-  auto padded = [](int64_t n, int64_t tile) { return (n + tile - 1) / tile * tile; };
-  int best = 128;
-  int64_t least = padded(M, 128) * padded(N, N % 128 == 0 ? 128 : 64);
-  for (int bm : {160, 96, 32})
-    if (padded(M, bm) * padded(N, 128) < least) {
-      best = bm;
-      least = padded(M, bm) * padded(N, 128);
-    }
-  return best;
-}
-// Output tiles of it
-inline int64_t gemm_tn_tiles(int64_t M, int64_t N) {
-  const int bm = gemm_tn_rows(M, N);
-  return ((M + bm - 1) / bm) * ((N + 127) / 128);
-}
-
 // Host-side dispatch.  Every caller's N is a hidden width or three of them (a multiple of 32), its B 16-byte aligned with
 // a row pitch that keeps it so; A may start and step at any 4-byte boundary.
 // Returns true when the launch wrote its k splits to g.split_out (false: it added to C / colsum directly).
@@ -572,13 +550,14 @@ inline bool launch_gemm(const GemmArgs& g_in, hipStream_t s) {
   const bool avec = aligned16(g.A.base) && g.A.ld % 4 == 0 && (MODE == GEMM_TN ? M % 4 == 0 : g.K % 4 == 0);
   if (!(MODE == GEMM_TN && EPI == EPI_ATOMIC_ADD && g.ldc == N && N % 4 == 0)) g.split_out = nullptr;
   if constexpr (MODE == GEMM_TN) {
-    const int bm = gemm_tn_rows(M, N);
-    if (bm != 128) {
-      if (bm == 32) launch_gemm_inst<MODE, EPI, 32, 128>(g, avec, s);
-      else if (bm == 96) launch_gemm_inst<MODE, EPI, 96, 128>(g, avec, s);
-      else launch_gemm_inst<MODE, EPI, 160, 128>(g, avec, s);
-      return g.split_out != nullptr;
-    }
+    const TnPlan p = tn_plan(M, N, g.K);
+    g.k_per_split = p.per;
+    if (p.bm == 32) launch_gemm_inst<MODE, EPI, 32, 128>(g, avec, s);
+    else if (p.bm == 96) launch_gemm_inst<MODE, EPI, 96, 128>(g, avec, s);
+    else if (p.bm == 160) launch_gemm_inst<MODE, EPI, 160, 128>(g, avec, s);
+    else if (p.bn == 128) launch_gemm_inst<MODE, EPI, 128, 128>(g, avec, s);
+    else launch_gemm_inst<MODE, EPI, 128, 64>(g, avec, s);
+    return g.split_out != nullptr;
   }
   // 64 columns where 128 would leave a half-empty last tile
   if (N % 128 == 0) launch_gemm_inst<MODE, EPI, 128, 128>(g, avec, s);

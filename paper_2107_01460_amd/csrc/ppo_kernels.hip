@@ -39,12 +39,8 @@ struct UpdateWsView {
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
-int64_t split_want(int64_t tiles_mn) { return std::max<int64_t>(1, 512 / std::max<int64_t>(1, tiles_mn)); }
-// floats of workspace for the k splits of dW2 (H x H + H) and dW1 (Din x H + H) of one layer-by-layer network
-int64_t split_ws_floats(int H, int Din) {
-  const int64_t t2 = gemm_tn_tiles(H, H), t1 = gemm_tn_tiles(Din, H);
-  return std::max(split_want(t2) * ((int64_t)H * H + H), split_want(t1) * ((int64_t)Din * H + H));
-}
+// floats of workspace for the k splits of dW2 (H x H + H) and dW1 (Din x H + H) of one layer-by-layer network of S samples
+int64_t split_ws_floats(int H, int Din, int64_t S) { return std::max(tn_copy_floats(H, H, S), tn_copy_floats(Din, H, S)); }
 
 UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
   const Dims d = dims_of(c);
@@ -74,10 +70,10 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
     if (fused_train_supported(d.Ha, d.D)) pmax = std::max<int64_t>(pmax, d.Pa);
     if (fused_train_supported(d.Hc, d.Dc)) pmax = std::max<int64_t>(pmax, d.P - d.Pa);
     v.partial = pmax > 0 ? (float*)take((int64_t)kFusedTrainMaxGrid * pmax * 4) : nullptr;
-    // the k splits of the layer-by-layer weight gradients (at most `want` splits of pick_k_split per product)
+    // the k splits of the weight gradients that are products of their own
     v.split_floats = 0;
-    if (!fused_train_supported(d.Ha, d.D)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Ha, d.D));
-    if (!fused_train_supported(d.Hc, d.Dc)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Hc, d.Dc));
+    if (!fused_train_supported(d.Ha, d.D)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Ha, d.D, Sa));
+    if (!fused_train_supported(d.Hc, d.Dc)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Hc, d.Dc, Sc));
     v.split_ws = v.split_floats > 0 ? (float*)take(v.split_floats * 4) : nullptr;
     int64_t head = std::max(loss_head_partial_floats(d.Ha, kActions), loss_head_partial_floats(d.Hc, 1));
     if (split_net_supported(d.Ha)) head = std::max(head, split_net_partial_floats(d.Ha, kActions));
@@ -96,22 +92,13 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
   return v;
 }
 
-int64_t pick_k_split(int64_t K, int64_t tiles_mn) {
-  // enough workgroups for two per CU, each with a k range that is a multiple of the k tile
-  int64_t want = split_want(tiles_mn);
-  int64_t per = (K + want - 1) / want;
-  per = std::max<int64_t>(256, ((per + kGemmBK - 1) / kGemmBK) * kGemmBK);
-  return per;
-}
-
 // gW [rows][H] += A^T B, gb += column sums of B.  The k splits go to split_ws and are added in a fixed order, where the workspace
 // has room and the bias gradient directly follows the weight gradient (its column sums ride along).
 void weight_gradient(const RowSrc& A, const float* B, int64_t S, int rows, int H, float* gW, float* gb, float* split_ws, int64_t split_floats, hipStream_t s) {
   GemmArgs g{};
   g.A = A; g.B = B; g.ldb = H; g.C = gW; g.ldc = H;
   g.M = rows; g.N = H; g.K = S; g.colsum = gb;
-  g.k_per_split = pick_k_split(S, gemm_tn_tiles(rows, H));
-  const int64_t count = (int64_t)rows * H + H, nz = (g.K + g.k_per_split - 1) / g.k_per_split;
+  const int64_t count = (int64_t)rows * H + H, nz = tn_plan(rows, H, S).splits;
   if (split_ws != nullptr && gb == gW + (int64_t)rows * H && nz * count <= split_floats) {
     g.split_out = split_ws;
     g.split_count = count;

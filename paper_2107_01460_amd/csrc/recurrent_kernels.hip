@@ -183,22 +183,16 @@ __global__ void gather_hidden_kernel(const float* __restrict__ h0, const int32_t
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-// Splits of a weight gradient's sum over the samples: two workgroups per CU, k ranges in multiples of the k tile.  Every
-// split stores its own copy and the copies are added in a fixed order; at 98 304 samples, 128 x 384 outputs: 341 splits
-// adding with atomics 186 us, 170 copies 70 us.
-int64_t split_want(int M, int N) { return std::max<int64_t>(1, 512 / gemm_tn_tiles(M, N)); }
-int64_t split_floats(int M, int N) { return split_want(M, N) * ((int64_t)M * N + N); }
-
-// gW [M][N] += A^T B over K samples, the column sums of B (the bias gradient) directly behind it
+// gW [M][N] += A^T B over K samples, the column sums of B (the bias gradient) directly behind it.  Every k range stores its own copy in
+// `split` and the copies are added in a fixed order; at 98 304 samples, 128 x 384 outputs: 341 ranges adding with atomics 186 us, 170
+// copies 70 us.
 void weight_gradient(const RowSrc& A, const float* B, int64_t ldb, int M, int N, int64_t K, int c_rot, float* gW, float* split, hipStream_t s) {
   GemmArgs g{};
   g.A = A; g.B = B; g.ldb = ldb; g.C = gW; g.ldc = N; g.c_rot = c_rot;
   g.M = M; g.N = N; g.K = K; g.colsum = gW + (int64_t)M * N;
-  const int64_t want = split_want(M, N), per = (K + want - 1) / want;
-  g.k_per_split = std::max<int64_t>(256, ((per + kGemmBK - 1) / kGemmBK) * kGemmBK);
   g.split_out = split; g.split_count = (int64_t)M * N + N;
   if (launch_gemm<GEMM_TN, EPI_ATOMIC_ADD>(g, s))
-    launch_reduce_partials(split, (int)((K + g.k_per_split - 1) / g.k_per_split), g.split_count, gW, s);
+    launch_reduce_partials(split, (int)tn_plan(M, N, K).splits, g.split_count, gW, s);
 }
 
 const float* stage_params(const Dims& d, const float* params, float* scratch, hipStream_t s) {
@@ -489,7 +483,7 @@ RecUpdateWs carve_rec_update(const marl_config& c, void* ws, int64_t* total) {
     n.hm = (float*)take(step * 4);
     n.dHp = (float*)take(2 * step * 4);
     n.partial = (float*)take(loss_head_partial_floats(H, k == 0 ? kActions : 1) * 4);
-    n.split = (float*)take(std::max(split_floats(H, 3 * H), split_floats(k == 0 ? d.D : d.Dc, H)) * 4);
+    n.split = (float*)take(std::max(tn_copy_floats(H, 3 * H, k == 0 ? Sa : Sc), tn_copy_floats(k == 0 ? d.D : d.Dc, H, k == 0 ? Sa : Sc)) * 4);
   }
   if (total) *total = off;
   return w;

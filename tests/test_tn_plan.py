@@ -1,0 +1,87 @@
+"""The rule that chooses a weight-gradient product's output tile and k ranges (csrc/tn_plan.h, plain C++), on the CPU."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+TILES = [(128, 128), (128, 64), (160, 128), (96, 128), (32, 128)]
+# us on an MI355X of the product and the reduction of its copies with each of TILES, by rows, columns and samples.  None: a tile that the
+# shape does not take.
+MEASURED = {
+    (27, 64, 262144): (65.1, 47.8, 74, 54.9, 36.3),
+    (54, 512, 16384): (29, None, 32.6, 25.4, 20.4),
+    (64, 64, 262144): (64.7, 47.3, 73.4, 54, 53.2),
+    (75, 128, 1024): (26.2, None, 29.3, 22.3, 14.4),
+    (75, 128, 65536): (33, None, 36.4, 28.6, 29.2),
+    (75, 512, 16384): (31.1, None, 34.8, 26.6, 27.6),
+    (108, 160, 262144): (111.4, 100.9, 133.5, 169.5, 188.6),
+    (108, 192, 65536): (40, 36.4, 45.3, 50.7, 52.1),
+    (128, 384, 65536): (56.4, None, 64.9, 73.9, 77.4),
+    (147, 192, 1024): (26.5, 20.4, 31.3, 22.9, 14.5),
+    (147, 192, 16384): (31.5, 28.9, 35.1, 27.6, 24.5),
+    (147, 192, 65536): (64.6, 64.8, 49, 54.3, 66.2),
+    (147, 256, 262144): (222.4, None, 150.5, 190.1, 257.6),
+    (160, 160, 1024): (25.6, 19.3, 30.2, 22.2, 14.5),
+    (216, 256, 262144): (210.9, None, 255.3, 260.7, 340.4),
+    (216, 512, 65536): (102.8, None, 123.1, 120.2, 152.7),
+    (224, 224, 4096): (27, 20.6, 31, 23.6, 15.9),
+    (224, 672, 16384): (53.1, 62.5, 61.4, 58.3, 65.1),
+    (300, 96, 1024): (25.6, 19.3, 30.6, 22.2, 14.5),
+    (300, 256, 1024): (26.2, None, 30.9, 22.6, 15),
+    (300, 256, 262144): (297.7, None, 251.1, 341.5, 460.2),
+    (352, 1056, 16384): (96.1, 119.8, 112.6, 94.7, 139.7),
+    (441, 512, 65536): (203.2, None, 195.7, 219.5, 318.9),
+    (448, 1344, 16384): (142.3, 183.3, 134.4, 138.5, 223.3),
+    (480, 480, 1024): (28.4, 21.8, 32.9, 24.7, 17.5),
+    (480, 480, 16384): (61.4, 73.2, 62, 63, 90.7),
+    (512, 512, 65536): (200.2, None, 241.7, 245.7, 340.8),
+    (588, 256, 65536): (133.1, None, 124.9, 140.9, 208.4),
+    (588, 512, 65536): (242.8, None, 234.4, 278.3, 440.1),
+    (600, 64, 65536): (75.1, 52.9, 72.6, 79.4, 113.9),
+    (1176, 32, 65536): (125.8, 88.2, 126.3, 141.8, None),
+    (1176, 128, 65536): (145.8, None, 140.7, 151.5, None),
+}
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tn_plan")
+    src = d / "plan.cpp"
+    src.write_text("""#include <cstdio>
+#include "tn_plan.h"
+int main() {
+  long long m, n, k;
+  while (std::scanf("%lld %lld %lld", &m, &n, &k) == 3) {
+    const marl::TnPlan p = marl::tn_plan(m, n, k);
+    std::printf("%d %d %lld %lld %lld\\n", p.bm, p.bn, (long long)p.per, (long long)p.splits, (long long)marl::tn_copy_floats(m, n, k));
+  }
+}
+""")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2107_01460_amd", "csrc"),
+                           str(src), "-o", str(d / "plan")])
+
+    def run(shapes):
+        text = "\n".join("%d %d %d" % s for s in shapes)
+        out = subprocess.run([str(d / "plan")], input=text, capture_output=True, text=True, check=True).stdout.split("\n")
+        return [tuple(int(x) for x in ln.split()) for ln in out if ln]
+    return run
+
+
+def test_the_tile_is_about_the_fastest(plan):
+    """Within 10 % of the fastest tile measured, and never more than 3 % behind the tile of 128 rows (32 up to 32 rows)."""
+    for (m, n, k), (bm, bn, *_) in zip(MEASURED, plan(list(MEASURED))):
+        us = MEASURED[m, n, k]
+        took = us[TILES.index((bm, bn))]
+        usual = us[4] if m <= 32 else us[0] if n % 128 == 0 else us[1]
+        assert took <= 1.1 * min(t for t in us if t is not None), ((m, n, k), (bm, bn), us)
+        assert took <= 1.03 * usual, ((m, n, k), (bm, bn), us)
+
+
+def test_ranges_cover_the_samples(plan):
+    shapes = [(m, n, k) for m in (27, 32, 33, 75, 147, 300, 512, 1176) for n in (32, 96, 128, 320, 512, 1536)
+              for k in (1, 31, 255, 256, 257, 4095, 65537, 2 ** 31 - 1)]
+    for (m, n, k), (bm, bn, per, splits, floats) in zip(shapes, plan(shapes)):
+        assert (bm, bn) in TILES and (bn == 128 or n % 128), (m, n, k)
+        assert per % 32 == 0 and per >= 256 and (splits - 1) * per < k <= splits * per, (m, n, k, per, splits)
+        assert splits <= 512 and floats == splits * (m * n + n), (m, n, k)
