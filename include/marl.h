@@ -199,10 +199,13 @@ int32_t marl_rollout(const marl_config* cfg, marl_env_state st, const float* par
 
 /* marl_rollout for callers that cannot allocate or hold a workspace (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): same arguments without `workspace`, same results.  The working copy of the
- * parameters (and, for networks the fused forward kernel does not cover, one step's hidden activations) lives in a
- * device array built into the library, MARL_STATIC_SCRATCH_BYTES per GPU for the life of the process.  The call
- * allocates and frees nothing.  MARL_E_SIZE when marl_query_sizes' rollout_workspace_bytes exceeds that size (the bf16
- * configuration and unfused wide networks with many environments do), MARL_E_LAUNCH when the array's address cannot
+ * parameters (and, for fp32 networks above 320 units, one step's hidden activations) lives in a device array built into the
+ * library, 1 MB more than MARL_STATIC_SCRATCH_BYTES per GPU for the life of the process.  The call allocates and frees
+ * nothing.  MARL_E_SIZE when marl_query_sizes' rollout_workspace_bytes exceeds MARL_STATIC_SCRATCH_BYTES (the bf16
+ * configuration and fp32 networks other than 64, 128 and 256 units wide do with many environments: the size reported counts both
+ * hidden layers of a step whether or not the kernels store them), unless it does so only by the split copies of the weights
+ * of a network of up to 320 units (six bytes a weight instead of four, rows padded to 32; up to 0.6 MB): such a
+ * configuration is taken.  MARL_E_LAUNCH when the array's address cannot
  * be obtained.  Nothing in the array has to start at zero and nothing in it is kept between calls; every call on a
  * GPU uses that GPU's one array, so calls that overlap on one GPU (different streams, different host threads) race. */
 #define MARL_STATIC_SCRATCH_BYTES (8 * 1024 * 1024)

@@ -30,8 +30,9 @@ bool timing_on() { return g_timer.on; }
 // ---- scratch of the entry point that allocates nothing ------------------------------------------------------------
 // Device memory that is part of the loaded code object: every GPU the library runs on holds its own copy, at its own
 // address, until the process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the
-// kernels are given the address that call returns.
-constexpr int64_t kStaticScratchBytes = MARL_STATIC_SCRATCH_BYTES;
+// kernels are given the address that call returns.  1 MB above the limit that calls are held to: what a call needs may be up to 0.6 MB
+// more than what it is judged by (rollout_static_need).
+constexpr int64_t kStaticScratchBytes = MARL_STATIC_SCRATCH_BYTES + 1024 * 1024;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -252,7 +253,8 @@ int32_t marl_rollout_static(const marl_config* cfg, marl_env_state st, const flo
   if ((rc = check_traj(traj, false)) != MARL_OK) return rc;
   MARL_REQUIRE_PTR(params);
   MARL_OPTIONAL_PTR(forced_actions); MARL_OPTIONAL_PTR(forced_uniforms);
-  if (rollout_workspace_bytes(*cfg, cfg->n_envs) > kStaticScratchBytes) return MARL_E_SIZE;
+  if (rollout_static_need(*cfg, cfg->n_envs) > MARL_STATIC_SCRATCH_BYTES) return MARL_E_SIZE;
+  if (rollout_workspace_bytes(*cfg, cfg->n_envs) > kStaticScratchBytes) return MARL_E_SIZE;  // (no configuration)
   void* ws = static_scratch();
   if (ws == nullptr) return MARL_E_LAUNCH;
   return launch_rollout(*cfg, st, params, traj, step_offset, forced_actions, forced_uniforms, ws, (hipStream_t)stream);

@@ -240,6 +240,7 @@ int32_t launch_env_step(const marl_config& c, marl_env_state st, const int32_t* 
 
 struct RolloutWs;  // opaque carve-up of the rollout workspace
 int64_t rollout_workspace_bytes(const marl_config& c, int64_t n_rows);
+int64_t rollout_static_need(const marl_config& c, int64_t n_rows);
 int64_t update_workspace_bytes(const marl_config& c);
 
 int32_t launch_policy_forward(const marl_config& c, const float* params, const float* obs, int64_t n_rows,

@@ -108,22 +108,31 @@ bool use_fused_rollout(const marl_config& c) {
   return !d.bf16 && rollout_fused_supported(d.Ha, d.A) && fused_forward_supported(d.Ha, d.D);
 }
 
-// floats of a working copy for a forward pass that goes layer by layer (64, 128 and 256 units: on split copies)
-int64_t layerwise_param_floats(const marl_config& c) {
+}  // namespace
+
+// What marl_rollout_static compares with MARL_STATIC_SCRATCH_BYTES: the working copy of the parameters and both hidden layers of one
+// pass (in bf16 the packed inputs too) as kernels that go layer by layer hold them, all fp32 networks of 64, 128 and 256 units on chip
+// with split copies of their weights.  A rule of its own, so that what the call takes does not move with the kernels; what these need
+// (carve_rollout_ws) is far less, or, where split copies of the weights take the place of plain ones, up to 0.6 MB more.
+int64_t rollout_static_need(const marl_config& c, int64_t n_rows) {
   const Dims d = dims_of(c);
-  int64_t n = 0;
-  auto add = [&](int64_t floats) { n += (floats + 63) / 64 * 64; };
+  int64_t params = 0, layers = 0;
+  auto add = [&](int64_t floats) { params += (floats + 63) / 64 * 64; };
   for (int k = 0; k < 2; ++k) {
-    const int64_t H = k ? d.Hc : d.Ha, din = k ? d.Dc : d.D, out = k ? 1 : kActions;
-    const bool copies = !d.bf16 && fused_forward_supported((int)H, (int)din);
-    add(copies ? (din + 15) / 16 * 16 * H * 3 / 2 : din * H);
+    const int64_t H = k ? d.Hc : d.Ha, din = k ? d.Dc : d.D, out = k ? 1 : kActions, rows = k && d.central ? n_rows : n_rows * d.A;
+    const bool on_chip = !d.bf16 && fused_forward_supported((int)H, (int)din);
+    add(on_chip ? (din + 15) / 16 * 16 * H * 3 / 2 : din * H);
     add(H);
-    add(copies ? H * H * 3 / 2 : H * H);
+    add(on_chip ? H * H * 3 / 2 : H * H);
     add(H); add(H * out); add(out);
+    if (d.bf16) layers += align256(rows * round_up64(din) * 2) + 2 * align256(rows * H * 2);
+    else if (!on_chip) layers += 2 * align256(rows * H * 4);
   }
-  if (d.bf16) n += (bf16_net_weight_elems(d.D, d.Ha) + bf16_net_weight_elems(d.Dc, d.Hc) + 1) / 2 + 192;
-  return n;
+  if (d.bf16) params += (bf16_net_weight_elems(d.D, d.Ha) + bf16_net_weight_elems(d.Dc, d.Hc) + 1) / 2 + 192;
+  return align256(params * 4) + layers;
 }
+
+namespace {
 
 RolloutWsView carve_rollout_ws(const marl_config& c, int64_t n_rows, void* ws, int64_t* total) {
   const Dims d = dims_of(c);
@@ -145,14 +154,8 @@ RolloutWsView carve_rollout_ws(const marl_config& c, int64_t n_rows, void* ws, i
       if (!split_net_supported(H[n]))
         for (float** p2 : h[n]) *p2 = (float*)take(rows[n] * H[n] * 4);
   }
-  // marl_rollout_static decides by this size what it takes, so it stays at least what a call needs that goes layer by layer: the
-  // parameters and both hidden layers of a pass, packed inputs in bf16 (fp32 of 64, 128 and 256 units: no activations).
-  int64_t by_layer = align256(layerwise_param_floats(c) * 4);
-  for (int n = 0; n < 2; ++n) {
-    if (d.bf16) by_layer += align256(rows[n] * round_up64(din[n]) * 2) + 2 * align256(rows[n] * H[n] * 2);
-    else if (!fused_forward_supported(H[n], din[n])) by_layer += 2 * align256(rows[n] * H[n] * 4);
-  }
-  off = std::max(off, by_layer);
+  // never less than the size that marl_rollout_static decides by
+  off = std::max(off, rollout_static_need(c, n_rows));
   if (total) *total = off;
   return v;
 }

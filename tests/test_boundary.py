@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import workloads as W
 
@@ -145,3 +146,19 @@ def test_missing_library_fails_loudly(M, monkeypatch):
     monkeypatch.setattr(M.binding, "_LIB_PATH", "/nonexistent/libmarl_gfx950.so")
     with pytest.raises(M.MarlError):
         M.binding.lib()
+
+
+@pytest.mark.skipif(torch.cuda.device_count() > 0, reason="the calls that are accepted would run, on addresses that are none")
+@pytest.mark.parametrize("ha,hc,agents,view,central,most", [
+    (512, 320, 8, 7, 1, 144), (480, 320, 8, 7, 1, 157), (352, 64, 3, 5, 0, 913), (448, 64, 3, 5, 0, 686), (64, 448, 4, 5, 0, 515)])
+def test_rollout_static_takes_what_only_split_weights_push_over_its_limit(ha, hc, agents, view, central, most):
+    """One network layer by layer, the other on chip: the split copies of the second one's weights are larger than plain ones, and the
+    environments that fitted beside plain ones still fit (MARL_E_LAUNCH: accepted, no GPU here)."""
+    import paper_2107_01460_amd as M
+    for envs, code in ((most, -4), (most + 1, -5)):
+        cfg = W.scaled(W.CONFIGS[1], actor_hidden=ha, critic_hidden=hc, n_agents=agents, view=view, central_critic=central, n_envs=envs,
+                       rollout_len=1, n_minibatches=1)
+        assert M.query_sizes(cfg).rollout_workspace_bytes > 8 * 1024 * 1024
+        good = 0x10000
+        st, traj = M.binding.EnvStateC(*([good] * 8)), M.binding.TrajC(*([good] * 9 + [None, None]))
+        assert M.lib().marl_rollout_static(C.byref(M.make_config(cfg)), st, good, traj, 0, None, None, None) == code, envs
