@@ -1,6 +1,6 @@
-// Clipped-PPO minibatch update: forward over the gathered minibatch, loss and its gradient with
-// respect to logits / values on the ALUs, backward through the two hidden layers as MFMA GEMMs,
-// gradient accumulation with fp32 atomics, global-norm clipping and Adam.
+// Clipped-PPO minibatch update: each network's forward pass over the gathered minibatch, loss and backward pass (fused_train.h,
+// split_net.h, bf16_net.h; fp32 networks above 320 units layer by layer on gemm.h), gradients as copies added in a fixed order,
+// global-norm clipping and Adam.
 #include <algorithm>
 #include <cmath>
 
@@ -30,8 +30,8 @@ struct UpdateWsView {
   float *h1a, *h2a, *dz1a;
   float *h1c, *h2c, *dz1c;
   float* partial;  // per-workgroup copies of one network's gradient (two-stage reduction of the fused training kernel)
-  float* partial_head;  // per-workgroup W3 / b3 gradients of the output-layer kernels
-  float* split_ws;      // fp32 layer-by-layer networks: the k splits of a weight-gradient product, added in a fixed order
+  float* partial_head;  // networks that fused_train_kernel does not take: per-workgroup W3 / b3 gradients (and loss statistics)
+  float* split_ws;      // theirs too: the k splits of a weight-gradient product, added in a fixed order
   int64_t split_floats;
   // bf16 configuration: one set of buffers, used by the actor and then by the critic
   bf16_t *bh1, *bdz2, *bdz1;
@@ -39,7 +39,7 @@ struct UpdateWsView {
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
-// floats of workspace for the k splits of dW2 (H x H + H) and dW1 (Din x H + H) of one layer-by-layer network of S samples
+// floats of workspace for the k splits of dW2 (H x H + H) and dW1 (Din x H + H) of one network of S samples
 int64_t split_ws_floats(int H, int Din, int64_t S) { return std::max(tn_copy_floats(H, H, S), tn_copy_floats(Din, H, S)); }
 
 UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
@@ -75,9 +75,10 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
     if (!fused_train_supported(d.Ha, d.D)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Ha, d.D, Sa));
     if (!fused_train_supported(d.Hc, d.Dc)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Hc, d.Dc, Sc));
     v.split_ws = v.split_floats > 0 ? (float*)take(v.split_floats * 4) : nullptr;
-    int64_t head = std::max(loss_head_partial_floats(d.Ha, kActions), loss_head_partial_floats(d.Hc, 1));
-    if (split_net_supported(d.Ha)) head = std::max(head, split_net_partial_floats(d.Ha, kActions));
-    if (split_net_supported(d.Hc)) head = std::max(head, split_net_partial_floats(d.Hc, 1));
+    auto head_floats = [](int H, int Din, int nout) -> int64_t {
+      return fused_train_supported(H, Din) ? 0 : split_net_supported(H) ? split_net_partial_floats(H, nout) : loss_head_partial_floats(H, nout);
+    };
+    const int64_t head = std::max(head_floats(d.Ha, d.D, kActions), head_floats(d.Hc, d.Dc, 1));
     v.partial_head = (float*)take(head * 4);
   } else {
     const int64_t SH = std::max(Sa * d.Ha, Sc * d.Hc);

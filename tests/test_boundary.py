@@ -148,6 +148,13 @@ def test_missing_library_fails_loudly(M, monkeypatch):
         M.binding.lib()
 
 
+@pytest.mark.parametrize("view", [3, 5])
+def test_update_workspace_of_networks_in_one_training_kernel(M, view):
+    """512 copies of the larger network's gradient and little else: the output-layer copies of the other routes are not counted."""
+    s = M.query_sizes(W.scaled(W.CONFIGS[0], n_envs=2, rollout_len=1, n_minibatches=1, view=view))
+    assert s.update_workspace_bytes < 4 * (512 * s.n_actor_params + 16 * s.n_params)
+
+
 @pytest.mark.skipif(torch.cuda.device_count() > 0, reason="the calls that are accepted would run, on addresses that are none")
 @pytest.mark.parametrize("ha,hc,agents,view,central,most", [
     (512, 320, 8, 7, 1, 144), (480, 320, 8, 7, 1, 157), (352, 64, 3, 5, 0, 913), (448, 64, 3, 5, 0, 686), (64, 448, 4, 5, 0, 515)])
