@@ -30,12 +30,15 @@ def run(M, cfg, params):
 
 
 # environments per launch around 512 workgroups of the rollout kernels (32 environments each at 64 units and two agents, 10 at
-# 128 units and three), and a handful; the layer-by-layer networks; the recurrent ones around 4096 samples per step, where
+# 128 units and three), and a handful; networks whose steps are launches of their own, in one kernel each (192 units; 64-row tiles from
+# 16 384 samples on) and layer by layer (352); the recurrent ones around 4096 samples per step, where
 # the cell's kernels change their tile, with weights in registers and streamed
 @pytest.mark.parametrize("k,sizes,kw", [
     (5, (37, 512 * 32, 512 * 32 + 1), {}),
     (2, (37, 512 * 10, 512 * 10 + 1), {}),
     (2, (37, 600), dict(actor_hidden=192, critic_hidden=256)),
+    (2, (37, 5461, 5462), dict(actor_hidden=192, critic_hidden=320)),
+    (2, (37, 600, 3000), dict(actor_hidden=352, critic_hidden=480)),
     (2, (37, 1365, 1366), dict(recurrent=1, actor_hidden=128, critic_hidden=192)),
     (2, (37, 1365, 1366), dict(recurrent=1, actor_hidden=256, critic_hidden=64)),
 ])
@@ -56,7 +59,7 @@ def test_rollout_does_not_depend_on_the_batch(M, k, sizes, kw):
             assert torch.equal(a, b[:n]), n
 
 
-@pytest.mark.parametrize("hidden", [64, 128, 192, 256])
+@pytest.mark.parametrize("hidden", [64, 128, 192, 256, 384])
 def test_evaluation_does_not_depend_on_the_batch(M, hidden):
     base = W.scaled(W.CONFIGS[1], rollout_len=1, n_minibatches=1, episode_cap=6, actor_hidden=hidden)
     params = dev(W.init_params(base, bias_scale=0.1))

@@ -1,5 +1,6 @@
 """Greedy evaluation blocks of shapes that none of the workloads has, against the oracle: both worlds, every view, both widths of
-the one-launch kernel, entity counts on both sides of its unrolled capacities, ragged last workgroups."""
+the one-launch kernel, entity counts on both sides of its unrolled capacities, ragged last workgroups; and actors whose steps are
+launches of their own, in one kernel (192 units) and layer by layer (448)."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +19,8 @@ def M():
 
 @pytest.mark.parametrize("kind,grid,agents,food,level,view,hidden,n_envs", [
     (0, 9, 6, 3, 2, 7, 128, 23), (0, 8, 3, 4, 2, 3, 64, 70), (0, 10, 5, 5, 3, 5, 64, 61), (0, 8, 2, 2, 2, 7, 64, 67),
-    (1, 8, 3, 5, 2, 3, 64, 45), (1, 10, 4, 4, 2, 7, 128, 33), (2, 9, 5, 6, 2, 5, 128, 41), (2, 8, 2, 8, 3, 7, 64, 97)])
+    (1, 8, 3, 5, 2, 3, 64, 45), (1, 10, 4, 4, 2, 7, 128, 33), (2, 9, 5, 6, 2, 5, 128, 41), (2, 8, 2, 8, 3, 7, 64, 97),
+    (0, 8, 3, 4, 2, 5, 192, 37), (0, 8, 2, 2, 2, 3, 448, 29)])
 def test_evaluation_block(M, orc, kind, grid, agents, food, level, view, hidden, n_envs):
     cfg = W.scaled(W.CONFIGS[0], env_kind=kind, grid=grid, n_agents=agents, n_food=food, max_level=level, view=view, n_envs=n_envs,
                    actor_hidden=hidden, critic_hidden=hidden, episode_cap=9, n_minibatches=1, rollout_len=1)

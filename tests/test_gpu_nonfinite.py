@@ -58,9 +58,9 @@ FEED_FORWARD = {
 }
 
 
-# the fused kernels of 64, 128 and 256 units, and the layer-by-layer products
+# the kernels of 64 and 128 units, the whole-network kernels of other widths up to 320, and the layer-by-layer products above
 @pytest.mark.parametrize("key", sorted(FEED_FORWARD))
-@pytest.mark.parametrize("ha,hc,central", [(128, 64, 0), (64, 256, 1), (192, 128, 0)])
+@pytest.mark.parametrize("ha,hc,central", [(128, 64, 0), (64, 256, 1), (192, 128, 0), (352, 512, 0)])
 def test_feed_forward(M, orc, ha, hc, central, key):
     cfg = dict(W.CONFIGS[1], n_envs=30, rollout_len=5, n_minibatches=1, n_epochs=1, actor_hidden=ha, critic_hidden=hc,
                central_critic=central, max_grad_norm=0.0)
@@ -94,7 +94,7 @@ def test_feed_forward(M, orc, ha, hc, central, key):
 
 
 # rows of the caller's own: small and large calls (they may take different kernels), the padding of the last input column
-@pytest.mark.parametrize("ha,hc,rows", [(128, 64, 40), (128, 256, 900), (96, 64, 40)])
+@pytest.mark.parametrize("ha,hc,rows", [(128, 64, 40), (128, 256, 900), (96, 64, 40), (384, 352, 40)])
 def test_observations(M, orc, ha, hc, rows):
     cfg = dict(W.CONFIGS[1], n_envs=rows, rollout_len=1, n_minibatches=1, n_epochs=1, actor_hidden=ha, critic_hidden=hc)
     print("case", ha, hc, rows, flush=True)

@@ -263,11 +263,12 @@ def test_bf16_other_widths(M, orc, ha, hc, view):
     check_single_minibatch_gradient(M, orc, small(4, n_epochs=1, n_minibatches=1, max_grad_norm=0.0, **kw), 4)
 
 
-@pytest.mark.parametrize("ha,hc", [(96, 512), (32, 160), (224, 192)])
-def test_fp32_other_widths(M, orc, ha, hc):
-    """fp32 networks of hidden widths that none of the workloads uses (any multiple of 32 up to 512 is accepted): they
-    take the generic tile GEMMs with the separate output-layer / loss / dz2 kernels instead of the fused ones."""
-    kw = dict(actor_hidden=ha, critic_hidden=hc)
+@pytest.mark.parametrize("ha,hc,central", [(96, 512, 0), (32, 160, 0), (224, 192, 0), (512, 96, 0), (352, 384, 0), (416, 480, 1)])
+def test_fp32_other_widths(M, orc, ha, hc, central):
+    """fp32 networks of hidden widths that none of the workloads uses (any multiple of 32 up to 512 is accepted).  Up to 320 units a row
+    tile goes through the whole network in one kernel; above, the network takes the tile GEMMs layer by layer with the separate
+    output-layer / loss / dz2 kernels."""
+    kw = dict(actor_hidden=ha, critic_hidden=hc, central_critic=central)
     check_policy_forward(M, orc, small(2, **kw), 60 + ha // 32)
     check_single_minibatch_gradient(M, orc, small(2, n_epochs=1, n_minibatches=1, max_grad_norm=0.0, **kw), 2)
 
@@ -279,8 +280,8 @@ def test_bf16_odd_chunk_count(M, orc):
 
 
 def test_wide_central_critic(M, orc):
-    """A centralised critic whose input (8 agents x 147 = 1176 values) is wider than the fused forward kernel
-    keeps in LDS: its forward pass, loss and gradient take the layer-by-layer kernels."""
+    """A centralised critic whose input (8 agents x 147 = 1176 values) is wider than the small calls' forward kernel
+    keeps in LDS, and goes through the whole-network kernels in seven pieces."""
     kw = dict(n_agents=8, view=7, n_food=5)
     check_policy_forward(M, orc, small(3, **kw), 31)
     check_single_minibatch_gradient(M, orc, small(3, n_epochs=1, n_minibatches=1, max_grad_norm=0.0, **kw), 3)
