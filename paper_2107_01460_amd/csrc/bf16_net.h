@@ -14,7 +14,8 @@
 // forward pass of 32 768 samples through both networks and the sampling 159 -> 73 us.
 // Bound: two workgroups of four wavefronts share a CU (64 rows each, 128 of a lane's 256 registers accumulators), and a tile is
 // a chain of products (39 of 107 thousand cycles for the pair), tanh (16), gradients on the output side (15), copies and barriers
-// that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile.  One workgroup of 128 rows per CU halves
+// that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile; at 512 units 58 (six outputs) and 44 (one)
+// registers are spilled.  One workgroup of 128 rows per CU halves
 // that and left every phase uncovered: 778 us; eight wavefronts of 128 registers per 64 rows: 750 us (spills).
 #pragma once
 #include "gemm.h"
@@ -461,7 +462,8 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
 // 256 units, 12 288: 16.1 / 15.4, 32 768: 20.7 / 24.8.  (Same bits: both take a sample's sums in the same order.)
 constexpr int64_t kBf16SmallRows = 16384;
 inline int64_t bf16_net_partial_floats(int H, int nout) { return (int64_t)H * nout + nout + 5; }
-// Workgroups of a launch at most: what fits the chip at once (a workgroup's prologue stages W3 and asks for its first weights).
+// Workgroups of a launch at most: what fits the chip at once above 256 units, up to twice as many below (a workgroup's prologue stages W3
+// and asks for its first weights).
 constexpr unsigned bf16_net_grid(int H) { return H > 256 ? 512 : 1024; }
 
 template <int H, int BM, int NOUT, bool TRAIN, class Fin>

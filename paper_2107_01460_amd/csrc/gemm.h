@@ -100,10 +100,10 @@ struct GemmArgs {
   int64_t split_count;
 };
 
-// The kernels that finish with one partial result per workgroup (the fused training kernel, the accumulator-resident
-// transposed product) store those with plain stores and add them up here: a few hundred workgroups adding to the same
-// cache lines with atomics at the same moment queue up at the L2 (60-180 us per launch).  The split-k tile kernel below
-// does the same with one slab per k split when the caller passes split_out; without it, it adds with atomics.
+// The kernels that finish with one partial result per workgroup (the training kernels of whole networks, the output-layer loss
+// kernel) store those with plain stores and add them up here: a few hundred workgroups adding to the same
+// cache lines with atomics at the same moment queue up at the L2 (60-180 us per launch).  The weight-gradient products
+// do the same with one slab per k split when the caller passes split_out; without it, they add with atomics.
 
 // out[i] += sum_b partial[b * count + i], the copies added in a fixed order, so that the result does not depend on the
 // run; elements from `head` on go to tail[i - head] instead.  A workgroup takes 32 consecutive elements; its 8 thread groups sum the copies b = g, g + 8, g + 16, ... of an
@@ -265,7 +265,7 @@ __device__ __forceinline__ void gemm_phase_direct(const float* __restrict__ As, 
 }
 
 
-// BM x BN tile, four wavefronts (2 x 2 at BM = 128, side by side at BM = 32), k tiles of 32 in one LDS buffer of split
+// BM x BN tile, four wavefronts (2 x 2 at BM = 128, side by side at the other heights of TN), k tiles of 32 in one LDS buffer of split
 // operands; the next k tile travels global -> registers while the current one is multiplied, and two workgroups per CU
 // cover each other's staging and barriers.  A tile is kept in LDS in its source orientation: k-contiguous tiles are read
 // with 16-byte reads (pitch 40 elements: an odd number of 16-byte units), the others with the transposing read (the

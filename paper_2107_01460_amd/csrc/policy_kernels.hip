@@ -1,8 +1,8 @@
 // Actor / critic forward pass of the rollout, categorical sampling, and the rollout driver.
 //
-// The two hidden layers of each network are MFMA GEMMs (gemm.h); the narrow output layer
-// (6 logits or 1 value) runs on the vector ALUs of the "head" kernel, which also draws the
-// action by Gumbel-max from Philox uniforms and evaluates its log-probability.
+// A forward pass is one kernel per network (split_net.h, bf16_net.h; small fp32 calls one for both, fused_forward.h), and fp32
+// networks above 320 units go layer by layer on gemm.h and the output-layer kernels of heads.h.  What the actor's kernel does with
+// a sample's logits includes the draw of the action by Gumbel-max from Philox uniforms and its log-probability.
 #include "bf16_net.h"
 #include "fused_forward.h"
 #include "gemm.h"
@@ -105,7 +105,7 @@ int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
 bool use_fused_rollout(const marl_config& c) {
   const Dims d = dims_of(c);
-  return !d.bf16 && rollout_fused_supported(d.Ha, d.A) && fused_forward_supported(d.Ha, d.D);
+  return !d.bf16 && rollout_fused_supported(d.Ha, d.A);
 }
 
 }  // namespace

@@ -5,22 +5,17 @@
 // hidden layers' pre-activations; h1 and h2 stay in registers for them, h1, dz2 and dz1 go to memory for the weight gradients.
 //
 // Measured on an MI355X against a kernel per layer (fp32 instruction, weights in registers, or 32-row tiles with the forward pass and the
-// loss in one kernel): critic minibatch of 262 144 samples, 300 inputs, 256 units: 345 + 327 + 294 -> 720 us (151 TFLOP/s of fp32
-// products); 50 000 samples of 147 inputs, 256 units: 142 us for the forward pass and the loss and 63 for dz1 -> 140 us for all.
-// Bound: matrix cores busy 43 % and vector instructions 24 % of the cycles; two workgroups of 32 rows per CU cover each other's
-// barriers and the weights' way from the L2 (1.25 MB a tile), and their 128 registers leave a ring of two k steps.  32 rows rather than 64 in
-// training: three planes of 64 rows leave room for one workgroup per CU.  h1 stored at the end of a tile instead of before layer 2's
-// product, so that no weight waits behind it: 720 -> 759 us.
-//
-// Measured on an MI355X.  Minibatch of 262 144 samples, 300 inputs, 256 units, one output, everything but the weight gradients:
-// 347 + 331 + 297 us as three kernels with the weights resident in registers, on the fp32 instruction -> 707 us here; 50 000 samples,
-// 147 inputs: 256 units, six outputs 143 + 64 (32-row tiles, then dz1 as a product of its own) -> 143 us, 192 units, one output 42 + 38
-// + 30 + 38 (layer by layer) -> 109 us.  Training iterations: 1000 environments, 256 / 192 units 15.8 -> 12.4 ms; 16 384 environments,
+// loss in one kernel).  Everything of a minibatch but the weight gradients: 262 144 samples, 300 inputs, 256 units, one output: 347 + 331 +
+// 297 -> 725 us (151 TFLOP/s of fp32 products); 50 000 samples, 147 inputs: 256 units, six outputs 143 + 64 -> 138 us, 192 units, one
+// output 42 + 38 + 30 + 38 -> 102 us.  Training iterations: 1000 environments, 256 / 192 units 15.8 -> 12.4 ms; 16 384 environments,
 // central critic of 256 units 96.7 -> 92.2 ms.
-// Bound: the weights' way from the L2 -- 1.28 MB per tile of 32 rows and 256 units, read at about 15 TB/s by the whole chip, which
-// two workgroups per CU keep going through each other's phases.  64-row tiles halve the bytes, but only one workgroup fits a CU and
-// its phases without products (tanh, loss, gradients: 37 of 81 thousand cycles) leave the L2 idle: 718 us at the first of these sizes,
-// 160 and 126 us at the others.  Forward passes of many samples hold less and take the 64-row tiles.
+// Bound (first of these sizes): no unit is full.  Matrix cores are busy 43 % and vector instructions 24 % of the cycles, and the weights
+// come from the L2 at 15 TB/s (1.28 MB per tile of 32 rows; 86 million reads of 128 bytes), which two workgroups per CU (one above 256
+// units) keep going through each other's phases; their 128 registers a lane leave a ring of two k steps of weights and up to 60 spilled
+// registers (7, 12 and 11 at the sizes above).  64-row tiles halve the bytes, but leave room for one workgroup per CU, whose phases
+// without products (tanh, loss, gradients: 37 of 81 thousand cycles) nothing covers: the same time at the first size, 7 % longer updates
+// at 50 000 samples.  Forward passes of many samples hold less and take the 64-row tiles.  h1 stored at the end of a tile instead of
+// before layer 2's product, so that no weight waits behind it: 720 -> 759 us.
 #pragma once
 #include <type_traits>
 
