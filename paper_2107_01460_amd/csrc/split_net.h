@@ -6,7 +6,7 @@
 //
 // Measured on an MI355X against a kernel per layer (fp32 instruction, weights in registers, or 32-row tiles with the forward pass and the
 // loss in one kernel).  Everything of a minibatch but the weight gradients: 262 144 samples, 300 inputs, 256 units, one output: 347 + 331 +
-// 297 -> 725 us (151 TFLOP/s of fp32 products); 50 000 samples, 147 inputs: 256 units, six outputs 143 + 64 -> 138 us, 192 units, one
+// 297 -> 725 us (150 TFLOP/s of fp32 products); 50 000 samples, 147 inputs: 256 units, six outputs 143 + 64 -> 138 us, 192 units, one
 // output 42 + 38 + 30 + 38 -> 102 us.  Training iterations: 1000 environments, 256 / 192 units 15.8 -> 12.4 ms; 16 384 environments,
 // central critic of 256 units 96.7 -> 92.2 ms.
 // Bound (first of these sizes): no unit is full.  Matrix cores are busy 43 % and vector instructions 24 % of the cycles, and the weights
