@@ -31,8 +31,9 @@ SIDE_RUNS = {1: (300, 30), 2: (30, 4), 3: (8, 2), 4: (4, 1), 5: (20, 3)}
 # rocprofv3 PMC summaries (FETCH_SIZE / WRITE_SIZE per launch, scaled by a plain copy of known size) by workload, and
 # a pattern of the kernel names of each timed kernel class in them
 PMC_PROFILE = {"c3_15x15_4ag_mappo": "profiles/bench_c3_pmc_hbm_traffic.txt",
+               "c4_20x20_8ag_ippo_bf16": "profiles/bench_c4_pmc_hbm_traffic.txt",
                "c5_8x8_2ag_ippo_wide": "profiles/bench_c5_pmc_hbm_traffic.txt"}
-CLASS_KERNEL = {"fused_train": r"fused_train_kernel<|split_net_kernel<\d+, \d+, \d+, true", "env_step": "env_step_kernel<", "gae": "gae_kernel",
+CLASS_KERNEL = {"fused_train": r"fused_train_kernel<|(split|bf16)_net_kernel<\d+, \d+, \d+, true", "env_step": "env_step_kernel<", "gae": "gae_kernel",
                 "rollout": "rollout_train_kernel<"}
 
 
