@@ -275,7 +275,8 @@ __device__ __forceinline__ void gemm_phase_direct(const float* __restrict__ As, 
 // contraction lengths of 128 .. 256 the activations' HBM traffic is the other bound.  Measured against the kernel on the
 // fp32 instruction that this one replaced: dW of 256 x 256 over 262 144 samples 295 -> 196 us; a training iteration whose
 // networks run layer by layer (147-256-6 and 147-192-1, 250 000 samples) 27.1 -> 19.9 ms.  The check for NaNs at the end of a
-// tile (values out of split_pair's range) costs 1 %.
+// tile (values out of split_pair's range) costs 1 %.  Requesting a k tile two tiles ahead instead of one changed nothing at 128 columns
+// and cost 40 % at 64: the loads are not what a k tile waits for.
 template <int MODE, int EPI, int BM, int BN, bool AVEC>
 __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   constexpr int BK = kGemmBK;
