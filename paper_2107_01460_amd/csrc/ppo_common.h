@@ -119,6 +119,7 @@ struct LossPrep {
 };
 
 struct ActorLoss {
+  static constexpr unsigned kStats = 0b11101;  // the statistics that compute() adds to, by their index
   LossCommon lc;
   const int32_t* action;
   const float* logp_old;
@@ -192,6 +193,7 @@ struct ActorLoss {
 };
 
 struct CriticLoss {
+  static constexpr unsigned kStats = 0b00010;
   LossCommon lc;
   const float* ret;
   const float* v_old;

@@ -66,10 +66,11 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
     v.h1c = (float*)take(Sc * d.Hc * 4);
     v.h2c = (float*)take(Sc * d.Hc * 4);
     v.dz1c = (float*)take(Sc * d.Hc * 4);
-    int64_t pmax = 0;
-    if (fused_train_supported(d.Ha, d.D)) pmax = std::max<int64_t>(pmax, d.Pa);
-    if (fused_train_supported(d.Hc, d.Dc)) pmax = std::max<int64_t>(pmax, d.P - d.Pa);
-    v.partial = pmax > 0 ? (float*)take((int64_t)kFusedTrainMaxGrid * pmax * 4) : nullptr;
+    int64_t copies = 0;
+    if (fused_train_supported(d.Ha, d.D)) copies = std::max(copies, fused_train_partial_floats(d.Ha, d.D, Sa, d.Pa));
+    if (fused_train_supported(d.Hc, d.Dc)) copies = std::max(copies, fused_train_partial_floats(d.Hc, d.Dc, Sc, d.P - d.Pa));
+    if (fused_train_pair_supported(d.Ha, d.D, Sa, d.Hc, d.Dc, Sc)) copies = std::max(copies, fused_train_pair_partial_floats(Sa, d.Pa, d.P - d.Pa));
+    v.partial = copies > 0 ? (float*)take(copies * 4) : nullptr;
     // the k splits of the weight gradients that are products of their own
     v.split_floats = 0;
     if (!fused_train_supported(d.Ha, d.D)) v.split_floats = std::max(v.split_floats, split_ws_floats(d.Ha, d.D, Sa));
@@ -223,24 +224,21 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
       lc.ent_coef = c.ent_coef; lc.vf_coef = c.vf_coef; lc.clip_value = c.clip_value;
       const RowSrc Xa{tr.obs, d.D, rows, d.A, Sa, make_small_div(d.A)};
       const RowSrc Xc{tr.obs, d.Dc, rows, d.central ? 1 : d.A, Sc, make_small_div(d.central ? 1 : d.A)};
+      auto train_args = [&](const RowSrc& X, int64_t S, int net) {
+        const NetOffsets& o = net == 0 ? oa : oc;
+        FusedTrainArgs t{};
+        t.X = X; t.S = S; t.Din = pm.din[net]; t.Kp = pm.kpad1[net]; t.W = eff + pm.sw_w1[net];
+        t.b1 = eff + o.b1; t.b2 = eff + o.b2; t.W3 = eff + o.W3; t.b3 = eff + o.b3;
+        t.grad = w.grad + (net == 0 ? ga : gc).W1; t.gcount = net == 0 ? d.Pa : d.P - d.Pa;
+        t.stats = sck->acc; t.partial = w.partial;
+        return t;
+      };
       // ---- both networks in one launch (same shape, few tiles)
       const bool pair = !d.bf16 && Sa < ((int64_t)1 << 31) && fused_train_pair_supported(d.Ha, d.D, Sa, d.Hc, d.Dc, Sc);
       if (pair) {
         ActorLoss fa{lc, tr.action, tr.logp, tr.adv};
         CriticLoss fc{lc, tr.ret, tr.value, d.central ? d.A : 1};
-        FusedTrainArgs ta{}, tc{};
-        ta.X = Xa; ta.S = Sa; ta.Din = d.D; ta.px = fused_train_px(d.D);
-        ta.W1 = eff + oa.W1; ta.b1 = eff + oa.b1; ta.W2 = eff + oa.W2; ta.b2 = eff + oa.b2; ta.W3 = eff + oa.W3;
-        ta.W1s = eff + pm.sw_w1[0]; ta.W2s = eff + pm.sw_w2[0]; ta.W2Ts = eff + pm.sw_w2t[0];
-        ta.b3 = eff + oa.b3; ta.gW1 = w.grad + ga.W1; ta.gb1 = w.grad + ga.b1; ta.gW2 = w.grad + ga.W2;
-        ta.gb2 = w.grad + ga.b2; ta.gW3 = w.grad + ga.W3; ta.gb3 = w.grad + ga.b3; ta.stats = sck->acc;
-        ta.partial = w.partial; ta.gcount = d.Pa;
-        tc.X = Xc; tc.S = Sc; tc.Din = d.Dc; tc.px = fused_train_px(d.Dc);
-        tc.W1 = eff + oc.W1; tc.b1 = eff + oc.b1; tc.W2 = eff + oc.W2; tc.b2 = eff + oc.b2; tc.W3 = eff + oc.W3;
-        tc.W1s = eff + pm.sw_w1[1]; tc.W2s = eff + pm.sw_w2[1]; tc.W2Ts = eff + pm.sw_w2t[1];
-        tc.b3 = eff + oc.b3; tc.gW1 = w.grad + gc.W1; tc.gb1 = w.grad + gc.b1; tc.gW2 = w.grad + gc.W2;
-        tc.gb2 = w.grad + gc.b2; tc.gW3 = w.grad + gc.W3; tc.gb3 = w.grad + gc.b3; tc.stats = sck->acc;
-        tc.gcount = d.P - d.Pa;
+        const FusedTrainArgs ta = train_args(Xa, Sa, 0), tc = train_args(Xc, Sc, 1);
         const int32_t rc = (launch_fused_train_pair<kActions, 1>(d.Ha, ta, fa, tc, fc, s));
         if (rc != MARL_OK) return rc;
       }
@@ -251,14 +249,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
           const int32_t rc = train_net_bf16<kActions>(Xa, Sa, d.D, d.Ha, effective_bf16_weights(c, eff, 0), eff, oa, w.grad, ga, fn, wk, s);
           if (rc != MARL_OK) return rc;
         } else if (fused_train_supported(d.Ha, d.D) && Sa < ((int64_t)1 << 31)) {
-          FusedTrainArgs ta{};
-          ta.X = Xa; ta.S = Sa; ta.Din = d.D; ta.px = fused_train_px(d.D);
-          ta.W1 = eff + oa.W1; ta.b1 = eff + oa.b1; ta.W2 = eff + oa.W2; ta.b2 = eff + oa.b2; ta.W3 = eff + oa.W3;
-          ta.W1s = eff + pm.sw_w1[0]; ta.W2s = eff + pm.sw_w2[0]; ta.W2Ts = eff + pm.sw_w2t[0];
-          ta.b3 = eff + oa.b3; ta.gW1 = w.grad + ga.W1; ta.gb1 = w.grad + ga.b1; ta.gW2 = w.grad + ga.W2;
-          ta.gb2 = w.grad + ga.b2; ta.gW3 = w.grad + ga.W3; ta.gb3 = w.grad + ga.b3; ta.stats = sck->acc;
-          ta.partial = w.partial; ta.gcount = d.Pa;
-          const int32_t rc = launch_fused_train<kActions>(d.Ha, ta, fn, s);
+          const int32_t rc = launch_fused_train<kActions>(d.Ha, train_args(Xa, Sa, 0), fn, s);
           if (rc != MARL_OK) return rc;
         } else if (split_net_supported(d.Ha)) {
           const int32_t rc = train_net_split<kActions>(Xa, Sa, d.D, d.Ha, eff, pm, 0, w.grad, ga, fn, wk, w.h1a, w.h2a, w.dz1a, s);
@@ -278,14 +269,7 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
           const int32_t rc = train_net_bf16<1>(Xc, Sc, d.Dc, d.Hc, effective_bf16_weights(c, eff, 1), eff, oc, w.grad, gc, fn, wk, s);
           if (rc != MARL_OK) return rc;
         } else if (fused_train_supported(d.Hc, d.Dc) && Sc < ((int64_t)1 << 31)) {
-          FusedTrainArgs ta{};
-          ta.X = Xc; ta.S = Sc; ta.Din = d.Dc; ta.px = fused_train_px(d.Dc);
-          ta.W1 = eff + oc.W1; ta.b1 = eff + oc.b1; ta.W2 = eff + oc.W2; ta.b2 = eff + oc.b2; ta.W3 = eff + oc.W3;
-          ta.W1s = eff + pm.sw_w1[1]; ta.W2s = eff + pm.sw_w2[1]; ta.W2Ts = eff + pm.sw_w2t[1];
-          ta.b3 = eff + oc.b3; ta.gW1 = w.grad + gc.W1; ta.gb1 = w.grad + gc.b1; ta.gW2 = w.grad + gc.W2;
-          ta.gb2 = w.grad + gc.b2; ta.gW3 = w.grad + gc.W3; ta.gb3 = w.grad + gc.b3; ta.stats = sck->acc;
-          ta.partial = w.partial; ta.gcount = d.P - d.Pa;
-          const int32_t rc = launch_fused_train<1>(d.Hc, ta, fn, s);
+          const int32_t rc = launch_fused_train<1>(d.Hc, train_args(Xc, Sc, 1), fn, s);
           if (rc != MARL_OK) return rc;
         } else if (split_net_supported(d.Hc)) {
           const int32_t rc = train_net_split<1>(Xc, Sc, d.Dc, d.Hc, eff, pm, 1, w.grad, gc, fn, wk, w.h1c, w.h2c, w.dz1c, s);
@@ -322,16 +306,3 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
 }
 
 }  // namespace marl
-
-#ifdef MARL_PHASE_TIMERS
-// Development aid (not part of the built library): cycles per phase of the fused training kernel, workgroup 0.
-extern "C" int32_t marl_debug_phase_cycles(long long* out16, int32_t reset) {
-  if (hipDeviceSynchronize() != hipSuccess) return -1;
-  if (out16 && hipMemcpyFromSymbol(out16, HIP_SYMBOL(marl::g_phase_cycles), 16 * sizeof(long long)) != hipSuccess) return -1;
-  if (reset) {
-    long long z[16] = {0};
-    if (hipMemcpyToSymbol(HIP_SYMBOL(marl::g_phase_cycles), z, sizeof(z)) != hipSuccess) return -1;
-  }
-  return 0;
-}
-#endif
