@@ -10,7 +10,7 @@
 // pieces of three bf16 planes in LDS (split_bf16.h), which every product afterwards reads as operands, by rows or, for the weight
 // gradients, through the transposing read.  Weights stream from the L2 in one sequence of k steps that runs on from layer to layer
 // and from tile to tile.  Per tile, a barrier where | stands:
-//   layer 1 -> h1 (A) | layer 2 -> h2 (registers, B) | output layer, loss -> dL/dout | W3 gradient, dz2 = (dL/dout W3^T)(1 - h2^2) -> B |
+//   layer 1 -> h1 (A) | layer 2 -> h2 (registers, B), output layer | loss -> dL/dout | W3 gradient, dz2 = (dL/dout W3^T)(1 - h2^2) -> B |
 //   dW2 += h1^T dz2, dz1 = (dz2 W2^T)(1 - h1^2), the next tile's X to LDS | dz1 -> A, dW1 += X^T dz1
 // A wavefront's share of dW1 needs no dz1 but its own.  The tiles' rows have no padding; a row's 16-byte units are permuted
 // (tile_swizzle) so that both ways of reading a plane and the epilogues' stores meet every bank once.
@@ -42,11 +42,17 @@ struct FusedTrainArgs {
 
 constexpr int kFusedTile = 32;  // samples of a tile
 
+// bf16 elements of LDS for two tiles of exact inputs and the wavefronts' shares of the outputs; the general form stages 32 columns in
+// three planes there.
+constexpr size_t fused_train_x_region(int H, int DMAX) {
+  const size_t exact = 2 * 32 * DMAX + 2 * (H / 32) * 32 * 8;
+  return exact > 3072 ? exact : 3072;
+}
 // Bytes of LDS (with DMAX columns of X).  Two workgroups of 128 units, four of 64 units and 32 inputs, three of 64 units and 96
 // inputs fit a CU's 160 KB.
 constexpr size_t fused_train_lds(int H, int NOUT, int DMAX) {
-  return sizeof(bf16_t) * (2 * 3 * 32 * H + (2 * 32 * DMAX > 3072 ? 2 * 32 * DMAX : 3072) + 24 * (H + 8) + 24 * 40) +
-         sizeof(float) * (2 * H + 32 * 8 + H * NOUT + 32 * (NOUT + 5) + 4);
+  return sizeof(bf16_t) * (2 * 3 * 32 * H + fused_train_x_region(H, DMAX) + 24 * (H + 8) + 24 * 40) +
+         sizeof(float) * (2 * H + 32 * 8 + H * NOUT + 32 * (NOUT + 5) + 12);
 }
 
 // Where the 16-byte unit u of row r of a tile with H elements a row (H = 32: blocks of X) stands: at unit u ^ tile_swizzle(r).
@@ -57,25 +63,42 @@ __device__ __forceinline__ int tile_swizzle(int r) {
   return H == 128 ? (r & 3) << 2 | low : H == 64 ? (r & 2) << 1 | low : low;
 }
 
+// c + the sum of eight values
+__device__ __forceinline__ float sum8(bf16x8 v, float c) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
+  c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(v, v, 0, 1), one, c, false);
+  c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(v, v, 2, 3), one, c, false);
+  c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(v, v, 4, 5), one, c, false);
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(v, v, 6, 7), one, c, false);
+}
+
 // The kernel's body: workgroup `bid` of `nblk` that share the tiles of one network's minibatch.
 template <int H, int NOUT, int DMAX, class LossFn>
 __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const LossFn& fn, const unsigned bid, const unsigned nblk) {
   constexpr int BM = kFusedTile, NW = H / 32, THREADS = 64 * NW, PLANE = BM * H, Q1 = DMAX / 32, XBUF = BM * DMAX;
   constexpr int XR = 8 / NW;                            // rows of X a lane stages of each 32-column block
   constexpr int P3 = H + 8, PLANE3 = 8 * P3, PD = BM + 8, AS = NOUT + 5, RING = 2;
+  // The next tile's rows are requested behind layer 2 or, where their registers would be spilled, behind dW2 (64 units, 27 inputs,
+  // 2 097 152 samples: 636 us behind layer 2, 660 us behind dW2; 128 units, 75 inputs, 98 304 samples: 117 us and 97 us).
+  constexpr bool X_EARLY = H == 64;
   constexpr int TI = NW == 4 ? 2 : 1, TJ = 2;           // dW2: a wavefront's block of 32 x 32 tiles
   static_assert((H == 64 || H == 128) && (DMAX == 32 || DMAX == 96), "tile shapes");
   extern __shared__ __attribute__((aligned(16))) bf16_t fused_lds[];
   bf16_t* const tA = fused_lds;                         // [3][BM][H] h1, later dz1
   bf16_t* const tB = tA + 3 * PLANE;                    // [3][BM][H] h2, later dz2
   bf16_t* const xs = tB + 3 * PLANE;                    // exact: [2][Q1][BM][32]; else one block as [3][BM][32]
-  bf16_t* const w3t = xs + (2 * XBUF > 3072 ? 2 * XBUF : 3072);  // [3][8][P3] W3 transposed, split, rows past NOUT zero
+  float* const outp = reinterpret_cast<float*>(xs + 2 * XBUF);   // [NW][BM][8] every wavefront's share of the outputs
+  bf16_t* const w3t = xs + fused_train_x_region(H, DMAX);        // [3][8][P3] W3 transposed, split, rows past NOUT zero
   bf16_t* const dlt = w3t + 3 * PLANE3;                 // [3][8][PD] dL/d(output), split and transposed
   float* const bias = reinterpret_cast<float*>(dlt + 24 * PD);  // [2][H]
   float* const dls = bias + 2 * H;                      // [BM][8] dL/d(output), zeros past NOUT
   float* const w3s = dls + BM * 8;                      // [H][NOUT]
   float* const accS = w3s + H * NOUT;                   // [BM][AS] per sample slot: b3 gradient, loss statistics
-  int* const inexact = reinterpret_cast<int*>(accS + BM * AS);
+  float* const b3s = accS + BM * AS;                    // [8]
+  typedef decltype(fn.prepare()) Prep;                  // two floats
+  Prep* const prep = reinterpret_cast<Prep*>(b3s + 8);
+  int* const inexact = reinterpret_cast<int*>(b3s + 10);
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63;
@@ -94,11 +117,11 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
   for (int e = tid; e < BM * 8; e += THREADS) dls[e] = 0.f;
   for (int e = tid; e < BM * AS; e += THREADS) accS[e] = 0.f;
-  if (tid == 0) *inexact = 0;
-  float bias3[NOUT];
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) bias3[k] = a.b3[k];
-  const auto prep = fn.prepare();
+  if (tid < NOUT) b3s[tid] = a.b3[tid];
+  if (tid == 0) {
+    *inexact = 0;
+    *prep = fn.prepare();
+  }
 
   // ---- weights: k step `nxt` of the sequence layer 1, layer 2, dz1, and again for the next tile
   const int steps1 = a.Kp / 16, total = steps1 + 2 * (H / 16);
@@ -114,14 +137,16 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
 #pragma unroll
   for (int u = 0; u < RING; ++u) load_w(u);
 
+  // dW2: this wavefront's block of tiles; of its two columns, the one whose sums (the b2 gradient) it takes
+  const int it0 = NW == 4 ? 2 * (wave >> 1) : wave, jt0 = NW == 4 ? 2 * (wave & 1) : 0, gb2_j = NW == 4 ? wave >> 1 : wave;
+  const int loss_wave = (bid >> 8) % NW;  // (workgroups 256 apart share a CU: another SIMD for each)
   floatx16 acc1[Q1], acc2[TI * TJ];  // dW1 / dW2 tiles of this wavefront, persistent
   floatx16 acc, h1, h2;              // a product; this wavefront's units of the samples (element r: unit 8 (r / 4) + 4 hi + r % 4, sample lo)
   typedef float f4 __attribute__((ext_vector_type(4)));
   f4 gw[2];                          // W3 gradient: units 32 wave + 16 u + 4 (lane / 16) + r, output lane % 16
-  float gb2[16];                     // b2 gradient of the units of `acc`, this lane's sample slot
+  float gb2 = 0.f;                   // b2 gradient of unit 32 * block gb2_block + lo, the samples of 8 hi .. 8 hi + 7 mod 16
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    gb2[r] = 0.f;
 #pragma unroll
     for (int q = 0; q < Q1; ++q) acc1[q][r] = 0.f;
 #pragma unroll
@@ -146,11 +171,11 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   auto product = [&](const bf16_t* tile, int plane, int steps, auto x32, auto one) {
     constexpr bool X32 = decltype(x32)::value, ONE = decltype(one)::value;
     constexpr int PITCH = X32 ? 32 : H;
-    const bf16_t* const row = tile + lo * PITCH;
-    const int sw = hi ^ tile_swizzle<PITCH>(lo);
+    // (a row's units stand within an aligned block of its size: the step is an exclusive or on the offset)
+    const int off0 = (int)(tile - fused_lds) + lo * PITCH + ((hi ^ tile_swizzle<PITCH>(lo)) << 3);
     Split8 x[2];
     auto read = [&](int step) {
-      const bf16_t* const p = X32 ? row + (step >> 1) * (BM * 32) + ((sw ^ (2 * (step & 1))) << 3) : row + ((sw ^ (2 * step)) << 3);
+      const bf16_t* const p = fused_lds + (X32 ? (step >> 1) * (BM * 32) + (off0 ^ (step & 1) << 4) : off0 ^ step << 4);
       if (!ONE) return frag_row(p, plane);
       Split8 f;
       f.h = *reinterpret_cast<const bf16x8*>(p);
@@ -208,10 +233,10 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     }
   };
   auto store_gradient = [&](bf16_t* tile, const floatx16& v) {
-    float top = 0.f;
+    float top = 0.f;  // (a NaN stays one: split with its neighbour it would reach that unit's weight gradient)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) top = fmaxf(top, fabsf(v[r]));
-    const bool wild = split_out_of_range(top);
+    for (int r = 0; r < 16; ++r) top = __builtin_elementwise_maximum(top, fabsf(v[r]));
+    const bool wild = __builtin_amdgcn_ballot_w64(!(top < kSplitLimit)) != 0;
 #pragma unroll
     for (int g4 = 0; g4 < 4; ++g4) store4(tile, g4, make_float4(v[4 * g4], v[4 * g4 + 1], v[4 * g4 + 2], v[4 * g4 + 3]), wild);
   };
@@ -226,9 +251,21 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
 #pragma unroll
     for (int i = 0; i < XR; ++i) xentry[i] = a.X.template gather_entry<true>(min(tile * BM + x_row(i), a.S - 1));
   };
-  auto load_x = [&](int64_t tile, int i, int q) {
-    const float* const row = a.X.template ptr_with<true>(min(tile * BM + x_row(i), a.S - 1), xentry[i]);
-    xr[q][i] = *reinterpret_cast<const f2*>(row + min(32 * q + 2 * l15, a.Din - 2));
+  // (32-bit products: the general address of RowSrc was a tenth of the tile's vector instructions)
+  const uint32_t row_floats = (uint32_t)a.X.ld, entry_floats = (uint32_t)(a.X.per * a.X.ld);
+  auto x_ptr = [&](int64_t tile, int i) {
+    const uint32_t smp = (uint32_t)min(tile * BM + x_row(i), a.S - 1);
+    const uint32_t agent = smp - (uint32_t)a.X.pd.template div<true>(smp, a.X.per) * (uint32_t)a.X.per;
+    return a.X.base + ((uint64_t)(uint32_t)xentry[i] * entry_floats + agent * row_floats);
+  };
+  auto x_col = [&](int q) { return min(32 * q + 2 * l15, a.Din - 2); };
+  auto request_x = [&](int64_t tile) {
+#pragma unroll
+    for (int i = 0; i < XR; ++i) {
+      const float* const row = x_ptr(min(tile, ntiles - 1), i);
+#pragma unroll
+      for (int q = 0; q < Q1; ++q) xr[q][i] = *reinterpret_cast<const f2*>(row + x_col(q));
+    }
   };
   auto fix_x = [&](int i, int q) {
     const int c = 32 * q + 2 * l15;
@@ -257,7 +294,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < XR; ++i) {
-      const f2 v = *reinterpret_cast<const f2*>(a.X.template ptr_with<true>(min(t * BM + x_row(i), a.S - 1), xentry[i]) + min(32 * q + 2 * l15, a.Din - 2));
+      const f2 v = *reinterpret_cast<const f2*>(x_ptr(t, i) + x_col(q));
       const int c = 32 * q + 2 * l15;
       const SplitPair s = split_pair_any(c >= a.Din ? 0.f : c == a.Din - 1 ? v.y : v.x, c + 1 < a.Din ? v.y : c + 1 == DMAX - 1 ? 1.f : 0.f);
       uint32_t* const d = reinterpret_cast<uint32_t*>(xs + x_slot(i));
@@ -277,8 +314,9 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       const int64_t s0 = t * BM;
       const bool more = t + nblk < ntiles;  // uniform
       bf16_t* const X = EXACT ? xs + (it & 1) * XBUF : xs;
-      const int64_t smp = s0 + 16 * min(wave, 1) + l15;  // the sample whose loss the first sixteen lanes of wavefronts 0 and 1 take
-      const int32_t lentry = fn.template row_entry<true>(min(smp, a.S - 1));
+      const int64_t smp = s0 + lo;  // the sample whose loss a lane of the wavefront `loss_wave` takes
+      int32_t lentry = 0;
+      if (wave == loss_wave) lentry = fn.template row_entry<true>(min(smp, a.S - 1));
       fetch_entries(EXACT ? min(t + nblk, ntiles - 1) : t);
       // ---- layer 1
       zero_acc();
@@ -296,50 +334,56 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       // ---- layer 2
       zero_acc();
       product(tA, PLANE, H / 16, std::false_type{}, std::false_type{});
-      const typename LossFn::In lin = fn.template load_with<true>(min(smp, a.S - 1), lentry);
-      if constexpr (EXACT) {
-#pragma unroll
-        for (int i = 0; i < XR; ++i)
-#pragma unroll
-          for (int q = 0; q < Q1; ++q) load_x(min(t + nblk, ntiles - 1), i, q);
-      }
+      typename LossFn::In lin;
+      if (wave == loss_wave) lin = fn.template load_with<true>(min(smp, a.S - 1), lentry);
+      if (EXACT && X_EARLY) request_x(t + nblk);
       tanh_out(tB, bias + H, h2);
-      __syncthreads();
-      // ---- output layer: W3^T x h2 for sixteen samples a wavefront; outputs 0 .. 3 land in lanes 0 .. 15, 4 .. 7 in the next sixteen
-      if (wave < 2) {
-        f4 o = {0.f, 0.f, 0.f, 0.f}, small = {0.f, 0.f, 0.f, 0.f};
-        const int row = 16 * wave + l15, sw = l4 ^ tile_swizzle<H>(row);
-#pragma unroll 2
-        for (int k = 0; k < H; k += 32) {
-          const Split8 wv = frag_row(&w3t[(lane & 7) * P3 + k + 8 * l4], PLANE3), xv = frag_row(&tB[row * H + ((sw ^ (k / 8)) << 3)], PLANE);
-          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.h, xv.l, small, 0, 0, 0);
-          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.l, xv.h, small, 0, 0, 0);
-          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.m, xv.m, small, 0, 0, 0);
-          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.h, xv.m, small, 0, 0, 0);
-          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.m, xv.h, small, 0, 0, 0);
-          o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.h, xv.h, o, 0, 0, 0);
+      // ---- output layer: W3^T x h2 over this wavefront's units for sixteen samples at a time; outputs 0 .. 3 land in lanes 0 .. 15,
+      // 4 .. 7 in the next sixteen
+      {
+        const Split8 wv = frag_row(&w3t[(lane & 7) * P3 + 32 * wave + 8 * l4], PLANE3);
+        Split8 xv[2];
+        f4 o[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int g = 0; g < 2; ++g) xv[g] = frag_row(&tB[(16 * g + l15) * H + (((4 * wave + l4) ^ tile_swizzle<H>(l15)) << 3)], PLANE);
+#define MARL_OUT(WP, XP) \
+  _Pragma("unroll") for (int g = 0; g < 2; ++g) o[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv.WP, xv[g].XP, o[g], 0, 0, 0);
+        MARL_OUT(h, l)
+        MARL_OUT(l, h)
+        MARL_OUT(m, m)
+        MARL_OUT(h, m)
+        MARL_OUT(m, h)
+        MARL_OUT(h, h)
+#undef MARL_OUT
+        if (lane < (NOUT > 4 ? 32 : 16)) {
+#pragma unroll
+          for (int g = 0; g < 2; ++g) *reinterpret_cast<f4*>(&outp[(wave * BM + 16 * g + l15) * 8 + 4 * l4]) = o[g];
         }
-        const f4 v = small + o;
+      }
+      __syncthreads();
+      if (wave == loss_wave && lane < BM) {
         float out[NOUT], dl[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int k = 0; k < NOUT; ++k) {
-          out[k] = (k < 4 ? v[k & 3] : __shfl(v[k & 3], (lane + 16) & 63)) + bias3[k];
+          out[k] = b3s[k];
           dl[k] = 0.f;
         }
-        if (lane < 16) {
-          if (smp < a.S) fn.compute(lin, prep, out, dl, st);
 #pragma unroll
-          for (int k = 0; k < NOUT; ++k) {
-            accS[row * AS + k] += dl[k];
-            dls[row * 8 + k] = dl[k];
-            const SplitPair sp = split_pair_any(dl[k], 0.f);
-            dlt[k * PD + row] = (bf16_t)sp.h;
-            dlt[(8 + k) * PD + row] = (bf16_t)sp.m;
-            dlt[(16 + k) * PD + row] = (bf16_t)sp.l;
-          }
+        for (int z = 0; z < NW; ++z)
 #pragma unroll
-          for (int k = 0; k < 5; ++k) accS[row * AS + NOUT + k] += st[k];
+          for (int k = 0; k < NOUT; ++k) out[k] += outp[(z * BM + lo) * 8 + k];
+        if (smp < a.S) fn.compute(lin, *prep, out, dl, st);
+#pragma unroll
+        for (int k = 0; k < NOUT; ++k) {
+          accS[lo * AS + k] += dl[k];
+          dls[lo * 8 + k] = dl[k];
+          const SplitPair sp = split_pair_any(dl[k], 0.f);
+          dlt[k * PD + lo] = (bf16_t)sp.h;
+          dlt[(8 + k) * PD + lo] = (bf16_t)sp.m;
+          dlt[(16 + k) * PD + lo] = (bf16_t)sp.l;
         }
+#pragma unroll
+        for (int k = 0; k < 5; ++k) accS[lo * AS + NOUT + k] += st[k];
       }
       __syncthreads();
       // From here to the next barrier a wavefront reads and writes nothing of B but its own columns.
@@ -378,7 +422,6 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           acc[r] *= 1.0f - h2[r] * h2[r];
-          gb2[r] += acc[r];
         }
         store_gradient(tB, acc);
       }
@@ -386,17 +429,18 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       // ---- dW2 += h1^T dz2
 #pragma unroll
       for (int kb = 0; kb < BM; kb += 16) {
-        const int it0 = NW == 4 ? 2 * (wave >> 1) : wave, jt0 = NW == 4 ? 2 * (wave & 1) : 0;
         Split8 x[TI];
 #pragma unroll
         for (int i = 0; i < TI; ++i) x[i] = col_split(tA, PLANE, TileP{}, it0 + i, kb);
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
           const Split8 y = col_split(tB, PLANE, TileP{}, jt0 + j, kb);
+          if (j == gb2_j) gb2 = sum8(y.h, sum8(y.m, sum8(y.l, gb2)));  // uniform
 #pragma unroll
           for (int i = 0; i < TI; ++i) acc2[i * TJ + j] = mfma_split(x[i], y, acc2[i * TJ + j]);
         }
       }
+      if (EXACT && !X_EARLY) request_x(t + nblk);
       // ---- dz1 = (W2 dz2^T) (1 - h1^2) over h1
       zero_acc();
       product(tB, PLANE, H / 16, std::false_type{}, std::false_type{});
@@ -433,10 +477,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   };
   if (t < ntiles) {
     fetch_entries(t);
-#pragma unroll
-    for (int i = 0; i < XR; ++i)
-#pragma unroll
-      for (int q = 0; q < Q1; ++q) load_x(t, i, q);
+    request_x(t);
   }
   __syncthreads();  // what was set up above, *inexact first of all
   if (t < ntiles) store_x(xs);
@@ -452,7 +493,6 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   float* const gW2 = gb1 + H;
   float* const gb2o = gW2 + H * H;
   float* const gW3 = gb2o + H;
-  const int it0 = NW == 4 ? 2 * (wave >> 1) : wave, jt0 = NW == 4 ? 2 * (wave & 1) : 0;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int row = 8 * (r / 4) + 4 * hi + (r % 4);
@@ -464,11 +504,9 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       if (d < a.Din) gW1[d * H + 32 * wave + lo] = acc1[q][r];
       if (d == DMAX - 1) gb1[32 * wave + lo] = acc1[q][r];
     }
-    float v = gb2[r];
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (lo == 0) gb2o[32 * wave + row] = v;
   }
+  gb2 += __shfl_xor(gb2, 32);
+  if (hi == 0) gb2o[32 * (jt0 + gb2_j) + lo] = gb2;
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll

@@ -27,7 +27,7 @@ struct SmallDiv {
   int shift = 0;
   template <bool FAST>
   __device__ __forceinline__ int64_t div(int64_t s, int d) const {
-    if (FAST) return (int64_t)(((uint64_t)(uint32_t)s * magic) >> shift);
+    if (FAST) return (int64_t)(__umulhi(2 * (uint32_t)s, magic) >> (shift - 31));  // s * magic >> shift, the upper half of one 32-bit product
     return s / d;
   }
 };
@@ -146,19 +146,17 @@ __device__ __forceinline__ float tanh_f32(float x) {
   return 1.0f - 2.0f * __builtin_amdgcn_rcpf(e + 1.0f);
 }
 
-// Products of a row tile against weights: A, the activations, in LDS as fp32 (split into bf16 parts on the way to the
-// instruction), B from a split operand-order copy of the weights (ParamMap) straight from the cache hierarchy into
+// Products of a row tile against weights: the weights from a split operand-order copy (ParamMap) straight from the cache hierarchy into
 // registers, so that a layer needs no staging buffer and no barrier of its own.  The first kPhaseRing groups of 16 along k
 // are requested one phase AHEAD of the product -- during the element-wise epilogue or the LDS-only product in front of it
 // -- and the others as their slots become free, so that the product does not wait for the L2.  The loads are buffer
 // loads: a resource descriptor in scalar registers, ONE vector register with the lane's byte offset for all of them, the
 // group's offset as a scalar (as global loads each of them got a 64-bit address register pair of its own).
-// NT column tiles of 32 side by side share their rows of A.
 constexpr int kPhaseRing = 4;
-template <int KG, int NT = 1>
+template <int KG>
 struct PhaseW {
   static constexpr int RING = KG < kPhaseRing ? KG : kPhaseRing;
-  bf16x8 w[RING][NT][3];
+  bf16x8 w[RING][3];
 };
 typedef __amdgpu_buffer_rsrc_t WeightRsrc;
 // descriptor of `floats` floats at p (raw buffer, no swizzle; reads past the end return zero)
@@ -168,42 +166,17 @@ __device__ __forceinline__ WeightRsrc weight_rsrc(const float* p, int floats) {
 // descriptor of a split [K][H] copy
 __device__ __forceinline__ WeightRsrc split_weight_rsrc(const float* p, int K, int H) { return weight_rsrc(p, K * H * 3 / 2); }
 // lane_off: (hi * H + n) * 4 for this lane's column n
-template <int H, int KG, int NT>
-__device__ __forceinline__ void phase_w_load_at(PhaseW<KG, NT>& pw, int slot, WeightRsrc B, int lane_off, int g) {
+template <int H, int KG>
+__device__ __forceinline__ void phase_w_load(PhaseW<KG>& pw, WeightRsrc B, int lane_off, int g, int kgroups) {
+  const int at = g < kgroups ? g : kgroups - 1;  // past the end: the last group again (never used)
 #pragma unroll
-  for (int q = 0; q < NT; ++q)
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-      pw.w[slot][q][p] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(B, lane_off * 4 + 512 * q, (g * 3 + p) * 32 * H, 0));
+  for (int p = 0; p < 3; ++p)
+    pw.w[g % PhaseW<KG>::RING][p] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(B, lane_off * 4, (at * 3 + p) * 32 * H, 0));
 }
-template <int H, int KG, int NT>
-__device__ __forceinline__ void phase_w_load(PhaseW<KG, NT>& pw, WeightRsrc B, int lane_off, int g, int kgroups) {
-  phase_w_load_at<H>(pw, g % PhaseW<KG, NT>::RING, B, lane_off, g < kgroups ? g : kgroups - 1);  // past the end: the last group again (never used)
-}
-template <int H, int KG, int NT = 1>
-__device__ __forceinline__ void phase_w_request(PhaseW<KG, NT>& pw, WeightRsrc B, int lane_off, int kgroups) {
+template <int H, int KG>
+__device__ __forceinline__ void phase_w_request(PhaseW<KG>& pw, WeightRsrc B, int lane_off, int kgroups) {
 #pragma unroll
-  for (int g = 0; g < PhaseW<KG, NT>::RING; ++g) phase_w_load<H>(pw, B, lane_off, g, kgroups);
-}
-// acc[q] += A B_q for this wavefront's 32x32 tiles: A rows in LDS (As points at this lane's row, + 8 * hi; the values of
-// the next group are read before the matrix instructions of the current one).  Both operands are readable (zero-padded) up
-// to 16 * kgroups along k.  ANY: A may hold values out of split_pair's range.
-template <int H, bool ANY, int KG, int NT = 1>
-__device__ __forceinline__ void gemm_phase_w(const float* __restrict__ As, WeightRsrc B, int lane_off, int kgroups, floatx16* acc, PhaseW<KG, NT>& pw) {
-  constexpr int RING = PhaseW<KG, NT>::RING;
-  float4 a0 = *reinterpret_cast<const float4*>(As), a1 = *reinterpret_cast<const float4*>(As + 4);
-#pragma unroll
-  for (int g = 0; g < KG; ++g) {
-    if (g < kgroups) {  // uniform
-      const Split8 a = split8<ANY>(a0, a1);
-      const int gn = g + 1 < kgroups ? g + 1 : g;
-      a0 = *reinterpret_cast<const float4*>(As + 16 * gn);
-      a1 = *reinterpret_cast<const float4*>(As + 16 * gn + 4);
-#pragma unroll
-      for (int q = 0; q < NT; ++q) acc[q] = mfma_split(a, Split8{pw.w[g % RING][q][0], pw.w[g % RING][q][1], pw.w[g % RING][q][2]}, acc[q]);
-      if (g + RING < KG) phase_w_load<H>(pw, B, lane_off, g + RING, kgroups);
-    }
-  }
+  for (int g = 0; g < PhaseW<KG>::RING; ++g) phase_w_load<H>(pw, B, lane_off, g, kgroups);
 }
 // The transposed product, weights x samples: acc += B^T A^T for this wavefront's 32 units x 32 samples, so that a lane holds
 // four times four consecutive units of one sample.  A by rows of split planes in LDS (xs points at this lane's row, + 8 * hi;
@@ -214,7 +187,7 @@ __device__ __forceinline__ void gemm_phase_t(const bf16_t* xs, int plane, Weight
 #pragma unroll
   for (int g = 0; g < KG; ++g) {
     if (g < kgroups) {  // uniform
-      const Split8 w{pw.w[g % RING][0][0], pw.w[g % RING][0][1], pw.w[g % RING][0][2]};
+      const Split8 w{pw.w[g % RING][0], pw.w[g % RING][1], pw.w[g % RING][2]};
       if (EXACT) {
         const bf16x8 x = *reinterpret_cast<const bf16x8*>(xs + 16 * g);
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w.l, x, acc, 0, 0, 0);
