@@ -442,7 +442,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
       if (lane == 0) G2[wave * (NOUT + 5) + k] = v;
     }
     __syncthreads();
-    float* const own = a.partial + (int64_t)blockIdx.x * COUNT;
+    float* const own = a.partial + blockIdx.x * copy_pitch(COUNT);
     for (int e = tid; e < COUNT; e += THREADS) {
       float v = 0.f;
       if (e < H * NOUT) {

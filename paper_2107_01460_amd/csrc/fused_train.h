@@ -542,7 +542,7 @@ inline int64_t fused_train_grid(int H, int Din, int64_t S) {
   return std::min<int64_t>(fused_train_tiles(S), H == 128 ? 512 : Din < 32 ? 1024 : 768);
 }
 // Floats of the copies of a network's gradient and statistics.
-inline int64_t fused_train_partial_floats(int H, int Din, int64_t S, int64_t gcount) { return fused_train_grid(H, Din, S) * (gcount + 5); }
+inline int64_t fused_train_partial_floats(int H, int Din, int64_t S, int64_t gcount) { return fused_train_grid(H, Din, S) * copy_pitch(gcount + 5); }
 
 template <class Kernel>
 inline int32_t fused_train_configure(Kernel kern, size_t bytes) {
@@ -558,10 +558,10 @@ inline int32_t launch_fused_train_inst(FusedTrainArgs a, const LossFn& fn, hipSt
   if (rc != MARL_OK) return rc;
   const unsigned grid = (unsigned)fused_train_grid(H, a.Din, a.S);
   a.stats_at = a.gcount;
-  a.pstride = a.gcount + 5;
+  a.pstride = copy_pitch(a.gcount + 5);
   a.stats_mask = 31;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(2 * H), bytes, s, a, fn);
-  launch_reduce_partials(a.partial, (int)grid, a.pstride, a.grad, s, a.gcount, a.stats);
+  launch_reduce_partials(a.partial, (int)grid, a.gcount + 5, a.grad, s, a.gcount, a.stats);
   return launch_status();
 }
 
@@ -574,14 +574,14 @@ inline int32_t launch_fused_train_pair_inst(FusedTrainArgs a, const LossA& fa, F
   const unsigned grid_a = (unsigned)fused_train_tiles(a.S);  // == the second network's (the caller checks the sizes)
   // copy k of the first network's range is directly followed by copy k of the second's and by their statistics: one reduction
   b.partial = a.partial + a.gcount;
-  a.pstride = b.pstride = a.gcount + b.gcount + 5;
+  a.pstride = b.pstride = copy_pitch(a.gcount + b.gcount + 5);
   a.stats_at = a.gcount + b.gcount;
   b.stats_at = b.gcount;
   a.stats_mask = LossA::kStats;
   b.stats_mask = LossB::kStats;
   static_assert((LossA::kStats & LossB::kStats) == 0 && (LossA::kStats | LossB::kStats) == 31, "every statistic from one network");
   hipLaunchKernelGGL(kern, dim3(2 * grid_a), dim3(2 * H), bytes, s, a, fa, b, fb, grid_a);
-  launch_reduce_partials(a.partial, (int)grid_a, a.pstride, a.grad, s, a.gcount + b.gcount, a.stats);
+  launch_reduce_partials(a.partial, (int)grid_a, a.gcount + b.gcount + 5, a.grad, s, a.gcount + b.gcount, a.stats);
   return launch_status();
 }
 
@@ -607,7 +607,7 @@ inline bool fused_train_pair_supported(int Ha, int Da, int64_t Sa, int Hb, int D
   return 2 * fused_train_tiles(Sa) <= (Ha == 128 ? 512 : Da < 32 ? 1024 : 768);
 }
 // Floats of the copies of both.
-inline int64_t fused_train_pair_partial_floats(int64_t S, int64_t gcount_a, int64_t gcount_b) { return fused_train_tiles(S) * (gcount_a + gcount_b + 5); }
+inline int64_t fused_train_pair_partial_floats(int64_t S, int64_t gcount_a, int64_t gcount_b) { return fused_train_tiles(S) * copy_pitch(gcount_a + gcount_b + 5); }
 
 // b.grad == a.grad + a.gcount
 template <int NOUT_A, int NOUT_B, class LossA, class LossB>

@@ -262,7 +262,7 @@ struct CriticLoss {
 // tile's loads, already in flight, cover.
 constexpr int kLossHeadGrid = 512;
 constexpr int kLossTile = 32;
-inline int64_t loss_head_partial_floats(int H, int nout) { return (int64_t)kLossHeadGrid * (H * nout + nout); }
+inline int64_t loss_head_partial_floats(int H, int nout) { return kLossHeadGrid * copy_pitch(H * nout + nout); }
 inline size_t loss_head_lds(int H, int nout) { return sizeof(float) * (kLossTile * (H + 4) + H * nout + 8 * nout * kLossTile + kLossTile * 8); }
 
 // NQ: 16-byte pieces of a row per staging thread, at least H / 32 (the last piece again beyond that)
@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(256, 2) loss_head_kernel(float* H2, int64_t S,
     }
     __syncthreads();  // the tile has been read
   }
-  float* const own = partial + (int64_t)blockIdx.x * (H * NOUT + NOUT);
+  float* const own = partial + blockIdx.x * copy_pitch(H * NOUT + NOUT);
   if (parts == 2) {  // H <= 128: the two halves of the samples
     if (part == 1) {
 #pragma unroll

@@ -86,7 +86,7 @@ UpdateWsView carve_update_ws(const marl_config& c, void* ws, int64_t* total) {
     v.bh1 = (bf16_t*)take(SH * 2);
     v.bdz2 = (bf16_t*)take(SH * 2);
     v.bdz1 = (bf16_t*)take(SH * 2);
-    v.partial_head = (float*)take(std::max(bf16_net_grid(d.Ha) * bf16_net_partial_floats(d.Ha, kActions), bf16_net_grid(d.Hc) * bf16_net_partial_floats(d.Hc, 1)) * 4);
+    v.partial_head = (float*)take(std::max(bf16_net_grid(d.Ha) * copy_pitch(bf16_net_partial_floats(d.Ha, kActions)), bf16_net_grid(d.Hc) * copy_pitch(bf16_net_partial_floats(d.Hc, 1))) * 4);
     v.split_ws = (float*)take(std::max(std::max(bf16_wgrad_floats(false, d.Ha, d.Ha, Sa), bf16_wgrad_floats(true, d.D, d.Ha, Sa)),
                                        std::max(bf16_wgrad_floats(false, d.Hc, d.Hc, Sc), bf16_wgrad_floats(true, d.Dc, d.Hc, Sc))) * 4);
   }

@@ -444,7 +444,7 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
       if (lane == 0) G2[wave * (NOUT + 5) + k] = v;
     }
     __syncthreads();
-    float* const own = a.partial + (int64_t)blockIdx.x * COUNT;
+    float* const own = a.partial + blockIdx.x * copy_pitch(COUNT);
     for (int e = tid; e < COUNT; e += THREADS) {
       float v = 0.f;
       if (e < H * NOUT) {
@@ -463,7 +463,7 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
 // 192 units: 132 us with as many as it holds, 104 with twice as many).
 constexpr unsigned split_net_grid(int H, int BM) { return H <= 128 ? 2048 : H <= 256 && BM == 32 ? 1024 : 512; }
 constexpr int kSplitTrainRows = 32;
-inline int64_t split_net_partial_floats(int H, int nout) { return split_net_grid(H, kSplitTrainRows) * ((int64_t)H * nout + nout + 5); }
+inline int64_t split_net_partial_floats(int H, int nout) { return split_net_grid(H, kSplitTrainRows) * copy_pitch((int64_t)H * nout + nout + 5); }
 
 template <int H, int BM, int NOUT, bool TRAIN, class Fin>
 inline int32_t launch_split_net_inst(const SplitNetArgs& a, const Fin& fin, unsigned* grid_out, hipStream_t s) {
