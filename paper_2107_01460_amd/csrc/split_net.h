@@ -18,6 +18,7 @@
 // before layer 2's product, so that no weight waits behind it: 720 -> 759 us.
 #pragma once
 #include <type_traits>
+#include <utility>
 
 #include "gemm.h"
 #include "heads.h"
@@ -45,14 +46,17 @@ struct SplitNetShape {
   // the wavefronts of a workgroup are dealt 2, 2, 1, 1)
   static constexpr int waves(bool train) { return train ? (NW > 8 ? 3 : 4) : NW > 8 ? 3 : H <= 128 ? 4 : 2; }
   static constexpr size_t lds(bool train, int nout) {
-    return sizeof(bf16_t) * 3 * (BM + 8) * P + sizeof(float) * (2 * H + 4) + (train ? sizeof(bf16_t) * 24 * PD + sizeof(float) * (BM * 8 + H * (nout > 1 ? 8 : 1)) : 0);
+    return sizeof(bf16_t) * 3 * (BM + 8) * P + sizeof(float) * (2 * H + 16) + (train ? sizeof(bf16_t) * 24 * PD + sizeof(float) * (BM * 8 + H * (nout > 1 ? 8 : 1) + BM * (nout + 5)) : 0);
   }
 };
 
 template <bool TRAIN, class Fin>
-struct SplitNetLossIn { typedef int type; };
+struct SplitNetLossIn { typedef int type, Prep; };
 template <class Fin>
-struct SplitNetLossIn<true, Fin> { typedef typename Fin::In type; };
+struct SplitNetLossIn<true, Fin> {
+  typedef typename Fin::In type;
+  typedef decltype(std::declval<Fin>().prepare()) Prep;  // two floats
+};
 
 // Fin: TRAIN: a loss functor (ActorLoss, CriticLoss); else what becomes of a sample's outputs, fin(s, out, nullptr, nullptr).
 template <int H, int BM, int NOUT, bool TRAIN, class Fin>
@@ -63,7 +67,7 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
   constexpr int XJ = H < 128 ? 1 : H < 192 ? 2 : 3;        // 64-column pieces of the input that are staged at a time
   constexpr int XR = (BM / 2 + NW - 1) / NW;               // pairs of input rows a wavefront stages
   constexpr int GPW = (BM / 16 + NW - 1) / NW;             // groups of 16 samples whose outputs a wavefront takes
-  constexpr int W3P = NOUT > 1 ? 8 : 1;
+  constexpr int W3P = NOUT > 1 ? 8 : 1, AS = NOUT + 5;
   // Forward passes above 128 units: the next tile's first piece of input waits in registers, and exact inputs take half of layer 1's
   // products (2.1 million samples, 300 inputs, 256 units: 3.61 -> 2.99 ms).  In training and in narrow networks other workgroups of the
   // CU cover the input's latency, and the registers are wanted for them (16.9 million samples, 27 inputs, 64 units: 2.23 ms with the
@@ -74,9 +78,12 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
   bf16_t* const w3t = tile + 3 * PLANE;                          // [3][8][P]  W3 transposed, split, rows past NOUT zero
   float* const bias = reinterpret_cast<float*>(w3t + 3 * PLANE3);  // [2][H]
   int* const inexact = reinterpret_cast<int*>(bias + 2 * H);     // [4] is a value of the tile's input not exact in bf16?
-  float* const dls = bias + 2 * H + 4;                           // TRAIN: [BM][8] dL/d(output), zeros past NOUT
+  float* const b3s = bias + 2 * H + 4;                           // [8]
+  auto* const prep = reinterpret_cast<typename SplitNetLossIn<TRAIN, Fin>::Prep*>(b3s + 8);  // TRAIN
+  float* const dls = bias + 2 * H + 16;                          // TRAIN: [BM][8] dL/d(output), zeros past NOUT
   float* const w3s = dls + BM * 8;                               // TRAIN: [H][W3P]
-  bf16_t* const dlt = reinterpret_cast<bf16_t*>(w3s + H * W3P);  // TRAIN: [3][8][PD] dL/d(output), split and transposed
+  float* const accS = w3s + H * W3P;                             // TRAIN: [BM][AS] per sample slot: b3 gradient, loss statistics
+  bf16_t* const dlt = reinterpret_cast<bf16_t*>(accS + BM * AS);  // TRAIN: [3][8][PD] dL/d(output), split and transposed
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63, lo = lane & 31, hi = lane >> 5, l15 = lane & 15, l4 = lane >> 4;
@@ -99,10 +106,12 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
     for (int e = tid; e < H * W3P; e += THREADS) w3s[e] = e % W3P < NOUT ? a.W3[e / W3P * NOUT + e % W3P] : 0.f;
     for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
     for (int e = tid; e < BM * 8; e += THREADS) dls[e] = 0.f;
+    for (int e = tid; e < BM * AS; e += THREADS) accS[e] = 0.f;
+    if constexpr (TRAIN) {
+      if (tid == 0) *prep = fin.prepare();
+    }
   }
-  float bias3[NOUT];
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) bias3[k] = a.b3[k];
+  if (tid < NOUT) b3s[tid] = a.b3[tid];
 
   // ---- weights: k step `nxt` of the sequence layer 1, layer 2 (, dz1), and again for the next tile
   const int steps1 = a.Kp / 16, total = steps1 + (TRAIN ? 2 : 1) * (H / 16);
@@ -248,12 +257,8 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
 
   typedef float f4 __attribute__((ext_vector_type(4)));
   f4 gw[2];  // TRAIN: W3 gradient: units 32 wn + 16 u + 4 l4 + r, output l15, this wavefront's samples
-  float gb[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
   floatx16 h1[TRAIN ? MT : 1], h2[TRAIN ? MT : 1];
   gw[0] = gw[1] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) gb[k] = 0.f;
-
   if ((int64_t)blockIdx.x < ntiles) {
     row_offsets(blockIdx.x);
     if (AHEAD) load_x(0);
@@ -268,7 +273,8 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
     [[maybe_unused]] int32_t entry[GPW];
     if constexpr (TRAIN) {
 #pragma unroll
-      for (int g = 0; g < GPW; ++g) entry[g] = fin.template row_entry<true>(min(s0 + min(16 * (wave + NW * g), BM - 16) + l15, a.S - 1));
+      for (int g = 0; g < GPW; ++g)
+        if (wave + NW * g < BM / 16) entry[g] = fin.template row_entry<true>(min(s0 + min(16 * (wave + NW * g), BM - 16) + l15, a.S - 1));
     }
     // ---- layer 1
     zero_acc();
@@ -294,7 +300,8 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
     typename SplitNetLossIn<TRAIN, Fin>::type lin[GPW];
     if constexpr (TRAIN) {
 #pragma unroll
-      for (int g = 0; g < GPW; ++g) lin[g] = fin.template load_with<true>(min(s0 + min(16 * (wave + NW * g), BM - 16) + l15, a.S - 1), entry[g]);
+      for (int g = 0; g < GPW; ++g)
+        if (wave + NW * g < BM / 16) lin[g] = fin.template load_with<true>(min(s0 + min(16 * (wave + NW * g), BM - 16) + l15, a.S - 1), entry[g]);
     }
     __syncthreads();
     tanh_out(bias + H, h2);
@@ -318,7 +325,7 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
         }
         const f4 v = small + o;
 #pragma unroll
-        for (int k = 0; k < NOUT; ++k) outs[g][k] = (k < 4 ? v[k & 3] : __shfl(v[k & 3], (lane + 16) & 63)) + bias3[k];
+        for (int k = 0; k < NOUT; ++k) outs[g][k] = (k < 4 ? v[k & 3] : __shfl(v[k & 3], (lane + 16) & 63)) + b3s[k];
       }
     }
     if constexpr (!TRAIN) {
@@ -329,25 +336,26 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
       }
       __syncthreads();  // the tile is free
     } else {
-      const auto prep = fin.prepare();
 #pragma unroll
       for (int g = 0; g < GPW; ++g) {
         const int grp = wave + NW * g;
         const int64_t s = s0 + 16 * grp + l15;
         if ((GPW * NW == BM / 16 || grp < BM / 16) && lane < 16) {
-          float dl[NOUT];
+          float dl[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int k = 0; k < NOUT; ++k) dl[k] = 0.f;
-          if (s < a.S) fin.compute(lin[g], prep, outs[g], dl, st);
+          if (s < a.S) fin.compute(lin[g], *prep, outs[g], dl, st);
 #pragma unroll
           for (int k = 0; k < NOUT; ++k) {
-            gb[k] += dl[k];
+            accS[(16 * grp + l15) * AS + k] += dl[k];
             dls[(16 * grp + l15) * 8 + k] = dl[k];
             const SplitPair sp = split_pair_any(dl[k], 0.f);
             dlt[k * PD + 16 * grp + l15] = (bf16_t)sp.h;
             dlt[(8 + k) * PD + 16 * grp + l15] = (bf16_t)sp.m;
             dlt[(16 + k) * PD + 16 * grp + l15] = (bf16_t)sp.l;
           }
+#pragma unroll
+          for (int k = 0; k < 5; ++k) accS[(16 * grp + l15) * AS + NOUT + k] += st[k];
         }
       }
       __syncthreads();
@@ -427,22 +435,15 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
     }
   }
   if constexpr (TRAIN) {
-    // this workgroup's sums: the WM wavefronts that share their columns and the NW that share the outputs meet in LDS
+    // this workgroup's sums: the WM wavefronts that share their columns meet in LDS
     constexpr int COUNT = H * NOUT + NOUT + 5;
-    float* const G = reinterpret_cast<float*>(tile);  // [WM][H * NOUT], [NW][NOUT + 5]
-    float* const G2 = G + WM * H * NOUT;
-    static_assert((WM * H * NOUT + NW * (NOUT + 5)) * 4 <= 3 * BM * P * 2, "room in the tile");
+    float* const G = reinterpret_cast<float*>(tile);  // [WM][H * NOUT]
+    static_assert(WM * H * NOUT * 4 <= 3 * BM * P * 2, "room in the tile");
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         if (l15 < NOUT) G[wm * H * NOUT + (32 * wn + 16 * u + 4 * l4 + r) * NOUT + l15] = gw[u][r];
-#pragma unroll
-    for (int k = 0; k < NOUT + 5; ++k) {
-      float v = k < NOUT ? gb[k < NOUT ? k : 0] : st[k < NOUT ? 0 : k - NOUT];
-      for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if (lane == 0) G2[wave * (NOUT + 5) + k] = v;
-    }
     __syncthreads();
     float* const own = a.partial + blockIdx.x * copy_pitch(COUNT);
     for (int e = tid; e < COUNT; e += THREADS) {
@@ -451,8 +452,7 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
 #pragma unroll
         for (int z = 0; z < WM; ++z) v += G[z * H * NOUT + e];
       } else {
-#pragma unroll
-        for (int z = 0; z < NW; ++z) v += G2[z * (NOUT + 5) + e - H * NOUT];
+        for (int z = 0; z < BM; ++z) v += accS[z * AS + e - H * NOUT];
       }
       own[e] = v;
     }
