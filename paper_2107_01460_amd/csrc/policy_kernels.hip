@@ -9,6 +9,7 @@
 #include "heads.h"
 #include "rollout_fused.h"
 #include "split_net.h"
+#include "stage_params.h"
 
 namespace marl {
 
@@ -16,41 +17,15 @@ int64_t effective_param_floats(const marl_config& c, bool update);
 
 namespace {
 
-__device__ __forceinline__ void store_split_weight(float* copy, float v, int64_t k, int64_t n, int H) {
-  const SplitPair s = split_pair_any(v, 0.f);
-  bf16_t* const d = reinterpret_cast<bf16_t*>(copy) + split_weight_index(k, n, H);
-  d[0] = (bf16_t)s.h;
-  d[split_weight_plane(H)] = (bf16_t)s.m;
-  d[2 * split_weight_plane(H)] = (bf16_t)s.l;
-}
-
-// Working copy of the parameters: blocks moved to their aligned offsets, optionally rounded to bf16, plus the copies of W1, W2
-// and W2 transposed that the fused kernels read.  for_rollout: the actor's in fp32 (ParamMap).
 __global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int round, int for_rollout, int for_update) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= pm.src[12]) return;
-  auto store = [&](int net, int64_t copy, float v, int64_t k, int64_t n) {
-    const int H = pm.hidden[net];
-    if (for_rollout && net == 0) dst[copy + ((k / 4) * H + n) * 4 + k % 4] = v;
-    else store_split_weight(dst + copy, v, k, n, H);
-  };
 #pragma unroll
   for (int net = 0; net < 2; ++net) {  // zero rows of the copies of W1 (fewer than 32 rows: far fewer floats than parameters)
     const int H = pm.hidden[net];
-    if (pm.fused[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) store(net, pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H);
+    if (pm.fused[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) stage_element(dst, pm, net, pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H, for_rollout != 0);
   }
-  int b = 0;
-#pragma unroll
-  for (int k = 1; k < 12; ++k) b += (i >= pm.src[k]) ? 1 : 0;
-  const float v = round ? round_to_bf16(src[i]) : src[i];
-  const int64_t e = i - pm.src[b];
-  const int net = b >= 6, H = pm.hidden[net];
-  const bool w1 = b == 0 || b == 6, w2 = b == 2 || b == 8;
-  if (pm.plain[net] || !(w1 || w2)) dst[pm.dst[b] + e] = v;
-  if (!pm.fused[net] || !(w1 || w2)) return;
-  const int64_t r = e / H, c = e - r * H;
-  store(net, w1 ? pm.sw_w1[net] : pm.sw_w2[net], v, r, c);
-  if (w2 && for_update) store_split_weight(dst + pm.sw_w2t[net], v, c, r, H);
+  stage_param(dst, pm, i, src[i], round != 0, for_rollout != 0, for_update != 0);
 }
 
 // What the rollout does with a sample's outputs.
@@ -189,16 +164,21 @@ Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, in
   return Bf16NetWeights{base + ((bf16_net_weight_elems(d.D, d.Ha) + 63) / 64) * 64, (int)round_up64(d.Dc)};
 }
 
+// The bf16 networks' weight copies (nothing for other configurations).
+void stage_bf16_weights(const marl_config& c, const float* params, float* scratch, hipStream_t s) {
+  const Dims d = dims_of(c);
+  if (!d.bf16) return;
+  const NetOffsets oa = net_offsets(0, d.D, d.Ha, kActions), oc = net_offsets(d.Pa, d.Dc, d.Hc, 1);
+  const Bf16NetWeights wa = effective_bf16_weights(c, scratch, 0), wc = effective_bf16_weights(c, scratch, 1);
+  launch_bf16_stage(Bf16StageNet{params + oa.W1, params + oa.W2, wa.w, d.D, wa.Kp, d.Ha},
+                    Bf16StageNet{params + oc.W1, params + oc.W2, wc.w, d.Dc, wc.Kp, d.Hc}, s);
+}
+
 const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use) {
   const Dims d = dims_of(c);
   hipLaunchKernelGGL(stage_params_kernel, dim3((unsigned)((d.P + 255) / 256)), dim3(256), 0, s, params, scratch,
                      param_map(d, use == USE_UPDATE), (int)d.bf16, (int)(use == USE_ROLLOUT && use_fused_rollout(c)), (int)(use == USE_UPDATE));
-  if (d.bf16) {
-    const NetOffsets oa = net_offsets(0, d.D, d.Ha, kActions), oc = net_offsets(d.Pa, d.Dc, d.Hc, 1);
-    const Bf16NetWeights wa = effective_bf16_weights(c, scratch, 0), wc = effective_bf16_weights(c, scratch, 1);
-    launch_bf16_stage(Bf16StageNet{params + oa.W1, params + oa.W2, wa.w, d.D, wa.Kp, d.Ha},
-                      Bf16StageNet{params + oc.W1, params + oc.W2, wc.w, d.Dc, wc.Kp, d.Hc}, s);
-  }
+  stage_bf16_weights(c, params, scratch, s);
   return scratch;
 }
 

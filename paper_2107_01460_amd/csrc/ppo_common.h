@@ -7,6 +7,7 @@
 
 #include "gemm.h"
 #include "heads.h"
+#include "stage_params.h"
 
 namespace marl {
 namespace {
@@ -456,12 +457,27 @@ struct AdamArgs {
   int k_local;            // corrections are computed on the device for step *k_base + k_local instead of bc1 / bc2
 };
 
+// What becomes of a new parameter besides its place in the parameter vector: nothing, or its places in the working copy that the next
+// optimiser step of the same update reads (a launch less per step; the copy's padding rows stay as the first step's staging left them).
+struct NoStage {
+  __device__ __forceinline__ void operator()(int64_t, float) const {}
+};
+struct StageNext {
+  float* dst;  // nullable: the update's last step
+  ParamMap pm;
+  int round;
+  __device__ __forceinline__ void operator()(int64_t i, float v) const {
+    if (dst != nullptr) stage_param(dst, pm, i, v, round != 0, false, true);
+  }
+};
+
 // sc_next (nullable): the gradient and that set of scalars are zeroed for the next optimiser step, which accumulates
 // into them (two sets of scalars alternate, so nobody reads the one being zeroed).
+template <class Stage>
 __global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ params, float* __restrict__ m,
                                                    float* __restrict__ v, float* __restrict__ grad, int64_t P,
                                                    AdamArgs a, const Scalars* sc, float* __restrict__ stats_row,
-                                                   float* __restrict__ grad_dump, Scalars* sc_next) {
+                                                   float* __restrict__ grad_dump, Scalars* sc_next, Stage stage) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   // the workgroups' shares of |grad|^2, added by a fixed tree (the same in every workgroup and every run)
   __shared__ double nparts[kNormBlocks];
@@ -484,7 +500,9 @@ __global__ void __launch_bounds__(256) adam_kernel(float* __restrict__ params, f
     const float vi = a.b2 * v[i] + (1.0f - a.b2) * g * g;
     m[i] = mi;
     v[i] = vi;
-    params[i] -= a.lr * (mi / a.bc1) / (sqrtf(vi / a.bc2) + a.eps);
+    const float p = params[i] - a.lr * (mi / a.bc1) / (sqrtf(vi / a.bc2) + a.eps);
+    params[i] = p;
+    stage(i, p);
     if (grad_dump) grad_dump[i] = g;
     if (sc_next != nullptr) grad[i] = 0.f;
   }

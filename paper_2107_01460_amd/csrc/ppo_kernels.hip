@@ -17,6 +17,7 @@ namespace marl {
 void mlp_hidden_forward(const RowSrc& X, int64_t S, int Din, int H, const float* W1, const float* b1, const float* W2,
                         const float* b2, float* h1, float* h2, hipStream_t s);
 const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use);
+void stage_bf16_weights(const marl_config& c, const float* params, float* scratch, hipStream_t s);
 int64_t effective_param_floats(const marl_config& c, bool update);
 Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, int net);
 
@@ -217,7 +218,9 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
       UpdateWsView wk = w;  // the view the helpers get: this step's scalars
       wk.sc = sck;
       const int32_t* rows = (perm ? perm + (int64_t)e * R : w.ident) + (int64_t)mb * rows_mb;
-      const float* eff = effective_params(c, params, w.eff_params, s, USE_UPDATE);
+      const float* const eff = w.eff_params;
+      if (step == 0) effective_params(c, params, w.eff_params, s, USE_UPDATE);
+      else stage_bf16_weights(c, params, w.eff_params, s);  // (the rest of the copy: the last step's Adam kernel)
       LossCommon lc{};
       lc.rows = rows; lc.A = d.A; lc.ad = make_small_div(d.A); lc.rows_mb = rows_mb; lc.inv_B = (float)(1.0 / (double)(rows_mb * d.A));
       lc.sc = sck; lc.adv_stats = w.adv_stats + 2 * step; lc.normalize = c.normalize_adv; lc.clip_eps = c.clip_eps;
@@ -295,9 +298,10 @@ int32_t launch_ppo_update(const marl_config& c, marl_traj tr, float* params, flo
       a.bc2 = (float)(1.0 - std::pow((double)c.beta2, (double)k));
       a.max_norm = c.max_grad_norm; a.ent_coef = c.ent_coef; a.vf_coef = c.vf_coef;
       const bool last = (e == c.n_epochs - 1 && mb == c.n_minibatches - 1);
-      hipLaunchKernelGGL(adam_kernel, dim3((unsigned)((d.P + 255) / 256)), dim3(256), 0, s, params, adam_m, adam_v,
+      hipLaunchKernelGGL(adam_kernel<StageNext>, dim3((unsigned)((d.P + 255) / 256)), dim3(256), 0, s, params, adam_m, adam_v,
                          w.grad, d.P, a, sck, stats + (int64_t)(e * c.n_minibatches + mb) * MARL_N_STATS,
-                         (last ? grad_dump : nullptr), w.sc + ((step + 1) & 1));
+                         (last ? grad_dump : nullptr), w.sc + ((step + 1) & 1),
+                         StageNext{last ? nullptr : w.eff_params, pm, (int)d.bf16});
       const int32_t rc = launch_status();
       if (rc != MARL_OK) return rc;
     }

@@ -596,9 +596,9 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
       a.bc2 = (float)(1.0 - std::pow((double)c.beta2, (double)k));
       a.max_norm = c.max_grad_norm; a.ent_coef = c.ent_coef; a.vf_coef = c.vf_coef;
       const bool last = (e == c.n_epochs - 1 && mb == c.n_minibatches - 1);
-      hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(d.P)), dim3(256), 0, s, params, adam_m, adam_v, w.grad, d.P, a, w.sc,
+      hipLaunchKernelGGL(adam_kernel<NoStage>, dim3(blocks_for(d.P)), dim3(256), 0, s, params, adam_m, adam_v, w.grad, d.P, a, w.sc,
                          stats + (int64_t)(e * c.n_minibatches + mb) * MARL_N_STATS, (last ? grad_dump : (float*)nullptr),
-                         (Scalars*)nullptr);
+                         (Scalars*)nullptr, NoStage{});
       const int32_t rc = launch_status();
       if (rc != MARL_OK) return rc;
     }

@@ -1,0 +1,38 @@
+// The working copy of a feed-forward system's parameters (ParamMap), one element at a time: blocks moved to their aligned offsets,
+// optionally rounded to bf16, plus the copies of W1, W2 and W2 transposed that the fused kernels read.
+#pragma once
+#include "common.h"
+#include "split_bf16.h"
+
+namespace marl {
+
+__device__ __forceinline__ void store_split_weight(float* copy, float v, int64_t k, int64_t n, int H) {
+  const SplitPair s = split_pair_any(v, 0.f);
+  bf16_t* const d = reinterpret_cast<bf16_t*>(copy) + split_weight_index(k, n, H);
+  d[0] = (bf16_t)s.h;
+  d[split_weight_plane(H)] = (bf16_t)s.m;
+  d[2 * split_weight_plane(H)] = (bf16_t)s.l;
+}
+// element (k, n) of a copy of network `net`; for_rollout: the actor's in fp32
+__device__ __forceinline__ void stage_element(float* dst, const ParamMap& pm, int net, int64_t copy, float v, int64_t k, int64_t n, bool for_rollout) {
+  const int H = pm.hidden[net];
+  if (for_rollout && net == 0) dst[copy + ((k / 4) * H + n) * 4 + k % 4] = v;
+  else store_split_weight(dst + copy, v, k, n, H);
+}
+// parameter i, of value v
+__device__ __forceinline__ void stage_param(float* dst, const ParamMap& pm, int64_t i, float v, bool round, bool for_rollout, bool for_update) {
+  int b = 0;
+#pragma unroll
+  for (int k = 1; k < 12; ++k) b += (i >= pm.src[k]) ? 1 : 0;
+  if (round) v = round_to_bf16(v);
+  const int64_t e = i - pm.src[b];
+  const int net = b >= 6, H = pm.hidden[net];
+  const bool w1 = b == 0 || b == 6, w2 = b == 2 || b == 8;
+  if (pm.plain[net] || !(w1 || w2)) dst[pm.dst[b] + e] = v;
+  if (!pm.fused[net] || !(w1 || w2)) return;
+  const uint32_t r = (uint32_t)e / (uint32_t)H, c = (uint32_t)e - r * (uint32_t)H;  // (a block has fewer than 2^32 elements; a 64-bit division is 180 instructions)
+  stage_element(dst, pm, net, w1 ? pm.sw_w1[net] : pm.sw_w2[net], v, r, c, for_rollout);
+  if (w2 && for_update) store_split_weight(dst + pm.sw_w2t[net], v, c, r, H);
+}
+
+}  // namespace marl
