@@ -18,6 +18,8 @@
 // registers are spilled.  One workgroup of 128 rows per CU halves
 // that and left every phase uncovered: 778 us; eight wavefronts of 128 registers per 64 rows: 750 us (spills).
 #pragma once
+#include <utility>
+
 #include "gemm.h"
 #include "heads.h"
 
@@ -86,7 +88,7 @@ struct Bf16Shape {
   static constexpr int WAVES = NW == 8 ? 4 : NW > 4 ? 3 : 2;
   static constexpr int P = H + 8;    // pitch of the tile: an odd number of 16-byte units
   static constexpr int PD = BM + 8;  // pitch of the output gradients
-  static constexpr size_t lds(bool train) { return sizeof(bf16_t) * ((BM + 8) * P + (train ? 32 * PD : 0) + 2 * H); }
+  static constexpr size_t lds(bool train) { return sizeof(bf16_t) * ((BM + 8) * P + (train ? 32 * PD : 0) + 2 * H) + sizeof(float) * (12 + (train ? NW * 12 : 0)); }
 };
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));  // 16 bytes between a load and an LDS store (HIP's uint4 arrays may stay in scratch memory)
@@ -95,9 +97,12 @@ typedef float bf16_floatx4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ bf16_floatx4 mfma16_bf16(const bf16x8& a, const bf16x8& b, const bf16_floatx4& c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
 template <bool TRAIN, class Fin>
-struct LossIn { typedef int type; };
+struct LossIn { typedef int type, Prep; };
 template <class Fin>
-struct LossIn<true, Fin> { typedef typename Fin::In type; };
+struct LossIn<true, Fin> {
+  typedef typename Fin::In type;
+  typedef decltype(std::declval<Fin>().prepare()) Prep;  // two floats
+};
 
 // Fin: TRAIN: a loss functor (ActorLoss, CriticLoss); else what becomes of a sample's outputs, fin(s, out, nullptr, nullptr).
 template <int H, int BM, int NOUT, bool TRAIN, class Fin>
@@ -116,6 +121,9 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   bf16_t* const w3t = tile + BM * P;                            // [8][P]  W3 transposed, rows past NOUT zero
   bf16_t* const dlt = w3t + 8 * P;                              // TRAIN: [4][8][PD] dL/d(output), split: three parts and zeros
   bf16_t* const bias = dlt + (TRAIN ? 32 * PD : 0);             // [2][H] (rounded values, exact)
+  float* const b3s = reinterpret_cast<float*>(bias + 2 * H);    // [8]
+  auto* const prep = reinterpret_cast<typename LossIn<TRAIN, Fin>::Prep*>(b3s + 8);  // TRAIN
+  float* const accS = b3s + 12;                                 // TRAIN: [NW][12] every wavefront's b3 gradient and loss statistics
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63, lo = lane & 31, hi = lane >> 5, l15 = lane & 15, l4 = lane >> 4;
@@ -132,9 +140,18 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   }
   if (TRAIN)
     for (int e = tid; e < 32 * PD; e += THREADS) dlt[e] = 0;
-  float bias3[NOUT];
+  // the output layer's bias: in LDS in training, whose registers are full, else in registers
+  float bias3[TRAIN ? 1 : NOUT];
+  if constexpr (TRAIN) {
+    if (tid < NOUT) b3s[tid] = a.b3[tid];
+  } else {
 #pragma unroll
-  for (int k = 0; k < NOUT; ++k) bias3[k] = a.b3[k];
+    for (int k = 0; k < NOUT; ++k) bias3[k] = a.b3[k];
+  }
+  if constexpr (TRAIN) {
+    if (tid == 0) *prep = fin.prepare();
+    for (int e = tid; e < NW * 12; e += THREADS) accS[e] = 0.f;
+  }
 
   // ---- weights: k step `nxt` of the sequence layer 1, layer 2 (, dz1), and again for the next tile
   const int steps1 = a.w.Kp / 16, total = steps1 + (TRAIN ? 2 : 1) * (H / 16);
@@ -267,11 +284,8 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   };
 
   bf16_floatx4 gw[TRAIN ? 2 * NT : 1];  // W3 gradient: units 16 u + 4 l4 + r of this wavefront's columns, output l15, its own samples
-  float gb[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int u = 0; u < (TRAIN ? 2 * NT : 1); ++u) gw[u] = bf16_floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < NOUT; ++k) gb[k] = 0.f;
 
   if ((int64_t)blockIdx.x < ntiles) row_offsets(blockIdx.x);
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
@@ -283,7 +297,8 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
     [[maybe_unused]] int32_t entry[GPW];       // the loss's row order entries of this wavefront's samples, requested long before the rows
     if constexpr (TRAIN) {
 #pragma unroll
-      for (int g = 0; g < GPW; ++g) entry[g] = fin.template row_entry<true>(min(s0 + 16 * (wave + NW * g) + l15, a.S - 1));
+      for (int g = 0; g < GPW; ++g)
+        if (GPW * NW == BM / 16 || wave + NW * g < BM / 16) entry[g] = fin.template row_entry<true>(min(s0 + 16 * (wave + NW * g) + l15, a.S - 1));
     }
     // ---- layer 1
     stage_x(0);
@@ -308,7 +323,8 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
     typename LossIn<TRAIN, Fin>::type lin[GPW];
     if constexpr (TRAIN) {
 #pragma unroll
-      for (int g = 0; g < GPW; ++g) lin[g] = fin.template load_with<true>(min(s0 + 16 * (wave + NW * g) + l15, a.S - 1), entry[g]);
+      for (int g = 0; g < GPW; ++g)
+        if (GPW * NW == BM / 16 || wave + NW * g < BM / 16) lin[g] = fin.template load_with<true>(min(s0 + 16 * (wave + NW * g) + l15, a.S - 1), entry[g]);
     }
     tanh_out(bias + H);
     __syncthreads();
@@ -328,7 +344,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
         }
         const bf16_floatx4 v = o[0] + o[1];
 #pragma unroll
-        for (int k = 0; k < NOUT; ++k) outs[g][k] = (k < 4 ? v[k & 3] : __shfl(v[k & 3], (lane + 16) & 63)) + bias3[k];
+        for (int k = 0; k < NOUT; ++k) outs[g][k] = (k < 4 ? v[k & 3] : __shfl(v[k & 3], (lane + 16) & 63)) + (TRAIN ? b3s[k] : bias3[TRAIN ? 0 : k]);
       }
     }
     if constexpr (!TRAIN) {
@@ -339,23 +355,27 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
       }
       __syncthreads();  // the tile is free
     } else {
-      const auto prep = fin.prepare();
 #pragma unroll
       for (int g = 0; g < GPW; ++g) {
         const int grp = wave + NW * g;
         const int64_t s = s0 + 16 * grp + l15;
         if ((GPW * NW == BM / 16 || grp < BM / 16) && lane < 16) {
-          float dl[NOUT];
+          float dl[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int k = 0; k < NOUT; ++k) dl[k] = 0.f;
-          if (s < a.S) fin.compute(lin[g], prep, outs[g], dl, st);
+          if (s < a.S) fin.compute(lin[g], *prep, outs[g], dl, st);
 #pragma unroll
           for (int k = 0; k < NOUT; ++k) {
-            gb[k] += dl[k];
             const SplitPair sp = split_pair_any(dl[k], 0.f);
             dlt[k * PD + 16 * grp + l15] = (bf16_t)sp.h;
             dlt[(8 + k) * PD + 16 * grp + l15] = (bf16_t)sp.m;
             dlt[(16 + k) * PD + 16 * grp + l15] = (bf16_t)sp.l;
+          }
+#pragma unroll
+          for (int k = 0; k < NOUT + 5; ++k) {  // (sums over the sixteen samples: there is no room for one per sample)
+            float v = k < NOUT ? dl[k < NOUT ? k : 0] : st[k < NOUT ? 0 : k - NOUT];
+            for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
+            if (lane == 0) accS[wave * 12 + k] += v;
           }
         }
       }
@@ -425,22 +445,15 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
     }
   }
   if constexpr (TRAIN) {
-    // this workgroup's sums: the WM wavefronts that share their columns and the NW that share the outputs meet in LDS
+    // this workgroup's sums: the WM wavefronts that share their columns meet in LDS
     constexpr int WM = Sh::WM, COUNT = H * NOUT + NOUT + 5;
-    float* const G = reinterpret_cast<float*>(tile);  // [WM][H * NOUT], [NW][NOUT + 5]
-    float* const G2 = G + WM * H * NOUT;
-    static_assert((WM * H * NOUT + NW * (NOUT + 5)) * 4 <= BM * P * 2, "room in the tile");
+    float* const G = reinterpret_cast<float*>(tile);  // [WM][H * NOUT]
+    static_assert(WM * H * NOUT * 4 <= BM * P * 2, "room in the tile");
 #pragma unroll
     for (int u = 0; u < 2 * NT; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         if (l15 < NOUT) G[wm * H * NOUT + (32 * wn * NT + 16 * u + 4 * l4 + r) * NOUT + l15] = gw[u][r];
-#pragma unroll
-    for (int k = 0; k < NOUT + 5; ++k) {
-      float v = k < NOUT ? gb[k < NOUT ? k : 0] : st[k < NOUT ? 0 : k - NOUT];
-      for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
-      if (lane == 0) G2[wave * (NOUT + 5) + k] = v;
-    }
     __syncthreads();
     float* const own = a.partial + blockIdx.x * copy_pitch(COUNT);
     for (int e = tid; e < COUNT; e += THREADS) {
@@ -450,7 +463,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
         for (int z = 0; z < WM; ++z) v += G[z * H * NOUT + e];
       } else {
 #pragma unroll
-        for (int z = 0; z < NW; ++z) v += G2[z * (NOUT + 5) + e - H * NOUT];
+        for (int z = 0; z < NW; ++z) v += accS[z * 12 + e - H * NOUT];
       }
       own[e] = v;
     }

@@ -111,7 +111,14 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
       if (tid == 0) *prep = fin.prepare();
     }
   }
-  if (tid < NOUT) b3s[tid] = a.b3[tid];
+  // the output layer's bias: in LDS in training, whose registers are full, else in registers
+  float bias3[TRAIN ? 1 : NOUT];
+  if constexpr (TRAIN) {
+    if (tid < NOUT) b3s[tid] = a.b3[tid];
+  } else {
+#pragma unroll
+    for (int k = 0; k < NOUT; ++k) bias3[k] = a.b3[k];
+  }
 
   // ---- weights: k step `nxt` of the sequence layer 1, layer 2 (, dz1), and again for the next tile
   const int steps1 = a.Kp / 16, total = steps1 + (TRAIN ? 2 : 1) * (H / 16);
@@ -325,7 +332,7 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
         }
         const f4 v = small + o;
 #pragma unroll
-        for (int k = 0; k < NOUT; ++k) outs[g][k] = (k < 4 ? v[k & 3] : __shfl(v[k & 3], (lane + 16) & 63)) + b3s[k];
+        for (int k = 0; k < NOUT; ++k) outs[g][k] = (k < 4 ? v[k & 3] : __shfl(v[k & 3], (lane + 16) & 63)) + (TRAIN ? b3s[k] : bias3[TRAIN ? 0 : k]);
       }
     }
     if constexpr (!TRAIN) {
