@@ -341,7 +341,11 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
         if (AVEC) {
           ra[p] = *reinterpret_cast<const float4*>(src + min(m, g.M - 4));
         } else {
-          ra[p] = make_float4(src[min(m, g.M - 1)], src[min(m + 1, g.M - 1)], src[min(m + 2, g.M - 1)], src[min(m + 3, g.M - 1)]);
+          // (16 bytes at any 4-byte boundary; up to three floats past the row, which feed outputs that are never stored: rows of the
+          // caller's that need this are observations, whose buffer goes on for a whole slab behind the last row)
+          typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+          const f4u v = *reinterpret_cast<const f4u*>(src + min(m, g.M - 1));
+          ra[p] = make_float4(v.x, v.y, v.z, v.w);
         }
         if (past) ra[p] = make_float4(0.f, 0.f, 0.f, 0.f);
         q[p] += dq;
