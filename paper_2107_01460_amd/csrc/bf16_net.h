@@ -14,7 +14,7 @@
 // forward pass of 32 768 samples through both networks and the sampling 159 -> 73 us.
 // Bound: two workgroups of four wavefronts share a CU (64 rows each, 128 of a lane's 256 registers accumulators), and a tile is
 // a chain of products (39 of 107 thousand cycles for the pair), tanh (16), gradients on the output side (15), copies and barriers
-// that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile; at 512 units 58 (six outputs) and 44 (one)
+// that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile; at 512 units 32 (six outputs) and 38 (one)
 // registers are spilled.  One workgroup of 128 rows per CU halves
 // that and left every phase uncovered: 778 us; eight wavefronts of 128 registers per 64 rows: 750 us (spills).
 #pragma once

@@ -11,8 +11,8 @@
 // central critic of 256 units 96.7 -> 92.2 ms.
 // Bound (first of these sizes): no unit is full.  Matrix cores are busy 43 % and vector instructions 24 % of the cycles, and the weights
 // come from the L2 at 15 TB/s (1.28 MB per tile of 32 rows; 86 million reads of 128 bytes), which two workgroups per CU (one above 256
-// units) keep going through each other's phases; their 128 registers a lane leave a ring of two k steps of weights and up to 60 spilled
-// registers (7, 12 and 11 at the sizes above).  64-row tiles halve the bytes, but leave room for one workgroup per CU, whose phases
+// units) keep going through each other's phases; their 128 registers a lane leave a ring of two k steps of weights and up to 15 spilled
+// registers (11, 0 and 15 at the sizes above; loss statistics and constants in LDS, 1-2 % of a training iteration).  64-row tiles halve the bytes, but leave room for one workgroup per CU, whose phases
 // without products (tanh, loss, gradients: 37 of 81 thousand cycles) nothing covers: the same time at the first size, 7 % longer updates
 // at 50 000 samples.  Forward passes of many samples hold less and take the 64-row tiles.  h1 stored at the end of a tile instead of
 // before layer 2's product, so that no weight waits behind it: 720 -> 759 us.
