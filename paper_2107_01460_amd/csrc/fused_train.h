@@ -393,7 +393,9 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       }
       __syncthreads();
       // From here to the next barrier a wavefront reads and writes nothing of B but its own columns.
-      // ---- W3 gradient: h2^T x dl
+      // ---- W3 gradient: h2^T x dl, a tile's sum by itself and then one fp32 addition.  (A matrix instruction cuts its addends off below
+      // the last bit of the largest, always downwards: with gw as the accumulator the error grew with the number of tiles, 2.0e-6 with
+      // 128 and 3.6e-6 with 256 tiles per workgroup, against 8e-8 now; no difference in time.)
       {
         const Split8 d = frag_row(&dlt[(lane & 7) * PD + 8 * l4], 8 * PD);
         const int r = 8 * l4 + (l15 >> 2), sw = (4 * wave + ((lane >> 1) & 1)) ^ tile_swizzle<H>(r);
@@ -407,12 +409,15 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
             return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
           };
           const Split8 h{part(tB), part(tB + PLANE), part(tB + 2 * PLANE)};
-          gw[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.l, d.h, gw[u], 0, 0, 0);
-          gw[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.h, d.l, gw[u], 0, 0, 0);
-          gw[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.m, d.m, gw[u], 0, 0, 0);
-          gw[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.m, d.h, gw[u], 0, 0, 0);
-          gw[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.h, d.m, gw[u], 0, 0, 0);
-          gw[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.h, d.h, gw[u], 0, 0, 0);
+          f4 small = {0.f, 0.f, 0.f, 0.f}, top = small;
+          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.l, d.h, small, 0, 0, 0);
+          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.h, d.l, small, 0, 0, 0);
+          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.m, d.m, small, 0, 0, 0);
+          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.m, d.h, small, 0, 0, 0);
+          small = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.h, d.m, small, 0, 0, 0);
+          top = __builtin_amdgcn_mfma_f32_16x16x32_bf16(h.h, d.h, top, 0, 0, 0);
+          gw[u] += small + top;
+          asm volatile("" : "+v"(gw[u]));  // (its addition stays here: moved, it cost 22 spilled registers at 128 units and 96 inputs)
         }
       }
       // ---- dz2 = (W3 dl) (1 - h2^2) over h2; the rank-NOUT product on the fp32 instruction, k = 4 hi + j

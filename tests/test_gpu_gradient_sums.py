@@ -1,0 +1,61 @@
+"""Long sums of the whole-minibatch training kernel (64 and 128 units): hundreds of row tiles per workgroup whose shares of the gradient
+are small against what the workgroup has summed so far.  A tile's sum has to be taken by itself and added once; matrix and dot
+instructions cut addends off below the last bit of the largest, which lost them one by one.  The critic's parameters are chosen so that
+every term of its sums is known exactly.
+"""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def M():
+    import paper_2107_01460_amd as m
+    return m
+
+
+def critic_gradient(M, hidden, view, n_envs, obs, critic, ret):
+    """Gradient blocks of the critic over one minibatch of n_envs * 64 * 2 samples in trajectory order (vf_coef 1/2)."""
+    cfg = W.scaled(W.CONFIGS[0], view=view, actor_hidden=hidden, critic_hidden=hidden, n_envs=n_envs, rollout_len=64, n_agents=2, n_epochs=1,
+                   n_minibatches=1, max_grad_norm=0.0, normalize_adv=0, vf_coef=0.5)
+    layout = W.param_layout(cfg)
+    params = np.concatenate([np.broadcast_to(np.asarray(critic.get(name[7:], 0.0) if name.startswith("critic") else 0.0, np.float32), shape).ravel()
+                             for name, shape in layout])
+    tr = M.Traj(cfg)
+    for f in ("obs", "action", "logp", "value", "reward", "adv", "ret", "done"):
+        getattr(tr, f).zero_()
+    tr.obs.fill_(obs)
+    tr.ret.view(-1).copy_(ret)
+    p, m, v = dev(params), torch.zeros(params.size, device="cuda"), torch.zeros(params.size, device="cuda")
+    stats, g = torch.zeros((1, 8), device="cuda"), torch.zeros(params.size, device="cuda")
+    M.ppo_update(cfg, tr, p, m, v, 0, None, stats, g, M.alloc_workspace(M.query_sizes(cfg).update_workspace_bytes))
+    g, out, off = g.cpu().numpy().astype(np.float64), {}, 0
+    for name, shape in layout:
+        n = int(np.prod(shape))
+        out[name] = g[off:off + n].reshape(shape)
+        off += n
+    return {k[7:]: x for k, x in out.items() if k.startswith("critic")}
+
+
+# inexact: observations of 0.1, which the weights of the first layer (zeros) do not let through
+@pytest.mark.parametrize("obs", [0.0, 0.1])
+@pytest.mark.parametrize("hidden,view", [(64, 3), (64, 5), (128, 3), (128, 5)])
+def test_output_weights(M, hidden, view, obs):
+    """Every sample has the same h2 and a prediction of zero: the W3 gradient is h2 times the sum of the returns.  Bound: 2^-22, two units
+    in the last place for the hyperbolic tangent and one for each of the scaled error and the result; the sums round once per tile and
+    at random, which is less."""
+    S = 1 << 22
+    print("case", hidden, view, obs, flush=True)
+    rng = np.random.default_rng(3)
+    b2 = rng.uniform(-1.5, 1.5, hidden).astype(np.float32)
+    ret = -(0.5 + 0.5 * torch.rand(S, device="cuda", generator=torch.Generator(device="cuda").manual_seed(5)))
+    g = critic_gradient(M, hidden, view, S // 128, obs, {"b2": b2}, ret)
+    want = np.tanh(b2.astype(np.float64)) * (-0.5 * ret.double().sum().item() / S)
+    e = np.linalg.norm(g["W3"][:, 0] - want) / np.linalg.norm(want)
+    print("error", e, flush=True)
+    assert e < 2.0 ** -22, e
