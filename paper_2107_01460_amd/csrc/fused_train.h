@@ -16,7 +16,7 @@
 // (tile_swizzle) so that both ways of reading a plane and the epilogues' stores meet every bank once.
 // Exact inputs: windows hold small integers and halves, whose lower split parts are zero.  X is then one plane and its products three
 // instead of six; the first tile with any other value, and all behind it, go through a second form of the loop, which splits X in
-// pieces of 32 columns.  The last column of the padded X is the constant one, which makes its row of dW1 the bias gradient.
+// pieces of 32 columns.
 // At the end a workgroup stores its partial gradient into a copy of its own, every sum in a fixed
 // order; reduce_partials_kernel adds the copies.
 // Against one workgroup of eight wavefronts per CU that split activations where it read them (MI355X): 1 048 576 samples of 75 inputs,
@@ -69,7 +69,9 @@ __device__ __forceinline__ int tile_swizzle(int r) {
   return H == 128 ? (r & 3) << 2 | low : H == 64 ? (r & 2) << 1 | low : low;
 }
 
-// c + the sum of eight values
+// c + the sum of eight values.  The dot instruction cuts its addends off below the last bit of the largest: first parts of a split are
+// summed by themselves (8 bits each, so that nothing is lost unless they are 2^16 apart), and the other parts by themselves.  All
+// three on one running sum over the tiles lost what a tile has to add where it is small against that sum.
 __device__ __forceinline__ float sum8(bf16x8 v, float c) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   const bf16x2 one = {(__bf16)1.0f, (__bf16)1.0f};
@@ -150,7 +152,9 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   floatx16 acc, h1, h2;              // a product; this wavefront's units of the samples (element r: unit 8 (r / 4) + 4 hi + r % 4, sample lo)
   typedef float f4 __attribute__((ext_vector_type(4)));
   f4 gw[2];                          // W3 gradient: units 32 wave + 16 u + 4 (lane / 16) + r, output lane % 16
-  float gb2 = 0.f;                   // b2 gradient of unit 32 (jt0 + gb2_j) + lo, samples 8 hi .. 8 hi + 7 of every sixteen (one register; a sum per sample slot takes sixteen)
+  // b1 gradient of unit 32 wave + lo, b2 gradient of unit 32 (jt0 + gb2_j) + lo: samples 8 hi .. 8 hi + 7 of every sixteen (one register
+  // each; a sum per sample slot takes sixteen), a tile's sum added at once
+  float gb1 = 0.f, gb2 = 0.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
 #pragma unroll
@@ -277,7 +281,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     const int c = 32 * q + 2 * l15;
     const f2 v = xr[q][i];
     xr[q][i].x = c >= a.Din ? 0.f : c == a.Din - 1 ? v.y : v.x;
-    xr[q][i].y = c + 1 < a.Din ? v.y : c + 1 == DMAX - 1 ? 1.f : 0.f;
+    xr[q][i].y = c + 1 < a.Din ? v.y : 0.f;
   };
   auto x_slot = [&](int i) { return x_row(i) * 32 + (((l15 >> 2) ^ tile_swizzle<32>(x_row(i))) << 3) + 2 * (l15 & 3); };
   // the rows to one plane; are they all exact?
@@ -302,7 +306,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     for (int i = 0; i < XR; ++i) {
       const f2 v = *reinterpret_cast<const f2*>(x_ptr(t, i) + x_col(q));
       const int c = 32 * q + 2 * l15;
-      const SplitPair s = split_pair_any(c >= a.Din ? 0.f : c == a.Din - 1 ? v.y : v.x, c + 1 < a.Din ? v.y : c + 1 == DMAX - 1 ? 1.f : 0.f);
+      const SplitPair s = split_pair_any(c >= a.Din ? 0.f : c == a.Din - 1 ? v.y : v.x, c + 1 < a.Din ? v.y : 0.f);
       uint32_t* const d = reinterpret_cast<uint32_t*>(xs + x_slot(i));
       d[0] = s.h;
       d[BM * 16] = s.m;
@@ -438,6 +442,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       }
       __syncthreads();
       // ---- dW2 += h1^T dz2
+      float b2h = 0.f, b2m = 0.f;
 #pragma unroll
       for (int kb = 0; kb < BM; kb += 16) {
         Split8 x[TI];
@@ -446,11 +451,15 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
           const Split8 y = col_split(tB, PLANE, TileP{}, jt0 + j, kb);
-          if (j == gb2_j) gb2 = sum8(y.h, sum8(y.m, sum8(y.l, gb2)));  // uniform
+          if (j == gb2_j) {  // uniform
+            b2h = sum8(y.h, b2h);
+            b2m = sum8(y.m, sum8(y.l, b2m));
+          }
 #pragma unroll
           for (int i = 0; i < TI; ++i) acc2[i * TJ + j] = mfma_split(x[i], y, acc2[i * TJ + j]);
         }
       }
+      gb2 += b2h + b2m;
       if (EXACT && !X_EARLY) request_x(t + nblk);
       // ---- dz1 = (W2 dz2^T) (1 - h1^2) over h1
       zero_acc();
@@ -461,10 +470,13 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       for (int r = 0; r < 16; ++r) acc[r] *= 1.0f - h1[r] * h1[r];
       store_gradient(tA, acc);
       // ---- dW1 += X^T dz1: all blocks of X, this wavefront's columns of dz1
+      float b1h = 0.f, b1m = 0.f;
       if constexpr (EXACT) {
 #pragma unroll
         for (int kb = 0; kb < BM; kb += 16) {
           const Split8 y = col_split(tA, PLANE, TileP{}, wave, kb);
+          b1h = sum8(y.h, b1h);
+          b1m = sum8(y.m, sum8(y.l, b1m));
           bf16x8 x[Q1];
 #pragma unroll
           for (int q = 0; q < Q1; ++q) x[q] = col8(X + q * (BM * 32), BlockP{}, 0, kb);
@@ -480,10 +492,17 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
         for (int q = 0; q < Q1; ++q) {
           stage_block(q);
 #pragma unroll
-          for (int kb = 0; kb < BM; kb += 16)
-            acc1[q] = mfma_split(col_split(xs, BM * 32, BlockP{}, 0, kb), col_split(tA, PLANE, TileP{}, wave, kb), acc1[q]);
+          for (int kb = 0; kb < BM; kb += 16) {
+            const Split8 y = col_split(tA, PLANE, TileP{}, wave, kb);
+            if (q == 0) {
+              b1h = sum8(y.h, b1h);
+              b1m = sum8(y.m, sum8(y.l, b1m));
+            }
+            acc1[q] = mfma_split(col_split(xs, BM * 32, BlockP{}, 0, kb), y, acc1[q]);
+          }
         }
       }
+      gb1 += b1h + b1m;
     }
   };
   if (t < ntiles) {
@@ -500,8 +519,8 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   lane_parts();
   __syncthreads();  // accS
   float* const gW1 = a.partial + (int64_t)bid * a.pstride;
-  float* const gb1 = gW1 + a.Din * H;
-  float* const gW2 = gb1 + H;
+  float* const gb1o = gW1 + a.Din * H;
+  float* const gW2 = gb1o + H;
   float* const gb2o = gW2 + H * H;
   float* const gW3 = gb2o + H;
 #pragma unroll
@@ -513,9 +532,10 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     for (int q = 0; q < Q1; ++q) {
       const int d = 32 * q + row;
       if (d < a.Din) gW1[d * H + 32 * wave + lo] = acc1[q][r];
-      if (d == DMAX - 1) gb1[32 * wave + lo] = acc1[q][r];
     }
   }
+  gb1 += __shfl_xor(gb1, 32);
+  if (hi == 0) gb1o[32 * wave + lo] = gb1;
   gb2 += __shfl_xor(gb2, 32);
   if (hi == 0) gb2o[32 * (jt0 + gb2_j) + lo] = gb2;
 #pragma unroll
@@ -524,7 +544,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
     for (int r = 0; r < 4; ++r)
       if (l15 < NOUT) gW3[(32 * wave + 16 * u + 4 * l4 + r) * NOUT + l15] = gw[u][r];
   if (tid < AS) {
-    float v = accS[tid];
+    double v = accS[tid];
     for (int s = 1; s < BM; ++s) v += accS[s * AS + tid];
     if (tid < NOUT) gW3[H * NOUT + tid] = v;
     else if (a.stats_mask >> (tid - NOUT) & 1) gW1[a.stats_at + tid - NOUT] = v;

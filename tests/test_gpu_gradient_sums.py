@@ -59,3 +59,22 @@ def test_output_weights(M, hidden, view, obs):
     e = np.linalg.norm(g["W3"][:, 0] - want) / np.linalg.norm(want)
     print("error", e, flush=True)
     assert e < 2.0 ** -22, e
+
+
+@pytest.mark.parametrize("obs", [0.0, 0.1])
+@pytest.mark.parametrize("hidden,view", [(64, 3), (64, 5), (128, 3), (128, 5)])
+def test_biases(M, hidden, view, obs):
+    """Hidden activations of zero, W2 the identity and W3 ones: every bias gradient is the sum of the scaled errors.  The first 1024 tiles
+    (at most two of a workgroup) hold errors of one, all others of 2^-22, which together are 7.4e-6 of the sum: below the last bit of a
+    workgroup's sum alone, not as a tile's sum.  All sums of a workgroup are exact in fp32; the copies of at most 1024 workgroups are added in
+    about ten roundings: 10 * 2^-24 < 1e-6."""
+    S = 1 << 20
+    print("case", hidden, view, obs, flush=True)
+    ret = torch.full((S,), -2.0 ** -22, device="cuda")
+    ret[:1024 * 32] = -1.0
+    g = critic_gradient(M, hidden, view, S // 128, obs, {"W2": np.eye(hidden), "W3": 1.0}, ret)
+    want = -0.5 * ret.double().sum().item() / S
+    for name in ("b1", "b2", "b3"):
+        e = np.abs(g[name] / want - 1.0).max()
+        print(name, e, flush=True)
+        assert e < 1e-6, (name, e)
