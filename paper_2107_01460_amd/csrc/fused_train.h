@@ -15,8 +15,9 @@
 // A wavefront's share of dW1 needs no dz1 but its own.  The tiles' rows have no padding; a row's 16-byte units are permuted
 // (tile_swizzle) so that both ways of reading a plane and the epilogues' stores meet every bank once.
 // Exact inputs: windows hold small integers and halves, whose lower split parts are zero.  X is then one plane and its products three
-// instead of six; the first tile with any other value, and all behind it, go through a second form of the loop, which splits X in
-// pieces of 32 columns.
+// instead of six; the first tile with any other value, and all behind it, go through a second form of the loop, which splits X into three
+// planes once per tile (16 minibatches of 98 304 samples of 75 inputs, both networks of 64 units: 1.97 ms, in the second form 2.18; of 128
+// units 3.47 and 3.79.  With X staged twice a tile in blocks of 32 columns, each waited for: 2.87 and 4.18).
 // At the end a workgroup stores its partial gradient into a copy of its own, every sum in a fixed
 // order; reduce_partials_kernel adds the copies.
 // Against one workgroup of eight wavefronts per CU that split activations where it read them (MI355X): 1 048 576 samples of 75 inputs,
@@ -48,18 +49,20 @@ struct FusedTrainArgs {
 
 constexpr int kFusedTile = 32;  // samples of a tile
 
-// bf16 elements of LDS for two tiles of exact inputs and the wavefronts' shares of the outputs; the general form stages 32 columns in
-// three planes there.
+// bf16 elements of LDS for two tiles of exact inputs and the wavefronts' shares of the outputs, or for one tile of any inputs in three
+// planes, the third of which begins where the outputs do.
 constexpr size_t fused_train_x_region(int H, int DMAX) {
-  const size_t exact = 2 * 32 * DMAX + 2 * (H / 32) * 32 * 8;
-  return exact > 3072 ? exact : 3072;
+  const size_t exact = 2 * 32 * DMAX + 2 * (H / 32) * 32 * 8, planes = 3 * 32 * DMAX;
+  return exact > planes ? exact : planes;
 }
 // Bytes of LDS (with DMAX columns of X).  Two workgroups of 128 units, four of 64 units and 32 inputs, three of 64 units and 96
 // inputs fit a CU's 160 KB.
 constexpr size_t fused_train_lds(int H, int NOUT, int DMAX) {
   return sizeof(bf16_t) * (2 * 3 * 32 * H + fused_train_x_region(H, DMAX) + 24 * (H + 8) + 24 * 40) +
-         sizeof(float) * (2 * H + 32 * 8 + H * NOUT + 32 * (NOUT + 5) + 12);
+         sizeof(float) * (2 * H + H * NOUT + 32 * (NOUT + 5) + 12);
 }
+static_assert(2 * fused_train_lds(128, 6, 96) <= 160 * 1024 && 4 * fused_train_lds(64, 6, 32) <= 160 * 1024 && 3 * fused_train_lds(64, 6, 96) <= 160 * 1024,
+              "workgroups per CU");
 
 // Where the 16-byte unit u of row r of a tile with H elements a row (H = 32: blocks of X) stands: at unit u ^ tile_swizzle(r).
 // Sixteen rows of one unit (row reads) and four units of four rows (transposing reads) then lie in 64 different banks each.
@@ -95,13 +98,13 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   extern __shared__ __attribute__((aligned(16))) bf16_t fused_lds[];
   bf16_t* const tA = fused_lds;                         // [3][BM][H] h1, later dz1
   bf16_t* const tB = tA + 3 * PLANE;                    // [3][BM][H] h2, later dz2
-  bf16_t* const xs = tB + 3 * PLANE;                    // exact: [2][Q1][BM][32]; else one block as [3][BM][32]
-  float* const outp = reinterpret_cast<float*>(xs + 2 * XBUF);   // [NW][BM][8] every wavefront's share of the outputs
+  bf16_t* const xs = tB + 3 * PLANE;                    // exact: [2][Q1][BM][32], one tile and the next; else [3][Q1][BM][32]
+  float* const outp = reinterpret_cast<float*>(xs + 2 * XBUF);   // [NW][BM][8] every wavefront's share of the outputs; then the first as
+  float* const dls = outp;                              // [BM][8] dL/d(output), zeros past NOUT
   bf16_t* const w3t = xs + fused_train_x_region(H, DMAX);        // [3][8][P3] W3 transposed, split, rows past NOUT zero
   bf16_t* const dlt = w3t + 3 * PLANE3;                 // [3][8][PD] dL/d(output), split and transposed
   float* const bias = reinterpret_cast<float*>(dlt + 24 * PD);  // [2][H]
-  float* const dls = bias + 2 * H;                      // [BM][8] dL/d(output), zeros past NOUT
-  float* const w3s = dls + BM * 8;                      // [H][NOUT]
+  float* const w3s = bias + 2 * H;                      // [H][NOUT]
   float* const accS = w3s + H * NOUT;                   // [BM][AS] per sample slot: b3 gradient, loss statistics
   float* const b3s = accS + BM * AS;                    // [8]
   typedef decltype(fn.prepare()) Prep;                  // two floats
@@ -123,7 +126,6 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   }
   for (int e = tid; e < H * NOUT; e += THREADS) w3s[e] = a.W3[e];
   for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
-  for (int e = tid; e < BM * 8; e += THREADS) dls[e] = 0.f;
   for (int e = tid; e < BM * AS; e += THREADS) accS[e] = 0.f;
   if (tid < NOUT) b3s[tid] = a.b3[tid];
   if (tid == 0) {
@@ -299,25 +301,50 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       }
     if (__builtin_amdgcn_ballot_w64((low_bits & 0xffffu) != 0 || __builtin_isinf(top)) != 0) *inexact = 1;
   };
-  // block q of the tile's rows to three planes (general form of the loop)
-  auto stage_block = [&](int q) {
-    __syncthreads();
+  // The rows, split, to three planes (general form of the loop).  The outputs overwrite the third plane's first KEEP blocks, whose pieces
+  // stay in registers.
+  constexpr int KEEP = NW / 2 < Q1 ? NW / 2 : Q1;
+  static_assert(NW * BM * 8 * 2 <= KEEP * BM * 32 || KEEP == Q1, "blocks under the outputs");
+  uint32_t low[KEEP][XR];
+  auto put_x = [&](auto any) {
 #pragma unroll
-    for (int i = 0; i < XR; ++i) {
-      const f2 v = *reinterpret_cast<const f2*>(x_ptr(t, i) + x_col(q));
-      const int c = 32 * q + 2 * l15;
-      const SplitPair s = split_pair_any(c >= a.Din ? 0.f : c == a.Din - 1 ? v.y : v.x, c + 1 < a.Din ? v.y : 0.f);
-      uint32_t* const d = reinterpret_cast<uint32_t*>(xs + x_slot(i));
-      d[0] = s.h;
-      d[BM * 16] = s.m;
-      d[2 * BM * 16] = s.l;
-    }
-    __syncthreads();
+    for (int q = 0; q < Q1; ++q)
+#pragma unroll
+      for (int i = 0; i < XR; ++i) {
+        const SplitPair s = split_two<decltype(any)::value>(xr[q][i].x, xr[q][i].y);
+        uint32_t* const d = reinterpret_cast<uint32_t*>(xs + q * (BM * 32) + x_slot(i));
+        d[0] = s.h;
+        d[XBUF / 2] = s.m;
+        d[XBUF] = s.l;
+        if (q < KEEP) low[q < KEEP ? q : 0][i] = s.l;
+      }
+  };
+  auto split_x = [&]() {
+    float top = 0.f;
+#pragma unroll
+    for (int q = 0; q < Q1; ++q)
+#pragma unroll
+      for (int i = 0; i < XR; ++i) {
+        fix_x(i, q);
+        top = __builtin_elementwise_maximum(top, __builtin_elementwise_maximum(fabsf(xr[q][i].x), fabsf(xr[q][i].y)));
+      }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(top < kSplitLimit)) != 0, 0)) put_x(std::true_type{});
+    else put_x(std::false_type{});
+  };
+  auto put_low = [&]() {
+#pragma unroll
+    for (int q = 0; q < KEEP; ++q)
+#pragma unroll
+      for (int i = 0; i < XR; ++i) reinterpret_cast<uint32_t*>(xs + 2 * XBUF + q * (BM * 32) + x_slot(i))[0] = low[q][i];
   };
 
   // All tiles from t on, or (EXACT) up to the first whose inputs are not exact.
   auto train_tiles = [&](auto exact) {
     constexpr bool EXACT = decltype(exact)::value;
+    if (!EXACT) {  // (store_x has set what is past a row's end)
+      fetch_entries(t);
+      request_x(t);
+    }
     for (int it = 0; t < ntiles; t += nblk, ++it) {
       if (EXACT && __builtin_amdgcn_readfirstlane(*inexact) != 0) break;
       lane_parts();
@@ -327,17 +354,18 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       const int64_t smp = s0 + lo;  // the sample whose loss a lane of the wavefront `loss_wave` takes
       int32_t lentry = 0;
       if (wave == loss_wave) lentry = fn.template row_entry<true>(min(smp, a.S - 1));
-      fetch_entries(EXACT ? min(t + nblk, ntiles - 1) : t);
+      fetch_entries(min(t + nblk, ntiles - 1));
       // ---- layer 1
+      if constexpr (!EXACT) {
+        __syncthreads();  // the last tile's X has been read
+        split_x();
+        __syncthreads();
+      }
       zero_acc();
       if constexpr (EXACT) {
         product(X, 0, steps1, std::true_type{}, std::true_type{});
       } else {
-#pragma unroll 1
-        for (int q = 0; 2 * q < steps1; ++q) {
-          stage_block(q);
-          product(xs, BM * 32, 2, std::true_type{}, std::false_type{});
-        }
+        product(X, XBUF, steps1, std::true_type{}, std::false_type{});
       }
       tanh_out(tA, bias, h1);
       __syncthreads();
@@ -346,7 +374,7 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
       product(tA, PLANE, H / 16, std::false_type{}, std::false_type{});
       typename LossFn::In lin;
       if (wave == loss_wave) lin = fn.template load_with<true>(min(smp, a.S - 1), lentry);
-      if (EXACT && X_EARLY) request_x(t + nblk);
+      if (X_EARLY) request_x(t + nblk);
       tanh_out(tB, bias + H, h2);
       // ---- output layer: W3^T x h2 over this wavefront's units for sixteen samples at a time; outputs 0 .. 3 land in lanes 0 .. 15,
       // 4 .. 7 in the next sixteen
@@ -386,7 +414,6 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
 #pragma unroll
         for (int k = 0; k < NOUT; ++k) {
           accS[lo * AS + k] += dl[k];
-          dls[lo * 8 + k] = dl[k];
           const SplitPair sp = split_pair_any(dl[k], 0.f);
           dlt[k * PD + lo] = (bf16_t)sp.h;
           dlt[(8 + k) * PD + lo] = (bf16_t)sp.m;
@@ -394,6 +421,10 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
         }
 #pragma unroll
         for (int k = 0; k < 5; ++k) accS[lo * AS + NOUT + k] += st[k];
+#pragma unroll
+        for (int k = 0; k < 8; k += 4)
+          *reinterpret_cast<float4*>(&dls[lo * 8 + k]) = make_float4(k < NOUT ? dl[k < NOUT ? k : 0] : 0.f, k + 1 < NOUT ? dl[k + 1 < NOUT ? k + 1 : 0] : 0.f,
+                                                                     k + 2 < NOUT ? dl[k + 2 < NOUT ? k + 2 : 0] : 0.f, k + 3 < NOUT ? dl[k + 3 < NOUT ? k + 3 : 0] : 0.f);
       }
       __syncthreads();
       // From here to the next barrier a wavefront reads and writes nothing of B but its own columns.
@@ -460,23 +491,24 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
         }
       }
       gb2 += b2h + b2m;
-      if (EXACT && !X_EARLY) request_x(t + nblk);
+      if (!X_EARLY) request_x(t + nblk);
       // ---- dz1 = (W2 dz2^T) (1 - h1^2) over h1
       zero_acc();
       product(tB, PLANE, H / 16, std::false_type{}, std::false_type{});
-      if (EXACT && more) store_x(xs + ((it & 1) ^ 1) * XBUF);  // the next tile's inputs
+      if (!EXACT) put_low();
+      else if (more) store_x(xs + ((it & 1) ^ 1) * XBUF);  // the next tile's inputs
       __syncthreads();  // h1 has been read
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] *= 1.0f - h1[r] * h1[r];
       store_gradient(tA, acc);
       // ---- dW1 += X^T dz1: all blocks of X, this wavefront's columns of dz1
       float b1h = 0.f, b1m = 0.f;
-      if constexpr (EXACT) {
 #pragma unroll
-        for (int kb = 0; kb < BM; kb += 16) {
-          const Split8 y = col_split(tA, PLANE, TileP{}, wave, kb);
-          b1h = sum8(y.h, b1h);
-          b1m = sum8(y.m, sum8(y.l, b1m));
+      for (int kb = 0; kb < BM; kb += 16) {
+        const Split8 y = col_split(tA, PLANE, TileP{}, wave, kb);
+        b1h = sum8(y.h, b1h);
+        b1m = sum8(y.m, sum8(y.l, b1m));
+        if constexpr (EXACT) {
           bf16x8 x[Q1];
 #pragma unroll
           for (int q = 0; q < Q1; ++q) x[q] = col8(X + q * (BM * 32), BlockP{}, 0, kb);
@@ -486,20 +518,9 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
           for (int q = 0; q < Q1; ++q) acc1[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[q], y.m, acc1[q], 0, 0, 0);
 #pragma unroll
           for (int q = 0; q < Q1; ++q) acc1[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[q], y.h, acc1[q], 0, 0, 0);
-        }
-      } else {
+        } else {
 #pragma unroll
-        for (int q = 0; q < Q1; ++q) {
-          stage_block(q);
-#pragma unroll
-          for (int kb = 0; kb < BM; kb += 16) {
-            const Split8 y = col_split(tA, PLANE, TileP{}, wave, kb);
-            if (q == 0) {
-              b1h = sum8(y.h, b1h);
-              b1m = sum8(y.m, sum8(y.l, b1m));
-            }
-            acc1[q] = mfma_split(col_split(xs, BM * 32, BlockP{}, 0, kb), y, acc1[q]);
-          }
+          for (int q = 0; q < Q1; ++q) acc1[q] = mfma_split(col_split(X + q * (BM * 32), XBUF, BlockP{}, 0, kb), y, acc1[q]);
         }
       }
       gb1 += b1h + b1m;
