@@ -106,47 +106,57 @@ struct GemmArgs {
 // do the same with one slab per k split when the caller passes split_out; without it, they add with atomics.
 
 // out[i] += sum_b partial[b * copy_pitch(count) + i], the copies added in a fixed order, so that the result does not depend on the
-// run; elements from `head` on go to tail[i - head] instead.  A workgroup takes 32 consecutive elements, eight lanes with 16 bytes
-// each; its 32 thread groups sum the copies b = g, g + 32, g + 64, ..., eight of them on their way at a time, and meet through lane
-// exchanges and LDS.  Bound: the copies' way from memory, and for few of them a launch.  (4-byte loads by eight groups, four at a
-// time: 512 copies of 27 000 floats 16.1 us, 15.6 here; 25 of 38 000 8.3 us, 5.7 here.)
+// run; elements from `head` on go to tail[i - head] instead.  A workgroup is G groups of 256 / G lanes with 16 bytes each; group g sums
+// the copies b = g, g + G, g + 2 G, ..., eight of them on their way at a time, and the groups meet through lane exchanges and LDS.
+// Bound: the copies' way from memory, and for few of them a launch.
 constexpr int64_t copy_pitch(int64_t count) { return (count + 3) & ~(int64_t)3; }
+template <int G>
 static __global__ void __launch_bounds__(256) reduce_partials_kernel(const float* __restrict__ partial, int nblocks, int64_t count,
                                                                      float* __restrict__ out, int64_t head, float* __restrict__ tail) {
   typedef float f4 __attribute__((ext_vector_type(4)));
-  __shared__ f4 part[4][8];
-  const int l = threadIdx.x & 7, g = threadIdx.x >> 3, wave = threadIdx.x >> 6;
-  const int64_t i0 = (int64_t)blockIdx.x * 32, pitch = copy_pitch(count);
+  constexpr int LANES = 256 / G;
+  static_assert(LANES <= 32, "groups of a wavefront meet in lanes");
+  __shared__ f4 part[4][LANES];
+  const int l = threadIdx.x % LANES, g = threadIdx.x / LANES, wave = threadIdx.x >> 6;
+  const int64_t i0 = (int64_t)blockIdx.x * (4 * LANES), pitch = copy_pitch(count);
   f4 s = {0.f, 0.f, 0.f, 0.f};
   if (i0 + 4 * l < pitch) {
     const float* const src = partial + i0 + 4 * l;
-    for (int b = g; b < nblocks; b += 256) {
+    for (int b = g; b < nblocks; b += 8 * G) {
       f4 v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         v[u] = f4{0.f, 0.f, 0.f, 0.f};
-        if (b + 32 * u < nblocks) v[u] = *reinterpret_cast<const f4*>(src + (b + 32 * u) * pitch);
+        if (b + G * u < nblocks) v[u] = *reinterpret_cast<const f4*>(src + (b + G * u) * pitch);
       }
       s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
   }
 #pragma unroll
-  for (int o = 8; o < 64; o *= 2)
+  for (int o = LANES; o < 64; o *= 2)
 #pragma unroll
     for (int k = 0; k < 4; ++k) s[k] += __shfl_xor(s[k], o);
-  if ((threadIdx.x & 63) < 8) part[wave][l] = s;
+  if ((threadIdx.x & 63) < LANES) part[wave][l] = s;
   __syncthreads();
   const int64_t i = i0 + threadIdx.x;
-  if (threadIdx.x < 32 && i < count) {
+  if (threadIdx.x < 4 * LANES && i < count) {
     const int q = threadIdx.x >> 2, k = threadIdx.x & 3;
     float* const dst = i < head ? out + i : tail + (i - head);
     *dst += (part[0][q][k] + part[1][q][k]) + (part[2][q][k] + part[3][q][k]);
   }
 }
-// `partial`: 16-byte aligned
+// `partial`: 16-byte aligned.  Small gradients want many groups, large ones fewer workgroups: MI355X, us, one launch between events (6.1
+// when empty), with 32, 16 and 8 groups, and with 8 groups of 4-byte loads: 1024 copies of 6464 floats 8.6, 9.9, 14.1, 14.4; 512 of 9728
+// 7.4, 7.6, 10.0, 9.6; 512 of 26 880 12.9, 12.0, 13.1, 11.8; 170 of 49 536 9.7, 9.3, 9.7, 9.6; 42 of 197 376 10.0, 9.0, 8.9, 10.2; 21 of
+// 197 376 8.8, 7.0, 6.4, 8.5; 8 of 197 376 7.7, 6.2, 6.2, 6.2; 32 of 262 656 11.8, 9.0, 8.9, 9.0.
 inline void launch_reduce_partials(const float* partial, int nblocks, int64_t count, float* out, hipStream_t s, int64_t head = INT64_MAX,
                                    float* tail = nullptr) {
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((count + 31) / 32)), dim3(256), 0, s, partial, nblocks, count, out, head, tail);
+  auto launch = [&](auto kern, int elements) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((count + elements - 1) / elements)), dim3(256), 0, s, partial, nblocks, count, out, head, tail);
+  };
+  if (count < 16384) launch(reduce_partials_kernel<32>, 32);
+  else if (count < 131072) launch(reduce_partials_kernel<16>, 64);
+  else launch(reduce_partials_kernel<8>, 128);
 }
 
 // tanh(x) = 1 - 2 / (e^{2x} + 1) with the hardware exp2 and reciprocal: absolute error ~1e-7 (the values feed
