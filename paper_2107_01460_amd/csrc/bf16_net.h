@@ -14,7 +14,7 @@
 // forward pass of 32 768 samples through both networks and the sampling 159 -> 73 us.
 // Bound: two workgroups of four wavefronts share a CU (64 rows each, 128 of a lane's 256 registers accumulators), and a tile is
 // a chain of products (39 of 107 thousand cycles for the pair), tanh (16), gradients on the output side (15), copies and barriers
-// that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile; at 512 units 32 (six outputs) and 38 (one)
+// that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile; at 512 units 40 (six outputs) and 38 (one)
 // registers are spilled.  One workgroup of 128 rows per CU halves
 // that and left every phase uncovered: 778 us; eight wavefronts of 128 registers per 64 rows: 750 us (spills).
 #pragma once
@@ -88,8 +88,11 @@ struct Bf16Shape {
   static constexpr int WAVES = NW == 8 ? 4 : NW > 4 ? 3 : 2;
   static constexpr int P = H + 8;    // pitch of the tile: an odd number of 16-byte units
   static constexpr int PD = BM + 8;  // pitch of the output gradients
-  static constexpr size_t lds(bool train) { return sizeof(bf16_t) * ((BM + 8) * P + (train ? 32 * PD : 0) + 2 * H) + sizeof(float) * (12 + (train ? NW * 12 : 0)); }
+  // (64 rows of 512 units in training: 80 KB, half of a CU's)
+  static constexpr size_t lds(bool train) { return sizeof(bf16_t) * ((BM + 8) * P + (train ? 32 * PD : 0) + 2 * H) + (train ? sizeof(double) * BM / 16 * 11 + sizeof(float) * 8 : 0); }
 };
+
+static_assert(2 * Bf16Shape<512, 64>::lds(true) <= 160 * 1024, "workgroups per CU");
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));  // 16 bytes between a load and an LDS store (HIP's uint4 arrays may stay in scratch memory)
 __device__ __forceinline__ floatx16 mfma32_bf16(const bf16x8& a, const bf16x8& b, const floatx16& c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
@@ -121,9 +124,10 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   bf16_t* const w3t = tile + BM * P;                            // [8][P]  W3 transposed, rows past NOUT zero
   bf16_t* const dlt = w3t + 8 * P;                              // TRAIN: [4][8][PD] dL/d(output), split: three parts and zeros
   bf16_t* const bias = dlt + (TRAIN ? 32 * PD : 0);             // [2][H] (rounded values, exact)
-  float* const b3s = reinterpret_cast<float*>(bias + 2 * H);    // [8]
-  auto* const prep = reinterpret_cast<typename LossIn<TRAIN, Fin>::Prep*>(b3s + 8);  // TRAIN
-  float* const accS = b3s + 12;                                 // TRAIN: [NW][12] every wavefront's b3 gradient and loss statistics
+  constexpr int AS = NOUT + 5;
+  double* const accD = reinterpret_cast<double*>(bias + 2 * H);  // TRAIN: [BM / 16][AS] per group of sixteen samples: b3 gradient, loss statistics
+  float* const b3s = reinterpret_cast<float*>(accD + BM / 16 * 11);  // TRAIN: [6]
+  auto* const prep = reinterpret_cast<typename LossIn<TRAIN, Fin>::Prep*>(b3s + 6);  // TRAIN
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63, lo = lane & 31, hi = lane >> 5, l15 = lane & 15, l4 = lane >> 4;
@@ -150,7 +154,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   }
   if constexpr (TRAIN) {
     if (tid == 0) *prep = fin.prepare();
-    for (int e = tid; e < NW * 12; e += THREADS) accS[e] = 0.f;
+    for (int e = tid; e < BM / 16 * AS; e += THREADS) accD[e] = 0.0;
   }
 
   // ---- weights: k step `nxt` of the sequence layer 1, layer 2 (, dz1), and again for the next tile
@@ -360,7 +364,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
         const int grp = wave + NW * g;
         const int64_t s = s0 + 16 * grp + l15;
         if ((GPW * NW == BM / 16 || grp < BM / 16) && lane < 16) {
-          float dl[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+          float dl[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, mine = 0.f;
 #pragma unroll
           for (int k = 0; k < NOUT; ++k) dl[k] = 0.f;
           if (s < a.S) fin.compute(lin[g], *prep, outs[g], dl, st);
@@ -372,11 +376,12 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
             dlt[(16 + k) * PD + 16 * grp + l15] = (bf16_t)sp.l;
           }
 #pragma unroll
-          for (int k = 0; k < NOUT + 5; ++k) {  // (sums over the sixteen samples: there is no room for one per sample)
-            float v = k < NOUT ? dl[k < NOUT ? k : 0] : st[k < NOUT ? 0 : k - NOUT];
-            for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
-            if (lane == 0) accS[wave * 12 + k] += v;
+          for (int k = 0; k < AS; ++k) {  // (sums over the sixteen samples: there is no room for one per sample)
+            if (k >= NOUT && (Fin::kStats >> (k >= NOUT ? k - NOUT : 0) & 1) == 0) continue;
+            const float v = row_sum16(k < NOUT ? dl[k < NOUT ? k : 0] : st[k < NOUT ? 0 : k - NOUT]);
+            mine = l15 == k ? v : mine;
           }
+          if (l15 < AS) accD[grp * AS + l15] += mine;
         }
       }
       __syncthreads();
@@ -462,8 +467,9 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
 #pragma unroll
         for (int z = 0; z < WM; ++z) v += G[z * H * NOUT + e];
       } else {
-#pragma unroll
-        for (int z = 0; z < NW; ++z) v += accS[z * 12 + e - H * NOUT];
+        double sum = 0.0;
+        for (int z = 0; z < BM / 16; ++z) sum += accD[z * AS + e - H * NOUT];
+        v = (float)sum;
       }
       own[e] = v;
     }

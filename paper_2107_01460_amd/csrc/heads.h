@@ -1,8 +1,20 @@
 // Output layers (6 logits / 1 value) on the vector ALUs, Gumbel-max sampling, log-softmax.
 #pragma once
+#include <type_traits>
+
 #include "common.h"
 
 namespace marl {
+
+// Sum over the sixteen lanes of a row, all of them active, in every lane.
+__device__ __forceinline__ float row_sum16(float v) {
+  auto add = [&](auto ctrl) { v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true)); };
+  add(std::integral_constant<int, 0xb1>{});   // the neighbour
+  add(std::integral_constant<int, 0x4e>{});   // the other pair of four
+  add(std::integral_constant<int, 0x141>{});  // the other four of eight
+  add(std::integral_constant<int, 0x140>{});  // the other eight
+  return v;
+}
 
 constexpr int kHeadTile = 64;    // samples per tile
 constexpr int kHeadChunk = 128;  // hidden units staged in LDS at a time

@@ -12,7 +12,7 @@
 // Bound (first of these sizes): no unit is full.  Matrix cores are busy 43 % and vector instructions 24 % of the cycles, and the weights
 // come from the L2 at 15 TB/s (1.28 MB per tile of 32 rows; 86 million reads of 128 bytes), which two workgroups per CU (one above 256
 // units) keep going through each other's phases; their 128 registers a lane leave a ring of two k steps of weights and up to 15 spilled
-// registers (11, 0 and 15 at the sizes above; loss statistics and constants in LDS, 1-2 % of a training iteration).  64-row tiles halve the bytes, but leave room for one workgroup per CU, whose phases
+// registers (11, 1 and 15 at the sizes above; 51 at 32 units; loss statistics and constants in LDS, 1-2 % of a training iteration).  64-row tiles halve the bytes, but leave room for one workgroup per CU, whose phases
 // without products (tanh, loss, gradients: 37 of 81 thousand cycles) nothing covers: the same time at the first size, 7 % longer updates
 // at 50 000 samples.  Forward passes of many samples hold less and take the 64-row tiles.  h1 stored at the end of a tile instead of
 // before layer 2's product, so that no weight waits behind it: 720 -> 759 us.
@@ -46,9 +46,14 @@ struct SplitNetShape {
   // the wavefronts of a workgroup are dealt 2, 2, 1, 1)
   static constexpr int waves(bool train) { return train ? (NW > 8 ? 3 : 4) : NW > 8 ? 3 : H <= 128 ? 4 : 2; }
   static constexpr size_t lds(bool train, int nout) {
-    return sizeof(bf16_t) * 3 * (BM + 8) * P + sizeof(float) * (2 * H + 16) + (train ? sizeof(bf16_t) * 24 * PD + sizeof(float) * (BM * 8 + H * (nout > 1 ? 8 : 1) + BM * (nout + 5)) : 0);
+    return sizeof(bf16_t) * 3 * (BM + 8) * P + sizeof(float) * (2 * H + 4) +
+           (train ? sizeof(bf16_t) * 24 * PD + sizeof(float) * (12 + BM * 8 + H * (nout > 1 ? 8 : 1)) + sizeof(double) * BM / 16 * (nout + 5) : 0);
   }
 };
+// Training workgroups of narrow networks that share a CU's LDS (loss statistics of 32 sample slots instead of two groups took one of
+// them: 50 000 samples of 147 inputs, 128 units, 20 minibatches 4.81 -> 4.97 ms)
+static_assert(4 * SplitNetShape<128, 32>::lds(true, 6) <= 160 * 1024 && 5 * SplitNetShape<96, 32>::lds(true, 6) <= 160 * 1024 &&
+                  7 * SplitNetShape<64, 32>::lds(true, 6) <= 160 * 1024, "workgroups per CU");
 
 template <bool TRAIN, class Fin>
 struct SplitNetLossIn { typedef int type, Prep; };
@@ -78,12 +83,12 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
   bf16_t* const w3t = tile + 3 * PLANE;                          // [3][8][P]  W3 transposed, split, rows past NOUT zero
   float* const bias = reinterpret_cast<float*>(w3t + 3 * PLANE3);  // [2][H]
   int* const inexact = reinterpret_cast<int*>(bias + 2 * H);     // [4] is a value of the tile's input not exact in bf16?
-  float* const b3s = bias + 2 * H + 4;                           // [8]
+  float* const b3s = bias + 2 * H + 4;                           // TRAIN: [8]
   auto* const prep = reinterpret_cast<typename SplitNetLossIn<TRAIN, Fin>::Prep*>(b3s + 8);  // TRAIN
-  float* const dls = bias + 2 * H + 16;                          // TRAIN: [BM][8] dL/d(output), zeros past NOUT
+  double* const accD = reinterpret_cast<double*>(bias + 2 * H + 16);  // TRAIN: [BM / 16][AS] per group of sixteen samples: b3 gradient, loss statistics
+  float* const dls = reinterpret_cast<float*>(accD + BM / 16 * AS);  // TRAIN: [BM][8] dL/d(output), zeros past NOUT
   float* const w3s = dls + BM * 8;                               // TRAIN: [H][W3P]
-  float* const accS = w3s + H * W3P;                             // TRAIN: [BM][AS] per sample slot: b3 gradient, loss statistics
-  bf16_t* const dlt = reinterpret_cast<bf16_t*>(accS + BM * AS);  // TRAIN: [3][8][PD] dL/d(output), split and transposed
+  bf16_t* const dlt = reinterpret_cast<bf16_t*>(w3s + H * W3P);  // TRAIN: [3][8][PD] dL/d(output), split and transposed
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63, lo = lane & 31, hi = lane >> 5, l15 = lane & 15, l4 = lane >> 4;
@@ -106,7 +111,7 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
     for (int e = tid; e < H * W3P; e += THREADS) w3s[e] = e % W3P < NOUT ? a.W3[e / W3P * NOUT + e % W3P] : 0.f;
     for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
     for (int e = tid; e < BM * 8; e += THREADS) dls[e] = 0.f;
-    for (int e = tid; e < BM * AS; e += THREADS) accS[e] = 0.f;
+    for (int e = tid; e < BM / 16 * AS; e += THREADS) accD[e] = 0.0;
     if constexpr (TRAIN) {
       if (tid == 0) *prep = fin.prepare();
     }
@@ -348,13 +353,12 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
         const int grp = wave + NW * g;
         const int64_t s = s0 + 16 * grp + l15;
         if ((GPW * NW == BM / 16 || grp < BM / 16) && lane < 16) {
-          float dl[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+          float dl[NOUT], st[5] = {0.f, 0.f, 0.f, 0.f, 0.f}, mine = 0.f;
 #pragma unroll
           for (int k = 0; k < NOUT; ++k) dl[k] = 0.f;
           if (s < a.S) fin.compute(lin[g], *prep, outs[g], dl, st);
 #pragma unroll
           for (int k = 0; k < NOUT; ++k) {
-            accS[(16 * grp + l15) * AS + k] += dl[k];
             dls[(16 * grp + l15) * 8 + k] = dl[k];
             const SplitPair sp = split_pair_any(dl[k], 0.f);
             dlt[k * PD + 16 * grp + l15] = (bf16_t)sp.h;
@@ -362,7 +366,12 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
             dlt[(16 + k) * PD + 16 * grp + l15] = (bf16_t)sp.l;
           }
 #pragma unroll
-          for (int k = 0; k < 5; ++k) accS[(16 * grp + l15) * AS + NOUT + k] += st[k];
+          for (int k = 0; k < AS; ++k) {
+            if (k >= NOUT && (Fin::kStats >> (k >= NOUT ? k - NOUT : 0) & 1) == 0) continue;
+            const float v = row_sum16(k < NOUT ? dl[k < NOUT ? k : 0] : st[k < NOUT ? 0 : k - NOUT]);
+            mine = l15 == k ? v : mine;
+          }
+          if (l15 < AS) accD[grp * AS + l15] += mine;
         }
       }
       __syncthreads();
@@ -459,7 +468,9 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
 #pragma unroll
         for (int z = 0; z < WM; ++z) v += G[z * H * NOUT + e];
       } else {
-        for (int z = 0; z < BM; ++z) v += accS[z * AS + e - H * NOUT];
+        double sum = 0.0;
+        for (int z = 0; z < BM / 16; ++z) sum += accD[z * AS + e - H * NOUT];
+        v = (float)sum;
       }
       own[e] = v;
     }
