@@ -87,8 +87,7 @@ struct ParamMap {
   // lanes.  W1 is zero-padded to kpad1 rows (a multiple of 32).  For a training rollout (rollout_train_kernel) the actor's two
   // copies hold fp32 values instead, element (k, n) at ((k / 4) * H + n) * 4 + k % 4.
   int64_t sw_w1[2], sw_w2[2], sw_w2t[2];
-  bool fused[2];  // these copies exist
-  bool plain[2];  // the blocks W1 and W2 are filled (otherwise they have no room)
+  bool fused[2];  // these copies exist, and the blocks W1 and W2 have no room
   int din[2], kpad1[2];
   int hidden[2];
   int64_t total;  // floats of the whole working copy
@@ -97,7 +96,7 @@ __host__ __device__ inline int64_t split_weight_index(int64_t k, int64_t n, int6
 __host__ __device__ inline int64_t split_weight_plane(int64_t H) { return 16 * H; }
 // What a working copy is staged for: a forward pass, a training rollout (a forward map, the actor in fp32), an update.
 enum WeightUse { USE_FORWARD, USE_ROLLOUT, USE_UPDATE };
-// update: for an optimiser step, which may also read the blocks W1 and W2 of a fused network; otherwise for forward passes
+// update: for an optimiser step, which also reads W2 transposed; otherwise for forward passes
 inline ParamMap param_map(const Dims& d, bool update) {
   ParamMap m;
   const NetOffsets a = net_offsets(0, d.D, d.Ha, kActions), c = net_offsets(d.Pa, d.Dc, d.Hc, 1);
@@ -109,7 +108,6 @@ inline ParamMap param_map(const Dims& d, bool update) {
   for (int n = 0; n < 2; ++n) {
     m.kpad1[n] = (m.din[n] + 31) / 32 * 32;
     m.fused[n] = !d.bf16 && split_net_supported(m.hidden[n]);
-    m.plain[n] = update || !m.fused[n];
   }
   int64_t off = 0;
   auto take = [&](int64_t floats) {
@@ -119,7 +117,7 @@ inline ParamMap param_map(const Dims& d, bool update) {
   };
   for (int i = 0; i < 12; ++i) {
     m.src[i] = src[i];
-    m.dst[i] = take((i % 6 == 0 || i % 6 == 2) && !m.plain[i / 6] ? 0 : src[i + 1] - src[i]);
+    m.dst[i] = take((i % 6 == 0 || i % 6 == 2) && m.fused[i / 6] ? 0 : src[i + 1] - src[i]);
   }
   m.src[12] = src[12];
   m.dst[12] = off;

@@ -85,22 +85,6 @@ struct Split8 {
 
 template <bool ANY>
 __device__ __forceinline__ SplitPair split_two(float x, float y) { return ANY ? split_pair_any(x, y) : split_pair(x, y); }
-template <bool ANY>
-__device__ __forceinline__ Split8 split8(const float (&v)[8]) {
-  const SplitPair a = split_two<ANY>(v[0], v[1]), b = split_two<ANY>(v[2], v[3]), c = split_two<ANY>(v[4], v[5]), d = split_two<ANY>(v[6], v[7]);
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  Split8 s;
-  s.h = __builtin_bit_cast(bf16x8, u32x4{a.h, b.h, c.h, d.h});
-  s.m = __builtin_bit_cast(bf16x8, u32x4{a.m, b.m, c.m, d.m});
-  s.l = __builtin_bit_cast(bf16x8, u32x4{a.l, b.l, c.l, d.l});
-  return s;
-}
-template <bool ANY>
-__device__ __forceinline__ Split8 split8(float4 x, float4 y) {
-  const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-  return split8<ANY>(v);
-}
-
 // acc += A B over sixteen k (the small products first)
 __device__ __forceinline__ floatx16 mfma_split(const Split8& a, const Split8& b, floatx16 acc) {
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);

@@ -28,8 +28,10 @@ __device__ __forceinline__ void stage_param(float* dst, const ParamMap& pm, int6
   const int64_t e = i - pm.src[b];
   const int net = b >= 6, H = pm.hidden[net];
   const bool w1 = b == 0 || b == 6, w2 = b == 2 || b == 8;
-  if (pm.plain[net] || !(w1 || w2)) dst[pm.dst[b] + e] = v;
-  if (!pm.fused[net] || !(w1 || w2)) return;
+  if (!pm.fused[net] || !(w1 || w2)) {
+    dst[pm.dst[b] + e] = v;
+    return;
+  }
   const uint32_t r = (uint32_t)e / (uint32_t)H, c = (uint32_t)e - r * (uint32_t)H;  // (a block has fewer than 2^32 elements; a 64-bit division is 180 instructions)
   stage_element(dst, pm, net, w1 ? pm.sw_w1[net] : pm.sw_w2[net], v, r, c, for_rollout);
   if (w2 && for_update) store_split_weight(dst + pm.sw_w2t[net], v, c, r, H);
