@@ -351,10 +351,9 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
         if (AVEC) {
           ra[p] = *reinterpret_cast<const float4*>(src + min(m, g.M - 4));
         } else {
-          // (16 bytes at any 4-byte boundary; up to three floats past the row, which feed outputs that are never stored: rows of the
-          // caller's that need this are observations, whose buffer goes on for a whole slab behind the last row)
+          // 16 bytes at any 4-byte boundary, within the row (M is at least 27): stage() moves the last columns into place
           typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-          const f4u v = *reinterpret_cast<const f4u*>(src + min(m, g.M - 1));
+          const f4u v = *reinterpret_cast<const f4u*>(src + min(m, g.M - 4));
           ra[p] = make_float4(v.x, v.y, v.z, v.w);
         }
         if (past) ra[p] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -385,6 +384,12 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
 #pragma unroll
     for (int p = 0; p < A_VECS; ++p) {
       const int f = tid + 256 * p;
+      if (!A_KCONT && !AVEC) {
+        const int64_t m = m0 + 4 * (f % (BM / 4));
+        const int move = (int)(m - min(m, g.M - 4));
+        if (move & 1) ra[p] = make_float4(ra[p].y, ra[p].z, ra[p].w, ra[p].w);
+        if (move & 2) ra[p] = make_float4(ra[p].z, ra[p].w, ra[p].w, ra[p].w);
+      }
       store_split4<ANY>(A_KCONT ? &As[(f >> 3) * PK + 4 * (f & 7)] : &As[(f / (BM / 4)) * PMA + 4 * (f % (BM / 4))], A_PLANE, ra[p]);
     }
 #pragma unroll
