@@ -637,10 +637,15 @@ inline int32_t launch_fused_train_pair_inst(FusedTrainArgs a, const LossA& fa, F
   return launch_status();
 }
 
+// The kernel finds a row through its row order entry (x_ptr) and divides sample indices by the rows' and the loss's agent counts with
+// SmallDiv's product.
+inline bool fused_train_rows_ok(const RowSrc& X, int64_t S, const SmallDiv& agents) {
+  return X.gather != nullptr && small_div_ok(X.pd, S) && small_div_ok(agents, S);
+}
+
 template <int NOUT, class LossFn>
 inline int32_t launch_fused_train(int H, const FusedTrainArgs& a, const LossFn& fn, hipStream_t s) {
-  // the kernel divides sample indices by the rows' and the loss's agent counts with SmallDiv's product
-  if (!small_div_ok(a.X.pd, a.S) || !small_div_ok(fn.lc.ad, a.S)) return MARL_E_SIZE;
+  if (!fused_train_rows_ok(a.X, a.S, fn.lc.ad)) return MARL_E_SIZE;
   // algorithmic flops: forward 2S(DH + HH), backward 2S(HH + HH + DH)
   TimedLaunch timed(KC_FUSED_TRAIN, 2.0 * (double)a.S * (2.0 * a.Din * H + 3.0 * H * H), s);
   if (H == 128) {
@@ -664,8 +669,7 @@ inline int64_t fused_train_pair_partial_floats(int64_t S, int64_t gcount_a, int6
 // b.grad == a.grad + a.gcount
 template <int NOUT_A, int NOUT_B, class LossA, class LossB>
 inline int32_t launch_fused_train_pair(int H, const FusedTrainArgs& a, const LossA& fa, const FusedTrainArgs& b, const LossB& fb, hipStream_t s) {
-  if (!small_div_ok(a.X.pd, a.S) || !small_div_ok(fa.lc.ad, a.S) || !small_div_ok(b.X.pd, b.S) || !small_div_ok(fb.lc.ad, b.S))
-    return MARL_E_SIZE;
+  if (!fused_train_rows_ok(a.X, a.S, fa.lc.ad) || !fused_train_rows_ok(b.X, b.S, fb.lc.ad)) return MARL_E_SIZE;
   if (b.grad != a.grad + a.gcount) return MARL_E_SIZE;
   TimedLaunch timed(KC_FUSED_TRAIN, 2.0 * (double)(a.S + b.S) * (2.0 * a.Din * H + 3.0 * H * H), s);
   if (H == 128) {
