@@ -15,17 +15,18 @@ struct TnPlan {
 
 // What a tile costs, in us (MI355X, product and reduction of its copies; 368 shapes of 27 .. 1176 x 32 .. 1536 outputs over 256 ..
 // 262 144 samples, fitted per tile to about 5 %): the launches, a MB of copies, and a step of kGemmBK samples with one, two, three or
-// four workgroups on each CU.  Index 1: the rows of A can be read 16 bytes at a time (M a multiple of four).
+// four workgroups on each CU.  Index 1: the rows of A are 16-byte aligned (M a multiple of four).  Index 0, for loads of 16 bytes at any
+// 4-byte boundary: 827 products of 27 .. 1029 x 32 .. 512 outputs over 1024 .. 262 144 samples, fitted to 3-4 %.
 struct TnTileCost {
   int bm, bn;
   float launch[2], copies[2], step[2][4];
 };
 constexpr TnTileCost kTnTiles[] = {
-    {160, 128, {9.2f, 7.6f}, {0.43f, 0.44f}, {{2.77f, 3.58f}, {2.87f, 3.33f}}},
-    {128, 128, {8.2f, 7.4f}, {0.52f, 0.53f}, {{2.28f, 3.00f}, {2.30f, 2.70f}}},
-    {128, 64, {4.2f, 5.0f}, {0.69f, 0.61f}, {{2.00f, 2.44f, 3.27f, 4.33f}, {1.79f, 2.06f, 2.54f, 3.55f}}},
-    {96, 128, {7.8f, 6.9f}, {0.52f, 0.59f}, {{1.89f, 2.44f}, {1.92f, 2.23f}}},
-    {32, 128, {6.2f, 6.2f}, {0.65f, 0.71f}, {{1.02f, 1.36f}, {1.03f, 1.29f}}},
+    {160, 128, {7.7f, 7.6f}, {0.41f, 0.44f}, {{2.81f, 3.39f}, {2.87f, 3.33f}}},
+    {128, 128, {9.2f, 7.4f}, {0.45f, 0.53f}, {{2.06f, 2.73f}, {2.30f, 2.70f}}},
+    {128, 64, {7.6f, 5.0f}, {0.42f, 0.61f}, {{1.50f, 1.98f, 2.61f, 3.65f}, {1.79f, 2.06f, 2.54f, 3.55f}}},
+    {96, 128, {6.9f, 6.9f}, {0.47f, 0.59f}, {{1.94f, 2.28f}, {1.92f, 2.23f}}},
+    {32, 128, {7.1f, 6.2f}, {0.51f, 0.71f}, {{0.98f, 1.26f}, {1.03f, 1.29f}}},
 };
 constexpr int64_t kTnCus = 256, kTnMinRange = 256;
 
@@ -48,9 +49,10 @@ inline double tn_cost(const TnTileCost& t, int64_t M, int64_t N, int64_t K) {
 // The tile that costs least.  Neither the padding alone nor the work of a tile decides it: a range of samples is a serial chain of steps,
 // so that few samples, which do not fill the chip, want the lowest tile (480 x 480, 1024 samples: 32 rows 17.5 us, 96 24.7, 128 x 64
 // 21.8), while many want the one that splits each value for the most products (588 x 512, 65 536 samples: 128 and 160 rows 243 and
-// 234 us, 32 rows 440 although they pad least); in between padding counts (147 x 256, 262 144 samples: 160 rows 150 us, 96 190, 128
-// 222, 32 258).  64 columns only where 128 would leave a half-empty last tile.  Among the 1864 products measured the choice is 0.1 % behind
-// the fastest tile on average; where two tiles are within 3 % the one that needs no further instantiation is taken.
+// 234 us, 32 rows 440 although they pad least); in between padding counts (147 x 256, 262 144 samples: 160 rows 143 us, 96 174, 128
+// 201, 32 231).  64 columns only where 128 would leave a half-empty last tile.  Among the 1864 products measured the choice is 0.1 % behind
+// the fastest tile on average (unaligned rows, 1667 products: 0.1 %, at most 10 %); where two tiles are within 3 % the one that needs no
+// further instantiation is taken.
 inline TnPlan tn_plan(int64_t M, int64_t N, int64_t K) {
   const bool halves = N % 128 != 0;
   const TnTileCost* best = nullptr;

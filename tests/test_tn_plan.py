@@ -9,20 +9,23 @@ TILES = [(128, 128), (128, 64), (160, 128), (96, 128), (32, 128)]
 # us on an MI355X of the product and the reduction of its copies with each of TILES, by rows, columns and samples.  None: a tile that the
 # shape does not take.
 MEASURED = {
-    (27, 64, 262144): (65.1, 47.8, 74, 54.9, 36.3),
-    (54, 512, 16384): (29, None, 32.6, 25.4, 20.4),
+    (27, 64, 262144): (58.9, 41.3, 65.2, 46, 30),
+    (54, 512, 16384): (29.9, None, 33.9, 25.7, 20.6),
     (64, 64, 262144): (64.7, 47.3, 73.4, 54, 53.2),
-    (75, 128, 1024): (26.2, None, 29.3, 22.3, 14.4),
-    (75, 128, 65536): (33, None, 36.4, 28.6, 29.2),
-    (75, 512, 16384): (31.1, None, 34.8, 26.6, 27.6),
+    (75, 128, 1024): (25.8, None, 29, 22.2, 14.9),
+    (75, 128, 65536): (31.5, None, 34.8, 27, 27),
+    (75, 512, 16384): (30.6, None, 34, 26.3, 26.5),
     (108, 160, 262144): (111.4, 100.9, 133.5, 169.5, 188.6),
     (108, 192, 65536): (40, 36.4, 45.3, 50.7, 52.1),
     (128, 384, 65536): (56.4, None, 64.9, 73.9, 77.4),
-    (147, 192, 1024): (26.5, 20.4, 31.3, 22.9, 14.5),
-    (147, 192, 16384): (31.5, 28.9, 35.1, 27.6, 24.5),
-    (147, 192, 65536): (64.6, 64.8, 49, 54.3, 66.2),
-    (147, 256, 262144): (222.4, None, 150.5, 190.1, 257.6),
+    (147, 192, 1024): (25.9, 19.8, 30.3, 22.6, 15),
+    (147, 192, 16384): (31.1, 27.3, 34.5, 27.4, 24.1),
+    (147, 192, 65536): (61.1, 55.3, 45.4, 49.8, 60.8),
+    (147, 256, 262144): (200.5, None, 142.8, 173.7, 231.4),
     (160, 160, 1024): (25.6, 19.3, 30.2, 22.2, 14.5),
+    (225, 160, 65536): (61.3, 55.5, 68.9, 67.4, 89.2),
+    (225, 192, 65536): (61.8, 55.8, 69.5, 67.4, 89.4),
+    (441, 160, 16384): (39.7, 35.6, 43.4, 38.6, 46.9),
     (216, 256, 262144): (210.9, None, 255.3, 260.7, 340.4),
     (216, 512, 65536): (102.8, None, 123.1, 120.2, 152.7),
     (224, 224, 4096): (27, 20.6, 31, 23.6, 15.9),
@@ -31,7 +34,7 @@ MEASURED = {
     (300, 256, 1024): (26.2, None, 30.9, 22.6, 15),
     (300, 256, 262144): (297.7, None, 251.1, 341.5, 460.2),
     (352, 1056, 16384): (96.1, 119.8, 112.6, 94.7, 139.7),
-    (441, 512, 65536): (203.2, None, 195.7, 219.5, 318.9),
+    (441, 512, 65536): (191.4, None, 186.2, 200.5, 300.6),
     (448, 1344, 16384): (142.3, 183.3, 134.4, 138.5, 223.3),
     (480, 480, 1024): (28.4, 21.8, 32.9, 24.7, 17.5),
     (480, 480, 16384): (61.4, 73.2, 62, 63, 90.7),
