@@ -106,37 +106,52 @@ struct GemmArgs {
 // do the same with one slab per k split when the caller passes split_out; without it, they add with atomics.
 
 // out[i] += sum_b partial[b * copy_pitch(count) + i], the copies added in a fixed order, so that the result does not depend on the
-// run; elements from `head` on go to tail[i - head] instead.  A workgroup is G groups of 256 / G lanes with 16 bytes each; group g sums
-// the copies b = g, g + G, g + 2 G, ..., eight of them on their way at a time, and the groups meet through lane exchanges and LDS.
+// run; elements from `head` on go to tail[i - head] instead.  The order: 32 sums of the copies b = g, g + 32, g + 64, ... (eight at a time, as
+// a tree), then a tree over g.  A group of 8 W lanes with 16 bytes each takes W of the 32 sums one after the other, so that a workgroup has
+// 32 W elements and a launch fewer workgroups; the results are the same for every W.
 // Bound: the copies' way from memory, and for few of them a launch.
 constexpr int64_t copy_pitch(int64_t count) { return (count + 3) & ~(int64_t)3; }
-template <int G>
+template <int W>
 static __global__ void __launch_bounds__(256) reduce_partials_kernel(const float* __restrict__ partial, int nblocks, int64_t count,
                                                                      float* __restrict__ out, int64_t head, float* __restrict__ tail) {
   typedef float f4 __attribute__((ext_vector_type(4)));
-  constexpr int LANES = 256 / G;
-  static_assert(LANES <= 32, "groups of a wavefront meet in lanes");
+  constexpr int LANES = 8 * W;
+  static_assert(W == 1 || W == 2, "groups of a wavefront meet in its lanes");
   __shared__ f4 part[4][LANES];
-  const int l = threadIdx.x % LANES, g = threadIdx.x / LANES, wave = threadIdx.x >> 6;
+  const int l = threadIdx.x % LANES, g = threadIdx.x / LANES * W, wave = threadIdx.x >> 6;
   const int64_t i0 = (int64_t)blockIdx.x * (4 * LANES), pitch = copy_pitch(count);
-  f4 s = {0.f, 0.f, 0.f, 0.f};
+  f4 s[W];
+#pragma unroll
+  for (int w = 0; w < W; ++w) s[w] = f4{0.f, 0.f, 0.f, 0.f};
   if (i0 + 4 * l < pitch) {
     const float* const src = partial + i0 + 4 * l;
-    for (int b = g; b < nblocks; b += 8 * G) {
-      f4 v[8];
+    if (nblocks <= 32) {  // one copy each
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        v[u] = f4{0.f, 0.f, 0.f, 0.f};
-        if (b + G * u < nblocks) v[u] = *reinterpret_cast<const f4*>(src + (b + G * u) * pitch);
-      }
-      s += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+      for (int w = 0; w < W; ++w)
+        if (g + w < nblocks) s[w] += *reinterpret_cast<const f4*>(src + (g + w) * pitch);
+    } else {
+#pragma unroll
+      for (int w = 0; w < W; ++w)
+        for (int b = g + w; b < nblocks; b += 256) {
+          f4 v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            v[u] = f4{0.f, 0.f, 0.f, 0.f};
+            if (b + 32 * u < nblocks) v[u] = *reinterpret_cast<const f4*>(src + (b + 32 * u) * pitch);
+          }
+          s[w] += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        }
     }
   }
 #pragma unroll
+  for (int w = 1; w < W; w *= 2)
+#pragma unroll
+    for (int u = 0; u < W; u += 2 * w) s[u] += s[u + w];
+#pragma unroll
   for (int o = LANES; o < 64; o *= 2)
 #pragma unroll
-    for (int k = 0; k < 4; ++k) s[k] += __shfl_xor(s[k], o);
-  if ((threadIdx.x & 63) < LANES) part[wave][l] = s;
+    for (int k = 0; k < 4; ++k) s[0][k] += __shfl_xor(s[0][k], o);
+  if ((threadIdx.x & 63) < LANES) part[wave][l] = s[0];
   __syncthreads();
   const int64_t i = i0 + threadIdx.x;
   if (threadIdx.x < 4 * LANES && i < count) {
@@ -145,18 +160,18 @@ static __global__ void __launch_bounds__(256) reduce_partials_kernel(const float
     *dst += (part[0][q][k] + part[1][q][k]) + (part[2][q][k] + part[3][q][k]);
   }
 }
-// `partial`: 16-byte aligned.  Small gradients want many groups, large ones fewer workgroups: MI355X, us, one launch between events (6.1
-// when empty), with 32, 16 and 8 groups, and with 8 groups of 4-byte loads: 1024 copies of 6464 floats 8.6, 9.9, 14.1, 14.4; 512 of 9728
-// 7.4, 7.6, 10.0, 9.6; 512 of 26 880 12.9, 12.0, 13.1, 11.8; 170 of 49 536 9.7, 9.3, 9.7, 9.6; 42 of 197 376 10.0, 9.0, 8.9, 10.2; 21 of
-// 197 376 8.8, 7.0, 6.4, 8.5; 8 of 197 376 7.7, 6.2, 6.2, 6.2; 32 of 262 656 11.8, 9.0, 8.9, 9.0.
+// `partial`: 16-byte aligned.  Workgroups of 32 elements for small gradients, of 64 for large ones, whose many workgroups cost more than
+// the longer way through the copies: MI355X, us, one launch between events (6.1 when empty), with 32, 64 and 128 elements, and with 8
+// groups of 32 4-byte loads: 1024 copies of 6464 floats 8.6, 10.5, 19.4, 14.5; 512 of 9728 7.5, 7.9, 12.4, 9.7; 512 of 26 880 13.0, 12.1,
+// 14.3, 11.7; 170 of 49 536 9.5, 9.7, 10.2, 9.4; 42 of 197 376 10.0, 9.7, 11.6, 10.2; 21 of 197 376 8.0, 7.0, 8.0, 8.6; 8 of 197 376 7.7,
+// 6.2, 7.3, 6.2; 32 of 262 656 10.0, 9.3, 10.9, 9.0.
 inline void launch_reduce_partials(const float* partial, int nblocks, int64_t count, float* out, hipStream_t s, int64_t head = INT64_MAX,
                                    float* tail = nullptr) {
   auto launch = [&](auto kern, int elements) {
     hipLaunchKernelGGL(kern, dim3((unsigned)((count + elements - 1) / elements)), dim3(256), 0, s, partial, nblocks, count, out, head, tail);
   };
-  if (count < 16384) launch(reduce_partials_kernel<32>, 32);
-  else if (count < 131072) launch(reduce_partials_kernel<16>, 64);
-  else launch(reduce_partials_kernel<8>, 128);
+  if (count < 16384) launch(reduce_partials_kernel<1>, 32);
+  else launch(reduce_partials_kernel<2>, 64);
 }
 
 // tanh(x) = 1 - 2 / (e^{2x} + 1) with the hardware exp2 and reciprocal: absolute error ~1e-7 (the values feed

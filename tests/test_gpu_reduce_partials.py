@@ -1,5 +1,5 @@
-"""Sums of the copies of a gradient, by the number of their groups: fewer than 16 384 floats, fewer than 131 072, more; counts that do not
-fill the last workgroup, few copies and many."""
+"""Sums of the copies of a gradient, below and above the 16 384 floats from which a workgroup takes twice as many: counts that do not fill the
+last workgroup, few copies and many."""
 import pytest
 
 import workloads as W
