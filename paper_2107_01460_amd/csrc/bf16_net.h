@@ -14,7 +14,7 @@
 // forward pass of 32 768 samples through both networks and the sampling 159 -> 73 us.
 // Bound: two workgroups of four wavefronts share a CU (64 rows each, 128 of a lane's 256 registers accumulators), and a tile is
 // a chain of products (39 of 107 thousand cycles for the pair), tanh (16), gradients on the output side (15), copies and barriers
-// that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile; at 512 units 40 (six outputs) and 38 (one)
+// that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile; at 512 units 36 (six outputs) and 38 (one)
 // registers are spilled.  One workgroup of 128 rows per CU halves
 // that and left every phase uncovered: 778 us; eight wavefronts of 128 registers per 64 rows: 750 us (spills).
 #pragma once
@@ -89,7 +89,7 @@ struct Bf16Shape {
   static constexpr int P = H + 8;    // pitch of the tile: an odd number of 16-byte units
   static constexpr int PD = BM + 8;  // pitch of the output gradients
   // (64 rows of 512 units in training: 80 KB, half of a CU's)
-  static constexpr size_t lds(bool train) { return sizeof(bf16_t) * ((BM + 8) * P + (train ? 32 * PD : 0) + 2 * H) + (train ? sizeof(double) * BM / 16 * 11 + sizeof(float) * 8 : 0); }
+  static constexpr size_t lds(bool train) { return sizeof(bf16_t) * ((BM + 8) * P + (train ? 32 * PD : 0) + 2 * H) + (train ? sizeof(float) * (NW * 11 + 8) : 0); }
 };
 
 static_assert(2 * Bf16Shape<512, 64>::lds(true) <= 160 * 1024, "workgroups per CU");
@@ -125,9 +125,9 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   bf16_t* const dlt = w3t + 8 * P;                              // TRAIN: [4][8][PD] dL/d(output), split: three parts and zeros
   bf16_t* const bias = dlt + (TRAIN ? 32 * PD : 0);             // [2][H] (rounded values, exact)
   constexpr int AS = NOUT + 5;
-  double* const accD = reinterpret_cast<double*>(bias + 2 * H);  // TRAIN: [BM / 16][AS] per group of sixteen samples: b3 gradient, loss statistics
-  float* const b3s = reinterpret_cast<float*>(accD + BM / 16 * 11);  // TRAIN: [6]
+  float* const b3s = reinterpret_cast<float*>(bias + 2 * H);    // TRAIN: [6]
   auto* const prep = reinterpret_cast<typename LossIn<TRAIN, Fin>::Prep*>(b3s + 6);  // TRAIN
+  float* const accS = b3s + 8;                                  // TRAIN: [NW][AS] every wavefront's b3 gradient and loss statistics
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63, lo = lane & 31, hi = lane >> 5, l15 = lane & 15, l4 = lane >> 4;
@@ -154,7 +154,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   }
   if constexpr (TRAIN) {
     if (tid == 0) *prep = fin.prepare();
-    for (int e = tid; e < BM / 16 * AS; e += THREADS) accD[e] = 0.0;
+    for (int e = tid; e < NW * AS; e += THREADS) accS[e] = 0.f;
   }
 
   // ---- weights: k step `nxt` of the sequence layer 1, layer 2 (, dz1), and again for the next tile
@@ -381,7 +381,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
             const float v = row_sum16(k < NOUT ? dl[k < NOUT ? k : 0] : st[k < NOUT ? 0 : k - NOUT]);
             mine = l15 == k ? v : mine;
           }
-          if (l15 < AS) accD[grp * AS + l15] += mine;
+          if (l15 < AS) accS[wave * AS + l15] += mine;
         }
       }
       __syncthreads();
@@ -467,9 +467,8 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
 #pragma unroll
         for (int z = 0; z < WM; ++z) v += G[z * H * NOUT + e];
       } else {
-        double sum = 0.0;
-        for (int z = 0; z < BM / 16; ++z) sum += accD[z * AS + e - H * NOUT];
-        v = (float)sum;
+#pragma unroll
+        for (int z = 0; z < NW; ++z) v += accS[z * AS + e - H * NOUT];
       }
       own[e] = v;
     }

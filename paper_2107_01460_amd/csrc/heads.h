@@ -6,13 +6,13 @@
 
 namespace marl {
 
-// Sum over the sixteen lanes of a row, all of them active, in every lane.
+// Sum over the sixteen lanes of a row, all of them active, in every lane: eight apart first.
 __device__ __forceinline__ float row_sum16(float v) {
   auto add = [&](auto ctrl) { v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true)); };
-  add(std::integral_constant<int, 0xb1>{});   // the neighbour
+  add(std::integral_constant<int, 0x128>{});  // rotations by eight and by four: lanes eight apart hold the same by then
+  add(std::integral_constant<int, 0x124>{});
   add(std::integral_constant<int, 0x4e>{});   // the other pair of four
-  add(std::integral_constant<int, 0x141>{});  // the other four of eight
-  add(std::integral_constant<int, 0x140>{});  // the other eight
+  add(std::integral_constant<int, 0xb1>{});   // the neighbour
   return v;
 }
 
