@@ -478,8 +478,12 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
 }
 
 // Workgroups of a launch at most: twice as many as the chip holds at once, so that the last tiles find a free place (50 000 samples,
-// 192 units: 132 us with as many as it holds, 104 with twice as many).
-constexpr unsigned split_net_grid(int H, int BM) { return H <= 128 ? 2048 : H <= 256 && BM == 32 ? 1024 : 512; }
+// 192 units: 132 us with as many as it holds, 104 with twice as many).  32-row tiles of 64 and 96 units: as many as it holds, seven and
+// five per CU (20 minibatches of 400 000 samples of 147 inputs, both networks of 64 units: 15.4 ms, with twice as many 15.8, with 2048, of
+// which the last 256 ran by themselves, 17.1; of 96 units 20.5, 20.7 and 21.7; of 50 000 samples and 96 units 4.08, 4.18 and 4.18).
+constexpr unsigned split_net_grid(int H, int BM) {
+  return BM == 32 && H == 64 ? 7 * 256 : BM == 32 && H == 96 ? 5 * 256 : H <= 128 ? 2048 : H <= 256 && BM == 32 ? 1024 : 512;
+}
 constexpr int kSplitTrainRows = 32;
 inline int64_t split_net_partial_floats(int H, int nout) { return split_net_grid(H, kSplitTrainRows) * copy_pitch((int64_t)H * nout + nout + 5); }
 
