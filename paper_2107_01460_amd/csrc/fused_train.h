@@ -13,7 +13,8 @@
 //   layer 1 -> h1 (A) | layer 2 -> h2 (registers, B), output layer | loss -> dL/dout | W3 gradient, dz2 = (dL/dout W3^T)(1 - h2^2) -> B |
 //   dW2 += h1^T dz2, dz1 = (dz2 W2^T)(1 - h1^2), the next tile's X to LDS | dz1 -> A, dW1 += X^T dz1
 // A wavefront's share of dW1 needs no dz1 but its own.  The tiles' rows have no padding; a row's 16-byte units are permuted
-// (tile_swizzle) so that both ways of reading a plane and the epilogues' stores meet every bank once.
+// (tile_swizzle) so that both ways of reading a plane meet every bank once.  (The epilogues' 8-byte stores do not: rows sixteen apart share
+// their places.  Bank conflicts are 7-8 % of the cycles at 128 units, 10-12 % at 64.)
 // Exact inputs: windows hold small integers and halves, whose lower split parts are zero.  X is then one plane and its products three
 // instead of six; the first tile with any other value, and all behind it, go through a second form of the loop, which splits X into three
 // planes once per tile (16 minibatches of 98 304 samples of 75 inputs, both networks of 64 units: 1.97 ms, in the second form 2.18; of 128
@@ -22,10 +23,10 @@
 // order; reduce_partials_kernel adds the copies.
 // Against one workgroup of eight wavefronts per CU that split activations where it read them (MI355X): 1 048 576 samples of 75 inputs,
 // 128 units, 6 outputs 1200 -> 890 us (161 TFLOP/s of fp32 products); 98 304 samples 141 -> 100 us; 2 097 152 of 27 inputs, 64 units 765 ->
-// 650 us.  Bound: the chain of a tile's phases.  Matrix cores are busy 41 % of the cycles at 128 units and 33 % at 64, vector
-// instructions 41 and 54 %; a wavefront waits a third of its time for barriers, LDS and memory and as long for an issue slot.  All
-// weights from the L1 instead of the L2 would save 5 % of a training iteration.  At 128 units and 96 inputs all 256 registers are in use:
-// with 77 of them spilled in the tile loop 98 304 samples took 119 us.  64-row tiles leave room for one workgroup per CU only.
+// 640 us.  Bound: the chain of a tile's phases.  Matrix cores are busy 41-46 % of the cycles at 128 units and 33 % at 64, vector
+// instructions 42 and 54 %; a wavefront waits a third of its time for barriers, LDS and memory and as long for an issue slot.  All
+// weights from the L1 instead of the L2 would save 5 % of a training iteration.  At 128 units and 96 inputs all 256 registers are in use;
+// a form with 77 of them spilled in the tile loop took a fifth longer.  64-row tiles leave room for one workgroup per CU only.
 #pragma once
 #include "gemm.h"
 
@@ -90,8 +91,8 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   constexpr int BM = kFusedTile, NW = H / 32, THREADS = 64 * NW, PLANE = BM * H, Q1 = DMAX / 32, XBUF = BM * DMAX;
   constexpr int XR = 8 / NW;                            // rows of X a lane stages of each 32-column block
   constexpr int P3 = H + 8, PLANE3 = 8 * P3, PD = BM + 8, AS = NOUT + 5, RING = 2;
-  // The next tile's rows are requested behind layer 2 or, where their registers would be spilled, behind dW2 (64 units, 27 inputs,
-  // 2 097 152 samples: 636 us behind layer 2, 660 us behind dW2; 128 units, 75 inputs, 98 304 samples: 117 us and 97 us).
+  // The next tile's rows are requested behind layer 2 or, where their registers would be spilled, behind dW2 (64 units, 27 inputs: 4 %
+  // longer behind dW2; 128 units, 75 inputs: a fifth longer behind layer 2).
   constexpr bool X_EARLY = H == 64;
   constexpr int TI = NW == 4 ? 2 : 1, TJ = 2;           // dW2: a wavefront's block of 32 x 32 tiles
   static_assert((H == 64 || H == 128) && (DMAX == 32 || DMAX == 96), "tile shapes");
@@ -589,7 +590,7 @@ __global__ void __launch_bounds__(2 * H, 2) fused_train_pair_kernel(FusedTrainAr
 inline bool fused_train_supported(int H, int Din) { return (H == 64 || H == 128) && Din <= 93; }
 
 inline int64_t fused_train_tiles(int64_t S) { return (S + kFusedTile - 1) / kFusedTile; }
-// Workgroups of a launch at most: as many as the chip holds at once.
+// Workgroups of a launch at most: as many as the chip holds at once.  Each has a copy of the gradient in the workspace.
 inline int64_t fused_train_grid(int H, int Din, int64_t S) {
   return std::min<int64_t>(fused_train_tiles(S), H == 128 ? 512 : Din < 32 ? 1024 : 768);
 }
