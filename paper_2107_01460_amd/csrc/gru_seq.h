@@ -1,6 +1,6 @@
 // The GRU cell over a whole sequence in one launch each way: h' = (1 - z) n + z h for t = 0 .. T-1 and its gradient for
-// t = T-1 .. 0.  Sequences are independent of one another, so a workgroup keeps SM * 16 of them from the first step to the
-// last: the hidden state (forward) or its gradient (backward) never leaves the registers, the operand of the next
+// t = T-1 .. 0.  Sequences are independent of one another, so a workgroup keeps SM * 16 of them (in an update:
+// of their runs between the beginnings of episodes, SeqRuns) from the first step to the last: the hidden state (forward) or its gradient (backward) never leaves the registers, the operand of the next
 // step's product is handed over through LDS, and nothing but the per-step records goes through memory.
 //
 // The product with the hidden-to-hidden weights runs transposed, weights x state, on v_mfma_f32_16x16x32_bf16 with split
@@ -13,7 +13,11 @@
 //     the L2 once per step, a contraction step or two ahead of their use.
 // Measured against one launch per step and direction on the fp32 instruction (128 steps of 768 sequences, 128 units):
 // forward 2.7 ms -> 0.25 ms, backward 3.6 ms -> 0.5 ms; a training iteration of 1024 environments 171 -> 51 ms.
-// Bound there: a step is a chain of 72 matrix instructions per wavefront, a barrier and the gate arithmetic, about 2 us.
+// Bound there: a step is a chain of 72 matrix instructions per wavefront, a barrier and the gate arithmetic, 2.6 us forward and 3.4 us
+// backward, and a launch takes as many as the longest run has: with episodes of at most 50 steps in place of 128-step rollouts 386 ->
+// 174 us and 436 -> 185 us, the two networks' kernels beside each other 335 -> 217 us and 474 -> 240 us.  With enough sequences the bound
+// is the records' way to memory (128 units, 1 048 576 steps: 1.00 and 1.09 ms, 4.3 TB/s) or, above 128 units, the weights' way from the L2
+// (256 units, 262 144 steps: 1.28 and 1.50 ms, 15 TB/s; whole sequences in 128 workgroups 1.96 and 2.41 ms).
 #pragma once
 #include "gemm.h"
 #include "heads.h"
@@ -43,6 +47,43 @@ __device__ __forceinline__ void gru_stage_weight(float v, int k, int c, int H, b
 
 __device__ __forceinline__ float sigmoid_f32(float x) { return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x)); }
 
+// The runs of a minibatch of sequences: a state is zeroed where an episode begins, so that the steps between two such places, a run, depend
+// on nothing before them, and the runs of all sequences can go side by side.  A chain is then as long as an episode at most, not as
+// the rollout.  Run i of `env[]` covers `y` steps from row x = t * (S1 / per) + environment on and stands for `per` sequences; the longest come first (that is
+// for speed alone: workgroups take the next MT sequences when they are done with the last, and lanes of a workgroup whose run has
+// ended wait for the others).
+struct SeqRuns {
+  const int2* env;
+  const int* count;
+  int* next;  // counter of the groups taken, zero before the launch
+};
+// The next group of MT sequences of a workgroup (whole workgroup, uniform); false: none is left.
+template <int MT>
+__device__ __forceinline__ bool next_group(const SeqRuns& runs, int per, int* slot, int& first, int& total) {
+  if (threadIdx.x == 0) *slot = atomicAdd(runs.next, 1);
+  __syncthreads();
+  first = __builtin_amdgcn_readfirstlane(*slot) * MT;
+  total = *runs.count * per;
+  return first < total;
+}
+// Sequence k's row of a step's S1 and steps; past the end: 0 steps of the first sequence's row.
+__device__ __forceinline__ void run_of(const SeqRuns& runs, int per, int k, int total, int64_t& row, int& len) {
+  const bool in = k < total;
+  const int i = (in ? k : 0) / per, a = in ? k - i * per : 0;
+  const int2 r = runs.env[i];
+  row = (int64_t)r.x * per + a;
+  len = in ? r.y : 0;
+}
+template <int SM>
+__device__ __forceinline__ int longest_run(const int (&len)[SM]) {
+  int n = 0;
+#pragma unroll
+  for (int m = 0; m < SM; ++m) n = max(n, len[m]);
+#pragma unroll
+  for (int o = 8; o > 0; o /= 2) n = max(n, __shfl_xor(n, o));
+  return __builtin_amdgcn_readfirstlane(n);
+}
+
 // The records of a step, [S1][4H]: forward (h Wh_n + bh_n, r, z, n); the backward pass replaces them by the gradients of
 // the pre-activations (of h Wh_n + bh_n, r, z, n), so that columns 0 .. 3H-1 are the gradient of the hidden products (new
 // gate first) and columns H .. 4H-1 that of the input products.
@@ -58,6 +99,7 @@ struct GruFwdArgs {
   int per;
   int64_t S1;
   int T;
+  SeqRuns runs;  // SEG
 };
 
 // acc[i] += W[i] x B over 32 along the contraction, i-th of N independent tiles (small products first)
@@ -71,30 +113,21 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int KS, int SM, bool RES>
+// SEG: the runs of a.runs, a workgroup taking group after group; otherwise workgroup i has sequences i * MT .. for all T steps.
+template <int KS, int SM, bool RES, bool SEG>
 __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kernel(GruFwdArgs a) {
   constexpr int H = 32 * KS, UB = RES ? 1 : 2, MT = 16 * SM, P = H + 8, PLANE = MT * P;
   constexpr int THREADS = RES ? 128 * KS : 64 * KS;
   __shared__ __attribute__((aligned(16))) bf16_t Hs[2][3 * PLANE];
   __shared__ __attribute__((aligned(16))) float bias[4][H];  // r and z: both biases; n: input, hidden
+  __shared__ int group;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
-  const int64_t s0 = (int64_t)blockIdx.x * MT;
   for (int j = tid; j < H; j += THREADS) {
     bias[0][j] = a.bi[j] + a.bh[j];
     bias[1][j] = a.bi[H + j] + a.bh[H + j];
     bias[2][j] = a.bi[2 * H + j];
     bias[3][j] = a.bh[2 * H + j];
   }
-  int64_t srow[SM];  // clamped: rows past the end compute on the last one and store nothing
-  bool live[SM];
-  int64_t env[SM];
-#pragma unroll
-  for (int m = 0; m < SM; ++m) {
-    live[m] = s0 + 16 * m + lo < a.S1;
-    srow[m] = live[m] ? s0 + 16 * m + lo : a.S1 - 1;
-    env[m] = srow[m] / a.per;
-  }
-  const int64_t nenv = a.S1 / a.per;
   int unit[UB];  // first of this lane's four units
 #pragma unroll
   for (int b = 0; b < UB; ++b) unit[b] = 16 * (UB * wave + b) + 4 * q;
@@ -120,110 +153,137 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
 #pragma unroll
   for (int i = 0; i < (RES ? NI : RING - 1); ++i) load_w(i, w[i]);
 
-  float4 h[UB][SM], gi[UB][SM][3];
-  auto load_gi = [&](int t, int b) {
+  for (;;) {
+    int64_t row[SM];  // of the current step
+    int64_t env[SM];  // without SEG
+    int len[SM], steps = a.T;  // a sequence past its last step stays at that row and stores nothing
+    if (SEG) {
+      int first, total;
+      if (!next_group<MT>(a.runs, a.per, &group, first, total)) return;  // uniform
 #pragma unroll
-    for (int m = 0; m < SM; ++m)
+      for (int m = 0; m < SM; ++m) run_of(a.runs, a.per, first + 16 * m + lo, total, row[m], len[m]);
+      steps = longest_run(len);
+    } else {
 #pragma unroll
-      for (int g = 0; g < 3; ++g) gi[b][m][g] = *reinterpret_cast<const float4*>(a.Gi + ((int64_t)t * a.S1 + srow[m]) * 3 * H + g * H + unit[b]);
-  };
-  bool wild = false;  // was a state out of split_pair's range to begin with?  (One step's state is at most the last one's or 1.)
-  auto hand_over = [&](int buf, int b, int m) {
-    bf16_t* const dst = &Hs[buf][(16 * m + lo) * P + unit[b]];
-    if (wild) store_split4<true>(dst, PLANE, h[b][m]);
-    else store_split4<false>(dst, PLANE, h[b][m]);
-  };
-  int rs[SM];  // does the coming step start from a zero state
-  auto load_reset = [&](int t) {
-#pragma unroll
-    for (int m = 0; m < SM; ++m) rs[m] = t > 0 ? a.reset[(t - 1) * nenv + env[m]] : (a.reset0 != nullptr ? a.reset0[env[m]] : 0);
-  };
-  load_reset(0);
-  float top = 0.f;
-#pragma unroll
-  for (int b = 0; b < UB; ++b) {
-    load_gi(0, b);
-#pragma unroll
-    for (int m = 0; m < SM; ++m) {
-      h[b][m] = *reinterpret_cast<const float4*>(a.h_first + srow[m] * H + unit[b]);
-      if (rs[m]) h[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
-      top = max_abs(top, h[b][m]);
+      for (int m = 0; m < SM; ++m) {
+        const int64_t k = (int64_t)blockIdx.x * MT + 16 * m + lo;
+        row[m] = min(k, a.S1 - 1);
+        len[m] = k < a.S1 ? a.T : 0;
+        env[m] = row[m] / a.per;
+      }
     }
-  }
-  wild = split_out_of_range(top * 0x1p10f);  // room for a million steps' rounding
+    const int64_t nenv = a.S1 / a.per;
+    float4 h[UB][SM], gi[UB][SM][3];
+    auto load_gi = [&](int b, const int64_t (&at)[SM]) {
 #pragma unroll
-  for (int b = 0; b < UB; ++b)
+      for (int m = 0; m < SM; ++m)
 #pragma unroll
-    for (int m = 0; m < SM; ++m) hand_over(0, b, m);
-  __syncthreads();
-
-#pragma unroll 1
-  for (int t = 0; t < a.T; ++t) {
-    if (!RES) asm volatile("" : "+v"(woff));  // the loads stay inside the loop: hoisted, they would be spilled
-    const bf16_t* const frag = &Hs[t & 1][lo * P + 8 * q];
-    if (t + 1 < a.T) load_reset(t + 1);
+        for (int g = 0; g < 3; ++g) gi[b][m][g] = *reinterpret_cast<const float4*>(a.Gi + at[m] * 3 * H + g * H + unit[b]);
+    };
+    bool wild = false;  // was a state out of split_pair's range to begin with?  (One step's state is at most the last one's or 1.)
+    auto hand_over = [&](int buf, int b, int m) {
+      bf16_t* const dst = &Hs[buf][(16 * m + lo) * P + unit[b]];
+      if (wild) store_split4<true>(dst, PLANE, h[b][m]);
+      else store_split4<false>(dst, PLANE, h[b][m]);
+    };
+    int rs[SM];  // does the coming step start from a zero state
+    auto load_reset = [&](int t) {
+#pragma unroll
+      for (int m = 0; m < SM; ++m) rs[m] = t > 0 ? a.reset[(t - 1) * nenv + env[m]] : (a.reset0 != nullptr ? a.reset0[env[m]] : 0);
+    };
+    if (!SEG) load_reset(0);
+    float top = 0.f;
 #pragma unroll
     for (int b = 0; b < UB; ++b) {
-      floatx4 acc[3][SM];
+      load_gi(b, row);
 #pragma unroll
-      for (int g = 0; g < 3; ++g)
+      for (int m = 0; m < SM; ++m) {
+        if (SEG) rs[m] = row[m] >= a.S1;  // a run that does not begin at step 0 begins where an episode does
+        h[b][m] = *reinterpret_cast<const float4*>(a.h_first + (SEG && rs[m] ? 0 : row[m]) * H + unit[b]);
+        if (rs[m]) h[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
+        top = max_abs(top, h[b][m]);
+      }
+    }
+    wild = split_out_of_range(top * 0x1p10f);  // room for a million steps' rounding
 #pragma unroll
-        for (int m = 0; m < SM; ++m) acc[g][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int b = 0; b < UB; ++b)
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int i = b * KS + ks, slot = i % RING;
-        if (!RES) load_w((i + RING - 1) % NI, w[(i + RING - 1) % RING]);
-        Split8 x[SM];
+      for (int m = 0; m < SM; ++m) hand_over(0, b, m);
+    __syncthreads();
+
+#pragma unroll 1
+    for (int t = 0; t < steps; ++t) {
+      if (!RES) asm volatile("" : "+v"(woff));  // the loads stay inside the loop: hoisted, they would be spilled
+      const bf16_t* const frag = &Hs[t & 1][lo * P + 8 * q];
+      if (!SEG && t + 1 < steps) load_reset(t + 1);
+      int64_t next[SM];
 #pragma unroll
-        for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * step_of(ks), PLANE);
+      for (int m = 0; m < SM; ++m) next[m] = t + 1 < len[m] ? row[m] + a.S1 : row[m];
+#pragma unroll
+      for (int b = 0; b < UB; ++b) {
+        floatx4 acc[3][SM];
+#pragma unroll
+        for (int g = 0; g < 3; ++g)
+#pragma unroll
+          for (int m = 0; m < SM; ++m) acc[g][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          const int i = b * KS + ks, slot = i % RING;
+          if (!RES) load_w((i + RING - 1) % NI, w[(i + RING - 1) % RING]);
+          Split8 x[SM];
+#pragma unroll
+          for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * step_of(ks), PLANE);
 #define MARL_GRU_PRODUCT(WP, XP)            \
   _Pragma("unroll") for (int g = 0; g < 3; ++g) \
   _Pragma("unroll") for (int m = 0; m < SM; ++m) acc[g][m] = mfma16(w[slot][3 * g + WP], x[m].XP, acc[g][m]);
-        MARL_GRU_PRODUCT(2, h)
-        MARL_GRU_PRODUCT(0, l)
-        MARL_GRU_PRODUCT(1, m)
-        MARL_GRU_PRODUCT(1, h)
-        MARL_GRU_PRODUCT(0, m)
-        MARL_GRU_PRODUCT(0, h)
+          MARL_GRU_PRODUCT(2, h)
+          MARL_GRU_PRODUCT(0, l)
+          MARL_GRU_PRODUCT(1, m)
+          MARL_GRU_PRODUCT(1, h)
+          MARL_GRU_PRODUCT(0, m)
+          MARL_GRU_PRODUCT(0, h)
 #undef MARL_GRU_PRODUCT
-      }
-      float4 bs[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) bs[k] = *reinterpret_cast<const float4*>(&bias[k][unit[b]]);
-      float4 vr[SM], vz[SM], vn[SM], vh[SM], out[SM];
-#pragma unroll
-      for (int m = 0; m < SM; ++m) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          auto at = [e](const float4& v) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; };
-          auto put = [e](float4& v, float f) { (e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w) = f; };
-          const float r = sigmoid_f32(at(gi[b][m][0]) + (acc[0][m][e] + at(bs[0])));
-          const float z = sigmoid_f32(at(gi[b][m][1]) + (acc[1][m][e] + at(bs[1])));
-          const float hn = acc[2][m][e] + at(bs[3]);
-          const float n = tanh_f32((at(gi[b][m][2]) + at(bs[2])) + r * hn);
-          put(vr[m], r); put(vz[m], z); put(vh[m], hn); put(vn[m], n);
-          put(out[m], (1.0f - z) * n + z * at(h[b][m]));
         }
-      }
-      if (t + 1 < a.T) load_gi(t + 1, b);  // ahead of this step's stores: the counter that loads wait on is in order
+        float4 bs[4];
 #pragma unroll
-      for (int m = 0; m < SM; ++m) {
-        const int64_t row = (int64_t)t * a.S1 + srow[m];
-        if (live[m]) {
-          if (a.rec != nullptr) {
-            float* const d = a.rec + row * 4 * H + unit[b];
-            *reinterpret_cast<float4*>(d) = vh[m];
-            *reinterpret_cast<float4*>(d + H) = vr[m];
-            *reinterpret_cast<float4*>(d + 2 * H) = vz[m];
-            *reinterpret_cast<float4*>(d + 3 * H) = vn[m];
+        for (int k = 0; k < 4; ++k) bs[k] = *reinterpret_cast<const float4*>(&bias[k][unit[b]]);
+        float4 vr[SM], vz[SM], vn[SM], vh[SM], out[SM];
+#pragma unroll
+        for (int m = 0; m < SM; ++m) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            auto at = [e](const float4& v) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; };
+            auto put = [e](float4& v, float f) { (e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w) = f; };
+            const float r = sigmoid_f32(at(gi[b][m][0]) + (acc[0][m][e] + at(bs[0])));
+            const float z = sigmoid_f32(at(gi[b][m][1]) + (acc[1][m][e] + at(bs[1])));
+            const float hn = acc[2][m][e] + at(bs[3]);
+            const float n = tanh_f32((at(gi[b][m][2]) + at(bs[2])) + r * hn);
+            put(vr[m], r); put(vz[m], z); put(vh[m], hn); put(vn[m], n);
+            put(out[m], (1.0f - z) * n + z * at(h[b][m]));
           }
-          *reinterpret_cast<float4*>(a.hs + row * H + unit[b]) = out[m];
         }
-        h[b][m] = rs[m] ? make_float4(0.f, 0.f, 0.f, 0.f) : out[m];
-        hand_over((t + 1) & 1, b, m);
+        if (t + 1 < steps) load_gi(b, next);  // ahead of this step's stores: the counter that loads wait on is in order
+#pragma unroll
+        for (int m = 0; m < SM; ++m) {
+          if (t < len[m]) {
+            if (SEG || a.rec != nullptr) {
+              float* const d = a.rec + row[m] * 4 * H + unit[b];
+              *reinterpret_cast<float4*>(d) = vh[m];
+              *reinterpret_cast<float4*>(d + H) = vr[m];
+              *reinterpret_cast<float4*>(d + 2 * H) = vz[m];
+              *reinterpret_cast<float4*>(d + 3 * H) = vn[m];
+            }
+            *reinterpret_cast<float4*>(a.hs + row[m] * H + unit[b]) = out[m];
+          }
+          h[b][m] = !SEG && rs[m] ? make_float4(0.f, 0.f, 0.f, 0.f) : out[m];
+          hand_over((t + 1) & 1, b, m);
+        }
       }
+#pragma unroll
+      for (int m = 0; m < SM; ++m) row[m] = next[m];
+      lds_barrier();
     }
-    lds_barrier();
+    if (!SEG) return;
   }
 }
 
@@ -233,10 +293,11 @@ struct GruBwdArgs {
   const float* dl;       // [T][S1][NOUT] gradient of the outputs
   float* rec;            // [T][S1][4H] records, replaced by gradients
   const float* hs;       // [T][S1][H] state before every step (before a reset)
-  const uint8_t* reset;  // [T - 1][S1 / per], as forward
+  const uint8_t* reset;  // [T - 1][S1 / per], as forward (step by step)
   int per;
   int64_t S1;
   int T;
+  SeqRuns runs;
 };
 
 template <int KS, int SM, bool RES, int NOUT>
@@ -245,18 +306,9 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
   constexpr int THREADS = RES ? 128 * KS : 64 * KS;
   __shared__ __attribute__((aligned(16))) bf16_t Gs[3 * PLANE];
   __shared__ __attribute__((aligned(16))) float W3s[H * NOUT];
+  __shared__ int group;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
-  const int64_t s0 = (int64_t)blockIdx.x * MT;
   for (int j = tid; j < H * NOUT; j += THREADS) W3s[j] = a.W3[j];
-  int64_t srow[SM], env[SM];
-  bool live[SM];
-#pragma unroll
-  for (int m = 0; m < SM; ++m) {
-    live[m] = s0 + 16 * m + lo < a.S1;
-    srow[m] = live[m] ? s0 + 16 * m + lo : a.S1 - 1;
-    env[m] = srow[m] / a.per;
-  }
-  const int64_t nenv = a.S1 / a.per;
   int unit[UB];
 #pragma unroll
   for (int b = 0; b < UB; ++b) unit[b] = 16 * (UB * wave + b) + 4 * q;
@@ -274,116 +326,125 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
 #pragma unroll
   for (int i = 0; i < (RES ? NI : RING - 1); ++i) load_w(i, w[i]);
 
-  float4 rec[UB][SM][4], hp[UB][SM], carry[UB][SM];
-  float dl[SM][NOUT];
-  int rs[SM];
-  auto load_step = [&](int t, int b, int m) {
-    const int64_t row = (int64_t)t * a.S1 + srow[m];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) rec[b][m][k] = *reinterpret_cast<const float4*>(a.rec + row * 4 * H + k * H + unit[b]);
-    hp[b][m] = *reinterpret_cast<const float4*>(a.hs + row * H + unit[b]);
-  };
-  auto load_row = [&](int t, int m) {
-    const int64_t row = (int64_t)t * a.S1 + srow[m];
-#pragma unroll
-    for (int k = 0; k < NOUT; ++k) dl[m][k] = a.dl[row * NOUT + k];
-    rs[m] = t > 0 ? a.reset[(t - 1) * nenv + env[m]] : 0;
-  };
-#pragma unroll
-  for (int m = 0; m < SM; ++m) {
-    load_row(a.T - 1, m);
-#pragma unroll
-    for (int b = 0; b < UB; ++b) {
-      load_step(a.T - 1, b, m);
-      carry[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
-  __syncthreads();
-
-#pragma unroll 1
-  for (int t = a.T - 1; t >= 0; --t) {
-    if (!RES) asm volatile("" : "+v"(woff));
-    int was_reset[SM];
+  for (;;) {
+    int first, total;
+    if (!next_group<MT>(a.runs, a.per, &group, first, total)) return;  // uniform
+    int64_t row[SM];  // of the current step; a sequence past its first step stays there and stores nothing
+    int len[SM];
+    bool from_zero[SM];
 #pragma unroll
     for (int m = 0; m < SM; ++m) {
-      was_reset[m] = rs[m];
+      run_of(a.runs, a.per, first + 16 * m + lo, total, row[m], len[m]);
+      from_zero[m] = row[m] >= a.S1;
+      row[m] += max(len[m] - 1, 0) * a.S1;
+    }
+    const int steps = longest_run(len);
+    float4 rec[UB][SM][4], hp[UB][SM], carry[UB][SM];
+    float dl[SM][NOUT];
+    auto load_step = [&](int b, int m) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) rec[b][m][k] = *reinterpret_cast<const float4*>(a.rec + row[m] * 4 * H + k * H + unit[b]);
+      hp[b][m] = *reinterpret_cast<const float4*>(a.hs + row[m] * H + unit[b]);
+    };
+    auto load_row = [&](int m) {
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) dl[m][k] = a.dl[row[m] * NOUT + k];
+    };
+#pragma unroll
+    for (int m = 0; m < SM; ++m) {
+      load_row(m);
 #pragma unroll
       for (int b = 0; b < UB; ++b) {
-        float4 gr, gz, gn, gh;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          auto at = [e](const float4& v) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; };
-          auto put = [e](float4& v, float f) { (e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w) = f; };
-          float dh = at(carry[b][m]);
-#pragma unroll
-          for (int k = 0; k < NOUT; ++k) dh = fmaf(dl[m][k], W3s[(unit[b] + e) * NOUT + k], dh);
-          const float hn = at(rec[b][m][0]), r = at(rec[b][m][1]), z = at(rec[b][m][2]), n = at(rec[b][m][3]);
-          const float hprev = rs[m] ? 0.f : at(hp[b][m]);
-          const float dpre_n = dh * (1.0f - z) * (1.0f - n * n);
-          put(gr, dpre_n * hn * r * (1.0f - r));
-          put(gz, dh * (hprev - n) * z * (1.0f - z));
-          put(gn, dpre_n);
-          put(gh, dpre_n * r);
-          put(carry[b][m], dh * z);
-        }
-        if (live[m]) {
-          float* const d = a.rec + ((int64_t)t * a.S1 + srow[m]) * 4 * H + unit[b];
-          *reinterpret_cast<float4*>(d) = gh;
-          *reinterpret_cast<float4*>(d + H) = gr;
-          *reinterpret_cast<float4*>(d + 2 * H) = gz;
-          *reinterpret_cast<float4*>(d + 3 * H) = gn;
-        }
-        bf16_t* const dst = &Gs[(16 * m + lo) * P + unit[b]];
-        if (split_out_of_range(max_abs(max_abs(max_abs(0.f, gr), gz), gh))) {
-          store_split4<true>(dst, PLANE, gr);
-          store_split4<true>(dst + H, PLANE, gz);
-          store_split4<true>(dst + 2 * H, PLANE, gh);
-        } else {
-          store_split4<false>(dst, PLANE, gr);
-          store_split4<false>(dst + H, PLANE, gz);
-          store_split4<false>(dst + 2 * H, PLANE, gh);
-        }
-        if (t > 0) load_step(t - 1, b, m);
+        load_step(b, m);
+        carry[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      if (t > 0) load_row(t - 1, m);
     }
-    if (t == 0) break;  // uniform: nothing flows into the initial state
-    lds_barrier();
-    floatx4 acc[UB][SM];
+
+#pragma unroll 1
+    for (int t = 0; t < steps; ++t) {  // t-th step from the end of each run
+      if (!RES) asm volatile("" : "+v"(woff));
 #pragma unroll
-    for (int b = 0; b < UB; ++b)
+      for (int m = 0; m < SM; ++m) {
+        const bool zero = from_zero[m] && t + 1 == len[m];
+        const int64_t here = row[m];
+        if (t + 1 < len[m]) row[m] -= a.S1;
 #pragma unroll
-      for (int m = 0; m < SM; ++m) acc[b][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const bf16_t* const frag = Gs + lo * P + 8 * q;
+        for (int b = 0; b < UB; ++b) {
+          float4 gr, gz, gn, gh;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int slot = i % RING;
-      if (!RES) load_w((i + RING - 1) % NI, w[(i + RING - 1) % RING]);
-      Split8 x[SM];
+          for (int e = 0; e < 4; ++e) {
+            auto at = [e](const float4& v) { return e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w; };
+            auto put = [e](float4& v, float f) { (e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w) = f; };
+            float dh = at(carry[b][m]);
 #pragma unroll
-      for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * i, PLANE);
+            for (int k = 0; k < NOUT; ++k) dh = fmaf(dl[m][k], W3s[(unit[b] + e) * NOUT + k], dh);
+            const float hn = at(rec[b][m][0]), r = at(rec[b][m][1]), z = at(rec[b][m][2]), n = at(rec[b][m][3]);
+            const float hprev = zero ? 0.f : at(hp[b][m]);
+            const float dpre_n = dh * (1.0f - z) * (1.0f - n * n);
+            put(gr, dpre_n * hn * r * (1.0f - r));
+            put(gz, dh * (hprev - n) * z * (1.0f - z));
+            put(gn, dpre_n);
+            put(gh, dpre_n * r);
+            put(carry[b][m], dh * z);
+          }
+          if (t < len[m]) {
+            float* const d = a.rec + here * 4 * H + unit[b];
+            *reinterpret_cast<float4*>(d) = gh;
+            *reinterpret_cast<float4*>(d + H) = gr;
+            *reinterpret_cast<float4*>(d + 2 * H) = gz;
+            *reinterpret_cast<float4*>(d + 3 * H) = gn;
+          }
+          bf16_t* const dst = &Gs[(16 * m + lo) * P + unit[b]];
+          if (split_out_of_range(max_abs(max_abs(max_abs(0.f, gr), gz), gh))) {
+            store_split4<true>(dst, PLANE, gr);
+            store_split4<true>(dst + H, PLANE, gz);
+            store_split4<true>(dst + 2 * H, PLANE, gh);
+          } else {
+            store_split4<false>(dst, PLANE, gr);
+            store_split4<false>(dst + H, PLANE, gz);
+            store_split4<false>(dst + 2 * H, PLANE, gh);
+          }
+          if (t + 1 < steps) load_step(b, m);
+        }
+        if (t + 1 < steps) load_row(m);
+      }
+      if (t + 1 == steps) break;  // uniform: nothing flows into the initial state
+      lds_barrier();
+      floatx4 acc[UB][SM];
+#pragma unroll
+      for (int b = 0; b < UB; ++b)
+#pragma unroll
+        for (int m = 0; m < SM; ++m) acc[b][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+      const bf16_t* const frag = Gs + lo * P + 8 * q;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int slot = i % RING;
+        if (!RES) load_w((i + RING - 1) % NI, w[(i + RING - 1) % RING]);
+        Split8 x[SM];
+#pragma unroll
+        for (int m = 0; m < SM; ++m) x[m] = frag_row(frag + 16 * m * P + 32 * i, PLANE);
 #define MARL_GRU_PRODUCT(WP, XP)             \
   _Pragma("unroll") for (int b = 0; b < UB; ++b) \
   _Pragma("unroll") for (int m = 0; m < SM; ++m) acc[b][m] = mfma16(w[slot][b][WP], x[m].XP, acc[b][m]);
-      MARL_GRU_PRODUCT(2, h)
-      MARL_GRU_PRODUCT(0, l)
-      MARL_GRU_PRODUCT(1, m)
-      MARL_GRU_PRODUCT(1, h)
-      MARL_GRU_PRODUCT(0, m)
-      MARL_GRU_PRODUCT(0, h)
+        MARL_GRU_PRODUCT(2, h)
+        MARL_GRU_PRODUCT(0, l)
+        MARL_GRU_PRODUCT(1, m)
+        MARL_GRU_PRODUCT(1, h)
+        MARL_GRU_PRODUCT(0, m)
+        MARL_GRU_PRODUCT(0, h)
 #undef MARL_GRU_PRODUCT
-    }
-#pragma unroll
-    for (int b = 0; b < UB; ++b)
-#pragma unroll
-      for (int m = 0; m < SM; ++m) {
-        const float keep = was_reset[m] ? 0.f : 1.f;
-        carry[b][m].x = (acc[b][m][0] + carry[b][m].x) * keep;
-        carry[b][m].y = (acc[b][m][1] + carry[b][m].y) * keep;
-        carry[b][m].z = (acc[b][m][2] + carry[b][m].z) * keep;
-        carry[b][m].w = (acc[b][m][3] + carry[b][m].w) * keep;
       }
-    lds_barrier();  // the tile has been read
+#pragma unroll
+      for (int b = 0; b < UB; ++b)
+#pragma unroll
+        for (int m = 0; m < SM; ++m) {
+          carry[b][m].x += acc[b][m][0];
+          carry[b][m].y += acc[b][m][1];
+          carry[b][m].z += acc[b][m][2];
+          carry[b][m].w += acc[b][m][3];
+        }
+      lds_barrier();  // the tile has been read
+    }
   }
 }
 
@@ -623,17 +684,20 @@ __global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_ste
   }
 }
 
-// Sequences per workgroup: 16 while that leaves compute units idle, 32 (the same weights for twice the work) beyond.  The
-// line is the same where the weights are streamed and the workgroups share the L2: 128 steps of 2100 sequences, 256 units,
-// backward: 2.4 ms in 132 workgroups of 16, 3.2 ms in 66 of 32.
+// Sequences per workgroup without runs: 16 while that leaves compute units idle, 32 (the same weights for twice the work) beyond.
 inline bool gru_seq_tiles16(int64_t S1) { return S1 <= 256 * 16; }
+// Workgroups for runs of S steps in all: as many as are resident at once (256 registers, eight wavefronts a compute unit).  16 sequences each for any
+// number of them: with 32 a minibatch's two directions take 0.30 + 0.34 ms where they take 0.17 + 0.18 (128 units, 98 304 steps), 1.02 + 1.20 where
+// 1.00 + 1.09 (128 units, 1 048 576 steps) and 1.73 + 2.17 where 1.28 + 1.50 (256 units, 262 144 steps).
+inline dim3 gru_run_grid(int64_t S, int waves) { return dim3((unsigned)std::min<int64_t>((S + 15) / 16, 256 * std::max(1, 8 / waves))); }
 
-template <int KS>
+template <int KS, bool SEG>
 inline void launch_gru_fwd_ks(const GruFwdArgs& a, hipStream_t s) {
   constexpr bool RES = KS <= 4;
-  const dim3 block(RES ? 128 * KS : 64 * KS);
-  if (gru_seq_tiles16(a.S1)) hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 1, RES>), dim3((unsigned)((a.S1 + 15) / 16)), block, 0, s, a);
-  else hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 2, RES>), dim3((unsigned)((a.S1 + 31) / 32)), block, 0, s, a);
+  constexpr int WAVES = RES ? 2 * KS : KS;
+  if constexpr (SEG) hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 1, RES, true>), gru_run_grid(a.T * a.S1, WAVES), dim3(64 * WAVES), 0, s, a);
+  else if (gru_seq_tiles16(a.S1)) hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 1, RES, false>), dim3((unsigned)((a.S1 + 15) / 16)), dim3(64 * WAVES), 0, s, a);
+  else hipLaunchKernelGGL((gru_seq_fwd_kernel<KS, 2, RES, false>), dim3((unsigned)((a.S1 + 31) / 32)), dim3(64 * WAVES), 0, s, a);
 }
 template <int KS>
 inline void launch_gru_actor_ks(const GruActorArgs& a, hipStream_t s) {
@@ -644,9 +708,8 @@ inline void launch_gru_actor_ks(const GruActorArgs& a, hipStream_t s) {
 template <int KS, int NOUT>
 inline void launch_gru_bwd_ks(const GruBwdArgs& a, hipStream_t s) {
   constexpr bool RES = KS <= 4;
-  const dim3 block(RES ? 128 * KS : 64 * KS);
-  if (gru_seq_tiles16(a.S1)) hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, NOUT>), dim3((unsigned)((a.S1 + 15) / 16)), block, 0, s, a);
-  else hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 2, RES, NOUT>), dim3((unsigned)((a.S1 + 31) / 32)), block, 0, s, a);
+  constexpr int WAVES = RES ? 2 * KS : KS;
+  hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, NOUT>), gru_run_grid(a.T * a.S1, WAVES), dim3(64 * WAVES), 0, s, a);
 }
 
 }  // namespace marl

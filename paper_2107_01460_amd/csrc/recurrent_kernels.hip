@@ -153,19 +153,92 @@ __global__ void __launch_bounds__(256) gru_backward_kernel(const float* __restri
   dhprev[i] = dh * z;
 }
 
-// Index arrays of a minibatch of sequences: row r = t * J + j is trajectory row t * N + envs[j]; reset[r] = the step before t
+// Index arrays of the minibatches of sequences of an update, blockIdx.y-th minibatch: row r = t * J + j is trajectory row t * N + envs[j]; reset[r] = the step before t
 // ended the episode of that environment (never at t = 0); hrows[r] = the state row that step t starts from, r, or the row of
-// zeros behind the T + 1 slabs.
-__global__ void seq_index_kernel(const int32_t* __restrict__ envs, const uint8_t* __restrict__ done, int J, int N, int T,
-                                 int32_t* __restrict__ rows, uint8_t* __restrict__ reset, int32_t* __restrict__ hrows) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= (int64_t)T * J) return;
-  const int t = (int)(r / J), j = (int)(r - (int64_t)t * J);
-  const int env = envs[j];
-  const bool z = t > 0 && done[(int64_t)(t - 1) * N + env];
-  rows[r] = t * N + env;
-  reset[r] = z;
-  hrows[r] = z ? (T + 1) * J : (int32_t)r;
+// zeros behind the T + 1 slabs.  And its runs (SeqRuns), the longest first, in no order among those of one length (a run's results do not
+// depend on which others it shares a workgroup with): the first pass counts them by length, the second one places them.
+// One thread per sequence, sixteen steps requested at a time; a workgroup's counts meet in LDS, so that a few atomics per workgroup remain.
+constexpr int kRunBins = 1024;  // lengths from here on count as one
+constexpr int kRunHead = 16;    // ints before a minibatch's bins: number of runs, groups taken by each of its four kernels
+struct SeqPlanArgs {
+  const int32_t* envs;  // [E][N], nullable: the identity
+  const uint8_t* done;  // [T][N]
+  int J, N, T, M;       // M minibatches per epoch
+  int32_t *rows, *hrows;  // [E * M][T * J]
+  uint8_t* reset;
+  int2* runs;
+  int32_t* head;        // [E * M][run_head_ints(T)], zero before the first pass
+  int q0;               // the first of this launch
+};
+__host__ __device__ inline int run_bins(int T) { return T < kRunBins ? T : kRunBins; }
+__host__ __device__ inline int64_t run_head_ints(int T) { return (kRunHead + 2 * (int64_t)run_bins(T) + 3) / 4 * 4; }
+template <bool PLACE>
+__global__ void __launch_bounds__(256) seq_plan_kernel(SeqPlanArgs a) {
+  __shared__ int32_t bin[kRunBins], at[kRunBins];
+  const int tid = threadIdx.x, j = blockIdx.x * 256 + tid, q = a.q0 + blockIdx.y, B = run_bins(a.T);
+  const int64_t TJ = (int64_t)a.T * a.J;
+  int32_t* const head = a.head + q * run_head_ints(a.T);
+  int32_t *const count = head + kRunHead, *const taken = count + B;  // by length, B first
+  for (int b = tid; b < B; b += 256) bin[b] = 0;
+  __syncthreads();
+  const int env = j >= a.J ? 0 : a.envs != nullptr ? a.envs[(int64_t)(q / a.M) * a.N + (int64_t)(q % a.M) * a.J + j] : q % a.M * a.J + j;
+  // visits the runs of this thread's sequence
+  auto runs = [&](auto&& run) {
+    if (j >= a.J) return;
+    int begin = 0;
+    for (int t0 = 0; t0 < a.T; t0 += 16) {
+      bool z[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) z[u] = t0 + u > 0 && a.done[(int64_t)(min(t0 + u, a.T) - 1) * a.N + env];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const int t = t0 + u;
+        if (t < a.T) {
+          if (!PLACE) {
+            const int64_t r = (int64_t)t * a.J + j;
+            a.rows[q * TJ + r] = t * a.N + env;
+            a.reset[q * TJ + r] = z[u];
+            a.hrows[q * TJ + r] = z[u] ? (a.T + 1) * a.J : (int32_t)r;
+          }
+          if (z[u]) {
+            run(begin, t - begin);
+            begin = t;
+          }
+        }
+      }
+    }
+    run(begin, a.T - begin);
+  };
+  runs([&](int, int len) { atomicAdd(&bin[B - min(len, B)], 1); });
+  __syncthreads();
+  if (!PLACE) {
+    for (int b = tid; b < B; b += 256)
+      if (bin[b] > 0) atomicAdd(&count[b], bin[b]);
+    return;
+  }
+  // where this workgroup's runs of each length begin: behind the longer ones and those other workgroups have placed
+  if (tid == 0) {
+    int sum = 0;
+    for (int b = 0; b < B; ++b) {
+      at[b] = sum;
+      sum += count[b];
+    }
+    if (blockIdx.x == 0) head[0] = sum;
+  }
+  __syncthreads();
+  for (int b = tid; b < B; b += 256)
+    if (bin[b] > 0) at[b] += atomicAdd(&taken[b], bin[b]);
+  __syncthreads();
+  runs([&](int begin, int len) { a.runs[q * TJ + atomicAdd(&at[B - min(len, B)], 1)] = make_int2(begin * a.J + j, len); });
+}
+
+void launch_seq_plan(SeqPlanArgs a, int minibatches, hipStream_t s) {
+  constexpr int kMost = 32768;  // of one launch
+  for (a.q0 = 0; a.q0 < minibatches; a.q0 += kMost) {
+    const dim3 grid((unsigned)((a.J + 255) / 256), (unsigned)std::min(kMost, minibatches - a.q0));
+    hipLaunchKernelGGL(seq_plan_kernel<false>, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(seq_plan_kernel<true>, grid, dim3(256), 0, s, a);
+  }
 }
 
 // dst[(j * per + a)][u] = h0[(envs[j] * per + a)][u]; zeros[0 .. per * H - 1] = 0
@@ -220,19 +293,20 @@ void hidden_gates(const float* hprev, int64_t S, int H, const float* eff, const 
   launch_gemm<GEMM_NN, EPI_STORE>(g, s);
 }
 
-// All steps of a, forward.  GhT [S1][3H] and hm [S1][H] are used above 256 units only.
+// All steps of a, forward; SEG: run by run of a.runs.  GhT [S1][3H] and hm [S1][H] are used above 256 units only.
+template <bool SEG>
 void gru_forward(const GruFwdArgs& a, int H, const float* eff, const RecOffsets& o, float* GhT, float* hm, hipStream_t s) {
   if (gru_seq_supported(H)) {
     TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)a.T * (double)a.S1 * H * 3.0 * H, s);
     switch (H / 32) {
-      case 1: return launch_gru_fwd_ks<1>(a, s);
-      case 2: return launch_gru_fwd_ks<2>(a, s);
-      case 3: return launch_gru_fwd_ks<3>(a, s);
-      case 4: return launch_gru_fwd_ks<4>(a, s);
-      case 5: return launch_gru_fwd_ks<5>(a, s);
-      case 6: return launch_gru_fwd_ks<6>(a, s);
-      case 7: return launch_gru_fwd_ks<7>(a, s);
-      default: return launch_gru_fwd_ks<8>(a, s);
+      case 1: return launch_gru_fwd_ks<1, SEG>(a, s);
+      case 2: return launch_gru_fwd_ks<2, SEG>(a, s);
+      case 3: return launch_gru_fwd_ks<3, SEG>(a, s);
+      case 4: return launch_gru_fwd_ks<4, SEG>(a, s);
+      case 5: return launch_gru_fwd_ks<5, SEG>(a, s);
+      case 6: return launch_gru_fwd_ks<6, SEG>(a, s);
+      case 7: return launch_gru_fwd_ks<7, SEG>(a, s);
+      default: return launch_gru_fwd_ks<8, SEG>(a, s);
     }
   }
   for (int t = 0; t < a.T; ++t) {
@@ -400,7 +474,7 @@ int32_t launch_rollout_recurrent(const marl_config& c, marl_env_state st, const 
       embed_and_input_gates(RowSrc{obs_t, d.D, nullptr, 1, NA}, NA, d.D, d.Ha, eff, oa, w.E, w.Gi, s);
       GruFwdArgs g{};
       g.Gi = w.Gi; g.bi = eff + oa.bi; g.bh = eff + oa.bh; g.h_first = h_in; g.hs = w.ha; g.reset0 = ended; g.per = d.A; g.S1 = NA; g.T = 1;
-      gru_forward(g, d.Ha, eff, oa, w.Gh, w.hm, s);
+      gru_forward<false>(g, d.Ha, eff, oa, w.Gh, w.hm, s);
       launch_actor_head_rollout(w.ha, NA, d.Ha, eff + oa.W3, eff + oa.b3, logits, &a, s);
     }
     rc = launch_env_step(c, st, a.action, tr.obs + (int64_t)(t + 1) * slab, tr.reward + (int64_t)t * NA,
@@ -421,7 +495,7 @@ int32_t launch_rollout_recurrent(const marl_config& c, marl_env_state st, const 
     g.h_first = t0 > 0 ? w.Hs + (n_prev - 1) * Sc * d.Hc : rec.hc0; g.hs = w.Hs;
     g.reset0 = t0 > 0 ? tr.done + (t0 - 1) * d.N : (const uint8_t*)nullptr; g.reset = tr.done + t0 * d.N;
     g.per = per_c; g.S1 = Sc; g.T = (int)n;
-    gru_forward(g, d.Hc, eff, oc, w.Gh, w.hm, s);
+    gru_forward<false>(g, d.Hc, eff, oc, w.Gh, w.hm, s);
     const int64_t nv = std::min<int64_t>(n, d.T - t0);  // steps with a value of their own
     if (nv > 0) launch_critic_head_rollout(w.Hs, nv * Sc, d.Hc, eff + oc.W3, eff + oc.b3, tr.value + t0 * NA, d.central ? d.A : 1, s);
     if (nv < n) launch_critic_head_rollout(w.Hs + nv * Sc * d.Hc, Sc, d.Hc, eff + oc.W3, eff + oc.b3, tr.last_value, d.central ? d.A : 1, s);
@@ -444,8 +518,7 @@ struct RecNetWs {
 struct RecUpdateWs {
   float *eff, *grad;
   Scalars* sc;
-  int32_t *ident, *rows, *hrows;
-  uint8_t* reset;
+  SeqPlanArgs plan;  // of all minibatches
   RecNetWs net[2];  // actor, critic: a set each, so that the two networks can run side by side
 };
 
@@ -465,10 +538,14 @@ RecUpdateWs carve_rec_update(const marl_config& c, void* ws, int64_t* total) {
   w.eff = (float*)take(rec_param_map(d).total * 4);
   w.grad = (float*)take(d.P * 4);
   w.sc = (Scalars*)take(sizeof(Scalars));
-  w.ident = (int32_t*)take((int64_t)d.N * 4);
-  w.rows = (int32_t*)take(TJ * 4);
-  w.hrows = (int32_t*)take(TJ * 4);
-  w.reset = (uint8_t*)take(TJ);
+  w.plan = SeqPlanArgs{};
+  w.plan.J = (int)J; w.plan.N = d.N; w.plan.T = d.T; w.plan.M = c.n_minibatches;
+  const int64_t EM = (int64_t)c.n_epochs * c.n_minibatches;
+  w.plan.rows = (int32_t*)take(EM * TJ * 4);
+  w.plan.hrows = (int32_t*)take(EM * TJ * 4);
+  w.plan.reset = (uint8_t*)take(EM * TJ);
+  w.plan.runs = (int2*)take(EM * TJ * 8);
+  w.plan.head = (int32_t*)take(EM * run_head_ints(d.T) * 4);
   for (int k = 0; k < 2; ++k) {
     const int64_t SH = k == 0 ? Sa * d.Ha : Sc * d.Hc, S1H = k == 0 ? S1a * d.Ha : S1c * d.Hc;
     const int H = k == 0 ? d.Ha : d.Hc;
@@ -495,20 +572,22 @@ template <int NOUT, class LossFn>
 int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din, int H, const float* h0,
                             const int32_t* envs, const float* eff, const RecOffsets& o, const float* wh_fwd,
                             const float* wh_bwd, float* grad, const RecOffsets& go, const LossFn& fn, const RecNetWs& w,
-                            const uint8_t* reset, const int32_t* hrows, Scalars* sc, hipStream_t s) {
+                            const uint8_t* reset, const int32_t* hrows, const SeqRuns& runs, Scalars* sc, hipStream_t s) {
   const int64_t S1 = J * per, S = (int64_t)T * S1;
   hipLaunchKernelGGL(gather_hidden_kernel, dim3(blocks_for(S1 * H)), dim3(256), 0, s, h0, envs, (int)J, per, H, w.Hs, w.Hs + (S + S1) * H);
   embed_and_input_gates(X, S, Din, H, eff, o, w.E, w.G, s);
   GruFwdArgs f{};
   f.Gi = w.G; f.W = reinterpret_cast<const bf16_t*>(wh_fwd); f.bi = eff + o.bi; f.bh = eff + o.bh;
   f.h_first = w.Hs; f.hs = w.Hs + S1 * H; f.rec = w.R; f.reset = reset + J; f.per = per; f.S1 = S1; f.T = T;
-  gru_forward(f, H, eff, o, w.GhT, w.hm, s);
+  f.runs = runs;
+  gru_forward<true>(f, H, eff, o, w.GhT, w.hm, s);
   // output layer, loss, dL/dout, W3 / b3 gradient over all steps
   const int32_t rc = launch_loss_head<NOUT, false>(w.Hs + S1 * H, S, H, eff + o.W3, eff + o.b3, fn, w.dl, grad + go.W3, w.partial, sc, s);
   if (rc != MARL_OK) return rc;
   GruBwdArgs bw{};
   bw.W = reinterpret_cast<const bf16_t*>(wh_bwd); bw.W3 = eff + o.W3; bw.dl = w.dl; bw.rec = w.R; bw.hs = w.Hs; bw.reset = reset + J;
   bw.per = per; bw.S1 = S1; bw.T = T;
+  bw.runs = SeqRuns{runs.env, runs.count, runs.next + 1};
   gru_backward<NOUT>(bw, H, eff, o, w.dHp, s);
   const float* const dgh = w.R;      // [S][4H], columns n, r, z
   const float* const dgi = w.R + H;  // [S][4H], columns r, z, n
@@ -539,20 +618,28 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
   const Dims d = dims_of(c);
   const RecUpdateWs w = carve_rec_update(c, workspace, nullptr);
   const int64_t J = d.N / c.n_minibatches, TJ = (int64_t)d.T * J;
-  if (perm == nullptr) hipLaunchKernelGGL(iota_kernel, dim3(blocks_for(d.N)), dim3(256), 0, s, w.ident, (int64_t)d.N);
   const RecOffsets ga = rec_offsets(0, d.D, d.Ha, kActions), gc = rec_offsets(d.Pa, d.Dc, d.Hc, 1);
   const RecParamMap pm = rec_param_map(d);
   const RecOffsets oa = rec_padded(pm, 0), oc = rec_padded(pm, 1);
   const SideStream* const side = side_stream();
+  const int EM = c.n_epochs * c.n_minibatches;
+  SeqPlanArgs plan = w.plan;
+  plan.envs = perm;
+  plan.done = tr.done;
   int64_t k = adam_step0;
   for (int e = 0; e < c.n_epochs; ++e) {
     for (int mb = 0; mb < c.n_minibatches; ++mb) {
-      const int32_t* envs = (perm ? perm + (int64_t)e * d.N : w.ident) + (int64_t)mb * J;
+      const int q = e * c.n_minibatches + mb;
+      int32_t *const rows = w.plan.rows + q * TJ, *const hrows = w.plan.hrows + q * TJ, *const head = w.plan.head + q * run_head_ints(d.T);
+      const uint8_t* const reset = w.plan.reset + q * TJ;
+      const SeqRuns runs_a{w.plan.runs + q * TJ, head, head + 4}, runs_c{w.plan.runs + q * TJ, head, head + 8};
       const float* eff = stage_params(d, params, w.eff, s);
-      hipLaunchKernelGGL(zero_step_kernel, dim3(blocks_for(d.P)), dim3(256), 0, s, w.grad, d.P, w.sc, 1, (double*)nullptr, 0);
-      hipLaunchKernelGGL(seq_index_kernel, dim3(blocks_for(TJ)), dim3(256), 0, s, envs, tr.done, (int)J, d.N, d.T, w.rows, w.reset, w.hrows);
+      const bool first = q == 0;  // clears the heads of all minibatches' plans too
+      hipLaunchKernelGGL(zero_step_kernel, dim3(blocks_for(d.P)), dim3(256), 0, s, w.grad, d.P, w.sc, 1, first ? (double*)w.plan.head : (double*)nullptr,
+                         first ? (int)(EM * run_head_ints(d.T) / 2) : 0);
+      if (first) launch_seq_plan(plan, EM, s);
       LossCommon lc{};
-      lc.rows = w.rows; lc.A = d.A; lc.ad = make_small_div(d.A); lc.rows_mb = TJ; lc.inv_B = (float)(1.0 / (double)(TJ * d.A));
+      lc.rows = rows; lc.A = d.A; lc.ad = make_small_div(d.A); lc.rows_mb = TJ; lc.inv_B = (float)(1.0 / (double)(TJ * d.A));
       lc.sc = w.sc; lc.adv_stats = &w.sc->adv_sum; lc.normalize = c.normalize_adv; lc.clip_eps = c.clip_eps; lc.ent_coef = c.ent_coef;
       lc.vf_coef = c.vf_coef; lc.clip_value = c.clip_value;
       if (c.normalize_adv) {
@@ -568,15 +655,15 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
       int32_t rc_a, rc_c;
       {
         ActorLoss fn{lc, tr.action, tr.logp, tr.adv};
-        rc_a = train_net_recurrent<kActions>(RowSrc{tr.obs, d.D, w.rows, d.A, TJ * d.A}, d.T, J, d.A, d.D, d.Ha, rec.ha0, envs,
-                                             eff, oa, eff + pm.wh_fwd[0], eff + pm.wh_bwd[0], w.grad, ga, fn, w.net[0], w.reset,
-                                             w.hrows, w.sc, s);
+        rc_a = train_net_recurrent<kActions>(RowSrc{tr.obs, d.D, rows, d.A, TJ * d.A}, d.T, J, d.A, d.D, d.Ha, rec.ha0, rows,
+                                             eff, oa, eff + pm.wh_fwd[0], eff + pm.wh_bwd[0], w.grad, ga, fn, w.net[0], reset,
+                                             hrows, runs_a, w.sc, s);
       }
       {
         CriticLoss fn{lc, tr.ret, tr.value, d.central ? d.A : 1};
         const int per = d.central ? 1 : d.A;
-        rc_c = train_net_recurrent<1>(RowSrc{tr.obs, d.Dc, w.rows, per, TJ * per}, d.T, J, per, d.Dc, d.Hc, rec.hc0, envs, eff,
-                                      oc, eff + pm.wh_fwd[1], eff + pm.wh_bwd[1], w.grad, gc, fn, w.net[1], w.reset, w.hrows, w.sc, s2);
+        rc_c = train_net_recurrent<1>(RowSrc{tr.obs, d.Dc, rows, per, TJ * per}, d.T, J, per, d.Dc, d.Hc, rec.hc0, rows, eff,
+                                      oc, eff + pm.wh_fwd[1], eff + pm.wh_bwd[1], w.grad, gc, fn, w.net[1], reset, hrows, runs_c, w.sc, s2);
       }
       if (s2 != s) {  // join also after an error, so that the caller's stream never runs ahead of work still queued beside it
         if (hipEventRecord(side->join, s2) != hipSuccess || hipStreamWaitEvent(s, side->join, 0) != hipSuccess) {

@@ -301,3 +301,33 @@ def test_recurrent_other_widths(M, orc, ha, hc, n_envs, T):
     st = stats.cpu().numpy()[0]
     for i in (0, 1, 2, 5, 6):
         assert abs(st[i] - ostats[0, i]) < tol * max(abs(ostats[0, i]), 1e-2), (i, st[i], ostats[0, i])
+
+
+# The runs between episodes' beginnings that the update goes through: one-step runs, none but whole sequences, runs of many lengths, more
+# sequences than a workgroup of the plan has threads, runs beyond the lengths that are told apart, and rollouts of one step.
+@pytest.mark.parametrize("n_envs,T,density,central,mb,width", [
+    (42, 11, 1.0, 0, 1, 64), (42, 11, 0.0, 1, 1, 64), (36, 33, 0.1, 0, 2, 128), (600, 5, 0.3, 1, 2, 64), (600, 1, 0.5, 0, 1, 64),
+    (2, 1100, 0.002, 1, 1, 64), (34, 40, 0.15, 0, 2, 160)])
+def test_recurrent_runs(M, orc, n_envs, T, density, central, mb, width):
+    from gpu_util import load_traj
+    cfg = dict(W.CONFIGS[0], n_envs=n_envs, rollout_len=T, actor_hidden=width, critic_hidden=width, episode_cap=50, n_minibatches=mb,
+               n_epochs=1, recurrent=1, max_grad_norm=0.0, lr=1e-30, central_critic=central)
+    print("case", n_envs, T, density, central, mb, width, flush=True)
+    params, _, otr, orec = oracle_rollout(orc, cfg)
+    rng = np.random.default_rng(5)
+    otr.done[:] = rng.random(otr.done.shape) < density  # any flags: the update takes the trajectory as it is
+    perm = W.make_env_perm(cfg, seed=3)
+    po, mo, vo = params.copy(), np.zeros_like(params), np.zeros_like(params)
+    ostats, ograd = orc.rec_ppo_update(cfg, otr, orec, po, mo, vo, adam_step0=0, perm=perm)
+    gtr, grec = load_traj(M, cfg, otr), load_rec(M, cfg, orec)
+    ws = M.alloc_workspace(M.query_sizes(cfg).update_workspace_bytes)
+    gp, gm, gv = dev(params), torch.zeros(params.size, device="cuda"), torch.zeros(params.size, device="cuda")
+    stats, gdump = torch.zeros((mb, 8), device="cuda"), torch.zeros(params.size, device="cuda")
+    M.ppo_update_recurrent(cfg, gtr, grec, gp, gm, gv, 0, dev(perm), stats, gdump, ws)
+    torch.cuda.synchronize()
+    g = gdump.cpu().numpy()
+    off = 0
+    for name, shape in W.param_layout(cfg):
+        n = int(np.prod(shape))
+        assert err(g[off:off + n], ograd[off:off + n], cfg) < REL_TOL[0], name
+        off += n
