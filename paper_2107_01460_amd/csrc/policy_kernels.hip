@@ -403,7 +403,9 @@ struct EvalWsView {
   float *obs, *logits, *reward;
   int32_t* action;
   uint8_t* done;
+  EvalEpisodes eps;  // slots: as many as there is room for
 };
+constexpr int kEvalSlots = 16384;  // episodes of all environments together that can be played by themselves (0.6 MB)
 
 EvalWsView carve_eval_ws(const marl_config& c, void* ws, int64_t* total) {
   const Dims d = dims_of(c);
@@ -421,6 +423,10 @@ EvalWsView carve_eval_ws(const marl_config& c, void* ws, int64_t* total) {
   v.reward = (float*)take(d.NA * 4);
   v.action = (int32_t*)take(d.NA * 4);
   v.done = (uint8_t*)take(d.N);
+  v.eps = EvalEpisodes{};
+  v.eps.slots = use_fused_rollout(c) ? kEvalSlots / d.N : 0;
+  v.eps.len = (int32_t*)take((int64_t)v.eps.slots * d.N * 4);
+  v.eps.rew = (float*)take((int64_t)v.eps.slots * d.N * kEpisodeRewards * 4);
   if (total) *total = off;
   return v;
 }
@@ -440,11 +446,21 @@ int32_t launch_evaluate(const marl_config& c, marl_env_state st, const float* pa
   const RolloutWsView w = carve_rollout_ws(c, d.N, e.rollout_ws, nullptr);
   const float* eff = effective_params(c, params, w.eff_params, s, USE_FORWARD);
   const int64_t steps = (int64_t)n_episodes * c.episode_cap;
-  if (use_fused_rollout(c)) {  // the whole block in one launch, statistics in registers
+  if (use_fused_rollout(c)) {  // the whole block in one launch, or in two (rollout_eval.h), statistics in registers
     RolloutArgs a = rollout_fused_args(c, st, eff);
     a.T = (int)steps;
     a.ev = out;
     a.n_episodes = n_episodes;
+    // rows beside one another as long as all of them are resident: beyond, they would only follow one another
+    const int slots = std::min(n_episodes, e.eps.slots), copies = std::min(slots, rollout_eval_places(d.Ha, d.A, d.F, d.V) / d.N);
+    if (copies > 1) {
+      a.eps = e.eps;
+      a.eps.slots = slots;
+      a.eps.copies = copies;
+      const int32_t rc = launch_rollout_fused(c, true, a, s);
+      if (rc != MARL_OK) return rc;
+      a.eps.copies = 0;
+    }
     return launch_rollout_fused(c, true, a, s);
   }
   const unsigned nb_env = (unsigned)((d.N + 255) / 256), nb_s = (unsigned)((d.NA + 255) / 256);

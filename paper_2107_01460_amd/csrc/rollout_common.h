@@ -7,6 +7,15 @@
 
 namespace marl {
 
+// Episodes of an evaluation block that were played by themselves (rollout_eval.h): of every environment's first `slots` episodes the
+// length (and above it, from bit 24 on, the number of steps with a reward) and those rewards in the order of time.
+constexpr int kEpisodeRewards = 8;
+struct EvalEpisodes {
+  int slots, copies;  // copies: rows per environment, row j plays episodes j, j + copies, ...; 0 in the call that plays what is left
+  int32_t* len;       // [slots][N]
+  float* rew;         // [slots][N][kEpisodeRewards]
+};
+
 struct RolloutArgs {
   EnvParams p;
   marl_env_state st;
@@ -28,6 +37,7 @@ struct RolloutArgs {
   // evaluation block
   marl_eval_stats ev;
   int n_episodes;
+  EvalEpisodes eps;
 };
 
 // Lane l < BM of ONE wavefront is agent l % A of env env0 + l / A.  Which wavefront it is rotates with the workgroup index, so
@@ -37,17 +47,18 @@ struct RolloutEnvs {
   static_assert(BM <= 64, "the env lanes are lanes of one wavefront");
   const EnvParams& p;
   const marl_env_state& st;
-  int lane, A, le, ai, samples_here, other;
+  int lane, A, le, ai, samples_here, other, copy = 0;
   int64_t env0, n, s_glob;  // s_glob: this env lane's sample index
   bool is_env_wave, active;
   uint32_t ag[CA], fd[CA];
   int t_ep = 0;
   uint32_t episode = 0;
 
-  __device__ __forceinline__ RolloutEnvs(const RolloutArgs& a, int wave, int lane_) : p(a.p), st(a.st), lane(lane_), A(a.p.A) {
+  // copies: how often every environment appears, as rows copy * N + n
+  __device__ __forceinline__ RolloutEnvs(const RolloutArgs& a, int wave, int lane_, int copies = 1) : p(a.p), st(a.st), lane(lane_), A(a.p.A) {
     const int epw = BM / A;  // envs of this workgroup
     env0 = (int64_t)blockIdx.x * epw;
-    const int envs_here = (int)min((int64_t)epw, (int64_t)p.N - env0);
+    const int envs_here = (int)min((int64_t)epw, (int64_t)p.N * copies - env0);
     samples_here = envs_here * A;
     const int env_wave = blockIdx.x & 3;
     is_env_wave = wave == env_wave;
@@ -56,6 +67,10 @@ struct RolloutEnvs {
     ai = lane - le * A;
     active = is_env_wave && lane < samples_here;
     n = env0 + le;
+    if (copies > 1) {
+      copy = (int)((uint32_t)n / (uint32_t)p.N);
+      n -= (int64_t)copy * p.N;
+    }
     s_glob = env0 * A + lane;
   }
   __device__ __forceinline__ void load() {
@@ -64,12 +79,19 @@ struct RolloutEnvs {
     t_ep = st.t_in_ep[nn];
     episode = st.episode_id[nn];
   }
+  // Start of episode e (all lanes of an env together).
+  __device__ __forceinline__ void restart(uint32_t e) {
+    episode = e;
+    t_ep = 0;
+    if (KIND == 0) reset_regs<CA, CA, true>(ag, fd, p, (uint32_t)n, e, ai);
+    else wh_reset_regs<CA, CA, true>(ag, fd, p, (uint32_t)n, e, ai);
+  }
   template <typename T>
   __device__ __forceinline__ void paint(T* window) const {
     if (KIND == 0) forage_paint<V, CA, CA>(window, ag, fd, ai, p);
     else wh_paint<V, CA, CA>(window, ag, fd, ai, p);
   }
-  // The whole wavefront runs this, so that the cross-lane reads find their source lanes running.
+  // All lanes of an env run this together, so that the cross-lane reads find their source lanes running.
   __device__ __forceinline__ void step(int my_act, float& rew, bool& dn) {
     int act[CA];
 #pragma unroll

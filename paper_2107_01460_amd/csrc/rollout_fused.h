@@ -1,5 +1,7 @@
 // Host-side dispatch of the rollout (rollout_train.h) and evaluation (rollout_eval.h) kernels.
 #pragma once
+#include <algorithm>
+
 #include "rollout_eval.h"
 #include "rollout_train.h"
 
@@ -8,16 +10,20 @@ namespace marl {
 // Networks the kernels are instantiated for: hidden width 64 (64-sample tiles) or 128 (32-sample tiles).
 inline bool rollout_fused_supported(int H, int A) { return (H == 64 || H == 128) && A <= 8; }
 
+// Workgroups of an evaluation block per CU, and as many as are resident at once.
+constexpr int rollout_eval_occupancy(int capacity, int V) { return capacity <= 4 && V <= 5 ? 2 : 1; }
+inline int rollout_eval_places(int H, int A, int F, int V) { return 256 * rollout_eval_occupancy(std::max(A, F), V) * ((H == 64 ? 64 : 32) / A); }
+
 template <int H, int BM, int V, int CA, int KIND, bool EVAL>
 inline int32_t launch_rollout_fused_inst(const RolloutArgs& a, hipStream_t s) {
   const int epw = BM / a.p.A;
-  const unsigned grid = (unsigned)((a.p.N + epw - 1) / epw);
+  const unsigned grid = (unsigned)(((int64_t)a.p.N * std::max(a.eps.copies, 1) + epw - 1) / epw);
   constexpr int D = 3 * V * V;
   void (*kern)(RolloutArgs);
   size_t bytes;
   if constexpr (EVAL) {
-    kern = rollout_eval_kernel<H, BM, V, CA, KIND, (CA <= 4 && V <= 5) ? 2 : 1>;
-    bytes = 2 * (size_t)BM * (2 * rollout_eval_px(D) + 3 * (H + 8)) + sizeof(float) * ((H / 32) * kActions * BM + H * kActions + 2 * H);
+    kern = rollout_eval_kernel<H, BM, V, CA, KIND, rollout_eval_occupancy(CA, V)>;
+    bytes = 2 * (size_t)BM * (2 * rollout_eval_px(D) + 3 * (H + 8)) + sizeof(float) * ((H / 32) * kActions * BM + H * kActions + 2 * H + 4);
   } else {
     kern = rollout_train_kernel<H, BM, V, CA, KIND, ((H == 64 && CA <= 2) || (CA <= 4 && V <= 5)) ? 3 : 1>;
     bytes = sizeof(float) * (2 * (size_t)BM * rollout_train_px(D) + (size_t)BM * (H + 4) + 256 * kActions + H * kActions + 2 * BM * 8);

@@ -44,3 +44,34 @@ def test_evaluation_block(M, orc, kind, grid, agents, food, level, view, hidden,
     host = gs.to_host()
     for f in M.EnvState.FIELDS:
         assert np.array_equal(host[f][..., clear], getattr(os_, f)[..., clear]), f
+
+
+# Episodes played beside one another: from states in the middle of an episode; more episodes than rows of an environment are resident
+# (700 environments with 8 to a workgroup and one of those per CU); more than there is room to record (5600 environments, two of three);
+# environments whose step count is past the cap already, which play their first episode for as long as it lasts.
+@pytest.mark.parametrize("agents,view,hidden,n_envs,cap,E,past", [(2, 3, 64, 45, 7, 4, 0), (4, 7, 128, 700, 3, 5, 0), (2, 3, 64, 5600, 2, 3, 0),
+                                                                 (3, 5, 128, 40, 6, 3, 1)])
+def test_evaluation_from_the_middle(M, orc, agents, view, hidden, n_envs, cap, E, past):
+    cfg = W.scaled(W.CONFIGS[0], grid=8, n_agents=agents, n_food=2, max_level=2, view=view, n_envs=n_envs, actor_hidden=hidden,
+                   critic_hidden=hidden, episode_cap=cap, n_minibatches=1, rollout_len=1)
+    print("case", agents, view, hidden, n_envs, cap, E, past, flush=True)
+    params = W.init_params(cfg, bias_scale=0.3)
+    os_ = orc.EnvState(cfg)
+    orc.env_reset(cfg, os_)
+    rng = np.random.default_rng(3)
+    os_.t_in_ep[:] = rng.integers(0, cap, n_envs)
+    if past:
+        os_.t_in_ep[::3] = cap + rng.integers(0, 4, len(os_.t_in_ep[::3]))
+    gs, out = M.EnvState(cfg), M.EvalStats(cfg)
+    for f in M.EnvState.FIELDS:
+        getattr(gs, f).copy_(torch.from_numpy(np.ascontiguousarray(getattr(os_, f))).view(getattr(gs, f).dtype))
+    oret, olen, oeps, gap = orc.evaluate(cfg, os_, params, E)
+    M.evaluate(cfg, gs, dev(params), E, out, M.alloc_workspace(M.query_sizes(cfg).eval_workspace_bytes))
+    torch.cuda.synchronize()
+    clear = gap > 8e-4 * max(1.0, float(np.abs(params).max()))
+    assert clear.mean() > 0.6, clear.mean()
+    for got, want in ((out.ret_sum, oret), (out.len_sum, olen), (out.episodes, oeps)):
+        assert np.array_equal(got.cpu().numpy()[clear], want[clear])
+    host = gs.to_host()
+    for f in M.EnvState.FIELDS:
+        assert np.array_equal(host[f][..., clear], getattr(os_, f)[..., clear]), f
