@@ -196,6 +196,30 @@ __device__ __forceinline__ void store_env_state(const uint32_t (&ag)[CA], const 
   }
 }
 
+// The transitions run in one lane per agent, a chain of instructions that nothing covers where a wavefront holds all environments of its workgroup
+// (the rollout kernels), so they are written for few instructions: cells are compared as 16 bits, several comparisons at a time (the smallest of some
+// exclusive ors is zero where one of them is), and a distance is one sum of absolute differences of bytes.
+// In cycles of a step of ten environments of three agents (five-wide windows): the transition 3870 -> 2250; the window, with 16-byte stores and a reload of a spilled
+// address gone from among them, 2810 -> 2300.
+constexpr uint32_t kNoCell = 0xfffeu;  // no entity's, and next to none that counts
+// The cell an agent's action leads to: 16 bits, the agent's own for actions that do not move; inside: it is in the grid.
+__device__ __forceinline__ uint32_t target_cell(uint32_t agent, int action, int G, bool& inside) {
+  const int shift = (uint32_t)action < 6u ? 2 * action : 0;
+  const int dr = __builtin_amdgcn_sbfe(0x1c, shift, 2), dc = __builtin_amdgcn_sbfe(0x1c0, shift, 2);  // -1, 0, 1: rows of actions 1 and 2, columns of 3 and 4
+  const uint32_t nr = (agent & 0xffu) + dr, nc = (agent >> 8 & 0xffu) + dc;
+  inside = max(nr, nc) < (uint32_t)G;
+  return nr | nc << 8;
+}
+template <int N>
+__device__ __forceinline__ bool any_equal(const uint32_t (&cells)[N], uint32_t cell, int except = -1) {
+  uint32_t m = 0xffffffffu;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i != except) m = min(m, cells[i] ^ cell);
+  return m == 0;
+}
+__device__ __forceinline__ bool next_to(uint32_t a, uint32_t b) { return __builtin_amdgcn_sad_u8(a, b, 0u) == 1u; }
+
 // One transition of the foraging world for the lane of agent `a` of env `env`: act[] holds the actions of all agents of
 // the env, ag / fd the start-of-step entities.  Leaves the post-step (after an auto-reset: the new episode's) entities,
 // step count and episode id in place; rew = this agent's reward, dn = the env finished its episode in this step.
@@ -203,60 +227,58 @@ template <int CA, int CF>
 __device__ __forceinline__ void forage_transition(uint32_t (&ag)[CA], uint32_t (&fd)[CF], const int (&act)[CA], int a,
                                                   bool active, const EnvParams& p, uint32_t env, int& t,
                                                   uint32_t& episode, float& rew_out, bool& dn_out) {
-  // ---- targets of every agent against the start-of-step state
-  uint32_t tgt[CA];  // target cell (row | col << 8), 0xffff when the agent does not move
+  uint32_t at[CA], food[CF], load[CA];  // cells; the levels of the agents that load
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
-    const int ac = act[b];
-    const int nr = e_row(ag[b]) + (ac == 2) - (ac == 1), nc = e_col(ag[b]) + (ac == 4) - (ac == 3);
-    bool ok = b < p.A && ac >= 1 && ac <= 4 && nr >= 0 && nr < p.G && nc >= 0 && nc < p.G;
-    const uint32_t cell = (uint32_t)nr | ((uint32_t)nc << 8);
+    at[b] = ag[b] & 0xffffu;
+    load[b] = act[b] == 5 ? ag[b] >> 16 : 0u;
+  }
 #pragma unroll
-    for (int o = 0; o < CA; ++o) ok = ok && (ag[o] & 0xffffu) != cell;
+  for (int f = 0; f < CF; ++f) food[f] = fd[f] >> 16 != 0 ? fd[f] & 0xffffu : kNoCell;
+  // ---- targets of every agent against the start-of-step state (an agent that does not move finds itself in its way)
+  uint32_t tgt[CA];  // target cell (row | col << 8), 0xffff when the agent does not move
+  bool ok[CA];
 #pragma unroll
-    for (int f = 0; f < CF; ++f) ok = ok && !(e_lvl(fd[f]) != 0 && (fd[f] & 0xffffu) == cell);
-    tgt[b] = ok ? cell : 0xffffu;
+  for (int b = 0; b < CA; ++b) {
+    const uint32_t cell = target_cell(at[b], act[b], p.G, ok[b]);
+    ok[b] = ok[b] && !any_equal(at, cell) && !any_equal(food, cell);
+    tgt[b] = ok[b] ? cell : 0xffffu;
   }
   // ---- cooperative loading: summed level of the adjacent loaders of each food
   float rew = 0.f;
-  uint32_t mine = 0;
-#pragma unroll
-  for (int b = 0; b < CA; ++b) mine = (b == a) ? ag[b] : mine;
-  int my_act = 0;
-#pragma unroll
-  for (int b = 0; b < CA; ++b) my_act = (b == a) ? act[b] : my_act;
-  bool any_food = false;
+  bool any_food = false, any_got = false, got[CF];
+  uint32_t sum[CF];
 #pragma unroll
   for (int f = 0; f < CF; ++f) {
-    const int fl = e_lvl(fd[f]);
-    if (f < p.F && fl != 0) {
-      const int fr = e_row(fd[f]), fc = e_col(fd[f]);
-      int lsum = 0;
+    const uint32_t level = fd[f] >> 16;
+    sum[f] = 0;
 #pragma unroll
-      for (int b = 0; b < CA; ++b) {
-        const int dist = abs(e_row(ag[b]) - fr) + abs(e_col(ag[b]) - fc);
-        lsum += (b < p.A && act[b] == 5 && dist == 1) ? e_lvl(ag[b]) : 0;
-      }
-      if (lsum >= fl) {
-        const int mdist = abs(e_row(mine) - fr) + abs(e_col(mine) - fc);
-        if (my_act == 5 && mdist == 1) rew += __fdiv_rn((float)(fl * e_lvl(mine)), (float)lsum);
+    for (int b = 0; b < CA; ++b) sum[f] += next_to(at[b], food[f]) ? load[b] : 0u;
+    got[f] = level != 0 && sum[f] >= level;
+    any_got = any_got || got[f];
+    any_food = any_food || (level != 0 && !got[f]);
+  }
+  if (any_got) {
+    uint32_t mine = 0, my_load = 0;
+#pragma unroll
+    for (int b = 0; b < CA; ++b) {
+      mine = (b == a) ? ag[b] : mine;
+      my_load = (b == a) ? load[b] : my_load;
+    }
+#pragma unroll
+    for (int f = 0; f < CF; ++f) {
+      if (got[f]) {
+        if (my_load != 0 && next_to(mine & 0xffffu, food[f])) rew += __fdiv_rn((float)((fd[f] >> 16) * my_load), (float)sum[f]);
         fd[f] &= 0xffffu;  // collected: level 0
-      } else {
-        any_food = true;
       }
     }
   }
   // ---- movement: two or more valid movers onto one cell all stay
-  uint32_t moved[CA];
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
-    bool go = tgt[b] != 0xffffu;
-#pragma unroll
-    for (int o = 0; o < CA; ++o) go = go && (o == b || tgt[o] != tgt[b]);
-    moved[b] = go ? ((ag[b] & 0xff0000u) | tgt[b]) : ag[b];
+    const bool go = ok[b] && !any_equal(tgt, tgt[b], b);
+    ag[b] = go ? ((ag[b] & 0xff0000u) | tgt[b]) : ag[b];
   }
-#pragma unroll
-  for (int b = 0; b < CA; ++b) ag[b] = moved[b];
   // ---- termination
   t += 1;
   const bool dn = active && (!any_food || t == p.cap);
@@ -275,36 +297,77 @@ __device__ __forceinline__ void forage_transition(uint32_t (&ag)[CA], uint32_t (
 __device__ __forceinline__ void paint_cell(float& o, float v) { o = v; }
 __device__ __forceinline__ void paint_cell(bf16_t& o, float v) { o = (bf16_t)(__float_as_uint(v) >> 16); }
 
-// The lane's V x V x 3 window into w[0 .. 3 V V): walls and zeros first, then the entities that fall inside it.
-template <int V, int CA, int CF, typename T>
-__device__ __forceinline__ void forage_paint(T* w, const uint32_t (&ag)[CA], const uint32_t (&fd)[CF], int a,
-                                             const EnvParams& p) {
-  constexpr int h = (V - 1) / 2;
+// The background of a window: channel 2 of cell (y, x) is value(y, x), the other two are zero.  WIDE: w is 16-byte aligned and the elements up to the next
+// multiple of 16 bytes belong to the window's row as zeros: 16-byte stores.
+template <int V, bool WIDE, typename T, class F>
+__device__ __forceinline__ void paint_background(T* w, F value) {
+  constexpr int D = 3 * V * V, PER = 16 / (int)sizeof(T);
+  if constexpr (!WIDE) {
+#pragma unroll
+    for (int c = 0; c < V * V; ++c) {
+      paint_cell(w[3 * c], 0.f);
+      paint_cell(w[3 * c + 1], 0.f);
+      paint_cell(w[3 * c + 2], value(c / V, c % V));
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < (D + PER - 1) / PER; ++q) {
+      uint32_t word[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        word[k] = 0u;
+#pragma unroll
+        for (int j = 0; j < PER / 4; ++j) {
+          const int e = q * PER + k * (PER / 4) + j;
+          if (e < D && e % 3 == 2) {
+            const uint32_t v = __float_as_uint(value(e / 3 / V, e / 3 % V));  // its lower half is zero (paint_cell)
+            word[k] = PER == 4 || j == 1 ? v : v >> 16;                       // at most one of a word's two
+          }
+        }
+      }
+      *reinterpret_cast<uint4*>(w + q * PER) = make_uint4(word[0], word[1], word[2], word[3]);
+    }
+  }
+}
+// Position of an entity in the window whose upper left cell is (r, c); false: outside.
+template <int V>
+__device__ __forceinline__ bool window_cell(uint32_t e, int r, int c, int& i) {
+  const uint32_t y = (uint32_t)(e_row(e) - r), x = (uint32_t)(e_col(e) - c);
+  i = 3 * (int)(y * V + x);
+  return max(y, x) < (uint32_t)V;
+}
+template <int CA>
+__device__ __forceinline__ uint32_t own_agent(const uint32_t (&ag)[CA], int a) {
   uint32_t me = 0;
 #pragma unroll
   for (int b = 0; b < CA; ++b) me = (b == a) ? ag[b] : me;
-  const int r0 = e_row(me), c0 = e_col(me);
+  return me;
+}
+
+// The lane's V x V x 3 window into w[0 .. 3 V V): walls and zeros first, then the entities that fall inside it.  (Slots past A and F lie off the grid,
+// absent food has no level.)
+template <int V, int CA, int CF, bool WIDE, typename T>
+__device__ __forceinline__ void forage_paint(T* w, const uint32_t (&ag)[CA], const uint32_t (&fd)[CF], int a,
+                                             const EnvParams& p) {
+  constexpr int h = (V - 1) / 2;
+  const uint32_t me = own_agent(ag, a);
+  const int r0 = e_row(me) - h, c0 = e_col(me) - h;
+  float wr[V], wc[V];
 #pragma unroll
-  for (int dy = -h; dy <= h; ++dy)
-#pragma unroll
-    for (int dx = -h; dx <= h; ++dx) {
-      const int rr = r0 + dy, cc = c0 + dx;
-      const bool wall = rr < 0 || rr >= p.G || cc < 0 || cc >= p.G;
-      T* o = w + ((dy + h) * V + (dx + h)) * 3;
-      paint_cell(o[0], 0.f);
-      paint_cell(o[1], 0.f);
-      paint_cell(o[2], wall ? 1.f : 0.f);
-    }
+  for (int i = 0; i < V; ++i) {
+    wr[i] = (uint32_t)(r0 + i) >= (uint32_t)p.G ? 1.f : 0.f;
+    wc[i] = (uint32_t)(c0 + i) >= (uint32_t)p.G ? 1.f : 0.f;
+  }
+  paint_background<V, WIDE>(w, [&](int y, int x) { return fmaxf(wr[y], wc[x]); });
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
-    const int dy = e_row(ag[b]) - r0, dx = e_col(ag[b]) - c0;
-    if (b < p.A && dy >= -h && dy <= h && dx >= -h && dx <= h) paint_cell(w[((dy + h) * V + (dx + h)) * 3 + 0], (float)e_lvl(ag[b]));
+    int i;
+    if (window_cell<V>(ag[b], r0, c0, i)) paint_cell(w[i], (float)e_lvl(ag[b]));
   }
 #pragma unroll
   for (int f = 0; f < CF; ++f) {
-    const int dy = e_row(fd[f]) - r0, dx = e_col(fd[f]) - c0;
-    if (f < p.F && e_lvl(fd[f]) != 0 && dy >= -h && dy <= h && dx >= -h && dx <= h)
-      paint_cell(w[((dy + h) * V + (dx + h)) * 3 + 1], (float)e_lvl(fd[f]));
+    int i;
+    if (window_cell<V>(fd[f], r0, c0, i) && e_lvl(fd[f]) != 0) paint_cell(w[i + 1], (float)e_lvl(fd[f]));
   }
 }
 
@@ -367,36 +430,29 @@ __device__ __forceinline__ void wh_transition(uint32_t (&ag)[CA], uint32_t (&fd)
                                               float& rew_out, bool& dn_out) {
   const uint32_t n = env;
   // ---- targets against the start-of-step state
+  uint32_t at[CA], shelf[CF];  // cells
+#pragma unroll
+  for (int b = 0; b < CA; ++b) at[b] = ag[b] & 0xffffu;
+#pragma unroll
+  for (int f = 0; f < CF; ++f) shelf[f] = fd[f] & 0xffffu;
   uint32_t tgt[CA];  // target cell, 0xffff when the robot does not move
-  bool collided = false;
+  bool ok[CA], collided = false;
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
-    const int ac = act[b];
-    const int nr = e_row(ag[b]) + (ac == 2) - (ac == 1), nc = e_col(ag[b]) + (ac == 4) - (ac == 3);
-    bool ok = b < p.A && ac >= 1 && ac <= 4 && nr >= 0 && nr < p.G && nc >= 0 && nc < p.G;
-    const uint32_t cell = (uint32_t)nr | ((uint32_t)nc << 8);
-    bool hit = false;
-#pragma unroll
-    for (int o = 0; o < CA; ++o) hit = hit || (ag[o] & 0xffffu) == cell;
-    collided = collided || (ok && hit);
-    ok = ok && !hit;
-    if (e_lvl(ag[b]) != 0) {
-#pragma unroll
-      for (int f = 0; f < CF; ++f) ok = ok && (fd[f] & 0xffffu) != cell;
-    }
-    tgt[b] = ok ? cell : 0xffffu;
+    const uint32_t cell = target_cell(at[b], act[b], p.G, ok[b]);
+    ok[b] = ok[b] && cell != at[b];
+    const bool hit = any_equal(at, cell);
+    collided = collided || (ok[b] && hit);
+    ok[b] = ok[b] && !hit && !(e_lvl(ag[b]) != 0 && any_equal(shelf, cell));
+    tgt[b] = ok[b] ? cell : 0xffffu;
   }
   // ---- contested cells; movement, carried shelves with their robots
   uint32_t moved[CA];
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
-    bool go = tgt[b] != 0xffffu;
-    bool contested = false;
-#pragma unroll
-    for (int o = 0; o < CA; ++o) contested = contested || (o != b && tgt[o] == tgt[b]);
-    collided = collided || (go && contested);
-    go = go && !contested;
-    moved[b] = go ? ((ag[b] & 0xff0000u) | tgt[b]) : ag[b];
+    const bool contested = any_equal(tgt, tgt[b], b);
+    collided = collided || (ok[b] && contested);
+    moved[b] = ok[b] && !contested ? ((ag[b] & 0xff0000u) | tgt[b]) : ag[b];
   }
   uint32_t fd0[CF];  // start-of-step shelves, for the toggle
 #pragma unroll
@@ -481,38 +537,33 @@ __device__ __forceinline__ void wh_transition(uint32_t (&ag)[CA], uint32_t (&fd)
   dn_out = dn;
 }
 
-template <int V, int CA, int CF, typename T>
+// (The largest state among the shelves of one cell is painted: a carried shelf may stand over another one.)
+template <int V, int CA, int CF, bool WIDE, typename T>
 __device__ __forceinline__ void wh_paint(T* w, const uint32_t (&ag)[CA], const uint32_t (&fd)[CF], int a,
                                          const EnvParams& p) {
   constexpr int h = (V - 1) / 2;
-  uint32_t me = 0;
+  const uint32_t me = own_agent(ag, a);
+  const int r0 = e_row(me) - h, c0 = e_col(me) - h;
+  float wr[V], wc[V], gr[V], gc[V];  // walls 1; goals where both are 0.5
 #pragma unroll
-  for (int b = 0; b < CA; ++b) me = (b == a) ? ag[b] : me;
-  const int r0 = e_row(me), c0 = e_col(me);
-#pragma unroll
-  for (int dy = -h; dy <= h; ++dy)
-#pragma unroll
-    for (int dx = -h; dx <= h; ++dx) {
-      const int rr = r0 + dy, cc = c0 + dx;
-      const bool wall = rr < 0 || rr >= p.G || cc < 0 || cc >= p.G;
-      T* o = w + ((dy + h) * V + (dx + h)) * 3;
-      paint_cell(o[0], 0.f);
-      paint_cell(o[1], 0.f);
-      paint_cell(o[2], wall ? 1.f : (wh_goal(p.G, rr, cc) ? 0.5f : 0.f));
-    }
+  for (int i = 0; i < V; ++i) {
+    wr[i] = (uint32_t)(r0 + i) >= (uint32_t)p.G ? 1.f : 0.f;
+    wc[i] = (uint32_t)(c0 + i) >= (uint32_t)p.G ? 1.f : 0.f;
+    gr[i] = r0 + i == p.G - 1 ? 0.5f : 0.f;
+    gc[i] = c0 + i == p.G / 2 - 1 || c0 + i == p.G / 2 ? 0.5f : 0.f;
+  }
+  paint_background<V, WIDE>(w, [&](int y, int x) { return fmaxf(fmaxf(wr[y], wc[x]), fminf(gr[y], gc[x])); });
 #pragma unroll
   for (int b = 0; b < CA; ++b) {
-    const int dy = e_row(ag[b]) - r0, dx = e_col(ag[b]) - c0;
-    if (b < p.A && dy >= -h && dy <= h && dx >= -h && dx <= h)
-      paint_cell(w[((dy + h) * V + (dx + h)) * 3 + 0], e_lvl(ag[b]) != 0 ? 2.f : 1.f);
+    int i;
+    if (window_cell<V>(ag[b], r0, c0, i)) paint_cell(w[i], e_lvl(ag[b]) != 0 ? 2.f : 1.f);
   }
 #pragma unroll
   for (int f = 0; f < CF; ++f) {
-    const int dy = e_row(fd[f]) - r0, dx = e_col(fd[f]) - c0;
-    if (f < p.F && dy >= -h && dy <= h && dx >= -h && dx <= h) {
-      T* o = &w[((dy + h) * V + (dx + h)) * 3 + 1];
-      paint_cell(*o, fmaxf(load_act(o, 0), (float)e_lvl(fd[f])));
-    }
+    int i, level = e_lvl(fd[f]);
+#pragma unroll
+    for (int g = 0; g < f; ++g) level = (fd[g] & 0xffffu) == (fd[f] & 0xffffu) ? max(level, e_lvl(fd[g])) : level;
+    if (window_cell<V>(fd[f], r0, c0, i)) paint_cell(w[i + 1], (float)level);
   }
 }
 

@@ -56,7 +56,6 @@ __global__ void __launch_bounds__(64 * NW) env_step_kernel(EnvParams p, marl_env
   const int64_t wave_env0 = ((int64_t)blockIdx.x * NW + wave) * ew;
   const int64_t n = wave_env0 + le;
   const bool active = le < ew && n < p.N;
-  const int N = p.N;
 
   // ---- the env's state, in registers.  All loads are issued branch-free (clamped indices) so that they are in
   // flight together; entries past A / F and inactive lanes are masked afterwards.
@@ -88,8 +87,8 @@ __global__ void __launch_bounds__(64 * NW) env_step_kernel(EnvParams p, marl_env
 
   if (obs == nullptr) return;
   if (active) {
-    if (KIND == 0) forage_paint<V, CA, CF>(slab + lane * D, ag, fd, a, p);
-    else wh_paint<V, CA, CF>(slab + lane * D, ag, fd, a, p);
+    if (KIND == 0) forage_paint<V, CA, CF, false>(slab + lane * D, ag, fd, a, p);
+    else wh_paint<V, CA, CF, false>(slab + lane * D, ag, fd, a, p);
   }
   // the slab is private to the wavefront, whose LDS operations execute in order: only the compiler has to keep them so
   // (no workgroup barrier: a wavefront that re-seeds episodes does not hold the others back)

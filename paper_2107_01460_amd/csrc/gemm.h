@@ -189,9 +189,9 @@ __device__ __forceinline__ float tanh_f32(float x) {
 // loads: a resource descriptor in scalar registers, ONE vector register with the lane's byte offset for all of them, the
 // group's offset as a scalar (as global loads each of them got a 64-bit address register pair of its own).
 constexpr int kPhaseRing = 4;
-template <int KG>
+template <int KG, int MOST = kPhaseRing>
 struct PhaseW {
-  static constexpr int RING = KG < kPhaseRing ? KG : kPhaseRing;
+  static constexpr int RING = KG < MOST ? KG : MOST;
   bf16x8 w[RING][3];
 };
 typedef __amdgpu_buffer_rsrc_t WeightRsrc;
@@ -202,24 +202,24 @@ __device__ __forceinline__ WeightRsrc weight_rsrc(const float* p, int floats) {
 // descriptor of a split [K][H] copy
 __device__ __forceinline__ WeightRsrc split_weight_rsrc(const float* p, int K, int H) { return weight_rsrc(p, K * H * 3 / 2); }
 // lane_off: (hi * H + n) * 4 for this lane's column n
-template <int H, int KG>
-__device__ __forceinline__ void phase_w_load(PhaseW<KG>& pw, WeightRsrc B, int lane_off, int g, int kgroups) {
+template <int H, int KG, int MOST>
+__device__ __forceinline__ void phase_w_load(PhaseW<KG, MOST>& pw, WeightRsrc B, int lane_off, int g, int kgroups) {
   const int at = g < kgroups ? g : kgroups - 1;  // past the end: the last group again (never used)
 #pragma unroll
   for (int p = 0; p < 3; ++p)
-    pw.w[g % PhaseW<KG>::RING][p] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(B, lane_off * 4, (at * 3 + p) * 32 * H, 0));
+    pw.w[g % PhaseW<KG, MOST>::RING][p] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(B, lane_off * 4, (at * 3 + p) * 32 * H, 0));
 }
-template <int H, int KG>
-__device__ __forceinline__ void phase_w_request(PhaseW<KG>& pw, WeightRsrc B, int lane_off, int kgroups) {
+template <int H, int KG, int MOST>
+__device__ __forceinline__ void phase_w_request(PhaseW<KG, MOST>& pw, WeightRsrc B, int lane_off, int kgroups) {
 #pragma unroll
-  for (int g = 0; g < PhaseW<KG>::RING; ++g) phase_w_load<H>(pw, B, lane_off, g, kgroups);
+  for (int g = 0; g < PhaseW<KG, MOST>::RING; ++g) phase_w_load<H>(pw, B, lane_off, g, kgroups);
 }
 // The transposed product, weights x samples: acc += B^T A^T for this wavefront's 32 units x 32 samples, so that a lane holds
 // four times four consecutive units of one sample.  A by rows of split planes in LDS (xs points at this lane's row, + 8 * hi;
 // planes `plane` elements apart).  EXACT: one plane, the values are exact in bf16 and the lower parts' products are zero.
-template <int H, int KG, bool EXACT>
-__device__ __forceinline__ void gemm_phase_t(const bf16_t* xs, int plane, WeightRsrc B, int lane_off, int kgroups, floatx16& acc, PhaseW<KG>& pw) {
-  constexpr int RING = PhaseW<KG>::RING;
+template <int H, int KG, bool EXACT, int MOST>
+__device__ __forceinline__ void gemm_phase_t(const bf16_t* xs, int plane, WeightRsrc B, int lane_off, int kgroups, floatx16& acc, PhaseW<KG, MOST>& pw) {
+  constexpr int RING = PhaseW<KG, MOST>::RING;
 #pragma unroll
   for (int g = 0; g < KG; ++g) {
     if (g < kgroups) {  // uniform

@@ -48,7 +48,7 @@ struct RolloutEnvs {
   const EnvParams& p;
   const marl_env_state& st;
   int lane, A, le, ai, samples_here, other, copy = 0;
-  int64_t env0, n, s_glob;  // s_glob: this env lane's sample index
+  int64_t env0, n;
   bool is_env_wave, active;
   uint32_t ag[CA], fd[CA];
   int t_ep = 0;
@@ -71,7 +71,6 @@ struct RolloutEnvs {
       copy = (int)((uint32_t)n / (uint32_t)p.N);
       n -= (int64_t)copy * p.N;
     }
-    s_glob = env0 * A + lane;
   }
   __device__ __forceinline__ void load() {
     const size_t nn = active ? (size_t)n : 0;
@@ -88,8 +87,8 @@ struct RolloutEnvs {
   }
   template <typename T>
   __device__ __forceinline__ void paint(T* window) const {
-    if (KIND == 0) forage_paint<V, CA, CA>(window, ag, fd, ai, p);
-    else wh_paint<V, CA, CA>(window, ag, fd, ai, p);
+    if (KIND == 0) forage_paint<V, CA, CA, true>(window, ag, fd, ai, p);
+    else wh_paint<V, CA, CA, true>(window, ag, fd, ai, p);
   }
   // All lanes of an env run this together, so that the cross-lane reads find their source lanes running.
   __device__ __forceinline__ void step(int my_act, float& rew, bool& dn) {

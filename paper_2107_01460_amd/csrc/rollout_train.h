@@ -208,7 +208,7 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
           for (int k = 0; k < NOUT; ++k) part[k] = fmaf(hh[j], wv[j * NOUT + k], part[k]);
       }
 #pragma unroll
-      for (int k = 0; k < NOUT; ++k) red[(grp * BM + s) * NOUT + k] = part[k];
+      for (int k = 0; k < NOUT; k += 2) *reinterpret_cast<float2*>(&red[(grp * BM + s) * NOUT + k]) = make_float2(part[k], part[k + 1]);
     }
     __syncthreads();
     if (!env.is_env_wave) {
@@ -218,19 +218,27 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
       // ---- the env lanes: logits -> action -> transition -> next window
       const int row = lane < BM ? lane : 0;
       float lg[NOUT];
+      static_assert(NOUT % 2 == 0, "shares are read two at a time");
 #pragma unroll
-      for (int k = 0; k < NOUT; ++k) {
-        float v = b3r[k];
+      for (int k = 0; k < NOUT; ++k) lg[k] = b3r[k];
 #pragma unroll
-        for (int gq = 0; gq < GROUPS; ++gq) v += red[(gq * BM + row) * NOUT + k];
-        lg[k] = v;
-      }
+      for (int gq = 0; gq < GROUPS; ++gq)
+#pragma unroll
+        for (int k = 0; k < NOUT; k += 2) {
+          const float2 v = *reinterpret_cast<const float2*>(&red[(gq * BM + row) * NOUT + k]);
+          lg[k] += v.x;
+          lg[k + 1] += v.y;
+        }
+      // Where this step's records of the workgroup begin, and a lane's place there that the compiler does not know from before: otherwise it keeps a 64-bit
+      // address of each array and lane across the steps, one of them in scratch memory, whose reload waited for all stores before it, 2000 cycles a step.
+      const int64_t sample0 = (int64_t)t * NA + env.env0 * env.A, env_row0 = (int64_t)t * a.p.N + env.env0;
+      uint32_t at = lane, at_env = env.le;
+      asm volatile("" : "+v"(at), "+v"(at_env));
       int my_act = 0;
       if (env.active) {
-        const int64_t o = (int64_t)t * NA + env.s_glob;
         if (a.logits) {
 #pragma unroll
-          for (int k = 0; k < NOUT; ++k) a.logits[o * NOUT + k] = lg[k];
+          for (int k = 0; k < NOUT; ++k) (a.logits + sample0 * NOUT)[at * NOUT + k] = lg[k];
         }
         // Gumbel-max: argmax_k lg[k] - log(-log u[k]), lowest k on exact ties
         const float* const g = noise + ((t & 1) * BM + lane) * 8;
@@ -246,17 +254,20 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
             my_act = k;
           }
         }
-        if (a.sampled) a.sampled[o] = my_act;
-        if (a.forced) my_act = a.forced[o];
-        a.action[o] = my_act;
-        a.logp[o] = log_softmax_fast(lg, my_act);
+        if (a.sampled) (a.sampled + sample0)[at] = my_act;
+        if (a.forced) {
+          my_act = (a.forced + sample0)[at];
+          asm volatile("" : "+v"(my_act));  // waited for here, not behind the branch
+        }
+        (a.action + sample0)[at] = my_act;
+        (a.logp + sample0)[at] = log_softmax_fast(lg, my_act);
       }
       float rew;
       bool dn;
       env.step(my_act, rew, dn);
       if (env.active) {
-        a.reward[(int64_t)t * NA + env.s_glob] = rew;
-        if (env.ai == 0) a.done[(int64_t)t * a.p.N + env.n] = dn ? 1 : 0;
+        (a.reward + sample0)[at] = rew;
+        if (env.ai == 0) (a.done + env_row0)[at_env] = dn ? 1 : 0;
         env.paint(Xs2 + ((t + 1) & 1) * BM * PX + lane * PX);  // the windows of step t + 1 into the other tile
       }
     }
