@@ -55,9 +55,8 @@ inline NetOffsets net_offsets(int64_t base, int Din, int H, int Dout) {
   return o;
 }
 
-// The forward kernel of small calls (fused_forward.h) keeps a row tile of the input in LDS at its whole width, which bounds the
-// input width (two workgroups per CU up to about 320 inputs at H = 256, one up to about 950); wider networks and other widths take
-// the larger calls' kernels.  Which (H, BM) pairs exist: H = 64 -> BM 64; H = 128 or 256 -> BM 32.
+// The networks that the forward kernel of small calls (fused_forward.h) takes: it keeps a row tile of the input in LDS at its whole width.  The rule
+// is for tiles of 64 (64 units) and 32 samples, so that a call's route, and with it the last bits of its results, does not depend on the kernel's tile.
 inline int fused_forward_px(int Din) {
   int px = (Din + 15) / 16 * 16;
   while ((px / 4) % 2 == 0) px += 4;

@@ -1,8 +1,12 @@
 // Forward pass of small calls: both hidden layers, the output layer and whatever consumes the outputs of both networks in one
 // launch, on the caller's unstaged parameters and the fp32 instruction, with the first hidden activation kept in LDS.
 //
-// Workgroup = 4 wavefronts on a tile of BM samples x H hidden units: (BM/32) x (H/32) MFMA tiles of 32x32, one or two per
-// wavefront.  The row tile of the input sits in LDS at its whole width; a tile's wavefronts read the weights once.
+// Such a call is a chain of latencies on a few compute units.  Workgroup = 16 samples, four wavefronts: each takes 64 columns with all samples, and
+// where the layer is narrower a part of the contraction (the parts meet in LDS, where bias and tanh are shared by all threads).  The weights
+// come straight from the parameters, 16 bytes a lane at any 4-byte boundary -- four columns of one row, which are the same lane's operands of four
+// v_mfma_f32_16x16x4_f32 -- and the first groups of both layers, the biases and the inputs are all requested before anything is waited for.  One
+// environment of three agents, 75 inputs, 128 / 128 units: 6.7 us; with 32 samples a workgroup, 4-byte loads of the weights three
+// groups ahead and biases loaded where they are added 11.0 us.  2040 samples of 147 inputs, 256 / 256 units, with the sampling behind it: 39.6 -> 19.8 us.
 #pragma once
 #include "gemm.h"
 #include "heads.h"
@@ -10,209 +14,185 @@
 namespace marl {
 
 struct FusedFwdArgs {
-  RowSrc X;   // S rows of Din floats (optionally gathered)
+  RowSrc X;   // S rows of Din floats
   int64_t S;
   int Din;
-  int xvec;   // 1: rows are 16-byte aligned and Din % 4 == 0: 16-byte loads of X.  2: rows start at any 4-byte boundary of a
-              // buffer whose two ends are 16-byte aligned: a row is fetched as the aligned 16-byte chunks that cover it
   const float *W1, *b1, *W2, *b2, *W3, *b3;  // W[in][H], at any 4-byte boundary
   int kpad1;               // Din rounded up to a multiple of 16
   int px;                  // pitch of the X tile in LDS: a multiple of 4 with px / 4 odd, >= kpad1
 };
+constexpr int kSmallRows = 16;  // samples of a workgroup
+inline size_t fused_forward_small_lds(int H, int px, int nout) {
+  return sizeof(float) * (kSmallRows * (size_t)px + kSmallRows * (H + 4) + (256 / H) * kSmallRows * (size_t)(H + 4) + (size_t)H * nout);
+}
 
-// The kernel's body: workgroup `bid` of `nblk` that share the tiles.
-template <int H, int BM, int NOUT, class Finish>
-__device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const Finish& fin, const unsigned bid, const unsigned nblk) {
-  constexpr int PH = H + 4, GROUPS = 256 / BM;
-  constexpr int NTN = H / 32, MT = BM / 32, TILES = MT * NTN, TPW = TILES / 4;
-  static_assert(TILES % 4 == 0 && (TPW == 1 || TPW == 2), "4 wavefronts share the tile evenly");
-  static_assert(TPW == 1 || NTN % 2 == 0, "two tiles of a wavefront share their rows");
-  constexpr int NTH = 256;
-  constexpr int TPR = NTH / BM;  // threads staging one row of X
+// The kernel's body: tile `bid` of 16 samples.
+template <int H, int NOUT, class Finish>
+__device__ __forceinline__ void fused_forward_body(const FusedFwdArgs& a, const Finish& fin, const unsigned bid) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+  constexpr int BM = kSmallRows, PH = H + 4, CB = H / 64, KW = 4 / CB, VPT = H / 16;
+  static_assert(H == 64 || H == 128 || H == 256, "the wavefronts share columns and contraction evenly");
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  struct {
-    float *Xs, *Hs, *red, *W3s;
-  } L;
   const int px = a.px;
-  L.Xs = lds;                          // [BM][px]   input rows, k-contiguous; columns Din .. px stay zero
-  L.Hs = L.Xs + BM * px;               // [BM][PH]   h1, then h2
-  L.red = L.Hs + BM * PH;              // [GROUPS][BM][NOUT]
-  L.W3s = L.red + GROUPS * BM * NOUT;  // [H][NOUT]
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lo = lane & 31, hi = lane >> 5;
-  const int mt = (wave * TPW) / NTN, nt0 = (wave * TPW) % NTN;  // this wavefront's tiles: (mt, nt0 .. nt0+TPW-1)
-
-  for (int i = tid; i < H * NOUT; i += NTH) L.W3s[i] = a.W3[i];  // ordered before its first use by the barriers of layer 1
-  for (int i = tid; i < BM * px; i += NTH) L.Xs[i] = 0.f;        // the padding columns stay zero for good
-  __syncthreads();
-  const int64_t ntiles = (a.S + BM - 1) / BM;
-  for (int64_t tile = bid; tile < ntiles; tile += nblk) {
-    const int64_t s0 = tile * BM;
-    // ---- this tile's rows to LDS: thread -> row tid / TPR, every TPR-th 16-byte (or 4-byte) piece of it, four
-    // (twelve) loads in flight at a time.  Rows past the end re-read the last row (their results are never stored).
-    {
-      const int xr_row = tid / TPR, c0 = tid % TPR;
-      const float* xrow = a.X.ptr(min(s0 + xr_row, a.S - 1));
-      float* xdst = L.Xs + xr_row * px;
-      if (a.xvec == 2) {
-        // element j of chunk q is column 4 q + j - xo of the row; the chunks never leave the buffer (its ends are aligned)
-        // (pointer arithmetic, not an integer round trip, so that the loads stay global loads)
-        const int xo = (int)((reinterpret_cast<uintptr_t>(xrow) >> 2) & 3), last = ((xo + a.Din + 3) >> 2) - 1;
-        const float4* const chunk = reinterpret_cast<const float4*>(xrow - xo);
-        constexpr int XC = 3;  // chunks in flight per thread: a 75-wide row is one batch
-        for (int q = c0; q <= last; q += XC * TPR) {
-          float4 v[XC];
+  float* const Xs = lds;                 // [BM][px]      input rows; columns Din .. px are zero
+  float* const Hs = Xs + BM * px;        // [BM][PH]      h1
+  float* const Ps = Hs + BM * PH;        // [KW][BM][PH]  parts of a layer
+  float* const W3s = Ps + KW * BM * PH;  // [H][NOUT]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i = lane & 15, q = lane >> 4;
+  const int cb = wave % CB, kw = wave / CB;         // this wavefront's columns and its part of the contraction: groups kw, kw + KW, ... of 16
+  const int row = tid / 16, c0 = (tid % 16) * VPT;  // this thread's sample and units between the layers
+  const int64_t s0 = (int64_t)bid * BM;
+  // ---- requests: inputs, first weights, biases
+  constexpr int XB = 6, R1 = 3, R2 = H / 16 / KW < 4 ? H / 16 / KW : 4;
+  const float* const xrow = a.X.base + min(s0 + row, a.S - 1) * a.X.ld;  // rows past the end are the last one again: their results are never stored
+  float x[XB];
 #pragma unroll
-          for (int u = 0; u < XC; ++u) v[u] = chunk[min(q + u * TPR, last)];
+  for (int u = 0; u < XB; ++u) x[u] = xrow[min(tid % 16 + 16 * u, a.Din - 1)];
+  const int ng1 = a.kpad1 / 16;
+  constexpr int NG2 = H / 16;
+  const int col = 64 * cb + 4 * i;
+  f4 w1[R1][4], w2[R2][4];
+  auto load = [&](const float* W, int K, int g, f4 (&w)[4]) {
 #pragma unroll
-          for (int u = 0; u < XC; ++u) {
-            const float e[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+    for (int j = 0; j < 4; ++j) w[j] = *reinterpret_cast<const f4u*>(W + (int64_t)min(16 * g + 4 * q + j, K - 1) * H + col);
+  };
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const int c = 4 * (q + u * TPR) + j - xo;
-              if (c >= 0 && c < a.Din && q + u * TPR <= last) xdst[c] = e[j];
-            }
-          }
-        }
-      } else if (a.xvec) {
-        const int nv = a.Din / 4;
-        for (int c = c0; c < nv; c += 4 * TPR) {
-          float4 v[4];
+  for (int t = 0; t < R1; ++t) load(a.W1, a.Din, kw + KW * t, w1[t]);
+  f4 bias1[VPT / 4], bias2[VPT / 4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int cu = min(c + u * TPR, nv - 1);
-            v[u] = *reinterpret_cast<const float4*>(xrow + 4 * cu);
-          }
+  for (int v = 0; v < VPT / 4; ++v) bias1[v] = *reinterpret_cast<const f4u*>(a.b1 + c0 + 4 * v);
+  constexpr int W3T = (H * NOUT + 255) / 256;
+  float w3[W3T];
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (c + u * TPR < nv) *reinterpret_cast<float4*>(xdst + 4 * (c + u * TPR)) = v[u];
-        }
-      } else {
-        constexpr int XB = 12;  // loads in flight per thread: a 75- or 27-wide row is one batch
-        for (int c = c0; c < a.Din; c += XB * TPR) {
-          float v[XB];
+  for (int u = 0; u < W3T; ++u) w3[u] = a.W3[min(tid + 256 * u, H * NOUT - 1)];
 #pragma unroll
-          for (int u = 0; u < XB; ++u) v[u] = xrow[min(c + u * TPR, a.Din - 1)];
+  for (int t = 0; t < R2; ++t) load(a.W2, H, kw + KW * t, w2[t]);
 #pragma unroll
-          for (int u = 0; u < XB; ++u)
-            if (c + u * TPR < a.Din) xdst[c + u * TPR] = v[u];
-        }
-      }
-    }
-    __syncthreads();
-    floatx16 acc[TPW];
-    auto zero_acc = [&]() {
+  for (int v = 0; v < VPT / 4; ++v) bias2[v] = *reinterpret_cast<const f4u*>(a.b2 + c0 + 4 * v);
+  float b3[NOUT];
 #pragma unroll
-      for (int q = 0; q < TPW; ++q)
+  for (int k = 0; k < NOUT; ++k) b3[k] = a.b3[k];
+  // ---- inputs and W3 to LDS
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[q][r] = 0.f;
-    };
-    // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS
-    zero_acc();
+  for (int u = 0; u < XB; ++u) {
+    const int c = tid % 16 + 16 * u;
+    if (c < px) Xs[row * px + c] = c < a.Din ? x[u] : 0.f;
+  }
+  for (int c1 = tid % 16 + 16 * XB; c1 < px; c1 += 16 * XB) {  // wide inputs
 #pragma unroll
-    for (int q = 0; q < TPW; ++q)
-      gemm_phase_direct<H>(L.Xs + (mt * 32 + lo) * px + 4 * hi, a.W1 + (nt0 + q) * 32 + lo, a.Din, hi, a.kpad1 / 16, acc[q]);
+    for (int u = 0; u < XB; ++u) x[u] = xrow[min(c1 + 16 * u, a.Din - 1)];
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      const int n = (nt0 + q) * 32 + lo;
-      const float bias = a.b1[n];
+    for (int u = 0; u < XB; ++u)
+      if (c1 + 16 * u < px) Xs[row * px + c1 + 16 * u] = c1 + 16 * u < a.Din ? x[u] : 0.f;
+  }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        float v = tanh_f32(acc[q][r] + bias);
-        L.Hs[m * PH + n] = v;
-        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four elements in flight at a time keeps registers bounded
-      }
-    }
-    __syncthreads();  // the h1 tile is complete
-    // ---- layer 2: h2 = tanh(h1 W2 + b2), kept in registers
-    zero_acc();
+  for (int u = 0; u < W3T; ++u)
+    if (tid + 256 * u < H * NOUT) W3s[tid + 256 * u] = w3[u];
+  lds_barrier();
+  floatx4 acc[4];  // register r of acc[e]: sample 4 q + r, column col + e
+  auto clear = [&]() {
 #pragma unroll
-    for (int q = 0; q < TPW; ++q)
-      gemm_phase_direct<H>(L.Hs + (mt * 32 + lo) * PH + 4 * hi, a.W2 + (nt0 + q) * 32 + lo, H, hi, H / 16, acc[q]);
-    __syncthreads();  // every wavefront is past its last read of h1
+    for (int e = 0; e < 4; ++e) acc[e] = floatx4{0.f, 0.f, 0.f, 0.f};
+  };
+  auto group = [&](const float* A, const f4 (&w)[4]) {  // A: this lane's sample, + 4 q of the group
+    const f4 v = *reinterpret_cast<const f4*>(A);
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-      const int n = (nt0 + q) * 32 + lo;
-      const float bias = a.b2[n];
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        float v = tanh_f32(acc[q][r] + bias);
-        L.Hs[m * PH + n] = v;
-        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    __syncthreads();
-    // ---- output layer on the ALUs: thread -> (sample tid % BM, slice tid / BM of the hidden units)
-    {
-      const int s = tid % BM, grp = tid / BM;
-      constexpr int PER = H / GROUPS;
-      float part[NOUT];
+      for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j], w[j][e], acc[e], 0, 0, 0);
+  };
+  auto put = [&]() {
 #pragma unroll
-      for (int k = 0; k < NOUT; ++k) part[k] = 0.f;
-      static_assert(PER % 4 == 0, "hidden units are read four at a time");
-#pragma unroll 2
-      for (int i = grp * PER; i < (grp + 1) * PER; i += 4) {
-        const float4 hv = *reinterpret_cast<const float4*>(&L.Hs[s * PH + i]);
-        const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
-        float wv[4 * NOUT];  // W3 rows i..i+3: 4 * NOUT consecutive floats, the same for every lane of the wavefront
+    for (int r = 0; r < 4; ++r) *reinterpret_cast<f4*>(&Ps[(kw * BM + 4 * q + r) * PH + col]) = f4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+    lds_barrier();
+  };
+  auto activation = [&](int v, const f4& bias) {  // units c0 + 4 v .. of this thread's sample
+    f4 t = *reinterpret_cast<const f4*>(&Ps[row * PH + c0 + 4 * v]);
 #pragma unroll
-        for (int q = 0; q < NOUT; ++q) {
-          const float4 t = *reinterpret_cast<const float4*>(&L.W3s[i * NOUT + 4 * q]);
-          wv[4 * q] = t.x; wv[4 * q + 1] = t.y; wv[4 * q + 2] = t.z; wv[4 * q + 3] = t.w;
-        }
+    for (int p = 1; p < KW; ++p) t += *reinterpret_cast<const f4*>(&Ps[(p * BM + row) * PH + c0 + 4 * v]);
+    t += bias;
+    return f4{tanh_f32(t[0]), tanh_f32(t[1]), tanh_f32(t[2]), tanh_f32(t[3])};
+  };
+  // ---- layer 1
+  clear();
+#pragma unroll 1
+  for (int t0 = 0; kw + KW * t0 < ng1; t0 += R1) {
+#pragma unroll
+    for (int d = 0; d < R1; ++d) {
+      const int g = kw + KW * (t0 + d);
+      if (g < ng1) {  // uniform
+        f4 w[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-          for (int k = 0; k < NOUT; ++k) part[k] = fmaf(hh[j], wv[j * NOUT + k], part[k]);
+          for (int e = 0; e < 4; ++e) w[j][e] = 16 * g + 4 * q + j < a.Din ? w1[d][j][e] : 0.f;
+        group(Xs + i * px + 16 * g + 4 * q, w);
+        if (g + KW * R1 < ng1) load(a.W1, a.Din, g + KW * R1, w1[d]);
       }
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) L.red[(grp * BM + s) * NOUT + k] = part[k];
     }
-    __syncthreads();
-    if (tid < BM) {
-      float out[NOUT];
-#pragma unroll
-      for (int k = 0; k < NOUT; ++k) {
-        float v = a.b3[k];
-#pragma unroll
-        for (int gq = 0; gq < GROUPS; ++gq) v += L.red[(gq * BM + tid) * NOUT + k];
-        out[k] = v;
-      }
-      if (s0 + tid < a.S) fin(s0 + tid, out, nullptr, nullptr);
-    }
-    __syncthreads();  // the tile buffers are reused by the next row tile
   }
+  put();
+#pragma unroll
+  for (int v = 0; v < VPT / 4; ++v) *reinterpret_cast<f4*>(&Hs[row * PH + c0 + 4 * v]) = activation(v, bias1[v]);
+  lds_barrier();
+  // ---- layer 2
+  clear();
+#pragma unroll
+  for (int t = 0; t < NG2 / KW; ++t) {
+    const int g = kw + KW * t;
+    group(Hs + i * PH + 16 * g + 4 * q, w2[t % R2]);
+    if (t + R2 < NG2 / KW) load(a.W2, H, g + KW * R2, w2[t % R2]);
+  }
+  put();
+  // ---- output layer: a thread's units, then the sixteen threads of a sample
+  float out[NOUT];
+#pragma unroll
+  for (int k = 0; k < NOUT; ++k) out[k] = 0.f;
+#pragma unroll
+  for (int v = 0; v < VPT / 4; ++v) {
+    const f4 h = activation(v, bias2[v]);
+    float w[4 * NOUT];
+#pragma unroll
+    for (int u = 0; u < NOUT; ++u) {
+      const f4 t = *reinterpret_cast<const f4*>(&W3s[(c0 + 4 * v) * NOUT + 4 * u]);
+      w[4 * u] = t[0]; w[4 * u + 1] = t[1]; w[4 * u + 2] = t[2]; w[4 * u + 3] = t[3];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int k = 0; k < NOUT; ++k) out[k] = fmaf(h[e], w[e * NOUT + k], out[k]);
+  }
+#pragma unroll
+  for (int o = 1; o < 16; o *= 2)
+#pragma unroll
+    for (int k = 0; k < NOUT; ++k) out[k] += __shfl_xor(out[k], o);
+#pragma unroll
+  for (int k = 0; k < NOUT; ++k) out[k] += b3[k];
+  if (tid % 16 == 0 && s0 + row < a.S) fin(s0 + row, out, nullptr, nullptr);
 }
 
 // Both networks of a small call in one launch, with unstaged weights: workgroups 0 .. grid_a - 1 the first.
 template <int HA, int HB, int NOUT_A, int NOUT_B, class FinishA, class FinishB>
 __global__ void __launch_bounds__(256, 2) fused_forward_small_kernel(FusedFwdArgs a, FinishA fa, FusedFwdArgs b, FinishB fb, unsigned grid_a) {
-  if (blockIdx.x < grid_a) fused_forward_body<HA, HA == 64 ? 64 : 32, NOUT_A, FinishA>(a, fa, blockIdx.x, grid_a);
-  else fused_forward_body<HB, HB == 64 ? 64 : 32, NOUT_B, FinishB>(b, fb, blockIdx.x - grid_a, gridDim.x - grid_a);
+  if (blockIdx.x < grid_a) fused_forward_body<HA, NOUT_A, FinishA>(a, fa, blockIdx.x);
+  else fused_forward_body<HB, NOUT_B, FinishB>(b, fb, blockIdx.x - grid_a);
 }
 
-// Few enough rows that a call is a chain of latencies: one launch on the unstaged parameters (a tile's wavefronts read
-// them once, 4 bytes at a time) against a staging kernel and a launch per network on split operands.  Measured, us, one
-// launch / staged:
-//   75 inputs, 128 / 128 units:   3 000 samples 12 / 24   12 288 samples 23 / 27   49 152 samples 80 / 53
-//   147 inputs, 256 / 256 units:  3 000 samples 39 / 44    5 000 samples 50 / 46   20 480 samples 147 / 83
-//   147 and 882 inputs, 256 / 128 units:  3 600 samples 41 / 65   24 576 samples 159 / 90
-// The line lies below the smallest size at which any of them crosses (about 4 000).  The one launch runs on the fp32
-// instruction, so that an output's last bits differ on the two sides.
+// Few enough rows that a call is a chain of latencies: one launch on the unstaged parameters against a staging kernel and a launch per network on split
+// operands.  The line was drawn for an earlier kernel of this path (us, one launch / staged: 75 inputs, 128 / 128 units, 3 000 samples 12 / 24, 12 288
+// samples 23 / 27; 147 inputs, 256 / 256 units, 3 000 samples 39 / 44, 5 000 samples 50 / 46); the present one takes half to two thirds of its times.  It stays
+// where it was because the one launch runs on the fp32 instruction, so that an output's last bits differ on the two sides.
 constexpr int64_t kForwardSmall = 2048;
 
 template <int HA, int HB, int NOUT_A, int NOUT_B, class FinishA, class FinishB>
 inline int32_t launch_fused_forward_small_inst(const FusedFwdArgs& a, const FinishA& fa, const FusedFwdArgs& b, const FinishB& fb, hipStream_t s) {
   auto kern = fused_forward_small_kernel<HA, HB, NOUT_A, NOUT_B, FinishA, FinishB>;
-  const size_t bytes = std::max(fused_forward_lds_bytes(HA, a.Din, NOUT_A), fused_forward_lds_bytes(HB, b.Din, NOUT_B));
+  const size_t bytes = std::max(fused_forward_small_lds(HA, a.px, NOUT_A), fused_forward_small_lds(HB, b.px, NOUT_B));
   if (bytes > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
     return MARL_E_LAUNCH;
-  const unsigned grid_a = (unsigned)((a.S + (HA == 64 ? 64 : 32) - 1) / (HA == 64 ? 64 : 32));
-  const unsigned grid_b = (unsigned)((b.S + (HB == 64 ? 64 : 32) - 1) / (HB == 64 ? 64 : 32));
+  const unsigned grid_a = (unsigned)((a.S + kSmallRows - 1) / kSmallRows), grid_b = (unsigned)((b.S + kSmallRows - 1) / kSmallRows);
   if (grid_a + grid_b == 0) return MARL_OK;
   hipLaunchKernelGGL(kern, dim3(grid_a + grid_b), dim3(256), bytes, s, a, fa, b, fb, grid_a);
   return launch_status();

@@ -237,43 +237,6 @@ __device__ __forceinline__ void gemm_phase_t(const bf16_t* xs, int plane, Weight
   }
 }
 
-// acc += A B on the fp32 instruction with B straight from the caller's parameters, W[K][H] at any 4-byte boundary: for
-// calls of so few rows that staging a copy of the weights would take longer than using it.  As points at this lane's row,
-// + 4 * hi, and is zero from K to 16 * kgroups; W at this lane's column.
-template <int H>
-__device__ __forceinline__ void gemm_phase_direct(const float* __restrict__ As, const float* __restrict__ W, int K, int hi, int kgroups, floatx16& acc) {
-  constexpr int kDepth = 3;  // groups in flight: the one in use and two on their way
-  float b[kDepth][8];
-  auto load = [&](int g, float (&v)[8]) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = 16 * g + 8 * (u / 4) + 4 * hi + u % 4;
-      const float w = W[(int64_t)min(k, K - 1) * H];
-      v[u] = k < K ? w : 0.f;
-    }
-  };
-  load(0, b[0]);
-  load(1, b[1]);
-#pragma unroll 1
-  for (int g0 = 0; g0 < kgroups; g0 += kDepth) {
-#pragma unroll
-    for (int d = 0; d < kDepth; ++d) {
-      const int g = g0 + d;
-      if (g < kgroups) {  // uniform
-        load(g + kDepth - 1, b[(d + kDepth - 1) % kDepth]);
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const float4 a = *reinterpret_cast<const float4*>(As + 16 * g + 8 * u);
-          const float af[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(af[j], b[d][4 * u + j], acc, 0, 0, 0);
-        }
-      }
-    }
-  }
-}
-
-
 // BM x BN tile, four wavefronts (2 x 2 at BM = 128, side by side at the other heights of TN), k tiles of 32 in one LDS buffer of split
 // operands; the next k tile travels global -> registers while the current one is multiplied, and two workgroups per CU
 // cover each other's staging and barriers.  A tile is kept in LDS in its source orientation: k-contiguous tiles are read

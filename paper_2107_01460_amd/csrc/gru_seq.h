@@ -24,8 +24,6 @@
 
 namespace marl {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-
 inline bool gru_seq_supported(int H) { return H % 32 == 0 && H <= 256; }
 inline int64_t gru_weight_floats(int H) { return (((int64_t)H * H * 9 / 2 + 63) / 64) * 64; }  // one staged copy
 
@@ -105,12 +103,6 @@ struct GruFwdArgs {
 // acc[i] += W[i] x B over 32 along the contraction, i-th of N independent tiles (small products first)
 __device__ __forceinline__ floatx4 mfma16(const bf16x8& a, const bf16x8& b, floatx4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-// Barrier for data exchanged through LDS only: global loads and stores stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // SEG: the runs of a.runs, a workgroup taking group after group; otherwise workgroup i has sequences i * MT .. for all T steps.

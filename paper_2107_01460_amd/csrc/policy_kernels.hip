@@ -57,8 +57,6 @@ struct CriticRolloutFinish {
 FusedFwdArgs direct_args(const RowSrc& X, int64_t S, int Din, const float* params, const NetOffsets& o) {
   FusedFwdArgs a{};
   a.X = X; a.S = S; a.Din = Din;
-  a.xvec = aligned16(X.base) && X.ld % 4 == 0 && Din % 4 == 0;
-  if (!a.xvec && X.gather == nullptr && aligned16(X.base) && (X.nrows * X.ld) % 4 == 0) a.xvec = 2;
   a.W1 = params + o.W1; a.b1 = params + o.b1; a.W2 = params + o.W2; a.b2 = params + o.b2; a.W3 = params + o.W3; a.b3 = params + o.b3;
   a.kpad1 = (Din + 15) / 16 * 16; a.px = fused_forward_px(Din);
   return a;

@@ -17,6 +17,7 @@
 
 namespace marl {
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
@@ -67,6 +68,12 @@ __device__ __forceinline__ float sum_of(float s, const floatx16& v) {  // (a NaN
   return s;
 }
 __device__ __forceinline__ bool any_in_workgroup(bool b) { return __builtin_amdgcn_readfirstlane(__syncthreads_or(b)) != 0; }
+// Barrier for data exchanged through LDS only: global loads and stores stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 // A zero that the compiler does not know
 __device__ __forceinline__ int opaque_zero() {
   int z = 0;
