@@ -134,27 +134,19 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   const int wn = wave % WN, wm = wave / WN;
   const int64_t ntiles = (a.S + BM - 1) / BM;
 
-  for (int e = tid; e < 8 * H; e += THREADS) {
-    const int k = e / H, u = e - k * H;
-    w3t[k * P + u] = k < NOUT ? to_bf16(a.W3[u * NOUT + (k < NOUT ? k : 0)]) : (bf16_t)0;
-  }
-  for (int e = tid; e < H; e += THREADS) {
-    bias[e] = to_bf16(a.b1[e]);
-    bias[H + e] = to_bf16(a.b2[e]);
-  }
-  if (TRAIN)
-    for (int e = tid; e < 32 * PD; e += THREADS) dlt[e] = 0;
+  GroupCopy<H * NOUT, THREADS> w3;
+  GroupCopy<H, THREADS> b1, b2;
+  w3.request(tid, a.W3);
+  b1.request(tid, a.b1);
+  b2.request(tid, a.b2);
   // the output layer's bias: in LDS in training, whose registers are full, else in registers
   float bias3[TRAIN ? 1 : NOUT];
+  [[maybe_unused]] float b3 = 0.f;
   if constexpr (TRAIN) {
-    if (tid < NOUT) b3s[tid] = a.b3[tid];
+    b3 = a.b3[min(tid, NOUT - 1)];
   } else {
 #pragma unroll
     for (int k = 0; k < NOUT; ++k) bias3[k] = a.b3[k];
-  }
-  if constexpr (TRAIN) {
-    if (tid == 0) *prep = fin.prepare();
-    for (int e = tid; e < NW * AS; e += THREADS) accS[e] = 0.f;
   }
 
   // ---- weights: k step `nxt` of the sequence layer 1, layer 2 (, dz1), and again for the next tile
@@ -170,6 +162,19 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   };
 #pragma unroll
   for (int u = 0; u < RING; ++u) load_w(u);
+
+  if constexpr (TRAIN) {
+    if (tid == 0) *prep = fin.prepare();
+    for (int e = tid; e < NW * AS; e += THREADS) accS[e] = 0.f;
+    for (int e = tid; e < 32 * PD; e += THREADS) dlt[e] = 0;
+  }
+  for (int e = tid; e < (8 - NOUT) * H; e += THREADS) w3t[(NOUT + e / H) * P + e % H] = 0;
+  w3.store(tid, [&](int e, float v) { w3t[e % NOUT * P + e / NOUT] = to_bf16(v); });
+  b1.store(tid, [&](int e, float v) { bias[e] = to_bf16(v); });
+  b2.store(tid, [&](int e, float v) { bias[H + e] = to_bf16(v); });
+  if constexpr (TRAIN) {
+    if (tid < NOUT) b3s[tid] = b3;
+  }
 
   floatx16 acc[MT][NT];
   auto zero_acc = [&]() {

@@ -114,25 +114,12 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63;
-  for (int e = tid; e < 8 * H; e += THREADS) {
-    const int k = e / H, u = e - k * H;
-    const SplitPair s = split_pair_any(k < NOUT ? a.W3[u * NOUT + (k < NOUT ? k : 0)] : 0.f, 0.f);
-    w3t[k * P3 + u] = (bf16_t)s.h;
-    w3t[PLANE3 + k * P3 + u] = (bf16_t)s.m;
-    w3t[2 * PLANE3 + k * P3 + u] = (bf16_t)s.l;
-  }
-  for (int e = tid; e < H; e += THREADS) {
-    bias[e] = a.b1[e];
-    bias[H + e] = a.b2[e];
-  }
-  for (int e = tid; e < H * NOUT; e += THREADS) w3s[e] = a.W3[e];
-  for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
-  for (int e = tid; e < BM * AS; e += THREADS) accS[e] = 0.f;
-  if (tid < NOUT) b3s[tid] = a.b3[tid];
-  if (tid == 0) {
-    *inexact = 0;
-    *prep = fn.prepare();
-  }
+  GroupCopy<H * NOUT, THREADS> w3;
+  GroupCopy<H, THREADS> b1, b2;
+  w3.request(tid, a.W3);
+  b1.request(tid, a.b1);
+  b2.request(tid, a.b2);
+  const float b3 = a.b3[min(tid, NOUT - 1)];
 
   // ---- weights: k step `nxt` of the sequence layer 1, layer 2, dz1, and again for the next tile
   const int steps1 = a.Kp / 16, total = steps1 + 2 * (H / 16);
@@ -147,6 +134,25 @@ __device__ __forceinline__ void fused_train_body(const FusedTrainArgs& a, const 
   };
 #pragma unroll
   for (int u = 0; u < RING; ++u) load_w(u);
+
+  if (tid == 0) {
+    *inexact = 0;
+    *prep = fn.prepare();
+  }
+  for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
+  for (int e = tid; e < BM * AS; e += THREADS) accS[e] = 0.f;
+  for (int e = tid; e < (8 - NOUT) * H; e += THREADS) w3t[(NOUT + e / H) * P3 + e % H] = w3t[PLANE3 + (NOUT + e / H) * P3 + e % H] = w3t[2 * PLANE3 + (NOUT + e / H) * P3 + e % H] = 0;
+  w3.store(tid, [&](int e, float v) {
+    const int u = e / NOUT, k = e % NOUT;
+    const SplitPair s = split_pair_any(v, 0.f);
+    w3t[k * P3 + u] = (bf16_t)s.h;
+    w3t[PLANE3 + k * P3 + u] = (bf16_t)s.m;
+    w3t[2 * PLANE3 + k * P3 + u] = (bf16_t)s.l;
+    w3s[e] = v;
+  });
+  b1.store(tid, [&](int e, float v) { bias[e] = v; });
+  b2.store(tid, [&](int e, float v) { bias[H + e] = v; });
+  if (tid < NOUT) b3s[tid] = b3;
 
   // dW2: this wavefront's block of tiles; of its two columns, the one whose sums (the b2 gradient) it takes
   const int it0 = NW == 4 ? 2 * (wave >> 1) : wave, jt0 = NW == 4 ? 2 * (wave & 1) : 0, gb2_j = NW == 4 ? wave >> 1 : wave;

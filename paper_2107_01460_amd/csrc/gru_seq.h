@@ -300,7 +300,9 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
   __shared__ __attribute__((aligned(16))) float W3s[H * NOUT];
   __shared__ int group;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
-  for (int j = tid; j < H * NOUT; j += THREADS) W3s[j] = a.W3[j];
+  GroupCopy<H * NOUT, THREADS> w3;
+  w3.request(tid, a.W3);
+  w3.store(tid, [&](int e, float v) { W3s[e] = v; });
   int unit[UB];
 #pragma unroll
   for (int b = 0; b < UB; ++b) unit[b] = 16 * (UB * wave + b) + 4 * q;
@@ -489,6 +491,8 @@ __global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_ste
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
   const int64_t s0 = (int64_t)blockIdx.x * MT;
   const int rows = (int)min((int64_t)MT, a.S - s0);
+  GroupCopy<H * NOUT, THREADS> w3;
+  w3.request(tid, a.W3);
   const int K1 = (a.D + 31) / 32 * 32, KS1 = K1 / 32;
 
   constexpr int NI = UB * KS, RING = SM == 1 ? 4 : 2;
@@ -536,7 +540,7 @@ __global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_ste
     bias[3][j] = a.bi[2 * H + j];
     bias[4][j] = a.bh[2 * H + j];
   }
-  for (int j = tid; j < H * NOUT; j += THREADS) W3s[j] = a.W3[j];
+  w3.store(tid, [&](int e, float v) { W3s[e] = v; });
   const SampleArgs& sa = a.sample;
   if (tid < 2 * MT && (tid >> 1) < rows) {  // log(-log u) of sample tid / 2, Philox call tid % 2 (see sample_uniforms)
     const int64_t s = s0 + (tid >> 1);

@@ -46,11 +46,11 @@ __global__ void __launch_bounds__(256, OCC) rollout_eval_kernel(RolloutArgs a) {
   int slot = env.copy, events = 0; // apart: the episode it plays and its steps with a reward
   uint32_t episode0 = 0;
 
-  for (int i = tid; i < H * NOUT; i += 256) W3s[i] = a.W3[i];
-  for (int i = tid; i < H; i += 256) {
-    b1s[i] = a.b1[i];
-    b2s[i] = a.b2[i];
-  }
+  GroupCopy<H * NOUT, 256> w3;
+  GroupCopy<H, 256> b1, b2;
+  w3.request(tid, a.W3);
+  b1.request(tid, a.b1);
+  b2.request(tid, a.b2);
   for (int i = tid; i < BM * PX; i += 256) reinterpret_cast<uint32_t*>(Xs2)[i] = 0u;  // padding columns and unused rows stay zero for good
   if (env.is_env_wave) {
     env.load();
@@ -79,6 +79,9 @@ __global__ void __launch_bounds__(256, OCC) rollout_eval_kernel(RolloutArgs a) {
       }
     }
   }
+  w3.store(tid, [&](int e, float v) { W3s[e] = v; });
+  b1.store(tid, [&](int e, float v) { b1s[e] = v; });
+  b2.store(tid, [&](int e, float v) { b2s[e] = v; });
   __syncthreads();
   if (left > 0) env.paint(Xs2 + lane * PX);
   if (env.is_env_wave) {

@@ -117,9 +117,11 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
     for (int k = 0; k < 4; ++k) dst[k] = logf(-logf(u[k]));  // the same fp32 operations as the per-step sampler
   };
 
-  for (int i = tid; i < H * NOUT; i += 256) W3s[i] = a.W3[i];
+  GroupCopy<H * NOUT, 256> w3;
+  w3.request(tid, a.W3);
   for (int i = tid; i < 2 * BM * PX; i += 256) Xs2[i] = 0.f;  // padding columns and unused rows stay zero for good
   if (env.is_env_wave) env.load();
+  w3.store(tid, [&](int e, float v) { W3s[e] = v; });
   __syncthreads();
   if (env.active) env.paint(Xs2 + lane * PX);
   if (a.T > 0) draw_noise(0);

@@ -95,31 +95,16 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
   const int wn = wave % WN, wm = wave / WN;
   const int64_t ntiles = (a.S + BM - 1) / BM;
 
-  for (int e = tid; e < 8 * H; e += THREADS) {
-    const int k = e / H, u = e - k * H;
-    const SplitPair s = split_pair_any(k < NOUT ? a.W3[u * NOUT + (k < NOUT ? k : 0)] : 0.f, 0.f);
-    w3t[k * P + u] = (bf16_t)s.h;
-    w3t[PLANE3 + k * P + u] = (bf16_t)s.m;
-    w3t[2 * PLANE3 + k * P + u] = (bf16_t)s.l;
-  }
-  if (tid == 0) *inexact = 0;
-  for (int e = tid; e < H; e += THREADS) {
-    bias[e] = a.b1[e];
-    bias[H + e] = a.b2[e];
-  }
-  if (TRAIN) {
-    for (int e = tid; e < H * W3P; e += THREADS) w3s[e] = e % W3P < NOUT ? a.W3[e / W3P * NOUT + e % W3P] : 0.f;
-    for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
-    for (int e = tid; e < BM * 8; e += THREADS) dls[e] = 0.f;
-    for (int e = tid; e < BM / 16 * AS; e += THREADS) accD[e] = 0.0;
-    if constexpr (TRAIN) {
-      if (tid == 0) *prep = fin.prepare();
-    }
-  }
+  GroupCopy<H * NOUT, THREADS> w3;
+  GroupCopy<H, THREADS> b1, b2;
+  w3.request(tid, a.W3);
+  b1.request(tid, a.b1);
+  b2.request(tid, a.b2);
   // the output layer's bias: in LDS in training, whose registers are full, else in registers
   float bias3[TRAIN ? 1 : NOUT];
+  [[maybe_unused]] float b3 = 0.f;
   if constexpr (TRAIN) {
-    if (tid < NOUT) b3s[tid] = a.b3[tid];
+    b3 = a.b3[min(tid, NOUT - 1)];
   } else {
 #pragma unroll
     for (int k = 0; k < NOUT; ++k) bias3[k] = a.b3[k];
@@ -138,6 +123,29 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
   };
 #pragma unroll
   for (int u = 0; u < RING; ++u) load_w(u);
+
+  if (tid == 0) *inexact = 0;
+  if constexpr (TRAIN) {
+    if (tid == 0) *prep = fin.prepare();
+    for (int e = tid; e < H * (W3P - NOUT); e += THREADS) w3s[e / (W3P - NOUT) * W3P + NOUT + e % (W3P - NOUT)] = 0.f;
+    for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
+    for (int e = tid; e < BM * 8; e += THREADS) dls[e] = 0.f;
+    for (int e = tid; e < BM / 16 * AS; e += THREADS) accD[e] = 0.0;
+  }
+  for (int e = tid; e < (8 - NOUT) * H; e += THREADS) w3t[(NOUT + e / H) * P + e % H] = w3t[PLANE3 + (NOUT + e / H) * P + e % H] = w3t[2 * PLANE3 + (NOUT + e / H) * P + e % H] = 0;
+  w3.store(tid, [&](int e, float v) {
+    const int u = e / NOUT, k = e % NOUT;
+    const SplitPair s = split_pair_any(v, 0.f);
+    w3t[k * P + u] = (bf16_t)s.h;
+    w3t[PLANE3 + k * P + u] = (bf16_t)s.m;
+    w3t[2 * PLANE3 + k * P + u] = (bf16_t)s.l;
+    if (TRAIN) w3s[u * W3P + k] = v;
+  });
+  b1.store(tid, [&](int e, float v) { bias[e] = v; });
+  b2.store(tid, [&](int e, float v) { bias[H + e] = v; });
+  if constexpr (TRAIN) {
+    if (tid < NOUT) b3s[tid] = b3;
+  }
 
   floatx16 acc[MT];
   auto zero_acc = [&]() {
