@@ -11,7 +11,7 @@
 // Measured on an MI355X against a kernel per layer with packed inputs and transposed copies, 147 inputs, 512 units: minibatch of
 // 262 144 samples, actor: pack 72 + layers 146 + 205 + output layer and loss 278 + dz1 203 us -> one launch of 491 us (W3 gradient
 // included; 671 TFLOP/s); weight gradients 237 + 104 -> 158 + 109 us; a training iteration of 4096 environments 164 -> 111 ms;
-// forward pass of 32 768 samples through both networks and the sampling 159 -> 73 us.
+// forward pass of 32 768 samples through both networks and the sampling 159 -> 73 us, with both networks and both stagings in one launch each 64 us.
 // Bound: two workgroups of four wavefronts share a CU (64 rows each, 128 of a lane's 256 registers accumulators), and a tile is
 // a chain of products (39 of 107 thousand cycles for the pair), tanh (16), gradients on the output side (15), copies and barriers
 // that the other workgroup's phases cover; the weights take 1.2 MB from the L2 per tile; at 512 units 36 (six outputs) and 38 (one)
@@ -44,8 +44,7 @@ struct Bf16StageNet {
   int Din, Kp, H;
 };
 // A thread takes eight consecutive k of one column: one 16-byte store.
-static __global__ void __launch_bounds__(256) bf16_stage_kernel(Bf16StageNet a, Bf16StageNet b) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void bf16_stage(const Bf16StageNet& a, const Bf16StageNet& b, int64_t i) {
   const int64_t na = (int64_t)(a.Kp + 2 * a.H) * a.H / 8;
   const bool second = i >= na;
   const Bf16StageNet n = second ? b : a;
@@ -62,9 +61,12 @@ static __global__ void __launch_bounds__(256) bf16_stage_kernel(Bf16StageNet a, 
   *reinterpret_cast<uint4*>(n.w + bf16_frag_index(k, c, n.H)) =
       make_uint4(pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3]), pack2_bf16(v[4], v[5]), pack2_bf16(v[6], v[7]));
 }
+static __global__ void __launch_bounds__(256) bf16_stage_kernel(Bf16StageNet a, Bf16StageNet b) { bf16_stage(a, b, (int64_t)blockIdx.x * 256 + threadIdx.x); }
+inline unsigned bf16_stage_blocks(const Bf16StageNet& a, const Bf16StageNet& b) {
+  return (unsigned)((((int64_t)(a.Kp + 2 * a.H) * a.H + (int64_t)(b.Kp + 2 * b.H) * b.H) / 8 + 255) / 256);
+}
 inline void launch_bf16_stage(const Bf16StageNet& a, const Bf16StageNet& b, hipStream_t s) {
-  const int64_t n = ((int64_t)(a.Kp + 2 * a.H) * a.H + (int64_t)(b.Kp + 2 * b.H) * b.H) / 8;
-  hipLaunchKernelGGL(bf16_stage_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a, b);
+  hipLaunchKernelGGL(bf16_stage_kernel, dim3(bf16_stage_blocks(a, b)), dim3(256), 0, s, a, b);
 }
 
 // ---- a row tile through a network -----------------------------------------------------------------------------
@@ -107,9 +109,10 @@ struct LossIn<true, Fin> {
   typedef decltype(std::declval<Fin>().prepare()) Prep;  // two floats
 };
 
+// The kernel's body: workgroup `bid` of `nblk` that share the tiles.
 // Fin: TRAIN: a loss functor (ActorLoss, CriticLoss); else what becomes of a sample's outputs, fin(s, out, nullptr, nullptr).
 template <int H, int BM, int NOUT, bool TRAIN, class Fin>
-__global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>::WAVES)) bf16_net_kernel(Bf16NetArgs a, Fin fin) {
+__device__ __forceinline__ void bf16_net_body(const Bf16NetArgs& a, const Fin& fin, const unsigned bid, const unsigned nblk) {
   using Sh = Bf16Shape<H, BM>;
   constexpr int NT = Sh::NT, MT = Sh::MT, WN = Sh::WN, NW = Sh::NW, P = Sh::P, PD = Sh::PD, THREADS = 64 * NW;
   constexpr int RING = NT == 1 ? 4 : 2;        // k steps of weights on their way
@@ -296,13 +299,13 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
 #pragma unroll
   for (int u = 0; u < (TRAIN ? 2 * NT : 1); ++u) gw[u] = bf16_floatx4{0.f, 0.f, 0.f, 0.f};
 
-  if ((int64_t)blockIdx.x < ntiles) row_offsets(blockIdx.x);
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+  if ((int64_t)bid < ntiles) row_offsets(bid);
+  for (int64_t t = bid; t < ntiles; t += nblk) {
     asm volatile("" : "+v"(lane));  // what depends on the lane is formed anew for every tile: kept, the many addresses were spilled
     lo = lane & 31; hi = lane >> 5; l15 = lane & 15; l4 = lane >> 4;
     const int64_t s0 = t * BM;
     const int rows = (int)min((int64_t)BM, a.S - s0);
-    const bool more = t + gridDim.x < ntiles;  // uniform
+    const bool more = t + nblk < ntiles;       // uniform
     [[maybe_unused]] int32_t entry[GPW];       // the loss's row order entries of this wavefront's samples, requested long before the rows
     if constexpr (TRAIN) {
 #pragma unroll
@@ -320,7 +323,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
       __syncthreads();
       product(min(steps1 - k0 / 16, 4 * XJ));
     }
-    if (more) row_offsets(t + gridDim.x);
+    if (more) row_offsets(t + nblk);
     __syncthreads();  // the input has been read
     tanh_out(bias);
     __syncthreads();
@@ -465,7 +468,7 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
       for (int r = 0; r < 4; ++r)
         if (l15 < NOUT) G[wm * H * NOUT + (32 * wn * NT + 16 * u + 4 * l4 + r) * NOUT + l15] = gw[u][r];
     __syncthreads();
-    float* const own = a.partial + blockIdx.x * copy_pitch(COUNT);
+    float* const own = a.partial + bid * copy_pitch(COUNT);
     for (int e = tid; e < COUNT; e += THREADS) {
       float v = 0.f;
       if (e < H * NOUT) {
@@ -480,6 +483,17 @@ __global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>
   }
 }
 
+template <int H, int BM, int NOUT, bool TRAIN, class Fin>
+__global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>::WAVES)) bf16_net_kernel(Bf16NetArgs a, Fin fin) {
+  bf16_net_body<H, BM, NOUT, TRAIN, Fin>(a, fin, blockIdx.x, gridDim.x);
+}
+// Forward pass of two networks of one width in one launch, workgroups 0 .. grid_a - 1 the first.
+template <int H, int BM, int NOUT_A, int NOUT_B, class FinA, class FinB>
+__global__ void __launch_bounds__((64 * Bf16Shape<H, BM>::NW), (Bf16Shape<H, BM>::WAVES)) bf16_net_pair_kernel(Bf16NetArgs a, FinA fa, Bf16NetArgs b, FinB fb, unsigned grid_a) {
+  if (blockIdx.x < grid_a) bf16_net_body<H, BM, NOUT_A, false, FinA>(a, fa, blockIdx.x, grid_a);
+  else bf16_net_body<H, BM, NOUT_B, false, FinB>(b, fb, blockIdx.x - grid_a, gridDim.x - grid_a);
+}
+
 // Forward passes of fewer samples take tiles of 32 rows instead of 64: below one taller tile per CU the lower ones occupy more of
 // the chip.  us, 64 / 32 rows, one network: 512 units, 8192 samples 31.8 / 27.1, 16 384: 33.6 / 34.2, 32 768: 42.6 / 52.4;
 // 256 units, 12 288: 16.1 / 15.4, 32 768: 20.7 / 24.8.  (Same bits: both take a sample's sums in the same order.)
@@ -489,6 +503,8 @@ inline int64_t bf16_net_partial_floats(int H, int nout) { return (int64_t)H * no
 // and asks for its first weights).
 constexpr unsigned bf16_net_grid(int H) { return H > 256 ? 512 : 1024; }
 
+inline unsigned bf16_net_blocks(int H, int BM, int64_t S) { return (unsigned)std::min<int64_t>((S + BM - 1) / BM, BM == 32 ? 2 * bf16_net_grid(H) : bf16_net_grid(H)); }
+
 template <int H, int BM, int NOUT, bool TRAIN, class Fin>
 inline int32_t launch_bf16_net_inst(const Bf16NetArgs& a, const Fin& fin, unsigned* grid_out, hipStream_t s) {
   auto kern = bf16_net_kernel<H, BM, NOUT, TRAIN, Fin>;
@@ -496,8 +512,7 @@ inline int32_t launch_bf16_net_inst(const Bf16NetArgs& a, const Fin& fin, unsign
   if (bytes > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
     return MARL_E_LAUNCH;
-  const int64_t tiles = (a.S + BM - 1) / BM;
-  const unsigned grid = (unsigned)std::min<int64_t>(tiles, BM == 32 ? 2 * bf16_net_grid(H) : bf16_net_grid(H));
+  const unsigned grid = bf16_net_blocks(H, BM, a.S);
   if (grid_out != nullptr) *grid_out = grid;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * Bf16Shape<H, BM>::NW), bytes, s, a, fin);
   return launch_status();
@@ -521,6 +536,38 @@ inline int32_t launch_bf16_forward(int H, const Bf16NetArgs& a, const Fin& fin, 
   TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)a.S * ((double)a.Din * H + (double)H * H), s);
   if (a.S < kBf16SmallRows) return launch_bf16_net_rows<32, NOUT, false>(H, a, fin, nullptr, s);
   return launch_bf16_net_rows<64, NOUT, false>(H, a, fin, nullptr, s);
+}
+// ... of two networks of one width whose tiles have the same height
+inline bool bf16_pair_supported(int Ha, int64_t Sa, int Hb, int64_t Sb) { return Ha == Hb && (Sa < kBf16SmallRows) == (Sb < kBf16SmallRows); }
+template <int H, int BM, int NOUT_A, int NOUT_B, class FinA, class FinB>
+inline int32_t launch_bf16_pair_inst(const Bf16NetArgs& a, const FinA& fa, const Bf16NetArgs& b, const FinB& fb, hipStream_t s) {
+  auto kern = bf16_net_pair_kernel<H, BM, NOUT_A, NOUT_B, FinA, FinB>;
+  const size_t bytes = Bf16Shape<H, BM>::lds(false);
+  if (bytes > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+    return MARL_E_LAUNCH;
+  const unsigned ga = bf16_net_blocks(H, BM, a.S), gb = bf16_net_blocks(H, BM, b.S);
+  hipLaunchKernelGGL(kern, dim3(ga + gb), dim3(64 * Bf16Shape<H, BM>::NW), bytes, s, a, fa, b, fb, ga);
+  return launch_status();
+}
+template <int BM, int NOUT_A, int NOUT_B, class FinA, class FinB>
+inline int32_t launch_bf16_pair_rows(int H, const Bf16NetArgs& a, const FinA& fa, const Bf16NetArgs& b, const FinB& fb, hipStream_t s) {
+  switch (H) {
+    case 64: return launch_bf16_pair_inst<64, BM, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 128: return launch_bf16_pair_inst<128, BM, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 192: return launch_bf16_pair_inst<192, BM, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 256: return launch_bf16_pair_inst<256, BM, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 320: return launch_bf16_pair_inst<320, BM, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 384: return launch_bf16_pair_inst<384, BM, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    case 448: return launch_bf16_pair_inst<448, BM, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+    default: return launch_bf16_pair_inst<512, BM, NOUT_A, NOUT_B>(a, fa, b, fb, s);
+  }
+}
+template <int NOUT_A, int NOUT_B, class FinA, class FinB>
+inline int32_t launch_bf16_forward_pair(int H, const Bf16NetArgs& a, const FinA& fa, const Bf16NetArgs& b, const FinB& fb, hipStream_t s) {
+  TimedLaunch timed(KC_GEMM_NN, 2.0 * (double)a.S * ((double)a.Din * H + (double)H * H) + 2.0 * (double)b.S * ((double)b.Din * H + (double)H * H), s);
+  if (a.S < kBf16SmallRows) return launch_bf16_pair_rows<32, NOUT_A, NOUT_B>(H, a, fa, b, fb, s);
+  return launch_bf16_pair_rows<64, NOUT_A, NOUT_B>(H, a, fa, b, fb, s);
 }
 
 

@@ -17,7 +17,7 @@ int64_t effective_param_floats(const marl_config& c, bool update);
 
 namespace {
 
-__global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int round, int for_rollout, int for_update) {
+__global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int for_rollout, int for_update) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= pm.src[12]) return;
 #pragma unroll
@@ -25,7 +25,17 @@ __global__ void stage_params_kernel(const float* __restrict__ src, float* __rest
     const int H = pm.hidden[net];
     if (pm.fused[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) stage_element(dst, pm, net, pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H, for_rollout != 0);
   }
-  stage_param(dst, pm, i, src[i], round != 0, for_rollout != 0, for_update != 0);
+  stage_param(dst, pm, i, src[i], false, for_rollout != 0, for_update != 0);
+}
+
+// The same for the bf16 configuration, the networks' fragment copies (bf16_stage) in the first `frag_blocks` workgroups of the launch.
+__global__ void __launch_bounds__(256) stage_bf16_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, Bf16StageNet a, Bf16StageNet b, unsigned frag_blocks) {
+  if (blockIdx.x < frag_blocks) {
+    bf16_stage(a, b, (int64_t)blockIdx.x * 256 + threadIdx.x);
+    return;
+  }
+  const int64_t i = (int64_t)(blockIdx.x - frag_blocks) * 256 + threadIdx.x;
+  if (i < pm.src[12]) stage_param(dst, pm, i, src[i], true, false, false);
 }
 
 // What the rollout does with a sample's outputs.
@@ -162,21 +172,31 @@ Bf16NetWeights effective_bf16_weights(const marl_config& c, const float* eff, in
   return Bf16NetWeights{base + ((bf16_net_weight_elems(d.D, d.Ha) + 63) / 64) * 64, (int)round_up64(d.Dc)};
 }
 
-// The bf16 networks' weight copies (nothing for other configurations).
-void stage_bf16_weights(const marl_config& c, const float* params, float* scratch, hipStream_t s) {
+// What the bf16 networks' weight copies are made from.
+std::pair<Bf16StageNet, Bf16StageNet> bf16_stage_nets(const marl_config& c, const float* params, const float* scratch) {
   const Dims d = dims_of(c);
-  if (!d.bf16) return;
   const NetOffsets oa = net_offsets(0, d.D, d.Ha, kActions), oc = net_offsets(d.Pa, d.Dc, d.Hc, 1);
   const Bf16NetWeights wa = effective_bf16_weights(c, scratch, 0), wc = effective_bf16_weights(c, scratch, 1);
-  launch_bf16_stage(Bf16StageNet{params + oa.W1, params + oa.W2, wa.w, d.D, wa.Kp, d.Ha},
-                    Bf16StageNet{params + oc.W1, params + oc.W2, wc.w, d.Dc, wc.Kp, d.Hc}, s);
+  return {Bf16StageNet{params + oa.W1, params + oa.W2, wa.w, d.D, wa.Kp, d.Ha}, Bf16StageNet{params + oc.W1, params + oc.W2, wc.w, d.Dc, wc.Kp, d.Hc}};
+}
+// The copies by themselves (nothing for other configurations).
+void stage_bf16_weights(const marl_config& c, const float* params, float* scratch, hipStream_t s) {
+  if (c.precision != 1) return;
+  const auto nets = bf16_stage_nets(c, params, scratch);
+  launch_bf16_stage(nets.first, nets.second, s);
 }
 
 const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use) {
   const Dims d = dims_of(c);
-  hipLaunchKernelGGL(stage_params_kernel, dim3((unsigned)((d.P + 255) / 256)), dim3(256), 0, s, params, scratch,
-                     param_map(d, use == USE_UPDATE), (int)d.bf16, (int)(use == USE_ROLLOUT && use_fused_rollout(c)), (int)(use == USE_UPDATE));
-  stage_bf16_weights(c, params, scratch, s);
+  const ParamMap pm = param_map(d, use == USE_UPDATE);
+  const unsigned blocks = (unsigned)((d.P + 255) / 256);
+  if (d.bf16) {
+    const auto nets = bf16_stage_nets(c, params, scratch);
+    const unsigned frag = bf16_stage_blocks(nets.first, nets.second);
+    hipLaunchKernelGGL(stage_bf16_params_kernel, dim3(frag + blocks), dim3(256), 0, s, params, scratch, pm, nets.first, nets.second, frag);
+  } else {
+    hipLaunchKernelGGL(stage_params_kernel, dim3(blocks), dim3(256), 0, s, params, scratch, pm, (int)(use == USE_ROLLOUT && use_fused_rollout(c)), (int)(use == USE_UPDATE));
+  }
   return scratch;
 }
 
@@ -201,15 +221,18 @@ static int32_t forward_rows(const marl_config& c, const float* eff, const float*
       a.b1 = eff + o.b1; a.b2 = eff + o.b2; a.W3 = eff + o.W3; a.b3 = eff + o.b3;
       return a;
     };
+    const int64_t Sc = d.central ? n_rows : S;
+    const ActorRolloutFinish fa{logits_out, sample ? *sample : SampleArgs{}, sample ? 1 : 0};
+    const CriticRolloutFinish fc{value_out, d.central ? d.A : 1, value_tail ? value_split : Sc, value_tail};
+    // both in one launch where they take the same kernel: the second network's tiles follow on the compute units as the first one's end
+    if (want_actor && value_out && bf16_pair_supported(d.Ha, S, d.Hc, Sc))
+      return launch_bf16_forward_pair<kActions, 1>(d.Ha, args(0, S, d.D), fa, args(1, Sc, d.Dc), fc, s);
     if (want_actor) {
-      ActorRolloutFinish fin{logits_out, sample ? *sample : SampleArgs{}, sample ? 1 : 0};
-      const int32_t rc = launch_bf16_forward<kActions>(d.Ha, args(0, S, d.D), fin, s);
+      const int32_t rc = launch_bf16_forward<kActions>(d.Ha, args(0, S, d.D), fa, s);
       if (rc != MARL_OK) return rc;
     }
     if (value_out) {
-      const int64_t Sc = d.central ? n_rows : S;
-      CriticRolloutFinish fin{value_out, d.central ? d.A : 1, value_tail ? value_split : Sc, value_tail};
-      const int32_t rc = launch_bf16_forward<1>(d.Hc, args(1, Sc, d.Dc), fin, s);
+      const int32_t rc = launch_bf16_forward<1>(d.Hc, args(1, Sc, d.Dc), fc, s);
       if (rc != MARL_OK) return rc;
     }
     return launch_status();

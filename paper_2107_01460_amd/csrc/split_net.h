@@ -127,7 +127,10 @@ __global__ void __launch_bounds__((64 * SplitNetShape<H, BM>::NW), (SplitNetShap
   if (tid == 0) *inexact = 0;
   if constexpr (TRAIN) {
     if (tid == 0) *prep = fin.prepare();
-    for (int e = tid; e < H * (W3P - NOUT); e += THREADS) w3s[e / (W3P - NOUT) * W3P + NOUT + e % (W3P - NOUT)] = 0.f;
+    if constexpr (W3P > NOUT) {
+      constexpr int PAD = W3P - NOUT;
+      for (int e = tid; e < H * PAD; e += THREADS) w3s[e / PAD * W3P + NOUT + e % PAD] = 0.f;
+    }
     for (int e = tid; e < 24 * PD; e += THREADS) dlt[e] = 0;
     for (int e = tid; e < BM * 8; e += THREADS) dls[e] = 0.f;
     for (int e = tid; e < BM / 16 * AS; e += THREADS) accD[e] = 0.0;
