@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(256, OCC) rollout_eval_kernel(RolloutArgs a) {
   PhaseW<KG1, RING> pw1;
   phase_w_request<H>(pw1, rsW1, wlane, KG1);
   for (int t = 0;; ++t) {
-    __syncthreads();  // the windows of step t are complete
+    loop_head_barrier();  // the windows of step t are complete
     if (__builtin_amdgcn_readfirstlane(*running) == 0) break;  // uniform; written again two barriers from here
     const bf16_t* const Xs = Xs2 + (t & 1) * BM * PX;
     int uw = u0;  // the weights and biases in LDS are read in every step: kept across steps, they would take 96 registers

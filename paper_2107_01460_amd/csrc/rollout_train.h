@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
   PhaseW32<KG1> pw1;
   phase_w32_request<H, KG1>(pw1, rsW1, wlane);
   for (int t = 0;; ++t) {
-    __syncthreads();  // the windows (and the noise) of step t are complete
+    loop_head_barrier();  // the windows (and the noise) of step t are complete
     if (t == a.T) {
       store_slab(t, tid, 256);  // the post-rollout observation
       break;

@@ -74,6 +74,13 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
+// Barrier of a loop's head after LDS writes at the loop's end.  The compiler leaves out the wait for writes that come in over
+// the back edge where other lanes' paths end without one (seen in the listing of the rollouts: ds_write, s_branch, s_barrier),
+// and the other wavefronts could then read an old value: the wait is written out.  A few cycles where nothing is pending.
+__device__ __forceinline__ void loop_head_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __syncthreads();
+}
 // A zero that the compiler does not know
 __device__ __forceinline__ int opaque_zero() {
   int z = 0;
