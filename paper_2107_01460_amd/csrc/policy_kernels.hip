@@ -23,9 +23,9 @@ __global__ void stage_params_kernel(const float* __restrict__ src, float* __rest
 #pragma unroll
   for (int net = 0; net < 2; ++net) {  // zero rows of the copies of W1 (fewer than 32 rows: far fewer floats than parameters)
     const int H = pm.hidden[net];
-    if (pm.fused[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) stage_element(dst, pm, net, pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H, for_rollout != 0);
+    if (pm.fused[net] && i < (int64_t)(pm.kpad1[net] - pm.din[net]) * H) stage_element(dst, pm, net, pm.sw_w1[net], 0.f, pm.din[net] + i / H, i % H, for_rollout);
   }
-  stage_param(dst, pm, i, src[i], false, for_rollout != 0, for_update != 0);
+  stage_param(dst, pm, i, src[i], false, for_rollout, for_update != 0);
 }
 
 // The same for the bf16 configuration, the networks' fragment copies (bf16_stage) in the first `frag_blocks` workgroups of the launch.
@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(256) stage_bf16_params_kernel(const float* __r
     return;
   }
   const int64_t i = (int64_t)(blockIdx.x - frag_blocks) * 256 + threadIdx.x;
-  if (i < pm.src[12]) stage_param(dst, pm, i, src[i], true, false, false);
+  if (i < pm.src[12]) stage_param(dst, pm, i, src[i], true, COPY_SPLIT, false);
 }
 
 // What the rollout does with a sample's outputs.
@@ -195,7 +195,8 @@ const float* effective_params(const marl_config& c, const float* params, float* 
     const unsigned frag = bf16_stage_blocks(nets.first, nets.second);
     hipLaunchKernelGGL(stage_bf16_params_kernel, dim3(frag + blocks), dim3(256), 0, s, params, scratch, pm, nets.first, nets.second, frag);
   } else {
-    hipLaunchKernelGGL(stage_params_kernel, dim3(blocks), dim3(256), 0, s, params, scratch, pm, (int)(use == USE_ROLLOUT && use_fused_rollout(c)), (int)(use == USE_UPDATE));
+    hipLaunchKernelGGL(stage_params_kernel, dim3(blocks), dim3(256), 0, s, params, scratch, pm,
+                       (int)(use != USE_ROLLOUT || !use_fused_rollout(c) ? COPY_SPLIT : rollout_rows(d.Ha, d.A, d.N) == 16 ? COPY_FP32_16 : COPY_FP32), (int)(use == USE_UPDATE));
   }
   return scratch;
 }

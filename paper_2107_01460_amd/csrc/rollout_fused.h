@@ -14,6 +14,16 @@ inline bool rollout_fused_supported(int H, int A) { return (H == 64 || H == 128)
 constexpr int rollout_eval_occupancy(int capacity, int V) { return capacity <= 4 && V <= 5 ? 2 : 1; }
 inline int rollout_eval_places(int H, int A, int F, int V) { return 256 * rollout_eval_occupancy(std::max(A, F), V) * ((H == 64 ? 64 : 32) / A); }
 
+// Samples of a training rollout's tile: 16 while the chip holds all of those workgroups at once (one per CU at 128 units, two
+// at 64), else 64 or 32.  A step is a chain of barriers, reads of weights and dependent sums, shorter in a tile of 16, and the
+// CUs that it takes would stand idle; where they would not, every tile's read of the weights counts.  32 steps, us, tiles of 64
+// or 32 / of 16: 64 units, two agents, view 3: 64 environments 149 / 104, 2048 172 / 126, 4096 194 / 167, 8192 233 / 244,
+// 16384 373 / 463; 128 units, three agents, view 5: 16 environments 245 / 195, 1280 274 / 226, 2048 290 / 308, 4096 466 / 587.
+inline int rollout_rows(int H, int A, int N) {
+  const int64_t groups = ((int64_t)N + 16 / A - 1) / (16 / A);
+  return groups <= (H == 64 ? 512 : 256) ? 16 : H == 64 ? 64 : 32;
+}
+
 template <int H, int BM, int V, int CA, int KIND, bool EVAL>
 inline int32_t launch_rollout_fused_inst(const RolloutArgs& a, hipStream_t s) {
   const int epw = BM / a.p.A;
@@ -25,8 +35,8 @@ inline int32_t launch_rollout_fused_inst(const RolloutArgs& a, hipStream_t s) {
     kern = rollout_eval_kernel<H, BM, V, CA, KIND, rollout_eval_occupancy(CA, V)>;
     bytes = 2 * (size_t)BM * (2 * rollout_eval_px(D) + 3 * (H + 8)) + sizeof(float) * ((H / 32) * kActions * BM + H * kActions + 2 * H + 4);
   } else {
-    kern = rollout_train_kernel<H, BM, V, CA, KIND, ((H == 64 && CA <= 2) || (CA <= 4 && V <= 5)) ? 3 : 1>;
-    bytes = sizeof(float) * (2 * (size_t)BM * rollout_train_px(D) + (size_t)BM * (H + 4) + 256 * kActions + H * kActions + 2 * BM * 8);
+    kern = rollout_train_kernel<H, BM, V, CA, KIND, BM == 16 ? 2 : ((H == 64 && CA <= 2) || (CA <= 4 && V <= 5)) ? 3 : 1>;
+    bytes = sizeof(float) * (2 * (size_t)BM * rollout_train_px(D) + (size_t)BM * (H + 4) + (H / 16) * (size_t)BM * kActions + H * kActions + 2 * BM * 8);
   }
   if (bytes > 64 * 1024 &&
       hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
@@ -35,18 +45,24 @@ inline int32_t launch_rollout_fused_inst(const RolloutArgs& a, hipStream_t s) {
   return launch_status();
 }
 
+template <int H, int V, int CA, int KIND, bool EVAL>
+inline int32_t launch_rollout_fused_rows(const RolloutArgs& a, hipStream_t s) {
+  if constexpr (!EVAL)
+    if (rollout_rows(H, a.p.A, a.p.N) == 16) return launch_rollout_fused_inst<H, 16, V, CA, KIND, false>(a, s);
+  return launch_rollout_fused_inst<H, H == 64 ? 64 : 32, V, CA, KIND, EVAL>(a, s);
+}
 template <int V, int KIND, bool EVAL>
 inline int32_t launch_rollout_fused_view(int H, const RolloutArgs& a, hipStream_t s) {
   const int cap = a.p.A > a.p.F ? a.p.A : a.p.F;  // every loop over entities is unrolled to the capacity
   if constexpr (V == 3 && KIND == 0) {  // the small foraging shape (two agents, one food): half the unrolled entity loops
-    if (cap <= 2 && H == 64) return launch_rollout_fused_inst<64, 64, V, 2, KIND, EVAL>(a, s);
+    if (cap <= 2 && H == 64) return launch_rollout_fused_rows<64, V, 2, KIND, EVAL>(a, s);
   }
   if (H == 64) {
-    if (cap <= 4) return launch_rollout_fused_inst<64, 64, V, 4, KIND, EVAL>(a, s);
-    return launch_rollout_fused_inst<64, 64, V, 8, KIND, EVAL>(a, s);
+    if (cap <= 4) return launch_rollout_fused_rows<64, V, 4, KIND, EVAL>(a, s);
+    return launch_rollout_fused_rows<64, V, 8, KIND, EVAL>(a, s);
   }
-  if (cap <= 4) return launch_rollout_fused_inst<128, 32, V, 4, KIND, EVAL>(a, s);
-  return launch_rollout_fused_inst<128, 32, V, 8, KIND, EVAL>(a, s);
+  if (cap <= 4) return launch_rollout_fused_rows<128, V, 4, KIND, EVAL>(a, s);
+  return launch_rollout_fused_rows<128, V, 8, KIND, EVAL>(a, s);
 }
 
 // Defined in rollout_v3.hip / rollout_v5.hip / rollout_v7.hip (one translation unit per view size).

@@ -69,15 +69,56 @@ __device__ __forceinline__ void gemm_phase_w32(const float* __restrict__ As, flo
   }
 }
 
+// The same for tiles of 16 samples, on v_mfma_f32_16x16x4_f32: NT column tiles of this wavefront, one 16-byte load each per group of 16 along k.  A chain of
+// either instruction is a chain of fused multiply-adds in the order of its k, and the order here is the one above -- k, k + 4, k + 1, k + 5, ... of
+// every eight -- so that a sample's sums have the same bits in tiles of either height.  A lane (quarter q of the wavefront) has k = step16_first(q) + 2 h of eight
+// in the h-th of their two instructions; the weights' copy has those four of every 16 beside one another (rollout_order16).
+__device__ __forceinline__ int step16_first(int q) { return 4 * (q & 1) + (q >> 1); }
+template <int KG, int NT>
+struct PhaseW16 {
+  float4 w[KG][NT];
+};
+template <int LDB, int KG, int NT>
+__device__ __forceinline__ void phase_w16_request(PhaseW16<KG, NT>& pw, WeightRsrc B, int lane_off) {
+#pragma unroll
+  for (int g = 0; g < KG; ++g)
+#pragma unroll
+    for (int c = 0; c < NT; ++c)
+      pw.w[g][c] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(B, lane_off * 4, 16 * g * LDB * 4 + 16 * c * 16, 0));
+}
+// As points at this lane's row, + step16_first(q)
+template <int KG, int NT>
+__device__ __forceinline__ void gemm_phase_w16(const float* __restrict__ As, floatx4 (&acc)[NT], const PhaseW16<KG, NT>& pw) {
+  float av[2][4];
+  auto read = [&](int g) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) av[g & 1][e] = As[16 * g + 8 * (e / 2) + 2 * (e % 2)];
+  };
+  read(0);
+#pragma unroll
+  for (int g = 0; g < KG; ++g) {
+    if (g + 1 < KG) read(g + 1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int c = 0; c < NT; ++c) {
+        const float4 w = pw.w[g][c];
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[g & 1][e], e == 0 ? w.x : e == 1 ? w.y : e == 2 ? w.z : w.w, acc[c], 0, 0, 0);
+      }
+  }
+}
+
 // pitch of a window in LDS, in floats: a multiple of four, with an odd number of 16-byte units
 constexpr int rollout_train_px(int D) { return (D + 15) / 16 * 16 + 4; }
 
 // OCC: workgroups per CU the registers are capped for
 template <int H, int BM, int V, int CA, int KIND, int OCC>
 __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) {
-  constexpr int D = 3 * V * V, PX = rollout_train_px(D), KPAD = (D + 15) / 16 * 16, PH = H + 4, GROUPS = 256 / BM, NOUT = kActions;
-  constexpr int NTN = H / 32, MT = BM / 32, TILES = MT * NTN;
-  static_assert(TILES == 4, "one 32x32 MFMA tile per wavefront");
+  constexpr int D = 3 * V * V, PX = rollout_train_px(D), KPAD = (D + 15) / 16 * 16, PH = H + 4, GROUPS = H / 16, NOUT = kActions;
+  constexpr bool SMALL = BM == 16;  // 16 x 16 tiles, H / 64 per wavefront
+  constexpr int NTN = H / 32, NT16 = H / 64;
+  static_assert(SMALL || BM / 32 * NTN == 4, "one 32x32 MFMA tile per wavefront");
+  static_assert(SMALL || GROUPS == 256 / BM, "one thread per sample and share of 16 units");
   extern __shared__ __attribute__((aligned(16))) float lds[];
   float* const Xs2 = lds;                      // [2][BM][PX]  observation windows of two consecutive steps, k-contiguous;
                                                //              columns D .. PX stay zero
@@ -89,6 +130,7 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo = lane & 31, hi = lane >> 5;
   const int mt = wave / NTN, nt = wave % NTN;
+  const int l15 = lane & 15, l4 = lane >> 4;
   RolloutEnvs<BM, V, CA, KIND> env(a, wave, lane);
   const int64_t NA = (int64_t)a.p.N * a.p.A;
   // ---- the other three wavefronts draw the sampling noise of the NEXT step while the env lanes work: it depends on
@@ -126,7 +168,14 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
   if (env.active) env.paint(Xs2 + lane * PX);
   if (a.T > 0) draw_noise(0);
   // the biases of this lane's column and of the output layer stay in registers for all T steps
-  const float bias1 = a.b1[nt * 32 + lo], bias2 = a.b2[nt * 32 + lo];
+  constexpr int NB = SMALL ? NT16 : 1;
+  float bias1[NB], bias2[NB];
+#pragma unroll
+  for (int c = 0; c < NB; ++c) {
+    const int n = SMALL ? 16 * (wave * NT16 + c) + l15 : nt * 32 + lo;
+    bias1[c] = a.b1[n];
+    bias2[c] = a.b2[n];
+  }
   float b3r[NOUT];
 #pragma unroll
   for (int k = 0; k < NOUT; ++k) b3r[k] = a.b3[k];
@@ -144,10 +193,45 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
 
   // the weights of a whole layer are requested a phase ahead (buffer loads: one descriptor, one lane offset)
   constexpr int KG1 = KPAD / 16, KG2 = H / 16;
-  const int wlane = (hi * H + nt * 32 + lo) * 4;
+  const int wlane = SMALL ? (l4 * H + 16 * wave * NT16 + l15) * 4 : (hi * H + nt * 32 + lo) * 4;
   const WeightRsrc rsW1 = weight_rsrc(a.W1, KPAD * H), rsW2 = weight_rsrc(a.W2, H * H);
-  PhaseW32<KG1> pw1;
-  phase_w32_request<H, KG1>(pw1, rsW1, wlane);
+  std::conditional_t<SMALL, PhaseW16<KG1, NT16>, PhaseW32<KG1>> pw1;
+  std::conditional_t<SMALL, PhaseW16<KG2, NT16>, PhaseW32<KG2>> pw2;
+  auto request1 = [&]() {
+    if constexpr (SMALL) phase_w16_request<H>(pw1, rsW1, wlane);
+    else phase_w32_request<H, KG1>(pw1, rsW1, wlane);
+  };
+  auto request2 = [&]() {
+    if constexpr (SMALL) phase_w16_request<H>(pw2, rsW2, wlane);
+    else phase_w32_request<H, KG2>(pw2, rsW2, wlane);
+  };
+  floatx16 acc;
+  floatx4 acc16[NT16];
+  // this wavefront's part of A (rows of pitch `pitch`) times the weights in pw
+  auto product = [&](const float* A, int pitch, const auto& pw) {
+    if constexpr (SMALL) {
+#pragma unroll
+      for (int c = 0; c < NT16; ++c) acc16[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+      gemm_phase_w16(A + l15 * pitch + step16_first(l4), acc16, pw);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+      gemm_phase_w32(A + (mt * 32 + lo) * pitch + 4 * hi, acc, pw);
+    }
+  };
+  auto store_tanh = [&](const float (&bias)[NB]) {  // -> Hs
+    if constexpr (SMALL) {
+#pragma unroll
+      for (int c = 0; c < NT16; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) Hs[(4 * l4 + r) * PH + 16 * (wave * NT16 + c) + l15] = tanh_f32(acc16[c][r] + bias[c]);
+    } else {
+      const int col = nt * 32 + lo;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) Hs[(mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4)) * PH + col] = tanh_f32(acc[r] + bias[0]);
+    }
+  };
+  request1();
   for (int t = 0;; ++t) {
     loop_head_barrier();  // the windows (and the noise) of step t are complete
     if (t == a.T) {
@@ -156,61 +240,54 @@ __global__ void __launch_bounds__(256, OCC) rollout_train_kernel(RolloutArgs a) 
     }
     const float* const Xs = Xs2 + (t & 1) * BM * PX;
     // ---- layer 1: h1 = tanh(X W1 + b1) -> LDS
-    floatx16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    gemm_phase_w32<KG1>(Xs + (mt * 32 + lo) * PX + 4 * hi, acc, pw1);
-    PhaseW32<KG2> pw2;  // layer 2's weights arrive during the tanh of layer 1
-    phase_w32_request<H, KG2>(pw2, rsW2, wlane);
-    {
-      const int col = nt * 32 + lo;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        Hs[m * PH + col] = tanh_f32(acc[r] + bias1);
-      }
-    }
+    product(Xs, PX, pw1);
+    request2();  // layer 2's weights arrive during the tanh of layer 1
+    store_tanh(bias1);
     __syncthreads();  // h1 complete; every wavefront is past its reads of the windows
     // ---- layer 2: h2 = tanh(h1 W2 + b2)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    gemm_phase_w32<KG2>(Hs + (mt * 32 + lo) * PH + 4 * hi, acc, pw2);
-    phase_w32_request<H, KG1>(pw1, rsW1, wlane);  // layer 1 of the next step
+    product(Hs, PH, pw2);
+    request1();  // layer 1 of the next step
     __syncthreads();  // every wavefront is past its last read of h1
-    {
-      const int col = nt * 32 + lo;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mt * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
-        Hs[m * PH + col] = tanh_f32(acc[r] + bias2);
-      }
-    }
+    store_tanh(bias2);
     __syncthreads();
-    // ---- output layer on the ALUs: thread -> (sample tid % BM, slice tid / BM of the hidden units)
+    // ---- output layer on the ALUs: thread -> (sample tid % BM, 16 of the hidden units and, in small tiles, some of the outputs)
     {
-      const int s = tid % BM, grp = tid / BM;
-      constexpr int PER = H / GROUPS;
-      static_assert(PER % 4 == 0, "hidden units are read four at a time");
-      float part[NOUT];
+      constexpr int SPLIT = !SMALL ? 1 : GROUPS == 8 ? 2 : 3, KO = NOUT / SPLIT, PER = 16;
+      const int s = tid % BM, grp = tid / BM % GROUPS, k0 = tid / (BM * GROUPS) * KO;
+      if (!SMALL || k0 < NOUT) {
+        float part[KO];
 #pragma unroll
-      for (int k = 0; k < NOUT; ++k) part[k] = 0.f;
+        for (int k = 0; k < KO; ++k) part[k] = 0.f;
 #pragma unroll 2
-      for (int i = grp * PER; i < (grp + 1) * PER; i += 4) {
-        const float4 hv = *reinterpret_cast<const float4*>(&Hs[s * PH + i]);
-        const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
-        float wv[4 * NOUT];
+        for (int i = grp * PER; i < (grp + 1) * PER; i += 4) {
+          const float4 hv = *reinterpret_cast<const float4*>(&Hs[s * PH + i]);
+          const float hh[4] = {hv.x, hv.y, hv.z, hv.w};
+          float wv[4 * KO];
+          if constexpr (!SMALL) {
 #pragma unroll
-        for (int q = 0; q < NOUT; ++q) {
-          const float4 w4 = *reinterpret_cast<const float4*>(&W3s[i * NOUT + 4 * q]);
-          wv[4 * q] = w4.x; wv[4 * q + 1] = w4.y; wv[4 * q + 2] = w4.z; wv[4 * q + 3] = w4.w;
+            for (int q = 0; q < KO; ++q) {
+              const float4 w4 = *reinterpret_cast<const float4*>(&W3s[i * NOUT + 4 * q]);
+              wv[4 * q] = w4.x; wv[4 * q + 1] = w4.y; wv[4 * q + 2] = w4.z; wv[4 * q + 3] = w4.w;
+            }
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int k = 0; k < KO; ++k) wv[j * KO + k] = W3s[(i + j) * NOUT + k0 + k];
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int k = 0; k < KO; ++k) part[k] = fmaf(hh[j], wv[j * KO + k], part[k]);
         }
+        if constexpr (!SMALL) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+          for (int k = 0; k < NOUT; k += 2) *reinterpret_cast<float2*>(&red[(grp * BM + s) * NOUT + k]) = make_float2(part[k], part[k + 1]);
+        } else {
 #pragma unroll
-          for (int k = 0; k < NOUT; ++k) part[k] = fmaf(hh[j], wv[j * NOUT + k], part[k]);
+          for (int k = 0; k < KO; ++k) red[(grp * BM + s) * NOUT + k0 + k] = part[k];
+        }
       }
-#pragma unroll
-      for (int k = 0; k < NOUT; k += 2) *reinterpret_cast<float2*>(&red[(grp * BM + s) * NOUT + k]) = make_float2(part[k], part[k + 1]);
     }
     __syncthreads();
     if (!env.is_env_wave) {

@@ -13,14 +13,23 @@ __device__ __forceinline__ void store_split_weight(float* copy, float v, int64_t
   d[split_weight_plane(H)] = (bf16_t)s.m;
   d[2 * split_weight_plane(H)] = (bf16_t)s.l;
 }
-// element (k, n) of a copy of network `net`; for_rollout: the actor's in fp32
-__device__ __forceinline__ void stage_element(float* dst, const ParamMap& pm, int net, int64_t copy, float v, int64_t k, int64_t n, bool for_rollout) {
+// What a working copy's actor is in.
+enum RolloutCopy { COPY_SPLIT, COPY_FP32, COPY_FP32_16 };  // split; fp32 for a training rollout in tiles of 32 or 64 samples, of 16
+// Where row k of a weight matrix stands for tiles of 16 samples: of every sixteen, quarter q of a wavefront takes k = 4 (q % 2) + q / 2 + 2 h of
+// either eight, its four values beside one another.
+__host__ __device__ inline int64_t rollout_order16(int64_t k) {
+  const int64_t q = (k & 1) << 1 | (k >> 2 & 1), e = (k >> 3 & 1) << 1 | (k >> 1 & 1);
+  return (k & ~(int64_t)15) | q << 2 | e;
+}
+// element (k, n) of a copy of network `net`
+__device__ __forceinline__ void stage_element(float* dst, const ParamMap& pm, int net, int64_t copy, float v, int64_t k, int64_t n, int for_rollout) {
   const int H = pm.hidden[net];
-  if (for_rollout && net == 0) dst[copy + ((k / 4) * H + n) * 4 + k % 4] = v;
+  if (for_rollout == COPY_FP32_16 && net == 0) k = rollout_order16(k);
+  if (for_rollout != COPY_SPLIT && net == 0) dst[copy + ((k / 4) * H + n) * 4 + k % 4] = v;
   else store_split_weight(dst + copy, v, k, n, H);
 }
 // parameter i, of value v
-__device__ __forceinline__ void stage_param(float* dst, const ParamMap& pm, int64_t i, float v, bool round, bool for_rollout, bool for_update) {
+__device__ __forceinline__ void stage_param(float* dst, const ParamMap& pm, int64_t i, float v, bool round, int for_rollout, bool for_update) {
   int b = 0;
 #pragma unroll
   for (int k = 1; k < 12; ++k) b += (i >= pm.src[k]) ? 1 : 0;
