@@ -249,6 +249,9 @@ __device__ __forceinline__ void gemm_phase_t(const bf16_t* xs, int plane, Weight
 // networks run layer by layer (147-256-6 and 147-192-1, 250 000 samples) 27.1 -> 19.9 ms.  The check for NaNs at the end of a
 // tile (values out of split_pair's range) costs 1 %.  Requesting a k tile two tiles ahead instead of one changed nothing at 128 columns
 // and cost 40 % at 64: the loads are not what a k tile waits for.
+// Tiles of 192 columns (NN, TN): a wavefront's 64 x 96 part reads 15 fragments for 36 matrix instructions' worth of sums where 64 x 64 reads
+// 12 for 24, and every value of A is split for 192 products in place of 128: 256 x 768 over 262 144 samples with its copies' sums
+// 629 -> 536 us, 128 x 384 over 1 048 576 703 -> 603, 262 144 x 768 x 256 forward 667 -> 604, 262 144 x 192 x 147 176 -> 141.
 template <int MODE, int EPI, int BM, int BN, bool AVEC>
 __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   constexpr int BK = kGemmBK;
@@ -261,6 +264,7 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   constexpr int A_PLANE = A_KCONT ? BM * PK : BK * PMA, B_PLANE = B_KCONT ? BN * PK : BK * PNB;
   constexpr int A_VECS = BK * BM / 4 / 256, B_VECS = BK * BN / 4 / 256;  // 16-byte pieces a thread stages
   static_assert(A_VECS >= 1 && B_VECS >= 1, "every thread stages");
+  constexpr int BCH = BN == 192 ? 3 : 1, BPC = BN / 4 / BCH;  // a thread's pieces of B (b_row, b_col) lie in BCH places of a row throughout
   __shared__ __attribute__((aligned(16))) bf16_t As[3 * A_PLANE];
   __shared__ __attribute__((aligned(16))) bf16_t Bs[3 * B_PLANE];
 
@@ -300,6 +304,8 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
       for (int p = 0; p < A_VECS; ++p) entry[p] = g.A.gather[min(q[p], q_last)];
     }
   };
+  auto b_row = [&](int p) { return tid / BPC + p / BCH * (256 / BPC); };  // of a tile of B in rows of k
+  auto b_col = [&](int p) { return 4 * (tid % BPC + p % BCH * BPC); };
   auto fetch = [&](int64_t k0) {
     if (A_KCONT) {
       const int64_t k = k0 + 4 * (tid & 7);
@@ -351,7 +357,7 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
         const int64_t k = k0 + 4 * (f & 7), n = n0 + (f >> 3);
         rb[p] = *reinterpret_cast<const float4*>(g.B + min(n, g.N - 1) * g.ldb + min(k, k_end - 4));
       } else {
-        const int64_t k = k0 + f / (BN / 4), n = n0 + 4 * (f % (BN / 4));
+        const int64_t k = k0 + b_row(p), n = n0 + b_col(p);
         const float4 v = *reinterpret_cast<const float4*>(g.B + min(k, k_end - 1) * g.ldb + min(n, g.N - 4));
         rb[p] = k < k_end ? v : make_float4(0.f, 0.f, 0.f, 0.f);
       }
@@ -373,12 +379,12 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
 #pragma unroll
     for (int p = 0; p < B_VECS; ++p) {
       const int f = tid + 256 * p;
-      store_split4<ANY>(B_KCONT ? &Bs[(f >> 3) * PK + 4 * (f & 7)] : &Bs[(f / (BN / 4)) * PNB + 4 * (f % (BN / 4))], B_PLANE, rb[p]);
+      store_split4<ANY>(B_KCONT ? &Bs[(f >> 3) * PK + 4 * (f & 7)] : &Bs[b_row(p) * PNB + b_col(p)], B_PLANE, rb[p]);
     }
   };
 
   // TN: column sums of B (the bias gradient) ride along: each thread adds up the values it stages
-  float4 bsum;
+  float4 bsum[BCH];
   const bool want_bsum = MODE == GEMM_TN && g.colsum != nullptr && bx == 0;
 
   floatx16 acc[TM][TN];
@@ -402,7 +408,8 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
       for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    bsum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int c = 0; c < BCH; ++c) bsum[c] = make_float4(0.f, 0.f, 0.f, 0.f);
     fetch_entries();
     fetch(kb);
     for (int64_t k0 = kb; k0 < k_end; k0 += BK) {
@@ -410,7 +417,8 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
       if (MODE == GEMM_TN && want_bsum) {
 #pragma unroll
         for (int p = 0; p < B_VECS; ++p) {
-          bsum.x += rb[p].x; bsum.y += rb[p].y; bsum.z += rb[p].z; bsum.w += rb[p].w;
+          float4& t = bsum[p % BCH];
+          t.x += rb[p].x; t.y += rb[p].y; t.z += rb[p].z; t.w += rb[p].w;
         }
       }
       __syncthreads();
@@ -441,18 +449,20 @@ __global__ void __launch_bounds__(256, 2) gemm_split_kernel(GemmArgs g) {
   if (__builtin_expect(any_in_workgroup(all != all), 0)) multiply(std::true_type{});
 
   if (MODE == GEMM_TN && want_bsum) {
-    // threads with equal tid % (BN/4) hold partial sums of the same four columns: combine them through LDS
+    // threads with equal tid % BPC hold partial sums of the same columns: combine them through LDS
     float4* red = reinterpret_cast<float4*>(Bs);  // the tile is no longer needed (the loop ended with a barrier)
-    static_assert(B_PLANE * 3 * 2 >= 256 * 16, "room for the partial column sums");
-    red[tid] = bsum;
+    static_assert(B_PLANE * 3 * 2 >= 256 * 16 * BCH, "room for the partial column sums");
+#pragma unroll
+    for (int c = 0; c < BCH; ++c) red[256 * c + tid] = bsum[c];
     __syncthreads();
-    constexpr int GROUPS = 256 / (BN / 4);
+    constexpr int GROUPS = 256 / BPC;
     if (tid < BN / 4 && n0 + 4 * tid < g.N) {
       const int64_t n = n0 + 4 * tid + g.c_rot, nd = n < g.N ? n : n - g.N;
-      float4 t = red[tid];
+      const float4* const mine = red + 256 * (tid / BPC) + tid % BPC;
+      float4 t = mine[0];
 #pragma unroll
       for (int u = 1; u < GROUPS; ++u) {
-        const float4 o = red[tid + u * (BN / 4)];
+        const float4 o = mine[u * BPC];
         t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
       }
       if (g.split_out != nullptr) {  // this k split's column sums, directly behind its copy of C
@@ -523,6 +533,17 @@ inline void launch_gemm_inst(const GemmArgs& g, bool avec, hipStream_t s) {
   if (avec) hipLaunchKernelGGL((gemm_split_kernel<MODE, EPI, BM, BN, true>), dim3(blocks), dim3(256), 0, s, g);
   else hipLaunchKernelGGL((gemm_split_kernel<MODE, EPI, BM, BN, false>), dim3(blocks), dim3(256), 0, s, g);
 }
+// Tiles of 192 columns for an NN product, by the rounds of 512 workgroups that either width takes: a round of 192 columns costs 1.39 of 128 and
+// a round of 64 columns 0.57; one of up to 256 workgroups, one per CU, three quarters of a full one.  135 products of 1024 .. 262 144
+// rows x 192 .. 960 columns: those chosen take 0.75 .. 1.01 of the other width's time; of those left out 1.05 .. 2 times it up to
+// 8192 rows (3072 x 384 x 128 13.2 us, 192 columns 17.3), 1.05 .. 0.96 above (50 000 x 384 x 128 42.0, 44.2).
+inline bool nn_wide(int64_t M, int64_t N) {
+  if (N % 192 != 0) return false;
+  const int64_t rows = (M + 127) / 128;
+  auto rounds = [](int64_t tiles) { return (double)(tiles / 512) + (tiles % 512 == 0 ? 0.0 : tiles % 512 <= 256 ? 0.75 : 1.0); };
+  const double other = N % 128 == 0 ? rounds(rows * (N / 128)) : 0.57 * rounds(rows * (N / 64));
+  return 1.39 * rounds(rows * (N / 192)) < other;
+}
 template <int MODE, int EPI>
 inline bool launch_gemm(const GemmArgs& g_in, hipStream_t s) {
   GemmArgs g = g_in;
@@ -534,7 +555,8 @@ inline bool launch_gemm(const GemmArgs& g_in, hipStream_t s) {
   if constexpr (MODE == GEMM_TN) {
     const TnPlan p = tn_plan(M, N, g.K);
     g.k_per_split = p.per;
-    if (p.bm == 32) launch_gemm_inst<MODE, EPI, 32, 128>(g, avec, s);
+    if (p.wide) launch_gemm_inst<MODE, EPI, 128, 192>(g, avec, s);
+    else if (p.bm == 32) launch_gemm_inst<MODE, EPI, 32, 128>(g, avec, s);
     else if (p.bm == 96) launch_gemm_inst<MODE, EPI, 96, 128>(g, avec, s);
     else if (p.bm == 160) launch_gemm_inst<MODE, EPI, 160, 128>(g, avec, s);
     else if (p.bn == 128) launch_gemm_inst<MODE, EPI, 128, 128>(g, avec, s);
@@ -542,6 +564,12 @@ inline bool launch_gemm(const GemmArgs& g_in, hipStream_t s) {
     return g.split_out != nullptr;
   }
   // 64 columns where 128 would leave a half-empty last tile
+  if constexpr (MODE == GEMM_NN) {
+    if (nn_wide(M, N)) {
+      launch_gemm_inst<MODE, EPI, 128, 192>(g, avec, s);
+      return false;
+    }
+  }
   if (N % 128 == 0) launch_gemm_inst<MODE, EPI, 128, 128>(g, avec, s);
   else launch_gemm_inst<MODE, EPI, 128, 64>(g, avec, s);
   return g.split_out != nullptr;

@@ -11,6 +11,7 @@ struct TnPlan {
   int bm, bn;         // output tile
   int64_t per;        // samples of a k range, a multiple of kGemmBK
   int64_t splits;     // k ranges: each writes its own copy of the M x N outputs and the N column sums
+  bool wide = false;  // tiles of 192 columns, two in place of three of bn = 128
 };
 
 // What a tile costs, in us (MI355X, product and reduction of its copies; 368 shapes of 27 .. 1176 x 32 .. 1536 outputs over 256 ..
@@ -66,7 +67,18 @@ inline TnPlan tn_plan(int64_t M, int64_t N, int64_t K) {
       least = cost;
     }
   }
-  return tn_ranges(best->bm, best->bn, M, N, K);
+  TnPlan p = tn_ranges(best->bm, best->bn, M, N, K);
+  // Where 128 x 128 tiles are the choice, whole tiles of 192 columns fit and the ranges of 512 workgroups of them have at least kTnMinRange
+  // samples: us with the sums of the copies, 128 / 192 columns: 128 x 384 over 98 304 samples 79.4 / 75.0, 1 048 576 702.9 / 602.7; 256 x 768
+  // over 16 384 60.4 / 56.1, 262 144 628.7 / 535.7; 512 x 1536 over 4096 61.8 / 56.3; below the line 128 x 384 over 49 152 51.6 / 53.1.
+  const int64_t tiles = ((M + 127) / 128) * (N / 192);
+  if (p.bm == 128 && p.bn == 128 && N % 384 == 0 && (double)K * (double)tiles >= (double)(2 * kTnCus * kTnMinRange)) {
+    const int64_t want = std::max<int64_t>(1, 2 * kTnCus / tiles);
+    p.per = std::max<int64_t>(kTnMinRange, ((K + want - 1) / want + kGemmBK - 1) / kGemmBK * kGemmBK);
+    p.splits = (K + p.per - 1) / p.per;
+    p.wide = true;
+  }
+  return p;
 }
 // floats of the copies of a product
 inline int64_t tn_copy_floats(int64_t M, int64_t N, int64_t K) { return tn_plan(M, N, K).splits * (M * N + N); }
