@@ -68,11 +68,13 @@ inline TnPlan tn_plan(int64_t M, int64_t N, int64_t K) {
     }
   }
   TnPlan p = tn_ranges(best->bm, best->bn, M, N, K);
-  // Where 128 x 128 tiles are the choice, whole tiles of 192 columns fit and the ranges of 512 workgroups of them have at least kTnMinRange
-  // samples: us with the sums of the copies, 128 / 192 columns: 128 x 384 over 98 304 samples 79.4 / 75.0, 1 048 576 702.9 / 602.7; 256 x 768
-  // over 16 384 60.4 / 56.1, 262 144 628.7 / 535.7; 512 x 1536 over 4096 61.8 / 56.3; below the line 128 x 384 over 49 152 51.6 / 53.1.
+  // Where 128 x 128 tiles are the choice, whole tiles of 192 columns fit and the ranges of 512 workgroups of them have at least 512
+  // samples: us with the sums of the copies, 128 / 192 columns: 128 x 384 over 262 144 samples 175.3 / 164.6, 1 048 576 702.9 / 602.7; 256 x 768
+  // over 49 152 138.1 / 118.6, 262 144 628.7 / 535.7; 512 x 1536 over 16 384 178.1 / 145.2.  Shorter ranges win alone from 256 samples on (128 x 384 over
+  // 98 304 79.4 / 75.0) but lose beside another network's kernels, to which half as many copies again are in the way: a recurrent
+  // iteration of 1024 environments, 128 units, 24.4 ms without them and 25.3 with.
   const int64_t tiles = ((M + 127) / 128) * (N / 192);
-  if (p.bm == 128 && p.bn == 128 && N % 384 == 0 && (double)K * (double)tiles >= (double)(2 * kTnCus * kTnMinRange)) {
+  if (p.bm == 128 && p.bn == 128 && N % 384 == 0 && (double)K * (double)tiles >= (double)(4 * kTnCus * kTnMinRange)) {
     const int64_t want = std::max<int64_t>(1, 2 * kTnCus / tiles);
     p.per = std::max<int64_t>(kTnMinRange, ((K + want - 1) / want + kGemmBK - 1) / kGemmBK * kGemmBK);
     p.splits = (K + p.per - 1) / p.per;

@@ -14,9 +14,9 @@ from gpu_util import dev, rel_err
 pytestmark = pytest.mark.gpu
 
 
-# 32 700 x 384 outputs in 512 workgroups and a 384 x 384 gradient in ranges of 416 samples, the last ragged (layer by layer); 98 175 x 384
-# gates, their 128 x 384 gradients; 24 540 x 768 gates, 256 x 768 gradients
-@pytest.mark.parametrize("recurrent,units,n_envs,T,parts", [(0, 384, 2180, 5, 4), (1, 128, 2975, 11, 5), (1, 256, 1636, 5, 4)])
+# 43 695 x 384 outputs and a 384 x 384 gradient in ranges of 544 samples, the last ragged (layer by layer); 131 076 x 384 gates, their 128 x 384
+# gradients, at their line; 49 140 x 768 gates, 256 x 768 gradients
+@pytest.mark.parametrize("recurrent,units,n_envs,T,parts", [(0, 384, 2913, 5, 3), (1, 128, 3972, 11, 12), (1, 256, 3276, 5, 6)])
 def test_one_minibatch_against_its_parts(recurrent, units, n_envs, T, parts):
     import paper_2107_01460_amd as M
     cfg = W.scaled(W.CONFIGS[1], view=3, n_envs=n_envs, rollout_len=T, actor_hidden=units, critic_hidden=units, episode_cap=4, n_epochs=1,
