@@ -55,9 +55,11 @@ struct SeqRuns {
   const int* count;
   int* next;  // counter of the groups taken, zero before the launch
 };
-// The next group of MT sequences of a workgroup (whole workgroup, uniform); false: none is left.
+// The next group of MT sequences of a workgroup (whole workgroup, uniform); false: none is left.  The first barrier keeps a wavefront that is through with
+// a group from overwriting the slot before the others have read it: a backward group of one-step runs has no other barrier.
 template <int MT>
 __device__ __forceinline__ bool next_group(const SeqRuns& runs, int per, int* slot, int& first, int& total) {
+  lds_barrier();
   if (threadIdx.x == 0) *slot = atomicAdd(runs.next, 1);
   __syncthreads();
   first = __builtin_amdgcn_readfirstlane(*slot) * MT;
