@@ -153,35 +153,38 @@ __global__ void __launch_bounds__(256) gru_backward_kernel(const float* __restri
   dhprev[i] = dh * z;
 }
 
-// Index arrays of the minibatches of sequences of an update, blockIdx.y-th minibatch: row r = t * J + j is trajectory row t * N + envs[j]; reset[r] = the step before t
+// Index arrays of the next minibatches of sequences of an update, blockIdx.y-th of them: row r = t * J + j is trajectory row t * N + envs[j]; reset[r] = the step before t
 // ended the episode of that environment (never at t = 0); hrows[r] = the state row that step t starts from, r, or the row of
 // zeros behind the T + 1 slabs.  And its runs (SeqRuns), the longest first, in no order among those of one length (a run's results do not
 // depend on which others it shares a workgroup with): the first pass counts them by length, the second one places them.
 // One thread per sequence, sixteen steps requested at a time; a workgroup's counts meet in LDS, so that a few atomics per workgroup remain.
 constexpr int kRunBins = 1024;  // lengths from here on count as one
 constexpr int kRunHead = 16;    // ints before a minibatch's bins: number of runs, groups taken by each of its four kernels
+// Minibatches planned at once: an epoch's, so that two launches serve them all, but no more than these, so that the room for plans grows neither
+// with the epochs nor with their minibatches.
+constexpr int kPlanned = 32;
 struct SeqPlanArgs {
-  const int32_t* envs;  // [E][N], nullable: the identity
+  const int32_t* envs;  // [N] the epoch's order, nullable: the identity
   const uint8_t* done;  // [T][N]
-  int J, N, T, M;       // M minibatches per epoch
-  int32_t *rows, *hrows;  // [E * M][T * J]
+  int J, N, T;
+  int first;            // minibatch of the epoch that is the plan's first
+  int32_t *rows, *hrows;  // [minibatch of the plan][T * J]
   uint8_t* reset;
   int2* runs;
-  int32_t* head;        // [E * M][run_head_ints(T)], zero before the first pass
-  int q0;               // the first of this launch
+  int32_t* head;        // [minibatch of the plan][run_head_ints(T)], zero before the first pass
 };
 __host__ __device__ inline int run_bins(int T) { return T < kRunBins ? T : kRunBins; }
 __host__ __device__ inline int64_t run_head_ints(int T) { return (kRunHead + 2 * (int64_t)run_bins(T) + 3) / 4 * 4; }
 template <bool PLACE>
 __global__ void __launch_bounds__(256) seq_plan_kernel(SeqPlanArgs a) {
   __shared__ int32_t bin[kRunBins], at[kRunBins];
-  const int tid = threadIdx.x, j = blockIdx.x * 256 + tid, q = a.q0 + blockIdx.y, B = run_bins(a.T);
+  const int tid = threadIdx.x, j = blockIdx.x * 256 + tid, q = blockIdx.y, B = run_bins(a.T);
   const int64_t TJ = (int64_t)a.T * a.J;
   int32_t* const head = a.head + q * run_head_ints(a.T);
   int32_t *const count = head + kRunHead, *const taken = count + B;  // by length, B first
   for (int b = tid; b < B; b += 256) bin[b] = 0;
   __syncthreads();
-  const int env = j >= a.J ? 0 : a.envs != nullptr ? a.envs[(int64_t)(q / a.M) * a.N + (int64_t)(q % a.M) * a.J + j] : q % a.M * a.J + j;
+  const int place = j >= a.J ? 0 : (a.first + q) * a.J + j, env = a.envs != nullptr ? a.envs[place] : place;
   // visits the runs of this thread's sequence
   auto runs = [&](auto&& run) {
     if (j >= a.J) return;
@@ -232,13 +235,10 @@ __global__ void __launch_bounds__(256) seq_plan_kernel(SeqPlanArgs a) {
   runs([&](int begin, int len) { a.runs[q * TJ + atomicAdd(&at[B - min(len, B)], 1)] = make_int2(begin * a.J + j, len); });
 }
 
-void launch_seq_plan(SeqPlanArgs a, int minibatches, hipStream_t s) {
-  constexpr int kMost = 32768;  // of one launch
-  for (a.q0 = 0; a.q0 < minibatches; a.q0 += kMost) {
-    const dim3 grid((unsigned)((a.J + 255) / 256), (unsigned)std::min(kMost, minibatches - a.q0));
-    hipLaunchKernelGGL(seq_plan_kernel<false>, grid, dim3(256), 0, s, a);
-    hipLaunchKernelGGL(seq_plan_kernel<true>, grid, dim3(256), 0, s, a);
-  }
+void launch_seq_plan(const SeqPlanArgs& a, int minibatches, hipStream_t s) {
+  const dim3 grid((unsigned)((a.J + 255) / 256), (unsigned)minibatches);
+  hipLaunchKernelGGL(seq_plan_kernel<false>, grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL(seq_plan_kernel<true>, grid, dim3(256), 0, s, a);
 }
 
 // dst[(j * per + a)][u] = h0[(envs[j] * per + a)][u]; zeros[0 .. per * H - 1] = 0
@@ -518,7 +518,7 @@ struct RecNetWs {
 struct RecUpdateWs {
   float *eff, *grad;
   Scalars* sc;
-  SeqPlanArgs plan;  // of all minibatches
+  SeqPlanArgs plan;
   RecNetWs net[2];  // actor, critic: a set each, so that the two networks can run side by side
 };
 
@@ -539,13 +539,13 @@ RecUpdateWs carve_rec_update(const marl_config& c, void* ws, int64_t* total) {
   w.grad = (float*)take(d.P * 4);
   w.sc = (Scalars*)take(sizeof(Scalars));
   w.plan = SeqPlanArgs{};
-  w.plan.J = (int)J; w.plan.N = d.N; w.plan.T = d.T; w.plan.M = c.n_minibatches;
-  const int64_t EM = (int64_t)c.n_epochs * c.n_minibatches;
-  w.plan.rows = (int32_t*)take(EM * TJ * 4);
-  w.plan.hrows = (int32_t*)take(EM * TJ * 4);
-  w.plan.reset = (uint8_t*)take(EM * TJ);
-  w.plan.runs = (int2*)take(EM * TJ * 8);
-  w.plan.head = (int32_t*)take(EM * run_head_ints(d.T) * 4);
+  w.plan.J = (int)J; w.plan.N = d.N; w.plan.T = d.T;
+  const int64_t planned = std::min(c.n_minibatches, kPlanned);
+  w.plan.rows = (int32_t*)take(planned * TJ * 4);
+  w.plan.hrows = (int32_t*)take(planned * TJ * 4);
+  w.plan.reset = (uint8_t*)take(planned * TJ);
+  w.plan.runs = (int2*)take(planned * TJ * 8);
+  w.plan.head = (int32_t*)take(planned * run_head_ints(d.T) * 4);
   for (int k = 0; k < 2; ++k) {
     const int64_t SH = k == 0 ? Sa * d.Ha : Sc * d.Hc, S1H = k == 0 ? S1a * d.Ha : S1c * d.Hc;
     const int H = k == 0 ? d.Ha : d.Hc;
@@ -622,22 +622,24 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
   const RecParamMap pm = rec_param_map(d);
   const RecOffsets oa = rec_padded(pm, 0), oc = rec_padded(pm, 1);
   const SideStream* const side = side_stream();
-  const int EM = c.n_epochs * c.n_minibatches;
   SeqPlanArgs plan = w.plan;
-  plan.envs = perm;
   plan.done = tr.done;
   int64_t k = adam_step0;
   for (int e = 0; e < c.n_epochs; ++e) {
     for (int mb = 0; mb < c.n_minibatches; ++mb) {
-      const int q = e * c.n_minibatches + mb;
+      const int q = mb % kPlanned;
       int32_t *const rows = w.plan.rows + q * TJ, *const hrows = w.plan.hrows + q * TJ, *const head = w.plan.head + q * run_head_ints(d.T);
       const uint8_t* const reset = w.plan.reset + q * TJ;
       const SeqRuns runs_a{w.plan.runs + q * TJ, head, head + 4}, runs_c{w.plan.runs + q * TJ, head, head + 8};
       const float* eff = stage_params(d, params, w.eff, s);
-      const bool first = q == 0;  // clears the heads of all minibatches' plans too
-      hipLaunchKernelGGL(zero_step_kernel, dim3(blocks_for(d.P)), dim3(256), 0, s, w.grad, d.P, w.sc, 1, first ? (double*)w.plan.head : (double*)nullptr,
-                         first ? (int)(EM * run_head_ints(d.T) / 2) : 0);
-      if (first) launch_seq_plan(plan, EM, s);
+      const int planned = q == 0 ? std::min(c.n_minibatches - mb, kPlanned) : 0;  // clears the heads of their plans too
+      hipLaunchKernelGGL(zero_step_kernel, dim3(blocks_for(d.P)), dim3(256), 0, s, w.grad, d.P, w.sc, 1, (double*)(planned ? w.plan.head : nullptr),
+                         (int)(planned * run_head_ints(d.T) / 2));
+      if (planned) {
+        plan.envs = perm != nullptr ? perm + (int64_t)e * d.N : nullptr;
+        plan.first = mb;
+        launch_seq_plan(plan, planned, s);
+      }
       LossCommon lc{};
       lc.rows = rows; lc.A = d.A; lc.ad = make_small_div(d.A); lc.rows_mb = TJ; lc.inv_B = (float)(1.0 / (double)(TJ * d.A));
       lc.sc = w.sc; lc.adv_stats = &w.sc->adv_sum; lc.normalize = c.normalize_adv; lc.clip_eps = c.clip_eps; lc.ent_coef = c.ent_coef;

@@ -1,0 +1,49 @@
+"""The recurrent update's plans of its minibatches (row order, state rows, resets, runs): as many as are planned at once, however many there are."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+
+def sizes(**kw):
+    import paper_2107_01460_amd as M
+    return M.query_sizes(W.scaled(W.CONFIGS[1], recurrent=1, n_envs=1280, rollout_len=128, **kw)).update_workspace_bytes
+
+
+def test_workspace_does_not_grow_with_the_epochs():
+    assert sizes(n_minibatches=4, n_epochs=1) == sizes(n_minibatches=4, n_epochs=2) == sizes(n_minibatches=4, n_epochs=100)
+
+
+def test_workspace_shrinks_with_the_minibatches():
+    """Smaller minibatches, smaller buffers, up to one environment each."""
+    by_count = [sizes(n_minibatches=m, n_epochs=2) for m in (1, 2, 4, 32, 64, 320, 1280)]
+    assert by_count == sorted(by_count, reverse=True), by_count
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("order", [True, False])
+def test_more_minibatches_than_are_planned_at_once(orc, order):
+    import paper_2107_01460_amd as M
+    from gpu_util import REL_TOL, dev, err, load_traj
+    from test_gpu_recurrent import load_rec, oracle_rollout
+    mb = 70  # two plans of 32 and one of 6
+    cfg = dict(W.CONFIGS[0], n_envs=140, rollout_len=6, actor_hidden=64, critic_hidden=96, episode_cap=4, n_minibatches=mb, n_epochs=2,
+               recurrent=1, max_grad_norm=0.0, lr=1e-30, central_critic=1)  # (the parameters stay: every minibatch by itself)
+    params, _, otr, orec = oracle_rollout(orc, cfg)
+    otr.done[:] = np.random.default_rng(5).random(otr.done.shape) < 0.3
+    perm = W.make_env_perm(cfg, seed=3) if order else None
+    ostats, ograd = orc.rec_ppo_update(cfg, otr, orec, params.copy(), np.zeros_like(params), np.zeros_like(params), adam_step0=0, perm=perm)
+    gtr, grec = load_traj(M, cfg, otr), load_rec(M, cfg, orec)
+    ws = M.alloc_workspace(M.query_sizes(cfg).update_workspace_bytes)
+    stats, g = torch.zeros((2 * mb, 8), device="cuda"), torch.zeros(params.size, device="cuda")
+    M.ppo_update_recurrent(cfg, gtr, grec, dev(params), torch.zeros_like(g), torch.zeros_like(g), 0, dev(perm) if order else None, stats, g, ws)
+    torch.cuda.synchronize()
+    got = stats.cpu().numpy()
+    for i in (0, 1, 2, 5, 6):  # (a minibatch has twelve samples per step and network: sums small enough to hold to the fp32 bound)
+        assert np.all(np.abs(got[:, i] - ostats[:, i]) < REL_TOL[0] * np.maximum(np.abs(ostats[:, i]), 1e-2)), i
+    off = 0
+    for name, shape in W.param_layout(cfg):
+        n = int(np.prod(shape))
+        assert err(g.cpu().numpy()[off:off + n], ograd[off:off + n], cfg) < REL_TOL[0], name
+        off += n
