@@ -48,23 +48,20 @@ __device__ __forceinline__ float sigmoid_f32(float x) { return __builtin_amdgcn_
 // The runs of a minibatch of sequences: a state is zeroed where an episode begins, so that the steps between two such places, a run, depend
 // on nothing before them, and the runs of all sequences can go side by side.  A chain is then as long as an episode at most, not as
 // the rollout.  Run i of `env[]` covers `y` steps from row x = t * (S1 / per) + environment on and stands for `per` sequences; the longest come first (that is
-// for speed alone: workgroups take the next MT sequences when they are done with the last, and lanes of a workgroup whose run has
-// ended wait for the others).
+// for speed alone: lanes of a workgroup whose run has ended wait for the others, and the workgroups' shares come out alike).
 struct SeqRuns {
   const int2* env;
   const int* count;
-  int* next;  // counter of the groups taken, zero before the launch
+  int turn;  // 1: the first round is dealt out from the last workgroup on
 };
-// The next group of MT sequences of a workgroup (whole workgroup, uniform); false: none is left.  The first barrier keeps a wavefront that is through with
-// a group from overwriting the slot before the others have read it: a backward group of one-step runs has no other barrier.
+// The first sequence of a workgroup's k-th group of MT: every round of gridDim.x groups is dealt out the other way round, so that who has the longest of one
+// round has the shortest of the next.  A workgroup without a group in a round has none in later ones.  The two networks, which run beside one another,
+// begin at opposite ends (turn): where the groups are few, most workgroups leave at once and the working ones of both would come to lie on the same compute
+// units (192 sequences x 128 steps, 64 units: an update of 1.17 of the time).  (Groups taken from a counter in memory came at 30 ns each, one after the
+// other: runs of five steps of 3072 sequences, 32 units, 131 and 170 us forward and backward, dealt out 35 and 40.)
 template <int MT>
-__device__ __forceinline__ bool next_group(const SeqRuns& runs, int per, int* slot, int& first, int& total) {
-  lds_barrier();
-  if (threadIdx.x == 0) *slot = atomicAdd(runs.next, 1);
-  __syncthreads();
-  first = __builtin_amdgcn_readfirstlane(*slot) * MT;
-  total = *runs.count * per;
-  return first < total;
+__device__ __forceinline__ int group_first(const SeqRuns& runs, int k) {
+  return MT * (int)(k * gridDim.x + ((k + runs.turn) & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x));
 }
 // Sequence k's row of a step's S1 and steps; past the end: 0 steps of the first sequence's row.
 __device__ __forceinline__ void run_of(const SeqRuns& runs, int per, int k, int total, int64_t& row, int& len) {
@@ -114,8 +111,9 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
   constexpr int THREADS = RES ? 128 * KS : 64 * KS;
   __shared__ __attribute__((aligned(16))) bf16_t Hs[2][3 * PLANE];
   __shared__ __attribute__((aligned(16))) float bias[4][H];  // r and z: both biases; n: input, hidden
-  __shared__ int group;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
+  const int total = SEG ? *a.runs.count * a.per : 0;
+  if (SEG && group_first<MT>(a.runs, 0) >= total) return;
   for (int j = tid; j < H; j += THREADS) {
     bias[0][j] = a.bi[j] + a.bh[j];
     bias[1][j] = a.bi[H + j] + a.bh[H + j];
@@ -147,22 +145,22 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
 #pragma unroll
   for (int i = 0; i < (RES ? NI : RING - 1); ++i) load_w(i, w[i]);
 
-  for (;;) {
+  for (int k = 0;; ++k) {
     int64_t row[SM];  // of the current step
     int64_t env[SM];  // without SEG
     int len[SM], steps = a.T;  // a sequence past its last step stays at that row and stores nothing
     if (SEG) {
-      int first, total;
-      if (!next_group<MT>(a.runs, a.per, &group, first, total)) return;  // uniform
+      const int first = group_first<MT>(a.runs, k);
+      if (first >= total) return;  // uniform
 #pragma unroll
       for (int m = 0; m < SM; ++m) run_of(a.runs, a.per, first + 16 * m + lo, total, row[m], len[m]);
       steps = longest_run(len);
     } else {
 #pragma unroll
       for (int m = 0; m < SM; ++m) {
-        const int64_t k = (int64_t)blockIdx.x * MT + 16 * m + lo;
-        row[m] = min(k, a.S1 - 1);
-        len[m] = k < a.S1 ? a.T : 0;
+        const int64_t at = (int64_t)blockIdx.x * MT + 16 * m + lo;
+        row[m] = min(at, a.S1 - 1);
+        len[m] = at < a.S1 ? a.T : 0;
         env[m] = row[m] / a.per;
       }
     }
@@ -287,21 +285,23 @@ struct GruBwdArgs {
   const float* dl;       // [T][S1][NOUT] gradient of the outputs
   float* rec;            // [T][S1][4H] records, replaced by gradients
   const float* hs;       // [T][S1][H] state before every step (before a reset)
-  const uint8_t* reset;  // [T - 1][S1 / per], as forward (step by step)
+  const uint8_t* reset;  // [T - 1][S1 / per], as forward
   int per;
   int64_t S1;
   int T;
   SeqRuns runs;
 };
 
-template <int KS, int SM, bool RES, int NOUT>
+// SEG as forward.
+template <int KS, int SM, bool RES, bool SEG, int NOUT>
 __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kernel(GruBwdArgs a) {
   constexpr int H = 32 * KS, UB = RES ? 1 : 2, MT = 16 * SM, P = 3 * H + 8, PLANE = MT * P;
   constexpr int THREADS = RES ? 128 * KS : 64 * KS;
   __shared__ __attribute__((aligned(16))) bf16_t Gs[3 * PLANE];
   __shared__ __attribute__((aligned(16))) float W3s[H * NOUT];
-  __shared__ int group;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
+  const int total = SEG ? *a.runs.count * a.per : 0;
+  if (SEG && group_first<MT>(a.runs, 0) >= total) return;
   GroupCopy<H * NOUT, THREADS> w3;
   w3.request(tid, a.W3);
   w3.store(tid, [&](int e, float v) { W3s[e] = v; });
@@ -322,19 +322,32 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
 #pragma unroll
   for (int i = 0; i < (RES ? NI : RING - 1); ++i) load_w(i, w[i]);
 
-  for (;;) {
-    int first, total;
-    if (!next_group<MT>(a.runs, a.per, &group, first, total)) return;  // uniform
+  __syncthreads();  // W3s
+  for (int k = 0;; ++k) {
     int64_t row[SM];  // of the current step; a sequence past its first step stays there and stores nothing
-    int len[SM];
-    bool from_zero[SM];
+    int64_t env[SM];  // without SEG
+    int len[SM], steps = a.T;
+    int from_zero[SM];  // SEG: does the run's first step start from zero, else the current one (a byte that is looked at a step after its request)
+    if (SEG) {
+      const int first = group_first<MT>(a.runs, k);
+      if (first >= total) return;  // uniform
 #pragma unroll
-    for (int m = 0; m < SM; ++m) {
-      run_of(a.runs, a.per, first + 16 * m + lo, total, row[m], len[m]);
-      from_zero[m] = row[m] >= a.S1;
-      row[m] += max(len[m] - 1, 0) * a.S1;
+      for (int m = 0; m < SM; ++m) {
+        run_of(a.runs, a.per, first + 16 * m + lo, total, row[m], len[m]);
+        from_zero[m] = row[m] >= a.S1;
+        row[m] += max(len[m] - 1, 0) * a.S1;
+      }
+      steps = longest_run(len);
+    } else {
+#pragma unroll
+      for (int m = 0; m < SM; ++m) {
+        const int64_t at = (int64_t)blockIdx.x * MT + 16 * m + lo, s = min(at, a.S1 - 1);
+        len[m] = at < a.S1 ? a.T : 0;
+        env[m] = s / a.per;
+        row[m] = (a.T - 1) * a.S1 + s;
+      }
     }
-    const int steps = longest_run(len);
+    const int64_t nenv = a.S1 / a.per;
     float4 rec[UB][SM][4], hp[UB][SM], carry[UB][SM];
     float dl[SM][NOUT];
     auto load_step = [&](int b, int m) {
@@ -342,13 +355,14 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
       for (int k = 0; k < 4; ++k) rec[b][m][k] = *reinterpret_cast<const float4*>(a.rec + row[m] * 4 * H + k * H + unit[b]);
       hp[b][m] = *reinterpret_cast<const float4*>(a.hs + row[m] * H + unit[b]);
     };
-    auto load_row = [&](int m) {
+    auto load_row = [&](int t, int m) {
 #pragma unroll
       for (int k = 0; k < NOUT; ++k) dl[m][k] = a.dl[row[m] * NOUT + k];
+      if (!SEG) from_zero[m] = t > 0 ? a.reset[(t - 1) * nenv + env[m]] : 0;
     };
 #pragma unroll
     for (int m = 0; m < SM; ++m) {
-      load_row(m);
+      load_row(steps - 1, m);
 #pragma unroll
       for (int b = 0; b < UB; ++b) {
         load_step(b, m);
@@ -359,9 +373,10 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
 #pragma unroll 1
     for (int t = 0; t < steps; ++t) {  // t-th step from the end of each run
       if (!RES) asm volatile("" : "+v"(woff));
+      bool zero[SM];
 #pragma unroll
       for (int m = 0; m < SM; ++m) {
-        const bool zero = from_zero[m] && t + 1 == len[m];
+        zero[m] = from_zero[m] != 0 && (!SEG || t + 1 == len[m]);
         const int64_t here = row[m];
         if (t + 1 < len[m]) row[m] -= a.S1;
 #pragma unroll
@@ -375,7 +390,7 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
 #pragma unroll
             for (int k = 0; k < NOUT; ++k) dh = fmaf(dl[m][k], W3s[(unit[b] + e) * NOUT + k], dh);
             const float hn = at(rec[b][m][0]), r = at(rec[b][m][1]), z = at(rec[b][m][2]), n = at(rec[b][m][3]);
-            const float hprev = zero ? 0.f : at(hp[b][m]);
+            const float hprev = zero[m] ? 0.f : at(hp[b][m]);
             const float dpre_n = dh * (1.0f - z) * (1.0f - n * n);
             put(gr, dpre_n * hn * r * (1.0f - r));
             put(gz, dh * (hprev - n) * z * (1.0f - z));
@@ -402,7 +417,7 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
           }
           if (t + 1 < steps) load_step(b, m);
         }
-        if (t + 1 < steps) load_row(m);
+        if (t + 1 < steps) load_row(steps - 2 - t, m);
       }
       if (t + 1 == steps) break;  // uniform: nothing flows into the initial state
       lds_barrier();
@@ -438,9 +453,11 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
           carry[b][m].y += acc[b][m][1];
           carry[b][m].z += acc[b][m][2];
           carry[b][m].w += acc[b][m][3];
+          if (!SEG && zero[m]) carry[b][m] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
       lds_barrier();  // the tile has been read
     }
+    if (!SEG) return;
   }
 }
 
@@ -686,8 +703,22 @@ __global__ void __launch_bounds__(KS <= 4 ? 128 * KS : 64 * KS, 2) gru_actor_ste
 inline bool gru_seq_tiles16(int64_t S1) { return S1 <= 256 * 16; }
 // Workgroups for runs of S steps in all: as many as are resident at once (256 registers, eight wavefronts a compute unit).  16 sequences each for any
 // number of them: with 32 a minibatch's two directions take 0.30 + 0.34 ms where they take 0.17 + 0.18 (128 units, 98 304 steps), 1.02 + 1.20 where
-// 1.00 + 1.09 (128 units, 1 048 576 steps) and 1.73 + 2.17 where 1.28 + 1.50 (256 units, 262 144 steps).
-inline dim3 gru_run_grid(int64_t S, int waves) { return dim3((unsigned)std::min<int64_t>((S + 15) / 16, 256 * std::max(1, 8 / waves))); }
+// 1.00 + 1.09 (128 units, 1 048 576 steps).
+inline int64_t gru_run_places(int waves) { return 256 * std::max(1, 8 / waves); }
+inline dim3 gru_run_grid(int64_t S, int waves) { return dim3((unsigned)std::min<int64_t>((S + 15) / 16, gru_run_places(waves))); }
+// Does an update of S1 sequences of T steps, episodes of at most `cap`, go run by run?  Where the sequences alone leave most of the chip idle and are long
+// enough to be cut.  An update's time in runs over that in whole sequences, 32 .. 256 units, episodes of ten steps / of 50 / none ending: 128 steps of 64
+// sequences 0.43 .. 0.61 / 0.45 .. 0.63 / 0.94 .. 1.00; of 512 sequences 0.69 .. 0.82 / 0.60 .. 0.68 / 0.94 .. 0.99; of 1024 0.84 .. 1.06 / 0.71 .. 0.83 /
+// 0.95 .. 1.01; of 1536 0.88 .. 1.01 / 0.82 .. 0.94 / 0.94 .. 1.02; of 2048 0.95 .. 1.06 / 0.87 .. 1.02 / 0.98 .. 1.00, so that from there on the longest chain
+// has to come out at two thirds or less (256 units, 2048 sequences beside 8192 of 128 units, episodes of 70 steps: an iteration of 387 ms in place of 397); of
+// 3072 at 96 units and more 1.02 .. 1.06 / 0.97 .. 1.03 / 0.99 .. 1.01; of 8192, above 128 units, 1.07 .. 1.11.  32 steps of 64 .. 1024 sequences 0.96 .. 1.11,
+// 16 steps up to 1.08.  At 128 units whole sequences in tiles of 32 spill registers: in runs 0.95 .. 1.00 of their time above 4096 sequences, of 16 steps as of 128.
+inline bool gru_by_runs(int T, int cap, int64_t S1, int H) {
+  if (!gru_seq_supported(H)) return false;
+  if (H == 128 && !gru_seq_tiles16(S1)) return true;
+  const int64_t chain = std::max<int64_t>(std::min(T, cap), T * S1 / (16 * gru_run_places(H <= 128 ? H / 16 : H / 32)));
+  return T > 32 && (S1 <= 1536 || (S1 <= 3072 && 2 * T >= 3 * chain));
+}
 
 template <int KS, bool SEG>
 inline void launch_gru_fwd_ks(const GruFwdArgs& a, hipStream_t s) {
@@ -703,11 +734,13 @@ inline void launch_gru_actor_ks(const GruActorArgs& a, hipStream_t s) {
   if (gru_seq_tiles16(a.S)) hipLaunchKernelGGL((gru_actor_step_kernel<KS, 1>), dim3((unsigned)((a.S + 15) / 16)), block, 0, s, a);
   else hipLaunchKernelGGL((gru_actor_step_kernel<KS, 2>), dim3((unsigned)((a.S + 31) / 32)), block, 0, s, a);
 }
-template <int KS, int NOUT>
+template <int KS, bool SEG, int NOUT>
 inline void launch_gru_bwd_ks(const GruBwdArgs& a, hipStream_t s) {
   constexpr bool RES = KS <= 4;
   constexpr int WAVES = RES ? 2 * KS : KS;
-  hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, NOUT>), gru_run_grid(a.T * a.S1, WAVES), dim3(64 * WAVES), 0, s, a);
+  if constexpr (SEG) hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, true, NOUT>), gru_run_grid(a.T * a.S1, WAVES), dim3(64 * WAVES), 0, s, a);
+  else if (KS == 4 || gru_seq_tiles16(a.S1)) hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, false, NOUT>), dim3((unsigned)((a.S1 + 15) / 16)), dim3(64 * WAVES), 0, s, a);
+  else if constexpr (KS != 4) hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 2, RES, false, NOUT>), dim3((unsigned)((a.S1 + 31) / 32)), dim3(64 * WAVES), 0, s, a);
 }
 
 }  // namespace marl

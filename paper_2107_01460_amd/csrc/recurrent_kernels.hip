@@ -153,16 +153,11 @@ __global__ void __launch_bounds__(256) gru_backward_kernel(const float* __restri
   dhprev[i] = dh * z;
 }
 
-// Index arrays of the next minibatches of sequences of an update, blockIdx.y-th of them: row r = t * J + j is trajectory row t * N + envs[j]; reset[r] = the step before t
-// ended the episode of that environment (never at t = 0); hrows[r] = the state row that step t starts from, r, or the row of
-// zeros behind the T + 1 slabs.  And its runs (SeqRuns), the longest first, in no order among those of one length (a run's results do not
-// depend on which others it shares a workgroup with): the first pass counts them by length, the second one places them.
-// One thread per sequence, sixteen steps requested at a time; a workgroup's counts meet in LDS, so that a few atomics per workgroup remain.
-constexpr int kRunBins = 1024;  // lengths from here on count as one
-constexpr int kRunHead = 16;    // ints before a minibatch's bins: number of runs, groups taken by each of its four kernels
-// Minibatches planned at once: an epoch's, so that two launches serve them all, but no more than these, so that the room for plans grows neither
-// with the epochs nor with their minibatches.
+// The next minibatches of sequences of an update, blockIdx.y-th of them in every kernel here.  Minibatches planned at once: an epoch's, so that
+// the same launches serve them all, but no more than these, so that the room for plans grows neither with the epochs nor with their minibatches.
 constexpr int kPlanned = 32;
+constexpr int kRunBins = 1024;  // lengths from here on count as one
+constexpr int kRunHead = 4;     // ints before a minibatch's bins: number of runs
 struct SeqPlanArgs {
   const int32_t* envs;  // [N] the epoch's order, nullable: the identity
   const uint8_t* done;  // [T][N]
@@ -172,47 +167,67 @@ struct SeqPlanArgs {
   uint8_t* reset;
   int2* runs;
   int32_t* head;        // [minibatch of the plan][run_head_ints(T)], zero before the first pass
+  __device__ __forceinline__ int env(int q, int j) const { const int place = (first + q) * J + j; return envs != nullptr ? envs[place] : place; }
 };
 __host__ __device__ inline int run_bins(int T) { return T < kRunBins ? T : kRunBins; }
 __host__ __device__ inline int64_t run_head_ints(int T) { return (kRunHead + 2 * (int64_t)run_bins(T) + 3) / 4 * 4; }
-template <bool PLACE>
-__global__ void __launch_bounds__(256) seq_plan_kernel(SeqPlanArgs a) {
-  __shared__ int32_t bin[kRunBins], at[kRunBins];
-  const int tid = threadIdx.x, j = blockIdx.x * 256 + tid, q = blockIdx.y, B = run_bins(a.T);
-  const int64_t TJ = (int64_t)a.T * a.J;
+
+// Index arrays: row r = t * J + j is trajectory row t * N + envs[j]; reset[r] = the step before t ended the episode of that environment (never at t = 0);
+// hrows[r] = the state row that step t starts from, r, or the row of zeros behind the T + 1 slabs.
+__global__ void __launch_bounds__(256) seq_index_kernel(SeqPlanArgs a) {
+  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x, TJ = (int64_t)a.T * a.J;
+  if (r >= TJ) return;
+  const int q = blockIdx.y, t = (int)(r / a.J), j = (int)(r - (int64_t)t * a.J), env = a.env(q, j);
+  const bool z = t > 0 && a.done[(int64_t)(t - 1) * a.N + env];
+  a.rows[q * TJ + r] = t * a.N + env;
+  a.reset[q * TJ + r] = z;
+  a.hrows[q * TJ + r] = z ? (a.T + 1) * a.J : (int32_t)r;
+}
+
+// Runs (SeqRuns), the longest first, in no order among those of one length (a run's results do not depend on which others it shares a workgroup
+// with): the first pass counts them by length, the second one places them.  A wavefront takes a sequence, 64 steps a lane each: a lane whose step begins an
+// episode ends the run before it.  Four pieces of 64 steps are requested together; a workgroup's counts meet in LDS, so that a few
+// atomics per workgroup remain.  (A thread per sequence, with the index arrays among its stores: 128 steps of 32 sequences 76 us in place of 16 with the index arrays' kernel.)
+template <bool PLACE, int PER>  // PER: sequences a wavefront takes
+__global__ void __launch_bounds__(256) seq_runs_kernel(SeqPlanArgs a) {
+  __shared__ int32_t bin[kRunBins], at[kRunBins], wave_sum[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = blockIdx.y, B = run_bins(a.T);
+  const int j0 = (blockIdx.x * 4 + wave) * PER, mine = max(0, min(PER, a.J - j0)), chunks = (a.T + 63) / 64;
   int32_t* const head = a.head + q * run_head_ints(a.T);
   int32_t *const count = head + kRunHead, *const taken = count + B;  // by length, B first
   for (int b = tid; b < B; b += 256) bin[b] = 0;
   __syncthreads();
-  const int place = j >= a.J ? 0 : (a.first + q) * a.J + j, env = a.envs != nullptr ? a.envs[place] : place;
-  // visits the runs of this thread's sequence
+  int env[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) env[i] = i < mine ? a.env(q, j0 + i) : 0;
+  // visits the runs of this wavefront's sequences, at most one a lane at a time
   auto runs = [&](auto&& run) {
-    if (j >= a.J) return;
-    int begin = 0;
-    for (int t0 = 0; t0 < a.T; t0 += 16) {
-      bool z[16];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) z[u] = t0 + u > 0 && a.done[(int64_t)(min(t0 + u, a.T) - 1) * a.N + env];
+    for (int i = 0; i < PER; ++i) {
+      if (i >= mine) break;
+      int begin = 0;
+      for (int c = 0; c < chunks; c += 4) {
+        bool z[4];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int t = t0 + u;
-        if (t < a.T) {
-          if (!PLACE) {
-            const int64_t r = (int64_t)t * a.J + j;
-            a.rows[q * TJ + r] = t * a.N + env;
-            a.reset[q * TJ + r] = z[u];
-            a.hrows[q * TJ + r] = z[u] ? (a.T + 1) * a.J : (int32_t)r;
-          }
+        for (int u = 0; u < 4; ++u) {
+          const int t = 64 * (c + u) + lane;
+          z[u] = t > 0 && t < a.T && a.done[(int64_t)(t - 1) * a.N + env[i]];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int t0 = 64 * (c + u);
+          const uint64_t mask = __builtin_amdgcn_ballot_w64(z[u]), below = mask & ((1ull << lane) - 1);
           if (z[u]) {
-            run(begin, t - begin);
-            begin = t;
+            const int from = below != 0 ? t0 + 63 - __builtin_clzll(below) : begin;
+            run(j0 + i, from, t0 + lane - from);
           }
+          if (mask != 0) begin = t0 + 63 - __builtin_clzll(mask);
         }
       }
+      if (lane == 0) run(j0 + i, begin, a.T - begin);
     }
-    run(begin, a.T - begin);
   };
-  runs([&](int, int len) { atomicAdd(&bin[B - min(len, B)], 1); });
+  runs([&](int, int, int len) { atomicAdd(&bin[B - min(len, B)], 1); });
   __syncthreads();
   if (!PLACE) {
     for (int b = tid; b < B; b += 256)
@@ -220,25 +235,48 @@ __global__ void __launch_bounds__(256) seq_plan_kernel(SeqPlanArgs a) {
     return;
   }
   // where this workgroup's runs of each length begin: behind the longer ones and those other workgroups have placed
-  if (tid == 0) {
-    int sum = 0;
-    for (int b = 0; b < B; ++b) {
-      at[b] = sum;
-      sum += count[b];
-    }
-    if (blockIdx.x == 0) head[0] = sum;
+  constexpr int OWN = kRunBins / 256;  // bins a thread adds up
+  int own[OWN], sum = 0;
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    const int b = OWN * tid + u;
+    own[u] = b < B ? count[b] : 0;
+    sum += own[u];
+  }
+  int before = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o *= 2) {
+    const int v = __shfl_up(before, o);
+    if (lane >= o) before += v;
+  }
+  if (lane == 63) wave_sum[wave] = before;
+  __syncthreads();
+  before -= sum;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) before += w < wave ? wave_sum[w] : 0;
+  if (blockIdx.x == 0 && tid == 255) head[0] = before + sum;
+#pragma unroll
+  for (int u = 0; u < OWN; ++u) {
+    const int b = OWN * tid + u;
+    if (b < B) at[b] = before + (bin[b] > 0 ? atomicAdd(&taken[b], bin[b]) : 0);
+    before += own[u];
   }
   __syncthreads();
-  for (int b = tid; b < B; b += 256)
-    if (bin[b] > 0) at[b] += atomicAdd(&taken[b], bin[b]);
-  __syncthreads();
-  runs([&](int begin, int len) { a.runs[q * TJ + atomicAdd(&at[B - min(len, B)], 1)] = make_int2(begin * a.J + j, len); });
+  runs([&](int j, int begin, int len) { a.runs[q * (int64_t)a.T * a.J + atomicAdd(&at[B - min(len, B)], 1)] = make_int2(begin * a.J + j, len); });
 }
 
-void launch_seq_plan(const SeqPlanArgs& a, int minibatches, hipStream_t s) {
-  const dim3 grid((unsigned)((a.J + 255) / 256), (unsigned)minibatches);
-  hipLaunchKernelGGL(seq_plan_kernel<false>, grid, dim3(256), 0, s, a);
-  hipLaunchKernelGGL(seq_plan_kernel<true>, grid, dim3(256), 0, s, a);
+// with_runs: the index arrays alone where no network takes the runs
+void launch_seq_plan(const SeqPlanArgs& a, int minibatches, bool with_runs, hipStream_t s) {
+  const unsigned my = (unsigned)minibatches;
+  hipLaunchKernelGGL(seq_index_kernel, dim3((unsigned)(((int64_t)a.T * a.J + 255) / 256), my), dim3(256), 0, s, a);
+  if (!with_runs) return;
+  if (a.J <= 1024) {  // few sequences: a wavefront each, for the shortest chain
+    hipLaunchKernelGGL((seq_runs_kernel<false, 1>), dim3((unsigned)((a.J + 3) / 4), my), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((seq_runs_kernel<true, 1>), dim3((unsigned)((a.J + 3) / 4), my), dim3(256), 0, s, a);
+  } else {  // fewer workgroups that add to the same counts
+    hipLaunchKernelGGL((seq_runs_kernel<false, 8>), dim3((unsigned)((a.J + 31) / 32), my), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((seq_runs_kernel<true, 8>), dim3((unsigned)((a.J + 31) / 32), my), dim3(256), 0, s, a);
+  }
 }
 
 // dst[(j * per + a)][u] = h0[(envs[j] * per + a)][u]; zeros[0 .. per * H - 1] = 0
@@ -320,19 +358,19 @@ void gru_forward(const GruFwdArgs& a, int H, const float* eff, const RecOffsets&
 }
 
 // All steps of a, backward.  dhp [2][S1][H] is used above 256 units only.
-template <int NOUT>
+template <bool SEG, int NOUT>
 void gru_backward(const GruBwdArgs& a, int H, const float* eff, const RecOffsets& o, float* dhp, hipStream_t s) {
   if (gru_seq_supported(H)) {
     TimedLaunch timed(KC_GEMM_NT, 2.0 * (double)(a.T - 1) * (double)a.S1 * H * 3.0 * H, s);
     switch (H / 32) {
-      case 1: return launch_gru_bwd_ks<1, NOUT>(a, s);
-      case 2: return launch_gru_bwd_ks<2, NOUT>(a, s);
-      case 3: return launch_gru_bwd_ks<3, NOUT>(a, s);
-      case 4: return launch_gru_bwd_ks<4, NOUT>(a, s);
-      case 5: return launch_gru_bwd_ks<5, NOUT>(a, s);
-      case 6: return launch_gru_bwd_ks<6, NOUT>(a, s);
-      case 7: return launch_gru_bwd_ks<7, NOUT>(a, s);
-      default: return launch_gru_bwd_ks<8, NOUT>(a, s);
+      case 1: return launch_gru_bwd_ks<1, SEG, NOUT>(a, s);
+      case 2: return launch_gru_bwd_ks<2, SEG, NOUT>(a, s);
+      case 3: return launch_gru_bwd_ks<3, SEG, NOUT>(a, s);
+      case 4: return launch_gru_bwd_ks<4, SEG, NOUT>(a, s);
+      case 5: return launch_gru_bwd_ks<5, SEG, NOUT>(a, s);
+      case 6: return launch_gru_bwd_ks<6, SEG, NOUT>(a, s);
+      case 7: return launch_gru_bwd_ks<7, SEG, NOUT>(a, s);
+      default: return launch_gru_bwd_ks<8, SEG, NOUT>(a, s);
     }
   }
   const int64_t J = a.S1 / a.per;
@@ -572,7 +610,7 @@ template <int NOUT, class LossFn>
 int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din, int H, const float* h0,
                             const int32_t* envs, const float* eff, const RecOffsets& o, const float* wh_fwd,
                             const float* wh_bwd, float* grad, const RecOffsets& go, const LossFn& fn, const RecNetWs& w,
-                            const uint8_t* reset, const int32_t* hrows, const SeqRuns& runs, Scalars* sc, hipStream_t s) {
+                            const uint8_t* reset, const int32_t* hrows, bool by_runs, const SeqRuns& runs, Scalars* sc, hipStream_t s) {
   const int64_t S1 = J * per, S = (int64_t)T * S1;
   hipLaunchKernelGGL(gather_hidden_kernel, dim3(blocks_for(S1 * H)), dim3(256), 0, s, h0, envs, (int)J, per, H, w.Hs, w.Hs + (S + S1) * H);
   embed_and_input_gates(X, S, Din, H, eff, o, w.E, w.G, s);
@@ -580,15 +618,17 @@ int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din,
   f.Gi = w.G; f.W = reinterpret_cast<const bf16_t*>(wh_fwd); f.bi = eff + o.bi; f.bh = eff + o.bh;
   f.h_first = w.Hs; f.hs = w.Hs + S1 * H; f.rec = w.R; f.reset = reset + J; f.per = per; f.S1 = S1; f.T = T;
   f.runs = runs;
-  gru_forward<true>(f, H, eff, o, w.GhT, w.hm, s);
+  if (by_runs) gru_forward<true>(f, H, eff, o, w.GhT, w.hm, s);
+  else gru_forward<false>(f, H, eff, o, w.GhT, w.hm, s);
   // output layer, loss, dL/dout, W3 / b3 gradient over all steps
   const int32_t rc = launch_loss_head<NOUT, false>(w.Hs + S1 * H, S, H, eff + o.W3, eff + o.b3, fn, w.dl, grad + go.W3, w.partial, sc, s);
   if (rc != MARL_OK) return rc;
   GruBwdArgs bw{};
   bw.W = reinterpret_cast<const bf16_t*>(wh_bwd); bw.W3 = eff + o.W3; bw.dl = w.dl; bw.rec = w.R; bw.hs = w.Hs; bw.reset = reset + J;
   bw.per = per; bw.S1 = S1; bw.T = T;
-  bw.runs = SeqRuns{runs.env, runs.count, runs.next + 1};
-  gru_backward<NOUT>(bw, H, eff, o, w.dHp, s);
+  bw.runs = runs;
+  if (by_runs) gru_backward<true, NOUT>(bw, H, eff, o, w.dHp, s);
+  else gru_backward<false, NOUT>(bw, H, eff, o, w.dHp, s);
   const float* const dgh = w.R;      // [S][4H], columns n, r, z
   const float* const dgi = w.R + H;  // [S][4H], columns r, z, n
   // gWh += (states the steps start from)^T dGh, the new gate's columns last; gWi += E^T dGi
@@ -622,6 +662,7 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
   const RecParamMap pm = rec_param_map(d);
   const RecOffsets oa = rec_padded(pm, 0), oc = rec_padded(pm, 1);
   const SideStream* const side = side_stream();
+  const bool by_runs_a = gru_by_runs(d.T, c.episode_cap, J * d.A, d.Ha), by_runs_c = gru_by_runs(d.T, c.episode_cap, d.central ? J : J * d.A, d.Hc);
   SeqPlanArgs plan = w.plan;
   plan.done = tr.done;
   int64_t k = adam_step0;
@@ -630,7 +671,7 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
       const int q = mb % kPlanned;
       int32_t *const rows = w.plan.rows + q * TJ, *const hrows = w.plan.hrows + q * TJ, *const head = w.plan.head + q * run_head_ints(d.T);
       const uint8_t* const reset = w.plan.reset + q * TJ;
-      const SeqRuns runs_a{w.plan.runs + q * TJ, head, head + 4}, runs_c{w.plan.runs + q * TJ, head, head + 8};
+      const SeqRuns runs_a{w.plan.runs + q * TJ, head, 0}, runs_c{w.plan.runs + q * TJ, head, 1};
       const float* eff = stage_params(d, params, w.eff, s);
       const int planned = q == 0 ? std::min(c.n_minibatches - mb, kPlanned) : 0;  // clears the heads of their plans too
       hipLaunchKernelGGL(zero_step_kernel, dim3(blocks_for(d.P)), dim3(256), 0, s, w.grad, d.P, w.sc, 1, (double*)(planned ? w.plan.head : nullptr),
@@ -638,7 +679,7 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
       if (planned) {
         plan.envs = perm != nullptr ? perm + (int64_t)e * d.N : nullptr;
         plan.first = mb;
-        launch_seq_plan(plan, planned, s);
+        launch_seq_plan(plan, planned, by_runs_a || by_runs_c, s);
       }
       LossCommon lc{};
       lc.rows = rows; lc.A = d.A; lc.ad = make_small_div(d.A); lc.rows_mb = TJ; lc.inv_B = (float)(1.0 / (double)(TJ * d.A));
@@ -659,13 +700,13 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
         ActorLoss fn{lc, tr.action, tr.logp, tr.adv};
         rc_a = train_net_recurrent<kActions>(RowSrc{tr.obs, d.D, rows, d.A, TJ * d.A}, d.T, J, d.A, d.D, d.Ha, rec.ha0, rows,
                                              eff, oa, eff + pm.wh_fwd[0], eff + pm.wh_bwd[0], w.grad, ga, fn, w.net[0], reset,
-                                             hrows, runs_a, w.sc, s);
+                                             hrows, by_runs_a, runs_a, w.sc, s);
       }
       {
         CriticLoss fn{lc, tr.ret, tr.value, d.central ? d.A : 1};
         const int per = d.central ? 1 : d.A;
         rc_c = train_net_recurrent<1>(RowSrc{tr.obs, d.Dc, rows, per, TJ * per}, d.T, J, per, d.Dc, d.Hc, rec.hc0, rows, eff,
-                                      oc, eff + pm.wh_fwd[1], eff + pm.wh_bwd[1], w.grad, gc, fn, w.net[1], reset, hrows, runs_c, w.sc, s2);
+                                      oc, eff + pm.wh_fwd[1], eff + pm.wh_bwd[1], w.grad, gc, fn, w.net[1], reset, hrows, by_runs_c, runs_c, w.sc, s2);
       }
       if (s2 != s) {  // join also after an error, so that the caller's stream never runs ahead of work still queued beside it
         if (hipEventRecord(side->join, s2) != hipSuccess || hipStreamWaitEvent(s, side->join, 0) != hipSuccess) {

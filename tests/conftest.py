@@ -1,5 +1,8 @@
 import os
+import shutil
+import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -18,3 +21,21 @@ def orc():
 
     oracle.build()
     return oracle
+
+
+@pytest.fixture(scope="session")
+def listings(tmp_path_factory):
+    """{source: the gfx950 listing of its kernels}, all translation units of the library compiled side by side."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("needs hipcc")
+    from paper_2107_01460_amd import build
+    folder = tmp_path_factory.mktemp("listings")
+
+    def listing(src):
+        out = str(folder / src.replace(".hip", ".s"))
+        subprocess.check_call(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, src), "-o", out])
+        with open(out) as f:
+            return f.read()
+
+    with ThreadPoolExecutor(max_workers=min(os.cpu_count() or 8, 8)) as ex:
+        return dict(zip(build.SOURCES, ex.map(listing, build.SOURCES)))
