@@ -17,8 +17,10 @@ int64_t effective_param_floats(const marl_config& c, bool update);
 
 namespace {
 
-__global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int for_rollout, int for_update) {
+// clear[0 .. n_clear - 1] = 0 beside it, for a kernel behind this one
+__global__ void stage_params_kernel(const float* __restrict__ src, float* __restrict__ dst, ParamMap pm, int for_rollout, int for_update, int32_t* clear, int n_clear) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t k = i; k < n_clear; k += (int64_t)gridDim.x * blockDim.x) clear[k] = 0;
   if (i >= pm.src[12]) return;
 #pragma unroll
   for (int net = 0; net < 2; ++net) {  // zero rows of the copies of W1 (fewer than 32 rows: far fewer floats than parameters)
@@ -186,7 +188,7 @@ void stage_bf16_weights(const marl_config& c, const float* params, float* scratc
   launch_bf16_stage(nets.first, nets.second, s);
 }
 
-const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use) {
+static const float* stage_working_copy(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use, int32_t* clear, int n_clear) {
   const Dims d = dims_of(c);
   const ParamMap pm = param_map(d, use == USE_UPDATE);
   const unsigned blocks = (unsigned)((d.P + 255) / 256);
@@ -196,9 +198,12 @@ const float* effective_params(const marl_config& c, const float* params, float* 
     hipLaunchKernelGGL(stage_bf16_params_kernel, dim3(frag + blocks), dim3(256), 0, s, params, scratch, pm, nets.first, nets.second, frag);
   } else {
     hipLaunchKernelGGL(stage_params_kernel, dim3(blocks), dim3(256), 0, s, params, scratch, pm,
-                       (int)(use != USE_ROLLOUT || !use_fused_rollout(c) ? COPY_SPLIT : rollout_rows(d.Ha, d.A, d.N) == 16 ? COPY_FP32_16 : COPY_FP32), (int)(use == USE_UPDATE));
+                       (int)(use != USE_ROLLOUT || !use_fused_rollout(c) ? COPY_SPLIT : rollout_rows(d.Ha, d.A, d.N) == 16 ? COPY_FP32_16 : COPY_FP32), (int)(use == USE_UPDATE), clear, n_clear);
   }
   return scratch;
+}
+const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use) {
+  return stage_working_copy(c, params, scratch, s, use, nullptr, 0);
 }
 
 int64_t rollout_workspace_bytes(const marl_config& c, int64_t n_rows) {
@@ -427,7 +432,10 @@ struct EvalWsView {
   uint8_t* done;
   EvalEpisodes eps;  // slots: as many as there is room for
 };
-constexpr int kEvalSlots = 16384;  // episodes of all environments together that can be played by themselves (0.6 MB)
+// Episodes of an environment that there is room for: sixteen, and more while that is 32 768 of all environments together (2.2 MB, 4.3 with more than four
+// agents or food; more than twice that at 5461 environments, the most that go side by side).  A block takes half of them at most, because the
+// rows play the block's steps, however many episodes these are: enough where episodes last half as long as they may.
+inline int eval_slots(int N) { return std::max(16, 32768 / N); }
 
 EvalWsView carve_eval_ws(const marl_config& c, void* ws, int64_t* total) {
   const Dims d = dims_of(c);
@@ -446,9 +454,10 @@ EvalWsView carve_eval_ws(const marl_config& c, void* ws, int64_t* total) {
   v.action = (int32_t*)take(d.NA * 4);
   v.done = (uint8_t*)take(d.N);
   v.eps = EvalEpisodes{};
-  v.eps.slots = use_fused_rollout(c) ? kEvalSlots / d.N : 0;
+  v.eps.slots = use_fused_rollout(c) && rollout_eval_apart(d.Ha, d.A, d.F, d.V, d.N) ? eval_slots(d.N) : 0;
   v.eps.len = (int32_t*)take((int64_t)v.eps.slots * d.N * 4);
-  v.eps.rew = (float*)take((int64_t)v.eps.slots * d.N * kEpisodeRewards * 4);
+  v.eps.record = (uint32_t*)take((int64_t)v.eps.slots * d.N * eval_record_words(std::max(d.A, d.F)) * 4);
+  v.eps.next = (int32_t*)take(v.eps.slots > 0 ? (int64_t)d.N * 4 : 0);
   if (total) *total = off;
   return v;
 }
@@ -466,19 +475,19 @@ int32_t launch_evaluate(const marl_config& c, marl_env_state st, const float* pa
   const Dims d = dims_of(c);
   const EvalWsView e = carve_eval_ws(c, workspace, nullptr);
   const RolloutWsView w = carve_rollout_ws(c, d.N, e.rollout_ws, nullptr);
-  const float* eff = effective_params(c, params, w.eff_params, s, USE_FORWARD);
+  const bool apart = n_episodes > 1 && 2 * (int64_t)n_episodes <= e.eps.slots;
+  const float* eff = stage_working_copy(c, params, w.eff_params, s, USE_FORWARD, e.eps.next, apart ? d.N : 0);
   const int64_t steps = (int64_t)n_episodes * c.episode_cap;
   if (use_fused_rollout(c)) {  // the whole block in one launch, or in two (rollout_eval.h), statistics in registers
     RolloutArgs a = rollout_fused_args(c, st, eff);
     a.T = (int)steps;
     a.ev = out;
     a.n_episodes = n_episodes;
-    // rows beside one another as long as all of them are resident: beyond, they would only follow one another
-    const int slots = std::min(n_episodes, e.eps.slots), copies = std::min(slots, rollout_eval_places(d.Ha, d.A, d.F, d.V) / d.N);
-    if (copies > 1) {
+    if (apart) {
       a.eps = e.eps;
-      a.eps.slots = slots;
-      a.eps.copies = copies;
+      a.eps.copies = rollout_eval_copies(d.Ha, d.A, d.F, d.V, d.N, n_episodes);
+      a.eps.steps = (int)((steps + a.eps.copies - 1) / a.eps.copies);
+      a.eps.every = (c.episode_cap + 2) / 3;
       const int32_t rc = launch_rollout_fused(c, true, a, s);
       if (rc != MARL_OK) return rc;
       a.eps.copies = 0;

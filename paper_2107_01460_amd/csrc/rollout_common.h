@@ -7,13 +7,18 @@
 
 namespace marl {
 
-// Episodes of an evaluation block that were played by themselves (rollout_eval.h): of every environment's first `slots` episodes the
-// length (and above it, from bit 24 on, the number of steps with a reward) and those rewards in the order of time.
+// Episodes of an evaluation block that were played by themselves (rollout_eval.h), at most `slots` of an environment: the length of each (and above
+// it, from bit 24 on, a counted one's number of steps with a reward) and a record, of a counted one those rewards in the order of time, of a later one its
+// entities a third and two thirds of the cap into it.
 constexpr int kEpisodeRewards = 8;
+constexpr int eval_record_words(int capacity) { return capacity <= 4 ? 16 : 32; }  // two sets of entities
 struct EvalEpisodes {
-  int slots, copies;  // copies: rows per environment, row j plays episodes j, j + copies, ...; 0 in the call that plays what is left
+  int slots, copies;  // copies: rows of an environment, which take its episodes in order; 0 in the call that plays what is left
+  int steps;          // a row that has taken so many begins no other episode: together they reach the end of the block
+  int every;          // a third of the cap, rounded up
   int32_t* len;       // [slots][N]
-  float* rew;         // [slots][N][kEpisodeRewards]
+  uint32_t* record;   // [slots][N][eval_record_words]
+  int32_t* next;      // [N] episodes taken beyond each row's first, zero before the launch
 };
 
 struct RolloutArgs {
@@ -89,6 +94,18 @@ struct RolloutEnvs {
   __device__ __forceinline__ void paint(T* window) const {
     if (KIND == 0) forage_paint<V, CA, CA, true>(window, ag, fd, ai, p);
     else wh_paint<V, CA, CA, true>(window, ag, fd, ai, p);
+  }
+  // The entities to and from 2 * CA words (16-byte aligned).
+  __device__ __forceinline__ void save(uint32_t* d) const {
+#pragma unroll
+    for (int i = 0; i < CA; i += 2) reinterpret_cast<uint4*>(d)[i / 2] = make_uint4(ag[i], fd[i], ag[i + 1], fd[i + 1]);
+  }
+  __device__ __forceinline__ void recall(const uint32_t* d) {
+#pragma unroll
+    for (int i = 0; i < CA; i += 2) {
+      const uint4 v = reinterpret_cast<const uint4*>(d)[i / 2];
+      ag[i] = v.x; fd[i] = v.y; ag[i + 1] = v.z; fd[i + 1] = v.w;
+    }
   }
   // All lanes of an env run this together, so that the cross-lane reads find their source lanes running.
   __device__ __forceinline__ void step(int my_act, float& rew, bool& dn) {

@@ -75,3 +75,37 @@ def test_evaluation_from_the_middle(M, orc, agents, view, hidden, n_envs, cap, E
     host = gs.to_host()
     for f in M.EnvState.FIELDS:
         assert np.array_equal(host[f][..., clear], getattr(os_, f)[..., clear]), f
+
+
+# Blocks whose episodes end early, in both worlds, from states with carried shelves and, in some environments, a step count past the cap: rows that play
+# several episodes and the block's last one in part, from its beginning and from either third of it (caps that are no multiple of three among
+# them); 2049 environments, whose rows take all the episodes there is room for; and more counted episodes than half of that room.
+@pytest.mark.parametrize("kind,agents,food,view,hidden,n_envs,cap,E,past", [
+    (2, 5, 4, 5, 64, 45, 31, 4, 1), (2, 8, 3, 7, 128, 33, 24, 7, 0), (1, 4, 5, 3, 128, 38, 11, 3, 1), (0, 3, 1, 5, 128, 40, 40, 2, 1),
+    (2, 3, 3, 3, 64, 2049, 20, 5, 0), (2, 3, 4, 3, 64, 2049, 6, 9, 0)])
+def test_evaluation_of_episodes_that_end_early(M, orc, kind, agents, food, view, hidden, n_envs, cap, E, past):
+    cfg = W.scaled(W.CONFIGS[0], env_kind=kind, grid=8, n_agents=agents, n_food=food, max_level=1 if kind == 0 else 2, view=view, n_envs=n_envs,
+                   actor_hidden=hidden, critic_hidden=hidden, episode_cap=cap, n_minibatches=1, rollout_len=1)
+    print("case", kind, agents, food, view, hidden, n_envs, cap, E, past, flush=True)
+    params = W.init_params(cfg, bias_scale=1.0 if kind else 0.3)
+    os_ = orc.EnvState(cfg)
+    orc.env_reset(cfg, os_)
+    rng = np.random.default_rng(11)
+    for _ in range(cap // 2):
+        orc.env_step(cfg, os_, rng.integers(0, 6, (n_envs, agents)).astype(np.int32))
+    if past:
+        os_.t_in_ep[::4] = cap + rng.integers(0, 3, len(os_.t_in_ep[::4]))
+    gs, out = M.EnvState(cfg), M.EvalStats(cfg)
+    for f in M.EnvState.FIELDS:
+        getattr(gs, f).copy_(torch.from_numpy(np.ascontiguousarray(getattr(os_, f))).view(getattr(gs, f).dtype))
+    oret, olen, oeps, gap = orc.evaluate(cfg, os_, params, E)
+    M.evaluate(cfg, gs, dev(params), E, out, M.alloc_workspace(M.query_sizes(cfg).eval_workspace_bytes))
+    torch.cuda.synchronize()
+    clear = gap > 8e-4 * max(1.0, float(np.abs(params).max()))
+    print("clear", clear.mean(), "steps of an episode", olen.mean() / E, flush=True)
+    assert clear.mean() > 0.3, clear.mean()
+    for got, want in ((out.ret_sum, oret), (out.len_sum, olen), (out.episodes, oeps)):
+        assert np.array_equal(got.cpu().numpy()[clear], want[clear])
+    host = gs.to_host()
+    for f in M.EnvState.FIELDS:
+        assert np.array_equal(host[f][..., clear], getattr(os_, f)[..., clear]), f
