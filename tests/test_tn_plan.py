@@ -57,7 +57,7 @@ int main() {
   long long m, n, k;
   while (std::scanf("%lld %lld %lld", &m, &n, &k) == 3) {
     const marl::TnPlan p = marl::tn_plan(m, n, k);
-    std::printf("%d %d %lld %lld %lld\\n", p.bm, p.bn, (long long)p.per, (long long)p.splits, (long long)marl::tn_copy_floats(m, n, k));
+    std::printf("%d %d %lld %lld %lld %d\\n", p.bm, p.bn, (long long)p.per, (long long)p.splits, (long long)marl::tn_copy_floats(m, n, k), (int)p.wide);
   }
 }
 """)
@@ -73,8 +73,9 @@ int main() {
 
 def test_the_tile_is_about_the_fastest(plan):
     """Within 10 % of the fastest tile measured, and never more than 3 % behind the tile of 128 rows (32 up to 32 rows)."""
-    for (m, n, k), (bm, bn, *_) in zip(MEASURED, plan(list(MEASURED))):
+    for (m, n, k), (bm, bn, *_, wide) in zip(MEASURED, plan(list(MEASURED))):
         us = MEASURED[m, n, k]
+        assert not wide  # its time is none of these: WIDE
         took = us[TILES.index((bm, bn))]
         usual = us[4] if m <= 32 else us[0] if n % 128 == 0 else us[1]
         assert took <= 1.1 * min(t for t in us if t is not None), ((m, n, k), (bm, bn), us)
@@ -84,7 +85,29 @@ def test_the_tile_is_about_the_fastest(plan):
 def test_ranges_cover_the_samples(plan):
     shapes = [(m, n, k) for m in (27, 32, 33, 75, 147, 300, 512, 1176) for n in (32, 96, 128, 320, 512, 1536)
               for k in (1, 31, 255, 256, 257, 4095, 65537, 2 ** 31 - 1)]
-    for (m, n, k), (bm, bn, per, splits, floats) in zip(shapes, plan(shapes)):
+    for (m, n, k), (bm, bn, per, splits, floats, wide) in zip(shapes, plan(shapes)):
         assert (bm, bn) in TILES and (bn == 128 or n % 128), (m, n, k)
         assert per % 32 == 0 and per >= 256 and (splits - 1) * per < k <= splits * per, (m, n, k, per, splits)
         assert splits <= 512 and floats == splits * (m * n + n), (m, n, k)
+        # of the tiles that are launched, as many workgroups as go at once
+        tiles = -(-m // bm) * (n // 192 if wide else -(-n // 128))
+        assert tiles > 512 and splits == 1 or tiles * splits <= 512, (m, n, k, wide, splits)
+
+
+# us with tiles of 128 and of 192 columns
+WIDE = {(128, 384, 262144): (175.3, 164.6), (128, 384, 1048576): (702.9, 602.7), (256, 768, 49152): (138.1, 118.6),
+        (256, 768, 262144): (628.7, 535.7), (512, 1536, 16384): (178.1, 145.2)}
+
+
+def test_wide_tiles(plan):
+    """Tiles of 192 columns where they have been measured to be faster, on both sides of every condition of theirs."""
+    for (m, n, k), (bm, bn, per, splits, floats, wide) in zip(WIDE, plan(list(WIDE))):
+        assert wide and WIDE[m, n, k][1] < WIDE[m, n, k][0], (m, n, k)
+        assert per >= 512 and -(-m // 128) * (n // 192) * splits <= 512, (m, n, k, per, splits)
+    line = {(128, 384): 131072, (256, 768): 32768, (128, 768): 65536, (512, 1536): 8192}  # samples: ranges of 512 for 512 workgroups
+    for (m, n), k in line.items():
+        below, at = plan([(m, n, k - 1), (m, n, k)])
+        assert not below[-1] and at[-1], (m, n, k)
+        assert at[0] == 128 and at[1] == 128
+    for m, n in ((128, 192), (128, 320), (128, 576), (96, 384), (32, 384)):  # no whole pairs of such tiles; other rows
+        assert not plan([(m, n, 1048576)])[0][-1], (m, n)
