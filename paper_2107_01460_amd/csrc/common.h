@@ -84,7 +84,8 @@ struct ParamMap {
   // operand straight from memory: part p of element (k, n) of a [K][H] matrix at split_weight_index(k, n, H) + p *
   // split_weight_plane(H), in bf16 elements, so that the eight k values of a lane are one 16-byte load, contiguous across
   // lanes.  W1 is zero-padded to kpad1 rows (a multiple of 32).  For a training rollout (rollout_train_kernel) the actor's two
-  // copies hold fp32 values instead, element (k, n) at ((k / 4) * H + n) * 4 + k % 4.
+  // copies hold fp32 values instead, element (k, n) at ((k / 4) * H + n) * 4 + k % 4, and for tiles of 16 samples every sixteen rows in another order
+  // (rollout_order16): launch_rollout chooses the tile once, for the copy and for the kernel (RolloutArgs::rows).
   int64_t sw_w1[2], sw_w2[2], sw_w2t[2];
   bool fused[2];  // these copies exist, and the blocks W1 and W2 have no room
   int din[2], kpad1[2];
@@ -93,8 +94,8 @@ struct ParamMap {
 };
 __host__ __device__ inline int64_t split_weight_index(int64_t k, int64_t n, int64_t H) { return ((k / 16 * 6 + k % 16 / 8) * H + n) * 8 + k % 8; }
 __host__ __device__ inline int64_t split_weight_plane(int64_t H) { return 16 * H; }
-// What a working copy is staged for: a forward pass, a training rollout (a forward map, the actor in fp32), an update.
-enum WeightUse { USE_FORWARD, USE_ROLLOUT, USE_UPDATE };
+// What a working copy is staged for: forward passes, those of a training rollout among them, or an update.
+enum WeightUse { USE_FORWARD, USE_UPDATE };
 // update: for an optimiser step, which also reads W2 transposed; otherwise for forward passes
 inline ParamMap param_map(const Dims& d, bool update) {
   ParamMap m;

@@ -188,7 +188,7 @@ void stage_bf16_weights(const marl_config& c, const float* params, float* scratc
   launch_bf16_stage(nets.first, nets.second, s);
 }
 
-static const float* stage_working_copy(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use, int32_t* clear, int n_clear) {
+static const float* stage_working_copy(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use, RolloutCopy actor, int32_t* clear, int n_clear) {
   const Dims d = dims_of(c);
   const ParamMap pm = param_map(d, use == USE_UPDATE);
   const unsigned blocks = (unsigned)((d.P + 255) / 256);
@@ -198,12 +198,12 @@ static const float* stage_working_copy(const marl_config& c, const float* params
     hipLaunchKernelGGL(stage_bf16_params_kernel, dim3(frag + blocks), dim3(256), 0, s, params, scratch, pm, nets.first, nets.second, frag);
   } else {
     hipLaunchKernelGGL(stage_params_kernel, dim3(blocks), dim3(256), 0, s, params, scratch, pm,
-                       (int)(use != USE_ROLLOUT || !use_fused_rollout(c) ? COPY_SPLIT : rollout_rows(d.Ha, d.A, d.N) == 16 ? COPY_FP32_16 : COPY_FP32), (int)(use == USE_UPDATE), clear, n_clear);
+                       (int)actor, (int)(use == USE_UPDATE), clear, n_clear);
   }
   return scratch;
 }
 const float* effective_params(const marl_config& c, const float* params, float* scratch, hipStream_t s, WeightUse use) {
-  return stage_working_copy(c, params, scratch, s, use, nullptr, 0);
+  return stage_working_copy(c, params, scratch, s, use, COPY_SPLIT, nullptr, 0);
 }
 
 int64_t rollout_workspace_bytes(const marl_config& c, int64_t n_rows) {
@@ -325,17 +325,19 @@ int32_t launch_rollout(const marl_config& c, marl_env_state st, const float* par
                        void* workspace, hipStream_t s, const uint64_t* step_base) {
   const Dims d = dims_of(c);
   const RolloutWsView w = carve_rollout_ws(c, d.N, workspace, nullptr);
-  const float* eff = effective_params(c, params, w.eff_params, s, USE_ROLLOUT);
+  const bool fused = use_fused_rollout(c);
+  const int rows = fused ? rollout_rows(d.Ha, d.A, d.N) : 0;
+  const float* eff = stage_working_copy(c, params, w.eff_params, s, USE_FORWARD, !fused ? COPY_SPLIT : rows == 16 ? COPY_FP32_16 : COPY_FP32, nullptr, 0);
   const int64_t NA = d.NA, slab = NA * d.D;
   int32_t rc;
   // The values do not steer the rollout (the parameters are constant during it): where the critic's forward pass
   // needs no per-row workspace (whole networks in one kernel), the values of all T steps and of the post-rollout observation
   // are computed in one pass over the stored observations afterwards instead of one small launch per step.
   const bool batch_values = d.bf16 || split_net_supported(d.Hc);
-  if (use_fused_rollout(c)) {
+  if (fused) {
     // all T steps in one launch: a workgroup keeps its environments on chip and streams the trajectory out
     RolloutArgs a = rollout_fused_args(c, st, eff);
-    a.T = d.T;
+    a.T = d.T; a.rows = rows;
     a.obs = tr.obs; a.action = tr.action; a.logp = tr.logp; a.reward = tr.reward; a.done = tr.done;
     a.logits = tr.logits; a.sampled = tr.sampled; a.uniforms = forced_uniforms; a.forced = forced_actions;
     a.step0 = step_offset; a.step_base = step_base;
@@ -476,7 +478,7 @@ int32_t launch_evaluate(const marl_config& c, marl_env_state st, const float* pa
   const EvalWsView e = carve_eval_ws(c, workspace, nullptr);
   const RolloutWsView w = carve_rollout_ws(c, d.N, e.rollout_ws, nullptr);
   const bool apart = n_episodes > 1 && 2 * (int64_t)n_episodes <= e.eps.slots;
-  const float* eff = stage_working_copy(c, params, w.eff_params, s, USE_FORWARD, e.eps.next, apart ? d.N : 0);
+  const float* eff = stage_working_copy(c, params, w.eff_params, s, USE_FORWARD, COPY_SPLIT, e.eps.next, apart ? d.N : 0);
   const int64_t steps = (int64_t)n_episodes * c.episode_cap;
   if (use_fused_rollout(c)) {  // the whole block in one launch, or in two (rollout_eval.h), statistics in registers
     RolloutArgs a = rollout_fused_args(c, st, eff);

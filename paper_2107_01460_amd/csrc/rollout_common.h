@@ -28,6 +28,7 @@ struct RolloutArgs {
   const float *b1, *b2, *W3, *b3;
   int T;  // steps to take
   // training rollout
+  int rows;    // samples of a tile (rollout_rows): the order of W1 and W2 goes by it
   float* obs;  // [T+1][N][A][D]
   int32_t* action;
   float* logp;

@@ -59,7 +59,7 @@ inline int32_t launch_rollout_fused_inst(const RolloutArgs& a, hipStream_t s) {
 template <int H, int V, int CA, int KIND, bool EVAL>
 inline int32_t launch_rollout_fused_rows(const RolloutArgs& a, hipStream_t s) {
   if constexpr (!EVAL)
-    if (rollout_rows(H, a.p.A, a.p.N) == 16) return launch_rollout_fused_inst<H, 16, V, CA, KIND, false>(a, s);
+    if (a.rows == 16) return launch_rollout_fused_inst<H, 16, V, CA, KIND, false>(a, s);
   return launch_rollout_fused_inst<H, H == 64 ? 64 : 32, V, CA, KIND, EVAL>(a, s);
 }
 template <int V, int KIND, bool EVAL>
