@@ -180,9 +180,10 @@ __global__ void __launch_bounds__(256, 2) fused_forward_small_kernel(FusedFwdArg
 }
 
 // Few enough rows that a call is a chain of latencies: one launch on the unstaged parameters against a staging kernel and a launch per network on split
-// operands.  The line was drawn for an earlier kernel of this path (us, one launch / staged: 75 inputs, 128 / 128 units, 3 000 samples 12 / 24, 12 288
-// samples 23 / 27; 147 inputs, 256 / 256 units, 3 000 samples 39 / 44, 5 000 samples 50 / 46); the present one takes half to two thirds of its times.  It stays
-// where it was because the one launch runs on the fp32 instruction, so that an output's last bits differ on the two sides.
+// operands.  us, one launch / staged, 2048 samples, 4096, 8192, 16 384: 75 inputs, 64 / 64 units 5.1 / 17.6, 6.0 / 17.8, 8.2 / 17.7, 13.6 / 19.3; 128 / 128 units
+// 7.0 / 19.6, 9.0 / 19.7, 15.9 / 20.2, 29.0 / 21.5; 147 inputs, 256 / 256 units 16.7 / 31.3, 23.7 / 31.3, 45.1 / 32.7, 85.4 / 56.7.  So the two cross at 6000 samples
+// (256 units), 11 000 (128) and beyond 16 384 (64), and calls between the line and there take the slower route: the line is an earlier kernel's,
+// which crossed at 4000.  The one launch runs on the fp32 instruction, so that wherever the line lies an output's last bits differ on its two sides.
 constexpr int64_t kForwardSmall = 2048;
 
 template <int HA, int HB, int NOUT_A, int NOUT_B, class FinishA, class FinishB>
