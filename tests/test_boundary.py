@@ -169,3 +169,26 @@ def test_rollout_static_takes_what_only_split_weights_push_over_its_limit(ha, hc
         good = 0x10000
         st, traj = M.binding.EnvStateC(*([good] * 8)), M.binding.TrajC(*([good] * 9 + [None, None]))
         assert M.lib().marl_rollout_static(C.byref(M.make_config(cfg)), st, good, traj, 0, None, None, None) == code, envs
+
+
+def test_current_stream_without_the_private_name(M, monkeypatch):
+    """A torch that lacks the short way to the current stream's handle takes the long one."""
+    class Current:
+        cuda_stream = 0x1234
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Current)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(M.binding, "_raw_stream", None)
+    assert M.binding._stream(None) == 0x1234
+    monkeypatch.setattr(M.binding, "_raw_stream", lambda device: 0x5678 + device)
+    assert M.binding._stream(None) == 0x5678
+    assert M.binding._stream(Current) == 0x1234
+
+
+@pytest.mark.gpu
+def test_current_stream_both_ways(M, monkeypatch):
+    for s in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(s):
+            short = M.binding._stream(None)
+            monkeypatch.setattr(M.binding, "_raw_stream", None)
+            assert M.binding._stream(None) == short == s.cuda_stream
+            monkeypatch.undo()
