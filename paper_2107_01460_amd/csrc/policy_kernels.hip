@@ -435,7 +435,7 @@ struct EvalWsView {
   EvalEpisodes eps;  // slots: as many as there is room for
 };
 // Episodes of an environment that there is room for: sixteen, and more while that is 32 768 of all environments together (2.2 MB, 4.3 with more than four
-// agents or food; more than twice that at 5461 environments, the most that go side by side).  A block takes half of them at most, because the
+// agents or food; four times that at 8192 environments, the most that go side by side).  A block takes half of them at most, because the
 // rows play the block's steps, however many episodes these are: enough where episodes last half as long as they may.
 inline int eval_slots(int N) { return std::max(16, 32768 / N); }
 
@@ -456,7 +456,7 @@ EvalWsView carve_eval_ws(const marl_config& c, void* ws, int64_t* total) {
   v.action = (int32_t*)take(d.NA * 4);
   v.done = (uint8_t*)take(d.N);
   v.eps = EvalEpisodes{};
-  v.eps.slots = use_fused_rollout(c) && rollout_eval_apart(d.Ha, d.A, d.F, d.V, d.N) ? eval_slots(d.N) : 0;
+  v.eps.slots = use_fused_rollout(c) && rollout_eval_places(d.Ha, d.A, d.F, d.V) / d.N >= 2 ? eval_slots(d.N) : 0;
   v.eps.len = (int32_t*)take((int64_t)v.eps.slots * d.N * 4);
   v.eps.record = (uint32_t*)take((int64_t)v.eps.slots * d.N * eval_record_words(std::max(d.A, d.F)) * 4);
   v.eps.next = (int32_t*)take(v.eps.slots > 0 ? (int64_t)d.N * 4 : 0);
@@ -477,18 +477,19 @@ int32_t launch_evaluate(const marl_config& c, marl_env_state st, const float* pa
   const Dims d = dims_of(c);
   const EvalWsView e = carve_eval_ws(c, workspace, nullptr);
   const RolloutWsView w = carve_rollout_ws(c, d.N, e.rollout_ws, nullptr);
-  const bool apart = n_episodes > 1 && 2 * (int64_t)n_episodes <= e.eps.slots;
-  const float* eff = stage_working_copy(c, params, w.eff_params, s, USE_FORWARD, COPY_SPLIT, e.eps.next, apart ? d.N : 0);
+  const int copies = 2 * (int64_t)n_episodes <= e.eps.slots ? rollout_eval_copies(d.Ha, d.A, d.F, d.V, d.N, n_episodes) : 0;
+  const float* eff = stage_working_copy(c, params, w.eff_params, s, USE_FORWARD, COPY_SPLIT, e.eps.next, copies > 0 ? d.N : 0);
   const int64_t steps = (int64_t)n_episodes * c.episode_cap;
   if (use_fused_rollout(c)) {  // the whole block in one launch, or in two (rollout_eval.h), statistics in registers
     RolloutArgs a = rollout_fused_args(c, st, eff);
     a.T = (int)steps;
     a.ev = out;
     a.n_episodes = n_episodes;
-    if (apart) {
+    if (copies > 0) {
       a.eps = e.eps;
-      a.eps.copies = rollout_eval_copies(d.Ha, d.A, d.F, d.V, d.N, n_episodes);
-      a.eps.steps = (int)((steps + a.eps.copies - 1) / a.eps.copies);
+      a.eps.copies = copies;
+      a.eps.idle = std::max(0, (copies - n_episodes) / 4);
+      a.eps.steps = (int)((steps + copies - a.eps.idle - 1) / (copies - a.eps.idle));
       a.eps.every = (c.episode_cap + 2) / 3;
       const int32_t rc = launch_rollout_fused(c, true, a, s);
       if (rc != MARL_OK) return rc;

@@ -14,11 +14,11 @@ constexpr int kEpisodeRewards = 8;
 constexpr int eval_record_words(int capacity) { return capacity <= 4 ? 16 : 32; }  // two sets of entities
 struct EvalEpisodes {
   int slots, copies;  // copies: rows of an environment, which take its episodes in order; 0 in the call that plays what is left
-  int steps;          // a row that has taken so many begins no other episode: together they reach the end of the block
+  int idle, steps;    // the first `idle` rows that are done before `steps` steps take no other episode; a row that has taken so many neither
   int every;          // a third of the cap, rounded up
   int32_t* len;       // [slots][N]
   uint32_t* record;   // [slots][N][eval_record_words]
-  int32_t* next;      // [N] episodes taken beyond each row's first, zero before the launch
+  int32_t* next;      // [N] rows that were done before `steps` steps so far, zero before the launch
 };
 
 struct RolloutArgs {

@@ -9,9 +9,10 @@
 // the chip has room, the block's episodes are played beside one another in a first launch (EvalEpisodes): the rows of an environment take them in order,
 // the counted ones and those behind them, until they have taken as many steps as the block has.  A second launch adds the counted ones up in the order of
 // time, finds the episode that the block's last step falls into and plays that one's part, from the third of it that was put down: nothing where every
-// episode lasts as long as it may.  R rows take n episodes' steps in a chain of n / R + 1 caps at most, and a third behind it.
+// episode lasts as long as it may.  R rows take n episodes' steps in a chain of n / R + 1 caps at most, and a third behind it.  Of 2 n rows n / 4 may end early
+// without another episode that may take a cap from there on, so that a few early ends cost nothing.
 // Four episodes of 50 steps as above: 296 us in place of 1200.  Where episodes end early, in one chain / side by side: 128 environments, five robots, 60
-// steps at most, 44 .. 47 on average, 128 units, two episodes 1340 / 1140, four 2670 / 1120, eight 5330 / 1110.  (Rows for the counted episodes alone, with
+// steps at most, 44 .. 47 on average, 128 units, two episodes 1340 / 1130, four 2670 / 1150, eight 5330 / 1090.  (Rows for the counted episodes alone, with
 // the rest of the block in the second launch: 1850, 2430 and 3940.)
 #pragma once
 #include "rollout_common.h"
@@ -49,6 +50,7 @@ __global__ void __launch_bounds__(256, OCC) rollout_eval_kernel(RolloutArgs a) {
   constexpr int REC = eval_record_words(CA);
   int left = 0;                    // steps this lane's environment still takes; apart: is it playing
   int slot = env.copy, events = 0; // apart: the episode it plays and its steps with a reward
+  int put_down = slot < a.n_episodes ? 0 : eps.every;  // apart: the step after which the entities are put down (0: of a counted episode, not at all)
   uint32_t episode0 = 0;
 
   GroupCopy<H * NOUT, 256> w3;
@@ -215,33 +217,36 @@ __global__ void __launch_bounds__(256, OCC) rollout_eval_kernel(RolloutArgs a) {
           if (b < env.A) team += rb;
         }
         if (apart) {
-          const int64_t i = (int64_t)slot * env.p.N + env.n;
-          uint32_t* const record = eps.record + REC * i;
-          const bool counted = slot < a.n_episodes;
+          const auto at = [&]() { return (int64_t)slot * env.p.N + env.n; };
           len_sum += 1;
-          if (KIND == 0 && counted && team != 0.f) {  // at most one for each food of an episode
-            if (env.ai == 0 && events < kEpisodeRewards) record[events] = __float_as_uint(team);
+          if (KIND == 0 && team != 0.f) {  // at most one for each food of an episode
+            if (slot < a.n_episodes && env.ai == 0 && events < kEpisodeRewards) eps.record[REC * at() + events] = __float_as_uint(team);
             events += 1;
           }
           if (KIND != 0) ret_sum += team;
           if (dn) {
+            const bool counted = slot < a.n_episodes;
             if (env.ai == 0) {
-              if (KIND != 0 && counted) record[0] = __float_as_uint(ret_sum);
-              eps.len[i] = len_sum | (!counted ? 0 : KIND != 0 ? 1 : events) << 24;
+              if (KIND != 0 && counted) eps.record[REC * at()] = __float_as_uint(ret_sum);
+              eps.len[at()] = len_sum | (!counted ? 0 : KIND != 0 ? 1 : events) << 24;
             }
             ret_sum = 0.f;
             len_sum = events = 0;
             slot = eps.slots;
             if (t + 1 < eps.steps) {
               int taken = 0;
-              if (env.ai == 0) taken = eps.copies + atomicAdd(eps.next + env.n, 1);
+              if (env.ai == 0) {
+                const int k = atomicAdd(eps.next + env.n, 1) - eps.idle;
+                taken = k < 0 ? eps.slots : eps.copies + k;
+              }
               slot = __shfl(taken, env.le * env.A);
             }
+            put_down = slot < a.n_episodes ? 0 : eps.every;
             if (slot < eps.slots) env.restart(episode0 + slot);
             else left = 0;
-          } else if (!counted && env.ai == 0) {
-            if (len_sum == eps.every) env.save(record);
-            if (len_sum == 2 * eps.every) env.save(record + 2 * CA);
+          } else if (len_sum == put_down) {
+            if (env.ai == 0) env.save(eps.record + REC * at() + (put_down == eps.every ? 0 : 2 * CA));
+            put_down += eps.every;
           }
         } else {
           left -= 1;

@@ -13,16 +13,16 @@ inline bool rollout_fused_supported(int H, int A) { return (H == 64 || H == 128)
 // Workgroups of an evaluation block per CU, and as many as are resident at once.
 constexpr int rollout_eval_occupancy(int capacity, int V) { return capacity <= 4 && V <= 5 ? 2 : 1; }
 inline int rollout_eval_places(int H, int A, int F, int V) { return 256 * rollout_eval_occupancy(std::max(A, F), V) * ((H == 64 ? 64 : 32) / A); }
-// Do a block's episodes go side by side?  From three rows of an environment on: with two the chain of two episodes is longer than the block where they end
-// early (n / 2 + 1 1/3 caps), and every compute unit has two workgroups, whose steps take longer: 6000 environments, two agents, 64 units, two episodes of
-// 15 of 25 steps 309 us against 218 in one chain.
-inline bool rollout_eval_apart(int H, int A, int F, int V, int N) { return rollout_eval_places(H, A, F, V) >= 3 * (int64_t)N; }
 // Rows of an environment in a block of n episodes: all resident at once (beyond that they would only follow one another), one for each counted episode
 // and, where those leave compute units without a workgroup, up to twice as many.  (Two workgroups share a unit's time: 512 environments of three agents,
 // 128 units, episodes of 60 of 60 steps, two of them in 205 workgroups 350 us, eight in 410 393 us.)
+// 0: in one chain.  Where no more than two rows have a place they go side by side only if every compute unit has one workgroup of theirs: else their
+// chain (n / 2 + 1 1/3 caps) is hardly shorter than the block's where episodes end early, at longer steps (6000 environments, two agents, 64
+// units, two episodes of 15 of 25 steps 309 us against 218 in one chain; 424 environments of eight agents, 128 units, a workgroup a unit, four
+// of 54 of 54 steps 840 against 1590).
 inline int rollout_eval_copies(int H, int A, int F, int V, int N, int n) {
   const int most = rollout_eval_places(H, A, F, V) / N, alone = 256 * ((H == 64 ? 64 : 32) / A) / N;
-  return std::min(most, std::max(n, std::min(2 * n, alone)));
+  return n >= 2 && (most >= 3 || alone >= 2) ? std::min(most, std::max(n, std::min(2 * n, alone))) : 0;
 }
 
 // Samples of a training rollout's tile: 16 while the chip holds all of those workgroups at once (one per CU at 128 units, two
