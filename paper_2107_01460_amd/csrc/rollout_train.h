@@ -8,10 +8,10 @@
 // the next observation -- only the trajectory (observations, actions, log-probabilities, rewards, dones) is streamed out.
 // The critic's values do not steer the rollout and are computed in one pass over the stored observations afterwards.
 //
-// The products run on the fp32 instruction for every number of environments.  Short rollouts of few environments, chains of
-// latencies, are a fifth faster on split bf16 operands as in rollout_eval.h (128 steps of 3072 samples at 128 units 0.83
-// against 1.02 ms), but a sampled action is a discrete choice: with one arithmetic below some number of environments and
-// another one above, an environment's run depends on how many others share the launch.
+// The products run on the fp32 instruction for every number of environments: a sampled action is a discrete choice, and with one arithmetic
+// below some number of environments and another one above, an environment's run would depend on how many others share the launch.  (On split bf16
+// operands as in rollout_eval.h, 128 steps of 3072 samples at 128 units took 0.83 ms where tiles of 32 samples took 1.02; tiles of 16 on the
+// fp32 instruction, the same bits as 32, take 0.77.)
 #pragma once
 #include "rollout_common.h"
 
