@@ -1,7 +1,8 @@
 // The GRU cell over a whole sequence in one launch each way: h' = (1 - z) n + z h for t = 0 .. T-1 and its gradient for
-// t = T-1 .. 0.  Sequences are independent of one another, so a workgroup keeps SM * 16 of them (in an update:
-// of their runs between the beginnings of episodes, SeqRuns) from the first step to the last: the hidden state (forward) or its gradient (backward) never leaves the registers, the operand of the next
-// step's product is handed over through LDS, and nothing but the per-step records goes through memory.
+// t = T-1 .. 0.  Sequences are independent of one another, so a workgroup keeps SM * 16 of them (in an update, where
+// gru_by_runs says so, of their runs between the beginnings of episodes, SeqRuns) from the first step to the last: the hidden state (forward) or its
+// gradient (backward) never leaves the registers, the operand of the next step's product is handed over through LDS, and nothing but the
+// per-step records goes through memory.
 //
 // The product with the hidden-to-hidden weights runs transposed, weights x state, on v_mfma_f32_16x16x32_bf16 with split
 // operands (split_bf16.h): its result gives a lane four consecutive units of one sequence, so that every load and store of
@@ -52,16 +53,23 @@ __device__ __forceinline__ float sigmoid_f32(float x) { return __builtin_amdgcn_
 struct SeqRuns {
   const int2* env;
   const int* count;
-  int turn;  // 1: the first round is dealt out from the last workgroup on
+  int* next;  // streamed weights: groups taken beyond each workgroup's first, zero before the launch
+  int turn;   // 1: the first round is dealt out from the last workgroup on
 };
-// The first sequence of a workgroup's k-th group of MT: every round of gridDim.x groups is dealt out the other way round, so that who has the longest of one
-// round has the shortest of the next.  A workgroup without a group in a round has none in later ones.  The two networks, which run beside one another,
-// begin at opposite ends (turn): where the groups are few, most workgroups leave at once and the working ones of both would come to lie on the same compute
-// units (192 sequences x 128 steps, 64 units: an update of 1.17 of the time).  (Groups taken from a counter in memory came at 30 ns each, one after the
-// other: runs of five steps of 3072 sequences, 32 units, 131 and 170 us forward and backward, dealt out 35 and 40.)
-template <int MT>
-__device__ __forceinline__ int group_first(const SeqRuns& runs, int k) {
-  return MT * (int)(k * gridDim.x + ((k + runs.turn) & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x));
+// The first sequence of a workgroup's k-th group of MT (whole workgroup, uniform).  With the weights in registers (DEALT) every round of gridDim.x groups is
+// dealt out the other way round, so that who has the longest of one round has the shortest of the next, and a workgroup without a group in a round has none in
+// later ones.  With streamed weights, whose steps are longer, a workgroup that is done takes the next one from a counter, so that who began with a long
+// group takes fewer: 1536 sequences of 128 steps in runs of ten, 256 units, dealt out an update of 8.8 ms, from the counter 8.3–8.5.  (For resident weights the counter, 30 ns
+// for each group, one after the other, is what bounds: runs of five steps of 3072 sequences, 32 units, 131 and 170 us forward and backward, dealt out 35 and 40.)
+// The two networks, which run beside one another, begin at opposite ends (turn): where the groups are few, most workgroups leave at once and the working ones of
+// both would come to lie on the same compute units (192 sequences x 128 steps, 64 units: an update of 1.17 of the time).
+template <int MT, bool DEALT>
+__device__ __forceinline__ int group_first(const SeqRuns& runs, int k, int* slot) {
+  if (DEALT || k == 0) return MT * (int)(k * gridDim.x + ((k + runs.turn) & 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x));
+  loop_head_barrier();  // every wavefront has read the last number
+  if (threadIdx.x == 0) *slot = (int)gridDim.x + atomicAdd(runs.next, 1);
+  __syncthreads();
+  return MT * __builtin_amdgcn_readfirstlane(*slot);
 }
 // Sequence k's row of a step's S1 and steps; past the end: 0 steps of the first sequence's row.
 __device__ __forceinline__ void run_of(const SeqRuns& runs, int per, int k, int total, int64_t& row, int& len) {
@@ -113,7 +121,8 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
   __shared__ __attribute__((aligned(16))) float bias[4][H];  // r and z: both biases; n: input, hidden
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
   const int total = SEG ? *a.runs.count * a.per : 0;
-  if (SEG && group_first<MT>(a.runs, 0) >= total) return;
+  __shared__ int group;  // SEG with streamed weights
+  if (SEG && group_first<MT, RES>(a.runs, 0, &group) >= total) return;
   for (int j = tid; j < H; j += THREADS) {
     bias[0][j] = a.bi[j] + a.bh[j];
     bias[1][j] = a.bi[H + j] + a.bh[H + j];
@@ -150,7 +159,7 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_fwd_kerne
     int64_t env[SM];  // without SEG
     int len[SM], steps = a.T;  // a sequence past its last step stays at that row and stores nothing
     if (SEG) {
-      const int first = group_first<MT>(a.runs, k);
+      const int first = group_first<MT, RES>(a.runs, k, &group);
       if (first >= total) return;  // uniform
 #pragma unroll
       for (int m = 0; m < SM; ++m) run_of(a.runs, a.per, first + 16 * m + lo, total, row[m], len[m]);
@@ -301,7 +310,8 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
   __shared__ __attribute__((aligned(16))) float W3s[H * NOUT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, q = lane >> 4;
   const int total = SEG ? *a.runs.count * a.per : 0;
-  if (SEG && group_first<MT>(a.runs, 0) >= total) return;
+  __shared__ int group;  // SEG with streamed weights
+  if (SEG && group_first<MT, RES>(a.runs, 0, &group) >= total) return;
   GroupCopy<H * NOUT, THREADS> w3;
   w3.request(tid, a.W3);
   w3.store(tid, [&](int e, float v) { W3s[e] = v; });
@@ -329,7 +339,7 @@ __global__ void __launch_bounds__(RES ? 128 * KS : 64 * KS, 2) gru_seq_bwd_kerne
     int len[SM], steps = a.T;
     int from_zero[SM];  // SEG: does the run's first step start from zero, else the current one (a byte that is looked at a step after its request)
     if (SEG) {
-      const int first = group_first<MT>(a.runs, k);
+      const int first = group_first<MT, RES>(a.runs, k, &group);
       if (first >= total) return;  // uniform
 #pragma unroll
       for (int m = 0; m < SM; ++m) {
@@ -711,13 +721,18 @@ inline dim3 gru_run_grid(int64_t S, int waves) { return dim3((unsigned)std::min<
 // sequences 0.43 .. 0.61 / 0.45 .. 0.63 / 0.94 .. 1.00; of 512 sequences 0.69 .. 0.82 / 0.60 .. 0.68 / 0.94 .. 0.99; of 1024 0.84 .. 1.06 / 0.71 .. 0.83 /
 // 0.95 .. 1.01; of 1536 0.88 .. 1.01 / 0.82 .. 0.94 / 0.94 .. 1.02; of 2048 0.95 .. 1.06 / 0.87 .. 1.02 / 0.98 .. 1.00, so that from there on the longest chain
 // has to come out at two thirds or less (256 units, 2048 sequences beside 8192 of 128 units, episodes of 70 steps: an iteration of 387 ms in place of 397); of
-// 3072 at 96 units and more 1.02 .. 1.06 / 0.97 .. 1.03 / 0.99 .. 1.01; of 8192, above 128 units, 1.07 .. 1.11.  32 steps of 64 .. 1024 sequences 0.96 .. 1.11,
-// 16 steps up to 1.08.  At 128 units whole sequences in tiles of 32 spill registers: in runs 0.95 .. 1.00 of their time above 4096 sequences, of 16 steps as of 128.
+// 3072 at 96 units and more 1.02 .. 1.06 / 0.97 .. 1.03 / 0.99 .. 1.01.  Shorter sequences have less to gain and as much to plan: 32 steps, episodes of
+// three steps / of ten / none ending, 192 sequences 0.58 .. 0.87 / 0.94 .. 1.01 / 0.98 .. 1.01, 768 0.79 .. 0.94 / 0.91 .. 1.08 / 0.96 .. 1.02, with resident
+// weights 1024 to 1536 of episodes of ten steps up to 1.13; 16 steps 0.95 .. 1.05.  Streamed weights, whose steps are longer: 16 steps of 192 sequences 0.88 .. 0.95 in
+// episodes of three steps, 32 steps of 1024 0.74 .. 0.84 / 0.95 .. 1.11, 4096 in episodes of five steps 0.90, 8192 1.07 .. 1.11.  At 128
+// units whole sequences in tiles of 32 spill registers: in runs 0.95 .. 1.00 of their time above 4096 sequences, of 16 steps as of 128.
 inline bool gru_by_runs(int T, int cap, int64_t S1, int H) {
   if (!gru_seq_supported(H)) return false;
   if (H == 128 && !gru_seq_tiles16(S1)) return true;
+  if (T < (H > 128 ? 16 : 24)) return false;
+  if (S1 <= (H > 128 ? 1536 : 24 * std::min(T, 64))) return true;
   const int64_t chain = std::max<int64_t>(std::min(T, cap), T * S1 / (16 * gru_run_places(H <= 128 ? H / 16 : H / 32)));
-  return T > 32 && (S1 <= 1536 || (S1 <= 3072 && 2 * T >= 3 * chain));
+  return S1 <= 3072 ? 2 * T >= 3 * chain : H > 128 && gru_seq_tiles16(S1);
 }
 
 template <int KS, bool SEG>
@@ -739,7 +754,8 @@ inline void launch_gru_bwd_ks(const GruBwdArgs& a, hipStream_t s) {
   constexpr bool RES = KS <= 4;
   constexpr int WAVES = RES ? 2 * KS : KS;
   if constexpr (SEG) hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, true, NOUT>), gru_run_grid(a.T * a.S1, WAVES), dim3(64 * WAVES), 0, s, a);
-  else if (KS == 4 || gru_seq_tiles16(a.S1)) hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, false, NOUT>), dim3((unsigned)((a.S1 + 15) / 16)), dim3(64 * WAVES), 0, s, a);
+  else if (KS == 4 || gru_seq_tiles16(a.S1))  // (128 units, more sequences: in runs)
+    hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 1, RES, false, NOUT>), dim3((unsigned)((a.S1 + 15) / 16)), dim3(64 * WAVES), 0, s, a);
   else if constexpr (KS != 4) hipLaunchKernelGGL((gru_seq_bwd_kernel<KS, 2, RES, false, NOUT>), dim3((unsigned)((a.S1 + 31) / 32)), dim3(64 * WAVES), 0, s, a);
 }
 

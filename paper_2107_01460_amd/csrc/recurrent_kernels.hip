@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(256) gru_backward_kernel(const float* __restri
 // the same launches serve them all, but no more than these, so that the room for plans grows neither with the epochs nor with their minibatches.
 constexpr int kPlanned = 32;
 constexpr int kRunBins = 1024;  // lengths from here on count as one
-constexpr int kRunHead = 4;     // ints before a minibatch's bins: number of runs
+constexpr int kRunHead = 8;     // ints before a minibatch's bins: number of runs, groups taken by each of its four kernels
 struct SeqPlanArgs {
   const int32_t* envs;  // [N] the epoch's order, nullable: the identity
   const uint8_t* done;  // [T][N]
@@ -627,6 +627,7 @@ int32_t train_net_recurrent(const RowSrc& X, int T, int64_t J, int per, int Din,
   bw.W = reinterpret_cast<const bf16_t*>(wh_bwd); bw.W3 = eff + o.W3; bw.dl = w.dl; bw.rec = w.R; bw.hs = w.Hs; bw.reset = reset + J;
   bw.per = per; bw.S1 = S1; bw.T = T;
   bw.runs = runs;
+  bw.runs.next += 1;
   if (by_runs) gru_backward<true, NOUT>(bw, H, eff, o, w.dHp, s);
   else gru_backward<false, NOUT>(bw, H, eff, o, w.dHp, s);
   const float* const dgh = w.R;      // [S][4H], columns n, r, z
@@ -671,7 +672,7 @@ int32_t launch_ppo_update_recurrent(const marl_config& c, marl_traj tr, marl_rec
       const int q = mb % kPlanned;
       int32_t *const rows = w.plan.rows + q * TJ, *const hrows = w.plan.hrows + q * TJ, *const head = w.plan.head + q * run_head_ints(d.T);
       const uint8_t* const reset = w.plan.reset + q * TJ;
-      const SeqRuns runs_a{w.plan.runs + q * TJ, head, 0}, runs_c{w.plan.runs + q * TJ, head, 1};
+      const SeqRuns runs_a{w.plan.runs + q * TJ, head, head + 1, 0}, runs_c{w.plan.runs + q * TJ, head, head + 3, 1};
       const float* eff = stage_params(d, params, w.eff, s);
       const int planned = q == 0 ? std::min(c.n_minibatches - mb, kPlanned) : 0;  // clears the heads of their plans too
       hipLaunchKernelGGL(zero_step_kernel, dim3(blocks_for(d.P)), dim3(256), 0, s, w.grad, d.P, w.sc, 1, (double*)(planned ? w.plan.head : nullptr),

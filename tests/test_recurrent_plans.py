@@ -54,11 +54,11 @@ def test_more_minibatches_than_are_planned_at_once(orc, order):
     against_the_oracle(orc, cfg, lambda rng, shape: rng.random(shape) < 0.3, order)
 
 
-# Run by run: from 33 steps on, pieces of 64 steps and four of them at a time, episodes that end at every step, at a few and at none, at the last step
-# of a piece and at its first; every width's kernels and, in the last case, two networks of which one goes in whole sequences.
+# Run by run: from 24 steps on (16 above 128 units, whose groups come from a counter), pieces of 64 steps and four of them at a time, episodes
+# that end at every step, at a few and at none, at the last step of a piece and at its first; every width's kernels and, in the last case, two networks of which one goes in whole sequences.
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,n_envs,ha,hc,central,ends", [
-    (33, 10, 32, 64, 0, 0.3), (64, 6, 96, 128, 0, 0.05), (65, 6, 160, 192, 1, 1.0), (129, 5, 224, 256, 0, 0.0), (300, 3, 64, 32, 0, "pieces"),
+    (24, 10, 32, 64, 0, 0.3), (16, 9, 160, 256, 1, 0.4), (33, 10, 32, 64, 0, 0.3), (64, 6, 96, 128, 0, 0.05), (65, 6, 160, 192, 1, 1.0), (129, 5, 224, 256, 0, 0.0), (300, 3, 64, 32, 0, "pieces"),
     (48, 9, 128, 352, 1, 0.1)])
 def test_runs(orc, T, n_envs, ha, hc, central, ends):
     cfg = dict(W.CONFIGS[0], n_envs=n_envs, rollout_len=T, actor_hidden=ha, critic_hidden=hc, episode_cap=20, n_minibatches=1, n_epochs=2,
